@@ -56,14 +56,12 @@ typedef struct {
     double sum_delta;    /* sum of the delta of every shrink: upper bound on ||A^T A - B^T B||_2 */
     double frob2;        /* ||A||_F^2 of the rows seen, fp32 products accumulated in fp32/fp64 */
     double last_delta;   /* delta of the most recent shrink */
-    int last_sweeps;     /* Jacobi sweeps used by the most recent eigensolve (100 + the sweeps launched if they did
-                            not reach the tolerance; the next solves then launch the full number) */
+    int last_sweeps;     /* sweeps of an iterative eigensolver; 0: the eigensolve is direct */
     int fill;            /* buffer rows in use, 0..2*ell-1 */
-    int64_t n_unconverged; /* eigensolves so far (shrinks and bases) that ended above their tolerance: sticky. Such a
-                            shrink is still a valid FD step (the rows are rotated by an exactly orthogonal matrix and
-                            damped; the Gram block the next cycle takes as known includes what was left off the
-                            diagonal), but its delta is not exactly sigma_ell^2 */
-    double last_offdiag; /* largest |off-diagonal| / trace the most recent eigensolve left */
+    int64_t n_unconverged; /* eigensolves so far (shrinks and bases) that could not be completed; 0 as long as the context
+                            works at all (the call after such a solve returns SAGE_ERR_HIP) */
+    double last_offdiag; /* largest |off-diagonal| / trace an iterative eigensolver left; 0: the eigensolve is direct, its
+                            residual is a few 2*ell * 2^-52 of the trace */
 } sage_stats_t;
 
 /* ---- the five calls of the path --------------------------------------------------------------------------- */
@@ -90,7 +88,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
  * row; whenever the buffer becomes full the shrink step runs: with sigma_j, v_j the singular values / right
  * singular vectors of the buffer, delta = sigma_ell^2 and row j becomes sqrt(max(sigma_j^2 - delta, 0)) v_j^T
  * (Method, FD paragraph). It is computed as: Gram C = B B^T (fp32 matrix cores, split over D, partial sums added
- * in fp64) -> Jacobi eigensolve C = Y Lambda Y^T (fp64) -> B[0:ell] <- diag(w) Y^T B with
+ * in fp64) -> eigensolve C = Y Lambda Y^T (fp64) -> B[0:ell] <- diag(w) Y^T B with
  * w_j = sqrt(max(lambda_j - delta, 0) / lambda_j) (fp32 matrix cores), rows ell.. zeroed.
  * G_batch: DEVICE, rows x D of the context's dtype. rows >= 0 (0 is a no-op). Asynchronous on the context's
  * stream. Invalidates a basis made earlier. The host never reads device data in this call.
@@ -299,7 +297,7 @@ int sage_topm_static(const float* alpha, int64_t N, int64_t m, int64_t* out_idx,
 
 /*
  * Stage probes for tests: run the Gram of the current buffer (C_out: DEVICE, n_pad*n_pad doubles, row-major,
- * n_pad returned in *n_pad) and, if eig != 0, the Jacobi eigensolve of it (Y_out: DEVICE n_pad*n_pad doubles
+ * n_pad returned in *n_pad) and, if eig != 0, the eigensolve of it (Y_out: DEVICE n_pad*n_pad doubles
  * with eigenvectors in columns, lam_out: DEVICE n_pad doubles, unsorted). Any output pointer may be NULL.
  * The sketch is not modified. Waits.
  */
@@ -314,10 +312,10 @@ int sage_probe_gram_eig(sage_ctx* ctx, double* C_out, int eig, double* Y_out, do
 int sage_probe_gram_split(sage_ctx* ctx, double* C_out, int* n_pad);
 
 /*
- * Stage probe: run the context's Jacobi eigensolve on a symmetric matrix given by the caller. C_in: DEVICE,
+ * Stage probe: run the context's eigensolve on a symmetric matrix given by the caller. C_in: DEVICE,
  * n_pad*n_pad doubles (n_pad as reported by sage_probe_gram_eig), left untouched. Y_out, lam_out as above.
- * sweep_stat_out: DEVICE, 18 doubles: [0] trace, [1+s] largest |off-diagonal| / trace met in sweep s (0 for
- * sweeps that were skipped), [17] the number of sweeps launched. Outputs may be NULL. The sketch is not modified. Waits.
+ * sweep_stat_out: DEVICE, 18 doubles: [0] trace, the others 0 (records of an iterative solver's sweeps; this one is
+ * direct). Outputs may be NULL. The sketch is not modified. Waits.
  */
 int sage_probe_eig_matrix(sage_ctx* ctx, const double* C_in, double* Y_out, double* lam_out, double* sweep_stat_out);
 
@@ -340,14 +338,8 @@ int sage_profile_enable(sage_ctx* ctx, int on);
 int sage_profile_read(sage_ctx* ctx, int which, double* ms, int64_t* launches);
 
 /*
- * How many Jacobi sweeps a shrink's eigensolve may use (Method, FD paragraph: the SVD of the buffer). Sweeps are
- * enqueued ahead of time, and a sweep that finds the matrix already diagonal to tolerance returns at once, but its
- * launches still cost time (about 50 us per sweep at ell = 256). SAGE_SWEEPS_ADAPTIVE (default): as many sweeps as
- * the most demanding of the last eight solves whose count has come back needed, plus two; a solve that still ends above the tolerance is
- * counted in sage_stats_t.n_unconverged (and the next 64 solves get every sweep); such a shrink remains a valid step,
- * see there. SAGE_SWEEPS_ALL: always the full 14 sweeps, for streams whose spectrum may change abruptly from one
- * cycle to the next: no solve ends early for want of sweeps, at about 4% of the update rate at ell = 256.
- * sage_fd_basis always has every sweep. May be changed between calls.
+ * How many sweeps an iterative eigensolver may use in a shrink (Method, FD paragraph: the SVD of the buffer). The
+ * eigensolve is direct (tridiagonal reduction, divide and conquer): both policies are accepted and mean the same.
  */
 typedef enum { SAGE_SWEEPS_ADAPTIVE = 0, SAGE_SWEEPS_ALL = 1 } sage_sweep_policy;
 int sage_set_sweep_policy(sage_ctx* ctx, int policy);

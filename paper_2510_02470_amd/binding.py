@@ -291,7 +291,7 @@ class Sage:
         return Y, lam, stat
 
     def set_sweep_policy(self, all_sweeps):
-        """True: every shrink's eigensolve gets all its sweeps; False (default): as many as recent solves needed, plus two."""
+        """Accepted for callers of earlier versions; the eigensolve is direct and has no sweeps."""
         _check(self.L.sage_set_sweep_policy(self.h, 1 if all_sweeps else 0), "sage_set_sweep_policy")
 
     def set_debug_checks(self, on=True):

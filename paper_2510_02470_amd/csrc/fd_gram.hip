@@ -696,8 +696,8 @@ __global__ __launch_bounds__(256, 2) void gram_new8_split_kernel(const float* __
 }
 
 // C (NP x NP, fp64, both triangles) = sum over groups of the partial tiles, in group order. With q = P/2:
-// known_top: tiles with ti < q are not summed, their block is `known` (the top rows are the rows the last shrink
-// wrote, whose Gram matrix it recorded: diagonal up to the tolerance of its eigensolve). Otherwise tile (ti, tj) comes from source A when its mode
+// known_top: tiles with ti < q are not summed, their block is diag(known) (the top rows are the rows the last shrink
+// wrote, whose Gram matrix it recorded). Otherwise tile (ti, tj) comes from source A when its mode
 // covers it, else from source B (mode-1 and mode-2 launches write separate partial buffers).
 struct GramSrc {
     const float* partial;
@@ -721,7 +721,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, 
     int gr = ti * 64 + r, gc = tj * 64 + c;
     double s = 0.0;
     if (known_top && ti < (P >> 1)) {
-        s = known[(int64_t)gr * (NP >> 1) + gc];
+        s = gr == gc ? known[gr] : 0.0;
     } else {
         int ia = gram_src_index(a, P, t, ti, tj);
         const GramSrc& g = ia >= 0 ? a : b;
@@ -857,7 +857,7 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
     return hipGetLastError();
 }
 
-// a, b: the launches whose partial tiles make up C (b may be null); known: LP x LP doubles, read when known_top
+// a, b: the launches whose partial tiles make up C (b may be null); known: LP doubles, read when known_top
 hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const float* partial_b, const GramPlan* b,
                               double* C, bool known_top, const double* known, const Dims& d, hipStream_t st) {
     const int P = d.NP / 64;

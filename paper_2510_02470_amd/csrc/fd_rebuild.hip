@@ -167,34 +167,10 @@ hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const fl
 //
 // Same decomposition as rebuild_kernel: a wave owns 32 columns for the whole product, its column operand comes from
 // global memory (8 rows of its k-half per stage of 16 buffer rows; k-slot (h, s) is buffer row 16*stage + 2s + h,
-// the order coeff_offset groups the coefficients in) and is split in registers; the coefficients are split once per
-// launch by coeff_split_kernel into the order LDS holds them, [stage][part][h][m][8 k-slots], and streamed through a
+// the order coeff_offset groups the coefficients in) and is split in registers; the coefficients come split
+// from coeffs_kernel in the order LDS holds them, [stage][part][h][m][8 k-slots], and streamed through a
 // ring of three LDS buffers with direct global->LDS loads two stages ahead. The column operand is requested two
 // stages ahead as well.
-template <int MT>
-__global__ __launch_bounds__(256) void coeff_split_kernel(const float* __restrict__ Mc, int NP, u32x4* __restrict__ Mc3) {
-    constexpr int MP = MT * 32;
-    const int i = blockIdx.x * 256 + threadIdx.x;  // (stage, h, m)
-    if (i >= (NP / 16) * 2 * MP) return;
-    const int m = i % MP, h = (i / MP) & 1, stg = i / (2 * MP);
-    float v[8];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = Mc[coeff_offset(stg * 16 + 2 * s + h, m, MP)];
-    u32x4 hi, mid, lo;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        unsigned a, b, c;
-        split3_bf16(v[2 * e], v[2 * e + 1], a, b, c);
-        hi[e] = a;
-        mid[e] = b;
-        lo[e] = c;
-    }
-    u32x4* dst = Mc3 + (int64_t)stg * (3 * 2 * MP) + h * MP + m;
-    dst[0] = hi;
-    dst[2 * MP] = mid;
-    dst[4 * MP] = lo;
-}
-
 // NPT > 0: the buffer has NPT rows and the new rows in use hold bf16 values; their stages take the hi part alone and
 // three products (the other three would add exact zeros). NPT = 0: any buffer, all parts.
 template <int MT, int NPT>
@@ -379,29 +355,25 @@ bool rebuild_split_ok(int MP) { return MP == 128 || MP == 256; }
 size_t rebuild_split_bytes(const Dims& d, int MP) { return (size_t)(d.NP / 16) * 3 * 2 * MP * 16; }
 
 template <int MT, int NPT>
-static hipError_t launch_rebuild_split_t(const float* top, const float* nw, int nfill, const float* Mc, void* Mc3,
-                                         float* out, int out_NP, const Dims& d, hipStream_t st) {
+static hipError_t launch_rebuild_split_t(const float* top, const float* nw, int nfill, const void* Mc3, float* out,
+                                         int out_NP, const Dims& d, hipStream_t st) {
     constexpr int MP = MT * 32;
     constexpr size_t LDS = (size_t)3 * 3 * 2 * MP * 16;
     if (hipError_t ea = ensure_dynamic_lds((const void*)rebuild_split_kernel<MT, NPT>, (int)LDS); ea != hipSuccess)
         return ea;
-    const int n = (d.NP / 16) * 2 * MP;
-    hipLaunchKernelGGL(coeff_split_kernel<MT>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Mc, d.NP, (u32x4*)Mc3);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     dim3 grid((unsigned)((d.Dp + 127) / 128));
     hipLaunchKernelGGL((rebuild_split_kernel<MT, NPT>), grid, dim3(256), LDS, st, top, nw, nfill, (const u32x4*)Mc3, out,
                        d.NP, out_NP, d.Dp);
     return hipGetLastError();
 }
 
-hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const float* Mc, void* Mc3, float* out,
-                                int out_NP, int MP, const Dims& d, hipStream_t st, bool new_one) {
-    if (MP == 256 && new_one && d.NP == 512) return launch_rebuild_split_t<8, 512>(top, nw, nfill, Mc, Mc3, out, out_NP, d, st);
-    if (MP == 256) return launch_rebuild_split_t<8, 0>(top, nw, nfill, Mc, Mc3, out, out_NP, d, st);
-    if (MP == 128 && new_one && d.NP == 512) return launch_rebuild_split_t<4, 512>(top, nw, nfill, Mc, Mc3, out, out_NP, d, st);
-    if (MP == 128 && new_one && d.NP == 256) return launch_rebuild_split_t<4, 256>(top, nw, nfill, Mc, Mc3, out, out_NP, d, st);
-    if (MP == 128) return launch_rebuild_split_t<4, 0>(top, nw, nfill, Mc, Mc3, out, out_NP, d, st);
+hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
+                                const Dims& d, hipStream_t st, bool new_one) {
+    if (MP == 256 && new_one && d.NP == 512) return launch_rebuild_split_t<8, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 256) return launch_rebuild_split_t<8, 0>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 128 && new_one && d.NP == 512) return launch_rebuild_split_t<4, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 128 && new_one && d.NP == 256) return launch_rebuild_split_t<4, 256>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 128) return launch_rebuild_split_t<4, 0>(top, nw, nfill, Mc3, out, out_NP, d, st);
     return hipErrorInvalidValue;
 }
 

@@ -3,6 +3,9 @@
 #include <new>
 #include <stdlib.h>
 #include <string.h>
+#include <mutex>
+#include <type_traits>
+#include <unistd.h>
 
 #include "sage_internal.h"
 
@@ -47,6 +50,7 @@ struct sage_ctx {
     float* gram_partial = nullptr;
     float* gram_partial_new[2] = {nullptr, nullptr};
     EigWork ew{};
+    char* eig_mem = nullptr;  // what ew points into
     float* Mt = nullptr;
     void* Mt3 = nullptr;   // the rebuild's coefficients split into bf16 parts (SAGE_MM_SPLIT)
     int mm_mode = SAGE_MM_SPLIT;
@@ -55,25 +59,16 @@ struct sage_ctx {
     // came from a bf16 batch (row-major or factored; not sage_fd_merge's fp32 rows). one_part: the shortcut is allowed (off under SAGE_MM_SPLIT_ALL_PARTS).
     bool nw_bf16[2] = {false, false};
     bool one_part = true;
-    double* acc = nullptr;  // [0] sum_delta [1] frob2 [2] last_delta [3] sweeps [4] unconverged solves [5] last off-diagonal
+    double* acc = nullptr;  // [0] sum_delta [1] frob2 [2] last_delta [4] failed solves
 
     bool poisoned = false;   // a HIP call failed while work of a call was partly enqueued: the state is not trustworthy
     int fail_in = 0;         // test hook (sage_debug_fail_launch): the fail_in-th launch from now fails without running
     bool debug_checks = false;      // sage_set_debug_checks: scan caller batches for non-finite values
     unsigned* dbg_count = nullptr;  // device counter of that scan
 
-    // Sweeps to launch for a shrink's eigensolve (a sweep that finds the matrix converged returns at once, but its 30
-    // launches still cost about 50 us): what the last read-back solve needed, plus two. The count comes back through
-    // pinned host memory without the host ever waiting for it.
-    int sweep_cap = MAX_SWEEPS;
-    int sweep_hold = 0;      // solves still to be launched with every sweep after one came back unconverged
-    int sweep_recent[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // sweeps the last eight reported solves needed
-    int sweep_recent_at = 0;
-    bool sweeps_all = false; // sage_set_sweep_policy(SAGE_SWEEPS_ALL): always launch MAX_SWEEPS
-    double* h_sweeps = nullptr;                    // pinned, SWEEP_RING slots
-    hipEvent_t ev_sweeps[4] = {nullptr, nullptr, nullptr, nullptr};
-    bool sweeps_pending[4] = {false, false, false, false};
-    int sweeps_next = 0;
+    int* h_failed = nullptr;  // pinned: set by the device when an eigensolve could not be completed (see ALIVE)
+    int xcd_slot = -1;        // registered use of an XCD by this context's eigensolves (-1: they need none)
+    int device = 0;
 
     int fill_top = 0, fill_new = 0;  // rows in use in top (0..ell) and in nw[cur] (0..ell)
     int cnt_top = 0, cnt_new = 0;    // of those, rows already counted in frob2
@@ -129,10 +124,11 @@ inline int hip_failed(sage_ctx* c) {
     } while (0)
 
 // first statement of every call on a context
-#define ALIVE(c)                                      \
-    do {                                              \
-        if (!(c)) return SAGE_ERR_ARG;                \
-        if ((c)->poisoned) return SAGE_ERR_STATE;     \
+#define ALIVE(c)                                                                       \
+    do {                                                                               \
+        if (!(c)) return SAGE_ERR_ARG;                                                 \
+        if ((c)->poisoned) return SAGE_ERR_STATE;                                      \
+        if ((c)->h_failed && *(volatile int*)(c)->h_failed) return hip_failed(c);      \
     } while (0)
 
 #define ALLOC(ptr, bytes)                                                  \
@@ -207,66 +203,76 @@ void note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
 }
 bool new_one(const sage_ctx* c, int i) { return c->one_part && c->nw_bf16[i]; }
 
-constexpr int SWEEP_RING = 4;
+// The reduction of a 256- or 512-row eigensolve keeps n / 16 work-groups of one XCD in step, so all of them must be
+// resident together. Contexts are spread over the XCDs; when two share one, their reductions are ordered by an event, so
+// that at most two (one launched before the second context appeared, one in the chain) are ever in flight on an XCD, and
+// two fit on its CUs side by side.
+struct XcdSlot {
+    int users = 0;
+    hipEvent_t last = nullptr;  // kept for the life of the process (at most 8 per device)
+    const void* owner = nullptr;
+};
+constexpr int MAX_DEVICES = 64;
+std::mutex g_xcd_lock;
+XcdSlot g_xcd[MAX_DEVICES][8];
 
-// Pick up the sweep counts that have arrived and set the number of sweeps to launch next.
-void poll_sweeps(sage_ctx* c) {
-    for (int i = 0; i < SWEEP_RING; ++i) {
-        if (!c->sweeps_pending[i]) continue;
-        hipError_t e = hipEventQuery(c->ev_sweeps[i]);
-        if (e == hipErrorNotReady) {
-            (void)hipGetLastError();
-            continue;
-        }
-        c->sweeps_pending[i] = false;
-        if (e != hipSuccess) continue;
-        const int used = (int)c->h_sweeps[i];
-        if (used >= SWEEPS_NOT_CONVERGED) {
-            // ran out (sage_stats counts it): every sweep is launched for the solves to come
-            c->sweep_cap = MAX_SWEEPS;
-            c->sweep_hold = 64;
-        } else {
-            c->sweep_recent[c->sweep_recent_at] = used;
-            c->sweep_recent_at = (c->sweep_recent_at + 1) & 7;
-            if (c->sweep_hold > 0) {
-                c->sweep_hold -= 1;
-            } else {
-                int most = used;
-                for (int v : c->sweep_recent) most = v > most ? v : most;
-                c->sweep_cap = most + 2 < 4 ? 4 : (most + 2 > MAX_SWEEPS ? MAX_SWEEPS : most + 2);
-            }
-        }
+int xcd_take(sage_ctx* c) {
+    if (c->d.NP < 256 || c->device < 0 || c->device >= MAX_DEVICES) return 0;
+    std::lock_guard<std::mutex> hold(g_xcd_lock);
+    const int first = (int)(getpid() & 7);  // other processes on the GPU most likely start at another one
+    int best = first;
+    for (int i = 1; i < 8; ++i) {
+        const int x = (first + i) & 7;
+        if (g_xcd[c->device][x].users < g_xcd[c->device][best].users) best = x;
     }
+    g_xcd[c->device][best].users += 1;
+    c->xcd_slot = best;
+    return best;
+}
+void xcd_release(sage_ctx* c) {
+    if (c->xcd_slot < 0) return;
+    std::lock_guard<std::mutex> hold(g_xcd_lock);
+    XcdSlot& x = g_xcd[c->device][c->xcd_slot];
+    x.users -= 1;
+    if (x.owner == c) x.owner = nullptr;  // the context's stream has been waited for
+    c->xcd_slot = -1;
 }
 
-// After a shrink's coefficient kernels: send the sweep count (acc[3]) home.
-void post_sweeps(sage_ctx* c) {
-    const int i = c->sweeps_next;
-    if (c->sweeps_pending[i] || !c->h_sweeps) return;  // slot still in flight: skip this one
-    if (hipMemcpyAsync(c->h_sweeps + i, c->acc + 3, sizeof(double), hipMemcpyDeviceToHost, c->st) != hipSuccess ||
-        hipEventRecord(c->ev_sweeps[i], c->st) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
+// Eigensolve of the Gram matrix of fill_top + fill_new rows; the `count` leading eigenvectors are formed.
+hipError_t eigensolve(sage_ctx* c, int m0, int n, int count) {
+    if (n < 1) m0 = n = 1;  // an empty buffer: one zero row
+    if (c->xcd_slot < 0) return launch_eig(c->ew, c->d.NP, m0, n, count, c->st);
+    std::unique_lock<std::mutex> hold(g_xcd_lock);
+    XcdSlot& x = g_xcd[c->device][c->xcd_slot];
+    const bool shared = x.users > 1;
+    if (!shared) hold.unlock();
+    if (shared) {
+        if (!x.last && hipEventCreateWithFlags(&x.last, hipEventDisableTiming) != hipSuccess) return hipErrorUnknown;
+        if (x.owner && x.owner != c)
+            if (hipError_t e = hipStreamWaitEvent(c->st, x.last, 0); e != hipSuccess) return e;
     }
-    c->sweeps_pending[i] = true;
-    c->sweeps_next = (i + 1) % SWEEP_RING;
+    hipError_t e = launch_tridiag(c->ew, c->d.NP, m0, n, c->st);
+    if (shared) {
+        if (e == hipSuccess) e = hipEventRecord(x.last, c->st);
+        x.owner = c;
+        hold.unlock();
+    }
+    if (e == hipSuccess) e = launch_dc(c->ew, c->d.NP, c->st);
+    if (e == hipSuccess) e = launch_tri_back(c->ew, c->d.NP, m0, n, count, c->st);
+    return e;
 }
 
-// Gram + eigensolve of the buffer as it stands. After a shrink the Gram matrix of the top rows is known (the shrink
-// recorded it: diagonal lambda_j - delta, off-diagonal what its eigensolve left), so their block is not recomputed.
-int decompose(sage_ctx* c, double tol, bool full) {
-    const bool skip = !full && c->top_shrunk && c->gp_skip.t0 > 0;
+// Gram + eigensolve (count leading eigenvectors) of the buffer as it stands. After a shrink the Gram matrix of the top rows
+// is known (diagonal lambda_j - delta, recorded by the shrink), so their block is not recomputed.
+int decompose(sage_ctx* c, int count) {
+    const bool skip = c->top_shrunk && c->gp_skip.t0 > 0;
     if (skip && c->fill_new == 0) {
-        // Only the rows the last shrink wrote are there: the Gram matrix is the block that shrink recorded, nothing to
-        // compute (its off-diagonal entries are at most the shrink's tolerance: a sweep or two at a tighter one).
+        // only the rows the last shrink wrote are there: nothing to compute
         GramPlan none = c->gp_skip;
         none.tiles = 0;
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, none, nullptr, nullptr, c->ew.C, true, c->ew.known, c->d, c->st));
-        RUN(K_EIG, launch_eig(c->ew, c->d.NP, tol, MAX_SWEEPS, c->st));
-        return SAGE_OK;
-    }
-    if (skip && c->mm_mode == SAGE_MM_SPLIT && c->gp_cross_split.tiles > 0 && c->gp_new2_split.tiles > 0 &&
-        !c->new_block_ready && !c->pre_stored) {
+    } else if (skip && c->mm_mode == SAGE_MM_SPLIT && c->gp_cross_split.tiles > 0 && c->gp_new2_split.tiles > 0 &&
+               !c->new_block_ready && !c->pre_stored) {
         // the two blocks that are not known, with the split-arithmetic kernels (the side stream is idle here: its
         // partial buffer of the current half is free)
         const bool one = new_one(c, c->cur);
@@ -280,7 +286,7 @@ int decompose(sage_ctx* c, double tol, bool full) {
         RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, gp, c->d, c->st));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st));
     }
-    RUN(K_EIG, launch_eig(c->ew, c->d.NP, tol, MAX_SWEEPS, c->st));
+    RUN(K_EIG, eigensolve(c, c->fill_top, c->fill_top + c->fill_new, count));
     return SAGE_OK;
 }
 
@@ -335,16 +341,15 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
         int rc = side_ahead(c, next);
         if (rc != SAGE_OK) return rc;
     }
-    poll_sweeps(c);
-    RUN(K_EIG, launch_eig(c->ew, c->d.NP, JACOBI_TOL_SHRINK, c->sweeps_all ? MAX_SWEEPS : c->sweep_cap, c->st));
-    RUN(K_COEFF, launch_shrink_coeffs(c->ew, c->d.NP, LP, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new,
-                                      c->Mt, c->acc, JACOBI_TOL_SHRINK, c->st));
-    if (c->mm_mode == SAGE_MM_SPLIT && c->Mt3)
-        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], ell, c->Mt, c->Mt3, c->top, LP, LP, c->d, c->st,
+    RUN(K_EIG, eigensolve(c, ell, 2 * ell, ell - 1));  // (row ell - 1 of the result is zero)
+    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3;
+    RUN(K_COEFF, launch_coeffs(c->ew, c->d.NP, LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new,
+                               LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc, c->h_failed, c->st));
+    if (split_rb)
+        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], ell, c->Mt3, c->top, LP, LP, c->d, c->st,
                                             new_one(c, c->cur)));
     else
         RUN(K_REBUILD, launch_rebuild(c->top, c->nw[c->cur], ell, c->Mt, c->top, LP, LP, c->d, c->st));
-    post_sweeps(c);
     if (use_side(c)) c->cur ^= 1;  // two new halves alternate; with a single Gram panel there is only nw[0]
     c->fill_top = ell;
     c->cnt_top = ell;
@@ -487,6 +492,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
         delete c;
         return SAGE_ERR_HIP;
     }
+    c->device = dev;
     c->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     const int P = c->d.NP / 64;
     c->gp = gram_plan(c->d, c->num_cu, 0, false, 2);
@@ -536,16 +542,31 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
         for (int i = 0; i < 2; ++i)
             if (hipEventCreateWithFlags(&c->ev_side[i], hipEventDisableTiming) != hipSuccess) return fail(SAGE_ERR_HIP);
     }
-    CALLOC(c->ew.C, (size_t)NP * NP * sizeof(double));
-    CALLOC(c->ew.Y, (size_t)NP * NP * sizeof(double));
-    CALLOC(c->ew.C2, (size_t)NP * NP * sizeof(double));
-    CALLOC(c->ew.Y2, (size_t)NP * NP * sizeof(double));
-    CALLOC(c->ew.Q, (size_t)(NP / 64) * 4096 * sizeof(double));
-    CALLOC(c->ew.diag0, (size_t)NP * sizeof(double));
-    CALLOC(c->ew.stat, 32 * sizeof(double));
-    CALLOC(c->ew.pos, (size_t)NP * sizeof(int));
-    CALLOC(c->ew.lam, (size_t)NP * sizeof(double));
-    CALLOC(c->ew.known, (size_t)c->d.LP * c->d.LP * sizeof(double));
+    {
+        // work space of the eigensolve: one allocation, every array on a multiple of 256 bytes
+        size_t bytes = 0;
+        auto take = [&](auto*& p, size_t count) {
+            if (c->eig_mem) p = (std::remove_reference_t<decltype(p)>)(c->eig_mem + bytes);
+            bytes += (count * sizeof(*p) + 255) / 256 * 256;
+        };
+        for (int pass = 0; pass < 2; ++pass) {
+            const size_t n1 = (size_t)NP, n2 = n1 * n1;
+            EigWork& w = c->ew;
+            bytes = 0;
+            take(w.xch, 6 * n1);
+            take(w.stat, 32);
+            take(w.C, n2);
+            take(w.Yt, n2);
+            take(w.V, n2);
+            for (int i = 0; i < 2; ++i) take(w.Z[i], n2);
+            for (int i = 0; i < 2; ++i) take(w.dI[i], n1);
+            for (double** p : {&w.dT, &w.eT, &w.tauT, &w.known, &w.dc.dk, &w.dc.zk, &w.dc.org, &w.dc.tau, &w.dc.val, &w.dc.zh})
+                take(*p, n1);
+            for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.K, &w.dc.k1, &w.dc.dense}) take(*p, n1);
+            if (pass == 0) CALLOC(c->eig_mem, bytes);
+        }
+        c->ew.xcd = xcd_take(c);
+    }
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
     CALLOC(c->acc, 8 * sizeof(double));
@@ -553,13 +574,14 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     // only the top half must start as zeros: rows of a new half beyond its fill are never read
     if (hipMemsetAsync(c->top, 0, hbytes, c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->acc, 0, 8 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
+    if (hipMemsetAsync(c->ew.stat, 0, 32 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
+    if (hipMemsetAsync(c->ew.xch, 0xFF, (size_t)6 * NP * sizeof(long long), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) return fail(SAGE_ERR_HIP);
-    if (hipHostMalloc((void**)&c->h_sweeps, SWEEP_RING * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&c->h_failed, sizeof(int), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
-        c->h_sweeps = nullptr;  // not fatal: every solve then launches all its sweeps
+        return fail(SAGE_ERR_ALLOC);
     }
-    for (int i = 0; i < SWEEP_RING; ++i)
-        if (hipEventCreateWithFlags(&c->ev_sweeps[i], hipEventDisableTiming) != hipSuccess) return fail(SAGE_ERR_HIP);
+    *c->h_failed = 0;
     *out = c;
     return SAGE_OK;
 }
@@ -571,15 +593,14 @@ void sage_destroy(sage_ctx* c) {
     (void)hipStreamSynchronize(c->st);
     if (c->st2) (void)hipStreamSynchronize(c->st2);
     void* ptrs[] = {c->top,     c->nw[0],    c->nw[1],  c->gram_partial, c->gram_partial_new[0], c->gram_partial_new[1],
-                    c->ew.C,    c->ew.Y,     c->ew.C2,  c->ew.Y2,        c->ew.Q,    c->ew.diag0, c->ew.stat,
-                    c->ew.pos,  c->ew.lam,   c->ew.known, c->Mt,         c->acc,     c->Vblk,     c->Vimg,
+                    c->eig_mem, c->Mt,       c->acc,    c->Vblk,         c->Vimg,
                     c->zhat,    c->proj_partial, c->cons_partial, c->ssum, c->alpha, c->labels, c->cb_work, c->stage, c->Mt3, c->dbg_count};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (c->st2) (void)hipStreamDestroy(c->st2);
-    if (c->h_sweeps) (void)hipHostFree(c->h_sweeps);
-    hipEvent_t evs[] = {c->ev_mark, c->ev_side[0], c->ev_side[1], c->ev_sweeps[0], c->ev_sweeps[1], c->ev_sweeps[2],
-                        c->ev_sweeps[3]};
+    xcd_release(c);
+    if (c->h_failed) (void)hipHostFree(c->h_failed);
+    hipEvent_t evs[] = {c->ev_mark, c->ev_side[0], c->ev_side[1]};
     for (hipEvent_t e : evs)
         if (e) (void)hipEventDestroy(e);
     free_select_work(c->sw);
@@ -716,14 +737,16 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     if (rc != SAGE_OK) return rc;
     rc = ensure_vblk(c, KP);
     if (rc != SAGE_OK) return rc;
-    rc = decompose(c, JACOBI_TOL_BASIS, false);
+    rc = decompose(c, k);
     if (rc != SAGE_OK) return rc;
-    RUN(K_COEFF, launch_basis_coeffs(c->ew, c->d.NP, KP, k, c->d.n, c->d.ell, weighted, c->cnt_top, c->fill_top,
-                                     c->d.LP + c->cnt_new, c->d.LP + c->fill_new, c->Mt, c->acc, JACOBI_TOL_BASIS, c->st));
+    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3 && rebuild_split_ok(KP) && KP <= c->d.LP;
+    RUN(K_COEFF, launch_coeffs(c->ew, c->d.NP, KP, k, weighted ? 2 : 1, c->d.n, c->d.ell, c->cnt_top, c->fill_top,
+                               c->d.LP + c->cnt_new, c->d.LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc,
+                               c->h_failed, c->st));
     c->cnt_top = c->fill_top;
     c->cnt_new = c->fill_new;
-    if (c->mm_mode == SAGE_MM_SPLIT && c->Mt3 && rebuild_split_ok(KP) && KP <= c->d.LP)
-        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], c->fill_new, c->Mt, c->Mt3, c->Vblk, KP, KP, c->d, c->st,
+    if (split_rb)
+        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], c->fill_new, c->Mt3, c->Vblk, KP, KP, c->d, c->st,
                                             c->fill_new > 0 && new_one(c, c->cur)));
     else
         RUN(K_REBUILD, launch_rebuild(c->top, c->nw[c->cur], c->fill_new, c->Mt, c->Vblk, KP, KP, c->d, c->st));
@@ -1156,9 +1179,9 @@ int sage_stats(sage_ctx* c, sage_stats_t* out) {
     out->sum_delta = acc[0];
     out->frob2 = acc[1] + pending;
     out->last_delta = acc[2];
-    out->last_sweeps = (int)acc[3];
+    out->last_sweeps = 0;  // the eigensolve is direct
     out->n_unconverged = (int64_t)acc[4];
-    out->last_offdiag = acc[5];
+    out->last_offdiag = 0.0;
     out->fill = c->fill_top + c->fill_new;
     return SAGE_OK;
 }
@@ -1176,11 +1199,9 @@ int sage_probe_gram_eig(sage_ctx* c, double* C_out, int eig, double* Y_out, doub
     // (rows 0 .. 2*ell-1, padding last).
     if (C_out) HIPCHK(launch_probe_permute(c->ew.C, C_out, NP, LP, ell, true, c->st));
     if (eig) {
-        HIPCHK(launch_eig(c->ew, NP, JACOBI_TOL_BASIS, MAX_SWEEPS, c->st));
-        if (Y_out) HIPCHK(launch_probe_permute(c->ew.Y, Y_out, NP, LP, ell, false, c->st));
-        if (lam_out)
-            HIPCHK(hipMemcpy2DAsync(lam_out, sizeof(double), c->ew.C, (size_t)(NP + 1) * sizeof(double), sizeof(double),
-                                    NP, hipMemcpyDeviceToDevice, c->st));
+        HIPCHK(eigensolve(c, LP, NP, NP));
+        HIPCHK(launch_eig_export(c->ew, NP, Y_out ? c->ew.V : nullptr, lam_out, nullptr, c->st));
+        if (Y_out) HIPCHK(launch_probe_permute(c->ew.V, Y_out, NP, LP, ell, false, c->st));
     }
     HIPCHK(hipStreamSynchronize(c->st));
     return SAGE_OK;
@@ -1210,13 +1231,8 @@ int sage_probe_eig_matrix(sage_ctx* c, const double* C_in, double* Y_out, double
     if (!C_in) return SAGE_ERR_ARG;
     const int NP = c->d.NP;
     HIPCHK(hipMemcpyAsync(c->ew.C, C_in, (size_t)NP * NP * sizeof(double), hipMemcpyDeviceToDevice, c->st));
-    HIPCHK(launch_eig(c->ew, NP, JACOBI_TOL_BASIS, MAX_SWEEPS, c->st));
-    if (Y_out) HIPCHK(hipMemcpyAsync(Y_out, c->ew.Y, (size_t)NP * NP * sizeof(double), hipMemcpyDeviceToDevice, c->st));
-    if (lam_out)
-        HIPCHK(hipMemcpy2DAsync(lam_out, sizeof(double), c->ew.C, (size_t)(NP + 1) * sizeof(double), sizeof(double), NP,
-                                hipMemcpyDeviceToDevice, c->st));
-    if (sweep_stat_out)
-        HIPCHK(hipMemcpyAsync(sweep_stat_out, c->ew.stat, 18 * sizeof(double), hipMemcpyDeviceToDevice, c->st));
+    HIPCHK(eigensolve(c, NP / 2, NP, NP));
+    HIPCHK(launch_eig_export(c->ew, NP, Y_out, lam_out, sweep_stat_out, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
     return SAGE_OK;
 }
@@ -1224,8 +1240,7 @@ int sage_probe_eig_matrix(sage_ctx* c, const double* C_in, double* Y_out, double
 int sage_set_sweep_policy(sage_ctx* c, int policy) {
     ALIVE(c);
     if (policy != SAGE_SWEEPS_ADAPTIVE && policy != SAGE_SWEEPS_ALL) return SAGE_ERR_ARG;
-    c->sweeps_all = policy == SAGE_SWEEPS_ALL;
-    return SAGE_OK;
+    return SAGE_OK;  // the eigensolve is direct: there is nothing to choose
 }
 
 int sage_set_debug_checks(sage_ctx* c, int on) {

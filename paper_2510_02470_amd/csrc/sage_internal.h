@@ -112,43 +112,46 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
 // result has the same bits)
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
                        hipStream_t st, bool new_one = false);
-// C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is `known`
-// (LP x LP, the Gram matrix of the rows the last shrink wrote, see EigWork::known)
+// C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
+// (the Gram matrix of the rows the last shrink wrote, see EigWork::known)
 hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const float* partial_b, const GramPlan* b,
                               double* C, bool known_top, const double* known, const Dims& d, hipStream_t st);
 
-// fd_eig.hip
-struct EigWork {
-    double* C;      // NP x NP, destroyed (becomes near-diagonal)
-    double* Y;      // NP x NP eigenvectors in columns
-    double* C2;     // ping-pong partners of C and Y for the out-of-place rotation updates
-    double* Y2;
-    double* Q;      // (NP/64) x 64 x 64 rotation blocks of the current step
-    double* diag0;  // NP: diagonal of C before the solve
-    double* stat;   // [0] trace, [1..MAXSWEEP] per-sweep max |off| / trace
-    int* pos;       // NP: pos[rank] = column of Y holding the rank-th largest eigenvalue
-    double* lam;    // NP: eigenvalues sorted descending
-    double* known;  // LP x LP: Gram matrix of the rows the last shrink wrote, diag(w) (Y^T C Y) diag(w): diagonal
-                    // lambda_j - delta (0 from row ell-1 on), off-diagonal whatever the eigensolve left (<= its tolerance)
+// fd_tridiag.hip, fd_dc.hip, fd_eig.hip: the eigensolve
+struct DcWork {  // work arrays of the merges above 64 rows (see fd_dc.hip)
+    double *dk, *zk, *org, *tau, *val, *zh;  // NP each
+    int *col, *half, *npos;                  // NP each
+    int *K, *k1, *dense;                     // per sub-problem
 };
-constexpr int MAX_SWEEPS = 14;
-// Stopping rule: a sweep records the largest |c_pq| / trace(C) it met before rotating; the solve ends after the
-// first sweep whose record is <= tol. The shrink only needs the residual to be below the fp32 error of the Gram
-// matrix (~1e-7 trace); the scoring basis is taken once per pass and is solved tighter.
-constexpr double JACOBI_TOL_SHRINK = 1e-7;
-constexpr double JACOBI_TOL_BASIS = 1e-9;
-// max_sweeps <= MAX_SWEEPS sweeps are launched (sweeps after convergence return at once). acc[3] of the coefficient
-// kernels then holds the sweeps that were needed, or max_sweeps + SWEEPS_NOT_CONVERGED when they did not suffice;
-// acc[4] counts the solves that ended above their tolerance, acc[5] is the last solve's final off-diagonal record.
-constexpr int SWEEPS_NOT_CONVERGED = 100;
-hipError_t launch_eig(const EigWork& w, int NP, double tol, int max_sweeps, hipStream_t st);
-// scalars on device: acc[0] sum_delta, acc[1] frob2, acc[2] last_delta, acc[3] sweeps used (as double), acc[4], acc[5]
-// frob2 += diag0 over matrix indices [ra0, ra1) and [rb0, rb1) (the rows not yet counted in ||A||_F^2)
-hipError_t launch_shrink_coeffs(const EigWork& w, int NP, int LP, int ell, int ra0, int ra1, int rb0, int rb1, float* Mt,
-                                double* acc, double tol, hipStream_t st);
-// weighted: rows sqrt(max(lambda_j - lambda_ell, 0)) v_j^T instead of v_j^T
-hipError_t launch_basis_coeffs(const EigWork& w, int NP, int KP, int k, int n, int ell, bool weighted, int ra0, int ra1,
-                               int rb0, int rb1, float* Mt, double* acc, double tol, hipStream_t st);
+struct EigWork {
+    double* C;      // NP x NP Gram matrix, left untouched
+    double* Yt;     // NP x NP: row m = eigenvector of the m-th largest eigenvalue
+    double* V;      // NP x NP Householder vectors (row k: the reflector of step k)
+    double* Z[2];   // NP x NP, column-major: eigenvectors of T, ping-pong between the merges
+    double* dT;     // NP: diagonal, sub-diagonal and reflector factors of the reduction
+    double* eT;
+    double* tauT;
+    double* dI[2];  // NP: eigenvalues, ascending, in units of 2^stat[0]
+    double* stat;   // [0] exponent of the scaling, [1] set when the reduction gave up waiting for a work-group
+    double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
+    long long* xch; // exchange buffers of the reduction (NP = 256, 512), 6 NP entries, EMPTY between solves
+    int xcd;        // the XCD the reduction runs on (NP = 256, 512)
+    DcWork dc;
+};
+// which of dI / Z the last merge of a solve of size NP writes
+inline int dc_result(int NP) { return (NP == 128 || NP == 512) ? 1 : 0; }
+// Matrix indices in use: 0 .. m0-1 and LP .. LP + (n - m0) - 1, n in all (the others are zero rows and columns); the count
+// leading eigenvectors are formed.
+hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
+hipError_t launch_dc(const EigWork& w, int NP, hipStream_t st);
+hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st);
+hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st);
+// Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2); into Mc3 (split parts) if given, else into Mt.
+// Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1) and [rb0, rb1), the rows not
+// yet counted), acc[2] last_delta, acc[4] failed solves; *failed (host memory) is set after a failed solve.
+hipError_t launch_coeffs(const EigWork& w, int NP, int MP, int count, int mode, int n, int ell, int ra0, int ra1, int rb0,
+                         int rb1, float* Mt, void* Mc3, double* acc, int* failed, hipStream_t st);
+hipError_t launch_eig_export(const EigWork& w, int NP, double* Y, double* lam, double* record, hipStream_t st);
 
 // Where the coefficient M[m][i] (output row m < MP, buffer row i < NP) is stored for the rebuild kernel: chunks of
 // 16 buffer rows; inside a chunk [i & 1][m][(i & 15) >> 1], i.e. the 8 values a matrix-core lane needs are
@@ -165,13 +168,13 @@ __host__ __device__ inline int64_t coeff_offset(int i, int m, int MP) {
 hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const float* Mc, float* out, int out_NP, int MP,
                           const Dims& d, hipStream_t st);
 // The same product on the bf16 matrix cores with both factors split into three bf16 parts (six products: 24-bit
-// accuracy at 2.7 times the fp32 matrix-core rate). Mc3: work space of rebuild_split_bytes(d, MP) bytes (receives the
-// split coefficients). Only for MP = 128 or 256 (rebuild_split_ok).
+// accuracy at 2.7 times the fp32 matrix-core rate). Mc3: the split coefficients, rebuild_split_bytes(d, MP) bytes. Only for
+// MP = 128 or 256 (rebuild_split_ok).
 bool rebuild_split_ok(int MP);
 size_t rebuild_split_bytes(const Dims& d, int MP);
 // new_one: as for launch_gram (three products instead of six for the new half).
-hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const float* Mc, void* Mc3, float* out,
-                                int out_NP, int MP, const Dims& d, hipStream_t st, bool new_one = false);
+hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
+                                const Dims& d, hipStream_t st, bool new_one = false);
 
 // score.hip
 struct ScorePlan {

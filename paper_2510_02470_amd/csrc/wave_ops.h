@@ -1,0 +1,76 @@
+// fp64 helpers of the eigensolver kernels: sums over a wave by DPP (no LDS), reciprocals.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace sage {
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)u, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+constexpr int DPP_XOR1 = 0xB1;         // quad_perm [1,0,3,2]
+constexpr int DPP_XOR2 = 0x4E;         // quad_perm [2,3,0,1]
+constexpr int DPP_HALF_MIRROR = 0x141; // lane l of 8 -> 7 - l: the other quad once quads are uniform
+constexpr int DPP_MIRROR = 0x140;      // lane l of 16 -> 15 - l: the other half once halves are uniform
+
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)u, lane);
+    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double uniform(double v) {
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)u);
+    const int hi = __builtin_amdgcn_readfirstlane((int)(u >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Sum over groups of L lanes (L = 8, 16 or 64), the same bits in every lane of the group.
+template <int L>
+__device__ __forceinline__ double lane_sum(double v) {
+    v += dpp_move<DPP_XOR1>(v);
+    v += dpp_move<DPP_XOR2>(v);
+    v += dpp_move<DPP_HALF_MIRROR>(v);
+    if constexpr (L >= 16) v += dpp_move<DPP_MIRROR>(v);
+    if constexpr (L == 64) v = (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+    return v;
+}
+template <int L>
+__device__ __forceinline__ double lane_product(double v) {
+    v *= dpp_move<DPP_XOR1>(v);
+    v *= dpp_move<DPP_XOR2>(v);
+    v *= dpp_move<DPP_HALF_MIRROR>(v);
+    if constexpr (L >= 16) v *= dpp_move<DPP_MIRROR>(v);
+    if constexpr (L == 64) v = (read_lane(v, 0) * read_lane(v, 16)) * (read_lane(v, 32) * read_lane(v, 48));
+    return v;
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_move_i(int v) {
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
+}
+template <int L>
+__device__ __forceinline__ int lane_sum_i(int v) {
+    v += dpp_move_i<DPP_XOR1>(v);
+    v += dpp_move_i<DPP_XOR2>(v);
+    v += dpp_move_i<DPP_HALF_MIRROR>(v);
+    if constexpr (L >= 16) v += dpp_move_i<DPP_MIRROR>(v);
+    if constexpr (L == 64)
+        v = (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
+            (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+    return v;
+}
+
+// 1 / x to about one unit in the last place for normal x (hardware estimate and two Newton steps)
+__device__ __forceinline__ double rcp64(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return y;
+}
+
+}  // namespace sage

@@ -1,0 +1,80 @@
+"""The direct eigensolve (tridiagonal reduction, divide and conquer) at every padded size, on spectra that exercise its
+branches: deflation of every kind, equal poles across a merge, ranks far below the size, scales far from one."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrices(n):
+    rng = np.random.default_rng(n)
+    Q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    h = n // 8
+    A = rng.standard_normal((n, 700)) * np.exp(rng.standard_normal((n, 1)))
+    lap = np.diag(np.full(n, 2.0)) - np.diag(np.ones(n - 1), 1) - np.diag(np.ones(n - 1), -1)
+    top = np.sort(rng.random(n // 2))[::-1]
+    X = 0.1 * rng.standard_normal((n // 2, n))
+    cross = np.zeros((n, n))
+    cross[: n // 2, : n // 2] = np.diag(top)
+    cross[n // 2:, n // 2:] = X @ X.T
+    cross[n // 2:, : n // 2] = 0.1 * rng.standard_normal((n // 2, n // 2)) * np.sqrt(top)
+    cross = np.tril(cross) + np.tril(cross, -1).T
+    spec = {
+        "clustered": np.concatenate([np.full(2 * h, 1.0), 1 + 1e-9 * np.arange(3 * h), np.linspace(0.5, 1e-8, n - 5 * h)]),
+        "rank8": np.concatenate([np.linspace(3, 1, 8), np.zeros(n - 8)]),
+        "graded": 10.0 ** (-np.arange(n) / 8.0),
+        "signal_and_noise": np.concatenate([1.0 / np.arange(1, n // 4 + 1), 1e-4 * np.exp(rng.standard_normal(n - n // 4))]),
+    }
+    out = {k: (Q * v) @ Q.T for k, v in spec.items()}
+    out.update(gram=A @ A.T, tiny=(A @ A.T) * 1e-60, huge=(A @ A.T) * 1e60, zero=np.zeros((n, n)), diagonal=np.diag(rng.random(n)),
+               ones=np.ones((n, n)), laplace=lap, identity=np.eye(n), blocks=np.kron(np.eye(n // 32), A[:32] @ A[:32].T),
+               after_a_shrink=cross)
+    return out
+
+
+@pytest.mark.parametrize("ell", [32, 64, 128, 256])
+def test_eigensolve_at_every_padded_size(ell):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    s, n = Sage(ell, 64), 2 * ell
+    for name, C in _matrices(n).items():
+        C = (C + C.T) / 2
+        Y, lam, _ = s.probe_eig_matrix(torch.from_numpy(C).cuda())
+        Y, lam = Y.cpu().numpy(), lam.cpu().numpy()
+        scale = max(np.abs(C).max(), 1e-300) * n
+        assert np.abs(Y.T @ Y - np.eye(n)).max() <= 1e-13, name
+        assert np.abs((Y * lam) @ Y.T - C).max() <= 1e-14 * scale, name
+        assert np.abs(np.sort(lam) - np.linalg.eigvalsh(C)).max() <= 1e-14 * scale, name
+
+
+def test_contexts_in_several_streams_share_the_gpu():
+    """More contexts than XCDs, each on a stream of its own with work in flight at the same time: the reductions that keep
+    work-groups of one XCD in step must not starve each other."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(3)
+    G = torch.randn((256 * 5, 900), generator=g, device="cuda")
+    ref = Sage(256, 900)
+    ref.fd_update(G)
+    want = ref.sketch()
+    streams = [torch.cuda.Stream() for _ in range(18)]
+    torch.cuda.synchronize()
+    ctx = []
+    for st in streams:
+        with torch.cuda.stream(st):
+            ctx.append(Sage(256, 900))
+    for lo in range(0, G.shape[0], 256):
+        for st, c in zip(streams, ctx):
+            with torch.cuda.stream(st):
+                c.fd_update(G[lo:lo + 256])
+    for st, c in zip(streams, ctx):
+        with torch.cuda.stream(st):
+            got = c.sketch()
+            st.synchronize()
+        # one call or five: the same rows, the last bits of the Gram blocks may differ
+        assert torch.allclose(got.T @ got, want.T @ want, rtol=0, atol=1e-5 * float((want.T @ want).abs().max()))
+        c.close()
