@@ -15,6 +15,7 @@
 // Every size, index and count derived here is clamped by construction (counts of comparisons between finite numbers), so
 // non-finite input gives wrong numbers but no access out of bounds.
 #include "sage_internal.h"
+#include "fd_wy.h"
 #include "wave_ops.h"
 
 namespace sage {
@@ -35,42 +36,48 @@ __device__ __forceinline__ double dc_tolerance(const double* __restrict__ dT, co
     return 4.0 * DC_EPS * m;
 }
 
+// sqrt(x) for x >= 0 to about one unit in the last place (hardware estimate, two Newton steps)
+__device__ __forceinline__ double sqrt64(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
+    double r = x * y;
+    r = __builtin_fma(__builtin_fma(-r, r, x), 0.5 * y, r);
+    return x > 1e-290 ? r : 0.0;
+}
+
 // Root q of 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending): lambda = org + tau with org the
-// nearer of the poles around it. A group of L lanes works on a root; lane l holds the poles l + L e, e < 8 (z = 0 and
-// d = 1e30 beyond K).
-template <int L>
-__device__ __forceinline__ void secular_root(int K, int q, int l, const double (&dj)[8], const double (&zj)[8],
-                                             double dq, double dq1, double zsum, double& org, double& tau) {
+// nearer of the poles around it. A group of L lanes works on a root; lane l holds the poles l + L e, e < E (z = 0 and
+// d = 1e30 beyond K). The interpolation converges quadratically: a step below 1e-9 of tau is the last one. About 3
+// evaluations a root.
+template <int L, int E>
+__device__ __forceinline__ void secular_root(int K, int q, int l, const double (&dj)[E], const double (&zj)[E], double dq,
+                                             double dq1, double zsum, double& org, double& tau) {
     const bool last = q == K - 1;
-    double lo, hi;
+    double lo = 0.0, hi = zsum * (1.0 + 4.0 * DC_EPS);
     org = dq;
     if (!last) {
         const double mid = 0.5 * (dq1 - dq);
         double f = 0.0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) f = __builtin_fma(zj[e], rcp64((dj[e] - dq) - mid), f);
+        for (int e = 0; e < E; ++e) f = __builtin_fma(zj[e], rcp64((dj[e] - dq) - mid), f);
         f = 1.0 + lane_sum<L>(f);
         if (f >= 0.0) {
-            lo = 0.0;
             hi = mid;
         } else {
             org = dq1;
             lo = -mid;
             hi = 0.0;
         }
-    } else {
-        lo = 0.0;
-        hi = zsum * (1.0 + 4.0 * DC_EPS);
     }
     double t = 0.5 * (lo + hi);
-    double dl[8];
+    double dl[E];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) dl[e] = dj[e] - org;
+    for (int e = 0; e < E; ++e) dl[e] = dj[e] - org;
     const double dlq = dq - org, dlq1 = dq1 - org;
     for (int it = 0; it < 60; ++it) {
         double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < E; ++e) {
             const double inv = rcp64(dl[e] - t);
             const double r = zj[e] * inv, r2 = r * inv;
             const bool low = l + L * e <= q;
@@ -96,36 +103,37 @@ __device__ __forceinline__ void secular_root(int K, int q, int l, const double (
             const double c = 1.0 + (psi - di * dpsi) + (phi - dn * dphi);
             // c + p / (di - x) + g / (dn - x) = 0, the root between the poles
             const double b = -(c * (di + dn) + p + g), a0 = c * di * dn + p * dn + g * di;
-            const double s = __builtin_sqrt(fmax(__builtin_fma(b, b, -4.0 * c * a0), 0.0));
+            const double s = sqrt64(fmax(__builtin_fma(b, b, -4.0 * c * a0), 0.0));
             const double h = -0.5 * (b + __builtin_copysign(s, b));
-            const double x1 = a0 / h, x2 = h / c;
+            const double x1 = a0 * rcp64(h), x2 = h * rcp64(c);
             x = (x1 > di && x1 < dn) ? x1 : x2;
             if (!(x > di && x < dn)) x = __builtin_nan("");
         } else {
             const double s = 1.0 + (psi - di * dpsi);
-            x = s > 0.0 ? di + di * di * dpsi / s : __builtin_nan("");
+            x = s > 0.0 ? di + di * di * dpsi * rcp64(s) : __builtin_nan("");
         }
         double tn = t + x;
-        if (!(tn > lo && tn < hi)) tn = 0.5 * (lo + hi);
-        if (tn == t || !(hi - lo > fabs(t) * DC_EPS)) break;
+        const bool in = tn > lo && tn < hi;
+        if (!in) tn = 0.5 * (lo + hi);
+        const bool done = tn == t || !(hi - lo > fabs(t) * DC_EPS) || (in && fabs(x) <= 1e-9 * fabs(tn));
         t = tn;
+        if (done) break;
     }
     tau = t;
 }
 
 // |z_j| of the rank-one problem whose eigenvalues are exactly the computed roots: the product over i != j of
 // (lambda_i - d_j) / (d_i - d_j), times (lambda_j - d_j). Lane l holds roots l + L e.
-template <int L>
-__device__ __forceinline__ double secular_z(int K, int j, int l, double dj, const double (&di)[8], const double (&org)[8],
-                                            const double (&tau)[8]) {
+template <int L, int E>
+__device__ __forceinline__ double secular_z(int K, int j, int l, double dj, const double (&di)[E], const double (&org)[E],
+                                            const double (&tau)[E]) {
     double pr = 1.0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < E; ++e) {
         const int i = l + L * e;
-        if (i < K) {
-            const double num = (org[e] - dj) + tau[e];
-            pr *= i == j ? num : num * rcp64(di[e] - dj);
-        }
+        const double num = (org[e] - dj) + tau[e];
+        const double f = i == j ? num : num * rcp64(di[e] - dj);
+        pr *= i < K ? f : 1.0;
     }
     pr = lane_product<L>(pr);
     return __builtin_sqrt(fabs(pr));
@@ -137,223 +145,291 @@ __device__ __forceinline__ bool poles_equal(double d0, double z0, double d1, dou
     return fabs((d1 - d0) * z0 * z1) <= tol * t2;
 }
 
-// ---- merges of 2 .. 64 rows, one work-group per 64 x 64 diagonal block --------------------------------------------
-// 512 threads: 8 lanes per index. All arrays of the block in LDS; Q column-major.
-constexpr int DCB_LD = 65;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+// fp64 matrix-core step acc(16x16) += a(16x4) b(4x16): lane l supplies a[l%16][l/16] and b[l/16][l%16];
+// acc element v of lane l is row 4v + l/16, column l%16.
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+}
+
+// ---- pairs in closed form and merges of 4 .. 64 rows, one work-group per 64 x 64 diagonal block ----------------------
+// 512 threads: 8 lanes per index, a sub-problem of M rows per 8 M threads. All arrays of the block in LDS; Q column-major.
+// A merge is a chain of short phases between barriers; half the time goes into the roots, which is why their loops are
+// unrolled to what M needs, and the products of 16 rows and more run on the matrix cores (in scalar code, bound by LDS
+// reads, the last product alone took 17 us). 45 us in all against 104 us for one loop over all sizes.
+constexpr int DCB_LD = 65;   // columns of Q
+constexpr int DCB_LDU = 68;  // columns of U: the 16 columns x 4 rows of a matrix-core operand fall on distinct banks
 struct DcBlockLds {
-    double Q[64 * DCB_LD], U[64 * DCB_LD];
-    double d[64], e[64], z[64], ds[64], zs[64], dk[64], zk[64], org[64], tau[64], zh[64], val[64];
-    double rc[64], rs[64];  // rotations
-    int cs[64], sv[64], col[64], ra[64], rb[64];
-    int K[64], nrot[64];    // per sub-problem (indexed by its base)
+    double Q[64 * DCB_LD], U[64 * DCB_LDU];
+    double d[64], e[64], ds[64], zs[64], dk[64], zk[64], org[64], tau[64], zh[64], val[64];
+    double rc[64], rs[64], td[64];  // rotations; poles they deflate
+    int cs[64], col[64], np[64], ra[64], rb[64], tc[64];
+    int K[64], nrot[64];            // per sub-problem (indexed by its base)
+    unsigned char mask[8];          // surviving entries, in order
     int any;
 };
 
-__global__ __launch_bounds__(512, 1) void dc_block_kernel(const double* __restrict__ dT, const double* __restrict__ eT, int N,
-                                                          double* __restrict__ dO, double* __restrict__ Z,
-                                                          long long* __restrict__ xch) {
-    // the exchange buffers of the reduction that has just ended, ready for the next one
-    if (xch)
-        for (int q = blockIdx.x * 512 + threadIdx.x; q < 6 * N; q += gridDim.x * 512) xch[q] = -1LL;
-    extern __shared__ char dc_lds[];
-    DcBlockLds& S = *reinterpret_cast<DcBlockLds*>(dc_lds);
-    const int tid = threadIdx.x, i = tid >> 3, l = tid & 7;
-    const int b0 = blockIdx.x * 64;
-    const double tol = dc_tolerance(dT, eT, N, tid & 63);
-    if (l == 0) {
-        const int g = b0 + i;
-        const double e0 = g > 0 ? fabs(finite_or_zero(eT[g - 1])) : 0.0;
-        const double e1 = finite_or_zero(eT[g]);
-        S.e[i] = e1;
-        S.d[i] = finite_or_zero(dT[g]) - e0 - fabs(e1);  // every cut is torn: both its neighbours lose |e|
-    }
-    for (int r = l; r < 64; r += 8) S.Q[i * DCB_LD + r] = r == i ? 1.0 : 0.0;
-    __syncthreads();
-
-    for (int m = 2; m <= 64; m *= 2) {
-        const int half = m >> 1, base = i & ~(m - 1), li = i & (m - 1);
-        const double ec = S.e[base + half - 1], rho = fabs(ec);
+template <int M>
+__device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
+    constexpr int H = M / 2, E = M > 8 ? M / 8 : 1, EH = H > 8 ? H / 8 : 1;
+    const int i = tid >> 3, l = tid & 7;
+    const int base = i & ~(M - 1), li = i & (M - 1);
+    const double ec = S.e[base + H - 1], rho = fabs(ec);
+    {
         const double di = S.d[i];
-        double zi;
-        if (li < half) zi = S.Q[i * DCB_LD + base + half - 1];
-        else zi = ec < 0.0 ? -S.Q[i * DCB_LD + base + half] : S.Q[i * DCB_LD + base + half];
-        zi = finite_or_zero(zi);
+        double zi = li < H ? S.Q[i * DCB_LD + base + H - 1] : S.Q[i * DCB_LD + base + H];
+        zi = finite_or_zero(li >= H && ec < 0.0 ? -zi : zi);
+        // both halves are sorted: rank = own position + entries of the other half that go before
+        const int o = base + (li < H ? H : 0);
         int cnt = 0;
-        for (int j = l; j < m; j += 8) {
-            const double x = S.d[base + j];
-            cnt += (x < di || (x == di && j < li)) ? 1 : 0;
+#pragma unroll
+        for (int e = 0; e < EH; ++e) {
+            const int j = l + 8 * e;
+            const double x = S.d[o + (j & (H - 1))];
+            cnt += j < H && (x < di || (x == di && li >= H)) ? 1 : 0;
         }
-        cnt = lane_sum_i<8>(cnt);
+        cnt = lane_sum_i<8>(cnt) + (li < H ? li : li - H);
         if (l == 0) {
             S.ds[base + cnt] = di;
             S.zs[base + cnt] = zi;
             S.cs[base + cnt] = i;
         }
-        if (tid == 0) S.any = 0;
-        __syncthreads();
-        // survivors in order, then the deflated
-        bool live = rho * fabs(S.zs[i]) > tol;
-        int before = 0, K = 0;
-        for (int j = l; j < m; j += 8) {
-            const int f = rho * fabs(S.zs[base + j]) > tol ? 1 : 0;
-            K += f;
-            before += j < li ? f : 0;
-        }
-        before = lane_sum_i<8>(before);
-        K = lane_sum_i<8>(K);
+    }
+    if (tid == 0) S.any = 0;
+    __syncthreads();
+    // survivors in order, then the deflated
+    const double dsi = S.ds[i], zsi = S.zs[i];
+    const int csi = S.cs[i];
+    const bool live = rho * fabs(zsi) > tol;
+    {
+        const unsigned long long b = __ballot(live) & 0x0101010101010101ull;  // bit 8 q: index 8 wave + q
+        if ((tid & 63) == 0) S.mask[tid >> 6] = (unsigned char)((b * 0x0102040810204080ull) >> 56);
+    }
+    __syncthreads();
+    const unsigned long long all = *reinterpret_cast<const unsigned long long*>(S.mask);
+    const unsigned long long sub = M == 64 ? all : (all >> base) & ((1ull << (M & 63)) - 1ull);
+    int K = __popcll(sub);
+    {
+        const int before = __popcll(sub & ((1ull << li) - 1ull));
+        const int pos = live ? before : K + li - before;
         if (l == 0) {
-            S.sv[base + (live ? before : K + li - before)] = i;
+            S.dk[base + pos] = dsi;
+            S.zk[base + pos] = zsi;
+            S.col[base + pos] = csi;
             if (li == 0) S.K[base] = K;
+            const unsigned long long after = li == 63 ? 0ull : sub >> (li + 1);
+            if (live && after) {
+                const int nx = base + li + 1 + __builtin_ctzll(after);
+                if (poles_equal(dsi, zsi, S.ds[nx], S.zs[nx], tol)) S.any = 1;
+            }
         }
-        __syncthreads();
-        if (l == 0 && li + 1 < K) {
-            const int s0 = S.sv[i], s1 = S.sv[i + 1];
-            if (poles_equal(S.ds[s0], S.zs[s0], S.ds[s1], S.zs[s1], tol)) S.any = 1;
-        }
-        __syncthreads();
-        if (S.any) {  // rare: walk the survivors in order, rotate equal poles together
-            if (tid < 64 && (tid & (m - 1)) == 0) {
-                const int bb = tid, Kb = S.K[bb];
-                int nk = 0, nr = 0, nd = 0, pj = -1;
-                // (col is free here: survivors are collected there, the deflated in ra's tail via a second list)
-                for (int q = 0; q < Kb; ++q) {
-                    const int nj = S.sv[bb + q];
-                    if (pj < 0) {
-                        pj = nj;
-                        continue;
-                    }
-                    const double z0 = S.zs[pj], z1 = S.zs[nj];
-                    if (poles_equal(S.ds[pj], z0, S.ds[nj], z1, tol)) {
-                        const double t = __builtin_sqrt(z0 * z0 + z1 * z1), c = z1 / t, s = -z0 / t;
-                        const double d0 = S.ds[pj], d1 = S.ds[nj];
-                        S.zs[nj] = t;
-                        S.zs[pj] = 0.0;
-                        S.ds[pj] = d0 * c * c + d1 * s * s;
-                        S.ds[nj] = d0 * s * s + d1 * c * c;
-                        S.ra[bb + nr] = S.cs[pj];
-                        S.rb[bb + nr] = S.cs[nj];
+    }
+    __syncthreads();
+    if (S.any) {  // rare: walk the survivors in order, rotate equal poles together
+        if (tid < 64 && (tid & (M - 1)) == 0) {
+            const int bb = tid, Kb = S.K[bb];
+            int nk = 0, nr = 0, pc = -1;
+            double pd = 0.0, pz = 0.0;
+            for (int q = 0; q < Kb; ++q) {
+                double nd = S.dk[bb + q], nz = S.zk[bb + q];
+                const int nc = S.col[bb + q];
+                if (pc >= 0) {
+                    if (poles_equal(pd, pz, nd, nz, tol)) {
+                        const double t = __builtin_sqrt(pz * pz + nz * nz), c = nz / t, s = -pz / t;
+                        S.td[bb + nr] = pd * c * c + nd * s * s;
+                        S.tc[bb + nr] = pc;
+                        nd = pd * s * s + nd * c * c;
+                        nz = t;
+                        S.ra[bb + nr] = pc;
+                        S.rb[bb + nr] = nc;
                         S.rc[bb + nr] = c;
                         S.rs[bb + nr] = s;
                         ++nr;
-                        S.col[bb + m - 1 - nd++] = pj;  // deflated, collected from the end
-                        pj = nj;
                     } else {
-                        S.col[bb + nk++] = pj;
-                        pj = nj;
+                        S.dk[bb + nk] = pd;
+                        S.zk[bb + nk] = pz;
+                        S.col[bb + nk] = pc;
+                        ++nk;
                     }
                 }
-                if (pj >= 0) S.col[bb + nk++] = pj;
-                // nk + nd == Kb; entries Kb .. m-1 of sv stay deflated
-                for (int q = 0; q < nk; ++q) S.sv[bb + q] = S.col[bb + q];
-                for (int q = 0; q < nd; ++q) S.sv[bb + nk + q] = S.col[bb + m - 1 - q];
-                S.K[bb] = nk;
-                S.nrot[bb] = nr;
+                pd = nd;
+                pz = nz;
+                pc = nc;
             }
-            __syncthreads();
-            if (l == 0) {
-                const int nr = S.nrot[base];
-                for (int q = 0; q < nr; ++q) {
-                    double* A = S.Q + S.ra[base + q] * DCB_LD + i;
-                    double* B = S.Q + S.rb[base + q] * DCB_LD + i;
-                    const double a = *A, b = *B, c = S.rc[base + q], s = S.rs[base + q];
-                    *A = c * a + s * b;
-                    *B = c * b - s * a;
-                }
+            if (pc >= 0) {
+                S.dk[bb + nk] = pd;
+                S.zk[bb + nk] = pz;
+                S.col[bb + nk] = pc;
+                ++nk;
             }
-            K = S.K[base];
-            __syncthreads();
+            for (int q = 0; q < nr; ++q) {  // nk + nr == Kb
+                S.dk[bb + nk + q] = S.td[bb + q];
+                S.zk[bb + nk + q] = 0.0;
+                S.col[bb + nk + q] = S.tc[bb + q];
+            }
+            S.K[bb] = nk;
+            S.nrot[bb] = nr;
         }
-        // compact arrays in the order of sv
-        const int sq = S.sv[i];
+        __syncthreads();
         if (l == 0) {
-            S.dk[i] = S.ds[sq];
-            S.zk[i] = S.zs[sq];
-            S.col[i] = S.cs[sq];
-        }
-        __syncthreads();
-        double dj[8], zj[8];
-        double zsum = 0.0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = l + 8 * e;
-            const bool on = j < K;
-            dj[e] = on ? S.dk[base + j] : 1e30;
-            const double z = on ? S.zk[base + j] : 0.0;
-            zj[e] = rho * z * z;
-            zsum += zj[e];
-        }
-        zsum = lane_sum<8>(zsum);
-        double org = 0.0, tau = 0.0, val = S.dk[i];
-        if (li < K) {
-            secular_root<8>(K, li, l, dj, zj, S.dk[i], li + 1 < K ? S.dk[i + 1] : 0.0, zsum, org, tau);
-            val = org + tau;
-            val = finite_or_zero(val);
-        }
-        if (l == 0) {
-            S.org[i] = org;
-            S.tau[i] = tau;
-            S.val[i] = val;
-        }
-        __syncthreads();
-        double og[8], ta[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = l + 8 * e;
-            og[e] = j < K ? S.org[base + j] : 0.0;
-            ta[e] = j < K ? S.tau[base + j] : 0.0;
-        }
-        if (li < K) {
-            const double zz = secular_z<8>(K, li, l, S.dk[i], dj, og, ta);
-            if (l == 0) S.zh[i] = __builtin_copysign(zz, S.zk[i]);
-        }
-        int np = 0;
-        for (int j = l; j < m; j += 8) {
-            const double x = S.val[base + j];
-            np += (x < val || (x == val && j < li)) ? 1 : 0;
-        }
-        np = lane_sum_i<8>(np);
-        __syncthreads();
-        if (li < K) {
-            double u[8], nn = 0.0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int j = l + 8 * e;
-                u[e] = j < K ? S.zh[base + j] * rcp64((dj[e] - org) - tau) : 0.0;
-                nn = __builtin_fma(u[e], u[e], nn);
-            }
-            nn = rcp64(__builtin_sqrt(lane_sum<8>(nn)));
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int j = l + 8 * e;
-                if (j < K) S.U[i * DCB_LD + j] = u[e] * nn;
+            const int nr = S.nrot[base];
+            for (int q = 0; q < nr; ++q) {
+                double* A = S.Q + S.ra[base + q] * DCB_LD + i;
+                double* B = S.Q + S.rb[base + q] * DCB_LD + i;
+                const double a = *A, b = *B, c = S.rc[base + q], s = S.rs[base + q];
+                *A = c * a + s * b;
+                *B = c * b - s * a;
             }
         }
-        __syncthreads();
-        double out[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) out[r] = 0.0;
-        const int nr8 = (m + 7) >> 3;
-        if (li < K) {
-            for (int j = 0; j < K; ++j) {
-                const double u = S.U[i * DCB_LD + j];
-                const double* qc = S.Q + S.col[base + j] * DCB_LD + base + l;
-#pragma unroll
-                for (int r = 0; r < 8; ++r)
-                    if (r < nr8 && l + 8 * r < m) out[r] = __builtin_fma(qc[8 * r], u, out[r]);
-            }
-        } else {
-            const double* qc = S.Q + S.col[i] * DCB_LD + base + l;
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                if (r < nr8 && l + 8 * r < m) out[r] = qc[8 * r];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            if (r < nr8 && l + 8 * r < m) S.Q[(base + np) * DCB_LD + base + l + 8 * r] = out[r];
-        if (l == 0) S.d[base + np] = val;
+        K = S.K[base];
         __syncthreads();
     }
+    const double dki = S.dk[i];
+    double dj[E], zj[E], zsum = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int j = l + 8 * e;
+        const bool on = j < K;
+        dj[e] = on ? S.dk[base + (j & (M - 1))] : 1e30;
+        const double z = on ? S.zk[base + (j & (M - 1))] : 0.0;
+        zj[e] = rho * z * z;
+        zsum += zj[e];
+    }
+    zsum = lane_sum<8>(zsum);
+    double org = 0.0, tau = 0.0, val = dki;
+    if (li < K) {
+        secular_root<8, E>(K, li, l, dj, zj, dki, li + 1 < K ? S.dk[i + 1] : 0.0, zsum, org, tau);
+        val = finite_or_zero(org + tau);
+    }
+    if (l == 0) {
+        S.org[i] = org;
+        S.tau[i] = tau;
+        S.val[i] = val;
+    }
+    __syncthreads();
+    {
+        double og[E], ta[E];
+        int np = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = l + 8 * e, jj = base + (j & (M - 1));
+            og[e] = S.org[jj];
+            ta[e] = S.tau[jj];
+            const double x = S.val[jj];
+            np += j < M && (x < val || (x == val && j < li)) ? 1 : 0;
+        }
+        np = lane_sum_i<8>(np);
+        const double zz = secular_z<8, E>(K, li, l, dki, dj, og, ta);
+        if (l == 0) {
+            S.zh[i] = __builtin_copysign(zz, S.zk[i]);
+            S.np[i] = base + np;
+            S.d[base + np] = val;
+        }
+    }
+    __syncthreads();
+    {
+        double u[E], nn = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = l + 8 * e;
+            u[e] = j < K ? S.zh[base + (j & (M - 1))] * rcp64((dj[e] - org) - tau) : 0.0;
+            nn = __builtin_fma(u[e], u[e], nn);
+        }
+        nn = lane_sum<8>(nn);
+        nn = rcp64(__builtin_sqrt(nn));
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = l + 8 * e;
+            if (j < M) S.U[i * DCB_LDU + j] = li < K ? u[e] * nn : (j == li ? 1.0 : 0.0);
+        }
+    }
+    __syncthreads();
+    if constexpr (M >= 16) {
+        constexpr int T = M / 16, TILES = (64 / M) * T * T, PER = TILES > 8 ? TILES / 8 : 1;
+        const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lk = lane >> 4;
+        f64x4 acc[PER];
+#pragma unroll
+        for (int g = 0; g < PER; ++g) {
+            acc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
+            const int t = wave + 8 * g;
+            if (t < TILES) {
+                const int sb = (t / (T * T)) * M, r0 = sb + ((t / T) % T) * 16, c0 = sb + (t % T) * 16;
+#pragma unroll
+                for (int k = 0; k < M; k += 4) {
+                    const double av = S.Q[S.col[sb + k + lk] * DCB_LD + r0 + l16];
+                    acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + k + lk], acc[g]);
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < PER; ++g) {
+            const int t = wave + 8 * g;
+            if (t < TILES) {
+                const int sb = (t / (T * T)) * M, r0 = sb + ((t / T) % T) * 16, c0 = sb + (t % T) * 16;
+                double* o = S.Q + S.np[c0 + l16] * DCB_LD + r0 + lk;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[4 * v] = acc[g][v];
+            }
+        }
+    } else {
+        double out = 0.0;
+        if (l < M) {
+#pragma unroll
+            for (int j = 0; j < M; ++j)
+                out = __builtin_fma(S.Q[S.col[base + j] * DCB_LD + base + l], S.U[i * DCB_LDU + j], out);
+        }
+        __syncthreads();
+        if (l < M) S.Q[S.np[i] * DCB_LD + base + l] = out;
+    }
+    __syncthreads();
+}
+
+// Work-groups 0 .. N/64 - 1: a diagonal block each. The N/64 after them form the triangular factors of the reduction's
+// blocks of reflectors meanwhile (a wave each; wy_factor), which the back-transformation needs.
+template <int J>
+__global__ __launch_bounds__(512, 1) void dc_block_kernel(const double* __restrict__ dT, const double* __restrict__ eT,
+                                                          double* __restrict__ dO, double* __restrict__ Z,
+                                                          const double* __restrict__ V, const double* __restrict__ tauT,
+                                                          int n, double* __restrict__ Tw) {
+    constexpr int N = 64 * J;
+    if (blockIdx.x >= J) {
+        const int b = (blockIdx.x - J) * 8 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (b * WY <= n - 2) wy_factor<J>(V, tauT, b, n, threadIdx.x & 63, Tw);
+        return;
+    }
+    extern __shared__ char dc_lds[];
+    DcBlockLds& S = *reinterpret_cast<DcBlockLds*>(dc_lds);
+    const int tid = threadIdx.x, i = tid >> 3, l = tid & 7;
+    const int b0 = blockIdx.x * 64;
+    const double tol = dc_tolerance(dT, eT, N, tid & 63);
+    for (int r = l; r < 64; r += 8) S.Q[i * DCB_LD + r] = 0.0;
+    __syncthreads();
+    if (l == 0) {
+        const int g = b0 + i, g0 = b0 + (i & ~1);
+        S.e[i] = finite_or_zero(eT[g]);
+        // every cut between pairs is torn: both its neighbours lose |e|; the pair itself is a 2 x 2 eigenproblem
+        const double a = finite_or_zero(dT[g0]) - (g0 > 0 ? fabs(finite_or_zero(eT[g0 - 1])) : 0.0);
+        const double c = finite_or_zero(dT[g0 + 1]) - fabs(finite_or_zero(eT[g0 + 1]));
+        const double b = finite_or_zero(eT[g0]);
+        double t = 0.0;
+        if (b != 0.0) {
+            const double z = (c - a) / (2.0 * b);
+            t = __builtin_copysign(1.0, z) / (fabs(z) + __builtin_sqrt(1.0 + z * z));
+        }
+        const double cc = 1.0 / __builtin_sqrt(1.0 + t * t), ss = t * cc;
+        const double l1 = a - t * b, l2 = c + t * b;  // vectors (cc, -ss) and (ss, cc)
+        const bool first = ((i & 1) == 0) == (l1 <= l2);  // this index takes l1
+        S.d[i] = first ? l1 : l2;
+        S.Q[i * DCB_LD + (i & ~1)] = first ? cc : ss;
+        S.Q[i * DCB_LD + (i | 1)] = first ? -ss : cc;
+    }
+    __syncthreads();
+    dc_level<4>(S, tid, tol);
+    dc_level<8>(S, tid, tol);
+    dc_level<16>(S, tid, tol);
+    dc_level<32>(S, tid, tol);
+    dc_level<64>(S, tid, tol);
     if (l == 0) dO[b0 + i] = S.d[i];
     for (int c = tid >> 6; c < 64; c += 8) Z[(int64_t)(b0 + c) * N + b0 + (tid & 63)] = S.Q[c * DCB_LD + (tid & 63)];
 }
@@ -531,7 +607,7 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
             zsum += zj[e];
         }
         zsum = lane_sum<64>(zsum);
-        secular_root<64>(K, q, lane, dj, zj, w.dk[base + q], q + 1 < K ? w.dk[base + q + 1] : 0.0, zsum, org, tau);
+        secular_root<64, 8>(K, q, lane, dj, zj, w.dk[base + q], q + 1 < K ? w.dk[base + q + 1] : 0.0, zsum, org, tau);
         val = finite_or_zero(org + tau);
     }
     if (lane == 0) {
@@ -568,7 +644,7 @@ __global__ __launch_bounds__(256) void dc_weights_kernel(int m, DcWork w, double
             og[e] = j < K ? w.org[base + j] : 0.0;
             ta[e] = j < K ? w.tau[base + j] : 0.0;
         }
-        zz = __builtin_copysign(secular_z<64>(K, q, lane, w.dk[base + q], di, og, ta), w.zk[base + q]);
+        zz = __builtin_copysign(secular_z<64, 8>(K, q, lane, w.dk[base + q], di, og, ta), w.zk[base + q]);
     }
     if (lane == 0) {
         w.zh[base + q] = zz;
@@ -577,21 +653,18 @@ __global__ __launch_bounds__(256) void dc_weights_kernel(int m, DcWork w, double
     }
 }
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-// fp64 matrix-core step acc(16x16) += a(16x4) b(4x16): lane l supplies a[l%16][l/16] and b[l/16][l%16];
-// acc element v of lane l is row 4v + l/16, column l%16.
-__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-}
-
 // Z_out(:, npos_q) = Z_in(:, survivors) u_q, u_q(j) = zh_j / (d_j - lambda_q) normalised; deflated columns are copied.
 // grid (m / 32 column tiles, m / 64 row tiles, sub-problems), 256 threads; a wave owns 16 rows x 32 columns. A row tile
-// of the left (right) half only meets the survivors that live there.
+// of the left (right) half only meets the survivors that live there. Poles, weights and column numbers are brought to LDS
+// once (chasing the column list through global memory in every step made the kernel 60 us at m = 512), the columns of
+// Z_in are requested a step ahead, and the entries of u are formed on the way into LDS.
 __global__ __launch_bounds__(256) void dc_vectors_kernel(const double* __restrict__ Zin, double* __restrict__ Zout, int N,
                                                          int m, DcWork w) {
     constexpr int KT = 32, LDA = 72, LDB = 40;
     __shared__ double As[KT * LDA], Bs[KT * LDB];
-    __shared__ double inv[32];
+    __shared__ double inv[32], og[32], ta[32];
+    __shared__ double dk[512], zh[512];
+    __shared__ int lj[512], lc[512];  // survivors of this row tile's half: index, column
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int base = blockIdx.z * m, half = m >> 1;
     const int q0 = blockIdx.x * 32, r0 = blockIdx.y * 64;
@@ -601,44 +674,64 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(const double* __restric
     const int* list = w.half + base + (dense || left ? 0 : k1);
     const int len = dense ? K : (left ? k1 : K - k1);
     if (q0 < K) {
-        {   // norms of the tile's vectors: 8 lanes per column
-            const int c = tid >> 3, l = tid & 7, q = q0 + c;
-            double nn = 0.0;
-            if (q < K) {
-                const double og = w.org[base + q], ta = w.tau[base + q];
-                for (int j = l; j < K; j += 8) {
-                    const double u = w.zh[base + j] * rcp64((w.dk[base + j] - og) - ta);
-                    nn = __builtin_fma(u, u, nn);
-                }
+        for (int j = tid; j < m; j += 256) {
+            dk[j] = j < K ? w.dk[base + j] : 1e30;
+            zh[j] = j < K ? w.zh[base + j] : 0.0;
+            if (j < len) {
+                const int q = list[j];
+                lj[j] = q;
+                lc[j] = w.col[base + q];
             }
-            nn = lane_sum<8>(nn);
+        }
+        if (tid < 32) {
+            og[tid] = w.org[base + q0 + tid];
+            ta[tid] = w.tau[base + q0 + tid];
+        }
+        __syncthreads();
+        double av[8];
+        auto fetch = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int kk = k0 + u * 4 + wave;
+                av[u] = kk < len ? Zin[(int64_t)lc[kk] * N + base + r0 + lane] : 0.0;
+            }
+        };
+        fetch(0);
+        {   // norms of the tile's vectors: 8 lanes per column
+            const int c = tid >> 3, l = tid & 7;
+            const double o = og[c], t = ta[c];
+            double n0 = 0.0, n1 = 0.0;
+            for (int j = l; j < m; j += 16) {
+                const double u0 = zh[j] * rcp64((dk[j] - o) - t), u1 = zh[j + 8] * rcp64((dk[j + 8] - o) - t);
+                n0 = __builtin_fma(u0, u0, n0);
+                n1 = __builtin_fma(u1, u1, n1);
+            }
+            const double nn = lane_sum<8>(n0 + n1);
             if (l == 0) inv[c] = nn > 0.0 ? rcp64(__builtin_sqrt(nn)) : 0.0;
         }
-        const int l16 = lane & 15, lk = lane >> 4;
+        const int l16 = lane & 15, lk = lane >> 4, bc = tid & 31;
         f64x4 acc[2] = {f64x4{0.0, 0.0, 0.0, 0.0}, f64x4{0.0, 0.0, 0.0, 0.0}};
         for (int k0 = 0; k0 < len; k0 += KT) {
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int kk = u * 4 + wave;
-                As[kk * LDA + lane] = k0 + kk < len ? Zin[(int64_t)w.col[base + list[k0 + kk]] * N + base + r0 + lane] : 0.0;
-            }
+            for (int u = 0; u < 8; ++u) As[(u * 4 + wave) * LDA + lane] = av[u];
+            fetch(k0 + KT);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int e = u * 256 + tid, kk = e >> 5, c = e & 31, q = q0 + c;
+                const int kk = u * 8 + (tid >> 5);
                 double v = 0.0;
-                if (k0 + kk < len && q < K) {
-                    const int j = list[k0 + kk];
-                    v = w.zh[base + j] * rcp64((w.dk[base + j] - w.org[base + q]) - w.tau[base + q]) * inv[c];
+                if (k0 + kk < len && q0 + bc < K) {
+                    const int j = lj[k0 + kk];
+                    v = zh[j] * rcp64((dk[j] - og[bc]) - ta[bc]) * inv[bc];
                 }
-                Bs[kk * LDB + c] = v;
+                Bs[kk * LDB + bc] = v;
             }
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < KT; k += 4) {
-                const double av = As[(k + lk) * LDA + wave * 16 + l16];
+                const double a = As[(k + lk) * LDA + wave * 16 + l16];
 #pragma unroll
-                for (int t = 0; t < 2; ++t) acc[t] = mfma64(av, Bs[(k + lk) * LDB + t * 16 + l16], acc[t]);
+                for (int t = 0; t < 2; ++t) acc[t] = mfma64(a, Bs[(k + lk) * LDB + t * 16 + l16], acc[t]);
             }
         }
 #pragma unroll
@@ -662,12 +755,25 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(const double* __restric
     }
 }
 
-// T = Z D Z^T: eigenvalues ascending in dI, eigenvectors in the columns of Z (buffer dc_result(N) of either).
-hipError_t launch_dc(const EigWork& w, int N, hipStream_t st) {
-    if (hipError_t e = ensure_dynamic_lds((const void*)dc_block_kernel, (int)sizeof(DcBlockLds)); e != hipSuccess) return e;
+template <int J>
+static hipError_t launch_dc_block(const EigWork& w, int n, hipStream_t st) {
+    if (hipError_t e = ensure_dynamic_lds((const void*)dc_block_kernel<J>, (int)sizeof(DcBlockLds)); e != hipSuccess) return e;
+    hipLaunchKernelGGL(dc_block_kernel<J>, dim3(2 * J), dim3(512), sizeof(DcBlockLds), st, w.dT, w.eT, w.dI[0], w.Z[0], w.V,
+                       w.tauT, n, w.Tw);
+    return hipGetLastError();
+}
+
+// T = Z D Z^T: eigenvalues ascending in dI, eigenvectors in the columns of Z (buffer dc_result(N) of either). n: rows in use.
+hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
+    hipError_t e = hipErrorInvalidValue;
+    switch (N / 64) {
+        case 1: e = launch_dc_block<1>(w, n, st); break;
+        case 2: e = launch_dc_block<2>(w, n, st); break;
+        case 4: e = launch_dc_block<4>(w, n, st); break;
+        case 8: e = launch_dc_block<8>(w, n, st); break;
+    }
+    if (e != hipSuccess) return e;
     int cur = 0;
-    hipLaunchKernelGGL(dc_block_kernel, dim3(N / 64), dim3(512), sizeof(DcBlockLds), st, w.dT, w.eT, N, w.dI[0], w.Z[0],
-                       w.xch);
     for (int m = 128; m <= N; m *= 2) {
         const int S = N / m;
         hipLaunchKernelGGL(dc_deflate_kernel, dim3(S), dim3(512), 0, st, w.dT, w.eT, N, m, w.dI[cur], w.Z[cur], w.dc);

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void coeffs_kernel(const double* __restrict__ 
 
 hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st) {
     if (hipError_t e = launch_tridiag(w, NP, m0, n, st); e != hipSuccess) return e;
-    if (hipError_t e = launch_dc(w, NP, st); e != hipSuccess) return e;
+    if (hipError_t e = launch_dc(w, NP, n, st); e != hipSuccess) return e;
     return launch_tri_back(w, NP, m0, n, count, st);
 }
 

@@ -11,7 +11,11 @@
 //                 the L2 they share (tri_many_kernel).
 // Every wave carries the vectors of the step (column, reflector, product) redundantly, so a step has one exchange and
 // no other synchronisation.
+#include <mutex>
+#include <type_traits>
+
 #include "sage_internal.h"
+#include "fd_wy.h"
 #include "wave_ops.h"
 
 namespace sage {
@@ -31,38 +35,57 @@ __device__ __forceinline__ double wave_max_diag(const double* __restrict__ C, in
     return m;
 }
 
-// The Householder vector of a column: x = (alpha; rest), rest2 = |rest|^2. H x = beta e_1, H = I - tau v v^T,
-// v = (1; scale * rest). A rest below 1e-30 of the matrix counts as zero (H = I, tau = 0): smaller ones, which a matrix of
-// low rank leaves, would lose their digits to underflow in |rest|^2 and H its orthogonality.
+// The reflector of a column (alpha; rest), rest2 = |rest|^2: H = I - tau v v^T, v = (v1; rest) takes it to (beta; 0). The
+// vector is not normalised: the matrix-vector product of a step can then start from the column itself, while the norm
+// is still being formed. A rest below 1e-30 of the matrix counts as zero (H = I): smaller ones, which a matrix of low
+// rank leaves, would lose their digits to underflow in |rest|^2 and H its orthogonality.
 constexpr double TRI_DROP2 = 1e-60;
-__device__ __forceinline__ void householder(double alpha, double rest2, double& beta, double& tau, double& scale) {
+__device__ __forceinline__ void householder(double alpha, double rest2, double& beta, double& tau, double& v1) {
     if (rest2 > TRI_DROP2) {
-        const double nrm = __builtin_sqrt(__builtin_fma(alpha, alpha, rest2));
+        const double s = __builtin_fma(alpha, alpha, rest2);
+        double y = __builtin_amdgcn_rsq(s);
+        y = __builtin_fma(y * 0.5, __builtin_fma(-s * y, y, 1.0), y);
+        y = __builtin_fma(y * 0.5, __builtin_fma(-s * y, y, 1.0), y);
+        double nrm = s * y;
+        nrm = __builtin_fma(__builtin_fma(-nrm, nrm, s), 0.5 * y, nrm);
+        const double m = fabs(alpha) + nrm;
         beta = alpha >= 0.0 ? -nrm : nrm;
-        tau = (beta - alpha) * rcp64(beta);
-        scale = rcp64(alpha - beta);
+        v1 = alpha >= 0.0 ? m : -m;
+        tau = rcp64(nrm * m);
     } else {
         beta = alpha;
         tau = 0.0;
-        scale = 0.0;
+        v1 = 0.0;
     }
+}
+// Orders this wave's LDS traffic before the barrier and nothing else: __syncthreads() would also wait for the global
+// stores in flight.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // ---- n = 64 J, J = 1, 2: one work-group ---------------------------------------------------------------------------
-// Wave w owns the columns of the 8-column blocks w, w + 4, ... Step k (column k known to every wave as x):
-// reflector v; own columns j > k: a_j -= v' w'_j + w' v'_j (primes: step k - 1), partial product sum_j a_j v_j; the
-// owner of column k + 1 publishes it; one barrier; p = tau sum of the partials, w = p + alpha v, and
-// x <- column k + 1 - v w_{k+1} - w v_{k+1} is the next column.
+// Waves 0..3 hold the matrix as 16 x 16 threads of R x R elements (rows rs + 16 t, columns cs + 16 u); wave 4 carries the
+// vectors, wave 5 stores the reflectors. Step k, with x = column k below row k + 1 and v', w' of step k - 1 in LDS:
+//   waves 0..3: a -= v' w'^T + w' v'^T, q = a x (summed over the 16 lanes of a row), c = column k + 1;
+//   wave 4 meanwhile: the reflector (tau, v1);                                                                  barrier
+//   wave 4: p = tau (q + v1 c), w = p - tau/2 (p.v) v, next column c - v w_{k+1} - w v1;                        barrier
+// A step is a chain of latencies (sum over a wave 160 cycles, LDS round trip 70, reductions over 16 lanes 105), at J = 2
+// also 3 x 64 fp64 operations a thread while nothing is done yet: finished rows and columns are left out in quarters.
+struct __attribute__((aligned(16))) Pair { double a, b; };
+
 template <int J>
-__global__ __launch_bounds__(256, 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
+__global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
                                                          double* __restrict__ dT, double* __restrict__ eT,
                                                          double* __restrict__ tauT, double* __restrict__ V,
                                                          double* __restrict__ stat) {
-    constexpr int N = 64 * J, W = 4, NB = N / (8 * W);  // NB blocks of 8 columns per wave
-    __shared__ double pbuf[2][W][N];                    // partial products
-    __shared__ double cbuf[2][N];                       // next column
-    __shared__ __attribute__((aligned(16))) double vs[W][2][N];  // each wave's own copies of v and w, by parity
-    __shared__ __attribute__((aligned(16))) double ws[W][2][N];
+    constexpr int N = 64 * J, R = N / 16;
+    __shared__ Pair vw[N], wx[N], qc[N];  // {v', w'}, {w', x} and {q, c}
+    __shared__ double vl[2][N];    // v, by step parity (for wave 5)
+    __shared__ double v1s;         // v1' of step k - 1: v' is the x before it with v1' in place k
+    __shared__ double dl[N], el[N], tl[N];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -70,412 +93,573 @@ __global__ __launch_bounds__(256, 1) void tri_one_kernel(const double* __restric
     const int ex = tri_exponent(md);
     const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
     if (tid == 0) stat[0] = (double)ex;
+    auto element = [&](int r, int c) __attribute__((always_inline)) {
+        return (r < n && c < n) ? C[(int64_t)active_index(c, m0, LP) * NP + active_index(r, m0, LP)] * sc0 : 0.0;
+    };
 
-    double a[NB][8][J];
-    int mrow[J];
+    if (wave < 4) {
+        const int rs = wave * 4 + (lane >> 4), cs = lane & 15;
+        double a[R][R], vc[R];  // vc: the x of the step before at the columns
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) a[t][u] = element(rs + 16 * t, cs + 16 * u);
+            vc[t] = 0.0;
+        }
+        const bool odd = lane & 1, hi = lane & 2;
+        lds_barrier();
+        for (int k = 0; k < n - 1; ++k) {
+            auto pass = [&](auto t0c) __attribute__((always_inline)) {
+                constexpr int T0 = decltype(t0c)::value;  // rows and columns below 16 T0 are done with
+                double q[R], wc[R], xc[R];
+                const double v1 = v1s;
+#pragma unroll
+                for (int u = T0; u < R; ++u) {
+                    const Pair e = wx[cs + 16 * u];
+                    wc[u] = e.a;
+                    xc[u] = e.b;
+                    vc[u] = cs + 16 * u == k ? v1 : vc[u];
+                }
+#pragma unroll
+                for (int t = T0; t < R; ++t) {
+                    const Pair e = vw[rs + 16 * t];
+                    double q0 = 0.0;
+#pragma unroll
+                    for (int u = T0; u < R; ++u) a[t][u] = __builtin_fma(-e.b, vc[u], a[t][u]);
+#pragma unroll
+                    for (int u = T0; u < R; ++u) a[t][u] = __builtin_fma(-e.a, wc[u], a[t][u]);
+#pragma unroll
+                    for (int u = T0; u < R; ++u) q0 = __builtin_fma(a[t][u], xc[u], q0);
+                    q[t] = q0;
+                }
+#pragma unroll
+                for (int u = T0; u < R; ++u) vc[u] = xc[u];
+                if (cs == ((k + 1) & 15)) {
+#pragma unroll
+                    for (int u = T0; u < R; ++u)
+                        if ((k + 1) >> 4 == u) {
+#pragma unroll
+                            for (int t = T0; t < R; ++t) {
+                                double c = a[t][u];
+                                asm volatile("" : "+v"(c));  // keeps the cases apart: merged, they index a[] by u at
+                                qc[rs + 16 * t].b = c;       // run time, which moves the matrix to scratch memory
+                            }
+                        }
+                }
+                // over the 16 lanes of a row: four (two) rows at a time, told apart by the low bits of the lane, then the
+                // ring of what is left
+                constexpr int Q4 = (R - T0) / 4 * 4;
+#pragma unroll
+                for (int g = T0; g < T0 + Q4; g += 4) {
+                    double t0 = odd ? q[g + 1] : q[g], o0 = odd ? q[g] : q[g + 1];
+                    double t1 = odd ? q[g + 3] : q[g + 2], o1 = odd ? q[g + 2] : q[g + 3];
+                    t0 += dpp_move<DPP_XOR1>(o0);
+                    t1 += dpp_move<DPP_XOR1>(o1);
+                    double t = hi ? t1 : t0, o = hi ? t0 : t1;
+                    t += dpp_move<DPP_XOR2>(o);
+                    t += dpp_move<0x124>(t);  // row_ror 4
+                    t += dpp_move<0x128>(t);  // row_ror 8
+                    if (cs < 4) qc[rs + 16 * (g + cs)].a = t;
+                }
+#pragma unroll
+                for (int g = T0 + Q4; g < R; g += 2) {
+                    double t = odd ? q[g + 1] : q[g], o = odd ? q[g] : q[g + 1];
+                    t += dpp_move<DPP_XOR1>(o);
+                    t += dpp_move<DPP_XOR2>(t);
+                    t += dpp_move<0x124>(t);
+                    t += dpp_move<0x128>(t);
+                    if (cs < 2) qc[rs + 16 * (g + cs)].a = t;
+                }
+            };
+            const int done = k / (N / 4);  // quarters of the matrix that are finished (rows and columns <= k - 1 are)
+            if constexpr (R == 8) {
+                if (done == 0) pass(std::integral_constant<int, 0>{});
+                else if (done == 1) pass(std::integral_constant<int, 2>{});
+                else if (done == 2) pass(std::integral_constant<int, 4>{});
+                else pass(std::integral_constant<int, 6>{});
+            } else {
+                if (done < 2) pass(std::integral_constant<int, 0>{});
+                else pass(std::integral_constant<int, 2>{});
+            }
+            lds_barrier();
+            lds_barrier();
+        }
+        return;
+    }
+
+    if (wave == 5) {
+        lds_barrier();
+        for (int k = 0; k < n - 1; ++k) {
+            lds_barrier();
+#pragma unroll
+            for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = vl[k & 1][lane + 64 * j];
+            lds_barrier();
+        }
+        // the padding: decoupled, below every eigenvalue of a Gram matrix
+        for (int i = lane; i < N; i += 64) {
+            dT[i] = i < n - 1 ? dl[i] : -1.0;
+            eT[i] = i < n - 1 ? el[i] : 0.0;
+            tauT[i] = i < n - 1 ? tl[i] : 0.0;
+        }
+        if (lane == 0) dT[n - 1] = dl[n - 1];
+        for (int k = n - 1; k % WY != 0; ++k)  // the rows of V that complete the last block of reflectors
+#pragma unroll
+            for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = 0.0;
+        return;
+    }
+
+    // ---- wave 4
+    double x[J], vf[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         const int r = lane + 64 * j;
-        mrow[j] = r < n ? active_index(r, m0, LP) : -1;
+        x[j] = element(r, 0);
+        qc[r] = Pair{0.0, 0.0};
+        vw[r] = Pair{0.0, 0.0};
+        wx[r] = Pair{0.0, r > 1 ? x[j] : 0.0};
     }
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int col = 8 * (wave + W * b) + q;
-            const double* src = C + (int64_t)active_index(col < n ? col : 0, m0, LP) * NP;
-#pragma unroll
-            for (int j = 0; j < J; ++j) a[b][q][j] = (col < n && mrow[j] >= 0) ? src[mrow[j]] * sc0 : 0.0;
-        }
-    double x[J], v[J], w[J];
-    {
-        const double* src = C + (int64_t)active_index(0, m0, LP) * NP;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            x[j] = mrow[j] >= 0 ? src[mrow[j]] * sc0 : 0.0;
-            v[j] = 0.0;
-            w[j] = 0.0;
-        }
+    double xk = element(0, 0), xk1 = element(1, 0);
+    if (lane == 0) {
+        v1s = 0.0;
+        if (n == 1) dl[0] = xk;
     }
-    double xk = C[(int64_t)active_index(0, m0, LP) * NP + active_index(0, m0, LP)] * sc0;
-    double xk1 = n > 1 ? C[(int64_t)active_index(0, m0, LP) * NP + active_index(1, m0, LP)] * sc0 : 0.0;
-
+    lds_barrier();
     for (int k = 0; k < n - 1; ++k) {
-        const int par = k & 1;
         double r2 = 0.0;
 #pragma unroll
-        for (int j = 0; j < J; ++j) r2 = __builtin_fma(lane + 64 * j > k + 1 ? x[j] : 0.0, x[j], r2);
+        for (int j = 0; j < J; ++j) {
+            vf[j] = lane + 64 * j > k + 1 ? x[j] : 0.0;
+            r2 = __builtin_fma(vf[j], vf[j], r2);
+        }
         r2 = lane_sum<64>(r2);
-        double beta, tau, scale;
-        householder(xk1, r2, beta, tau, scale);
-        const double v1 = r2 > TRI_DROP2 ? 1.0 : 0.0;
-        double vn[J];
+        double beta, tau, v1;
+        householder(xk1, r2, beta, tau, v1);
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int r = lane + 64 * j;
-            vn[j] = r > k + 1 ? x[j] * scale : (r == k + 1 ? v1 : 0.0);
-            vs[wave][par][r] = vn[j];
+            vf[j] = r == k + 1 ? v1 : vf[j];
+            vl[k & 1][r] = vf[j];
         }
-        if (tid == 0) {
-            dT[k] = xk;
-            eT[k] = beta;
-            tauT[k] = tau;
+        if (lane == 0) {
+            dl[k] = xk;
+            el[k] = beta;
+            tl[k] = tau;
         }
-        if (wave == (k & 3)) {
-#pragma unroll
-            for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = vn[j];
-        }
-        asm volatile("" ::: "memory");
-        double acc[J];
-#pragma unroll
-        for (int j = 0; j < J; ++j) acc[j] = 0.0;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c0 = 8 * (wave + W * b);
-            if (c0 + 7 > k && c0 < n) {
-                double vj[8], vp[8], wp[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    vj[q] = vs[wave][par][c0 + q];
-                    vp[q] = k > 0 ? vs[wave][par ^ 1][c0 + q] : 0.0;
-                    wp[q] = k > 0 ? ws[wave][par ^ 1][c0 + q] : 0.0;
-                }
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-#pragma unroll
-                    for (int j = 0; j < J; ++j) {
-                        a[b][q][j] = __builtin_fma(-v[j], wp[q], __builtin_fma(-w[j], vp[q], a[b][q][j]));
-                        acc[j] = __builtin_fma(a[b][q][j], vj[q], acc[j]);
-                    }
-                if (k + 1 >= c0 && k + 1 < c0 + 8) {
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        if (c0 + q == k + 1) {
-#pragma unroll
-                            for (int j = 0; j < J; ++j) cbuf[par][lane + 64 * j] = a[b][q][j];
-                        }
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < J; ++j) pbuf[par][wave][lane + 64 * j] = acc[j];
-        __syncthreads();
-        double p[J], c[J];
-        double dot = 0.0;
+        lds_barrier();
+        double p[J], c[J], dot = 0.0;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int r = lane + 64 * j;
-            p[j] = tau * ((pbuf[par][0][r] + pbuf[par][1][r]) + (pbuf[par][2][r] + pbuf[par][3][r]));
-            c[j] = cbuf[par][r];
-            if (r <= k) p[j] = 0.0;
-            dot = __builtin_fma(p[j], vn[j], dot);
+            const Pair e = qc[r];
+            c[j] = e.b;
+            p[j] = r > k ? tau * __builtin_fma(v1, e.b, e.a) : 0.0;
+            dot = __builtin_fma(p[j], vf[j], dot);
         }
-        const int r2i = k + 2 < n ? k + 2 : k + 1;
-        const double p1 = tau * ((pbuf[par][0][k + 1] + pbuf[par][1][k + 1]) + (pbuf[par][2][k + 1] + pbuf[par][3][k + 1]));
-        const double p2 = tau * ((pbuf[par][0][r2i] + pbuf[par][1][r2i]) + (pbuf[par][2][r2i] + pbuf[par][3][r2i]));
-        const double c1 = cbuf[par][k + 1], c2 = cbuf[par][r2i], v2 = vs[wave][par][r2i];
+        const Pair e1 = qc[k + 1];
         dot = lane_sum<64>(dot);
         const double al = -0.5 * tau * dot;
-        const double w1 = __builtin_fma(al, v1, p1), w2 = __builtin_fma(al, v2, p2);
+        const double w1 = __builtin_fma(al, v1, tau * __builtin_fma(v1, e1.b, e1.a));
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int r = lane + 64 * j;
-            v[j] = vn[j];
-            w[j] = __builtin_fma(al, vn[j], p[j]);
-            ws[wave][par][r] = w[j];
-            x[j] = __builtin_fma(-v[j], w1, __builtin_fma(-w[j], v1, c[j]));
+            const double w = __builtin_fma(al, vf[j], p[j]);
+            x[j] = __builtin_fma(-vf[j], w1, __builtin_fma(-w, v1, c[j]));
+            vw[r] = Pair{vf[j], w};
+            wx[r] = Pair{w, r > k + 2 ? x[j] : 0.0};
         }
-        xk = __builtin_fma(-2.0 * v1, w1, c1);
-        xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, c2));
-    }
-    if (tid == 0) {
-        dT[n - 1] = xk;
-        eT[n - 1] = 0.0;
-        tauT[n - 1] = 0.0;
-    }
-    // the padding: decoupled, below every eigenvalue of a Gram matrix
-    for (int i = n + tid; i < N; i += 256) {
-        dT[i] = -1.0;
-        eT[i] = 0.0;
-        tauT[i] = 0.0;
+        xk = __builtin_fma(-2.0 * v1, w1, e1.b);
+        if (lane == 0) {
+            v1s = v1;
+            if (k == n - 2) dl[n - 1] = xk;
+        }
+        lds_barrier();
+        xk1 = read_lane((J == 1 || k + 2 < 64) ? x[0] : x[J - 1], (k + 2) & 63);
     }
 }
 
 // ---- n = 64 J, J = 4, 8: n / 16 work-groups on one XCD ------------------------------------------------------------
-// Exchange buffers: [3][2][N] doubles (ring slot, product p / next column c), every entry the EMPTY pattern before the
-// launch. An entry is published by a relaxed agent-scope store and picked up by spinning on it with relaxed agent-scope
-// loads until it is not EMPTY: no flags, no fences, an entry carries its own validity. Ring slot k % 3 serves step k.
-// Once a work-group has all of step k it knows that everyone has finished reading step k - 1, so it sets its own
-// entries of slot (k + 2) % 3 = (k - 1) % 3 back to EMPTY, waits for those stores before it publishes step k + 1, and
-// nobody reads that slot before having all of step k + 1.
-// A spin ends after SPIN_LIMIT polls (seconds; the partners are resident or about to be, whatever else the GPU runs
+// As above, but a wave owns 4 whole columns, carries all vectors itself and sums its products over the lanes, and q and c go through the L2 the
+// work-groups share. An exchanged value is a 16-byte entry {low word, tag, high word, tag}; the tag (solve number and step)
+// makes each 8-byte half carry its own validity, so there are no flags, no fences and nothing to clear: a reader polls an
+// entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough: once a
+// work-group has all of step k + 1, everyone has finished reading step k.
+// Stores: the L1 is write-through, so a plain store reaches the XCD's L2 (local = 1). Where the work-groups cannot be
+// relied on to sit on one XCD (launch_tridiag checks the mapping once) they are device-scope stores instead, which go on
+// to memory: 3.4 us per step instead of 1.9 us at n = 512.
+// Waves 0..3 compute and publish, waves 4..7 only poll and hand over through LDS: loads and stores of a wave retire in
+// order, so one that did both would wait, with every poll, for its own stores. They wait for c first, which is out before
+// the products are formed, then for q: a poll of one vector takes 550 cycles, of both 830.
+// A poll loop ends after SPIN_LIMIT rounds (seconds; the partners are resident or about to be, whatever else the GPU runs
 // ends by itself): the kernel then gives up, reports in stat[1], and every further wait returns at once.
-constexpr long long EMPTY = -1LL;  // a NaN no arithmetic produces (published NaNs are replaced by the default one)
-constexpr int SPIN_LIMIT = 1 << 23;
+constexpr int SPIN_LIMIT = 1 << 22;
 
-__device__ __forceinline__ void put(long long* p, double v) {
-    long long u = __double_as_longlong(v);
-    if (v != v) u = 0x7FF8000000000000LL;
-    __hip_atomic_store(p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <bool LOCAL>
+__device__ __forceinline__ void put_entry(u32x4* p, double v, unsigned tag) {
+    const long long u = __double_as_longlong(v);
+    const u32x4 e = {(unsigned)u, tag, (unsigned)(u >> 32), tag};
+    if constexpr (LOCAL) {
+        *p = e;
+        asm volatile("" ::: "memory");  // stays here
+    } else {
+        // (s_nop: the data registers of a 16-byte store must not be written in the next cycle, which the compiler only
+        // takes care of for stores of its own)
+        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(e) : "memory");
+    }
 }
-__device__ __forceinline__ long long get(const long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void wait_stores() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+__device__ __forceinline__ bool fresh(const u32x4& e, unsigned tag) { return e[1] == tag && e[3] == tag; }
+__device__ __forceinline__ double entry_value(const u32x4& e) {
+    return __longlong_as_double(((long long)e[2] << 32) | e[0]);
 }
 
-template <int J>
-__global__ __launch_bounds__(256, 1) void tri_many_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
+template <int J, bool LOCAL>
+__global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
-                                                          double* __restrict__ stat, long long* __restrict__ xch,
-                                                          int xcd) {
-    constexpr int N = 64 * J, NW = N / 4;  // NW waves in all, 4 columns each: gw, gw + NW, gw + 2 NW, gw + 3 NW
-    constexpr int PT = N / 256;            // entries per thread and vector of the exchange
+                                                          double* __restrict__ stat, u32x4* __restrict__ xch,
+                                                          unsigned tag0, int xcd) {
+    constexpr int N = 64 * J, NW = N / 4;  // NW waves in all
     if ((int)(blockIdx.x & 7) != xcd) return;  // consecutive work-groups go to consecutive XCDs
     __builtin_amdgcn_s_setprio(3);
-    __shared__ double pb[2][N], cb[2][N];
+    __shared__ Pair qc[2][N];  // {q, c} by step parity
     __shared__ double vs[4][N];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg = blockIdx.x >> 3;
-    const int gw = wg * 4 + wave;
 
+    if (wave >= 4) {  // ---- pollers: entries t, t + 256, .. of c and q
+        constexpr int PT = N / 256;
+        const int t = tid & 255;
+        int spins = SPIN_LIMIT;
+        for (int k = 0; k < n - 1; ++k) {
+            const int par = k & 1;
+            const unsigned tag = tag0 + (unsigned)k;
+            // all of this thread's entries of a vector in one round trip; it is done with the entries of rows <= k
+            auto poll = [&](const u32x4* src, double (&val)[PT]) __attribute__((always_inline)) {
+                u32x4 e[PT];
+#pragma unroll
+                for (int u = 0; u < PT; ++u) e[u] = u32x4{0u, 0u, 0u, 0u};
+                if (t + 256 * (PT - 1) > k && t < n) {
+                    bool more;
+                    do {
+                        if constexpr (PT == 2) {
+                            asm volatile(
+                                "global_load_dwordx4 %0, %2, off sc1\n\t"
+                                "global_load_dwordx4 %1, %3, off sc1\n\t"
+                                "s_waitcnt vmcnt(0)"
+                                : "=&v"(e[0]), "=&v"(e[PT - 1])
+                                : "v"(src), "v"(src + 256)
+                                : "memory");
+                        } else {
+                            asm volatile(
+                                "global_load_dwordx4 %0, %1, off sc1\n\t"
+                                "s_waitcnt vmcnt(0)"
+                                : "=&v"(e[0])
+                                : "v"(src)
+                                : "memory");
+                        }
+                        more = false;
+#pragma unroll
+                        for (int u = 0; u < PT; ++u) {
+                            const int i = t + 256 * u;
+                            more = more || (i > k && i < n && !fresh(e[u], tag));
+                        }
+                        if (more && --spins <= 0) {
+                            stat[1] = 1.0;
+                            spins = 1;  // every further wait gives up after one round
+                            more = false;
+                        }
+                    } while (more);
+                }
+#pragma unroll
+                for (int u = 0; u < PT; ++u) {
+                    const int i = t + 256 * u;
+                    val[u] = i > k && i < n ? entry_value(e[u]) : 0.0;
+                }
+            };
+            const u32x4* const qx = xch + par * 2 * N + t;
+            double cv[PT], qv[PT];
+            poll(qx + N, cv);
+            poll(qx, qv);
+#pragma unroll
+            for (int u = 0; u < PT; ++u) qc[par][t + 256 * u] = Pair{qv[u], cv[u]};
+            lds_barrier();
+        }
+        return;
+    }
+
+    // Wave gw owns the columns of lane gw % 64: cl + 64 (H + s J / 4), s < 4, H = gw / 64 < J / 4. So the entries of v and w at
+    // its own columns are in one lane of its own registers.
+    const int gw = wg * 4 + wave, cl = gw & 63;
     const double md = wave_max_diag(C, NP, lane);
     const int ex = tri_exponent(md);
     const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
     if (wg == 0 && tid == 0) stat[0] = (double)ex;
 
-    double a[4][J], x[J], v[J], w[J];
-    double vcol[4], wcol[4];
-    {
-        int mrow[J];
+    auto reduce = [&](auto hc) __attribute__((always_inline)) {
+        constexpr int H = decltype(hc)::value, ST = J / 4;  // register index of column s: H + ST * s
+        double a[4][J], x[J], v[J], w[J];
+        {
+            int mrow[J];
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = lane + 64 * j;
-            mrow[j] = r < n ? active_index(r, m0, LP) : -1;
+            for (int j = 0; j < J; ++j) {
+                const int r = lane + 64 * j;
+                mrow[j] = r < n ? active_index(r, m0, LP) : -1;
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int col = cl + 64 * (H + ST * s);
+                const double* src = C + (int64_t)active_index(col < n ? col : 0, m0, LP) * NP;
+#pragma unroll
+                for (int j = 0; j < J; ++j) a[s][j] = (col < n && mrow[j] >= 0) ? src[mrow[j]] * sc0 : 0.0;
+            }
+            const double* src = C + (int64_t)active_index(0, m0, LP) * NP;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                x[j] = mrow[j] >= 0 ? src[mrow[j]] * sc0 : 0.0;
+                v[j] = 0.0;
+                w[j] = 0.0;
+            }
         }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int col = gw + NW * s;
-            const double* src = C + (int64_t)active_index(col < n ? col : 0, m0, LP) * NP;
-#pragma unroll
-            for (int j = 0; j < J; ++j) a[s][j] = (col < n && mrow[j] >= 0) ? src[mrow[j]] * sc0 : 0.0;
-            vcol[s] = 0.0;
-            wcol[s] = 0.0;
-        }
-        const double* src = C + (int64_t)active_index(0, m0, LP) * NP;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            x[j] = mrow[j] >= 0 ? src[mrow[j]] * sc0 : 0.0;
-            v[j] = 0.0;
-            w[j] = 0.0;
-        }
-    }
-    double xk = C[(int64_t)active_index(0, m0, LP) * NP + active_index(0, m0, LP)] * sc0;
-    double xk1 = n > 1 ? C[(int64_t)active_index(0, m0, LP) * NP + active_index(1, m0, LP)] * sc0 : 0.0;
-    int spins = SPIN_LIMIT;
-    int slot = 0;
+        double xk = C[(int64_t)active_index(0, m0, LP) * NP + active_index(0, m0, LP)] * sc0;
+        double xk1 = n > 1 ? C[(int64_t)active_index(0, m0, LP) * NP + active_index(1, m0, LP)] * sc0 : 0.0;
 
-    for (int k = 0; k < n - 1; ++k) {
-        const int par = k & 1;
-        long long* const px = xch + (int64_t)slot * 2 * N;
-        long long* const cx = px + N;
-        double r2 = 0.0;
+        for (int k = 0; k < n - 1; ++k) {
+            const int par = k & 1;
+            const unsigned tag = tag0 + (unsigned)k;
+            u32x4* const qx = xch + par * 2 * N;
+            u32x4* const cx = qx + N;
 #pragma unroll
-        for (int j = 0; j < J; ++j) r2 = __builtin_fma(lane + 64 * j > k + 1 ? x[j] : 0.0, x[j], r2);
-        r2 = lane_sum<64>(r2);
-        double beta, tau, scale;
-        householder(xk1, r2, beta, tau, scale);
-        const double v1 = r2 > TRI_DROP2 ? 1.0 : 0.0;
-        double vn[J];
+            for (int j = 0; j < J; ++j) x[j] = lane + 64 * j > k + 1 ? x[j] : 0.0;
+            double acc[4], vcol[4], wcol[4];
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = lane + 64 * j;
-            vn[j] = r > k + 1 ? x[j] * scale : (r == k + 1 ? v1 : 0.0);
-            vs[wave][r] = vn[j];
-        }
-        wait_stores();  // last step's resets (long done)
-        double acc[4];
+            for (int s = 0; s < 4; ++s) {
+                vcol[s] = read_lane(v[H + ST * s], cl);
+                wcol[s] = read_lane(w[H + ST * s], cl);
+            }
+            // Straight-line code over all four columns: finished ones are carried along (nothing reads them), because a
+            // branch per column or register leaves the fp64 pipeline waiting for every result. Rows below 64 J0 are done
+            // with.
+            auto pass = [&](auto j0c) __attribute__((always_inline)) {
+                constexpr int J0 = decltype(j0c)::value;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            acc[s] = 0.0;
-            const int col = gw + NW * s;
-            if (col > k && col < n) {
+                for (int s = 0; s < 4; ++s)
 #pragma unroll
-                for (int j = 0; j < J; ++j)
-                    if (64 * j + 63 > k) {
-                        a[s][j] = __builtin_fma(-v[j], wcol[s], __builtin_fma(-w[j], vcol[s], a[s][j]));
-                        acc[s] = __builtin_fma(a[s][j], vn[j], acc[s]);
-                    }
-                if (col == k + 1) {
+                    for (int j = J0; j < J; ++j) a[s][j] = __builtin_fma(-w[j], vcol[s], a[s][j]);
 #pragma unroll
-                    for (int j = 0; j < J; ++j)
-                        if (64 * j + 63 > k && lane + 64 * j > k && lane + 64 * j < n) put(cx + lane + 64 * j, a[s][j]);
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int j = J0; j < J; ++j) a[s][j] = __builtin_fma(-v[j], wcol[s], a[s][j]);
+                if (((k + 1) & 63) == cl && (((k + 1) >> 6) & (ST - 1)) == H) {  // column k + 1 is this wave's
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        if ((k + 1) >> 6 == H + ST * s) {
+#pragma unroll
+                            for (int j = J0; j < J; ++j) {
+                                double c = a[s][j];
+                                asm volatile("" : "+v"(c));  // keeps the cases apart (no run-time index into a[])
+                                put_entry<LOCAL>(cx + lane + 64 * j, c, tag);
+                            }
+                        }
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc[s] = a[s][J0] * x[J0];
+#pragma unroll
+                for (int j = J0 + 1; j < J; ++j)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) acc[s] = __builtin_fma(a[s][j], x[j], acc[s]);
+            };
+            if (k < 32 * J) pass(std::integral_constant<int, 0>{});
+            else pass(std::integral_constant<int, J / 2>{});
+            {   // the four sums over the wave: two at a time per lane pair, then one per lane of a quad
+                const bool odd = lane & 1, hi = lane & 2;
+                double t0 = odd ? acc[1] : acc[0], o0 = odd ? acc[0] : acc[1];
+                double t1 = odd ? acc[3] : acc[2], o1 = odd ? acc[2] : acc[3];
+                t0 += dpp_move<DPP_XOR1>(o0);   // lane parity q: column q
+                t1 += dpp_move<DPP_XOR1>(o1);   // ... column 2 + q
+                double t = hi ? t1 : t0, o = hi ? t0 : t1;
+                t += dpp_move<DPP_XOR2>(o);     // lane & 3 = column; sums over quads so far
+                t += dpp_move<0x124>(t);        // row_ror 4
+                t += dpp_move<0x128>(t);        // row_ror 8: sums over rows of 16
+                double b0, b1;
+                swap_rows<16>(t, b0, b1);
+                t = b0 + b1;
+                swap_rows<32>(t, b0, b1);
+                t = b0 + b1;
+                const int col = cl + 64 * (H + ST * (lane & 3));
+                if (lane < 4 && col > k && col < n) put_entry<LOCAL>(qx + col, t, tag);
+            }
+            // while the entries travel: the reflector
+            double r2 = 0.0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) r2 = __builtin_fma(x[j], x[j], r2);
+            r2 = lane_sum<64>(r2);
+            double beta, tau, v1;
+            householder(xk1, r2, beta, tau, v1);
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int r = lane + 64 * j;
+                v[j] = r == k + 1 ? v1 : x[j];
+                vs[wave][r] = v[j];
+            }
+            asm volatile("" ::: "memory");
+            const int i2 = k + 2 < n ? k + 2 : k + 1;
+            const double v2 = vs[wave][i2];
+            if (wg == (k & (N / 16 - 1))) {
+                if (wave == 0) {
+#pragma unroll
+                    for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = v[j];
+                }
+                if (tid == 64) {
+                    dT[k] = xk;
+                    eT[k] = beta;
+                    tauT[k] = tau;
                 }
             }
-        }
-        // the four sums over the wave, two at a time per lane pair, then one per lane of a quad
-        {
-            const bool odd = lane & 1, hi = lane & 2;
-            double t0 = odd ? acc[1] : acc[0], o0 = odd ? acc[0] : acc[1];
-            double t1 = odd ? acc[3] : acc[2], o1 = odd ? acc[2] : acc[3];
-            t0 += dpp_move<DPP_XOR1>(o0);   // lane parity q: column q
-            t1 += dpp_move<DPP_XOR1>(o1);   // ... column 2 + q
-            double t = hi ? t1 : t0, o = hi ? t0 : t1;
-            t += dpp_move<DPP_XOR2>(o);     // lane & 3 = column; sums over quads so far
-            t += dpp_move<0x124>(t);        // row_ror 4
-            t += dpp_move<0x128>(t);        // row_ror 8: sums over rows of 16
-            t += __shfl_xor(t, 16);
-            t += __shfl_xor(t, 32);
-            const int col = gw + NW * (lane & 3);
-            if (lane < 4 && col > k && col < n) put(px + col, tau * t);
-        }
-        if (wg == (k & (N / 16 - 1))) {
-            if (wave == 0) {
+            lds_barrier();
+            const Pair e1 = qc[par][k + 1], e2 = qc[par][i2];
+            double c[J], dot = 0.0;
 #pragma unroll
-                for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = vn[j];
+            for (int j = 0; j < J; ++j) {
+                const Pair e = qc[par][lane + 64 * j];  // (entries of rows <= k are zero)
+                c[j] = e.b;
+                w[j] = tau * __builtin_fma(v1, e.b, e.a);
+                dot = __builtin_fma(w[j], v[j], dot);
             }
-            if (tid == 64) {
-                dT[k] = xk;
-                eT[k] = beta;
-                tauT[k] = tau;
+            dot = lane_sum<64>(dot);
+            const double al = -0.5 * tau * dot;
+            const double w1 = __builtin_fma(al, v1, tau * __builtin_fma(v1, e1.b, e1.a));
+            const double w2 = __builtin_fma(al, v2, tau * __builtin_fma(v1, e2.b, e2.a));
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                w[j] = __builtin_fma(al, v[j], w[j]);
+                x[j] = __builtin_fma(-v[j], w1, __builtin_fma(-w[j], v1, c[j]));
             }
+            xk = __builtin_fma(-2.0 * v1, w1, e1.b);
+            xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, e2.b));
         }
-        // pick up this thread's entries
-        {
-            long long up[PT], uc[PT];
-            bool need[PT];
-#pragma unroll
-            for (int q = 0; q < PT; ++q) {
-                const int i = tid + 256 * q;
-                need[q] = i > k && i < n;
-                up[q] = need[q] ? EMPTY : 0;
-                uc[q] = need[q] ? EMPTY : 0;
-            }
-            bool more = true;
-            while (more) {
-#pragma unroll
-                for (int q = 0; q < PT; ++q) {
-                    if (need[q]) {
-                        up[q] = get(px + tid + 256 * q);
-                        uc[q] = get(cx + tid + 256 * q);
-                    }
-                }
-                more = false;
-#pragma unroll
-                for (int q = 0; q < PT; ++q) more = more || up[q] == EMPTY || uc[q] == EMPTY;
-                if (more && --spins <= 0) {
-                    if (spins == 0) stat[1] = 1.0;
-                    spins = -1000000;
-                    more = false;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < PT; ++q) {
-                pb[par][tid + 256 * q] = __longlong_as_double(up[q]);
-                cb[par][tid + 256 * q] = __longlong_as_double(uc[q]);
-            }
+        if (wg == 0 && tid == 0) {
+            dT[n - 1] = xk;
+            eT[n - 1] = 0.0;
+            tauT[n - 1] = 0.0;
         }
-        __syncthreads();
-        {   // free the slot of step k - 1 for step k + 2
-            const int old = slot == 0 ? 2 : slot - 1;
-            const int col = gw + NW * (lane & 3);
-            if (lane < 8 && col < n) {
-                long long* const e = xch + (int64_t)old * 2 * N + (lane >> 2) * N + col;
-                __hip_atomic_store(e, EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        double p[J], c[J];
-        double dot = 0.0;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            p[j] = pb[par][lane + 64 * j];
-            c[j] = cb[par][lane + 64 * j];
-            dot = __builtin_fma(p[j], vn[j], dot);
-        }
-        const int i2 = k + 2 < n ? k + 2 : k + 1;
-        const double p1 = pb[par][k + 1], p2 = pb[par][i2], c1 = cb[par][k + 1], c2 = cb[par][i2], v2 = vs[wave][i2];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            vcol[s] = vs[wave][gw + NW * s];
-            wcol[s] = pb[par][gw + NW * s];
-        }
-        dot = lane_sum<64>(dot);
-        const double al = -0.5 * tau * dot;
-        const double w1 = __builtin_fma(al, v1, p1), w2 = __builtin_fma(al, v2, p2);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) wcol[s] = __builtin_fma(al, vcol[s], wcol[s]);
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            v[j] = vn[j];
-            w[j] = __builtin_fma(al, vn[j], p[j]);
-            x[j] = __builtin_fma(-v[j], w1, __builtin_fma(-w[j], v1, c[j]));
-        }
-        xk = __builtin_fma(-2.0 * v1, w1, c1);
-        xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, c2));
-        slot = slot == 2 ? 0 : slot + 1;
-    }
-    if (wg == 0 && tid == 0) {
-        dT[n - 1] = xk;
-        eT[n - 1] = 0.0;
-        tauT[n - 1] = 0.0;
-    }
-    if (wg == 0)
+    };
+    static_assert(J == 4 || J == 8, "one or two columns a lane");
+    if (J == 4 || gw < 64) reduce(std::integral_constant<int, 0>{});
+    else reduce(std::integral_constant<int, J / 4 - 1>{});
+    if (wg == 0) {
         for (int i = n + tid; i < N; i += 256) {
             dT[i] = -1.0;
             eT[i] = 0.0;
             tauT[i] = 0.0;
         }
+        for (int k = n - 1; k % WY != 0; ++k)  // the rows of V that complete the last block of reflectors
+            for (int i = tid; i < N; i += 256) V[(int64_t)k * N + i] = 0.0;
+    }
 }
 
 // ---- Y = H Z --------------------------------------------------------------------------------------------------------
-// One wave per eigenvector: the vector in registers (rows lane, lane + 64, ...), the reflectors n - 3 .. 0 applied one
-// after the other (they stream through L2 / L1; four requested ahead). Column `col` of Z (column-major, ascending
-// eigenvalues) becomes row N - 1 - col of Yt (descending), in matrix indices; padding indices are zero.
+// One wave per eigenvector, the vector in registers (rows lane, lane + 64, ...); the reflectors are applied eight at a time
+// as I - V T V^T (T from wy_factor), last block first, the next block's V and T on their way meanwhile. A block is 8
+// products summed over the wave together, an 8 x 8 triangle and 8 updates, so the latency of a sum over the wave is paid
+// once per eight reflectors (one or two at a time it was the bound). Rows before a block's first are zero in V and left
+// out in quarters, each a loop of its own: with the choice inside one loop the waits for the next block's loads came
+// early. Column `col` of Z (column-major, ascending eigenvalues) becomes row N - 1 - col of Yt (descending), in matrix
+// indices.
 template <int J>
-__global__ __launch_bounds__(64) void tri_back_kernel(const double* __restrict__ Z, const double* __restrict__ V,
-                                                      const double* __restrict__ tauT, int m0, int LP, int n,
-                                                      double* __restrict__ Yt, int NP) {
-    constexpr int N = 64 * J;
+__global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restrict__ Z, const double* __restrict__ V,
+                                                         const double* __restrict__ Tw, int m0, int LP, int n,
+                                                         double* __restrict__ Yt, int NP) {
+    constexpr int N = 64 * J, NQ = J >= 4 ? 4 : 1, QS = J / NQ, QB = N / WY / NQ;  // parts; registers, blocks of a part
     const int lane = threadIdx.x;
     const int rank = blockIdx.x, col = N - 1 - rank;
     double z[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) z[j] = Z[(int64_t)col * N + lane + 64 * j];
-    // pairs of reflectors: (I - t1 v1 v1^T)(I - t2 v2 v2^T) z with both products formed at once
-    double va[2][J], vb[2][J];
-    int k = n - 3;
-    auto load = [&](int kk, double (&u)[J]) {
-#pragma unroll
-        for (int j = 0; j < J; ++j) u[j] = (kk >= 0 && 64 * j + 63 > kk) ? V[(int64_t)kk * N + lane + 64 * j] : 0.0;
+    struct Block {
+        double v[WY][J], t;  // t: entry (lane >> 3, lane & 7) of T
     };
-    load(k, vb[0]);
-    load(k - 1, va[0]);
-    load(k - 2, vb[1]);
-    load(k - 3, va[1]);
-    auto pair = [&](double (&ua)[J], double (&ub)[J], int kk) {  // reflectors kk (ub), then kk - 1 (ua)
-        const double ta = kk >= 1 ? tauT[kk - 1] : 0.0, tb = tauT[kk];
-        double sa = 0.0, sb = 0.0, sab = 0.0;
+    Block va, vb;
+    const bool odd = lane & 1, hi = lane & 2;
+
+    auto load = [&](auto qc, int b, Block& k) __attribute__((always_inline)) {
+        constexpr int J0 = decltype(qc)::value * QS;
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            sb = __builtin_fma(ub[j], z[j], sb);
-            sa = __builtin_fma(ua[j], z[j], sa);
-            sab = __builtin_fma(ua[j], ub[j], sab);
+        for (int i = 0; i < WY; ++i)
+#pragma unroll
+            for (int j = J0; j < J; ++j) k.v[i][j] = V[(int64_t)(b * WY + i) * N + lane + 64 * j];
+        k.t = Tw[b * WY * WY + lane];
+    };
+    auto apply = [&](auto qc, const Block& k) __attribute__((always_inline)) {
+        constexpr int J0 = decltype(qc)::value * QS;
+        double p[WY];
+#pragma unroll
+        for (int i = 0; i < WY; ++i) p[i] = k.v[i][J0] * z[J0];
+#pragma unroll
+        for (int j = J0 + 1; j < J; ++j)
+#pragma unroll
+            for (int i = 0; i < WY; ++i) p[i] = __builtin_fma(k.v[i][j], z[j], p[i]);
+        // sums over the wave of the eight: lane & 3 tells four apart, two registers the halves
+        double s2[2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const double* q = p + 4 * g;
+            double t0 = odd ? q[1] : q[0], o0 = odd ? q[0] : q[1];
+            double t1 = odd ? q[3] : q[2], o1 = odd ? q[2] : q[3];
+            t0 += dpp_move<DPP_XOR1>(o0);
+            t1 += dpp_move<DPP_XOR1>(o1);
+            double t = hi ? t1 : t0, o = hi ? t0 : t1;
+            t += dpp_move<DPP_XOR2>(o);
+            t += dpp_move<0x124>(t);  // row_ror 4
+            t += dpp_move<0x128>(t);  // row_ror 8
+            double a0, a1;
+            swap_rows<16>(t, a0, a1);
+            t = a0 + a1;
+            swap_rows<32>(t, a0, a1);
+            s2[g] = a0 + a1;
         }
-        sb = lane_sum<64>(sb);
-        sa = lane_sum<64>(sa);
-        sab = lane_sum<64>(sab);
-        const double fb = tb * sb, fa = ta * (sa - fb * sab);
+        double y = k.t * (lane & 4 ? s2[1] : s2[0]);  // y_p = sum_q T_pq s_q, p = lane >> 3, q = lane & 7
+        y = lane_sum<8>(y);
 #pragma unroll
-        for (int j = 0; j < J; ++j) z[j] = __builtin_fma(-fa, ua[j], __builtin_fma(-fb, ub[j], z[j]));
-        load(kk - 4, ub);
-        load(kk - 5, ua);
+        for (int i = 0; i < WY; ++i) {
+            const double yi = -read_lane(y, 8 * i);
+#pragma unroll
+            for (int j = J0; j < J; ++j) z[j] = __builtin_fma(yi, k.v[i][j], z[j]);
+        }
     };
-    for (; k >= 0; k -= 4) {
-        pair(va[0], vb[0], k);
-        if (k - 2 >= 0) pair(va[1], vb[1], k - 2);
+    // the blocks of part q, from b (in va already) down to the part's first; leaves the block below in va
+    auto part = [&](auto qc, int b) __attribute__((always_inline)) {
+        constexpr int Q = decltype(qc)::value;
+        constexpr std::integral_constant<int, (Q > 0 ? Q - 1 : 0)> below{};
+        if (((b - Q * QB) & 1) == 0) {  // odd number of blocks: one first
+            load(below, max(b - 1, 0), vb);
+            apply(qc, va);
+            va = vb;
+            --b;
+        }
+        for (; b > Q * QB + 1; b -= 2) {
+            load(qc, b - 1, vb);
+            apply(qc, va);
+            load(qc, b - 2, va);
+            apply(qc, vb);
+        }
+        if (b > Q * QB) {
+            load(qc, b - 1, vb);
+            apply(qc, va);
+            load(below, max(b - 2, 0), va);
+            apply(qc, vb);
+        }
+        return Q * QB - 1;
+    };
+    // (the reduction leaves zeros in the rows of V that complete its last block)
+    if (n >= 2) {
+        int b = (n - 2) / WY;
+        load(std::integral_constant<int, 0>{}, b, va);
+        if constexpr (NQ == 4) {
+            if (b >= 3 * QB) b = part(std::integral_constant<int, 3>{}, b);
+            if (b >= 2 * QB) b = part(std::integral_constant<int, 2>{}, b);
+            if (b >= QB) b = part(std::integral_constant<int, 1>{}, b);
+        }
+        part(std::integral_constant<int, 0>{}, b);
     }
     // Padding indices (matrix indices outside the active ones): a padding eigenvector is its own unit vector.
     double* out = Yt + (int64_t)rank * NP;
@@ -487,32 +671,69 @@ __global__ __launch_bounds__(64) void tri_back_kernel(const double* __restrict__
     }
 }
 
+// Do work-groups whose numbers are congruent modulo 8 run on one XCD of the current device? Asked once per device.
+__global__ void xcd_probe_kernel(int* __restrict__ out) {
+    int id;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(id));
+    if (threadIdx.x == 0) out[blockIdx.x] = id;
+}
+static bool xcd_mapping_known() {
+    static std::mutex lock;
+    static int known[64] = {0};  // 0: not asked yet, 1: yes, 2: no
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+    std::lock_guard<std::mutex> hold(lock);
+    if (known[dev] == 0) {
+        constexpr int B = 512;
+        int* d = nullptr;
+        int h[B];
+        bool ok = hipMalloc((void**)&d, sizeof(h)) == hipSuccess;
+        if (ok) {
+            hipStream_t st = nullptr;
+            ok = hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
+            if (ok) {
+                hipLaunchKernelGGL(xcd_probe_kernel, dim3(B), dim3(64), 0, st, d);
+                ok = hipMemcpyAsync(h, d, sizeof(h), hipMemcpyDeviceToHost, st) == hipSuccess &&
+                     hipStreamSynchronize(st) == hipSuccess;
+                (void)hipStreamDestroy(st);
+            }
+            (void)hipFree(d);
+        }
+        for (int i = 8; ok && i < B; ++i) ok = h[i] == h[i - 8];
+        known[dev] = ok ? 1 : 2;
+    }
+    return known[dev] == 1;
+}
+
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st) {
     const int LP = NP / 2;
+#define SAGE_TRI_ONE(J)                                                                                           \
+    hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
+#define SAGE_TRI_MANY(J, L)                                                                                       \
+    hipLaunchKernelGGL((tri_many_kernel<J, L>), dim3(8 * 4 * J), dim3(512), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, \
+                       w.V, w.stat, w.xch, w.epoch << 10, w.xcd)
     switch (NP / 64) {
-        case 1:
-            hipLaunchKernelGGL(tri_one_kernel<1>, dim3(1), dim3(256), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat);
-            break;
-        case 2:
-            hipLaunchKernelGGL(tri_one_kernel<2>, dim3(1), dim3(256), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat);
-            break;
+        case 1: SAGE_TRI_ONE(1); break;
+        case 2: SAGE_TRI_ONE(2); break;
         case 4:
-            hipLaunchKernelGGL(tri_many_kernel<4>, dim3(8 * 16), dim3(256), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT,
-                               w.V, w.stat, w.xch, w.xcd);
+            if (w.local) SAGE_TRI_MANY(4, true); else SAGE_TRI_MANY(4, false);
             break;
         case 8:
-            hipLaunchKernelGGL(tri_many_kernel<8>, dim3(8 * 32), dim3(256), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT,
-                               w.V, w.stat, w.xch, w.xcd);
+            if (w.local) SAGE_TRI_MANY(8, true); else SAGE_TRI_MANY(8, false);
             break;
         default: return hipErrorInvalidValue;
     }
+#undef SAGE_TRI_ONE
+#undef SAGE_TRI_MANY
     return hipGetLastError();
 }
+
+bool tridiag_local_ok() { return xcd_mapping_known(); }
 
 hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st) {
     const int LP = NP / 2;
 #define SAGE_BACK(J)                                                                                              \
-    hipLaunchKernelGGL(tri_back_kernel<J>, dim3(count), dim3(64), 0, st, w.Z[dc_result(NP)], w.V, w.tauT, m0, LP, n, w.Yt, NP)
+    hipLaunchKernelGGL(tri_back_kernel<J>, dim3(count), dim3(64), 0, st, w.Z[dc_result(NP)], w.V, w.Tw, m0, LP, n, w.Yt, NP)
     switch (NP / 64) {
         case 1: SAGE_BACK(1); break;
         case 2: SAGE_BACK(2); break;

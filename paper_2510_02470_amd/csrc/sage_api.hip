@@ -241,6 +241,8 @@ void xcd_release(sage_ctx* c) {
 // Eigensolve of the Gram matrix of fill_top + fill_new rows; the `count` leading eigenvectors are formed.
 hipError_t eigensolve(sage_ctx* c, int m0, int n, int count) {
     if (n < 1) m0 = n = 1;  // an empty buffer: one zero row
+    c->ew.epoch = (c->ew.epoch + 1) & 0x3fffffu;
+    if (c->ew.epoch == 0) c->ew.epoch = 1;
     if (c->xcd_slot < 0) return launch_eig(c->ew, c->d.NP, m0, n, count, c->st);
     std::unique_lock<std::mutex> hold(g_xcd_lock);
     XcdSlot& x = g_xcd[c->device][c->xcd_slot];
@@ -257,7 +259,7 @@ hipError_t eigensolve(sage_ctx* c, int m0, int n, int count) {
         x.owner = c;
         hold.unlock();
     }
-    if (e == hipSuccess) e = launch_dc(c->ew, c->d.NP, c->st);
+    if (e == hipSuccess) e = launch_dc(c->ew, c->d.NP, n, c->st);
     if (e == hipSuccess) e = launch_tri_back(c->ew, c->d.NP, m0, n, count, c->st);
     return e;
 }
@@ -553,11 +555,12 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             const size_t n1 = (size_t)NP, n2 = n1 * n1;
             EigWork& w = c->ew;
             bytes = 0;
-            take(w.xch, 6 * n1);
+            take(w.xch, 4 * n1);
             take(w.stat, 32);
             take(w.C, n2);
             take(w.Yt, n2);
             take(w.V, n2);
+            take(w.Tw, 8 * n1);
             for (int i = 0; i < 2; ++i) take(w.Z[i], n2);
             for (int i = 0; i < 2; ++i) take(w.dI[i], n1);
             for (double** p : {&w.dT, &w.eT, &w.tauT, &w.known, &w.dc.dk, &w.dc.zk, &w.dc.org, &w.dc.tau, &w.dc.val, &w.dc.zh})
@@ -566,6 +569,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             if (pass == 0) CALLOC(c->eig_mem, bytes);
         }
         c->ew.xcd = xcd_take(c);
+        c->ew.local = NP >= 256 && tridiag_local_ok();
     }
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
@@ -575,7 +579,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     if (hipMemsetAsync(c->top, 0, hbytes, c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->acc, 0, 8 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->ew.stat, 0, 32 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
-    if (hipMemsetAsync(c->ew.xch, 0xFF, (size_t)6 * NP * sizeof(long long), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
+    if (hipMemsetAsync(c->ew.xch, 0, (size_t)4 * NP * sizeof(u32x4), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipHostMalloc((void**)&c->h_failed, sizeof(int), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();

@@ -127,6 +127,7 @@ struct EigWork {
     double* C;      // NP x NP Gram matrix, left untouched
     double* Yt;     // NP x NP: row m = eigenvector of the m-th largest eigenvalue
     double* V;      // NP x NP Householder vectors (row k: the reflector of step k)
+    double* Tw;     // 8 NP: triangular factors of the blocks of eight reflectors (fd_wy.h)
     double* Z[2];   // NP x NP, column-major: eigenvectors of T, ping-pong between the merges
     double* dT;     // NP: diagonal, sub-diagonal and reflector factors of the reduction
     double* eT;
@@ -134,16 +135,19 @@ struct EigWork {
     double* dI[2];  // NP: eigenvalues, ascending, in units of 2^stat[0]
     double* stat;   // [0] exponent of the scaling, [1] set when the reduction gave up waiting for a work-group
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
-    long long* xch; // exchange buffers of the reduction (NP = 256, 512), 6 NP entries, EMPTY between solves
+    u32x4* xch;     // exchange buffers of the reduction (NP = 256, 512), 4 NP entries
     int xcd;        // the XCD the reduction runs on (NP = 256, 512)
+    bool local;     // work-groups with the same number modulo 8 share an XCD (tridiag_local_ok)
+    unsigned epoch; // number of the solve, from 1 (tags of the exchange)
     DcWork dc;
 };
 // which of dI / Z the last merge of a solve of size NP writes
 inline int dc_result(int NP) { return (NP == 128 || NP == 512) ? 1 : 0; }
 // Matrix indices in use: 0 .. m0-1 and LP .. LP + (n - m0) - 1, n in all (the others are zero rows and columns); the count
 // leading eigenvectors are formed.
+bool tridiag_local_ok();  // asks the current device (once)
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
-hipError_t launch_dc(const EigWork& w, int NP, hipStream_t st);
+hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
 hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st);
 hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st);
 // Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2); into Mc3 (split parts) if given, else into Mt.

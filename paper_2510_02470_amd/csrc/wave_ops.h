@@ -23,11 +23,19 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
     const int hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-__device__ __forceinline__ double uniform(double v) {
+
+// Partner of a lane 16 (32) lanes away: the swap instruction on two copies leaves one value of each pair in either result.
+template <int D>
+__device__ __forceinline__ void swap_rows(double v, double& a, double& b) {
+    static_assert(D == 16 || D == 32, "rows of 16 or halves of 32 lanes");
     const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)u);
-    const int hi = __builtin_amdgcn_readfirstlane((int)(u >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+    const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+    const auto l = D == 16 ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
+                           : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = D == 16 ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false)
+                           : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    a = __longlong_as_double(((long long)h[0] << 32) | l[0]);
+    b = __longlong_as_double(((long long)h[1] << 32) | l[1]);
 }
 
 // Sum over groups of L lanes (L = 8, 16 or 64), the same bits in every lane of the group.
@@ -37,7 +45,13 @@ __device__ __forceinline__ double lane_sum(double v) {
     v += dpp_move<DPP_XOR2>(v);
     v += dpp_move<DPP_HALF_MIRROR>(v);
     if constexpr (L >= 16) v += dpp_move<DPP_MIRROR>(v);
-    if constexpr (L == 64) v = (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+    if constexpr (L == 64) {
+        double a, b;
+        swap_rows<16>(v, a, b);
+        v = a + b;
+        swap_rows<32>(v, a, b);
+        v = a + b;
+    }
     return v;
 }
 template <int L>
@@ -46,7 +60,13 @@ __device__ __forceinline__ double lane_product(double v) {
     v *= dpp_move<DPP_XOR2>(v);
     v *= dpp_move<DPP_HALF_MIRROR>(v);
     if constexpr (L >= 16) v *= dpp_move<DPP_MIRROR>(v);
-    if constexpr (L == 64) v = (read_lane(v, 0) * read_lane(v, 16)) * (read_lane(v, 32) * read_lane(v, 48));
+    if constexpr (L == 64) {
+        double a, b;
+        swap_rows<16>(v, a, b);
+        v = a * b;
+        swap_rows<32>(v, a, b);
+        v = a * b;
+    }
     return v;
 }
 template <int CTRL>
