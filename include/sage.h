@@ -27,6 +27,7 @@
 #ifndef SAGE_H
 #define SAGE_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -63,6 +64,18 @@ typedef struct {
     double last_offdiag; /* largest |off-diagonal| / trace an iterative eigensolver left; 0: the eigensolve is direct, its
                             residual is a few 2*ell * 2^-52 of the trace */
 } sage_stats_t;
+
+/*
+ * Where device memory comes from, for the contexts created and the sage_topm calls made from now on in this process
+ * (NULL, NULL: hipMalloc and hipFree, the default). alloc returns DEVICE memory on the current device, aligned to 256
+ * bytes, for use on hip_stream and on streams ordered with it, or NULL; free is called when nothing enqueued uses the
+ * memory any more. A context keeps the pair it was created with. Both may be called from any thread that calls the
+ * library. A program that creates contexts again and again gives its own pool here: a large context's hipMalloc and
+ * hipFree take milliseconds, and memory freed to the driver is cleared before it is handed out again.
+ */
+typedef void* (*sage_alloc_fn)(size_t bytes, void* hip_stream, void* user);
+typedef void (*sage_free_fn)(void* ptr, void* user);
+int sage_set_allocator(sage_alloc_fn alloc, sage_free_fn free, void* user);
 
 /* ---- the five calls of the path --------------------------------------------------------------------------- */
 
@@ -278,14 +291,14 @@ int sage_stats(sage_ctx* ctx, sage_stats_t* out);
  * Stand-alone top-m (Algorithm 1, "Select top-k by alpha_i") of any fp32 score vector: the m indices greatest
  * under (alpha descending, index ascending), written ascending. alpha: DEVICE, N floats (NaN not allowed);
  * out_idx: DEVICE, m int64; 0 <= m <= N; hip_stream as in sage_fd_create_ex. Allocates and frees its own work
- * space; returns after the result is complete.
+ * space (none for N <= 32768); returns after the result is complete.
  */
 int sage_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* hip_stream);
 
 /*
  * sage_topm for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc. Same arguments and result as sage_topm, but the work space (a histogram, the
- * select state and two counters per block of 2048 keys, 67 KB in all) is a fixed array inside the library, one copy
+ * harnesses that forbid hipMalloc. Same arguments and result as sage_topm, but the work space (histograms, the
+ * select state and two counters per block of 4096 keys, 57 KB in all) is a fixed array inside the library, one copy
  * per GPU, held until the process ends; the call allocates and frees nothing and does not wait: the work is enqueued
  * on hip_stream and out_idx is complete when that stream reaches the end of it. N > SAGE_TOPM_STATIC_MAX_N gives
  * SAGE_ERR_CAPACITY. All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two

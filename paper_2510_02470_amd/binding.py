@@ -18,7 +18,7 @@ KERNEL_CLASSES = ("gram", "gram_reduce", "eigensolve", "coefficients", "rebuild"
 
 # every symbol include/sage.h declares
 EXPORTS = (
-    "sage_fd_create", "sage_fd_create_ex", "sage_fd_update", "sage_fd_merge", "sage_set_update_arithmetic", "sage_probe_gram_split", "sage_fd_update_outer", "sage_score_outer", "sage_rescore_outer", "sage_set_score_store", "sage_rescore", "sage_fd_basis", "sage_fd_basis_weighted", "sage_score", "sage_select", "sage_score_labeled", "sage_select_cb", "sage_select_cb_ex",
+    "sage_set_allocator", "sage_fd_create", "sage_fd_create_ex", "sage_fd_update", "sage_fd_merge", "sage_set_update_arithmetic", "sage_probe_gram_split", "sage_fd_update_outer", "sage_score_outer", "sage_rescore_outer", "sage_set_score_store", "sage_rescore", "sage_fd_basis", "sage_fd_basis_weighted", "sage_score", "sage_select", "sage_score_labeled", "sage_select_cb", "sage_select_cb_ex",
     "sage_destroy", "sage_sync", "sage_set_projection_mode", "sage_fd_sketch_export", "sage_basis_export", "sage_set_basis", "sage_scores",
     "sage_scores_export", "sage_zhat_export", "sage_stats", "sage_topm", "sage_topm_static", "sage_probe_gram_eig", "sage_probe_eig_matrix",
     "sage_profile_enable", "sage_copy_probe", "sage_set_debug_checks", "sage_debug_fail_launch", "sage_set_sweep_policy",
@@ -41,6 +41,33 @@ class SageError(RuntimeError):
 
 _lib = None
 
+_ALLOC_FN = C.CFUNCTYPE(C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p)
+_FREE_FN = C.CFUNCTYPE(None, C.c_void_p, C.c_void_p)
+
+
+_memory = None  # the callbacks in use (they must outlive every context)
+
+
+def _torch_memory(L):
+    """Device memory of contexts from torch's caching allocator, on the context's stream: shared with, and given back
+    to, the rest of the program like any tensor's."""
+    global _memory
+    import torch
+
+    take, give = torch._C._cuda_cudaCachingAllocator_raw_alloc, torch._C._cuda_cudaCachingAllocator_raw_delete
+
+    def alloc(nbytes, stream, user):
+        try:
+            return take(nbytes, stream or 0)
+        except RuntimeError:
+            return None  # out of memory: the library reports it
+
+    def free(ptr, user):
+        give(ptr)
+
+    _memory = _ALLOC_FN(alloc), _FREE_FN(free)
+    _check(L.sage_set_allocator(*_memory, None), "sage_set_allocator")
+
 
 def lib():
     """Load libsage_hip.so (built by ``paper_2510_02470_amd.build``). Raises if it is missing."""
@@ -51,6 +78,7 @@ def lib():
         raise RuntimeError("HIP library not built: %s is missing (run __graft_entry__.build())" % LIB_PATH)
     L = C.CDLL(LIB_PATH)
     vp, i64, i32, dbl = C.c_void_p, C.c_int64, C.c_int, C.c_double
+    L.sage_set_allocator.argtypes = [_ALLOC_FN, _FREE_FN, vp]
     L.sage_fd_create.argtypes = [C.POINTER(vp), i32, i64]
     L.sage_fd_create_ex.argtypes = [C.POINTER(vp), i32, i64, i32, i64, vp]
     L.sage_fd_update.argtypes = [vp, vp, i64]
@@ -96,6 +124,7 @@ def lib():
         if name not in ("sage_destroy", "sage_strerror"):
             getattr(L, name).restype = i32
     _lib = L
+    _torch_memory(L)
     return L
 
 
@@ -213,8 +242,7 @@ class Sage:
 
     def select_cb(self, keep_rate, n_classes, cap=None, rule="proportional"):
         """Class-balanced selection; rule: how the subset size is shared out ("proportional" or "equal")."""
-        st = self.stats()
-        cap = st.n_scored if cap is None else int(cap)
+        cap = self._n_scored() if cap is None else int(cap)
         out = self.torch.empty(max(cap, 1), dtype=self.torch.int64, device="cuda")
         m = C.c_int64(0)
         code = {"proportional": CB_PROPORTIONAL, "equal": CB_EQUAL}[rule]
@@ -222,10 +250,21 @@ class Sage:
                "sage_select_cb_ex")
         return out[: m.value]
 
+    def _select_count(self, keep_rate):
+        """Rows that select(keep_rate) returns: with room for none the library reports the number and does no work."""
+        m = C.c_int64(0)
+        rc = self.L.sage_select(self.h, float(keep_rate), C.c_void_p(0), 0, C.byref(m))
+        if rc != SAGE_ERR_CAPACITY:
+            _check(rc, "sage_select")
+        return m.value
+
+    def _n_scored(self):
+        return self._select_count(1.0)
+
     def select(self, keep_rate, cap=None):
-        st = self.stats()
-        N = st.n_scored
-        cap = N if cap is None else int(cap)
+        if cap is None:
+            cap = self._select_count(keep_rate)
+        cap = int(cap)
         out = self.torch.empty(max(cap, 1), dtype=self.torch.int64, device="cuda")
         m = C.c_int64(0)
         _check(self.L.sage_select(self.h, float(keep_rate), _ptr(out), cap, C.byref(m)), "sage_select")
@@ -245,8 +284,9 @@ class Sage:
         return out
 
     def scores(self):
-        st = self.stats()
-        out = self.torch.empty(st.n_scored, dtype=self.torch.float32, device="cuda")
+        alpha, n = C.c_void_p(0), C.c_int64(0)
+        _check(self.L.sage_scores(self.h, C.byref(alpha), C.byref(n)), "sage_scores_export")
+        out = self.torch.empty(n.value, dtype=self.torch.float32, device="cuda")
         _check(self.L.sage_scores_export(self.h, _ptr(out)), "sage_scores_export")
         return out
 

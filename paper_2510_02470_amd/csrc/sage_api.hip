@@ -19,7 +19,24 @@ enum { K_GRAM = 0, K_REDUCE, K_EIG, K_COEFF, K_REBUILD, K_INSERT, K_PROJECT, K_F
 
 }  // namespace
 
+// What a context needs from the driver besides memory. Creating and destroying it costs more than a small context's first
+// cycles (a stream and a pinned word: 100 us and more, 0.6 ms at destruction), so a few kits are kept for the next context
+// on the same device (kit_take, kit_give).
+struct SideKit {
+    hipStream_t stream = nullptr;
+    hipEvent_t mark = nullptr, side[2] = {nullptr, nullptr};
+    int* host = nullptr;  // pinned words: [0] a solve failed, [1], [2] report of the class-balanced selection
+};
+
+// Where device memory comes from (sage_set_allocator); a context keeps the pair it was created with.
+struct Allocator {
+    sage_alloc_fn alloc = nullptr;  // null: hipMalloc and hipFree
+    sage_free_fn free = nullptr;
+    void* user = nullptr;
+};
+
 struct sage_ctx {
+    Allocator mem{};
     Dims d{};
     int dtype = SAGE_F32;
     hipStream_t st = nullptr;
@@ -32,6 +49,7 @@ struct sage_ctx {
     float* top = nullptr;
     float* nw[2] = {nullptr, nullptr};
     int cur = 0;
+    SideKit kit{};                               // the stream, events and host word the next five name
     hipStream_t st2 = nullptr;                   // side stream (only when the Gram has >= 2 row panels)
     hipEvent_t ev_mark = nullptr;                // context stream: the Gram matrix of the current cycle is complete
     hipEvent_t ev_side[2] = {nullptr, nullptr};  // side stream: rows stored in nw[i] and their Gram block formed
@@ -131,19 +149,46 @@ inline int hip_failed(sage_ctx* c) {
         if ((c)->h_failed && *(volatile int*)(c)->h_failed) return hip_failed(c);      \
     } while (0)
 
-#define ALLOC(ptr, bytes)                                                  \
-    do {                                                                   \
-        if (hipMalloc((void**)&(ptr), (bytes)) != hipSuccess) {            \
-            (void)hipGetLastError();                                       \
-            return SAGE_ERR_ALLOC;                                         \
-        }                                                                  \
+std::mutex g_mem_lock;
+Allocator g_mem;
+
+bool dev_alloc(const Allocator& m, hipStream_t st, void** p, size_t bytes) {
+    *p = nullptr;
+    if (m.alloc) {
+        *p = m.alloc(bytes, (void*)st, m.user);
+        return *p != nullptr;
+    }
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+}
+void dev_free(const Allocator& m, void* p) {
+    if (!p) return;
+    if (m.free) m.free(p, m.user);
+    else (void)hipFree(p);
+}
+
+// (`c` must be in scope)
+#define ALLOC(ptr, bytes)                                                                    \
+    do {                                                                                     \
+        if (!dev_alloc(c->mem, c->st, (void**)&(ptr), (bytes))) return SAGE_ERR_ALLOC;       \
+    } while (0)
+#define FREE(ptr)                       \
+    do {                                \
+        dev_free(c->mem, (void*)(ptr)); \
+        (ptr) = nullptr;                \
     } while (0)
 
 // run a launcher, optionally bracketed by events of kernel class `cls`
 template <typename F>
 int run(sage_ctx* c, int cls, F&& f) {
     if (c->fail_in > 0 && --c->fail_in == 0) return hip_failed(c);  // sage_debug_fail_launch
-    if (c->prof) HIPCHK(hipEventRecord(c->ev0, c->st));
+    if (c->prof) {
+        if (!c->ev0) HIPCHK(hipEventCreate(&c->ev0));
+        if (!c->ev1) HIPCHK(hipEventCreate(&c->ev1));
+        HIPCHK(hipEventRecord(c->ev0, c->st));
+    }
     HIPCHK(f());
     if (c->prof) {
         HIPCHK(hipEventRecord(c->ev1, c->st));
@@ -215,6 +260,55 @@ struct XcdSlot {
 constexpr int MAX_DEVICES = 64;
 std::mutex g_xcd_lock;
 XcdSlot g_xcd[MAX_DEVICES][8];
+
+constexpr int KITS_KEPT = 4;  // per device
+std::mutex g_kit_lock;
+SideKit g_kit[MAX_DEVICES][KITS_KEPT];
+int g_kits[MAX_DEVICES] = {0};
+
+void kit_destroy(SideKit& k) {
+    if (k.stream) (void)hipStreamDestroy(k.stream);
+    for (hipEvent_t e : {k.mark, k.side[0], k.side[1]})
+        if (e) (void)hipEventDestroy(e);
+    if (k.host) (void)hipHostFree(k.host);
+    k = SideKit{};
+}
+// (the current device is `device`)
+bool kit_take(int device, SideKit& k) {
+    if (device >= 0 && device < MAX_DEVICES) {
+        std::lock_guard<std::mutex> hold(g_kit_lock);
+        if (g_kits[device] > 0) {
+            k = g_kit[device][--g_kits[device]];
+            *k.host = 0;
+            return true;
+        }
+    }
+    k = SideKit{};
+    bool ok = hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking) == hipSuccess;
+    for (hipEvent_t* e : {&k.mark, &k.side[0], &k.side[1]})
+        ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipHostMalloc((void**)&k.host, 4 * sizeof(int), hipHostMallocDefault) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        kit_destroy(k);
+        return false;
+    }
+    *k.host = 0;
+    return true;
+}
+// (everything enqueued with it is complete)
+void kit_give(int device, SideKit& k, bool reuse) {
+    if (!k.stream) return;
+    if (reuse && device >= 0 && device < MAX_DEVICES) {
+        std::lock_guard<std::mutex> hold(g_kit_lock);
+        if (g_kits[device] < KITS_KEPT) {
+            g_kit[device][g_kits[device]++] = k;
+            k = SideKit{};
+            return;
+        }
+    }
+    kit_destroy(k);
+}
 
 int xcd_take(sage_ctx* c) {
     if (c->d.NP < 256 || c->device < 0 || c->device >= MAX_DEVICES) return 0;
@@ -389,8 +483,7 @@ int ensure_vblk(sage_ctx* c, int KP) {
     if (c->Vblk && c->Vblk_KP == KP) return SAGE_OK;
     if (c->Vblk) {
         HIPCHK(hipStreamSynchronize(c->st));
-        HIPCHK(hipFree(c->Vblk));
-        c->Vblk = nullptr;
+        FREE(c->Vblk);
     }
     ALLOC(c->Vblk, (size_t)c->d.S * KP * DC * sizeof(float));
     c->Vblk_KP = KP;
@@ -404,8 +497,7 @@ int ensure_images(sage_ctx* c) {
     if (need > c->Vimg_bytes) {
         if (c->Vimg) {
             HIPCHK(hipStreamSynchronize(c->st));
-            (void)hipFree(c->Vimg);
-            c->Vimg = nullptr;
+            FREE(c->Vimg);
             c->Vimg_bytes = 0;
         }
         ALLOC(c->Vimg, need);
@@ -437,23 +529,17 @@ int64_t keep_count(double keep_rate, int64_t N) {
     return m;
 }
 
-int alloc_select_work(SelectWork& w, int64_t N) {
-    int64_t nblk = (N + SELECT_BLOCK - 1) / SELECT_BLOCK;
-    if (nblk < 1) nblk = 1;
-    ALLOC(w.hist, 256 * sizeof(uint32_t));
-    ALLOC(w.state, 4 * sizeof(uint32_t));
-    ALLOC(w.blk_gt, (size_t)nblk * sizeof(uint32_t));
-    ALLOC(w.blk_eq, (size_t)nblk * sizeof(uint32_t));
-    w.nblk_cap = nblk;
-    return SAGE_OK;
-}
-
-void free_select_work(SelectWork& w) {
-    if (w.hist) (void)hipFree(w.hist);
-    if (w.state) (void)hipFree(w.state);
-    if (w.blk_gt) (void)hipFree(w.blk_gt);
-    if (w.blk_eq) (void)hipFree(w.blk_eq);
-    w = SelectWork{};
+// one allocation: histograms, state, counters
+int64_t select_blocks(int64_t N) { return N > 0 ? (N + SELECT_BLOCK - 1) / SELECT_BLOCK : 1; }
+size_t select_work_bytes(int64_t N) { return ((size_t)TOPM_HIST_WORDS + 64 + 2 * (size_t)select_blocks(N)) * sizeof(uint32_t); }
+SelectWork select_work_layout(void* p, int64_t N) {
+    SelectWork w{};
+    w.nblk_cap = select_blocks(N);
+    w.hist = (uint32_t*)p;
+    w.state = w.hist + TOPM_HIST_WORDS;
+    w.blk_gt = w.state + 64;
+    w.blk_eq = w.blk_gt + w.nblk_cap;
+    return w;
 }
 
 }  // namespace
@@ -472,6 +558,15 @@ const char* sage_strerror(int code) {
     }
 }
 
+int sage_set_allocator(sage_alloc_fn alloc, sage_free_fn free_, void* user) {
+    if ((alloc == nullptr) != (free_ == nullptr)) return SAGE_ERR_ARG;
+    std::lock_guard<std::mutex> hold(g_mem_lock);
+    g_mem.alloc = alloc;
+    g_mem.free = free_;
+    g_mem.user = user;
+    return SAGE_OK;
+}
+
 int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64_t max_rows, void* hip_stream) {
     if (!out) return SAGE_ERR_ARG;
     *out = nullptr;
@@ -488,14 +583,19 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     c->d.Dp = c->d.S * DC;
     c->dtype = in_dtype;
     c->st = (hipStream_t)hip_stream;
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
         delete c;
         return SAGE_ERR_HIP;
     }
     c->device = dev;
-    c->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+    c->num_cu = cus > 0 ? cus : 256;
+    {
+        std::lock_guard<std::mutex> hold(g_mem_lock);
+        c->mem = g_mem;
+    }
     const int P = c->d.NP / 64;
     c->gp = gram_plan(c->d, c->num_cu, 0, false, 2);
     c->gp_skip = gram_plan(c->d, c->num_cu, 0, P >= 2, 2);
@@ -518,12 +618,11 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     };
     const int NP = c->d.NP;
     size_t hbytes = (size_t)c->d.S * c->d.LP * DC * sizeof(float);  // one half buffer
+    if (!kit_take(dev, c->kit)) return fail(SAGE_ERR_HIP);
+    c->h_failed = c->kit.host;
 #define CALLOC(ptr, bytes)                                                        \
     do {                                                                          \
-        if (hipMalloc((void**)&(ptr), (bytes)) != hipSuccess) {                   \
-            (void)hipGetLastError();                                              \
-            return fail(SAGE_ERR_ALLOC);                                          \
-        }                                                                         \
+        if (!dev_alloc(c->mem, c->st, (void**)&(ptr), (bytes))) return fail(SAGE_ERR_ALLOC); \
     } while (0)
     CALLOC(c->top, hbytes);
     CALLOC(c->nw[0], hbytes);
@@ -539,10 +638,9 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
                                                                                 : c->gp_new2.partial_floats;
         CALLOC(c->gram_partial_new[0], pn * sizeof(float));
         CALLOC(c->gram_partial_new[1], pn * sizeof(float));
-        if (hipStreamCreateWithFlags(&c->st2, hipStreamNonBlocking) != hipSuccess) return fail(SAGE_ERR_HIP);
-        if (hipEventCreateWithFlags(&c->ev_mark, hipEventDisableTiming) != hipSuccess) return fail(SAGE_ERR_HIP);
-        for (int i = 0; i < 2; ++i)
-            if (hipEventCreateWithFlags(&c->ev_side[i], hipEventDisableTiming) != hipSuccess) return fail(SAGE_ERR_HIP);
+        c->st2 = c->kit.stream;
+        c->ev_mark = c->kit.mark;
+        for (int i = 0; i < 2; ++i) c->ev_side[i] = c->kit.side[i];
     }
     {
         // work space of the eigensolve: one allocation, every array on a multiple of 256 bytes
@@ -580,12 +678,6 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     if (hipMemsetAsync(c->acc, 0, 8 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->ew.stat, 0, 32 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->ew.xch, 0, (size_t)4 * NP * sizeof(u32x4), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
-    if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) return fail(SAGE_ERR_HIP);
-    if (hipHostMalloc((void**)&c->h_failed, sizeof(int), hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(SAGE_ERR_ALLOC);
-    }
-    *c->h_failed = 0;
     *out = c;
     return SAGE_OK;
 }
@@ -599,15 +691,10 @@ void sage_destroy(sage_ctx* c) {
     void* ptrs[] = {c->top,     c->nw[0],    c->nw[1],  c->gram_partial, c->gram_partial_new[0], c->gram_partial_new[1],
                     c->eig_mem, c->Mt,       c->acc,    c->Vblk,         c->Vimg,
                     c->zhat,    c->proj_partial, c->cons_partial, c->ssum, c->alpha, c->labels, c->cb_work, c->stage, c->Mt3, c->dbg_count};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
-    if (c->st2) (void)hipStreamDestroy(c->st2);
+    for (void* p : ptrs) dev_free(c->mem, p);
     xcd_release(c);
-    if (c->h_failed) (void)hipHostFree(c->h_failed);
-    hipEvent_t evs[] = {c->ev_mark, c->ev_side[0], c->ev_side[1]};
-    for (hipEvent_t e : evs)
-        if (e) (void)hipEventDestroy(e);
-    free_select_work(c->sw);
+    kit_give(c->device, c->kit, !c->poisoned);
+    dev_free(c->mem, c->sw.hist);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     delete c;
@@ -800,8 +887,7 @@ static int ensure_partial(sage_ctx* c, size_t need) {
     if (need <= c->proj_partial_floats) return SAGE_OK;
     if (c->proj_partial) {
         HIPCHK(hipStreamSynchronize(c->st));
-        (void)hipFree(c->proj_partial);
-        c->proj_partial = nullptr;
+        FREE(c->proj_partial);
         c->proj_partial_floats = 0;
     }
     size_t want = (size_t)512 * 128 * 128 > need ? (size_t)512 * 128 * 128 : need;
@@ -815,8 +901,7 @@ static int ensure_stage(sage_ctx* c, size_t need) {
     if (need <= c->stage_bytes) return SAGE_OK;
     if (c->stage) {
         HIPCHK(hipStreamSynchronize(c->st));
-        (void)hipFree(c->stage);
-        c->stage = nullptr;
+        FREE(c->stage);
         c->stage_bytes = 0;
     }
     ALLOC(c->stage, need);
@@ -904,10 +989,10 @@ static int score_impl(sage_ctx* c, RowSrc g, const int* labels, int64_t rows) {
         if (hipMemcpyAsync(nz, c->zhat, (size_t)c->n_scored * c->k * sizeof(float), hipMemcpyDeviceToDevice, c->st) !=
                 hipSuccess ||
             hipStreamSynchronize(c->st) != hipSuccess) {
-            (void)hipFree(nz);
+            FREE(nz);
             return hip_failed(c);
         }
-        (void)hipFree(c->zhat);
+        FREE(c->zhat);
         c->zhat = nz;
         if (c->labels) {
             int* nl = nullptr;
@@ -915,10 +1000,10 @@ static int score_impl(sage_ctx* c, RowSrc g, const int* labels, int64_t rows) {
             if (hipMemcpyAsync(nl, c->labels, (size_t)c->n_scored * sizeof(int), hipMemcpyDeviceToDevice, c->st) !=
                     hipSuccess ||
                 hipStreamSynchronize(c->st) != hipSuccess) {
-                (void)hipFree(nl);
+                FREE(nl);
                 return hip_failed(c);
             }
-            (void)hipFree(c->labels);
+            FREE(c->labels);
             c->labels = nl;
         }
         c->cap_rows = ncap;
@@ -948,21 +1033,26 @@ static int score_impl(sage_ctx* c, RowSrc g, const int* labels, int64_t rows) {
 static int ensure_alpha(sage_ctx* c, int64_t N) {
     if (N <= c->alpha_cap) return SAGE_OK;
     float* na = nullptr;
+    void* work = nullptr;
     int64_t ncap = N > c->cap_rows ? N : c->cap_rows;
     ALLOC(na, (size_t)ncap * sizeof(float));
+    if (!dev_alloc(c->mem, c->st, &work, select_work_bytes(ncap))) {
+        FREE(na);
+        return SAGE_ERR_ALLOC;
+    }
     if (c->alpha) {
         // keep what a running rescoring pass has written
         if (hipMemcpyAsync(na, c->alpha, (size_t)c->alpha_cap * sizeof(float), hipMemcpyDeviceToDevice, c->st) != hipSuccess ||
             hipStreamSynchronize(c->st) != hipSuccess) {
-            (void)hipFree(na);
+            FREE(na);
+            FREE(work);
             return hip_failed(c);
         }
-        (void)hipFree(c->alpha);
+        FREE(c->alpha);
+        FREE(c->sw.hist);
     }
     c->alpha = na;
-    free_select_work(c->sw);
-    int rc = alloc_select_work(c->sw, ncap);
-    if (rc != SAGE_OK) return rc;
+    c->sw = select_work_layout(work, ncap);
     c->alpha_cap = ncap;
     return SAGE_OK;
 }
@@ -1055,43 +1145,47 @@ int sage_select_cb_ex(sage_ctx* c, double keep_rate, int n_classes, int rule, in
     if (need > c->cb_work_bytes) {
         if (c->cb_work) {
             HIPCHK(hipStreamSynchronize(c->st));
-            (void)hipFree(c->cb_work);
-            c->cb_work = nullptr;
+            FREE(c->cb_work);
             c->cb_work_bytes = 0;
         }
         ALLOC(c->cb_work, need);
         c->cb_work_bytes = need;
     }
     const CbWork w = cb_work_layout(c->cb_work, n_classes, N);
-    RUN(K_SELECT, launch_cb_scores(c->zhat, c->labels, N, c->k, n_classes, keep_rate, rule, c->alpha, w, c->st));
+    uint32_t* report = (uint32_t*)c->kit.host + 1;
+    RUN(K_SELECT, launch_cb_select(c->zhat, c->labels, N, c->k, n_classes, keep_rate, rule, c->alpha, cap, out_idx, report, w,
+                                   c->st));
     c->alpha_n = N;
-    uint32_t misc[2] = {0, 0};
-    HIPCHK(hipMemcpyAsync(misc, w.misc, sizeof(misc), hipMemcpyDeviceToHost, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
-    if (misc[1]) return SAGE_ERR_ARG;  // a label outside [0, n_classes)
-    const int64_t m = (int64_t)misc[0];
+    if (((volatile uint32_t*)report)[1]) return SAGE_ERR_ARG;  // a label outside [0, n_classes)
+    const int64_t m = (int64_t)((volatile uint32_t*)report)[0];
     *out_m = m;
     if (m > cap) return SAGE_ERR_CAPACITY;
     if (m > 0 && !out_idx) return SAGE_ERR_ARG;
-    if (m > 0) RUN(K_SELECT, launch_cb_select(c->alpha, c->labels, N, n_classes, out_idx, w, c->st));
-    HIPCHK(hipStreamSynchronize(c->st));
     return SAGE_OK;
 }
 
 int sage_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* hip_stream) {
     if (N < 0 || m < 0 || m > N || (N > 0 && !alpha) || (m > 0 && !out_idx)) return SAGE_ERR_ARG;
     if (m == 0) return SAGE_OK;
-    SelectWork w{};
-    int rc = alloc_select_work(w, N);
-    if (rc != SAGE_OK) {
-        free_select_work(w);
-        return rc;
-    }
     hipStream_t st = (hipStream_t)hip_stream;
+    Allocator mem;
+    {
+        std::lock_guard<std::mutex> hold(g_mem_lock);
+        mem = g_mem;
+    }
+    SelectWork w{};
+    if (topm_needs_work(N)) {
+        void* p = nullptr;
+        if (!dev_alloc(mem, st, &p, select_work_bytes(N))) return SAGE_ERR_ALLOC;
+        w = select_work_layout(p, N);
+    }
     hipError_t e = launch_topm(alpha, N, m, out_idx, w, st);
     hipError_t e2 = hipStreamSynchronize(st);
-    free_select_work(w);
-    return (e == hipSuccess && e2 == hipSuccess) ? SAGE_OK : SAGE_ERR_HIP;
+    dev_free(mem, w.hist);
+    if (e == hipSuccess && e2 == hipSuccess) return SAGE_OK;
+    (void)hipGetLastError();
+    return SAGE_ERR_HIP;
 }
 
 int sage_fd_sketch_export(sage_ctx* c, float* B_out) {

@@ -219,36 +219,36 @@ hipError_t launch_project_outer(const void* E, const void* H, int dtype, int64_t
 // select.hip
 hipError_t launch_cosine(const float* zhat, int64_t N, int k, const double* ssum, float* alpha, hipStream_t st);
 struct SelectWork {
-    uint32_t* hist;      // 256 bins
-    uint32_t* state;     // [0] prefix key, [1] remaining m, [2] count greater, [3] ties to take
+    uint32_t* hist;      // TOPM_HIST_WORDS: one histogram per digit
+    uint32_t* state;     // 8: {prefix key, count left} after each digit
     uint32_t* blk_gt;    // per block: count of keys > threshold
     uint32_t* blk_eq;    // per block: count of keys == threshold
     int64_t nblk_cap;
 };
-constexpr int SELECT_BLOCK = 2048;  // keys per block in the compaction passes
+constexpr int TOPM_HIST_WORDS = 4096 + 2 * 1024;
+constexpr int SELECT_BLOCK = 4096;  // keys per block in the compaction passes
+bool topm_needs_work(int64_t N);    // false: launch_topm uses no work space
 hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w,
                        hipStream_t st);
 
 // select_cb.hip: class-balanced selection (per-class centroid, cosine to it, top k_c of every class)
 struct CbWork {
     long long* sums;   // C x 128 fixed-point class sums of zhat
-    double* ucls;      // C x 128 unit centroids
     uint32_t* counts;  // rows per class
     uint32_t* kc;      // rows kept per class
-    uint32_t* prefix;  // radix-select state: key prefix decided so far (after the index phase: index threshold)
-    uint32_t* remain;  // ... keys still to take among those matching the prefix
-    uint32_t* thr;     // score-key threshold per class
-    uint32_t* hist;    // C x 256 bins
+    uint32_t* start;   // first place of the class in ord
+    uint32_t* cursor;  // ... next free one
     uint32_t* misc;    // [0] total kept, [1] a label was out of range
-    uint32_t* blk;     // per block of SELECT_BLOCK rows: rows kept (then their exclusive scan)
+    uint32_t* blk;     // per block of SELECT_BLOCK rows: rows kept
+    uint32_t* ord;     // the rows, class after class
+    uint32_t* skey;    // their score keys, in that order
     uint8_t* sel;      // per row: kept
 };
 size_t cb_work_bytes(int C, int64_t N);
 CbWork cb_work_layout(void* base, int C, int64_t N);
-// rule: sage_cb_rule (how the subset size is shared out among the classes)
-hipError_t launch_cb_scores(const float* zhat, const int* labels, int64_t N, int k, int C, double keep, int rule,
-                            float* alpha, const CbWork& w, hipStream_t st);
-hipError_t launch_cb_select(const float* alpha, const int* labels, int64_t N, int C, int64_t* out_idx, const CbWork& w,
-                            hipStream_t st);
+// rule: sage_cb_rule (how the subset size is shared out among the classes). Scores to alpha; the kept rows, ascending, to
+// out_idx if there are at most cap; report (host memory the device can write): {rows kept, a label was out of range}.
+hipError_t launch_cb_select(const float* zhat, const int* labels, int64_t N, int k, int C, double keep, int rule,
+                            float* alpha, int64_t cap, int64_t* out_idx, uint32_t* report, const CbWork& w, hipStream_t st);
 
 }  // namespace sage

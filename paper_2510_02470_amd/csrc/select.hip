@@ -1,7 +1,7 @@
 // Scoring pass, second half (Algorithm 1, Phase II: "u <- zbar/||zbar||", "alpha_i <- <zhat_i, u>",
 // "Select top-k by alpha_i"): consensus direction, cosine scores, radix-select of the m-th largest score and a
 // stable compaction of the selected indices in ascending order.
-#include "sage_internal.h"
+#include "select_ops.h"
 
 namespace sage {
 
@@ -52,178 +52,208 @@ hipError_t launch_cosine(const float* zhat, int64_t N, int k, const double* ssum
     return hipGetLastError();
 }
 
-// order-preserving key: larger alpha <-> larger key; -0 and +0 share a key
-__device__ __forceinline__ uint32_t score_key(float a) {
-    uint32_t b = __float_as_uint(a);
-    if (b == 0x80000000u) b = 0u;
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
+// ---- top-m ----------------------------------------------------------------------------------------------------------
+// Radix select of the m-th largest key, 12 + 10 + 10 bits from the top, then compaction in ascending index. All the data
+// there is to move is 4 N bytes, so what counts is the number of launches (about 3 us each with its gap) and serial work
+// inside them:
+//   N <= TOPM_ONE: one work-group does everything, keys in registers, histograms in LDS; one launch, no work space;
+//   else: clear, three histograms, count, emit. Every work-group of the next kernel reads the histogram and finds the
+//         digit itself (a scan over the bins by 1024 threads), so there are no kernels between them.
+// The first digit has 12 bits because scores crowd into a few binary orders of magnitude: with 8 bits most lanes of a wave
+// add to one of two or three LDS words and the adds are done one after the other.
+// (One digit of 8 bits per launch with a one-thread pick kernel after each took 13 launches: 86 us at N = 2048 and 80 us at
+// a million, host and waiting included.)
+constexpr int BINS1 = 4096, BINS2 = 1024;
+constexpr int TOPM_T = 1024;  // threads of every kernel below
 
-// state: [0] prefix of the threshold key decided so far, [1] how many keys are still to be taken among those
-// that match the prefix, [2] scratch, [3] scratch
-__global__ void select_init_kernel(uint32_t* __restrict__ hist, uint32_t* __restrict__ state, uint32_t m) {
-    int t = threadIdx.x;
-    if (t < 256) hist[t] = 0;
-    if (t == 0) { state[0] = 0; state[1] = m; state[2] = 0; state[3] = 0; }
-}
-
-// histogram of byte `shift/8` of the keys whose higher bytes equal the prefix
-__global__ __launch_bounds__(256) void select_hist_kernel(const float* __restrict__ alpha, int64_t N, int shift,
-                                                          const uint32_t* __restrict__ state,
-                                                          uint32_t* __restrict__ hist) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t prefix = state[0];
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 256) {
-        uint32_t key = score_key(alpha[i]);
-        bool match = (shift == 24) ? true : ((key >> (shift + 8)) == prefix);
-        if (match) atomicAdd(&h[(key >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    uint32_t v = h[threadIdx.x];
-    if (v) atomicAdd(&hist[threadIdx.x], v);
-}
-
-// walk the bins from the top until the remaining count is covered; extend the prefix; clear the histogram
-__global__ void select_pick_kernel(uint32_t* __restrict__ hist, uint32_t* __restrict__ state) {
-    if (threadIdx.x == 0) {
-        uint32_t remaining = state[1];
-        uint32_t cum = 0;
-        int chosen = 0;
-        for (int b = 255; b >= 0; --b) {
-            uint32_t c = hist[b];
-            if (cum + c >= remaining) { chosen = b; break; }
-            cum += c;
-        }
-        state[0] = (state[0] << 8) | (uint32_t)chosen;
-        state[1] = remaining - cum;
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-}
-
-// per block of SELECT_BLOCK keys: how many are above / equal to the threshold key
-__global__ __launch_bounds__(256) void select_count_kernel(const float* __restrict__ alpha, int64_t N,
-                                                           const uint32_t* __restrict__ state,
-                                                           uint32_t* __restrict__ blk_gt, uint32_t* __restrict__ blk_eq) {
-    __shared__ uint32_t sg[256], se[256];
-    const uint32_t T = state[0];
-    int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK + (int64_t)threadIdx.x * 8;
-    uint32_t g = 0, e = 0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        int64_t i = base + c;
-        if (i < N) {
-            uint32_t key = score_key(alpha[i]);
-            g += key > T;
-            e += key == T;
-        }
-    }
-    sg[threadIdx.x] = g;
-    se[threadIdx.x] = e;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) { sg[threadIdx.x] += sg[threadIdx.x + w]; se[threadIdx.x] += se[threadIdx.x + w]; }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) { blk_gt[blockIdx.x] = sg[0]; blk_eq[blockIdx.x] = se[0]; }
-}
-
-// exclusive scan of the per-block counts, in place (single work-group, sequential over chunks of 256 blocks)
-__global__ __launch_bounds__(256) void select_scan_kernel(uint32_t* __restrict__ blk_gt, uint32_t* __restrict__ blk_eq,
-                                                          int nblk) {
-    __shared__ uint32_t sg[256], se[256];
-    uint32_t carry_g = 0, carry_e = 0;
-    for (int base = 0; base < nblk; base += 256) {
-        int i = base + threadIdx.x;
-        uint32_t g = i < nblk ? blk_gt[i] : 0, e = i < nblk ? blk_eq[i] : 0;
-        sg[threadIdx.x] = g;
-        se[threadIdx.x] = e;
-        __syncthreads();
-        for (int o = 1; o < 256; o <<= 1) {  // Hillis-Steele inclusive scan
-            uint32_t ag = 0, ae = 0;
-            if ((int)threadIdx.x >= o) { ag = sg[threadIdx.x - o]; ae = se[threadIdx.x - o]; }
-            __syncthreads();
-            sg[threadIdx.x] += ag;
-            se[threadIdx.x] += ae;
-            __syncthreads();
-        }
-        if (i < nblk) {
-            blk_gt[i] = carry_g + sg[threadIdx.x] - g;
-            blk_eq[i] = carry_e + se[threadIdx.x] - e;
-        }
-        uint32_t tg = sg[255], te = se[255];
-        __syncthreads();
-        carry_g += tg;
-        carry_e += te;
-    }
-}
-
-// element i is kept when key > T, or key == T and fewer than `take` equal keys precede it; its output slot is
-// (#greater before i) + min(#equal before i, take), which makes the output ascending in i.
-__global__ __launch_bounds__(256) void select_emit_kernel(const float* __restrict__ alpha, int64_t N,
-                                                          const uint32_t* __restrict__ state,
-                                                          const uint32_t* __restrict__ blk_gt,
-                                                          const uint32_t* __restrict__ blk_eq,
+// one work-group, N <= 1024 C
+template <int C>
+__global__ __launch_bounds__(TOPM_T) void topm_one_kernel(const float* __restrict__ alpha, int N, uint32_t m,
                                                           int64_t* __restrict__ out_idx) {
-    __shared__ uint32_t sg[256], se[256];
-    const uint32_t T = state[0], take = state[1];
-    int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK + (int64_t)threadIdx.x * 8;
-    uint32_t keys[8];
+    static_assert(C <= 32, "emit_keys packs counts of 16 bits");
+    __shared__ uint32_t h[BINS1 + 2 * BINS2];
+    __shared__ uint32_t cnt[16 * C], tot[16];
+    __shared__ PickWork pw;
+    const int tid = threadIdx.x;
+    uint32_t key[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int i = c * TOPM_T + tid;
+        key[c] = i < N ? score_key(alpha[i]) : 0u;
+    }
+    for (int b = tid; b < BINS1 + 2 * BINS2; b += TOPM_T) h[b] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if (c * TOPM_T + tid < N) atomicAdd(&h[key[c] >> 20], 1u);
+    __syncthreads();
+    uint32_t d1, d2, d3, rest;
+    pick_bin<TOPM_T, BINS1>(h, m, pw, d1, rest);
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if (c * TOPM_T + tid < N && (key[c] >> 20) == d1) atomicAdd(&h[BINS1 + ((key[c] >> 10) & 1023u)], 1u);
+    __syncthreads();
+    pick_bin<TOPM_T, BINS2>(h + BINS1, rest, pw, d2, rest);
+    const uint32_t p2 = (d1 << 10) | d2;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if (c * TOPM_T + tid < N && (key[c] >> 10) == p2) atomicAdd(&h[BINS1 + BINS2 + (key[c] & 1023u)], 1u);
+    __syncthreads();
+    pick_bin<TOPM_T, BINS2>(h + BINS1 + BINS2, rest, pw, d3, rest);
+    emit_keys<TOPM_T, C>(key, 0, (p2 << 10) | d3, rest, 0u, 0u, cnt, tot, out_idx);
+}
+
+// hist: BINS1 + 2 BINS2 words
+__global__ __launch_bounds__(TOPM_T) void topm_clear_kernel(uint32_t* __restrict__ hist) {
+    hist[blockIdx.x * TOPM_T + threadIdx.x] = 0;
+}
+
+// Histogram of digit P (0: bits 31..20, 1: bits 19..10, 2: bits 9..0) of the keys that share the digits found so far.
+// state[2 (P - 1)], state[2 (P - 1) + 1]: the prefix and the count left, found from the previous histogram, left for the
+// next kernel.
+template <int P>
+__global__ __launch_bounds__(TOPM_T) void topm_hist_kernel(const float* __restrict__ alpha, int64_t N, uint32_t m,
+                                                           uint32_t* __restrict__ hist, uint32_t* __restrict__ state) {
+    constexpr int BINS = P == 0 ? BINS1 : BINS2;
+    __shared__ uint32_t h[BINS];
+    __shared__ PickWork pw;
+    const int tid = threadIdx.x;
+    for (int b = tid; b < BINS; b += TOPM_T) h[b] = 0;
+    uint32_t prefix = 0;
+    if constexpr (P > 0) {
+        uint32_t digit, rest;
+        if constexpr (P == 1) {
+            pick_bin<TOPM_T, BINS1>(hist, m, pw, digit, rest);
+            prefix = digit;
+        } else {
+            pick_bin<TOPM_T, BINS2>(hist + BINS1, state[1], pw, digit, rest);
+            prefix = (state[0] << 10) | digit;
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            state[2 * (P - 1)] = prefix;
+            state[2 * (P - 1) + 1] = rest;
+        }
+    } else {
+        __syncthreads();
+    }
+    const int64_t stride = (int64_t)gridDim.x * TOPM_T;
+    for (int64_t i0 = (int64_t)blockIdx.x * TOPM_T + tid; i0 < N; i0 += 4 * stride) {
+        float a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = i0 + u * stride < N ? alpha[i0 + u * stride] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t key = score_key(a[u]);
+            if (i0 + u * stride >= N) continue;
+            if (P == 0) atomicAdd(&h[key >> 20], 1u);
+            if (P == 1 && (key >> 20) == prefix) atomicAdd(&h[(key >> 10) & 1023u], 1u);
+            if (P == 2 && (key >> 10) == prefix) atomicAdd(&h[key & 1023u], 1u);
+        }
+    }
+    __syncthreads();
+    uint32_t* g = hist + (P == 0 ? 0 : P == 1 ? BINS1 : BINS1 + BINS2);
+    for (int b = tid; b < BINS; b += TOPM_T)
+        if (const uint32_t v = h[b]) atomicAdd(&g[b], v);
+}
+
+// per block of SELECT_BLOCK keys: how many are above / equal to the threshold key, which goes to state[4], state[5]
+__global__ __launch_bounds__(TOPM_T) void topm_count_kernel(const float* __restrict__ alpha, int64_t N,
+                                                            const uint32_t* __restrict__ hist, uint32_t* __restrict__ state,
+                                                            uint32_t* __restrict__ blk_gt, uint32_t* __restrict__ blk_eq) {
+    constexpr int C = SELECT_BLOCK / TOPM_T;
+    __shared__ PickWork pw;
+    __shared__ uint32_t sg, se;
+    const int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK + threadIdx.x;
+    uint32_t key[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) key[c] = base + c * TOPM_T < N ? score_key(alpha[base + c * TOPM_T]) : 0u;
+    if (threadIdx.x == 0) sg = se = 0;
+    uint32_t digit, rest;
+    pick_bin<TOPM_T, BINS2>(hist + BINS1 + BINS2, state[3], pw, digit, rest);
+    const uint32_t T = (state[2] << 10) | digit;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        state[4] = T;
+        state[5] = rest;
+    }
     uint32_t g = 0, e = 0;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        int64_t i = base + c;
-        keys[c] = 0;
-        if (i < N) {
-            keys[c] = score_key(alpha[i]);
-            g += keys[c] > T;
-            e += keys[c] == T;
-        }
+    for (int c = 0; c < C; ++c) {
+        const bool in = base + c * TOPM_T < N;
+        g += (uint32_t)__popcll(__ballot(in && key[c] > T));
+        e += (uint32_t)__popcll(__ballot(in && key[c] == T));
     }
-    sg[threadIdx.x] = g;
-    se[threadIdx.x] = e;
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&sg, g);
+        atomicAdd(&se, e);
+    }
     __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        uint32_t ag = 0, ae = 0;
-        if ((int)threadIdx.x >= o) { ag = sg[threadIdx.x - o]; ae = se[threadIdx.x - o]; }
-        __syncthreads();
-        sg[threadIdx.x] += ag;
-        se[threadIdx.x] += ae;
-        __syncthreads();
-    }
-    uint32_t gt_before = blk_gt[blockIdx.x] + sg[threadIdx.x] - g;
-    uint32_t eq_before = blk_eq[blockIdx.x] + se[threadIdx.x] - e;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        int64_t i = base + c;
-        if (i >= N) break;
-        bool isg = keys[c] > T, ise = keys[c] == T;
-        if (isg || (ise && eq_before < take)) {
-            uint32_t slot = gt_before + (eq_before < take ? eq_before : take);
-            out_idx[slot] = i;
-        }
-        gt_before += isg;
-        eq_before += ise;
+    if (threadIdx.x == 0) {
+        blk_gt[blockIdx.x] = sg;
+        blk_eq[blockIdx.x] = se;
     }
 }
+
+// every work-group adds up the counts of the blocks before its own (at most 4096 of them for 16.7 million keys)
+__global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restrict__ alpha, int64_t N,
+                                                           const uint32_t* __restrict__ state,
+                                                           const uint32_t* __restrict__ blk_gt,
+                                                           const uint32_t* __restrict__ blk_eq,
+                                                           int64_t* __restrict__ out_idx) {
+    constexpr int C = SELECT_BLOCK / TOPM_T;
+    __shared__ uint32_t cnt[16 * C], tot[16], sg, se;
+    const int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK;
+    uint32_t key[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int64_t i = base + c * TOPM_T + threadIdx.x;
+        key[c] = i < N ? score_key(alpha[i]) : 0u;
+    }
+    if (threadIdx.x == 0) sg = se = 0;
+    uint32_t g = 0, e = 0;
+    for (unsigned b = threadIdx.x; b < blockIdx.x; b += TOPM_T) {
+        g += blk_gt[b];
+        e += blk_eq[b];
+    }
+    g = wave_scan(g);
+    e = wave_scan(e);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 63 && (g | e)) {
+        atomicAdd(&sg, g);
+        atomicAdd(&se, e);
+    }
+    __syncthreads();
+    emit_keys<TOPM_T, C>(key, base, state[4], state[5], sg, se, cnt, tot, out_idx);
+}
+
+// One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of six launches wins.
+constexpr int64_t TOPM_ONE = 32 * TOPM_T;
+
+bool topm_needs_work(int64_t N) { return N > TOPM_ONE; }
 
 hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w,
                        hipStream_t st) {
     if (m <= 0 || N <= 0) return hipSuccess;
-    int64_t nblk = (N + SELECT_BLOCK - 1) / SELECT_BLOCK;
-    if (nblk > w.nblk_cap) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(256), 0, st, w.hist, w.state, (uint32_t)m);
-    int64_t hb = (N + 255) / 256;
-    if (hb > 1024) hb = 1024;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(select_hist_kernel, dim3((unsigned)hb), dim3(256), 0, st, alpha, N, shift, w.state, w.hist);
-        hipLaunchKernelGGL(select_pick_kernel, dim3(1), dim3(256), 0, st, w.hist, w.state);
+    if (N <= TOPM_ONE) {
+#define SAGE_ONE(C) \
+    hipLaunchKernelGGL(topm_one_kernel<C>, dim3(1), dim3(TOPM_T), 0, st, alpha, (int)N, (uint32_t)m, out_idx)
+        if (N <= 2 * TOPM_T) SAGE_ONE(2);
+        else if (N <= 4 * TOPM_T) SAGE_ONE(4);
+        else if (N <= 8 * TOPM_T) SAGE_ONE(8);
+        else if (N <= 16 * TOPM_T) SAGE_ONE(16);
+        else SAGE_ONE(32);
+#undef SAGE_ONE
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(select_count_kernel, dim3((unsigned)nblk), dim3(256), 0, st, alpha, N, w.state, w.blk_gt, w.blk_eq);
-    hipLaunchKernelGGL(select_scan_kernel, dim3(1), dim3(256), 0, st, w.blk_gt, w.blk_eq, (int)nblk);
-    hipLaunchKernelGGL(select_emit_kernel, dim3((unsigned)nblk), dim3(256), 0, st, alpha, N, w.state, w.blk_gt, w.blk_eq,
+    const int64_t nblk = (N + SELECT_BLOCK - 1) / SELECT_BLOCK;
+    if (nblk > w.nblk_cap) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(topm_clear_kernel, dim3(TOPM_HIST_WORDS / TOPM_T), dim3(TOPM_T), 0, st, w.hist);
+    const dim3 hb((unsigned)(nblk < 512 ? nblk : 512));
+    hipLaunchKernelGGL(topm_hist_kernel<0>, hb, dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
+    hipLaunchKernelGGL(topm_hist_kernel<1>, hb, dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
+    hipLaunchKernelGGL(topm_hist_kernel<2>, hb, dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
+    hipLaunchKernelGGL(topm_count_kernel, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.hist, w.state, w.blk_gt,
+                       w.blk_eq);
+    hipLaunchKernelGGL(topm_emit_kernel, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.state, w.blk_gt, w.blk_eq,
                        out_idx);
     return hipGetLastError();
 }

@@ -7,65 +7,193 @@
 // Everything that decides the result is integer work, so the outcome does not depend on timing:
 //   * class sums are accumulated in 64-bit fixed point (zhat * 2^40, |zhat| <= 1, up to 2^23 rows per class) with
 //     integer atomics -- addition of integers is associative, unlike floating point;
-//   * the k_c-th largest score of every class comes from one radix select run for all classes at once (a 256-bin
-//     histogram per class and byte, four passes over order-preserving 32-bit keys);
-//   * ties at a class threshold go to the lowest row indices: a second radix select, over the row index, among the
-//     rows that sit exactly on their class threshold;
-//   * the selected rows are compacted in ascending row order (per-block counts, scan, emit).
-#include "sage_internal.h"
+//   * the k_c largest of a class are found by rank or radix select on order-preserving 32-bit keys, ties at the threshold
+//     going to the lowest row indices;
+//   * the selected rows are compacted in ascending row order (per-block counts, emit).
+//
+// The rows are listed by class first (count, scan, scatter; the order inside a class is arbitrary). Then a wave sums 32 rows
+// of one class in registers before it touches memory (an atomic per row and coordinate was 66 us at 20,000 rows), and a
+// work-group has a whole class to select from: one launch where a histogram and a pick per byte and for all classes at
+// once were 17 (of 21 us each for the picks). Nine launches and one wait in all.
+#include <type_traits>
+
+#include "select_ops.h"
 
 namespace sage {
 
 constexpr double CB_SCALE = 1099511627776.0;  // 2^40
-
-__device__ __forceinline__ uint32_t cb_key(float a) {  // larger alpha <-> larger key; -0 and +0 share a key
-    uint32_t b = __float_as_uint(a);
-    if (b == 0x80000000u) b = 0u;
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
+constexpr int CB_LDS_CLASSES = 4096;          // up to here a work-group counts its rows in LDS before it counts in memory
 
 __global__ __launch_bounds__(256) void cb_zero_kernel(uint32_t* __restrict__ counts, long long* __restrict__ sums,
-                                                      uint32_t* __restrict__ hist, uint32_t* __restrict__ misc, int C) {
+                                                      uint32_t* __restrict__ misc, int C) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < C) counts[i] = 0;
     if (i < (int64_t)C * 128) sums[i] = 0;
-    if (i < (int64_t)C * 256) hist[i] = 0;
     if (i < 4) misc[i] = 0;  // [0] total kept, [1] a label was out of range
 }
 
-// one wave per row: count the row for its class and add its zhat to the class sum (fixed point)
-__global__ __launch_bounds__(256) void cb_accumulate_kernel(const float* __restrict__ zhat, const int* __restrict__ labels,
-                                                            int64_t N, int k, int C, uint32_t* __restrict__ counts,
-                                                            long long* __restrict__ sums, uint32_t* __restrict__ misc) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < N; r += (int64_t)gridDim.x * 4) {
-        const int c = labels[r];
-        if (c < 0 || c >= C) {
-            if (lane == 0) misc[1] = 1;
-            continue;
+// rows per class
+__global__ __launch_bounds__(1024) void cb_count_kernel(const int* __restrict__ labels, int64_t N, int C,
+                                                        uint32_t* __restrict__ counts, uint32_t* __restrict__ misc) {
+    __shared__ uint32_t h[CB_LDS_CLASSES];
+    const bool lds = C <= CB_LDS_CLASSES;
+    if (lds)
+        for (int c = threadIdx.x; c < C; c += 1024) h[c] = 0;
+    __syncthreads();
+    for (int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 1024) {
+        const int c = labels[i];
+        if (c < 0 || c >= C) misc[1] = 1;
+        else if (lds) atomicAdd(&h[c], 1u);
+        else atomicAdd(&counts[c], 1u);
+    }
+    __syncthreads();
+    if (lds)
+        for (int c = threadIdx.x; c < C; c += 1024)
+            if (const uint32_t v = h[c]) atomicAdd(&counts[c], v);
+}
+
+// The rows of every class, one class after the other (cursor[c]: first free place of class c). 4 rows a thread.
+__global__ __launch_bounds__(1024) void cb_scatter_kernel(const int* __restrict__ labels, int64_t N, int C,
+                                                          uint32_t* __restrict__ cursor, uint32_t* __restrict__ ord,
+                                                          float* __restrict__ alpha) {
+    __shared__ uint32_t h[CB_LDS_CLASSES];
+    const bool lds = C <= CB_LDS_CLASSES;
+    const int64_t i0 = (int64_t)blockIdx.x * 4096 + threadIdx.x;
+    int c[4];
+    uint32_t rank[4];
+    if (lds)
+        for (int j = threadIdx.x; j < C; j += 1024) h[j] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t i = i0 + u * 1024;
+        c[u] = i < N ? labels[i] : -1;
+        if (c[u] < 0 || c[u] >= C) {
+            if (i < N) alpha[i] = 0.f;  // (the call reports the label)
+            c[u] = -1;
         }
-        if (lane == 0) atomicAdd(&counts[c], 1u);
-        const float* z = zhat + r * k;
-        unsigned long long* s = reinterpret_cast<unsigned long long*>(sums + (int64_t)c * 128);
-        if (lane < k) atomicAdd(&s[lane], (unsigned long long)__double2ll_rn((double)z[lane] * CB_SCALE));
-        if (lane + 64 < k) atomicAdd(&s[lane + 64], (unsigned long long)__double2ll_rn((double)z[lane + 64] * CB_SCALE));
+        rank[u] = c[u] < 0 ? 0u : (lds ? atomicAdd(&h[c[u]], 1u) : atomicAdd(&cursor[c[u]], 1u));
+    }
+    if (lds) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < C; j += 1024)
+            if (const uint32_t v = h[j]) h[j] = atomicAdd(&cursor[j], v);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (c[u] >= 0) ord[(lds ? h[c[u]] : 0u) + rank[u]] = (uint32_t)(i0 + u * 1024);
+}
+
+constexpr int CB_RUN = 32;  // listed rows a wave goes through
+
+// class sums, fixed point
+__global__ __launch_bounds__(256) void cb_sum_kernel(const float* __restrict__ zhat, const int* __restrict__ labels,
+                                                     const uint32_t* __restrict__ ord, int64_t N, int k, int C,
+                                                     long long* __restrict__ sums, const uint32_t* __restrict__ misc) {
+    if (misc[1]) return;  // (fewer than N rows are listed)
+    const int lane = threadIdx.x & 63;
+    const int64_t p0 = ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * CB_RUN;
+    if (p0 >= N) return;
+    const int64_t left = N - p0;
+    const int cnt = left < CB_RUN ? (int)left : CB_RUN;
+    const uint32_t myrow = lane < cnt ? ord[p0 + lane] : 0u;
+    const int mycls = lane < cnt ? labels[myrow] : -1;
+    long long s0 = 0, s1 = 0;
+    for (int g = 0; g < cnt; g += 8) {
+        float z0[8], z1[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float* z = zhat + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)myrow, g + u) * k;
+            z0[u] = g + u < cnt && lane < k ? z[lane] : 0.f;
+            z1[u] = g + u < cnt && lane + 64 < k ? z[lane + 64] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (g + u >= cnt) break;
+            s0 += __double2ll_rn((double)z0[u] * CB_SCALE);
+            s1 += __double2ll_rn((double)z1[u] * CB_SCALE);
+            const int c = __builtin_amdgcn_readlane(mycls, g + u);
+            const int next = g + u + 1 < cnt ? __builtin_amdgcn_readlane(mycls, (g + u + 1) & 63) : -1;
+            if (c != next) {
+                unsigned long long* s = reinterpret_cast<unsigned long long*>(sums + (int64_t)c * 128);
+                if (lane < k) atomicAdd(&s[lane], (unsigned long long)s0);
+                if (lane + 64 < k) atomicAdd(&s[lane + 64], (unsigned long long)s1);
+                s0 = s1 = 0;
+            }
+        }
     }
 }
 
-// one work-group per class: u_c = S_c / ||S_c|| (0 if S_c = 0)
-__global__ __launch_bounds__(128) void cb_unit_kernel(const long long* __restrict__ sums, int k,
-                                                      double* __restrict__ ucls) {
-    __shared__ double red[128];
-    const int c = blockIdx.x, j = threadIdx.x;
-    const double s = j < k ? (double)sums[(int64_t)c * 128 + j] / CB_SCALE : 0.0;
-    red[j] = s * s;
-    __syncthreads();
-    for (int w = 64; w >= 1; w >>= 1) {  // fixed-shape tree
-        if (j < w) red[j] += red[j + w];
-        __syncthreads();
+// alpha_i = clamp(<zhat_i, u_c>, -1, 1), -0 stored as +0, u_c = S_c / ||S_c|| (0 if S_c = 0), and the keys in list order
+__global__ __launch_bounds__(256) void cb_cosine_kernel(const float* __restrict__ zhat, const int* __restrict__ labels,
+                                                        const uint32_t* __restrict__ ord, int64_t N, int k, int C,
+                                                        const long long* __restrict__ sums,
+                                                        const uint32_t* __restrict__ misc, float* __restrict__ alpha,
+                                                        uint32_t* __restrict__ skey) {
+    if (misc[1]) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t p0 = ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * CB_RUN;
+    if (p0 >= N) return;
+    const int64_t left = N - p0;
+    const int cnt = left < CB_RUN ? (int)left : CB_RUN;
+    const uint32_t myrow = lane < cnt ? ord[p0 + lane] : 0u;
+    const int mycls = lane < cnt ? labels[myrow] : -1;
+    int cls = -1;
+    double u0 = 0.0, u1 = 0.0;
+    float mine = 0.f;
+    for (int g = 0; g < cnt; g += 8) {
+        float z0[8], z1[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float* z = zhat + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)myrow, g + u) * k;
+            z0[u] = g + u < cnt && lane < k ? z[lane] : 0.f;
+            z1[u] = g + u < cnt && lane + 64 < k ? z[lane + 64] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (g + u >= cnt) break;
+            const int c = __builtin_amdgcn_readlane(mycls, g + u);
+            if (c != cls) {
+                cls = c;
+                u0 = lane < k ? (double)sums[(int64_t)c * 128 + lane] / CB_SCALE : 0.0;
+                u1 = lane + 64 < k ? (double)sums[(int64_t)c * 128 + lane + 64] / CB_SCALE : 0.0;
+                double q2 = u0 * u0 + u1 * u1;
+                for (int o = 32; o >= 1; o >>= 1) q2 += __shfl_xor(q2, o);
+                const double nrm = sqrt(q2);
+                u0 = nrm > 0.0 ? u0 / nrm : 0.0;
+                u1 = nrm > 0.0 ? u1 / nrm : 0.0;
+            }
+            double a = (double)z0[u] * u0 + (double)z1[u] * u1;
+            for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
+            if (a > 1.0) a = 1.0;
+            if (a < -1.0) a = -1.0;
+            float f = (float)a;
+            if (f == 0.f) f = 0.f;
+            if (lane == g + u) mine = f;
+        }
     }
-    const double nrm = sqrt(red[0]);
-    ucls[(int64_t)c * 128 + j] = nrm > 0.0 ? s / nrm : 0.0;
+    if (lane < cnt) {
+        alpha[myrow] = mine;
+        skey[p0 + lane] = score_key(mine);
+    }
+}
+
+// exclusive scan of the class counts into start and cursor, by the 1024 threads of a work-group (every thread owns a
+// contiguous run of classes); red: 1024 words
+__device__ __forceinline__ void cb_starts(const uint32_t* __restrict__ counts, int C, uint32_t* __restrict__ start,
+                                          uint32_t* __restrict__ cursor, unsigned long long* red) {
+    const int t = threadIdx.x, chunk = (C + 1023) / 1024;
+    const int c0 = t * chunk, c1 = c0 + chunk < C ? c0 + chunk : C;
+    uint32_t sum = 0;
+    for (int c = c0; c < c1; ++c) sum += counts[c];
+    __syncthreads();
+    uint32_t at = block_scan<1024>(sum, (uint32_t*)red) - sum;
+    for (int c = c0; c < c1; ++c) {
+        start[c] = at;
+        cursor[c] = at;
+        at += counts[c];
+    }
 }
 
 // The class budgets (Algorithm 1, class-balanced branch: sum_c k_c = k). With N_c rows in class c and N in all,
@@ -73,24 +201,22 @@ __global__ __launch_bounds__(128) void cb_unit_kernel(const long long* __restric
 // m - sum_c floor(q_c) rows still to hand out go one each to the classes with the largest fractional part
 // q_c - floor(q_c) (equal parts: the lower class first) among those with k_c < N_c. All of it is exact integer or
 // correctly rounded fp64 work, so the host-side definition gives the same numbers. One work-group of 1024 threads;
-// also sets the start state of the selects (prefix 0, remain k_c) and misc[0] = sum_c k_c.
+// also sets the places of the classes in the list and misc[0] = sum_c k_c.
 __global__ __launch_bounds__(1024) void cb_quota_kernel(const uint32_t* __restrict__ counts, int C, double keep,
-                                                        uint32_t* __restrict__ kc, uint32_t* __restrict__ prefix,
-                                                        uint32_t* __restrict__ remain, uint32_t* __restrict__ misc) {
+                                                        uint32_t* __restrict__ kc, uint32_t* __restrict__ start,
+                                                        uint32_t* __restrict__ cursor, uint32_t* __restrict__ misc) {
 #pragma clang fp contract(off)
     __shared__ unsigned long long red[1024];
-    __shared__ uint32_t hist[256];
-    __shared__ unsigned long long s_pre;
-    __shared__ uint32_t s_rem;
+    __shared__ uint32_t hist[1024];
+    __shared__ PickWork pw;
     const int t = threadIdx.x;
     auto block_sum = [&](unsigned long long v) {
-        red[t] = v;
+        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+        if ((t & 63) == 0) red[t >> 6] = v;
         __syncthreads();
-        for (int w = 512; w >= 1; w >>= 1) {
-            if (t < w) red[t] += red[t + w];
-            __syncthreads();
-        }
-        const unsigned long long r = red[0];
+        unsigned long long r = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) r += red[w];
         __syncthreads();
         return r;
     };
@@ -129,32 +255,36 @@ __global__ __launch_bounds__(1024) void cb_quota_kernel(const uint32_t* __restri
     unsigned long long rem = m > base ? m - base : 0ull;
     if (rem > ncand) rem = ncand;
     if (rem > 0) {
-        // radix select of the rem-th largest key among the candidates, a byte at a time from the top
-        if (t == 0) { s_pre = 0ull; s_rem = (uint32_t)rem; }
-        for (int shift = 56; shift >= 0; shift -= 8) {
-            if (t < 256) hist[t] = 0;
+        // Radix select of the rem-th largest key among the candidates, ten bits at a time from the top. It ends early when
+        // a bin is taken whole (then T is its lower bound and no class on it is left out): seldom more than three rounds.
+        unsigned long long T = 0;
+        uint32_t take = (uint32_t)rem;
+        for (int shift = 54, bits = 10;;) {
+            const unsigned long long mask = (1ull << bits) - 1;
+            hist[t] = 0;
             __syncthreads();
-            const unsigned long long pre = s_pre;
             for (int c = t; c < C; c += 1024) {
                 if (kc[c] >= counts[c]) continue;
                 const unsigned long long key = frac_key(counts[c]);
-                if (shift == 56 || (key >> (shift + 8)) == pre) atomicAdd(&hist[(key >> shift) & 255ull], 1u);
+                if (shift == 54 || (key >> (shift + bits)) == (T >> (shift + bits))) atomicAdd(&hist[(key >> shift) & mask], 1u);
             }
             __syncthreads();
-            if (t == 0) {
-                uint32_t want = s_rem, cum = 0;
-                int chosen = 0;
-                for (int b = 255; b >= 0; --b) {
-                    if (cum + hist[b] >= want) { chosen = b; break; }
-                    cum += hist[b];
-                }
-                s_pre = (pre << 8) | (unsigned long long)chosen;
-                s_rem = want - cum;
-            }
+            uint32_t digit, rest;
+            pick_bin<1024, 1024>(hist, take, pw, digit, rest);
+            const uint32_t full = hist[digit];
+            T |= (unsigned long long)digit << shift;
+            take = rest;
             __syncthreads();
+            if (shift == 0) break;
+            if (rest == full) {
+                take = 0xFFFFFFFFu;  // every class at or above T gets a row
+                break;
+            }
+            bits = shift < 10 ? shift : 10;  // (64 bits: six digits of ten and one of four)
+            shift -= bits;
         }
-        const unsigned long long T = s_pre;
-        const uint32_t take = s_rem;  // classes exactly on the threshold that still get a row, lowest class first
+        const bool whole = take == 0xFFFFFFFFu;
+        // otherwise `take` of the classes exactly on the threshold still get a row, lowest class first
         // ordered count of the threshold classes: every thread owns a contiguous run of classes
         const int chunk = (C + 1023) / 1024;
         const int c0 = t * chunk, c1 = c0 + chunk < C ? c0 + chunk : C;
@@ -173,7 +303,7 @@ __global__ __launch_bounds__(1024) void cb_quota_kernel(const uint32_t* __restri
         for (int c = c0; c < c1; ++c) {
             if (kc[c] >= counts[c]) continue;
             const unsigned long long key = frac_key(counts[c]);
-            if (key > T) kc[c] += 1;
+            if (key > T || (whole && key == T)) kc[c] += 1;
             else if (key == T) {
                 if (before < take) kc[c] += 1;
                 before += 1;
@@ -183,44 +313,44 @@ __global__ __launch_bounds__(1024) void cb_quota_kernel(const uint32_t* __restri
     }
     unsigned long long tot = 0;
     for (int c = t; c < C; c += 1024) {
-        prefix[c] = 0;
-        remain[c] = kc[c];
         tot += kc[c];
     }
     tot = block_sum(tot);
     if (t == 0) misc[0] = (uint32_t)tot;
+    cb_starts(counts, C, start, cursor, red);
 }
 
 // The other budget rule: equal budgets. The m = floor(keep * N + 0.5) rows are dealt one at a time to the classes in
 // turn, lowest class first, a full class being passed over. In closed form: with q the largest level for which
 // sum_c min(N_c, q) <= m, class c gets min(N_c, q), and the m - sum_c min(N_c, q) rows left (fewer than there are
 // classes larger than q) go one each to the lowest-numbered classes with N_c > q. Integer work throughout. One
-// work-group of 1024 threads; also sets the start state of the selects and misc[0] = sum_c k_c, like cb_quota_kernel.
+// work-group of 1024 threads; also sets the places of the classes in the list and misc[0] = sum_c k_c, like cb_quota_kernel.
 __global__ __launch_bounds__(1024) void cb_quota_equal_kernel(const uint32_t* __restrict__ counts, int C, double keep,
-                                                              uint32_t* __restrict__ kc, uint32_t* __restrict__ prefix,
-                                                              uint32_t* __restrict__ remain, uint32_t* __restrict__ misc) {
+                                                              uint32_t* __restrict__ kc, uint32_t* __restrict__ start,
+                                                              uint32_t* __restrict__ cursor, uint32_t* __restrict__ misc) {
 #pragma clang fp contract(off)
     __shared__ unsigned long long red[1024];
     const int t = threadIdx.x;
     auto block_sum = [&](unsigned long long v) {
-        red[t] = v;
+        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+        if ((t & 63) == 0) red[t >> 6] = v;
         __syncthreads();
-        for (int w = 512; w >= 1; w >>= 1) {
-            if (t < w) red[t] += red[t + w];
-            __syncthreads();
-        }
-        const unsigned long long r = red[0];
+        unsigned long long r = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) r += red[w];
         __syncthreads();
         return r;
     };
     auto block_max = [&](unsigned long long v) {
-        red[t] = v;
-        __syncthreads();
-        for (int w = 512; w >= 1; w >>= 1) {
-            if (t < w) red[t] = red[t] > red[t + w] ? red[t] : red[t + w];
-            __syncthreads();
+        for (int o = 32; o >= 1; o >>= 1) {
+            const unsigned long long x = __shfl_xor(v, o);
+            v = v > x ? v : x;
         }
-        const unsigned long long r = red[0];
+        if ((t & 63) == 0) red[t >> 6] = v;
+        __syncthreads();
+        unsigned long long r = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) r = r > red[w] ? r : red[w];
         __syncthreads();
         return r;
     };
@@ -278,253 +408,196 @@ __global__ __launch_bounds__(1024) void cb_quota_equal_kernel(const uint32_t* __
             before += 1;
         }
         kc[c] = (uint32_t)b;
-        prefix[c] = 0;
-        remain[c] = (uint32_t)b;
         tot += b;
     }
     tot = block_sum(tot);
     if (t == 0) misc[0] = (uint32_t)tot;
+    cb_starts(counts, C, start, cursor, red);
 }
 
-// alpha_i = clamp(<zhat_i, u_c(i)>, -1, 1), -0 stored as +0; one wave per row
-__global__ __launch_bounds__(256) void cb_cosine_kernel(const float* __restrict__ zhat, const int* __restrict__ labels,
-                                                        int64_t N, int k, int C, const double* __restrict__ ucls,
-                                                        float* __restrict__ alpha) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < N; r += (int64_t)gridDim.x * 4) {
-        int c = labels[r];
-        if (c < 0 || c >= C) c = 0;  // reported by cb_accumulate_kernel; keep the reads in bounds
-        const float* z = zhat + r * k;
-        const double* u = ucls + (int64_t)c * 128;
-        double a = 0.0;
-        if (lane < k) a = (double)z[lane] * u[lane];
-        if (lane + 64 < k) a += (double)z[lane + 64] * u[lane + 64];
-        for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
-        if (lane == 0) {
-            if (a > 1.0) a = 1.0;
-            if (a < -1.0) a = -1.0;
-            float f = (float)a;
-            if (f == 0.f) f = 0.f;
-            alpha[r] = f;
-        }
+// One work-group of T threads per class: which of its rows are kept. Up to 256 rows: by rank, a thread comparing its key
+// with all of them from LDS (the square of the rows in LDS reads: 10 us at 256, which the select needs too). More: radix select of the k_c-th largest key (12 + 10 + 10 bits) and, if not all rows on the
+// threshold can be kept, of the row index among those (10 + 10 + 12 bits).
+template <int T>
+__global__ __launch_bounds__(T) void cb_select_kernel(const uint32_t* __restrict__ skey, const uint32_t* __restrict__ ord,
+                                                      const uint32_t* __restrict__ counts,
+                                                      const uint32_t* __restrict__ start, const uint32_t* __restrict__ kc,
+                                                      const uint32_t* __restrict__ misc, uint8_t* __restrict__ sel) {
+    __shared__ uint32_t h[4096];
+    __shared__ PickWork pw;
+    if (misc[1]) return;
+    const int c = blockIdx.x, t = threadIdx.x;
+    const uint32_t n = counts[c], k = kc[c];
+    if (n == 0) return;
+    const uint32_t* key = skey + start[c];
+    const uint32_t* row = ord + start[c];
+    if (k == 0 || k >= n) {
+        for (uint32_t i = t; i < n; i += T) sel[row[i]] = k != 0;
+        return;
     }
-}
-
-// phase 0: histogram of byte shift/8 of the score keys whose higher bytes equal their class prefix
-// phase 1: the same over the row index, among the rows whose score key equals their class threshold
-__global__ __launch_bounds__(256) void cb_hist_kernel(const float* __restrict__ alpha, const int* __restrict__ labels,
-                                                      int64_t N, int C, int phase, int shift,
-                                                      const uint32_t* __restrict__ kc, const uint32_t* __restrict__ thr,
-                                                      const uint32_t* __restrict__ prefix, uint32_t* __restrict__ hist) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 256) {
-        const int c = labels[i];
-        if (c < 0 || c >= C || kc[c] == 0) continue;
-        uint32_t key = cb_key(alpha[i]);
-        if (phase == 1) {
-            if (key != thr[c]) continue;
-            key = (uint32_t)i;
+    if (n <= 256) {
+        uint2* kr = reinterpret_cast<uint2*>(h);
+        const uint2 mine = (uint32_t)t < n ? make_uint2(key[t], row[t]) : make_uint2(0u, 0xFFFFFFFFu);
+        if (t < 256) kr[t] = mine;
+        __syncthreads();
+        if ((uint32_t)t >= n) return;
+        uint32_t rank = 0;
+#pragma unroll 4
+        for (uint32_t j = 0; j < n; ++j) {
+            const uint2 o = kr[j];
+            rank += o.x > mine.x || (o.x == mine.x && o.y < mine.y);
         }
-        const bool match = shift == 24 ? true : ((key >> (shift + 8)) == prefix[c]);
-        if (match) atomicAdd(&hist[(int64_t)c * 256 + ((key >> shift) & 255u)], 1u);
+        sel[mine.y] = rank < k;
+        return;
     }
-}
-
-// one thread per class: walk the class's bins (from the top in phase 0: k-th largest score; from the bottom in phase 1:
-// k-th smallest index) until the remaining count is covered, extend the prefix, clear the bins
-__global__ __launch_bounds__(256) void cb_pick_kernel(uint32_t* __restrict__ hist, int C, int phase,
-                                                      const uint32_t* __restrict__ kc, uint32_t* __restrict__ prefix,
-                                                      uint32_t* __restrict__ remain) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= C) return;
-    uint32_t* h = hist + (int64_t)c * 256;
-    if (kc[c]) {
-        const uint32_t want = remain[c];
-        uint32_t cum = 0;
-        int chosen = phase == 0 ? 0 : 255;
-        for (int t = 0; t < 256; ++t) {
-            const int b = phase == 0 ? 255 - t : t;
-            const uint32_t n = h[b];
-            if (cum + n >= want) { chosen = b; break; }
-            cum += n;
+    // digit of the want-th largest among those that `digit_of` accepts (it returns the bin, or -1)
+    auto pick = [&](auto bins, uint32_t want, auto digit_of, uint32_t& digit, uint32_t& rest) {
+        constexpr int B = decltype(bins)::value;
+        for (int b = t; b < B; b += T) h[b] = 0;
+        __syncthreads();
+        for (uint32_t i = t; i < n; i += T) {
+            const int d = digit_of(i);
+            if (d >= 0) atomicAdd(&h[d], 1u);
         }
-        prefix[c] = (prefix[c] << 8) | (uint32_t)chosen;
-        remain[c] = want - cum;
+        __syncthreads();
+        pick_bin<T, B>(h, want, pw, digit, rest);
+        const uint32_t whole = h[digit];
+        __syncthreads();
+        return whole;
+    };
+    using B12 = std::integral_constant<int, 4096>;
+    using B10 = std::integral_constant<int, 1024>;
+    uint32_t d1, d2, d3, rest;
+    pick(B12{}, k, [&](uint32_t i) { return (int)(key[i] >> 20); }, d1, rest);
+    pick(B10{}, rest, [&](uint32_t i) { return (key[i] >> 20) == d1 ? (int)((key[i] >> 10) & 1023u) : -1; }, d2, rest);
+    const uint32_t p2 = (d1 << 10) | d2;
+    const uint32_t ties =
+        pick(B10{}, rest, [&](uint32_t i) { return (key[i] >> 10) == p2 ? (int)(key[i] & 1023u) : -1; }, d3, rest);
+    const uint32_t thr = (p2 << 10) | d3;
+    uint32_t lowest = 0;  // threshold on ~row: the `rest` lowest rows on the key threshold are kept
+    if (rest < ties) {
+        uint32_t e1, e2, e3;
+        pick(B10{}, rest, [&](uint32_t i) { return key[i] == thr ? (int)(~row[i] >> 22) : -1; }, e1, rest);
+        pick(B10{}, rest,
+             [&](uint32_t i) { return key[i] == thr && (~row[i] >> 22) == e1 ? (int)((~row[i] >> 12) & 1023u) : -1; }, e2,
+             rest);
+        const uint32_t q2 = (e1 << 10) | e2;
+        pick(B12{}, rest, [&](uint32_t i) { return key[i] == thr && (~row[i] >> 12) == q2 ? (int)(~row[i] & 4095u) : -1; },
+             e3, rest);
+        lowest = (q2 << 12) | e3;
     }
-    for (int b = 0; b < 256; ++b) h[b] = 0;
+    for (uint32_t i = t; i < n; i += T) sel[row[i]] = key[i] > thr || (key[i] == thr && ~row[i] >= lowest);
 }
 
-// between the phases: the score prefix is the class threshold; the index select starts with `remain` ties to take
-__global__ __launch_bounds__(256) void cb_phase_kernel(int C, uint32_t* __restrict__ thr, uint32_t* __restrict__ prefix) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= C) return;
-    thr[c] = prefix[c];
-    prefix[c] = 0;
-}
+constexpr int CB_T = 1024, CB_C = SELECT_BLOCK / CB_T;
 
-// row i is kept when its class keeps anything and its key is above the class threshold, or on it with an index not
-// above the class's index threshold; per block of SELECT_BLOCK rows the number kept
-__global__ __launch_bounds__(256) void cb_count_kernel(const float* __restrict__ alpha, const int* __restrict__ labels,
-                                                       int64_t N, int C, const uint32_t* __restrict__ kc,
-                                                       const uint32_t* __restrict__ thr, const uint32_t* __restrict__ tidx,
-                                                       uint8_t* __restrict__ sel, uint32_t* __restrict__ blk) {
-    __shared__ uint32_t sg[256];
-    const int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK + (int64_t)threadIdx.x * 8;
+// rows kept per block of SELECT_BLOCK
+__global__ __launch_bounds__(CB_T) void cb_kept_kernel(const uint8_t* __restrict__ sel, int64_t N,
+                                                       const uint32_t* __restrict__ misc, uint32_t* __restrict__ blk) {
+    __shared__ uint32_t s;
+    if (misc[1]) return;
+    if (threadIdx.x == 0) s = 0;
+    __syncthreads();
     uint32_t g = 0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int64_t i = base + q;
-        if (i < N) {
-            const int c = labels[i];
-            bool keepit = false;
-            if (c >= 0 && c < C && kc[c]) {
-                const uint32_t key = cb_key(alpha[i]);
-                keepit = key > thr[c] || (key == thr[c] && (uint32_t)i <= tidx[c]);
-            }
-            sel[i] = keepit ? 1 : 0;
-            g += keepit;
-        }
+    for (int c = 0; c < CB_C; ++c) {
+        const int64_t i = (int64_t)blockIdx.x * SELECT_BLOCK + c * CB_T + threadIdx.x;
+        g += (uint32_t)__popcll(__ballot(i < N && sel[i]));
     }
-    sg[threadIdx.x] = g;
+    if ((threadIdx.x & 63) == 0) atomicAdd(&s, g);
     __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) sg[threadIdx.x] += sg[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) blk[blockIdx.x] = sg[0];
+    if (threadIdx.x == 0) blk[blockIdx.x] = s;
 }
 
-// exclusive scan of the per-block counts, in place (single work-group, sequential over chunks of 256 blocks)
-__global__ __launch_bounds__(256) void cb_scan_kernel(uint32_t* __restrict__ blk, int nblk) {
-    __shared__ uint32_t sg[256];
-    uint32_t carry = 0;
-    for (int base = 0; base < nblk; base += 256) {
-        const int i = base + threadIdx.x;
-        const uint32_t g = i < nblk ? blk[i] : 0;
-        sg[threadIdx.x] = g;
-        __syncthreads();
-        for (int o = 1; o < 256; o <<= 1) {  // Hillis-Steele inclusive scan
-            uint32_t ag = 0;
-            if ((int)threadIdx.x >= o) ag = sg[threadIdx.x - o];
-            __syncthreads();
-            sg[threadIdx.x] += ag;
-            __syncthreads();
-        }
-        if (i < nblk) blk[i] = carry + sg[threadIdx.x] - g;
-        const uint32_t t = sg[255];
-        __syncthreads();
-        carry += t;
+// The kept rows, ascending; every work-group adds up the counts of the blocks before its own. Writes nothing if there is
+// not room for all of them. report (host memory): {rows kept, a label was out of range}.
+__global__ __launch_bounds__(CB_T) void cb_emit_kernel(const uint8_t* __restrict__ sel, int64_t N,
+                                                       const uint32_t* __restrict__ misc, const uint32_t* __restrict__ blk,
+                                                       int64_t cap, int64_t* __restrict__ out_idx,
+                                                       uint32_t* __restrict__ report) {
+    __shared__ uint32_t cnt[CB_C * (CB_T / 64)], tot[16], before;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        report[0] = misc[0];
+        report[1] = misc[1];
     }
-}
-
-__global__ __launch_bounds__(256) void cb_emit_kernel(const uint8_t* __restrict__ sel, int64_t N,
-                                                      const uint32_t* __restrict__ blk, int64_t* __restrict__ out_idx) {
-    __shared__ uint32_t sg[256];
-    const int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK + (int64_t)threadIdx.x * 8;
-    uint8_t f[8];
+    if (misc[1] || (int64_t)misc[0] > cap || !out_idx) return;
+    uint32_t key[CB_C];
+#pragma unroll
+    for (int c = 0; c < CB_C; ++c) {
+        const int64_t i = (int64_t)blockIdx.x * SELECT_BLOCK + c * CB_T + threadIdx.x;
+        key[c] = i < N && sel[i];
+    }
+    if (threadIdx.x == 0) before = 0;
     uint32_t g = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int64_t i = base + q;
-        f[q] = i < N ? sel[i] : 0;
-        g += f[q];
-    }
-    sg[threadIdx.x] = g;
+    for (unsigned b = threadIdx.x; b < blockIdx.x; b += CB_T) g += blk[b];
+    g = wave_scan(g);
     __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        uint32_t ag = 0;
-        if ((int)threadIdx.x >= o) ag = sg[threadIdx.x - o];
-        __syncthreads();
-        sg[threadIdx.x] += ag;
-        __syncthreads();
-    }
-    uint32_t slot = blk[blockIdx.x] + sg[threadIdx.x] - g;
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        if (f[q]) out_idx[slot++] = base + q;
+    if ((threadIdx.x & 63) == 63 && g) atomicAdd(&before, g);
+    __syncthreads();
+    emit_keys<CB_T, CB_C>(key, (int64_t)blockIdx.x * SELECT_BLOCK, 0u, 0u, before, 0u, cnt, tot, out_idx);
+}
+
+// sets the pointers (base may be null: only the size is wanted) and returns the bytes needed
+static size_t cb_work_fill(CbWork& w, char* base, int C, int64_t N) {
+    size_t at = 0;
+    auto take = [&](auto*& p, size_t count) {
+        p = (std::remove_reference_t<decltype(p)>)(base + at);
+        at += (count * sizeof(*p) + 255) / 256 * 256;
+    };
+    const size_t rows = N > 0 ? (size_t)N : 1;
+    take(w.sums, (size_t)C * 128);
+    take(w.counts, (size_t)C);
+    take(w.kc, (size_t)C);
+    take(w.start, (size_t)C);
+    take(w.cursor, (size_t)C);
+    take(w.misc, 64);
+    take(w.blk, (rows + SELECT_BLOCK - 1) / SELECT_BLOCK);
+    take(w.ord, rows);
+    take(w.skey, rows);
+    take(w.sel, rows);
+    return at;
 }
 
 size_t cb_work_bytes(int C, int64_t N) {
-    const int64_t nblk = (N + SELECT_BLOCK - 1) / SELECT_BLOCK;
-    size_t b = 0;
-    b += (size_t)C * 4 * 6;             // counts, kc, prefix, remain, thr, (spare)
-    b += (size_t)C * 128 * 8 * 2;       // sums, ucls
-    b += (size_t)C * 256 * 4;           // hist
-    b += 64;                            // misc
-    b += (size_t)(nblk > 0 ? nblk : 1) * 4;  // blk
-    b += (size_t)(N > 0 ? N : 1);       // sel
-    return b + 4096;                    // alignment slack
+    CbWork w{};
+    return cb_work_fill(w, nullptr, C, N);
 }
 
 CbWork cb_work_layout(void* base, int C, int64_t N) {
     CbWork w{};
-    char* p = (char*)base;
-    auto take = [&](size_t bytes) {
-        char* q = p;
-        p += (bytes + 255) / 256 * 256;
-        return q;
-    };
-    w.sums = (long long*)take((size_t)C * 128 * 8);
-    w.ucls = (double*)take((size_t)C * 128 * 8);
-    w.counts = (uint32_t*)take((size_t)C * 4);
-    w.kc = (uint32_t*)take((size_t)C * 4);
-    w.prefix = (uint32_t*)take((size_t)C * 4);
-    w.remain = (uint32_t*)take((size_t)C * 4);
-    w.thr = (uint32_t*)take((size_t)C * 4);
-    w.hist = (uint32_t*)take((size_t)C * 256 * 4);
-    w.misc = (uint32_t*)take(64);
-    const int64_t nblk = (N + SELECT_BLOCK - 1) / SELECT_BLOCK;
-    w.blk = (uint32_t*)take((size_t)(nblk > 0 ? nblk : 1) * 4);
-    w.sel = (uint8_t*)take((size_t)(N > 0 ? N : 1));
+    cb_work_fill(w, (char*)base, C, N);
     return w;
 }
 
-// Stage 1: class counts, sums, centroids, k_c, scores. Afterwards misc[0] = total kept, misc[1] = bad label seen.
-hipError_t launch_cb_scores(const float* zhat, const int* labels, int64_t N, int k, int C, double keep, int rule,
-                            float* alpha, const CbWork& w, hipStream_t st) {
-    const int64_t zi = (int64_t)C * 256;
-    hipLaunchKernelGGL(cb_zero_kernel, dim3((unsigned)((zi + 255) / 256)), dim3(256), 0, st, w.counts, w.sums, w.hist,
+hipError_t launch_cb_select(const float* zhat, const int* labels, int64_t N, int k, int C, double keep, int rule,
+                            float* alpha, int64_t cap, int64_t* out_idx, uint32_t* report, const CbWork& w, hipStream_t st) {
+    hipLaunchKernelGGL(cb_zero_kernel, dim3((unsigned)(((int64_t)C * 128 + 255) / 256)), dim3(256), 0, st, w.counts, w.sums,
                        w.misc, C);
-    if (N > 0) {
-        int64_t blocks = (N + 3) / 4;
-        if (blocks > 8192) blocks = 8192;
-        hipLaunchKernelGGL(cb_accumulate_kernel, dim3((unsigned)blocks), dim3(256), 0, st, zhat, labels, N, k, C, w.counts,
-                           w.sums, w.misc);
-    }
-    hipLaunchKernelGGL(cb_unit_kernel, dim3(C), dim3(128), 0, st, w.sums, k, w.ucls);
+    int64_t cb = (N + 4095) / 4096;
+    const unsigned nblk = (unsigned)(cb > 0 ? cb : 1);
+    if (cb > 512) cb = 512;
+    if (N > 0) hipLaunchKernelGGL(cb_count_kernel, dim3((unsigned)cb), dim3(1024), 0, st, labels, N, C, w.counts, w.misc);
     if (rule == SAGE_CB_EQUAL)
-        hipLaunchKernelGGL(cb_quota_equal_kernel, dim3(1), dim3(1024), 0, st, w.counts, C, keep, w.kc, w.prefix, w.remain,
+        hipLaunchKernelGGL(cb_quota_equal_kernel, dim3(1), dim3(1024), 0, st, w.counts, C, keep, w.kc, w.start, w.cursor,
                            w.misc);
     else
-        hipLaunchKernelGGL(cb_quota_kernel, dim3(1), dim3(1024), 0, st, w.counts, C, keep, w.kc, w.prefix, w.remain, w.misc);
+        hipLaunchKernelGGL(cb_quota_kernel, dim3(1), dim3(1024), 0, st, w.counts, C, keep, w.kc, w.start, w.cursor, w.misc);
     if (N > 0) {
-        int64_t blocks = (N + 3) / 4;
-        if (blocks > 8192) blocks = 8192;
-        hipLaunchKernelGGL(cb_cosine_kernel, dim3((unsigned)blocks), dim3(256), 0, st, zhat, labels, N, k, C, w.ucls, alpha);
+        hipLaunchKernelGGL(cb_scatter_kernel, dim3(nblk), dim3(1024), 0, st, labels, N, C, w.cursor, w.ord, alpha);
+        const unsigned runs = (unsigned)((N + 4 * CB_RUN - 1) / (4 * CB_RUN));
+        hipLaunchKernelGGL(cb_sum_kernel, dim3(runs), dim3(256), 0, st, zhat, labels, w.ord, N, k, C, w.sums, w.misc);
+        hipLaunchKernelGGL(cb_cosine_kernel, dim3(runs), dim3(256), 0, st, zhat, labels, w.ord, N, k, C, w.sums, w.misc, alpha,
+                           w.skey);
+        // the radix select of a large class wants the wider work-group, the ranks of a small one no more than 256 threads
+        if (N / C > 256)
+            hipLaunchKernelGGL(cb_select_kernel<1024>, dim3(C), dim3(1024), 0, st, w.skey, w.ord, w.counts, w.start, w.kc,
+                               w.misc, w.sel);
+        else
+            hipLaunchKernelGGL(cb_select_kernel<256>, dim3(C), dim3(256), 0, st, w.skey, w.ord, w.counts, w.start, w.kc,
+                               w.misc, w.sel);
+        hipLaunchKernelGGL(cb_kept_kernel, dim3(nblk), dim3(CB_T), 0, st, w.sel, N, w.misc, w.blk);
     }
-    return hipGetLastError();
-}
-
-// Stage 2: thresholds per class, flags, compaction. out_idx receives misc[0] indices, ascending.
-hipError_t launch_cb_select(const float* alpha, const int* labels, int64_t N, int C, int64_t* out_idx, const CbWork& w,
-                            hipStream_t st) {
-    if (N <= 0) return hipSuccess;
-    int64_t hb = (N + 255) / 256;
-    if (hb > 2048) hb = 2048;
-    const unsigned cb = (unsigned)((C + 255) / 256);
-    for (int phase = 0; phase < 2; ++phase) {
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            hipLaunchKernelGGL(cb_hist_kernel, dim3((unsigned)hb), dim3(256), 0, st, alpha, labels, N, C, phase, shift, w.kc,
-                               w.thr, w.prefix, w.hist);
-            hipLaunchKernelGGL(cb_pick_kernel, dim3(cb), dim3(256), 0, st, w.hist, C, phase, w.kc, w.prefix, w.remain);
-        }
-        if (phase == 0) hipLaunchKernelGGL(cb_phase_kernel, dim3(cb), dim3(256), 0, st, C, w.thr, w.prefix);
-    }
-    const int64_t nblk = (N + SELECT_BLOCK - 1) / SELECT_BLOCK;
-    // after phase 1 `prefix` is the index threshold of every class
-    hipLaunchKernelGGL(cb_count_kernel, dim3((unsigned)nblk), dim3(256), 0, st, alpha, labels, N, C, w.kc, w.thr, w.prefix,
-                       w.sel, w.blk);
-    hipLaunchKernelGGL(cb_scan_kernel, dim3(1), dim3(256), 0, st, w.blk, (int)nblk);
-    hipLaunchKernelGGL(cb_emit_kernel, dim3((unsigned)nblk), dim3(256), 0, st, w.sel, N, w.blk, out_idx);
+    hipLaunchKernelGGL(cb_emit_kernel, dim3(nblk), dim3(CB_T), 0, st, w.sel, N, w.misc, w.blk, cap, out_idx, report);
     return hipGetLastError();
 }
 

@@ -7,11 +7,11 @@
 
 namespace {
 
-// Work space of one top-m run over at most SAGE_TOPM_STATIC_MAX_N keys: 256 histogram bins, 4 state words, and two
-// per-block counters for every block of SELECT_BLOCK keys.
+// Work space of one top-m run over at most SAGE_TOPM_STATIC_MAX_N keys: the histograms, the state, and two per-block
+// counters for every block of SELECT_BLOCK keys.
 constexpr int64_t MAX_N = SAGE_TOPM_STATIC_MAX_N;
 constexpr int64_t MAX_BLOCKS = (MAX_N + sage::SELECT_BLOCK - 1) / sage::SELECT_BLOCK;
-constexpr size_t HIST_WORDS = 256, STATE_WORDS = 64;  // the state gets a 256-byte slot of its own
+constexpr size_t HIST_WORDS = sage::TOPM_HIST_WORDS, STATE_WORDS = 64;  // the state gets a 256-byte slot of its own
 constexpr size_t SCRATCH_WORDS = HIST_WORDS + STATE_WORDS + 2 * (size_t)MAX_BLOCKS;
 
 // One copy per GPU, at that GPU's own address; host code never uses this name as a pointer (it is a host-side stand-in
@@ -58,7 +58,7 @@ extern "C" int sage_topm_static(const float* alpha, int64_t N, int64_t m, int64_
     w.blk_gt = base + HIST_WORDS + STATE_WORDS;
     w.blk_eq = w.blk_gt + MAX_BLOCKS;
     w.nblk_cap = MAX_BLOCKS;
-    // the first kernel of the run clears the histogram and the state; every per-block counter that is read is
+    // the first kernel of the run clears the histograms; the state and every per-block counter that is read are
     // written earlier in the same run, so nothing of the previous call's contents is used
     if (sage::launch_topm(alpha, N, m, out_idx, w, (hipStream_t)hip_stream) != hipSuccess) {
         (void)hipGetLastError();

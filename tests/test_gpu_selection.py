@@ -1,0 +1,49 @@
+"""Selections at the edges of their variants: one work-group against several, slices of a work-group, class sizes around
+the rank / radix boundary, ties at every threshold."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N", [1, 63, 1024, 1025, 2047, 2049, 4097, 8193, 16_385, 32_767, 32_768, 32_769, 36_865, 600_001])
+@pytest.mark.parametrize("ties", [False, True])
+def test_topm_at_the_edges_of_its_variants(N, ties):
+    import torch
+
+    from paper_2510_02470_amd.binding import topm, topm_static
+
+    rng = np.random.default_rng(N)
+    a = (rng.integers(-3, 4, size=N) / 4.0 if ties else np.tanh(0.1 + 0.3 * rng.standard_normal(N))).astype(np.float32)
+    ad = torch.from_numpy(a).cuda()
+    for m in sorted({1, (N + 2) // 3, N - 1, N} - {0}):
+        want = oracle.topm_f32(a, m).tolist()
+        assert topm(ad, m).cpu().tolist() == want
+        assert topm_static(ad, m, torch.empty(m, dtype=torch.int64, device="cuda")).cpu().tolist() == want
+
+
+# class sizes: the rank select takes up to 256 rows; a mean above 256 rows takes the wider work-group; many classes leave
+# no room for counters in LDS
+@pytest.mark.parametrize("sizes", [(255, 256, 257, 0, 1, 30), (3000, 256, 257, 1025), (5000,), (2,) * 300 + (700,),
+                                   (1,) * 4090 + (0,) * 10], ids=["small", "large", "single", "many", "no_lds"])
+@pytest.mark.parametrize("distinct", [3, 100_000])
+def test_class_selection_at_the_edges_of_its_variants(sizes, distinct):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    rng = np.random.default_rng(len(sizes))
+    N, C = sum(sizes), len(sizes)
+    labels = rng.permutation(np.repeat(np.arange(C), sizes)).astype(np.int32)
+    G = rng.standard_normal((min(distinct, N), 40)).astype(np.float32)[rng.integers(0, min(distinct, N), size=N)]
+    s = Sage(16, 40)
+    s.set_basis(torch.from_numpy(rng.standard_normal((6, 40)).astype(np.float32)).cuda())
+    s.score_labeled(torch.from_numpy(G).cuda(), torch.from_numpy(labels).cuda())
+    for keep in (0.03, 0.4, 0.999):
+        for rule in ("proportional", "equal"):
+            idx = s.select_cb(keep, C, rule=rule).cpu().numpy()
+            want = oracle.cb_select_from_alpha(s.scores().cpu().numpy(), labels, C, keep, rule)
+            assert idx.tolist() == want.tolist()
+    s.close()
