@@ -45,13 +45,9 @@ _ALLOC_FN = C.CFUNCTYPE(C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p)
 _FREE_FN = C.CFUNCTYPE(None, C.c_void_p, C.c_void_p)
 
 
-_memory = None  # the callbacks in use (they must outlive every context)
-
-
 def _torch_memory(L):
     """Device memory of contexts from torch's caching allocator, on the context's stream: shared with, and given back
     to, the rest of the program like any tensor's."""
-    global _memory
     import torch
 
     take, give = torch._C._cuda_cudaCachingAllocator_raw_alloc, torch._C._cuda_cudaCachingAllocator_raw_delete
@@ -65,8 +61,10 @@ def _torch_memory(L):
     def free(ptr, user):
         give(ptr)
 
-    _memory = _ALLOC_FN(alloc), _FREE_FN(free)
-    _check(L.sage_set_allocator(*_memory, None), "sage_set_allocator")
+    memory = _ALLOC_FN(alloc), _FREE_FN(free)
+    for f in memory:  # a context may be closed when the interpreter has cleared this module: these two stay for good
+        C.pythonapi.Py_IncRef(C.py_object(f))
+    _check(L.sage_set_allocator(*memory, None), "sage_set_allocator")
 
 
 def lib():

@@ -385,17 +385,18 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
     __syncthreads();
 }
 
-// Work-groups 0 .. N/64 - 1: a diagonal block each. The N/64 after them form the triangular factors of the reduction's
-// blocks of reflectors meanwhile (a wave each; wy_factor), which the back-transformation needs.
-template <int J>
-__global__ __launch_bounds__(512, 1) void dc_block_kernel(const double* __restrict__ dT, const double* __restrict__ eT,
-                                                          double* __restrict__ dO, double* __restrict__ Z,
+// A work-group per diagonal block of 64. WITH_WY (N = 64): the work-group after it forms the triangular factors of the
+// reduction's blocks of reflectors meanwhile (a wave each; wy_factor), which the back-transformation needs; for larger N that
+// is done beside the first merge's roots (dc_roots_kernel). Without it the kernel stays below 128 registers and fits on a
+// CU beside a work-group of the Gram kernel that runs on the side stream (it waited 400 us for one to end otherwise).
+template <bool WITH_WY>
+__global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const double* __restrict__ dT, const double* __restrict__ eT,
+                                                          int N, double* __restrict__ dO, double* __restrict__ Z,
                                                           const double* __restrict__ V, const double* __restrict__ tauT,
                                                           int n, double* __restrict__ Tw) {
-    constexpr int N = 64 * J;
-    if (blockIdx.x >= J) {
-        const int b = (blockIdx.x - J) * 8 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        if (b * WY <= n - 2) wy_factor<J>(V, tauT, b, n, threadIdx.x & 63, Tw);
+    if (WITH_WY && blockIdx.x == 1) {
+        const int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (b * WY <= n - 2) wy_factor<1>(V, tauT, b, n, threadIdx.x & 63, Tw);
         return;
     }
     extern __shared__ char dc_lds[];
@@ -587,10 +588,21 @@ __global__ __launch_bounds__(512) void dc_deflate_kernel(const double* __restric
     }
 }
 
-// one wave per root
-__global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict__ eT, int m, DcWork w) {
+// One wave per root. WYJ > 0 (the first merge of N = 64 WYJ): the row of work-groups after the last sub-problem's forms the
+// triangular factors of the reduction's blocks of reflectors, a wave each (wy_factor).
+template <int WYJ>
+__global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict__ eT, int m, DcWork w,
+                                                       const double* __restrict__ V, const double* __restrict__ tauT, int n,
+                                                       double* __restrict__ Tw) {
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (WYJ > 0) {
+        static_assert(8 * WYJ <= 128, "as many waves in a row of work-groups as blocks");
+        if (blockIdx.y == gridDim.y - 1) {
+            if (q * WY <= n - 2) wy_factor<WYJ>(V, tauT, q, n, lane, Tw);
+            return;
+        }
+    }
     const int base = blockIdx.y * m;
     const int K = w.K[blockIdx.y];
     double org = 0.0, tau = 0.0, val = w.dk[base + q];
@@ -755,29 +767,30 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(const double* __restric
     }
 }
 
-template <int J>
-static hipError_t launch_dc_block(const EigWork& w, int n, hipStream_t st) {
-    if (hipError_t e = ensure_dynamic_lds((const void*)dc_block_kernel<J>, (int)sizeof(DcBlockLds)); e != hipSuccess) return e;
-    hipLaunchKernelGGL(dc_block_kernel<J>, dim3(2 * J), dim3(512), sizeof(DcBlockLds), st, w.dT, w.eT, w.dI[0], w.Z[0], w.V,
-                       w.tauT, n, w.Tw);
-    return hipGetLastError();
-}
-
-// T = Z D Z^T: eigenvalues ascending in dI, eigenvectors in the columns of Z (buffer dc_result(N) of either). n: rows in use.
+// T = Z D Z^T: eigenvalues ascending in dI, eigenvectors in the columns of Z (buffer dc_result(N) of either), and the
+// triangular factors of the reflectors in Tw. n: rows in use.
 hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
-    hipError_t e = hipErrorInvalidValue;
-    switch (N / 64) {
-        case 1: e = launch_dc_block<1>(w, n, st); break;
-        case 2: e = launch_dc_block<2>(w, n, st); break;
-        case 4: e = launch_dc_block<4>(w, n, st); break;
-        case 8: e = launch_dc_block<8>(w, n, st); break;
-    }
-    if (e != hipSuccess) return e;
+    if (N != 64 && N != 128 && N != 256 && N != 512) return hipErrorInvalidValue;
+    const void* block = N == 64 ? (const void*)dc_block_kernel<true> : (const void*)dc_block_kernel<false>;
+    if (hipError_t e = ensure_dynamic_lds(block, (int)sizeof(DcBlockLds)); e != hipSuccess) return e;
+    if (N == 64)
+        hipLaunchKernelGGL(dc_block_kernel<true>, dim3(2), dim3(512), sizeof(DcBlockLds), st, w.dT, w.eT, N, w.dI[0], w.Z[0],
+                           w.V, w.tauT, n, w.Tw);
+    else
+        hipLaunchKernelGGL(dc_block_kernel<false>, dim3(N / 64), dim3(512), sizeof(DcBlockLds), st, w.dT, w.eT, N, w.dI[0],
+                           w.Z[0], w.V, w.tauT, n, w.Tw);
     int cur = 0;
     for (int m = 128; m <= N; m *= 2) {
         const int S = N / m;
         hipLaunchKernelGGL(dc_deflate_kernel, dim3(S), dim3(512), 0, st, w.dT, w.eT, N, m, w.dI[cur], w.Z[cur], w.dc);
-        hipLaunchKernelGGL(dc_roots_kernel, dim3(m / 4, S), dim3(256), 0, st, w.eT, m, w.dc);
+#define SAGE_ROOTS(WYJ)                                                                                              \
+    hipLaunchKernelGGL(dc_roots_kernel<WYJ>, dim3(m / 4, WYJ > 0 ? S + 1 : S), dim3(256), 0, st, w.eT, m, w.dc, w.V, \
+                       w.tauT, n, w.Tw)
+        if (m > 128) SAGE_ROOTS(0);
+        else if (N == 128) SAGE_ROOTS(2);
+        else if (N == 256) SAGE_ROOTS(4);
+        else SAGE_ROOTS(8);
+#undef SAGE_ROOTS
         hipLaunchKernelGGL(dc_weights_kernel, dim3(m / 4, S), dim3(256), 0, st, m, w.dc, w.dI[cur ^ 1]);
         hipLaunchKernelGGL(dc_vectors_kernel, dim3(m / 32, m / 64, S), dim3(256), 0, st, w.Z[cur], w.Z[cur ^ 1], N, m, w.dc);
         cur ^= 1;

@@ -44,12 +44,13 @@ template <int P>
 __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ top, const float* __restrict__ nw,
                                                       int nfill, float* __restrict__ partial, int mode, int t0,
                                                       int tiles, int wg_per_group, int64_t slabs_total,
-                                                      int64_t slabs_per_group) {
+                                                      int64_t slabs_per_group, int wgs, int skip) {
     constexpr int NP = P * 64;
     constexpr int STAGE = NP * 4;  // 16-byte pieces per stage
     extern __shared__ f32x4 lds[];
 
-    const int id = blockIdx.x;
+    const int id = (int)xcd_rank(blockIdx.x, skip);
+    if (id < 0 || id >= wgs) return;
     const int xcd = id & 7;  // consecutive block ids go to consecutive XCDs: keep a group on one XCD (shared L2)
     const int y = id >> 3;
     const int w = y % wg_per_group;
@@ -679,9 +680,10 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
 template <bool NEW1>
 __global__ __launch_bounds__(256, 2) void gram_new8_split_kernel(const float* __restrict__ nw, int nfill,
                                                                  float* __restrict__ partial, int64_t slabs_total,
-                                                                 int64_t slabs_per_group) {
+                                                                 int64_t slabs_per_group, int groups, int skip) {
     extern __shared__ u32x4 ldsn[];
-    const int group = blockIdx.x;
+    const int group = (int)xcd_rank(blockIdx.x, skip);
+    if (group < 0 || group >= groups) return;
     int64_t s0 = (int64_t)group * slabs_per_group;
     int64_t s1 = s0 + slabs_per_group;
     if (s1 > slabs_total) s1 = slabs_total;
@@ -744,9 +746,8 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, 
     C[(int64_t)gc * NP + gr] = s;
 }
 
-// wg_per_cu = 2 fills the chip. wg_per_cu = 1 is for the launch that shares the chip with the eigensolve (side
-// stream): it also leaves 16 CUs (two per XCD) without any of its work-groups, because the eigensolve's pivot
-// kernel needs more registers than remain on a CU that holds one of them.
+// wg_per_cu = 2 fills the chip. wg_per_cu = 1 is for the launch that shares the chip with the eigensolve (side stream): it
+// leaves an eighth of the CUs, an XCD, to the eigensolve's reduction (see xcd_rank).
 GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_per_cu) {
     GramPlan p;
     const bool side = wg_per_cu == 1;
@@ -763,11 +764,9 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
     }
     p.wg_per_group = (p.tiles + 5) / 6;
     if (mode == 1 && P == 8) p.wg_per_group = 2;  // gram_cross8_kernel: 8 wave tiles of 128 x 64
-    // gram_new8_kernel (the whole triangle in one work-group) when the launch has the chip to itself. Beside the
-    // eigensolve the slower gram_kernel is the better neighbour: measured on one box, the eigensolve lost more time to
-    // the denser kernel than the side stream gained (21.7 k rows/s against 22.8 k for the whole update at config 5).
+    // gram_new8_kernel (the whole triangle in one work-group) when the launch has the chip to itself
     if (mode == 2 && P == 8 && !side) p.wg_per_group = 1;
-    const int cus = side && num_cu > 32 ? num_cu - 16 : num_cu;
+    const int cus = side && num_cu > 32 ? num_cu / 8 * 7 : num_cu;
     int g = (wg_per_cu * cus / p.wg_per_group) / 8 * 8;
     if (g < 8) g = 8;
     // keep at least 4 slabs per group so that tiny problems do not drown in partial tiles
@@ -800,7 +799,7 @@ GramPlan gram_plan_split(const GramPlan& base, const Dims& d, int groups) {
 }
 
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
-                       hipStream_t st, bool new_one) {
+                       hipStream_t st, bool new_one, int skip) {
     if (p.tiles <= 0) return hipSuccess;
     dim3 grid((unsigned)(p.groups * p.wg_per_group));
     size_t lds = (size_t)2 * d.NP * 64;
@@ -822,16 +821,13 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
         return hipGetLastError();
     }
     if (p.mode == 2 && d.NP == 512 && p.split) {
-        // 49.5 KB are used; 64 KB are asked for, so that the eigensolve's pivot kernel (which asks for 100 KB for this
-        // purpose) never shares a CU with one of these work-groups when the launch runs beside it
-        constexpr int LDS_SPLIT = 65536;
-        static_assert(2 * 3 * 2 * (256 + 8) * 16 <= LDS_SPLIT, "two stages must fit");
+        constexpr int LDS_SPLIT = 2 * 3 * 2 * (256 + 8) * 16;  // two stages
         if (new_one)
-            hipLaunchKernelGGL(gram_new8_split_kernel<true>, grid, dim3(256), LDS_SPLIT, st, nw, nfill, partial, d.S,
-                               p.slabs_per_group);
+            hipLaunchKernelGGL(gram_new8_split_kernel<true>, dim3((unsigned)xcd_grid(p.groups, skip)), dim3(256), LDS_SPLIT, st, nw,
+                               nfill, partial, d.S, p.slabs_per_group, p.groups, skip);
         else
-            hipLaunchKernelGGL(gram_new8_split_kernel<false>, grid, dim3(256), LDS_SPLIT, st, nw, nfill, partial, d.S,
-                               p.slabs_per_group);
+            hipLaunchKernelGGL(gram_new8_split_kernel<false>, dim3((unsigned)xcd_grid(p.groups, skip)), dim3(256), LDS_SPLIT, st, nw,
+                               nfill, partial, d.S, p.slabs_per_group, p.groups, skip);
         return hipGetLastError();
     }
     if (p.mode == 2 && d.NP == 512 && p.wg_per_group == 1) {
@@ -843,8 +839,8 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
 #define SAGE_GRAM_CASE(PP)                                                                                          \
     case PP: {                                                                                                      \
         if (hipError_t ea = ensure_dynamic_lds((const void*)gram_kernel<PP>, 65536); ea != hipSuccess) return ea;   \
-        hipLaunchKernelGGL(gram_kernel<PP>, grid, dim3(256), lds, st, top, nw, nfill, partial, p.mode, p.t0, p.tiles,    \
-                           p.wg_per_group, d.S, p.slabs_per_group);                                                 \
+        hipLaunchKernelGGL(gram_kernel<PP>, dim3((unsigned)xcd_grid(grid.x, skip)), dim3(256), lds, st, top, nw, nfill,   \
+                           partial, p.mode, p.t0, p.tiles, p.wg_per_group, d.S, p.slabs_per_group, (int)grid.x, skip);  \
     } break;
         SAGE_GRAM_CASE(1)
         SAGE_GRAM_CASE(2)

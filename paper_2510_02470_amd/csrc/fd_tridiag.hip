@@ -318,7 +318,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                                                           double* __restrict__ stat, u32x4* __restrict__ xch,
                                                           unsigned tag0, int xcd) {
     constexpr int N = 64 * J, NW = N / 4;  // NW waves in all
-    if ((int)(blockIdx.x & 7) != xcd) return;  // consecutive work-groups go to consecutive XCDs
+    if ((LOCAL ? xcd_id() : (int)(blockIdx.x & 7)) != xcd) return;  // one of eight consecutive work-groups
     __builtin_amdgcn_s_setprio(3);
     __shared__ Pair qc[2][N];  // {q, c} by step parity
     __shared__ double vs[4][N];
@@ -671,11 +671,10 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
     }
 }
 
-// Do work-groups whose numbers are congruent modulo 8 run on one XCD of the current device? Asked once per device.
+// Do eight consecutive work-groups run on the eight XCDs of the current device, in an order that repeats? Asked once per
+// device.
 __global__ void xcd_probe_kernel(int* __restrict__ out) {
-    int id;
-    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(id));
-    if (threadIdx.x == 0) out[blockIdx.x] = id;
+    if (threadIdx.x == 0) out[blockIdx.x] = xcd_id();
 }
 static bool xcd_mapping_known() {
     static std::mutex lock;
@@ -699,6 +698,9 @@ static bool xcd_mapping_known() {
             }
             (void)hipFree(d);
         }
+        unsigned seen = 0;
+        for (int i = 0; ok && i < 8; ++i) seen |= 1u << h[i];
+        ok = ok && seen == 0xFF;
         for (int i = 8; ok && i < B; ++i) ok = h[i] == h[i - 8];
         known[dev] = ok ? 1 : 2;
     }

@@ -236,9 +236,10 @@ struct RowSrc {
     }
 };
 
-hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int half_rows, const Dims& d, hipStream_t st) {
-    if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, st);
-    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, st);
+hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int half_rows, const Dims& d, hipStream_t st,
+                       int skip = -1) {
+    if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, skip, st);
+    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, skip, st);
 }
 
 // Rows of `s` are about to be stored in nw[i] from row row0 on.
@@ -397,9 +398,10 @@ int side_ahead(sage_ctx* c, const RowSrc* next) {
     HIPCHK(hipEventRecord(c->ev_mark, c->st));
     HIPCHK(hipStreamWaitEvent(c->st2, c->ev_mark, 0));
     note_new_rows(c, o, 0, *next);
-    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->st2));
+    const int skip = c->ew.local ? c->ew.xcd : -1;
+    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->st2, skip));
     c->gp_side_used[o] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
-    HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o)));
+    HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), skip));
     HIPCHK(hipEventRecord(c->ev_side[o], c->st2));
     return SAGE_OK;
 }
@@ -605,9 +607,9 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
         c->gp_new2 = gram_plan(c->d, c->num_cu, 2, false, 2);
         c->gp_cross_split = gram_plan_split(c->gp_cross, c->d, 0);
         c->gp_new2_split = gram_plan_split(c->gp_new2, c->d, 0);
-        // beside the eigensolve: one work-group per CU, 16 CUs left free (see gram_plan); 64, 120 and 240 work-groups
-        // gave the same update rate, 480 a lower one
-        c->gp_new_split = gram_plan_split(c->gp_new2, c->d, c->num_cu > 32 ? (c->num_cu - 16) / 8 * 8 : 8);
+        // beside the eigensolve: one work-group per CU of the seven XCDs that it leaves alone, so that the kernels after
+        // the reduction find room beside them
+        c->gp_new_split = gram_plan_split(c->gp_new2, c->d, c->num_cu > 32 ? c->num_cu / 8 * 7 : 8);
     }
     c->fixed_cap = max_rows > 0;
     c->cap_rows = max_rows > 0 ? max_rows : 65536;

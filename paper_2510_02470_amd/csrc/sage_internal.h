@@ -73,14 +73,31 @@ __device__ __forceinline__ unsigned hi_bf16(float x, float y) {
 // ---- kernel launchers (each enqueues on `st` and returns hipGetLastError()) ---------------------------------
 // launch_util.hip: raise a kernel's dynamic LDS limit, once per (device, kernel); thread-safe
 hipError_t ensure_dynamic_lds(const void* kernel, int bytes);
+// The XCD this work-group runs on, 0..7. Eight consecutive work-groups run on eight different ones (checked once per device,
+// tridiag_local_ok); which of them the first gets differs from queue to queue, so nothing may be concluded from blockIdx alone.
+__device__ __forceinline__ int xcd_id() {
+    int id;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(id));
+    return id & 7;
+}
+// Work that runs beside an eigensolve keeps off the XCD the reduction has to itself: work-groups on XCD `skip` return at once
+// and the others take the work between them (skip = -1: all eight).
+// xcd_rank: this work-group's number among those that work, or -1.
+__device__ __forceinline__ int64_t xcd_rank(unsigned block, int skip) {
+    if (skip < 0) return block;
+    const int x = xcd_id();
+    if (x == skip) return -1;
+    return (int64_t)(block >> 3) * 7 + x - (x > skip);
+}
+inline int64_t xcd_grid(int64_t work, int skip) { return skip < 0 ? work : (work + 6) / 7 * 8; }  // work-groups to launch
 // fd_insert.hip
 // copy `rows` batch rows into rows row0.. of a half buffer (half_rows rows per slab)
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         hipStream_t st);
+                         int skip, hipStream_t st);
 // factored rows (E: rows x C logit errors, H: rows x dh features, both of the row type): column c*dh + t = e_c * h_t
 // rounded as a stored row would be, column C*dh + c = e_c; requires D = C * (dh + 1)
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, hipStream_t st);
+                               float* half, int half_rows, const Dims& d, int skip, hipStream_t st);
 // ... written out row-major (rows x D of the row type)
 hipError_t launch_expand_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, void* out,
                                const Dims& d, hipStream_t st);
@@ -111,7 +128,7 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
 // new_one: every new row in use holds bf16 values (one part instead of three in the split-arithmetic kernels; the
 // result has the same bits)
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
-                       hipStream_t st, bool new_one = false);
+                       hipStream_t st, bool new_one = false, int skip = -1);
 // C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
 // (the Gram matrix of the rows the last shrink wrote, see EigWork::known)
 hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const float* partial_b, const GramPlan* b,
