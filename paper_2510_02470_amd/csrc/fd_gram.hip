@@ -699,8 +699,8 @@ __global__ __launch_bounds__(256, 2) void gram_new8_split_kernel(const float* __
 
 // C (NP x NP, fp64, both triangles) = sum over groups of the partial tiles, in group order. With q = P/2:
 // known_top: tiles with ti < q are not summed, their block is diag(known) (the top rows are the rows the last shrink
-// wrote, whose Gram matrix it recorded). Otherwise tile (ti, tj) comes from source A when its mode
-// covers it, else from source B (mode-1 and mode-2 launches write separate partial buffers).
+// wrote, whose Gram matrix it recorded). Otherwise tile (ti, tj) comes from the first of the sources whose mode covers it
+// (launches of different modes write separate partial buffers; mode 3: the mode-2 kernel given the top rows).
 struct GramSrc {
     const float* partial;
     int mode, t0, tiles, groups;
@@ -709,9 +709,10 @@ __device__ __forceinline__ int gram_src_index(const GramSrc& g, int P, int t, in
     const int q = P >> 1;
     if (g.mode == 0) return (t >= g.t0 && t < g.t0 + g.tiles) ? t - g.t0 : -1;
     if (g.mode == 1) return (ti >= q && tj < q) ? (ti - q) * q + tj : -1;
+    if (g.mode == 3) return ti < q ? t : -1;
     return (ti >= q && tj >= q) ? (ti - q) * (ti - q + 1) / 2 + (tj - q) : -1;
 }
-__global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, double* __restrict__ C, int NP,
+__global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, GramSrc top, double* __restrict__ C, int NP,
                                                           int known_top, const double* __restrict__ known) {
     const int P = NP / 64;
     int t = blockIdx.x;
@@ -726,8 +727,9 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, 
         s = gr == gc ? known[gr] : 0.0;
     } else {
         int ia = gram_src_index(a, P, t, ti, tj);
-        const GramSrc& g = ia >= 0 ? a : b;
-        int idx = ia >= 0 ? ia : gram_src_index(b, P, t, ti, tj);
+        const int ib = gram_src_index(b, P, t, ti, tj);
+        const GramSrc& g = ia >= 0 ? a : (ib >= 0 ? b : top);
+        const int idx = ia >= 0 ? ia : (ib >= 0 ? ib : gram_src_index(top, P, t, ti, tj));
         if (idx >= 0) {
             const float* p0 = g.partial + (int64_t)idx * 4096 + e;
             const int64_t gstride = (int64_t)g.tiles * 4096;
@@ -853,13 +855,16 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
     return hipGetLastError();
 }
 
-// a, b: the launches whose partial tiles make up C (b may be null); known: LP doubles, read when known_top
+// a, b: the launches whose partial tiles make up C (b may be null); known: LP doubles, read when known_top.
+// partial_top, top: a mode-2 launch that was given the top rows in place of the new ones (may be null)
 hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const float* partial_b, const GramPlan* b,
-                              double* C, bool known_top, const double* known, const Dims& d, hipStream_t st) {
+                              double* C, bool known_top, const double* known, const Dims& d, hipStream_t st,
+                              const float* partial_top, const GramPlan* top) {
     const int P = d.NP / 64;
     GramSrc sa{partial_a, a.mode, a.t0, a.tiles, a.groups};
     GramSrc sb{partial_b, b ? b->mode : 0, b ? b->t0 : 0, b ? b->tiles : 0, b ? b->groups : 0};
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3(P * (P + 1) / 2, 16), dim3(256), 0, st, sa, sb, C, d.NP, known_top ? 1 : 0,
+    GramSrc stop{partial_top, top ? 3 : 0, 0, top ? top->tiles : 0, top ? top->groups : 0};
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3(P * (P + 1) / 2, 16), dim3(256), 0, st, sa, sb, stop, C, d.NP, known_top ? 1 : 0,
                        known);
     return hipGetLastError();
 }

@@ -108,42 +108,54 @@ __device__ __forceinline__ float outer_value(const T* __restrict__ e, const T* _
     }
 }
 
-// Factored rows for insert_kernel. One division per thread: the class and feature of its first column, then steps of
-// sixteen columns with wrap-around.
+// Four neighbouring values at any element boundary.
+template <typename T>
+struct __attribute__((packed, aligned(sizeof(T)))) Four {
+    T v[4];
+};
+
+// Factored rows for insert_kernel. One division per thread, for the class and feature of its first column, then steps of
+// sixteen columns with wrap-around; four columns of one class take one load of h and one of e.
 template <typename T>
 struct OuterRows {
     const T* E;
     const T* H;
     int64_t C, dh;
+    static __device__ __forceinline__ float value(T e, T h) {
+        if constexpr (sizeof(T) == 2) return (float)(__bf16)(bf16_to_f32(e) * bf16_to_f32(h));
+        else return e * h;
+    }
     template <int NS>
     __device__ __forceinline__ void load(int r, int64_t d0, int64_t D, float4 (&v)[NS]) const {
         const int64_t main = C * dh;
         const T* e = E + r * C;
         const T* h = H + r * dh;
         int64_t cls = d0 / dh, t = d0 - cls * dh;
+        T ev[NS];
+        Four<T> hv[NS];
+        bool fast[NS];
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
-            const int64_t d = d0 + i * DC;
-            float x[4];
-            if (d + 3 < main) {
-                int64_t cl = cls, tt = t;
+            fast[i] = cls < C && t + 3 < dh;
+            if (fast[i]) {
+                ev[i] = e[cls];
+                hv[i] = *reinterpret_cast<const Four<T>*>(h + t);
+            }
+            t += DC;
+            while (t >= dh) {
+                t -= dh;
+                ++cls;
+            }
+        }
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if constexpr (sizeof(T) == 2) x[c] = (float)(__bf16)(bf16_to_f32(e[cl]) * bf16_to_f32(h[tt]));
-                    else x[c] = e[cl] * h[tt];
-                    if (++tt == dh) {
-                        tt = 0;
-                        ++cl;
-                    }
-                }
-                t += DC;
-                while (t >= dh) {
-                    t -= dh;
-                    ++cls;
-                }
+        for (int i = 0; i < NS; ++i) {
+            float x[4];
+            if (fast[i]) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[c] = value(ev[i], hv[i].v[c]);
             } else {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) x[c] = outer_value(e, h, d + c, main, dh, D);
+                for (int c = 0; c < 4; ++c) x[c] = outer_value(e, h, d0 + i * DC + c, main, dh, D);
             }
             v[i] = make_float4(x[0], x[1], x[2], x[3]);
         }
