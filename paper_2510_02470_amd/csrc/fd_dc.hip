@@ -47,8 +47,9 @@ __device__ __forceinline__ double sqrt64(double x) {
 
 // Root q of 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending): lambda = org + tau with org the
 // nearer of the poles around it. A group of L lanes works on a root; lane l holds the poles l + L e, e < E (z = 0 and
-// d = 1e30 beyond K). The interpolation converges quadratically: a step below 1e-9 of tau is the last one. About 3
-// evaluations a root.
+// d = 1e30 beyond K). The interpolation converges quadratically: a step below 1e-9 of tau is the last one. About four
+// evaluations a root, six for the slowest of a wave. What counts is the number of fp64 instructions (4 cycles each on a
+// SIMD, 16 for the reciprocal estimate): a pole costs 11 of them, a root's step 45 and 12 per stage of the sums over L.
 template <int L, int E>
 __device__ __forceinline__ void secular_root(int K, int q, int l, const double (&dj)[E], const double (&zj)[E], double dq,
                                              double dq1, double zsum, double& org, double& tau) {
@@ -70,21 +71,24 @@ __device__ __forceinline__ void secular_root(int K, int q, int l, const double (
         }
     }
     double t = 0.5 * (lo + hi);
-    double dl[E];
+    double dl[E], zl[E], zr[E];  // distance of the poles; weights of those up to q, of those above
 #pragma unroll
-    for (int e = 0; e < E; ++e) dl[e] = dj[e] - org;
+    for (int e = 0; e < E; ++e) {
+        dl[e] = dj[e] - org;
+        const bool low = l + L * e <= q;
+        zl[e] = low ? zj[e] : 0.0;
+        zr[e] = low ? 0.0 : zj[e];
+    }
     const double dlq = dq - org, dlq1 = dq1 - org;
     for (int it = 0; it < 60; ++it) {
         double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const double inv = rcp64(dl[e] - t);
-            const double r = zj[e] * inv, r2 = r * inv;
-            const bool low = l + L * e <= q;
-            psi += low ? r : 0.0;
-            dpsi += low ? r2 : 0.0;
-            phi += low ? 0.0 : r;
-            dphi += low ? 0.0 : r2;
+            const double inv = rcp64(dl[e] - t), inv2 = inv * inv;
+            psi = __builtin_fma(zl[e], inv, psi);
+            phi = __builtin_fma(zr[e], inv, phi);
+            dpsi = __builtin_fma(zl[e], inv2, dpsi);
+            dphi = __builtin_fma(zr[e], inv2, dphi);
         }
         psi = lane_sum<L>(psi);
         dpsi = lane_sum<L>(dpsi);
@@ -93,29 +97,36 @@ __device__ __forceinline__ void secular_root(int K, int q, int l, const double (
         const double f = 1.0 + psi + phi;
         // psi < 0 < phi: phi - psi is the sum of the magnitudes
         if (!(fabs(f) > 0.5 * DC_EPS * K * (1.0 + (phi - psi)))) break;
-        if (f < 0.0) lo = fmax(lo, t);
-        else hi = fmin(hi, t);
-        double x;
+        lo = f < 0.0 ? t : lo;  // (t lies inside the bracket)
+        hi = f < 0.0 ? hi : t;
         const double di = dlq - t;
+        // A step needs few digits: its error shrinks with the step, which is below 1e-9 of t when it is the last. So the
+        // square root is the hardware's estimate with one correction, and so is the quotient.
+        double num, den, off = 0.0, lim0 = di, lim1 = 1e300;
         if (!last) {
             const double dn = dlq1 - t;  // di < 0 < dn
             const double p = di * di * dpsi, g = dn * dn * dphi;
-            const double c = 1.0 + (psi - di * dpsi) + (phi - dn * dphi);
-            // c + p / (di - x) + g / (dn - x) = 0, the root between the poles
-            const double b = -(c * (di + dn) + p + g), a0 = c * di * dn + p * dn + g * di;
-            const double s = sqrt64(fmax(__builtin_fma(b, b, -4.0 * c * a0), 0.0));
-            const double h = -0.5 * (b + __builtin_copysign(s, b));
-            const double x1 = a0 * rcp64(h), x2 = h * rcp64(c);
-            x = (x1 > di && x1 < dn) ? x1 : x2;
-            if (!(x > di && x < dn)) x = __builtin_nan("");
+            const double c = 1.0 + __builtin_fma(-di, dpsi, psi) + __builtin_fma(-dn, dphi, phi);
+            // c + p / (di - x) + g / (dn - x) = 0, the root between the poles: c x^2 - a x + b = 0
+            const double a = __builtin_fma(c, di + dn, p + g), b = __builtin_fma(c * di, dn, __builtin_fma(p, dn, g * di));
+            const double disc = fmax(__builtin_fma(a, a, -4.0 * c * b), 1e-280);
+            const double y = __builtin_amdgcn_rsq(disc), r = disc * y;
+            const double sq = __builtin_fma(__builtin_fma(-r, r, disc), 0.5 * y, r);
+            const double h = 0.5 * (a + __builtin_copysign(sq, a));
+            num = a > 0.0 ? b : h;
+            den = a > 0.0 ? h : c;
+            lim1 = dn;
         } else {
-            const double s = 1.0 + (psi - di * dpsi);
-            x = s > 0.0 ? di + di * di * dpsi * rcp64(s) : __builtin_nan("");
+            num = di * di * dpsi;
+            den = 1.0 + __builtin_fma(-di, dpsi, psi);  // (not positive: the step leaves the bracket, which is halved)
+            off = di;
         }
-        double tn = t + x;
-        const bool in = tn > lo && tn < hi;
-        if (!in) tn = 0.5 * (lo + hi);
-        const bool done = tn == t || !(hi - lo > fabs(t) * DC_EPS) || (in && fabs(x) <= 1e-9 * fabs(tn));
+        double y = __builtin_amdgcn_rcp(den);
+        y = __builtin_fma(__builtin_fma(-den, y, 1.0), y, y);
+        const double x = __builtin_fma(num, y, off), step = t + x;
+        const bool in = x > lim0 && x < lim1 && step > lo && step < hi;  // (false for NaN)
+        const double tn = in ? step : 0.5 * (lo + hi);
+        const bool done = in ? fabs(x) <= 1e-9 * fabs(tn) : !(hi - lo > fabs(tn) * DC_EPS);
         t = tn;
         if (done) break;
     }
@@ -165,7 +176,8 @@ struct DcBlockLds {
     double rc[64], rs[64], td[64];  // rotations; poles they deflate
     int cs[64], col[64], np[64], ra[64], rb[64], tc[64];
     int K[64], nrot[64];            // per sub-problem (indexed by its base)
-    unsigned char mask[8];          // surviving entries, in order
+    int lst[64];                    // entries (in dk order) whose columns belong to the left half, then the others
+    unsigned char mask[8], maskl[8];  // surviving entries, entries of the left half, in order
     int any;
 };
 
@@ -203,7 +215,11 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
     const bool live = rho * fabs(zsi) > tol;
     {
         const unsigned long long b = __ballot(live) & 0x0101010101010101ull;  // bit 8 q: index 8 wave + q
-        if ((tid & 63) == 0) S.mask[tid >> 6] = (unsigned char)((b * 0x0102040810204080ull) >> 56);
+        const unsigned long long c = __ballot((csi & (M - 1)) < H) & 0x0101010101010101ull;
+        if ((tid & 63) == 0) {
+            S.mask[tid >> 6] = (unsigned char)((b * 0x0102040810204080ull) >> 56);
+            S.maskl[tid >> 6] = (unsigned char)((c * 0x0102040810204080ull) >> 56);
+        }
     }
     __syncthreads();
     const unsigned long long all = *reinterpret_cast<const unsigned long long*>(S.mask);
@@ -212,6 +228,15 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
     {
         const int before = __popcll(sub & ((1ull << li) - 1ull));
         const int pos = live ? before : K + li - before;
+        if (M >= 32 && l == 1) {
+            const unsigned long long alll = *reinterpret_cast<const unsigned long long*>(S.maskl);
+            const unsigned long long ones = M == 64 ? ~0ull : (1ull << (M & 63)) - 1ull, below = (1ull << li) - 1ull;
+            const unsigned long long subl = (M == 64 ? alll : alll >> base) & ones;
+            const bool left = (csi & (M - 1)) < H;
+            const unsigned long long side = left ? subl : ~subl & ones;  // entries of this one's half
+            const int r = live ? __popcll(side & sub & below) : __popcll(side & sub) + __popcll(side & ~sub & below);
+            S.lst[base + (left ? r : H + r)] = pos;
+        }
         if (l == 0) {
             S.dk[base + pos] = dsi;
             S.zk[base + pos] = zsi;
@@ -285,28 +310,43 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
         __syncthreads();
     }
     const double dki = S.dk[i];
-    double dj[E], zj[E], zsum = 0.0;
+    // Four lanes a root up to 16 rows, where most of a step does not depend on the number of poles; eight above (two waves
+    // per SIMD, of which each issues an instruction every five cycles at best).
+    constexpr int LR = M >= 32 ? 8 : 4, ER = M / LR;
+    if (LR == 8 || tid < 256) {
+        const int ir = tid / LR, lr = tid & (LR - 1), br = ir & ~(M - 1), lir = ir & (M - 1);
+        const int Kr = LR == 8 ? K : S.K[br];
+        const double dkr = S.dk[ir], rhor = fabs(S.e[br + H - 1]);
+        double dj[ER], zj[ER], zsum = 0.0;
+#pragma unroll
+        for (int e = 0; e < ER; ++e) {
+            const int j = lr + LR * e;
+            const bool on = j < Kr;
+            dj[e] = on ? S.dk[br + j] : 1e30;
+            const double z = on ? S.zk[br + j] : 0.0;
+            zj[e] = rhor * z * z;
+            zsum += zj[e];
+        }
+        zsum = lane_sum<LR>(zsum);
+        double org = 0.0, tau = 0.0, val = dkr;
+        if (lir < Kr) {
+            secular_root<LR, ER>(Kr, lir, lr, dj, zj, dkr, lir + 1 < Kr ? S.dk[ir + 1] : 0.0, zsum, org, tau);
+            val = finite_or_zero(org + tau);
+        }
+        if (lr == 0) {
+            S.org[ir] = org;
+            S.tau[ir] = tau;
+            S.val[ir] = val;
+        }
+    }
+    __syncthreads();
+    const double org = S.org[i], tau = S.tau[i], val = S.val[i];
+    double dj[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int j = l + 8 * e;
-        const bool on = j < K;
-        dj[e] = on ? S.dk[base + (j & (M - 1))] : 1e30;
-        const double z = on ? S.zk[base + (j & (M - 1))] : 0.0;
-        zj[e] = rho * z * z;
-        zsum += zj[e];
+        dj[e] = j < K ? S.dk[base + (j & (M - 1))] : 1e30;
     }
-    zsum = lane_sum<8>(zsum);
-    double org = 0.0, tau = 0.0, val = dki;
-    if (li < K) {
-        secular_root<8, E>(K, li, l, dj, zj, dki, li + 1 < K ? S.dk[i + 1] : 0.0, zsum, org, tau);
-        val = finite_or_zero(org + tau);
-    }
-    if (l == 0) {
-        S.org[i] = org;
-        S.tau[i] = tau;
-        S.val[i] = val;
-    }
-    __syncthreads();
     {
         double og[E], ta[E];
         int np = 0;
@@ -346,6 +386,8 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
     __syncthreads();
     if constexpr (M >= 16) {
         constexpr int T = M / 16, TILES = (64 / M) * T * T, PER = TILES > 8 ? TILES / 8 : 1;
+        // The columns of Q are still those of the halves: a row tile meets the H of its own half, unless rotations mixed them.
+        const bool dense = M == 16 || S.any != 0;  // (a tile of 16 rows spans both halves of 16)
         const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lk = lane >> 4;
         f64x4 acc[PER];
 #pragma unroll
@@ -354,10 +396,20 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
             const int t = wave + 8 * g;
             if (t < TILES) {
                 const int sb = (t / (T * T)) * M, r0 = sb + ((t / T) % T) * 16, c0 = sb + (t % T) * 16;
+                if (!dense) {
+                    const int half = (r0 - sb) & H;
 #pragma unroll
-                for (int k = 0; k < M; k += 4) {
-                    const double av = S.Q[S.col[sb + k + lk] * DCB_LD + r0 + l16];
-                    acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + k + lk], acc[g]);
+                    for (int k = 0; k < H; k += 4) {
+                        const int j = S.lst[sb + half + k + lk];
+                        const double av = S.Q[S.col[sb + j] * DCB_LD + r0 + l16];
+                        acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + j], acc[g]);
+                    }
+                } else {
+#pragma unroll 4
+                    for (int k = 0; k < M; k += 4) {
+                        const double av = S.Q[S.col[sb + k + lk] * DCB_LD + r0 + l16];
+                        acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + k + lk], acc[g]);
+                    }
                 }
             }
         }
@@ -590,7 +642,7 @@ __global__ __launch_bounds__(512) void dc_deflate_kernel(const double* __restric
 
 // One wave per root. WYJ > 0 (the first merge of N = 64 WYJ): the row of work-groups after the last sub-problem's forms the
 // triangular factors of the reduction's blocks of reflectors, a wave each (wy_factor).
-template <int WYJ>
+template <int E, int WYJ>  // m = 64 E
 __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict__ eT, int m, DcWork w,
                                                        const double* __restrict__ V, const double* __restrict__ tauT, int n,
                                                        double* __restrict__ Tw) {
@@ -608,9 +660,9 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
     double org = 0.0, tau = 0.0, val = w.dk[base + q];
     if (q < K) {
         const double rho = fabs(finite_or_zero(eT[base + (m >> 1) - 1]));
-        double dj[8], zj[8], zsum = 0.0;
+        double dj[E], zj[E], zsum = 0.0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < E; ++e) {
             const int j = lane + 64 * e;
             const bool on = j < K;
             dj[e] = on ? w.dk[base + j] : 1e30;
@@ -619,7 +671,7 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
             zsum += zj[e];
         }
         zsum = lane_sum<64>(zsum);
-        secular_root<64, 8>(K, q, lane, dj, zj, w.dk[base + q], q + 1 < K ? w.dk[base + q + 1] : 0.0, zsum, org, tau);
+        secular_root<64, E>(K, q, lane, dj, zj, w.dk[base + q], q + 1 < K ? w.dk[base + q + 1] : 0.0, zsum, org, tau);
         val = finite_or_zero(org + tau);
     }
     if (lane == 0) {
@@ -630,6 +682,7 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
 }
 
 // one wave per index: z of the merge, and the place of its eigenvalue among all
+template <int E>  // m = 64 E
 __global__ __launch_bounds__(256) void dc_weights_kernel(int m, DcWork w, double* __restrict__ dO) {
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -638,7 +691,7 @@ __global__ __launch_bounds__(256) void dc_weights_kernel(int m, DcWork w, double
     const double val = w.val[base + q];
     int np = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < E; ++e) {
         const int j = lane + 64 * e;
         if (j < m) {
             const double x = w.val[base + j];
@@ -648,15 +701,15 @@ __global__ __launch_bounds__(256) void dc_weights_kernel(int m, DcWork w, double
     np = lane_sum_i<64>(np);
     double zz = 0.0;
     if (q < K) {
-        double di[8], og[8], ta[8];
+        double di[E], og[E], ta[E];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < E; ++e) {
             const int j = lane + 64 * e;
             di[e] = j < K ? w.dk[base + j] : 0.0;
             og[e] = j < K ? w.org[base + j] : 0.0;
             ta[e] = j < K ? w.tau[base + j] : 0.0;
         }
-        zz = __builtin_copysign(secular_z<64, 8>(K, q, lane, w.dk[base + q], di, og, ta), w.zk[base + q]);
+        zz = __builtin_copysign(secular_z<64, E>(K, q, lane, w.dk[base + q], di, og, ta), w.zk[base + q]);
     }
     if (lane == 0) {
         w.zh[base + q] = zz;
@@ -783,15 +836,18 @@ hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
     for (int m = 128; m <= N; m *= 2) {
         const int S = N / m;
         hipLaunchKernelGGL(dc_deflate_kernel, dim3(S), dim3(512), 0, st, w.dT, w.eT, N, m, w.dI[cur], w.Z[cur], w.dc);
-#define SAGE_ROOTS(WYJ)                                                                                              \
-    hipLaunchKernelGGL(dc_roots_kernel<WYJ>, dim3(m / 4, WYJ > 0 ? S + 1 : S), dim3(256), 0, st, w.eT, m, w.dc, w.V, \
-                       w.tauT, n, w.Tw)
-        if (m > 128) SAGE_ROOTS(0);
-        else if (N == 128) SAGE_ROOTS(2);
-        else if (N == 256) SAGE_ROOTS(4);
-        else SAGE_ROOTS(8);
+#define SAGE_ROOTS(E, WYJ)                                                                                              \
+    do {                                                                                                                \
+        hipLaunchKernelGGL((dc_roots_kernel<E, WYJ>), dim3(m / 4, WYJ > 0 ? S + 1 : S), dim3(256), 0, st, w.eT, m, w.dc, \
+                           w.V, w.tauT, n, w.Tw);                                                                       \
+        hipLaunchKernelGGL(dc_weights_kernel<E>, dim3(m / 4, S), dim3(256), 0, st, m, w.dc, w.dI[cur ^ 1]);              \
+    } while (0)
+        if (m == 512) SAGE_ROOTS(8, 0);
+        else if (m == 256) SAGE_ROOTS(4, 0);
+        else if (N == 128) SAGE_ROOTS(2, 2);
+        else if (N == 256) SAGE_ROOTS(2, 4);
+        else SAGE_ROOTS(2, 8);
 #undef SAGE_ROOTS
-        hipLaunchKernelGGL(dc_weights_kernel, dim3(m / 4, S), dim3(256), 0, st, m, w.dc, w.dI[cur ^ 1]);
         hipLaunchKernelGGL(dc_vectors_kernel, dim3(m / 32, m / 64, S), dim3(256), 0, st, w.Z[cur], w.Z[cur ^ 1], N, m, w.dc);
         cur ^= 1;
     }

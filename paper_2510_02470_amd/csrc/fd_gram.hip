@@ -771,8 +771,10 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
     const int cus = side && num_cu > 32 ? num_cu / 8 * 7 : num_cu;
     int g = (wg_per_cu * cus / p.wg_per_group) / 8 * 8;
     if (g < 8) g = 8;
-    // keep at least 4 slabs per group so that tiny problems do not drown in partial tiles
-    int64_t gmax = ((d.S + 3) / 4 + 7) / 8 * 8;
+    // At least 4 slabs per group so that small problems do not drown in partial tiles; 2 where there are so few slabs that
+    // the chain of loads of a group is what counts (64 rows x 512 columns: 9.3 us -> 5).
+    const int64_t least = d.S <= 256 ? 2 : 4;
+    int64_t gmax = ((d.S + least - 1) / least + 7) / 8 * 8;
     if (gmax < 8) gmax = 8;
     if (g > gmax) g = (int)gmax;
     p.groups = g;

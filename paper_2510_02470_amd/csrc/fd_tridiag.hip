@@ -311,13 +311,15 @@ __device__ __forceinline__ double entry_value(const u32x4& e) {
     return __longlong_as_double(((long long)e[2] << 32) | e[0]);
 }
 
+constexpr int many_columns(int J) { return J >= 4 ? 4 : 2; }
+
 template <int J, bool LOCAL>
 __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, u32x4* __restrict__ xch,
                                                           unsigned tag0, int xcd) {
-    constexpr int N = 64 * J, NW = N / 4;  // NW waves in all
+    constexpr int N = 64 * J, CW = many_columns(J), NW = N / CW, NWG = NW / 4;  // columns of a wave; waves, work-groups
     if ((LOCAL ? xcd_id() : (int)(blockIdx.x & 7)) != xcd) return;  // one of eight consecutive work-groups
     __builtin_amdgcn_s_setprio(3);
     __shared__ Pair qc[2][N];  // {q, c} by step parity
@@ -327,8 +329,10 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
     const int wg = blockIdx.x >> 3;
 
     if (wave >= 4) {  // ---- pollers: entries t, t + 256, .. of c and q
-        constexpr int PT = N / 256;
-        const int t = tid & 255;
+        // J = 2: half the waves wait for c and half for q
+        constexpr int PT = J >= 4 ? N / 256 : 1;
+        const int t = tid & (J >= 4 ? 255 : 127);
+        const bool for_c = J >= 4 || wave < 6;
         int spins = SPIN_LIMIT;
         for (int k = 0; k < n - 1; ++k) {
             const int par = k & 1;
@@ -378,16 +382,22 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             };
             const u32x4* const qx = xch + par * 2 * N + t;
             double cv[PT], qv[PT];
-            poll(qx + N, cv);
-            poll(qx, qv);
+            if constexpr (J >= 4) {
+                poll(qx + N, cv);
+                poll(qx, qv);
 #pragma unroll
-            for (int u = 0; u < PT; ++u) qc[par][t + 256 * u] = Pair{qv[u], cv[u]};
+                for (int u = 0; u < PT; ++u) qc[par][t + 256 * u] = Pair{qv[u], cv[u]};
+            } else {
+                poll(for_c ? qx + N : qx, cv);
+                if (for_c) qc[par][t].b = cv[0];
+                else qc[par][t].a = cv[0];
+            }
             lds_barrier();
         }
         return;
     }
 
-    // Wave gw owns the columns of lane gw % 64: cl + 64 (H + s J / 4), s < 4, H = gw / 64 < J / 4. So the entries of v and w at
+    // Wave gw owns the columns of lane gw % 64: cl + 64 (H + s J / CW), s < CW, H = gw / 64 < J / CW. So the entries of v and w at
     // its own columns are in one lane of its own registers.
     const int gw = wg * 4 + wave, cl = gw & 63;
     const double md = wave_max_diag(C, NP, lane);
@@ -396,8 +406,8 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
     if (wg == 0 && tid == 0) stat[0] = (double)ex;
 
     auto reduce = [&](auto hc) __attribute__((always_inline)) {
-        constexpr int H = decltype(hc)::value, ST = J / 4;  // register index of column s: H + ST * s
-        double a[4][J], x[J], v[J], w[J];
+        constexpr int H = decltype(hc)::value, ST = J / CW;  // register index of column s: H + ST * s
+        double a[CW][J], x[J], v[J], w[J];
         {
             int mrow[J];
 #pragma unroll
@@ -406,7 +416,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                 mrow[j] = r < n ? active_index(r, m0, LP) : -1;
             }
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < CW; ++s) {
                 const int col = cl + 64 * (H + ST * s);
                 const double* src = C + (int64_t)active_index(col < n ? col : 0, m0, LP) * NP;
 #pragma unroll
@@ -430,9 +440,9 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             u32x4* const cx = qx + N;
 #pragma unroll
             for (int j = 0; j < J; ++j) x[j] = lane + 64 * j > k + 1 ? x[j] : 0.0;
-            double acc[4], vcol[4], wcol[4];
+            double acc[CW], vcol[CW], wcol[CW];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < CW; ++s) {
                 vcol[s] = read_lane(v[H + ST * s], cl);
                 wcol[s] = read_lane(w[H + ST * s], cl);
             }
@@ -442,16 +452,16 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             auto pass = [&](auto j0c) __attribute__((always_inline)) {
                 constexpr int J0 = decltype(j0c)::value;
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
+                for (int s = 0; s < CW; ++s)
 #pragma unroll
                     for (int j = J0; j < J; ++j) a[s][j] = __builtin_fma(-w[j], vcol[s], a[s][j]);
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
+                for (int s = 0; s < CW; ++s)
 #pragma unroll
                     for (int j = J0; j < J; ++j) a[s][j] = __builtin_fma(-v[j], wcol[s], a[s][j]);
                 if (((k + 1) & 63) == cl && (((k + 1) >> 6) & (ST - 1)) == H) {  // column k + 1 is this wave's
 #pragma unroll
-                    for (int s = 0; s < 4; ++s)
+                    for (int s = 0; s < CW; ++s)
                         if ((k + 1) >> 6 == H + ST * s) {
 #pragma unroll
                             for (int j = J0; j < J; ++j) {
@@ -462,15 +472,15 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                         }
                 }
 #pragma unroll
-                for (int s = 0; s < 4; ++s) acc[s] = a[s][J0] * x[J0];
+                for (int s = 0; s < CW; ++s) acc[s] = a[s][J0] * x[J0];
 #pragma unroll
                 for (int j = J0 + 1; j < J; ++j)
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) acc[s] = __builtin_fma(a[s][j], x[j], acc[s]);
+                    for (int s = 0; s < CW; ++s) acc[s] = __builtin_fma(a[s][j], x[j], acc[s]);
             };
             if (k < 32 * J) pass(std::integral_constant<int, 0>{});
             else pass(std::integral_constant<int, J / 2>{});
-            {   // the four sums over the wave: two at a time per lane pair, then one per lane of a quad
+            if constexpr (CW == 4) {  // the four sums over the wave: two at a time per lane pair, then one per lane of a quad
                 const bool odd = lane & 1, hi = lane & 2;
                 double t0 = odd ? acc[1] : acc[0], o0 = odd ? acc[0] : acc[1];
                 double t1 = odd ? acc[3] : acc[2], o1 = odd ? acc[2] : acc[3];
@@ -488,6 +498,20 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                 const int col = cl + 64 * (H + ST * (lane & 3));
                 if (lane < 4 && col > k && col < n) put_entry<LOCAL>(qx + col, t, tag);
             }
+            else {  // two sums: one per lane of a pair
+                const bool odd = lane & 1;
+                double x = (odd ? acc[1] : acc[0]) + dpp_move<DPP_XOR1>(odd ? acc[0] : acc[1]);
+                x += dpp_move<DPP_XOR2>(x);
+                x += dpp_move<0x124>(x);  // row_ror 4
+                x += dpp_move<0x128>(x);  // row_ror 8
+                double b0, b1;
+                swap_rows<16>(x, b0, b1);
+                x = b0 + b1;
+                swap_rows<32>(x, b0, b1);
+                x = b0 + b1;
+                const int col = cl + 64 * (H + ST * (lane & 1));
+                if (lane < 2 && col > k && col < n) put_entry<LOCAL>(qx + col, x, tag);
+            }
             // while the entries travel: the reflector
             double r2 = 0.0;
 #pragma unroll
@@ -504,7 +528,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             asm volatile("" ::: "memory");
             const int i2 = k + 2 < n ? k + 2 : k + 1;
             const double v2 = vs[wave][i2];
-            if (wg == (k & (N / 16 - 1))) {
+            if (wg == (k & (NWG - 1))) {
                 if (wave == 0) {
 #pragma unroll
                     for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = v[j];
@@ -543,9 +567,9 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             tauT[n - 1] = 0.0;
         }
     };
-    static_assert(J == 4 || J == 8, "one or two columns a lane");
-    if (J == 4 || gw < 64) reduce(std::integral_constant<int, 0>{});
-    else reduce(std::integral_constant<int, J / 4 - 1>{});
+    static_assert(NW == 64 || NW == 128, "one or two columns a lane");
+    if (NW == 64 || gw < 64) reduce(std::integral_constant<int, 0>{});
+    else reduce(std::integral_constant<int, NW / 64 - 1>{});
     if (wg == 0) {
         for (int i = n + tid; i < N; i += 256) {
             dT[i] = -1.0;
@@ -563,15 +587,100 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
 // products summed over the wave together, an 8 x 8 triangle and 8 updates, so the latency of a sum over the wave is paid
 // once per eight reflectors (one or two at a time it was the bound). Rows before a block's first are zero in V and left
 // out in quarters, each a loop of its own: with the choice inside one loop the waits for the next block's loads came
-// early. Column `col` of Z (column-major, ascending eigenvalues) becomes row N - 1 - col of Yt (descending), in matrix
-// indices.
-template <int J>
+// early. Column N - 1 - m of Z (column-major, ascending eigenvalues) is the eigenvector of the m-th largest eigenvalue.
+//
+// OUT_Y: the vectors are stored, row m of Yt, in matrix indices. Otherwise a wave goes on to the rebuild's coefficients made
+// from its vector, row m < count of diag(f) Y^T (zero rows up to MP), which saves a launch and a trip through memory (4.5 us
+// at n = 64, 7.5 at 512):
+//   mode 0, shrink (delta = sigma_ell^2, Sigma'_jj = sqrt(max(sigma_j^2 - delta, 0))): f_m = sqrt(max(lambda_m - delta, 0) /
+//           lambda_m), so that row m is sqrt(sigma_m^2 - delta) v_m^T. Also records the Gram matrix of the rows the
+//           rebuild is about to write, diag(max(lambda_m - delta, 0)), in `known`: the next cycle takes that block as
+//           known instead of recomputing it.
+//   mode 1, basis: f_m = 1 / sqrt(lambda_m), or 0 when lambda_m <= n 2^-23 lambda_1.
+//   mode 2, weighted basis: f_m = sqrt(max(lambda_m - delta, 0) / lambda_m) under the same rank test, which makes the row the
+//           m-th of the sketch a shrink of the buffer would write ("Two-pass scoring": z = S g).
+// A lane makes the 8 coefficients (stage, k-half h, row m) that a matrix-core lane of the rebuild takes per stage of 16
+// buffer rows: buffer rows 16 * stage + 2 s + h, s < 8. OUT_SPLIT: as three bf16 parts in the order rebuild_split_kernel
+// streams them; OUT_F32: in coeff_offset order. The work-group after the last row does the scalars.
+enum { OUT_Y, OUT_F32, OUT_SPLIT };
+struct Coeffs8 {
+    float c[8];
+};
+template <int OUT>
+__device__ __forceinline__ void store_coeffs(const CoeffArgs& cf, int stg, int h, int m, const Coeffs8& v) {
+    if constexpr (OUT == OUT_SPLIT) {
+        u32x4 hi, mid, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            unsigned a, b, c;
+            split3_bf16(v.c[2 * e], v.c[2 * e + 1], a, b, c);
+            hi[e] = a;
+            mid[e] = b;
+            lo[e] = c;
+        }
+        u32x4* dst = (u32x4*)cf.Mc3 + (int64_t)stg * (3 * 2 * cf.MP) + h * cf.MP + m;
+        dst[0] = hi;
+        dst[2 * cf.MP] = mid;
+        dst[4 * cf.MP] = lo;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            *reinterpret_cast<f32x4*>(cf.Mt + coeff_offset(stg * 16 + h + 8 * q, m, cf.MP)) =
+                f32x4{v.c[4 * q], v.c[4 * q + 1], v.c[4 * q + 2], v.c[4 * q + 3]};
+    }
+}
+template <int J, int OUT>
 __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restrict__ Z, const double* __restrict__ V,
                                                          const double* __restrict__ Tw, int m0, int LP, int n,
-                                                         double* __restrict__ Yt, int NP) {
+                                                         double* __restrict__ Yt, int NP, CoeffArgs cf,
+                                                         const double* __restrict__ dv, const double* __restrict__ C,
+                                                         double* __restrict__ stat, double* __restrict__ known) {
     constexpr int N = 64 * J, NQ = J >= 4 ? 4 : 1, QS = J / NQ, QB = N / WY / NQ;  // parts; registers, blocks of a part
     const int lane = threadIdx.x;
     const int rank = blockIdx.x, col = N - 1 - rank;
+    double f = 0.0;
+    if constexpr (OUT != OUT_Y) {
+        const int ex = (int)stat[0];
+        auto lam = [&](int m) {  // m-th largest eigenvalue, clamped at 0
+            const double v = dv[N - 1 - m];
+            return v > 0.0 ? __builtin_amdgcn_ldexp(v, ex) : 0.0;
+        };
+        const double delta = lam(cf.ell - 1);
+        if (rank == cf.MP) {  // scalars
+            if (cf.mode == 0)
+                for (int i = lane; i < N / 2; i += 64) known[i] = i < cf.ell ? fmax(lam(i) - delta, 0.0) : 0.0;
+            // rows not yet counted in ||A||_F^2: their squared norms are on the diagonal of C
+            double q = 0.0;
+            for (int r = cf.ra0 + lane; r < cf.ra1; r += 64) q += C[(int64_t)r * NP + r];
+            for (int r = cf.rb0 + lane; r < cf.rb1; r += 64) q += C[(int64_t)r * NP + r];
+            q = lane_sum<64>(q);
+            if (lane == 0) {
+                cf.acc[1] += q;
+                if (cf.mode == 0) {
+                    cf.acc[0] += delta;
+                    cf.acc[2] = delta;
+                }
+                if (stat[1] != 0.0) {  // the reduction gave up waiting: the host refuses the context from its next call on
+                    cf.acc[4] += 1.0;
+                    stat[1] = 0.0;
+                    *(volatile int*)cf.failed = 1;
+                }
+            }
+            return;
+        }
+        if (rank < cf.count) {
+            const double lm = lam(rank), keep = lm - delta;
+            if (cf.mode == 0) {
+                f = keep > 0.0 ? sqrt(keep / lm) : 0.0;
+            } else if (lm > (double)cf.n * 1.1920928955078125e-07 * lam(0)) {
+                f = cf.mode == 1 ? 1.0 / sqrt(lm) : (keep > 0.0 ? sqrt(keep / lm) : 0.0);
+            }
+        }
+        if (f == 0.0) {  // a zero row
+            if (lane < 8 * J) store_coeffs<OUT>(cf, lane >> 1, lane & 1, rank, {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f});
+            return;
+        }
+    }
     double z[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) z[j] = Z[(int64_t)col * N + lane + 64 * j];
@@ -662,12 +771,27 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
         part(std::integral_constant<int, 0>{}, b);
     }
     // Padding indices (matrix indices outside the active ones): a padding eigenvector is its own unit vector.
-    double* out = Yt + (int64_t)rank * NP;
     const int gap = LP - m0;  // padding indices m0 .. LP-1 come first
+    auto place = [&](int r) {
+        const int q = r - n;
+        return r < n ? active_index(r, m0, LP) : (q < gap ? m0 + q : n - m0 + LP + q - gap);
+    };
+    if constexpr (OUT == OUT_Y) {
+        double* out = Yt + (int64_t)rank * NP;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int r = lane + 64 * j, q = r - n;
-        out[r < n ? active_index(r, m0, LP) : (q < gap ? m0 + q : n - m0 + LP + q - gap)] = z[j];
+        for (int j = 0; j < J; ++j) out[place(lane + 64 * j)] = z[j];
+    } else {
+        __shared__ double y[N];
+#pragma unroll
+        for (int j = 0; j < J; ++j) y[place(lane + 64 * j)] = z[j];
+        __syncthreads();
+        if (lane < 8 * J) {
+            const int stg = lane >> 1, h = lane & 1;
+            Coeffs8 v;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) v.c[s] = (float)(f * y[stg * 16 + h + 2 * s]);
+            store_coeffs<OUT>(cf, stg, h, rank, v);
+        }
     }
 }
 
@@ -712,11 +836,13 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
 #define SAGE_TRI_ONE(J)                                                                                           \
     hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
 #define SAGE_TRI_MANY(J, L)                                                                                       \
-    hipLaunchKernelGGL((tri_many_kernel<J, L>), dim3(8 * 4 * J), dim3(512), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, \
+    hipLaunchKernelGGL((tri_many_kernel<J, L>), dim3(8 * (64 * J / many_columns(J) / 4)), dim3(512), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, \
                        w.V, w.stat, w.xch, w.epoch << 10, w.xcd)
     switch (NP / 64) {
         case 1: SAGE_TRI_ONE(1); break;
-        case 2: SAGE_TRI_ONE(2); break;
+        case 2:
+            if (w.local) SAGE_TRI_MANY(2, true); else SAGE_TRI_ONE(2);
+            break;
         case 4:
             if (w.local) SAGE_TRI_MANY(4, true); else SAGE_TRI_MANY(4, false);
             break;
@@ -732,17 +858,26 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
 
 bool tridiag_local_ok() { return xcd_mapping_known(); }
 
-hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st) {
+hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st) {
     const int LP = NP / 2;
-#define SAGE_BACK(J)                                                                                              \
-    hipLaunchKernelGGL(tri_back_kernel<J>, dim3(count), dim3(64), 0, st, w.Z[dc_result(NP)], w.V, w.Tw, m0, LP, n, w.Yt, NP)
+    const double* dv = w.dI[dc_result(NP)];
+    const CoeffArgs args = cf ? *cf : CoeffArgs{};
+#define SAGE_BACK(J, OUT)                                                                                                 \
+    hipLaunchKernelGGL((tri_back_kernel<J, OUT>), dim3(OUT == OUT_Y ? count : args.MP + 1), dim3(64), 0, st,               \
+                       w.Z[dc_result(NP)], w.V, w.Tw, m0, LP, n, w.Yt, NP, args, dv, w.C, w.stat, w.known)
+#define SAGE_BACK_J(J)                        \
+    if (!cf) SAGE_BACK(J, OUT_Y);             \
+    else if (args.Mc3) SAGE_BACK(J, OUT_SPLIT); \
+    else SAGE_BACK(J, OUT_F32);               \
+    break
     switch (NP / 64) {
-        case 1: SAGE_BACK(1); break;
-        case 2: SAGE_BACK(2); break;
-        case 4: SAGE_BACK(4); break;
-        case 8: SAGE_BACK(8); break;
+        case 1: SAGE_BACK_J(1);
+        case 2: SAGE_BACK_J(2);
+        case 4: SAGE_BACK_J(4);
+        case 8: SAGE_BACK_J(8);
         default: return hipErrorInvalidValue;
     }
+#undef SAGE_BACK_J
 #undef SAGE_BACK
     return hipGetLastError();
 }

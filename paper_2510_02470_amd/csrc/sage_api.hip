@@ -312,7 +312,7 @@ void kit_give(int device, SideKit& k, bool reuse) {
 }
 
 int xcd_take(sage_ctx* c) {
-    if (c->d.NP < 256 || c->device < 0 || c->device >= MAX_DEVICES) return 0;
+    if (c->d.NP < 128 || c->device < 0 || c->device >= MAX_DEVICES) return 0;
     std::lock_guard<std::mutex> hold(g_xcd_lock);
     const int first = (int)(getpid() & 7);  // other processes on the GPU most likely start at another one
     int best = first;
@@ -333,12 +333,13 @@ void xcd_release(sage_ctx* c) {
     c->xcd_slot = -1;
 }
 
-// Eigensolve of the Gram matrix of fill_top + fill_new rows; the `count` leading eigenvectors are formed.
-hipError_t eigensolve(sage_ctx* c, int m0, int n, int count) {
+// Eigensolve of the Gram matrix of fill_top + fill_new rows; the `count` leading eigenvectors are formed, or (cf given) the
+// coefficients made from its own count of them.
+hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf = nullptr) {
     if (n < 1) m0 = n = 1;  // an empty buffer: one zero row
     c->ew.epoch = (c->ew.epoch + 1) & 0x3fffffu;
     if (c->ew.epoch == 0) c->ew.epoch = 1;
-    if (c->xcd_slot < 0) return launch_eig(c->ew, c->d.NP, m0, n, count, c->st);
+    if (c->xcd_slot < 0) return launch_eig(c->ew, c->d.NP, m0, n, count, cf, c->st);
     std::unique_lock<std::mutex> hold(g_xcd_lock);
     XcdSlot& x = g_xcd[c->device][c->xcd_slot];
     const bool shared = x.users > 1;
@@ -355,7 +356,7 @@ hipError_t eigensolve(sage_ctx* c, int m0, int n, int count) {
         hold.unlock();
     }
     if (e == hipSuccess) e = launch_dc(c->ew, c->d.NP, n, c->st);
-    if (e == hipSuccess) e = launch_tri_back(c->ew, c->d.NP, m0, n, count, c->st);
+    if (e == hipSuccess) e = launch_tri_back(c->ew, c->d.NP, m0, n, count, cf, c->st);
     return e;
 }
 
@@ -377,9 +378,9 @@ int gram_whole_split(sage_ctx* c) {
     return SAGE_OK;
 }
 
-// Gram + eigensolve (count leading eigenvectors) of the buffer as it stands. After a shrink the Gram matrix of the top rows
+// Gram + eigensolve of the buffer as it stands, and the coefficients of a basis. After a shrink the Gram matrix of the top rows
 // is known (diagonal lambda_j - delta, recorded by the shrink), so their block is not recomputed.
-int decompose(sage_ctx* c, int count) {
+int decompose(sage_ctx* c, const CoeffArgs& cf) {
     const bool skip = c->top_shrunk && c->gp_skip.t0 > 0;
     if (skip && c->fill_new == 0) {
         // only the rows the last shrink wrote are there: nothing to compute
@@ -402,7 +403,7 @@ int decompose(sage_ctx* c, int count) {
         RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, gp, c->d, c->st));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st));
     }
-    RUN(K_EIG, eigensolve(c, c->fill_top, c->fill_top + c->fill_new, count));
+    RUN(K_EIG, eigensolve(c, c->fill_top, c->fill_top + c->fill_new, cf.count, &cf));
     return SAGE_OK;
 }
 
@@ -460,10 +461,10 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
         int rc = side_ahead(c, next);
         if (rc != SAGE_OK) return rc;
     }
-    RUN(K_EIG, eigensolve(c, ell, 2 * ell, ell - 1));  // (row ell - 1 of the result is zero)
     const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3;
-    RUN(K_COEFF, launch_coeffs(c->ew, c->d.NP, LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new,
-                               LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc, c->h_failed, c->st));
+    const CoeffArgs cf{LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new, c->Mt,
+                       split_rb ? c->Mt3 : nullptr, c->acc, c->h_failed};  // (row ell - 1 of the result is zero)
+    RUN(K_EIG, eigensolve(c, ell, 2 * ell, cf.count, &cf));
     if (split_rb)
         RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], ell, c->Mt3, c->top, LP, LP, c->d, c->st,
                                             new_one(c, c->cur)));
@@ -690,7 +691,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             if (pass == 0) CALLOC(c->eig_mem, bytes);
         }
         c->ew.xcd = xcd_take(c);
-        c->ew.local = NP >= 256 && tridiag_local_ok();
+        c->ew.local = NP >= 128 && tridiag_local_ok();
     }
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
@@ -851,12 +852,11 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     if (rc != SAGE_OK) return rc;
     rc = ensure_vblk(c, KP);
     if (rc != SAGE_OK) return rc;
-    rc = decompose(c, k);
-    if (rc != SAGE_OK) return rc;
     const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3 && rebuild_split_ok(KP) && KP <= c->d.LP;
-    RUN(K_COEFF, launch_coeffs(c->ew, c->d.NP, KP, k, weighted ? 2 : 1, c->d.n, c->d.ell, c->cnt_top, c->fill_top,
-                               c->d.LP + c->cnt_new, c->d.LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc,
-                               c->h_failed, c->st));
+    const CoeffArgs cf{KP, k, weighted ? 2 : 1, c->d.n, c->d.ell, c->cnt_top, c->fill_top, c->d.LP + c->cnt_new,
+                       c->d.LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc, c->h_failed};
+    rc = decompose(c, cf);
+    if (rc != SAGE_OK) return rc;
     c->cnt_top = c->fill_top;
     c->cnt_new = c->fill_new;
     if (split_rb)

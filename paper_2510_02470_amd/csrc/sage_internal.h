@@ -166,13 +166,20 @@ inline int dc_result(int NP) { return (NP == 128 || NP == 512) ? 1 : 0; }
 bool tridiag_local_ok();  // asks the current device (once)
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
-hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st);
-hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, hipStream_t st);
-// Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2); into Mc3 (split parts) if given, else into Mt.
-// Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1) and [rb0, rb1), the rows not
-// yet counted), acc[2] last_delta, acc[4] failed solves; *failed (host memory) is set after a failed solve.
-hipError_t launch_coeffs(const EigWork& w, int NP, int MP, int count, int mode, int n, int ell, int ra0, int ra1, int rb0,
-                         int rb1, float* Mt, void* Mc3, double* acc, int* failed, hipStream_t st);
+// Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Mc3 (split
+// parts) if given, else into Mt. Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1)
+// and [rb0, rb1), the rows not yet counted), acc[2] last_delta, acc[4] failed solves; *failed (host memory) is set after a
+// failed solve.
+struct CoeffArgs {
+    int MP, count, mode, n, ell, ra0, ra1, rb0, rb1;
+    float* Mt;
+    void* Mc3;
+    double* acc;
+    int* failed;
+};
+// the `count` leading eigenvectors into Yt, or (cf given) only the coefficients made from them
+hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st);
+hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st);
 hipError_t launch_eig_export(const EigWork& w, int NP, double* Y, double* lam, double* record, hipStream_t st);
 
 // Where the coefficient M[m][i] (output row m < MP, buffer row i < NP) is stored for the rebuild kernel: chunks of

@@ -38,12 +38,12 @@ __device__ __forceinline__ void swap_rows(double v, double& a, double& b) {
     b = __longlong_as_double(((long long)h[1] << 32) | l[1]);
 }
 
-// Sum over groups of L lanes (L = 8, 16 or 64), the same bits in every lane of the group.
+// Sum over groups of L lanes (L = 4, 8, 16 or 64), the same bits in every lane of the group.
 template <int L>
 __device__ __forceinline__ double lane_sum(double v) {
     v += dpp_move<DPP_XOR1>(v);
     v += dpp_move<DPP_XOR2>(v);
-    v += dpp_move<DPP_HALF_MIRROR>(v);
+    if constexpr (L >= 8) v += dpp_move<DPP_HALF_MIRROR>(v);
     if constexpr (L >= 16) v += dpp_move<DPP_MIRROR>(v);
     if constexpr (L == 64) {
         double a, b;
@@ -85,12 +85,12 @@ __device__ __forceinline__ int lane_sum_i(int v) {
     return v;
 }
 
-// 1 / x to about one unit in the last place for normal x (hardware estimate and two Newton steps)
+// 1 / x to about one unit in the last place for normal x: the hardware estimate y, good to 2^-22 or better, and one step of
+// third order, y (1 + e + e^2) with e = 1 - x y.
 __device__ __forceinline__ double rcp64(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    return y;
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, y, 1.0);
+    return __builtin_fma(y, __builtin_fma(e, e, e), y);
 }
 
 }  // namespace sage
