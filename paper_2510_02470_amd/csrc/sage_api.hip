@@ -99,7 +99,7 @@ struct sage_ctx {
     void* Vimg = nullptr;      // bf16 hi/lo chunk images of the basis (score_split.hip); built when the rows allow it
     size_t Vimg_bytes = 0;
     bool img_ok = false;       // ... and usable for row-major batches of this D
-    bool img_built = false;    // the images hold the current basis
+    int img_parts = 0;         // the images hold the current basis in this many parts (0: they do not)
     void* stage = nullptr;     // factored rows written out, for shapes the factored projection does not take
     size_t stage_bytes = 0;
     int proj_mode = SAGE_PROJ_AUTO;
@@ -115,7 +115,8 @@ struct sage_ctx {
     float* proj_partial = nullptr;
     size_t proj_partial_floats = 0;
     double* cons_partial = nullptr;
-    double* ssum = nullptr;
+    double* ssum = nullptr;      // (the first batch of a pass sets it)
+    unsigned* ticket = nullptr;  // beside it
     float* alpha = nullptr;
     int64_t alpha_cap = 0, alpha_n = 0;
     SelectWork sw{};
@@ -497,9 +498,12 @@ void reset_scoring(sage_ctx* c) {
 }
 
 int ensure_score_buffers(sage_ctx* c) {
-    if (!c->ssum) ALLOC(c->ssum, 128 * sizeof(double));
+    if (!c->ssum) {
+        ALLOC(c->ssum, 128 * sizeof(double) + 256);
+        c->ticket = (unsigned*)(c->ssum + 128);
+        HIPCHK(hipMemsetAsync(c->ssum, 0, 128 * sizeof(double) + 256, c->st));
+    }
     if (!c->cons_partial) ALLOC(c->cons_partial, (size_t)(SCORE_CHUNK / 4) * 128 * sizeof(double));  // one per 4 rows
-    HIPCHK(hipMemsetAsync(c->ssum, 0, 128 * sizeof(double), c->st));
     return SAGE_OK;
 }
 
@@ -515,9 +519,9 @@ int ensure_vblk(sage_ctx* c, int KP) {
 }
 
 // The bf16 hi/lo images of the basis in Vblk (score_split.hip).
-int ensure_images(sage_ctx* c) {
-    if (c->img_built) return SAGE_OK;
-    const size_t need = basis_image_bytes(c->KP, c->dtype, c->d);
+int ensure_images(sage_ctx* c, int parts) {
+    if (c->img_parts == parts) return SAGE_OK;
+    const size_t need = basis_image_bytes(c->KP, c->dtype, parts, c->d);
     if (need > c->Vimg_bytes) {
         if (c->Vimg) {
             HIPCHK(hipStreamSynchronize(c->st));
@@ -527,19 +531,20 @@ int ensure_images(sage_ctx* c) {
         ALLOC(c->Vimg, need);
         c->Vimg_bytes = need;
     }
-    RUN(K_REBUILD, launch_basis_split(c->Vblk, c->KP, c->dtype, c->Vimg, c->d, c->st));
-    c->img_built = true;
+    c->img_parts = 0;
+    RUN(K_REBUILD, launch_basis_split(c->Vblk, c->KP, c->dtype, parts, c->Vimg, c->d, c->st));
+    c->img_parts = parts;
     return SAGE_OK;
 }
 
 // After Vblk holds a new basis: build the images when the split projection can be used for row-major batches of
-// this D (factored rows build them on first use otherwise).
+// this D (factored rows, and rows of other widths, build theirs on first use).
 int finish_basis(sage_ctx* c) {
     c->img_ok = false;
-    c->img_built = false;
+    c->img_parts = 0;
     if (c->proj_mode == SAGE_PROJ_F32) return SAGE_OK;
     if (!split_path_ok(nullptr, c->dtype, c->d)) return SAGE_OK;  // nullptr is "aligned": only D is judged here
-    int rc = ensure_images(c);
+    int rc = ensure_images(c, 2);
     if (rc != SAGE_OK) return rc;
     c->img_ok = true;
     return SAGE_OK;
@@ -937,7 +942,7 @@ static int project_rows(sage_ctx* c, const RowSrc& src, int64_t R, int* slots) {
     const void* g = src.G;
     if (src.outer()) {
         if (c->proj_mode != SAGE_PROJ_F32 && outer_path_ok(src.E, src.H, src.dtype, src.C, src.dh)) {
-            int rc = ensure_images(c);
+            int rc = ensure_images(c, 2);
             if (rc != SAGE_OK) return rc;
             rc = ensure_stage(c, outer_work_bytes(R, src.dtype, src.C));
             if (rc != SAGE_OK) return rc;
@@ -955,12 +960,16 @@ static int project_rows(sage_ctx* c, const RowSrc& src, int64_t R, int* slots) {
         RUN(K_INSERT, launch_expand_outer(src.E, src.H, src.dtype, src.C, src.dh, R, c->stage, c->d, c->st));
         g = c->stage;
     }
-    const bool split = c->img_ok && split_path_ok(g, c->dtype, c->d);
-    ScorePlan p = split ? score_split_plan(R, c->dtype, c->d, c->num_cu) : score_plan(R, c->d, c->num_cu);
+    int parts = c->img_ok && split_path_ok(g, c->dtype, c->d) ? 2 : 0;
+    if (!parts && c->proj_mode != SAGE_PROJ_F32 && any_path_ok(g, c->dtype, c->d)) parts = 3;
+    if (parts) {
+        if (int rc = ensure_images(c, parts); rc != SAGE_OK) return rc;
+    }
+    ScorePlan p = parts ? score_split_plan(R, c->dtype, c->d, c->num_cu) : score_plan(R, c->d, c->num_cu);
     int rc = ensure_partial(c, (size_t)p.splits * R * c->KP);
     if (rc != SAGE_OK) return rc;
-    if (split)
-        RUN(K_PROJECT, launch_project_split(g, c->dtype, R, c->Vimg, c->KP, c->proj_partial, p, c->d, c->st));
+    if (parts)
+        RUN(K_PROJECT, launch_project_split(g, c->dtype, R, parts, c->Vimg, c->KP, c->proj_partial, p, c->d, c->st));
     else
         RUN(K_PROJECT, launch_project(g, c->dtype, R, c->Vblk, c->KP, c->proj_partial, p, c->d, c->st));
     *slots = p.splits;
@@ -1033,7 +1042,6 @@ static int score_impl(sage_ctx* c, RowSrc g, const int* labels, int64_t rows) {
     }
     if (labels) {
         if (!c->labels) ALLOC(c->labels, (size_t)c->cap_rows * sizeof(int));
-        HIPCHK(hipMemcpyAsync(c->labels + c->n_scored, labels, (size_t)rows * sizeof(int), hipMemcpyDeviceToDevice, c->st));
         if (c->n_labeled == c->n_scored) c->n_labeled += rows;  // stays behind for good once an unlabeled batch came
     }
     while (rows > 0) {
@@ -1043,7 +1051,9 @@ static int score_impl(sage_ctx* c, RowSrc g, const int* labels, int64_t rows) {
         if (rcp != SAGE_OK) return rcp;
         RUN(K_FINALIZE, launch_score_finalize(c->proj_partial, R, c->KP, c->k, slots,
                                              c->store_zhat ? c->zhat + (size_t)c->n_scored * c->k : nullptr,
-                                             c->cons_partial, c->ssum, c->store_zhat ? 0 : 1, nullptr, c->st));
+                                             c->cons_partial, c->ticket, c->ssum, c->store_zhat ? 0 : 1, c->n_scored == 0,
+                                             nullptr, labels, labels ? c->labels + c->n_scored : nullptr, c->st));
+        if (labels) labels += R;
         c->n_scored += R;
         g = g.after(R, c->d.D);
         rows -= R;
@@ -1084,7 +1094,6 @@ int sage_set_score_store(sage_ctx* c, int store_zhat) {
     ALIVE(c);
     c->store_zhat = store_zhat != 0;
     reset_scoring(c);
-    if (c->ssum) HIPCHK(hipMemsetAsync(c->ssum, 0, 128 * sizeof(double), c->st));
     return SAGE_OK;
 }
 
@@ -1100,8 +1109,8 @@ static int rescore_impl(sage_ctx* c, RowSrc g, int64_t rows) {
         int slots = 0;
         rc = project_rows(c, g, R, &slots);
         if (rc != SAGE_OK) return rc;
-        RUN(K_FINALIZE, launch_score_finalize(c->proj_partial, R, c->KP, c->k, slots, nullptr, c->cons_partial, c->ssum, 2,
-                                             c->alpha + c->n_rescored, c->st));
+        RUN(K_FINALIZE, launch_score_finalize(c->proj_partial, R, c->KP, c->k, slots, nullptr, c->cons_partial, c->ticket,
+                                             c->ssum, 2, false, c->alpha + c->n_rescored, nullptr, nullptr, c->st));
         c->n_rescored += R;
         g = g.after(R, c->d.D);
         rows -= R;

@@ -1,7 +1,7 @@
 // Scoring pass, first half (Algorithm 1, Phase II, first line; Method, "Two-pass scoring"):
 //   z_i = V_k^T g_i  (fp32 matrix cores, split over D),  zhat_i = z_i / ||z_i||_2 (0 if z_i = 0),
 //   consensus sum  s += sum_i zhat_i  (fixed-order reductions, fp64).
-#include "sage_internal.h"
+#include "score_ops.h"
 
 namespace sage {
 
@@ -147,132 +147,130 @@ __global__ __launch_bounds__(256) void project_kernel(const T* __restrict__ G, i
         }
 }
 
-// Sum of the split-K partial projections, normalisation and consensus partial sums.
-// A work-group of 1024 threads takes 4 rows, four waves per row: wave (row, quarter) adds a quarter of the splits
-// in order, lane j holding coordinates 2j and 2j + 1, with all its loads (up to 32 at a time) in flight together;
-// the quarter sums are added in quarter order by the row's first wave, which normalises. Writes zhat (R x k, fp32)
-// and cons_partial[block][128] (fp64 sums of the block's zhat, the four rows added in row order). All in fp64, fixed
-// order: the result does not depend on timing.
-constexpr int FIN_ROWS = 4;
-// mode 0: as above. mode 1: consensus partial sums only, zhat is not kept (first scoring pass of a run that does not
-// store zhat). mode 2: the second such pass: alpha_i = clamp(<zhat_i, u>, -1, 1) straight from the recomputed zhat_i,
-// with u = ssum / ||ssum|| rebuilt by every work-group and the arithmetic of cosine_kernel (same lanes, same order),
-// so that the scores are bit-equal to those of the run that stores zhat.
-__global__ __launch_bounds__(1024) void score_finalize_kernel(const float* __restrict__ partial, int64_t R, int KP, int k,
-                                                              int splits, float* __restrict__ zhat,
-                                                              double* __restrict__ cons_partial, int mode,
-                                                              const double* __restrict__ ssum,
-                                                              float* __restrict__ alpha) {
-    __shared__ double red[FIN_ROWS][4][128];
-    __shared__ double cs[FIN_ROWS][128];
-    __shared__ double u[128];
+// Sum of the split-K partial projections, normalisation, consensus sum. A wave works on a row (WPR = 1) or a quarter of its
+// splits (WPR = 4, many splits): KP / 4 lanes hold four coordinates each, the 64 / (KP / 4) groups of such lanes take the
+// splits in turn. fp64 in a fixed order throughout: the result does not depend on timing.
+// mode 0: zhat (R x k, fp32) and the consensus sum. mode 1: the consensus sum only (first scoring pass of a run that does not
+// store zhat). mode 2: the second such pass: alpha_i = clamp(<zhat_i, u>, -1, 1) straight from the recomputed zhat_i, by the
+// functions cosine_kernel uses, so that the scores are bit-equal to those of the run that stores zhat.
+// The consensus sums of the work-groups go to memory past the L2 (device scope), and the work-group that comes last adds
+// them up, in their order, to ssum: a kernel of its own for that was 5 to 10 us more. src_labels (may be null): the labels of
+// the rows, kept in dst_labels.
+template <int KP, int WPR>
+__global__ __launch_bounds__(1024) void score_finalize_kernel(const float* __restrict__ partial, int64_t R, int k, int splits,
+                                                              float* __restrict__ zhat, double* __restrict__ cons_partial,
+                                                              unsigned* __restrict__ ticket, int mode, int first,
+                                                              double* __restrict__ ssum, float* __restrict__ alpha,
+                                                              const int* __restrict__ src_labels,
+                                                              int* __restrict__ dst_labels) {
+    constexpr int L = KP / 4, G = 64 / L, ROWS = 16 / WPR;
+    __shared__ double red[WPR == 4 ? 16 : 1][KP];
+    __shared__ double cs[ROWS][KP];
+    __shared__ double part[8][128];
+    __shared__ bool is_last;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if (mode == 2) {  // work-group uniform
-        double* tree = &red[0][0][0];
-        if (tid < 128) {
-            const double sv = tid < k ? ssum[tid] : 0.0;
-            u[tid] = sv;
-            tree[tid] = sv * sv;
-        }
-        __syncthreads();
-        for (int w = 64; w >= 1; w >>= 1) {  // fixed-shape tree, as in cosine_kernel
-            if (tid < w) tree[tid] += tree[tid + w];
-            __syncthreads();
-        }
-        const double nrm = sqrt(tree[0]);
-        __syncthreads();
-        if (tid < 128) u[tid] = nrm > 0.0 ? u[tid] / nrm : 0.0;
-        __syncthreads();
-    }
-    const int rr = wave >> 2, quarter = wave & 3;
-    const int64_t r = (int64_t)blockIdx.x * FIN_ROWS + rr;
-    const bool on = 2 * lane < KP;  // KP is a multiple of 32
-    double z0 = 0.0, z1 = 0.0;
-    if (r < R && on) {
-        const int per = (splits + 3) / 4;
+    const int rr = wave / WPR, quarter = wave % WPR, g = lane / L, c0 = (lane % L) * 4;
+    const int64_t r = (int64_t)blockIdx.x * ROWS + rr;
+    double z[4] = {0.0, 0.0, 0.0, 0.0};
+    if (r < R) {
+        const int per = (splits + WPR - 1) / WPR;
         const int sa = quarter * per, sb = sa + per < splits ? sa + per : splits;
-        const float2* p0 = reinterpret_cast<const float2*>(partial + r * KP) + lane;
-        const int64_t sstride = R * KP / 2;  // in float2
-        for (int s = sa; s < sb; s += 32) {
-            float2 v[32];
+        const float4* p = reinterpret_cast<const float4*>(partial + r * KP + c0);
+        const int64_t stride = R * KP / 4;
+        constexpr int U = 16;
+        for (int s0 = sa; s0 < sb; s0 += U * G) {
+            float4 v[U];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                const int ss = s + u < sb ? s + u : sb - 1;  // repeats are not added
-                v[u] = p0[ss * sstride];
+            for (int u = 0; u < U; ++u) {
+                const int ss = s0 + u * G + g;
+                v[u] = p[(ss < sb ? ss : sb - 1) * stride];  // repeats are not added
             }
 #pragma unroll
-            for (int u = 0; u < 32; ++u)
-                if (s + u < sb) {
-                    z0 += (double)v[u].x;
-                    z1 += (double)v[u].y;
+            for (int u = 0; u < U; ++u)
+                if (s0 + u * G + g < sb) {
+                    z[0] += (double)v[u].x;
+                    z[1] += (double)v[u].y;
+                    z[2] += (double)v[u].z;
+                    z[3] += (double)v[u].w;
                 }
         }
     }
-    red[rr][quarter][2 * lane] = z0;
-    red[rr][quarter][2 * lane + 1] = z1;
-    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) z[c] = group_sum<L>(z[c]);
+    if constexpr (WPR == 4) {
+        if (g == 0) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) red[wave][c0 + c] = z[c];
+        }
+        __syncthreads();
+        if (quarter == 0) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                z[c] = ((red[wave][c0 + c] + red[wave + 1][c0 + c]) + red[wave + 2][c0 + c]) + red[wave + 3][c0 + c];
+        }
+    }
     if (quarter == 0) {
-        float h0 = 0.f, h1 = 0.f;
-        if (r < R) {
-            // lane j now holds coordinates j and j + 64
-            double a0 = ((red[rr][0][lane] + red[rr][1][lane]) + red[rr][2][lane]) + red[rr][3][lane];
-            double a1 = ((red[rr][0][lane + 64] + red[rr][1][lane + 64]) + red[rr][2][lane + 64]) + red[rr][3][lane + 64];
-            if (lane >= k) a0 = 0.0;
-            if (lane + 64 >= k) a1 = 0.0;
-            double q2 = a0 * a0 + a1 * a1;
-            for (int o = 32; o >= 1; o >>= 1) q2 += __shfl_xor(q2, o);
-            const double nrm = sqrt(q2);
-            if (nrm > 0.0) {
-                h0 = (float)(a0 / nrm);
-                h1 = (float)(a1 / nrm);
-            }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) z[c] = c0 + c < k ? z[c] : 0.0;
+        const double nrm = sqrt(row_dot<L>(z, z));
+        float zh[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) zh[c] = r < R && nrm > 0.0 ? (float)(z[c] / nrm) : 0.f;
+        if (r < R && g == 0) {
             if (mode == 0) {
-                if (lane < k) zhat[r * k + lane] = h0;
-                if (lane + 64 < k) zhat[r * k + lane + 64] = h1;
-            } else if (mode == 2) {
-                double a = 0.0;
-                if (lane < k) a = (double)h0 * u[lane];
-                if (lane + 64 < k) a += (double)h1 * u[lane + 64];
-                for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
-                if (lane == 0) {
-                    if (a > 1.0) a = 1.0;
-                    if (a < -1.0) a = -1.0;
-                    float f = (float)a;
-                    if (f == 0.f) f = 0.f;  // -0 -> +0
-                    alpha[r] = f;
-                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (c0 + c < k) zhat[r * k + c0 + c] = zh[c];
             }
+            if (dst_labels && lane == 0) dst_labels[r] = src_labels[r];
         }
-        cs[rr][lane] = (double)h0;
-        cs[rr][lane + 64] = (double)h1;
+        if (mode == 2) {
+            double u[4], h[4];
+            consensus_unit<L>(ssum, k, c0, u);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) h[c] = (double)zh[c];
+            const float f = clamp_score(row_dot<L>(h, u));
+            if (r < R && lane == 0) alpha[r] = f;
+        } else if (g == 0) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) cs[rr][c0 + c] = (double)zh[c];
+        }
     }
+    if (mode == 2) return;  // (uniform)
     __syncthreads();
-    if (mode != 2 && tid < 128)
-        cons_partial[(int64_t)blockIdx.x * 128 + tid] = ((cs[0][tid] + cs[1][tid]) + cs[2][tid]) + cs[3][tid];
-}
-
-// ssum[j] += sum over blocks of cons_partial[block][j]: thread (group g = tid / 128, coordinate j = tid % 128) adds
-// blocks g, g + 8, ... in order, the 8 group sums are then added in group order.
-__global__ __launch_bounds__(1024) void consensus_add_kernel(const double* __restrict__ cons_partial, int nblocks, int k,
-                                                             double* __restrict__ ssum) {
-    __shared__ double red[8][128];
-    const int j = threadIdx.x & 127, g = threadIdx.x >> 7;
+    if (tid < KP) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) s += cs[q][tid];
+        __hip_atomic_store(cons_partial + (int64_t)blockIdx.x * 128 + tid, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores have reached memory
+    __syncthreads();
+    if (tid == 0) is_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!is_last) return;
+    const int j = tid & 127, h = tid >> 7, nblocks = (int)gridDim.x;
     double s = 0.0;
-    for (int b = g; b < nblocks; b += 32) {
-        double v[4];
+    if (j < KP)
+        for (int b = h; b < nblocks; b += 64) {
+            double v[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = (b + 8 * u < nblocks) ? cons_partial[(int64_t)(b + 8 * u) * 128 + j] : 0.0;
+            for (int u = 0; u < 8; ++u)
+                v[u] = b + 8 * u < nblocks ? __hip_atomic_load(cons_partial + (int64_t)(b + 8 * u) * 128 + j, __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT)
+                                           : 0.0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s += v[u];
-    }
-    red[g][j] = s;
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+    part[h][j] = s;
     __syncthreads();
-    if (g == 0 && j < k) {
+    if (h == 0 && j < k) {
         double t = 0.0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) t += red[u][j];
-        ssum[j] += t;
+        for (int u = 0; u < 8; ++u) t += part[u][j];
+        ssum[j] = first ? t : ssum[j] + t;
     }
+    if (tid == 0) *ticket = 0;
 }
 
 ScorePlan score_plan(int64_t R, const Dims& d, int num_cu) {
@@ -318,11 +316,21 @@ hipError_t launch_project(const void* G, int dtype, int64_t R, const float* Vblk
 }
 
 hipError_t launch_score_finalize(const float* partial, int64_t R, int KP, int k, int splits, float* zhat_out,
-                                 double* cons_partial, double* ssum, int mode, float* alpha_out, hipStream_t st) {
-    int nblocks = (int)((R + FIN_ROWS - 1) / FIN_ROWS);
-    hipLaunchKernelGGL(score_finalize_kernel, dim3(nblocks), dim3(1024), 0, st, partial, R, KP, k, splits, zhat_out,
-                       cons_partial, mode, ssum, alpha_out);
-    if (mode != 2) hipLaunchKernelGGL(consensus_add_kernel, dim3(1), dim3(1024), 0, st, cons_partial, nblocks, k, ssum);
+                                 double* cons_partial, unsigned* ticket, double* ssum, int mode, bool first, float* alpha_out,
+                                 const int* src_labels, int* dst_labels, hipStream_t st) {
+    // four waves a row where a lane would add up more than 32 splits
+    const int wpr = splits * KP / 256 > 32 ? 4 : 1;
+    const unsigned blocks = (unsigned)((R * wpr + 15) / 16);
+#define SAGE_FIN(K, W)                                                                                                  \
+    hipLaunchKernelGGL((score_finalize_kernel<K, W>), dim3(blocks), dim3(1024), 0, st, partial, R, k, splits, zhat_out, \
+                       cons_partial, ticket, mode, first ? 1 : 0, ssum, alpha_out, src_labels, dst_labels)
+    switch (KP / 32) {
+        case 1: if (wpr == 4) SAGE_FIN(32, 4); else SAGE_FIN(32, 1); break;
+        case 2: if (wpr == 4) SAGE_FIN(64, 4); else SAGE_FIN(64, 1); break;
+        case 4: if (wpr == 4) SAGE_FIN(128, 4); else SAGE_FIN(128, 1); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef SAGE_FIN
     return hipGetLastError();
 }
 

@@ -36,19 +36,21 @@ __device__ __forceinline__ int img_piece(int cc, int p) {
     else return cc * 4 + (p ^ ((cc >> 2) & 3));
 }
 
+// (Images of three parts, for project_any_kernel, have KP rows more: hi, mid, lo.)
+//
 // One thread writes one 16-byte piece. Vblk is the fp32 column-slab basis (KP rows); columns >= D are zero there and
 // columns >= Dp are written as zero here.
-template <int KC>
+template <int KC, int PARTS>
 __global__ __launch_bounds__(256) void basis_split_kernel(const float* __restrict__ Vblk, int KP, int64_t Dp,
                                                           int64_t chunks, u32x4* __restrict__ img) {
     constexpr int PPR = KC / 8;
-    const int64_t per_chunk = (int64_t)2 * KP * PPR;
+    const int64_t per_chunk = (int64_t)PARTS * KP * PPR;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= chunks * per_chunk) return;
     const int64_t c = i / per_chunk;
     const int rem = (int)(i % per_chunk);
     const int cc = rem / PPR, p = rem % PPR;
-    const int row = cc < KP ? cc : cc - KP;
+    const int part = cc < KP ? 0 : (cc < 2 * KP ? 1 : 2), row = cc - part * KP;
     const int64_t d0 = c * KC + p * 8;
     float v[8];
 #pragma unroll
@@ -62,33 +64,42 @@ __global__ __launch_bounds__(256) void basis_split_kernel(const float* __restric
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         float x = v[2 * e], y = v[2 * e + 1];
-        unsigned hi = pack_bf16(x, y);
-        if (cc < KP) {
-            out[e] = hi;
+        if constexpr (PARTS == 3) {
+            unsigned a, b, l;
+            split3_bf16(x, y, a, b, l);
+            out[e] = part == 0 ? a : (part == 1 ? b : l);
         } else {
-            float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xffff0000u);
-            out[e] = pack_bf16(rx, ry);
+            unsigned hi = pack_bf16(x, y);
+            if (cc < KP) {
+                out[e] = hi;
+            } else {
+                float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xffff0000u);
+                out[e] = pack_bf16(rx, ry);
+            }
         }
     }
     img[c * per_chunk + img_piece<KC>(cc, p)] = out;
 }
 
-hipError_t launch_basis_split(const float* Vblk, int KP, int dtype, void* img, const Dims& d, hipStream_t st) {
+hipError_t launch_basis_split(const float* Vblk, int KP, int dtype, int parts, void* img, const Dims& d, hipStream_t st) {
     const int KC = dtype == SAGE_BF16 ? 64 : 32;
     const int64_t chunks = (d.D + KC - 1) / KC;
-    const int64_t total = chunks * 2 * KP * (KC / 8);
+    const int64_t total = chunks * parts * KP * (KC / 8);
     dim3 grid((unsigned)((total + 255) / 256));
-    if (KC == 64)
-        hipLaunchKernelGGL(basis_split_kernel<64>, grid, dim3(256), 0, st, Vblk, KP, d.Dp, chunks, (u32x4*)img);
-    else
-        hipLaunchKernelGGL(basis_split_kernel<32>, grid, dim3(256), 0, st, Vblk, KP, d.Dp, chunks, (u32x4*)img);
+#define SAGE_IMG(K, P) \
+    hipLaunchKernelGGL((basis_split_kernel<K, P>), grid, dim3(256), 0, st, Vblk, KP, d.Dp, chunks, (u32x4*)img)
+    if (KC == 64 && parts == 2) SAGE_IMG(64, 2);
+    else if (KC == 64) SAGE_IMG(64, 3);
+    else if (parts == 2) SAGE_IMG(32, 2);
+    else SAGE_IMG(32, 3);
+#undef SAGE_IMG
     return hipGetLastError();
 }
 
-size_t basis_image_bytes(int KP, int dtype, const Dims& d) {
+size_t basis_image_bytes(int KP, int dtype, int parts, const Dims& d) {
     const int KC = dtype == SAGE_BF16 ? 64 : 32;
     const int64_t chunks = (d.D + KC - 1) / KC;
-    return (size_t)chunks * 2 * KP * KC * 2;
+    return (size_t)chunks * parts * KP * KC * 2;
 }
 
 // ---- projection -------------------------------------------------------------------------------------------
@@ -340,6 +351,220 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
             }
 }
 
+// ---- projection of rows of any width and alignment ---------------------------------------------------------------
+// Where rows do not start on a multiple of 8 columns' bytes, windows are counted from the row's first column, wherever that
+// lies in a memory line, and a piece is loaded at any element boundary. Such rows went through the fp32 matrix cores
+// before (157 us for 2048 rows of 51,300 with 64 vectors), so here the basis has three bf16 parts (24 bits) and fp32 rows
+// are split the same way: six products (three for bf16 rows, which are exact), the fp32 result to a few 2^-24 per term.
+//
+// Shapes as in project_split_kernel: 512 threads, a wave owns 64 rows x KP columns, its row pieces come from global memory
+// two windows ahead (one with four column tiles, whose accumulators leave no room for a third set of row registers).
+// Every window is a whole image, so the ring has three slots. The last, partial window of the row is taken element by
+// element after the others, by the split that owns it.
+template <typename T>
+struct __attribute__((packed, aligned(sizeof(T)))) AnyPiece {
+    u32x4 v;
+};
+
+template <int NT, typename T>
+__global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict__ G, int64_t R,
+                                                             const u32x4* __restrict__ img, float* __restrict__ partial,
+                                                             int row_tiles, int64_t D, int64_t chunks_total,
+                                                             int64_t chunks_per_split) {
+    constexpr int KP = NT * 32;
+    constexpr int KC = 128 / (int)sizeof(T);
+    constexpr int PPR = KC / 8;
+    constexpr int IMG = 3 * KP * PPR;
+    constexpr int KS = KC / 16;
+    constexpr int NB = NT == 4 ? 2 : 3;  // sets of row registers
+    extern __shared__ u32x4 lds[];       // 3 * IMG
+
+    const int id = blockIdx.x;
+    const int xcd = id & 7, y = id >> 3;
+    const int rt = y % row_tiles;
+    const int split = (y / row_tiles) * 8 + xcd;
+    const int64_t full = D / KC;  // whole windows of a row
+    const int64_t c0 = (int64_t)split * chunks_per_split;
+    int64_t c1 = c0 + chunks_per_split;
+    if (c1 > chunks_total) c1 = chunks_total;
+    const bool tail = c0 < c1 && c1 > full;
+    if (c1 > full) c1 = full;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, h = lane >> 5;
+    const int64_t S = D * (int64_t)sizeof(T);
+    const int64_t row0 = (int64_t)rt * 512;
+    const char* gbase = reinterpret_cast<const char*>(G) + row0 * S;
+    unsigned lrow[2];  // rows >= R repeat row R - 1; their results are not written
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        int64_t r = row0 + wave * 64 + t * 32 + n;
+        if (r > R - 1) r = R - 1;
+        lrow[t] = (unsigned)((r - row0) * S) + 8u * (unsigned)sizeof(T) * (unsigned)h;
+    }
+    // register x of a row operand: bf16: k-step x; fp32: half x & 1 of k-step x >> 1
+    auto piece_at = [](int x) { return sizeof(T) == 2 ? 32 * x : 64 * (x >> 1) + 16 * (x & 1); };
+    auto load_rows = [&](RowOp<T>& a, int t, int64_t m) __attribute__((always_inline)) {
+        const unsigned o = lrow[t] + (unsigned)(m * 128);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) a.v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + o + piece_at(x))->v;
+    };
+    int boff[KS];
+#pragma unroll
+    for (int j = 0; j < KS; ++j) boff[j] = img_piece<KC>(n, 2 * j + h);
+
+    f32x16 acc[2][NT];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[t][ct][i] = 0.f;
+
+    constexpr int VL = (IMG + 511) / 512;
+    auto stage = [&](int64_t c, int slot) __attribute__((always_inline)) {
+        if (c > chunks_total - 1) c = chunks_total - 1;  // beyond the end: repeat (never used)
+        const u32x4* src = img + c * IMG;
+#pragma unroll
+        for (int q = 0; q < VL; ++q) {
+            // (where IMG is no multiple of 512 the waves left over repeat its start: every wave has VL loads in flight)
+            const int at = (q * 512 + wave * 64) % IMG;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + at + lane),
+                                             (__attribute__((address_space(3))) void*)(lds + slot * IMG + at), 16, 0, 0);
+        }
+    };
+
+    static_assert(8 + VL <= 15, "the low field of the count");
+    // the products of one window: row operands a, image in slot sc
+    auto multiply = [&](const RowOp<T> (&a)[2], int sc, auto&& half_way) __attribute__((always_inline)) {
+        constexpr int STEPS = KS * 3 * NT;  // (k-step, part of the basis, column tile)
+        auto addr = [&](int s) {
+            const int j = s / (3 * NT), pt = (s / NT) % 3, ct = s % NT;
+            return boff[j] + sc * IMG + (pt * KP + ct * 32) * PPR;
+        };
+        u32x4 b[2];
+        b[0] = lds[addr(0)];
+        u32x4 ap[2][3];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const int j = s / (3 * NT), pt = (s / NT) % 3, ct = s % NT;
+            if (s % (3 * NT) == 0) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    if constexpr (sizeof(T) == 2) {
+                        ap[t][0] = a[t].v[j];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const u32x4& x = a[t].v[2 * j + (e >> 1)];
+                            unsigned p0, p1, p2;
+                            split3_bf16(__uint_as_float(x[(2 * e) & 3]), __uint_as_float(x[(2 * e + 1) & 3]), p0, p1, p2);
+                            ap[t][0][e] = p0;
+                            ap[t][1][e] = p1;
+                            ap[t][2][e] = p2;
+                        }
+                    }
+                }
+            }
+            if (s + 1 < STEPS) b[(s + 1) % 2] = lds[addr(s + 1)];
+            if (s == STEPS / 2) half_way();
+            const u32x4 bb = b[s % 2];
+            constexpr int QS = sizeof(T) == 2 ? 1 : 3;
+#pragma unroll
+            for (int q = 0; q < QS; ++q)
+                if (q + pt <= 2) {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) acc[t][ct] = mfma_bf16(ap[t][q], bb, acc[t][ct]);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // One window: its image is in slot sc; the image of m + 2 and the rows of m + NB - 1 are requested.
+    auto visit = [&](const RowOp<T> (&a)[2], RowOp<T> (&afar)[2], int64_t m, int sc) __attribute__((always_inline)) {
+        stage(m + 2, sc == 0 ? 2 : sc - 1);
+        const int64_t mf = m + NB - 1 > c1 - 1 ? c1 - 1 : m + NB - 1;  // beyond the last window: repeat it (never used)
+        load_rows(afar[0], 0, mf);
+        multiply(a, sc, [&]() __attribute__((always_inline)) { load_rows(afar[1], 1, mf); });
+        // at most this window's loads stay outstanding: image m + 1 (and rows m + 1) have landed
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (8 + VL));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    RowOp<T> a0[2], a1[2], a2[2];
+    const int64_t len = c1 - c0;
+    if (len > 0) {
+        stage(c0, 0);
+        stage(c0 + 1, 1);
+        const int64_t m1 = len > 1 ? c0 + 1 : c0;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            load_rows(a0[t], t, c0);
+            if (NB == 3) load_rows(a1[t], t, m1);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        int64_t i = 0;
+        if constexpr (NB == 3) {
+            for (; i + 2 < len; i += 3) {
+                visit(a0, a2, c0 + i, 0);
+                visit(a1, a0, c0 + i + 1, 1);
+                visit(a2, a1, c0 + i + 2, 2);
+            }
+            if (i < len) visit(a0, a2, c0 + i, 0);
+            if (i + 1 < len) visit(a1, a0, c0 + i + 1, 1);
+        } else {
+            for (int sc = 0; i < len; i += 2) {
+                visit(a0, a1, c0 + i, sc);
+                sc = sc == 2 ? 0 : sc + 1;
+                if (i + 1 < len) visit(a1, a0, c0 + i + 1, sc);
+                sc = sc == 2 ? 0 : sc + 1;
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS any more
+    }
+    if (tail) {  // work-group uniform
+        __syncthreads();
+        stage(full, 0);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                constexpr int E = 16 / (int)sizeof(T);
+                const int64_t col = full * KC + (piece_at(x) + 8 * (int)sizeof(T) * h) / (int)sizeof(T);
+                const T* src = reinterpret_cast<const T*>(gbase + lrow[t] + (unsigned)(full * 128) + piece_at(x));
+                T v[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] = col + e < D ? src[e] : (T)0;
+                __builtin_memcpy(&a0[t].v[x], v, 16);
+            }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        multiply(a0, 0, []() {});
+    }
+
+    float* out = partial + (int64_t)split * R * KP;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int64_t r = row0 + wave * 64 + t * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+                if (r < R) out[r * KP + ct * 32 + n] = acc[t][ct][i];
+            }
+}
+
+// Any row start that is a multiple of the element, a row of at least one window, lane offsets of 32 bits.
+bool any_path_ok(const void* G, int dtype, const Dims& d) {
+    const int64_t esz = dtype == SAGE_BF16 ? 2 : 4;
+    return d.D >= 128 / esz && d.D * esz * 513 + 256 < ((int64_t)1 << 32) && ((uintptr_t)G) % esz == 0;
+}
+
 // Every row must start on a multiple of the bytes of 8 columns (16 for bf16, 32 for fp32 rows), hold at least one
 // chunk, and 512 rows plus a line must span < 4 GiB (lane offsets are 32-bit).
 bool split_path_ok(const void* G, int dtype, const Dims& d) {
@@ -355,7 +580,9 @@ ScorePlan score_split_plan(int64_t R, int dtype, const Dims& d, int num_cu) {
     p.row_tiles = (int)((R + 511) / 512);
     int64_t want = ((int64_t)num_cu + p.row_tiles - 1) / p.row_tiles;  // one work-group per CU
     int64_t s = (want + 7) / 8 * 8;
-    int64_t smax = ((chunks + 7) / 8 + 7) / 8 * 8;  // at least ~8 chunks per split
+    // At least ~2 chunks per split: a small projection is a chain of loads, 1 us per chunk and more (1024 rows of 5136 fp32:
+    // 25.7 us at 8 chunks, 16.2 at 2, with the finish of the more numerous partial sums as fast)
+    int64_t smax = ((chunks + 1) / 2 + 7) / 8 * 8;
     if (s > smax) s = smax;
     if (s < 8) s = 8;
     if (s > 512) s = 512;
@@ -365,31 +592,36 @@ ScorePlan score_split_plan(int64_t R, int dtype, const Dims& d, int num_cu) {
 }
 
 template <int NT, typename T>
-static hipError_t launch_split_t(const T* G, int64_t R, const void* img, float* partial, const ScorePlan& p,
+static hipError_t launch_split_t(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
                                  const Dims& d, hipStream_t st) {
     constexpr int KC = 128 / (int)sizeof(T);
-    constexpr size_t LDS = (size_t)4 * 2 * NT * 32 * (KC / 8) * 16;
-    if (hipError_t ea = ensure_dynamic_lds((const void*)project_split_kernel<NT, T>, (int)LDS); ea != hipSuccess) return ea;
+    const int lds = (parts == 3 ? 3 * 3 : 4 * 2) * NT * 32 * (KC / 8) * 16;
+    const void* kern = parts == 3 ? (const void*)project_any_kernel<NT, T> : (const void*)project_split_kernel<NT, T>;
+    if (hipError_t ea = ensure_dynamic_lds(kern, lds); ea != hipSuccess) return ea;
     const int64_t chunks = (d.D + KC - 1) / KC;
     dim3 grid((unsigned)(p.row_tiles * p.splits));
-    hipLaunchKernelGGL((project_split_kernel<NT, T>), grid, dim3(512), LDS, st, G, R, (const u32x4*)img, partial,
-                       p.row_tiles, d.D, chunks, p.slabs_per_split);
+    if (parts == 3)
+        hipLaunchKernelGGL((project_any_kernel<NT, T>), grid, dim3(512), lds, st, G, R, (const u32x4*)img, partial,
+                           p.row_tiles, d.D, chunks, p.slabs_per_split);
+    else
+        hipLaunchKernelGGL((project_split_kernel<NT, T>), grid, dim3(512), lds, st, G, R, (const u32x4*)img, partial,
+                           p.row_tiles, d.D, chunks, p.slabs_per_split);
     return hipGetLastError();
 }
 
 template <int NT>
-static hipError_t launch_split_nt(const void* G, int dtype, int64_t R, const void* img, float* partial,
+static hipError_t launch_split_nt(const void* G, int dtype, int64_t R, int parts, const void* img, float* partial,
                                   const ScorePlan& p, const Dims& d, hipStream_t st) {
-    if (dtype == SAGE_BF16) return launch_split_t<NT, uint16_t>((const uint16_t*)G, R, img, partial, p, d, st);
-    return launch_split_t<NT, float>((const float*)G, R, img, partial, p, d, st);
+    if (dtype == SAGE_BF16) return launch_split_t<NT, uint16_t>((const uint16_t*)G, R, parts, img, partial, p, d, st);
+    return launch_split_t<NT, float>((const float*)G, R, parts, img, partial, p, d, st);
 }
 
-hipError_t launch_project_split(const void* G, int dtype, int64_t R, const void* img, int KP, float* partial,
+hipError_t launch_project_split(const void* G, int dtype, int64_t R, int parts, const void* img, int KP, float* partial,
                                 const ScorePlan& p, const Dims& d, hipStream_t st) {
     switch (KP / 32) {
-        case 1: return launch_split_nt<1>(G, dtype, R, img, partial, p, d, st);
-        case 2: return launch_split_nt<2>(G, dtype, R, img, partial, p, d, st);
-        case 4: return launch_split_nt<4>(G, dtype, R, img, partial, p, d, st);
+        case 1: return launch_split_nt<1>(G, dtype, R, parts, img, partial, p, d, st);
+        case 2: return launch_split_nt<2>(G, dtype, R, parts, img, partial, p, d, st);
+        case 4: return launch_split_nt<4>(G, dtype, R, parts, img, partial, p, d, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -1,54 +1,43 @@
 // Scoring pass, second half (Algorithm 1, Phase II: "u <- zbar/||zbar||", "alpha_i <- <zhat_i, u>",
 // "Select top-k by alpha_i"): consensus direction, cosine scores, radix-select of the m-th largest score and a
 // stable compaction of the selected indices in ascending order.
+#include "score_ops.h"
 #include "select_ops.h"
 
 namespace sage {
 
-// One wave per row (lane j holds coordinates j, j+64); every work-group first rebuilds u from the consensus sum.
-// alpha_i = clamp(<zhat_i, u>, -1, 1), -0 stored as +0.
+// alpha_i = clamp(<zhat_i, u>, -1, 1), -0 stored as +0, with u = ssum / ||ssum|| made by every wave. A wave takes a row per
+// group of L = KP / 4 lanes, four times over.
+template <int L>
 __global__ __launch_bounds__(256) void cosine_kernel(const float* __restrict__ zhat, int64_t N, int k,
                                                      const double* __restrict__ ssum, float* __restrict__ alpha) {
-    __shared__ double u[128];
-    __shared__ double red[128];
-    const int tid = threadIdx.x;
-    if (tid < 128) {
-        double s = tid < k ? ssum[tid] : 0.0;
-        u[tid] = s;
-        red[tid] = s * s;
-    }
-    __syncthreads();
-    for (int w = 64; w >= 1; w >>= 1) {  // fixed-shape tree
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-    }
-    const double nrm = sqrt(red[0]);
-    __syncthreads();
-    if (tid < 128) u[tid] = nrm > 0.0 ? u[tid] / nrm : 0.0;
-    __syncthreads();
-    const int wave = tid >> 6, lane = tid & 63;
-    const double u0 = u[lane], u1 = u[lane + 64];
-    for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < N; r += (int64_t)gridDim.x * 4) {
-        const float* z = zhat + r * k;
-        double a = 0.0;
-        if (lane < k) a = (double)z[lane] * u0;
-        if (lane + 64 < k) a += (double)z[lane + 64] * u1;
-        for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
-        if (lane == 0) {
-            if (a > 1.0) a = 1.0;
-            if (a < -1.0) a = -1.0;
-            float f = (float)a;
-            if (f == 0.f) f = 0.f;  // -0 -> +0
-            alpha[r] = f;
-        }
+    constexpr int G = 64 / L, U = 4;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane / L, c0 = (lane % L) * 4;
+    const int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * (U * G) + g;
+    double z[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            z[u][c] = r0 + u * G < N && c0 + c < k ? (double)zhat[(r0 + u * G) * k + c0 + c] : 0.0;
+    double cu[4];
+    consensus_unit<L>(ssum, k, c0, cu);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float f = clamp_score(row_dot<L>(z[u], cu));
+        if (r0 + u * G < N && lane % L == 0) alpha[r0 + u * G] = f;
     }
 }
 
 hipError_t launch_cosine(const float* zhat, int64_t N, int k, const double* ssum, float* alpha, hipStream_t st) {
     if (N <= 0) return hipSuccess;
-    int64_t blocks = (N + 3) / 4;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(cosine_kernel, dim3((unsigned)blocks), dim3(256), 0, st, zhat, N, k, ssum, alpha);
+    const int L = k <= 32 ? 8 : (k <= 64 ? 16 : 32);
+    const unsigned blocks = (unsigned)((N * L + 1023) / 1024);
+    switch (L) {
+        case 8: hipLaunchKernelGGL(cosine_kernel<8>, dim3(blocks), dim3(256), 0, st, zhat, N, k, ssum, alpha); break;
+        case 16: hipLaunchKernelGGL(cosine_kernel<16>, dim3(blocks), dim3(256), 0, st, zhat, N, k, ssum, alpha); break;
+        default: hipLaunchKernelGGL(cosine_kernel<32>, dim3(blocks), dim3(256), 0, st, zhat, N, k, ssum, alpha); break;
+    }
     return hipGetLastError();
 }
 

@@ -47,3 +47,32 @@ def test_class_selection_at_the_edges_of_its_variants(sizes, distinct):
             want = oracle.cb_select_from_alpha(s.scores().cpu().numpy(), labels, C, keep, rule)
             assert idx.tolist() == want.tolist()
     s.close()
+
+
+# Rows of any width and start: whole windows only, a partial one, less than one; every basis width; a batch that starts in the
+# middle of a line. The 3-part products are good to fp32, so the tolerance is fp32's.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [31, 33, 64, 65, 127, 1001, 4099])
+@pytest.mark.parametrize("k", [3, 40, 100])
+def test_projection_of_rows_of_any_alignment(dtype, D, k):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    rng = np.random.default_rng(D + k)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    n = 700
+    flat = torch.from_numpy(rng.standard_normal(n * D + 1).astype(np.float32)).to(td).cuda()
+    G = flat[1:].view(n, D)  # not on a multiple of 16 bytes
+    V = torch.from_numpy(rng.standard_normal((k, D)).astype(np.float32)).cuda()
+    s = Sage(max(2 * k, 2), D, dtype=dtype, max_rows=2 * n)
+    s.set_basis(V)
+    s.score(G)
+    s.score(G[:1].clone())
+    got = s.zhat().cpu().double()
+    Z = G.double().cpu() @ V.double().cpu().T
+    norm = Z.norm(dim=1, keepdim=True)
+    scale = G.double().cpu().norm(dim=1, keepdim=True) * V.double().cpu().norm(dim=1).max()
+    assert ((got[:n] - Z / norm).abs() * norm / scale).max() <= 3e-7
+    assert (got[n] - got[0]).abs().max() <= 1e-4  # (an aligned start may take the two-part basis)
+    s.close()
