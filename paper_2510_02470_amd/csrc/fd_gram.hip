@@ -305,8 +305,8 @@ __global__ __launch_bounds__(256, 2) void gram_cross8_kernel(const float* __rest
 // instructions (all waves of a work-group run in step: conversions done in one block would leave the matrix cores
 // idle), from registers that were loaded a stage earlier and are reloaded, for the slab after next, as soon as they
 // have been consumed.
-// NEW1: every new row in use is a bf16 value stored as fp32 (rows of a bf16 stream): its mid and lo parts are zero, so
-// only its hi part is staged and only the three products with it are issued. The three left out would add exact
+// NEW1: the new half is kept in pieces of bf16 (half16): its mid and lo parts are zero, so only one part is staged, as it
+// is, and only the three products with it are issued. The three left out would add exact
 // zeros: the result has the same bits either way.
 template <bool NEW1>
 __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* __restrict__ top,
@@ -344,8 +344,11 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
             for (int e = 0; e < 16; ++e) acc[i][b][e] = 0.f;
 
     // staging: piece ps = it * 512 + tid is columns 4p .. 4p+3 of row ps >> 2 (rows >= LP: the new half)
+    // (NEW1: the new rows' pieces are those of half16: piece tid is k-half tid >> 8 of row tid & 255)
     const f32x4* Tv = reinterpret_cast<const f32x4*>(top);
     const f32x4* Nv = reinterpret_cast<const f32x4*>(nw);
+    const u32x4* N16 = half16(nw, LP, slabs_total);
+    constexpr int IT = NEW1 ? 3 : 4;
     int src[4], dst8[4];  // source piece in the half buffer (-1: a new row not in use), LDS offset in 8-byte units
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
@@ -354,18 +357,25 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
         src[it] = (row >= LP && hr >= nfill) ? -1 : hr * 4 + p;
         dst8[it] = (((p >> 1) * HREG + row) << 1) + (p & 1);
     }
+    const bool used16 = (tid & 255) < nfill;
+    const int dst16 = (tid >> 8) * HREG + LP + (tid & 255);
     f32x4 pre[4];
+    u32x4 pre16;
     auto fetch1 = [&](int it, int64_t sl) __attribute__((always_inline)) {
         const int64_t sc = sl < s1 ? sl : s1 - 1;  // beyond the end: repeat (never used)
+        if (NEW1 && it == 2) {
+            pre16 = N16[sc * 512 + tid];
+            return;
+        }
         const f32x4* base = (it >= 2 ? Nv : Tv) + sc * HALF4;
         pre[it] = src[it] >= 0 ? base[src[it]] : f32x4{0.f, 0.f, 0.f, 0.f};
     };
     auto store1 = [&](int it, int buf) __attribute__((always_inline)) {
-        uint2* d = reinterpret_cast<uint2*>(ldsx + buf * STAGE16) + dst8[it];
-        if (NEW1 && it >= 2) {  // new rows (pieces 1024 ..)
-            d[0] = make_uint2(hi_bf16(pre[it][0], pre[it][1]), hi_bf16(pre[it][2], pre[it][3]));
+        if (NEW1 && it == 2) {
+            ldsx[buf * STAGE16 + dst16] = used16 ? pre16 : u32x4{0u, 0u, 0u, 0u};
             return;
         }
+        uint2* d = reinterpret_cast<uint2*>(ldsx + buf * STAGE16) + dst8[it];
         unsigned a0, a1, a2, b0, b1, b2;
         split3_bf16(pre[it][0], pre[it][1], a0, a1, a2);
         split3_bf16(pre[it][2], pre[it][3], b0, b1, b2);
@@ -375,9 +385,9 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
     };
     if (s0 < s1) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) fetch1(it, s0);
+        for (int it = 0; it < IT; ++it) fetch1(it, s0);
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
+        for (int it = 0; it < IT; ++it) {
             store1(it, 0);
             fetch1(it, s0 + 1);
         }
@@ -416,10 +426,6 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
             if (NEW1) {
                 store1(q, cur ^ 1);
                 fetch1(q, s + 2);
-                if (q == 2) {
-                    store1(3, cur ^ 1);
-                    fetch1(3, s + 2);
-                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -577,8 +583,8 @@ __global__ __launch_bounds__(256, 2) void gram_new8_kernel(const float* __restri
 // The same triangle on the bf16 matrix cores with three-way split values (see gram_cross8_split_kernel): the new rows
 // of a slab are split when they are staged ([part][k-half][row] pieces, 24 KB per stage), a wave's six operand row
 // blocks are 18 LDS reads per 54 matrix-core instructions, and the next slab is split and stored between the six
-// groups of matrix-core instructions. NEW1 (see gram_cross8_split_kernel): one part, one product.
-template <int W, bool NEW1>
+// groups of matrix-core instructions.
+template <int W>
 __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ Nv, int nfill, float* __restrict__ partial,
                                                      int group, int64_t s0, int64_t s1, u32x4* lds) {
     using M = New8Map<W>;
@@ -609,10 +615,6 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
     };
     auto store1 = [&](int it, int buf) __attribute__((always_inline)) {
         uint2* d = reinterpret_cast<uint2*>(lds + buf * STAGE16) + dst8[it];
-        if (NEW1) {
-            d[0] = make_uint2(hi_bf16(pre[it][0], pre[it][1]), hi_bf16(pre[it][2], pre[it][3]));
-            return;
-        }
         unsigned a0, a1, a2, b0, b1, b2;
         split3_bf16(pre[it][0], pre[it][1], a0, a1, a2);
         split3_bf16(pre[it][2], pre[it][3], b0, b1, b2);
@@ -634,7 +636,7 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
     for (int64_t s = s0; s < s1; ++s) {
         const int cur = (int)((s - s0) & 1);
         const u32x4* st = lds + cur * STAGE16 + h * HREG + l32;
-        constexpr int NP3 = NEW1 ? 1 : 3, NQ = NEW1 ? 1 : 6;
+        constexpr int NP3 = 3, NQ = 6;
         u32x4 op[6][NP3];
 #pragma unroll
         for (int p = 0; p < NP3; ++p)
@@ -646,13 +648,7 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
             constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
             for (int q = 0; q < 9; ++q) acc[q] = mfma_bf16(op[M::pa[q]][PA[k]], op[M::pb[q]][PB[k]], acc[q]);
-            if (NEW1) {
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    store1(it, cur ^ 1);
-                    fetch1(it, s + 2);
-                }
-            } else if (k < 4) {
+            if (k < 4) {
                 store1(k, cur ^ 1);
                 fetch1(k, s + 2);
             }
@@ -677,7 +673,6 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
     }
 }
 
-template <bool NEW1>
 __global__ __launch_bounds__(256, 2) void gram_new8_split_kernel(const float* __restrict__ nw, int nfill,
                                                                  float* __restrict__ partial, int64_t slabs_total,
                                                                  int64_t slabs_per_group, int groups, int skip) {
@@ -690,10 +685,102 @@ __global__ __launch_bounds__(256, 2) void gram_new8_split_kernel(const float* __
     if (s0 > s1) s0 = s1;
     const f32x4* Nv = reinterpret_cast<const f32x4*>(nw);
     switch (threadIdx.x >> 6) {  // wave-uniform
-        case 0: gram_new8_split_wave<0, NEW1>(Nv, nfill, partial, group, s0, s1, ldsn); break;
-        case 1: gram_new8_split_wave<1, NEW1>(Nv, nfill, partial, group, s0, s1, ldsn); break;
-        case 2: gram_new8_split_wave<2, NEW1>(Nv, nfill, partial, group, s0, s1, ldsn); break;
-        default: gram_new8_split_wave<3, NEW1>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+        case 0: gram_new8_split_wave<0>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+        case 1: gram_new8_split_wave<1>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+        case 2: gram_new8_split_wave<2>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+        default: gram_new8_split_wave<3>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+    }
+}
+
+// The triangle of a new half kept in pieces of bf16 (half16): one part, one product, and nothing to convert, so the pieces go
+// straight to LDS, three slabs (24 KB) at a time into a ring of three: a barrier per three slabs, two stages on their way.
+// (By way of registers and fp32, a slab at a time, the kernel took 590 us beside the eigensolve at D = 2,049,000.)
+// FULL: all 256 rows are in use; otherwise the rows beyond nfill are taken as zero.
+template <int W, bool FULL>
+__device__ __forceinline__ void gram_new8_half_wave(const u32x4* __restrict__ N16, int nfill, float* __restrict__ partial,
+                                                    int group, int64_t s0, int64_t s1, u32x4* lds) {
+    using M = New8Map<W>;
+    constexpr int LP = 256, SL = 3, STAGE = SL * 2 * LP, ML = STAGE / 256;
+    const int tid = threadIdx.x & 255, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+
+    f32x16 acc[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+
+    auto stage = [&](int64_t sl, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < ML; ++q) {
+            const int64_t s = sl + q / 2;  // (512 pieces a slab, two loads of 256)
+            const int64_t sc = s < s1 ? s : s1 - 1;  // beyond the end: repeat (never used)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)(N16 + sc * (2 * LP) + (q & 1) * 256 + tid),
+                (__attribute__((address_space(3))) void*)(lds + buf * STAGE + q * 256 + wave * 64), 16, 0, 0);
+        }
+    };
+    if (s0 < s1) {
+        stage(s0, 0);
+        stage(s0 + SL, 1);
+    }
+    int buf = 0;
+    for (int64_t s = s0; s < s1; s += SL) {
+        // all but the last stage's loads have landed; everyone is done with the buffer of the stage before
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0F70 | ML);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        stage(s + 2 * SL, buf == 0 ? 2 : buf - 1);
+        const u32x4* st = lds + buf * STAGE + h * LP + l32;
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            if (s + u >= s1) break;  // (uniform)
+            u32x4 op[6];
+#pragma unroll
+            for (int o = 0; o < 6; ++o) {
+                op[o] = st[u * 2 * LP + M::rows[o] * 32];
+                if (!FULL && M::rows[o] * 32 + l32 >= nfill) op[o] = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int q = 0; q < 9; ++q) acc[q] = mfma_bf16(op[M::pa[q]], op[M::pb[q]], acc[q]);
+        }
+        buf = buf == 2 ? 0 : buf + 1;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS when the work-group ends
+
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        const int bi = M::rows[M::pa[q]], bj = M::rows[M::pb[q]];
+        const int ti = bi >> 1, tj = bj >> 1;
+        float* out = partial + ((int64_t)group * 10 + ti * (ti + 1) / 2 + tj) * 4096 + (bi & 1) * 2048 + (bj & 1) * 32;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int r = 8 * (e >> 2) + 4 * h + (e & 3);
+            out[r * 64 + l32] = acc[q][e];
+        }
+    }
+}
+
+template <bool FULL>
+__global__ __launch_bounds__(256, 2) void gram_new8_half_kernel(const float* __restrict__ nw, int nfill,
+                                                                float* __restrict__ partial, int64_t slabs_total,
+                                                                int64_t slabs_per_group, int groups, int skip) {
+    extern __shared__ u32x4 ldsh[];
+    const int group = (int)xcd_rank(blockIdx.x, skip);
+    if (group < 0 || group >= groups) return;
+    int64_t s0 = (int64_t)group * slabs_per_group;
+    int64_t s1 = s0 + slabs_per_group;
+    if (s1 > slabs_total) s1 = slabs_total;
+    if (s0 > s1) s0 = s1;
+    const u32x4* N16 = half16(nw, 256, slabs_total);
+    switch (threadIdx.x >> 6) {  // wave-uniform
+        case 0: gram_new8_half_wave<0, FULL>(N16, nfill, partial, group, s0, s1, ldsh); break;
+        case 1: gram_new8_half_wave<1, FULL>(N16, nfill, partial, group, s0, s1, ldsh); break;
+        case 2: gram_new8_half_wave<2, FULL>(N16, nfill, partial, group, s0, s1, ldsh); break;
+        default: gram_new8_half_wave<3, FULL>(N16, nfill, partial, group, s0, s1, ldsh); break;
     }
 }
 
@@ -825,13 +912,23 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
         return hipGetLastError();
     }
     if (p.mode == 2 && d.NP == 512 && p.split) {
-        constexpr int LDS_SPLIT = 2 * 3 * 2 * (256 + 8) * 16;  // two stages
-        if (new_one)
-            hipLaunchKernelGGL(gram_new8_split_kernel<true>, dim3((unsigned)xcd_grid(p.groups, skip)), dim3(256), LDS_SPLIT, st, nw,
-                               nfill, partial, d.S, p.slabs_per_group, p.groups, skip);
-        else
-            hipLaunchKernelGGL(gram_new8_split_kernel<false>, dim3((unsigned)xcd_grid(p.groups, skip)), dim3(256), LDS_SPLIT, st, nw,
-                               nfill, partial, d.S, p.slabs_per_group, p.groups, skip);
+        const dim3 wgs((unsigned)xcd_grid(p.groups, skip));
+        if (new_one) {
+            constexpr int LDS = 3 * 3 * 2 * 256 * 16;  // three stages of three slabs
+            const bool full = nfill >= 256;
+            const void* kern = full ? (const void*)gram_new8_half_kernel<true> : (const void*)gram_new8_half_kernel<false>;
+            if (hipError_t ea = ensure_dynamic_lds(kern, LDS); ea != hipSuccess) return ea;
+            if (full)
+                hipLaunchKernelGGL(gram_new8_half_kernel<true>, wgs, dim3(256), LDS, st, nw, nfill, partial, d.S,
+                                   p.slabs_per_group, p.groups, skip);
+            else
+                hipLaunchKernelGGL(gram_new8_half_kernel<false>, wgs, dim3(256), LDS, st, nw, nfill, partial, d.S,
+                                   p.slabs_per_group, p.groups, skip);
+        } else {
+            constexpr int LDS = 2 * 3 * 2 * (256 + 8) * 16;  // two stages
+            hipLaunchKernelGGL(gram_new8_split_kernel, wgs, dim3(256), LDS, st, nw, nfill, partial, d.S, p.slabs_per_group,
+                               p.groups, skip);
+        }
         return hipGetLastError();
     }
     if (p.mode == 2 && d.NP == 512 && p.wg_per_group == 1) {

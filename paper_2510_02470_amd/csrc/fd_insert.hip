@@ -27,10 +27,32 @@ __global__ __launch_bounds__(256) void insert_kernel(Src src, int rows, int row0
         if (s0 + i < S) dst[(int64_t)i * NP * (DC / 4)] = v[i];
 }
 
+struct __attribute__((packed, aligned(2))) Eight {  // eight bf16 values at any element boundary
+    u32x4 v;
+};
+
 // Rows of a row-major batch. VEC: every row starts on a multiple of four elements.
 template <typename T, bool VEC>
 struct DenseRows {
+    static constexpr bool BF16 = sizeof(T) == 2;
     const T* G;
+    // pieces of 8 columns, 32 columns apart, of a bf16 row (at any element boundary)
+    template <int NS>
+    __device__ __forceinline__ void load16(int r, int64_t d0, int64_t D, u32x4 (&v)[NS]) const {
+        const T* g = G + r * D + d0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int64_t d = d0 + 32 * i;
+            if (d + 8 <= D) {
+                v[i] = reinterpret_cast<const Eight*>(g + 32 * i)->v;
+            } else {
+                T x[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) x[c] = d + c < D ? g[32 * i + c] : (T)0;
+                __builtin_memcpy(&v[i], x, sizeof(x) < 16 ? sizeof(x) : 16);
+            }
+        }
+    }
     template <int NS>
     __device__ __forceinline__ void load(int r, int64_t d0, int64_t D, float4 (&v)[NS]) const {
         const T* g = G + r * D + d0;
@@ -64,11 +86,38 @@ struct DenseRows {
     }
 };
 
+// The same for a half kept in pieces of bf16: lane = (row, piece of four neighbours), so that a store is four runs of 16
+// rows, 256 bytes each, and a work-group's are 1 KB.
+template <int NS, typename Src>
+__global__ __launch_bounds__(256) void insert16_kernel(Src src, int rows, int row0, u32x4* __restrict__ B, int LP, int64_t D,
+                                                       int64_t Q, int row_groups, int64_t units, int skip) {
+    const int64_t unit = xcd_rank(blockIdx.x, skip);
+    if (unit < 0 || unit >= units) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = (int)((unsigned)unit % (unsigned)row_groups) * 64 + wave * 16 + (lane & 15);
+    if (r >= rows) return;
+    const int64_t q0 = (int64_t)((unsigned)unit / (unsigned)row_groups) * (4 * NS) + (lane >> 4);
+    u32x4 v[NS];
+    src.template load16<NS>(r, q0 * 8, D, v);
+    u32x4* dst = B + q0 * LP + row0 + r;
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+        if (q0 + 4 * i < Q) dst[(int64_t)(4 * i) * LP] = v[i];
+}
+
 template <typename Src>
 static hipError_t launch_insert_src(const Src& src, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                                    int skip, hipStream_t st) {
+                                    bool to16, int skip, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
     const int row_groups = (int)((rows + 63) / 64);
+    if constexpr (Src::BF16) {
+        if (to16) {
+            const int64_t Q = 2 * d.S, units = (Q + 31) / 32 * row_groups;  // 8 loads a lane, 512 bytes of a row
+            hipLaunchKernelGGL((insert16_kernel<8, Src>), dim3((unsigned)xcd_grid(units, skip)), dim3(256), 0, st, src, (int)rows,
+                               row0, const_cast<u32x4*>(half16(half, half_rows, d.S)), half_rows, d.D, Q, row_groups, units, skip);
+            return hipGetLastError();
+        }
+    }
     // 16 slabs a wave, 16 KB of fp32 stores; 4 where that would leave the chip short of waves
     const int64_t wide = (d.S + 15) / 16 * row_groups;
     const int64_t units = wide >= 1024 ? wide : (d.S + 3) / 4 * row_groups;
@@ -83,12 +132,49 @@ static hipError_t launch_insert_src(const Src& src, int64_t rows, int row0, floa
 }
 
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         int skip, hipStream_t st) {
+                         bool to16, int skip, hipStream_t st) {
     const bool vec = d.D % 4 == 0 && (uintptr_t)G % (dtype == SAGE_BF16 ? 8 : 16) == 0;
-#define SAGE_INSERT(T, V) launch_insert_src(DenseRows<T, V>{(const T*)G}, rows, row0, half, half_rows, d, skip, st)
+#define SAGE_INSERT(T, V) launch_insert_src(DenseRows<T, V>{(const T*)G}, rows, row0, half, half_rows, d, to16, skip, st)
     if (dtype == SAGE_BF16) return vec ? SAGE_INSERT(uint16_t, true) : SAGE_INSERT(uint16_t, false);
     return vec ? SAGE_INSERT(float, true) : SAGE_INSERT(float, false);
 #undef SAGE_INSERT
+}
+
+// Pieces of bf16 to the fp32 half, in place: slab s goes to bytes [16 KB s ..) of LP = 256 rows, its pieces lie at half the
+// memory plus 8 KB s. The first half of the slabs overwrites no pieces, the next quarter only such as are done with, and so
+// on; the last slab overwrites its own, which its work-group has read by then.
+__global__ __launch_bounds__(512) void widen_kernel(float* __restrict__ half, int LP, int64_t S, int64_t s0) {
+    const int64_t s = s0 + blockIdx.x;
+    const u32x4* src = half16(half, LP, S) + 2 * s * LP;
+    u32x4 v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int p = i * 512 + threadIdx.x;  // piece (column group p / LP, row p % LP)
+        v[i] = p < 2 * LP ? src[p] : u32x4{0u, 0u, 0u, 0u};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int p = i * 512 + threadIdx.x;
+        if (p >= 2 * LP) continue;
+        float4* dst = reinterpret_cast<float4*>(half + (s * LP + p % LP) * DC + (p / LP) * 8);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            dst[h] = make_float4(__uint_as_float(v[i][2 * h] << 16), __uint_as_float(v[i][2 * h] & 0xffff0000u),
+                                 __uint_as_float(v[i][2 * h + 1] << 16), __uint_as_float(v[i][2 * h + 1] & 0xffff0000u));
+    }
+}
+
+hipError_t launch_widen(float* half, const Dims& d, hipStream_t st) {
+    if (d.LP > 512) return hipErrorInvalidValue;
+    for (int64_t lo = 0; lo < d.S;) {
+        int64_t hi = (d.S + lo) / 2;
+        if (hi == lo) hi = lo + 1;
+        hipLaunchKernelGGL(widen_kernel, dim3((unsigned)(hi - lo)), dim3(512), 0, st, half, d.LP, d.S, lo);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        lo = hi;
+    }
+    return hipSuccess;
 }
 
 // Factored rows (a linear last layer: column c*dh + t of row r is e_rc * h_rt, column C*dh + c is e_rc; Method,
@@ -118,12 +204,50 @@ struct __attribute__((packed, aligned(sizeof(T)))) Four {
 // sixteen columns with wrap-around; four columns of one class take one load of h and one of e.
 template <typename T>
 struct OuterRows {
+    static constexpr bool BF16 = sizeof(T) == 2;
     const T* E;
     const T* H;
     int64_t C, dh;
     static __device__ __forceinline__ float value(T e, T h) {
         if constexpr (sizeof(T) == 2) return (float)(__bf16)(bf16_to_f32(e) * bf16_to_f32(h));
         else return e * h;
+    }
+    // pieces of 8 columns, 32 columns apart
+    template <int NS>
+    __device__ __forceinline__ void load16(int r, int64_t d0, int64_t D, u32x4 (&v)[NS]) const {
+        const int64_t main = C * dh;
+        const T* e = E + r * C;
+        const T* h = H + r * dh;
+        int64_t cls = d0 / dh, t = d0 - cls * dh;
+        T ev[NS];
+        bool fast[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            fast[i] = cls < C && t + 7 < dh;
+            if (fast[i]) {
+                ev[i] = e[cls];
+                v[i] = reinterpret_cast<const Eight*>(h + t)->v;
+            }
+            t += 32;
+            while (t >= dh) {
+                t -= dh;
+                ++cls;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            if (fast[i]) {
+                const float s = bf16_to_f32((uint16_t)ev[i]);
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    v[i][w] = pack_bf16(s * __uint_as_float(v[i][w] << 16), s * __uint_as_float(v[i][w] & 0xffff0000u));
+            } else {
+#pragma unroll
+                for (int w = 0; w < 4; ++w)  // (outer_value's are bf16 values already)
+                    v[i][w] = hi_bf16(outer_value(e, h, d0 + 32 * i + 2 * w, main, dh, D),
+                                      outer_value(e, h, d0 + 32 * i + 2 * w + 1, main, dh, D));
+            }
+        }
     }
     template <int NS>
     __device__ __forceinline__ void load(int r, int64_t d0, int64_t D, float4 (&v)[NS]) const {
@@ -163,12 +287,12 @@ struct OuterRows {
 };
 
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, int skip, hipStream_t st) {
+                               float* half, int half_rows, const Dims& d, bool to16, int skip, hipStream_t st) {
     if (dtype == SAGE_BF16)
         return launch_insert_src(OuterRows<uint16_t>{(const uint16_t*)E, (const uint16_t*)H, C, dh}, rows, row0, half,
-                                 half_rows, d, skip, st);
-    return launch_insert_src(OuterRows<float>{(const float*)E, (const float*)H, C, dh}, rows, row0, half, half_rows, d, skip,
-                             st);
+                                 half_rows, d, to16, skip, st);
+    return launch_insert_src(OuterRows<float>{(const float*)E, (const float*)H, C, dh}, rows, row0, half, half_rows, d, false,
+                             skip, st);
 }
 
 // The same rows written out row-major in their own type (for shapes the factored projection does not take).

@@ -172,7 +172,8 @@ hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const fl
 // ring of three LDS buffers with direct global->LDS loads two stages ahead. The column operand is requested two
 // stages ahead as well.
 // NPT > 0: the buffer has NPT rows and the new rows in use hold bf16 values; their stages take the hi part alone and
-// three products (the other three would add exact zeros). NPT = 0: any buffer, all parts.
+// three products (the other three would add exact zeros). NPT = 0: any buffer, all parts. NPT = 512: the new half is kept in
+// pieces of bf16 (half16); a lane loads the 4 bytes that hold its column's value and picks its half.
 template <int MT, int NPT>
 __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top, const float* __restrict__ nw, int nfill,
                                                                const u32x4* __restrict__ Mc3, float* out, int NP,
@@ -196,12 +197,21 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
     const float* tcol = (live ? top : nw) + coff;
     const float* ncol = nw + coff;
     const int nstage = NP / 16;
-    auto fetch_b = [&](int stg, float (&b)[8]) __attribute__((always_inline)) {
+    constexpr bool HALF = NPT == 512;
+    const float* hcol = HALF ? reinterpret_cast<const float*>(half16(nw, LP, Dp / DC) + (dc / 8) * LP + h) + (dc % 8) / 2 : nw;
+    const unsigned pick = HALF && !(dc & 1) ? 0x05040100u : 0x07060302u;  // lower or upper halves of two words
+    auto fetch_b = [&](auto from_half, int stg, float (&b)[8]) __attribute__((always_inline)) {
         const int sg = stg < nstage ? stg : nstage - 1;  // beyond the end: repeat (never used)
         const int r0 = sg * 16;
-        const float* bn = r0 >= LP ? ncol + (int64_t)(r0 - LP) * DC : tcol + (int64_t)r0 * DC;
+        if constexpr (decltype(from_half)::value) {
+            const float* bn = hcol + (r0 - LP) * 4;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) b[s] = bn[(int64_t)(2 * s) * DC];
+            for (int s = 0; s < 8; ++s) b[s] = bn[2 * s * 4];
+        } else {
+            const float* bn = r0 >= LP ? ncol + (int64_t)(r0 - LP) * DC : tcol + (int64_t)r0 * DC;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) b[s] = bn[(int64_t)(2 * s) * DC];
+        }
     };
     auto fetch_m = [&](int stg, int buf) __attribute__((always_inline)) {
         const int sg = stg < nstage ? stg : nstage - 1;
@@ -220,7 +230,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
         for (int i = 0; i < 16; ++i) acc[m][i] = 0.f;
 
     // One stage: 16 buffer rows. b: its column operand (requested two stages ago); bfar receives that of stage + 2.
-    auto stage = [&](auto one_c, const float (&b)[8], float (&bfar)[8], int stg, int cur) __attribute__((always_inline)) {
+    auto stage = [&](auto one_c, auto far_half, const float (&b)[8], float (&bfar)[8], int stg, int cur) __attribute__((always_inline)) {
         constexpr bool one = decltype(one_c)::value;  // a stage of new rows with one part
         const u32x4* A = Ms + cur * STAGE16 + h * MP + c;  // + part * 2 * MP + tile * 32
         u32x4 a[2][2][3];  // [buffer][tile of the pair][part]
@@ -236,7 +246,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
         for (int e = 0; e < 4; ++e) {
             const float x = 4 * e < limit ? b[2 * e] : 0.f, y = 4 * e + 2 < limit ? b[2 * e + 1] : 0.f;
             if constexpr (one) {
-                bh[e] = hi_bf16(x, y);
+                bh[e] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), pick);
                 bm[e] = 0u;
                 bl[e] = 0u;
             } else {
@@ -248,7 +258,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
             }
         }
         fetch_m(stg + 2, cur == 0 ? 2 : cur - 1);
-        fetch_b(stg + 2, bfar);
+        fetch_b(far_half, stg + 2, bfar);
         __builtin_amdgcn_sched_barrier(0);
         // two tiles at a time, their instructions alternating (an instruction never waits for the one just issued)
 #pragma unroll
@@ -294,23 +304,25 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
     float b0[8], b1[8], b2[8];
     constexpr std::false_type all_parts{};
     constexpr std::true_type one_part{};
-    auto triples = [&](auto one_c, int s, int end) __attribute__((always_inline)) {  // from ring position 0
+    auto triples = [&](auto one_c, auto far_half, int s, int end) __attribute__((always_inline)) {  // from ring position 0
         for (; s + 2 < end; s += 3) {
-            stage(one_c, b0, b2, s, 0);
-            stage(one_c, b1, b0, s + 1, 1);
-            stage(one_c, b2, b1, s + 2, 2);
+            stage(one_c, far_half, b0, b2, s, 0);
+            stage(one_c, far_half, b1, b0, s + 1, 1);
+            stage(one_c, far_half, b2, b1, s + 2, 2);
         }
-        if (s < end) stage(one_c, b0, b2, s, 0);
-        if (s + 1 < end) stage(one_c, b1, b0, s + 1, 1);
+        if (s < end) stage(one_c, far_half, b0, b2, s, 0);
+        if (s + 1 < end) stage(one_c, far_half, b1, b0, s + 1, 1);
     };
+    constexpr std::false_type fp32{};
+    constexpr std::integral_constant<bool, HALF> halves{};
     if constexpr (NPT == 0) {
         fetch_m(0, 0);
         fetch_m(1, 1);
-        fetch_b(0, b0);
-        fetch_b(1, b1);
+        fetch_b(fp32, 0, b0);
+        fetch_b(fp32, 1, b1);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        triples(all_parts, 0, nstage);
+        triples(all_parts, fp32, 0, nstage);
     } else {
         // The top half's NPT / 32 stages start at the ring position that lets the new half's start at position 0.
         constexpr int S1 = NPT / 32, R = S1 % 3;
@@ -318,24 +330,29 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
         if constexpr (R == 1) {
             fetch_m(0, 2);
             fetch_m(1, 0);
-            fetch_b(0, b2);
-            fetch_b(1, b0);
+            fetch_b(fp32, 0, b2);
+            fetch_b(fp32, 1, b0);
         } else {
             fetch_m(0, 1);
             fetch_m(1, 2);
-            fetch_b(0, b1);
-            fetch_b(1, b2);
+            fetch_b(fp32, 0, b1);
+            fetch_b(fp32, 1, b2);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if constexpr (R == 1) {
-            stage(all_parts, b2, b1, 0, 2);
+            stage(all_parts, fp32, b2, b1, 0, 2);
         } else {
-            stage(all_parts, b1, b0, 0, 1);
-            stage(all_parts, b2, b1, 1, 2);
+            stage(all_parts, fp32, b1, b0, 0, 1);
+            stage(all_parts, fp32, b2, b1, 1, 2);
         }
-        triples(all_parts, R, S1);
-        triples(one_part, S1, 2 * S1);
+        // (the last two stages of the top half request the first two of the new half)
+        static_assert((S1 - R) % 3 == 0 && S1 - R >= 3, "whole triples");
+        triples(all_parts, fp32, R, S1 - 3);
+        stage(all_parts, fp32, b0, b2, S1 - 3, 0);
+        stage(all_parts, halves, b1, b0, S1 - 2, 1);
+        stage(all_parts, halves, b2, b1, S1 - 1, 2);
+        triples(one_part, halves, S1, 2 * S1);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS when the work-group ends
 

@@ -76,6 +76,7 @@ struct sage_ctx {
     // the products with the new rows' mid and lo parts (exact zeros; same bits). nw_bf16[i]: every row in use in nw[i]
     // came from a bf16 batch (row-major or factored; not sage_fd_merge's fp32 rows). one_part: the shortcut is allowed (off under SAGE_MM_SPLIT_ALL_PARTS).
     bool nw_bf16[2] = {false, false};
+    bool nw_half[2] = {false, false};  // nw[i] is kept in pieces of bf16 (half16), not as fp32
     bool one_part = true;
     double* acc = nullptr;  // [0] sum_delta [1] frob2 [2] last_delta [4] failed solves
 
@@ -237,18 +238,36 @@ struct RowSrc {
     }
 };
 
-hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int half_rows, const Dims& d, hipStream_t st,
-                       int skip = -1) {
-    if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, skip, st);
-    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, skip, st);
+hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int half_rows, const Dims& d, bool to16,
+                       hipStream_t st, int skip = -1) {
+    if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, to16, skip, st);
+    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, to16, skip, st);
 }
 
-// Rows of `s` are about to be stored in nw[i] from row row0 on.
-void note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
-    const bool b = s.dtype == SAGE_BF16;  // factored rows of a bf16 context are rounded to bf16 when they are stored
-    c->nw_bf16[i] = row0 == 0 ? b : (c->nw_bf16[i] && b);
+bool split_grams(const sage_ctx* c) {
+    return c->mm_mode == SAGE_MM_SPLIT && c->gp_cross_split.tiles > 0 && c->gp_new2_split.tiles > 0;
 }
-bool new_one(const sage_ctx* c, int i) { return c->one_part && c->nw_bf16[i]; }
+
+// The new half nw[i] as fp32 (on the context stream; the side stream is done with it): for the kernels that know no other form.
+int widen(sage_ctx* c, int i) {
+    if (!c->nw_half[i]) return SAGE_OK;
+    if (c->st2) HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[i], 0));  // (never recorded: nothing to wait for)
+    HIPCHK(launch_widen(c->nw[i], c->d, c->st));
+    c->nw_half[i] = false;
+    return SAGE_OK;
+}
+
+// Rows of `s` are about to be stored in nw[i] from row row0 on (by the context stream unless row0 = 0).
+int note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
+    const bool b = s.dtype == SAGE_BF16;  // factored rows of a bf16 context are rounded to bf16 when they are stored
+    if (row0 == 0) c->nw_half[i] = b && c->d.NP == 512 && c->one_part && split_grams(c) && c->Mt3;
+    else if (!b)
+        if (int rc = widen(c, i); rc != SAGE_OK) return rc;
+    c->nw_bf16[i] = row0 == 0 ? b : (c->nw_bf16[i] && b);
+    return SAGE_OK;
+}
+// (at NP = 512 the kernels that take one part read pieces of bf16)
+bool new_one(const sage_ctx* c, int i) { return c->one_part && c->nw_bf16[i] && (c->d.NP < 512 || c->nw_half[i]); }
 
 // The reduction of a 256- or 512-row eigensolve keeps n / 16 work-groups of one XCD in step, so all of them must be
 // resident together. Contexts are spread over the XCDs; when two share one, their reductions are ordered by an event, so
@@ -361,10 +380,6 @@ hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf
     return e;
 }
 
-bool split_grams(const sage_ctx* c) {
-    return c->mm_mode == SAGE_MM_SPLIT && c->gp_cross_split.tiles > 0 && c->gp_new2_split.tiles > 0;
-}
-
 // The Gram matrix of a buffer of which no block is known, with the split-arithmetic kernels: new x top, new x new and, by
 // the latter's kernel, top x top (the fp32 kernel took 5.8 ms for it at D = 2,049,000, this takes 2.2). The side stream
 // is idle here.
@@ -401,6 +416,7 @@ int decompose(sage_ctx* c, const CoeffArgs& cf) {
                                          c->ew.C, true, c->ew.known, c->d, c->st));
     } else {
         const GramPlan& gp = skip ? c->gp_skip : c->gp;
+        if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
         RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, gp, c->d, c->st));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st));
     }
@@ -418,9 +434,9 @@ int side_ahead(sage_ctx* c, const RowSrc* next) {
     const int LP = c->d.LP, ell = c->d.ell, o = c->cur ^ 1;
     HIPCHK(hipEventRecord(c->ev_mark, c->st));
     HIPCHK(hipStreamWaitEvent(c->st2, c->ev_mark, 0));
-    note_new_rows(c, o, 0, *next);
+    if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
     const int skip = c->ew.local ? c->ew.xcd : -1;
-    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->st2, skip));
+    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, skip));
     c->gp_side_used[o] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
     HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), skip));
     HIPCHK(hipEventRecord(c->ev_side[o], c->st2));
@@ -451,6 +467,7 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
     } else {
         const bool skip = c->top_shrunk && c->gp_skip.t0 > 0;
         const GramPlan& gp = skip ? c->gp_skip : c->gp;
+        if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
         RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial, gp, c->d, c->st));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st));
     }
@@ -754,7 +771,7 @@ static int update_rows(sage_ctx* c, RowSrc g, int64_t rows) {
         if (c->fill_top < ell) {
             // first fill of the buffer: rows go into the top half
             take = (int)((int64_t)(ell - c->fill_top) < rows ? (ell - c->fill_top) : rows);
-            RUN(K_INSERT, insert_rows(g, take, c->fill_top, c->top, LP, c->d, c->st));
+            RUN(K_INSERT, insert_rows(g, take, c->fill_top, c->top, LP, c->d, false, c->st));
             c->fill_top += take;
         } else if (c->pre_stored) {
             // the previous shrink of this call has had these ell rows stored already (side stream)
@@ -763,8 +780,8 @@ static int update_rows(sage_ctx* c, RowSrc g, int64_t rows) {
             c->fill_new = ell;
         } else {
             take = (int)((int64_t)(ell - c->fill_new) < rows ? (ell - c->fill_new) : rows);
-            note_new_rows(c, c->cur, c->fill_new, g);
-            RUN(K_INSERT, insert_rows(g, take, c->fill_new, c->nw[c->cur], LP, c->d, c->st));
+            if (int rc = note_new_rows(c, c->cur, c->fill_new, g); rc != SAGE_OK) return rc;
+            RUN(K_INSERT, insert_rows(g, take, c->fill_new, c->nw[c->cur], LP, c->d, c->nw_half[c->cur], c->st));
             c->fill_new += take;
         }
         c->rows_seen += take;
@@ -867,8 +884,11 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     if (split_rb)
         RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], c->fill_new, c->Mt3, c->Vblk, KP, KP, c->d, c->st,
                                             c->fill_new > 0 && new_one(c, c->cur)));
-    else
+    else {
+        if (c->fill_new > 0)
+            if (int rcw = widen(c, c->cur); rcw != SAGE_OK) return rcw;
         RUN(K_REBUILD, launch_rebuild(c->top, c->nw[c->cur], c->fill_new, c->Mt, c->Vblk, KP, KP, c->d, c->st));
+    }
     c->k = k;
     c->KP = KP;
     rc = finish_basis(c);
@@ -891,6 +911,9 @@ int sage_set_update_arithmetic(sage_ctx* c, int mode) {
     if (mode != SAGE_MM_F32 && mode != SAGE_MM_SPLIT && mode != SAGE_MM_SPLIT_ALL_PARTS) return SAGE_ERR_ARG;
     c->mm_mode = mode == SAGE_MM_F32 ? SAGE_MM_F32 : SAGE_MM_SPLIT;
     c->one_part = mode != SAGE_MM_SPLIT_ALL_PARTS;
+    if (mode != SAGE_MM_SPLIT)
+        for (int i = 0; i < 2; ++i)
+            if (int rc = widen(c, i); rc != SAGE_OK) return rc;
     return SAGE_OK;
 }
 
@@ -1226,6 +1249,8 @@ int sage_fd_sketch_export(sage_ctx* c, float* B_out) {
     int rcf = flush_pending(c);
     if (rcf != SAGE_OK) return rcf;
     const int ell = c->d.ell;
+    if (c->fill_new > 0)
+        if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
     HIPCHK(launch_export_rows(c->top, c->d.LP, ell, B_out, c->d, c->st));
     HIPCHK(launch_export_rows(c->nw[c->cur], c->d.LP, c->fill_new, B_out + (size_t)ell * c->d.D, c->d, c->st));
     if (c->fill_new < ell)
@@ -1285,10 +1310,16 @@ int sage_stats(sage_ctx* c, sage_stats_t* out) {
     double pending = 0.0;
     if (c->cnt_top < c->fill_top || c->cnt_new < c->fill_new) {
         // rows inserted since the last decomposition: add their squared norms from a Gram of the buffer
-        hipError_t e = launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp, c->d, c->st);
-        if (e == hipSuccess)
-            e = launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st);
-        if (e != hipSuccess) return hip_failed(c);
+        hipError_t e = hipSuccess;
+        if (split_grams(c) && !c->new_block_ready && !c->pre_stored) {
+            if (int rc = gram_whole_split(c); rc != SAGE_OK) return rc;
+        } else {
+            if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
+            e = launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp, c->d, c->st);
+            if (e == hipSuccess)
+                e = launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st);
+            if (e != hipSuccess) return hip_failed(c);
+        }
         const int NP = c->d.NP, LP = c->d.LP;
         double* diag = (double*)malloc(sizeof(double) * NP);
         if (!diag) return SAGE_ERR_ALLOC;
@@ -1323,6 +1354,7 @@ int sage_probe_gram_eig(sage_ctx* c, double* C_out, int eig, double* Y_out, doub
     if (!C_out && !eig) return SAGE_OK;
     int rcf = flush_pending(c);
     if (rcf != SAGE_OK) return rcf;
+    if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
     HIPCHK(launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp, c->d, c->st));
     HIPCHK(launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st));
     // Inside the library matrix index LP + j stands for buffer row ell + j; the probe reports buffer-row order

@@ -70,6 +70,13 @@ __device__ __forceinline__ unsigned hi_bf16(float x, float y) {
     return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
 }
 
+// The new half of a bf16 stream at the largest size (256 rows) is kept in bf16: pieces of 8 columns (16 bytes), those of
+// column group q and row r at (q * LP + r), in the upper half of the memory of the fp32 half (so that it can be widened in
+// place). Half the bytes, and a piece is what a matrix-core lane of the Gram kernels takes.
+__host__ __device__ inline const u32x4* half16(const float* half, int LP, int64_t S) {
+    return reinterpret_cast<const u32x4*>(half + S * LP * (DC / 2));
+}
+
 // ---- kernel launchers (each enqueues on `st` and returns hipGetLastError()) ---------------------------------
 // launch_util.hip: raise a kernel's dynamic LDS limit, once per (device, kernel); thread-safe
 hipError_t ensure_dynamic_lds(const void* kernel, int bytes);
@@ -92,12 +99,14 @@ __device__ __forceinline__ int64_t xcd_rank(unsigned block, int skip) {
 inline int64_t xcd_grid(int64_t work, int skip) { return skip < 0 ? work : (work + 6) / 7 * 8; }  // work-groups to launch
 // fd_insert.hip
 // copy `rows` batch rows into rows row0.. of a half buffer (half_rows rows per slab)
+// (to16: in pieces of bf16, see half16; rows of bf16 only)
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         int skip, hipStream_t st);
+                         bool to16, int skip, hipStream_t st);
 // factored rows (E: rows x C logit errors, H: rows x dh features, both of the row type): column c*dh + t = e_c * h_t
 // rounded as a stored row would be, column C*dh + c = e_c; requires D = C * (dh + 1)
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, int skip, hipStream_t st);
+                               float* half, int half_rows, const Dims& d, bool to16, int skip, hipStream_t st);
+hipError_t launch_widen(float* half, const Dims& d, hipStream_t st);  // pieces of bf16 -> the fp32 half
 // ... written out row-major (rows x D of the row type)
 hipError_t launch_expand_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, void* out,
                                const Dims& d, hipStream_t st);
@@ -125,8 +134,8 @@ struct GramPlan {
 // tiles; groups > 0 overrides the group count (tiles = 0 in the result: not available for this sketch size).
 GramPlan gram_plan_split(const GramPlan& base, const Dims& d, int groups);
 GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_per_cu);
-// new_one: every new row in use holds bf16 values (one part instead of three in the split-arithmetic kernels; the
-// result has the same bits)
+// new_one (split-arithmetic kernels): the new half is kept in pieces of bf16 (half16): one part instead of three, the result
+// has the same bits
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
                        hipStream_t st, bool new_one = false, int skip = -1);
 // C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
@@ -201,7 +210,8 @@ hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const fl
 // MP = 128 or 256 (rebuild_split_ok).
 bool rebuild_split_ok(int MP);
 size_t rebuild_split_bytes(const Dims& d, int MP);
-// new_one: as for launch_gram (three products instead of six for the new half).
+// new_one: every new row in use holds bf16 values (three products instead of six for the new half, the same bits); at NP = 512
+// the new half is then kept in pieces of bf16.
 hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
                                 const Dims& d, hipStream_t st, bool new_one = false);
 
