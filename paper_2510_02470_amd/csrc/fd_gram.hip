@@ -4,6 +4,8 @@
 // it is taken through the eigen-decomposition of this Gram matrix. Only the lower triangle is computed, in
 // 64x64 tiles. The long dimension (D) is split over work-group "groups"; each group writes fp32 partial tiles
 // that gram_reduce adds in a fixed order in fp64.
+#include <type_traits>
+
 #include "sage_internal.h"
 
 namespace sage {
@@ -60,16 +62,16 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
     if (s1 > slabs_total) s1 = slabs_total;
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l32 = lane & 31, h = lane >> 5;
 
-    // unit u = 2 * tile + row half
+    // unit u = 2 * tile + row half; dealt to the waves in turn, so that few units are spread evenly
     int arow[3], brow[3];
     bool on[3];
-    const int ubase = (w * 4 + wave) * 3;
+    const int ubase = w * 12 + wave;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        int u = ubase + q;
+        int u = ubase + 4 * q;
         on[q] = u < 2 * tiles;
         int ti = 0, tj = 0;
         if (on[q]) gram_tile(mode, P, t0, u >> 1, ti, tj);
@@ -102,68 +104,89 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
     }
     const f32x4* Tv = reinterpret_cast<const f32x4*>(top);
     const f32x4* Nv = reinterpret_cast<const f32x4*>(nw);
-    f32x4 pre[P];
-    auto fetch = [&](int64_t sl) {
+    // Slabs are requested two stages before they are used: one set of registers goes to LDS while the other fills (with P = 8
+    // there are registers for one set only: one stage).
+    constexpr bool TWO = P < 8;
+    f32x4 pre0[P], pre1[P];
+    auto fetch = [&](int64_t sl, f32x4 (&pre)[P]) __attribute__((always_inline)) {
+        const int64_t sc = sl < s1 ? sl : s1 - 1;  // beyond the end: repeat (never used)
 #pragma unroll
         for (int it = 0; it < P; ++it) {
-            const f32x4* base = (isnew[it] ? Nv : Tv) + sl * HALF4;
+            const f32x4* base = (isnew[it] ? Nv : Tv) + sc * HALF4;
             pre[it] = src[it] >= 0 ? base[src[it]] : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     };
 
     if (s0 < s1) {
-        fetch(s0);
+        fetch(s0, pre0);
+        if constexpr (TWO) fetch(s0 + 1, pre1);
 #pragma unroll
-        for (int it = 0; it < P; ++it) lds[it * 256 + tid] = pre[it];
+        for (int it = 0; it < P; ++it) lds[it * 256 + tid] = pre0[it];
     }
     __syncthreads();
 
-    for (int64_t s = s0; s < s1; ++s) {
-        const int cur = (int)((s - s0) & 1);
-        const bool more = (s + 1 < s1);
-        if (more) fetch(s + 1);
+    auto step = [&](int64_t s, int cur, f32x4 (&next)[P], f32x4 (&far)[P]) __attribute__((always_inline)) {
+        fetch(TWO ? s + 2 : s + 1, far);
         const f32x4* st = lds + cur * STAGE;
         // operands of the whole stage are fetched up front, first the pieces of k-half 0 for every unit, then those of
-        // k-half 1, which land while the matrix cores work on half 0 (units that are switched off read rows that
-        // exist and are simply not written back, so the stage is one straight-line block)
-        f32x4 a[2][3], b[2][3][2];
+        // k-half 1, which land while the matrix cores work on half 0; one straight-line block per number of units
+        auto products = [&](auto nq) __attribute__((always_inline)) {
+            constexpr int NQ = decltype(nq)::value;
+            f32x4 a[2][NQ], b[2][NQ][2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int p = 2 * j + h;
+            for (int j = 0; j < 2; ++j) {
+                const int p = 2 * j + h;
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int ra = arow[q];
-                a[j][q] = st[ra * 4 + (p ^ ((ra >> 2) & 3))];
+                for (int q = 0; q < NQ; ++q) {
+                    const int ra = arow[q];
+                    a[j][q] = st[ra * 4 + (p ^ ((ra >> 2) & 3))];
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb) {
-                    const int rb = brow[q] + cb * 32;
-                    b[j][q][cb] = st[rb * 4 + (p ^ ((rb >> 2) & 3))];
+                    for (int cb = 0; cb < 2; ++cb) {
+                        const int rb = brow[q] + cb * 32;
+                        b[j][q][cb] = st[rb * 4 + (p ^ ((rb >> 2) & 3))];
+                    }
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);  // keep the LDS reads above: the scheduler would sink each next to its use
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                        for (int cb = 0; cb < 2; ++cb) acc[q][cb] = mfma32(a[j][q][c], b[j][q][cb][c], acc[q][cb]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // (wave-uniform; a work-group of a small triangle has no third, second or any unit for some of its waves: carried
+        // along they cost 48 matrix-core instructions a slab where 16 are needed)
+        if (on[2]) products(std::integral_constant<int, 3>{});
+        else if (on[1]) products(std::integral_constant<int, 2>{});
+        else if (on[0]) products(std::integral_constant<int, 1>{});
+        f32x4* nx = lds + (cur ^ 1) * STAGE;
+#pragma unroll
+        for (int it = 0; it < P; ++it) nx[it * 256 + tid] = next[it];
+        // a bare barrier after the LDS traffic: __syncthreads() would also wait for the loads of the slab after next
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    for (int64_t s = s0; s < s1; s += 2) {
+        if constexpr (TWO) {
+            step(s, 0, pre1, pre0);
+            if (s + 1 < s1) step(s + 1, 1, pre0, pre1);
+        } else {
+            step(s, 0, pre0, pre0);
+            if (s + 1 < s1) step(s + 1, 1, pre0, pre0);
         }
-        __builtin_amdgcn_sched_barrier(0);  // keep the LDS reads above: the scheduler would sink each next to its use
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb) acc[q][cb] = mfma32(a[j][q][c], b[j][q][cb][c], acc[q][cb]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (more) {
-            f32x4* nx = lds + (cur ^ 1) * STAGE;
-#pragma unroll
-            for (int it = 0; it < P; ++it) nx[it * 256 + tid] = pre[it];
-        }
-        __syncthreads();
     }
 
     // partial[group][tile - t0][64 x 64]; unit u covers rows (u & 1) * 32 .. + 32 of tile t0 + u / 2
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         if (!on[q]) continue;
-        const int u = ubase + q;
+        const int u = ubase + 4 * q;
         float* out = partial + ((int64_t)group * tiles + (u >> 1)) * 4096 + (u & 1) * 2048;
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb)
@@ -799,38 +822,53 @@ __device__ __forceinline__ int gram_src_index(const GramSrc& g, int P, int t, in
     if (g.mode == 3) return ti < q ? t : -1;
     return (ti >= q && tj >= q) ? (ti - q) * (ti - q + 1) / 2 + (tj - q) : -1;
 }
+// SEG threads share an element's groups (in runs, added in order afterwards): with one thread each, a loop over hundreds of
+// groups with eight loads in flight, the kernel took 22 to 25 us after the launches that fill the chip.
+template <int SEG>
 __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, GramSrc top, double* __restrict__ C, int NP,
                                                           int known_top, const double* __restrict__ known) {
+    constexpr int EL = 256 / SEG;  // elements of a work-group
+    __shared__ double part[SEG > 1 ? SEG : 1][EL];
     const int P = NP / 64;
-    int t = blockIdx.x;
-    int e = blockIdx.y * 256 + threadIdx.x;  // 0..4095
+    const int t = blockIdx.x;
+    const int el = threadIdx.x % EL, seg = threadIdx.x / EL;
+    const int e = blockIdx.y * EL + el;  // 0..4095
     int ti, tj;
     tile_coords(t, ti, tj);
-    int r = e >> 6, c = e & 63;
-    if (ti == tj && c > r) return;  // the diagonal tiles hold both triangles; keep one
-    int gr = ti * 64 + r, gc = tj * 64 + c;
+    const int r = e >> 6, c = e & 63;
+    const int gr = ti * 64 + r, gc = tj * 64 + c;
+    const bool diag = known_top && ti < (P >> 1);
     double s = 0.0;
-    if (known_top && ti < (P >> 1)) {
-        s = gr == gc ? known[gr] : 0.0;
-    } else {
-        int ia = gram_src_index(a, P, t, ti, tj);
+    if (!diag) {
+        const int ia = gram_src_index(a, P, t, ti, tj);
         const int ib = gram_src_index(b, P, t, ti, tj);
         const GramSrc& g = ia >= 0 ? a : (ib >= 0 ? b : top);
         const int idx = ia >= 0 ? ia : (ib >= 0 ? ib : gram_src_index(top, P, t, ti, tj));
         if (idx >= 0) {
             const float* p0 = g.partial + (int64_t)idx * 4096 + e;
             const int64_t gstride = (int64_t)g.tiles * 4096;
-            int k = 0;
-            for (; k + 8 <= g.groups; k += 8) {  // eight loads in flight, added in group order
+            const int per = (g.groups + SEG - 1) / SEG;
+            int k = seg * per;
+            const int k1 = k + per < g.groups ? k + per : g.groups;
+            for (; k + 8 <= k1; k += 8) {  // eight loads in flight, added in group order
                 float v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = p0[(k + u) * gstride];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) s += (double)v[u];
             }
-            for (; k < g.groups; ++k) s += (double)p0[k * gstride];
+            for (; k < k1; ++k) s += (double)p0[k * gstride];
         }
     }
+    if constexpr (SEG > 1) {
+        part[seg][el] = s;
+        __syncthreads();
+        if (seg > 0) return;
+#pragma unroll
+        for (int q = 1; q < SEG; ++q) s += part[q][el];
+    }
+    if (ti == tj && c > r) return;  // the diagonal tiles hold both triangles; keep one
+    if (diag) s = gr == gc ? known[gr] : 0.0;
     C[(int64_t)gr * NP + gc] = s;
     C[(int64_t)gc * NP + gr] = s;
 }
@@ -963,8 +1001,12 @@ hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const f
     GramSrc sa{partial_a, a.mode, a.t0, a.tiles, a.groups};
     GramSrc sb{partial_b, b ? b->mode : 0, b ? b->t0 : 0, b ? b->tiles : 0, b ? b->groups : 0};
     GramSrc stop{partial_top, top ? 3 : 0, 0, top ? top->tiles : 0, top ? top->groups : 0};
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3(P * (P + 1) / 2, 16), dim3(256), 0, st, sa, sb, stop, C, d.NP, known_top ? 1 : 0,
-                       known);
+    if (sa.groups >= 64)
+        hipLaunchKernelGGL(gram_reduce_kernel<8>, dim3(P * (P + 1) / 2, 128), dim3(256), 0, st, sa, sb, stop, C, d.NP,
+                           known_top ? 1 : 0, known);
+    else
+        hipLaunchKernelGGL(gram_reduce_kernel<1>, dim3(P * (P + 1) / 2, 16), dim3(256), 0, st, sa, sb, stop, C, d.NP,
+                           known_top ? 1 : 0, known);
     return hipGetLastError();
 }
 

@@ -241,11 +241,30 @@ struct OuterRows {
 #pragma unroll
                 for (int w = 0; w < 4; ++w)
                     v[i][w] = pack_bf16(s * __uint_as_float(v[i][w] << 16), s * __uint_as_float(v[i][w] & 0xffff0000u));
-            } else {
+            }
+        }
+        // pieces across a class boundary or among the bias columns, by a loop that is not unrolled: with the divisions of 64
+        // columns in line the kernel had 194 registers and too few waves in flight (853 us for 256 rows of 1000 x 2049)
+        bool all = true;
 #pragma unroll
-                for (int w = 0; w < 4; ++w)  // (outer_value's are bf16 values already)
-                    v[i][w] = hi_bf16(outer_value(e, h, d0 + 32 * i + 2 * w, main, dh, D),
-                                      outer_value(e, h, d0 + 32 * i + 2 * w + 1, main, dh, D));
+        for (int i = 0; i < NS; ++i) all = all && fast[i];
+        if (!all) {
+#pragma unroll 1
+            for (int i = 0; i < NS; ++i) {
+                bool todo = false;
+#pragma unroll
+                for (int q = 0; q < NS; ++q) todo = q == i ? !fast[q] : todo;
+                if (!todo) continue;
+                unsigned w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll 1
+                for (int c = 0; c < 8; ++c) {  // (outer_value's are bf16 values already)
+                    const unsigned x = __float_as_uint(outer_value(e, h, d0 + 32 * i + c, main, dh, D)) >> 16;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) w[q] |= (c >> 1) == q ? x << (16 * (c & 1)) : 0u;
+                }
+#pragma unroll
+                for (int q = 0; q < NS; ++q)
+                    if (q == i) v[q] = u32x4{w[0], w[1], w[2], w[3]};
             }
         }
     }

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_kernel(const float* top, const
     float bpre[8];
     f32x4 mpre[PERC];
     // prologue: coefficients of stages 0 and 1 into LDS, row operand of stage 0 on its way
-    const int nstage = NP / 16;
+    const int nstage = (LP + (nfill + 15) / 16 * 16) / 16;  // no stage without rows in use
     fetch_b(0, bpre);
 #pragma unroll
     for (int u = 0; u < PERC; ++u)
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
     // writes (out may be top: top and out are the same memory then, hence not declared restrict)
     const float* tcol = (live ? top : nw) + coff;
     const float* ncol = nw + coff;
-    const int nstage = NP / 16;
+    const int nstage = (LP + (nfill + 15) / 16 * 16) / 16;  // no stage without rows in use (a basis right after a shrink: half)
     constexpr bool HALF = NPT == 512;
     const float* hcol = HALF ? reinterpret_cast<const float*>(half16(nw, LP, Dp / DC) + (dc / 8) * LP + h) + (dc % 8) / 2 : nw;
     const unsigned pick = HALF && !(dc & 1) ? 0x05040100u : 0x07060302u;  // lower or upper halves of two words
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
         const int sg = stg < nstage ? stg : nstage - 1;  // beyond the end: repeat (never used)
         const int r0 = sg * 16;
         if constexpr (decltype(from_half)::value) {
-            const float* bn = hcol + (r0 - LP) * 4;
+            const float* bn = hcol + (r0 > LP ? r0 - LP : 0) * 4;
 #pragma unroll
             for (int s = 0; s < 8; ++s) b[s] = bn[2 * s * 4];
         } else {
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
         stage(all_parts, fp32, b0, b2, S1 - 3, 0);
         stage(all_parts, halves, b1, b0, S1 - 2, 1);
         stage(all_parts, halves, b2, b1, S1 - 1, 2);
-        triples(one_part, halves, S1, 2 * S1);
+        triples(one_part, halves, S1, nstage);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS when the work-group ends
 
@@ -386,6 +386,7 @@ static hipError_t launch_rebuild_split_t(const float* top, const float* nw, int 
 
 hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
                                 const Dims& d, hipStream_t st, bool new_one) {
+    if (nfill == 0) new_one = false;  // (no stages of the new half)
     if (MP == 256 && new_one && d.NP == 512) return launch_rebuild_split_t<8, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);
     if (MP == 256) return launch_rebuild_split_t<8, 0>(top, nw, nfill, Mc3, out, out_NP, d, st);
     if (MP == 128 && new_one && d.NP == 512) return launch_rebuild_split_t<4, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);

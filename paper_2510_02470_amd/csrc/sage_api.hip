@@ -244,6 +244,12 @@ hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int
     return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, to16, skip, st);
 }
 
+// Before the top half is read while the stream has not filled it yet: its other rows count as zero.
+int clear_top(sage_ctx* c) {
+    if (c->fill_top < c->d.ell) HIPCHK(launch_zero_rows(c->top, c->d.LP, c->fill_top, c->d.ell, c->d, c->st));
+    return SAGE_OK;
+}
+
 bool split_grams(const sage_ctx* c) {
     return c->mm_mode == SAGE_MM_SPLIT && c->gp_cross_split.tiles > 0 && c->gp_new2_split.tiles > 0;
 }
@@ -397,6 +403,7 @@ int gram_whole_split(sage_ctx* c) {
 // Gram + eigensolve of the buffer as it stands, and the coefficients of a basis. After a shrink the Gram matrix of the top rows
 // is known (diagonal lambda_j - delta, recorded by the shrink), so their block is not recomputed.
 int decompose(sage_ctx* c, const CoeffArgs& cf) {
+    if (int rc = clear_top(c); rc != SAGE_OK) return rc;
     const bool skip = c->top_shrunk && c->gp_skip.t0 > 0;
     if (skip && c->fill_new == 0) {
         // only the rows the last shrink wrote are there: nothing to compute
@@ -719,8 +726,9 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
     CALLOC(c->acc, 8 * sizeof(double));
 #undef CALLOC
-    // only the top half must start as zeros: rows of a new half beyond its fill are never read
-    if (hipMemsetAsync(c->top, 0, hbytes, c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
+    // Rows of the top half that the stream never fills are zero. (Those it has not filled yet are cleared when something
+    // looks at them, see clear_top; rows of a new half beyond its fill are never used.)
+    if (ell < c->d.LP && launch_zero_rows(c->top, c->d.LP, ell, c->d.LP, c->d, c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->acc, 0, 8 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->ew.stat, 0, 32 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->ew.xch, 0, (size_t)4 * NP * sizeof(u32x4), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
@@ -1249,6 +1257,7 @@ int sage_fd_sketch_export(sage_ctx* c, float* B_out) {
     int rcf = flush_pending(c);
     if (rcf != SAGE_OK) return rcf;
     const int ell = c->d.ell;
+    if (int rc = clear_top(c); rc != SAGE_OK) return rc;
     if (c->fill_new > 0)
         if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
     HIPCHK(launch_export_rows(c->top, c->d.LP, ell, B_out, c->d, c->st));
@@ -1311,6 +1320,7 @@ int sage_stats(sage_ctx* c, sage_stats_t* out) {
     if (c->cnt_top < c->fill_top || c->cnt_new < c->fill_new) {
         // rows inserted since the last decomposition: add their squared norms from a Gram of the buffer
         hipError_t e = hipSuccess;
+        if (int rc = clear_top(c); rc != SAGE_OK) return rc;
         if (split_grams(c) && !c->new_block_ready && !c->pre_stored) {
             if (int rc = gram_whole_split(c); rc != SAGE_OK) return rc;
         } else {
@@ -1354,6 +1364,7 @@ int sage_probe_gram_eig(sage_ctx* c, double* C_out, int eig, double* Y_out, doub
     if (!C_out && !eig) return SAGE_OK;
     int rcf = flush_pending(c);
     if (rcf != SAGE_OK) return rcf;
+    if (int rc = clear_top(c); rc != SAGE_OK) return rc;
     if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
     HIPCHK(launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp, c->d, c->st));
     HIPCHK(launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st));
@@ -1378,6 +1389,7 @@ int sage_probe_gram_split(sage_ctx* c, double* C_out, int* n_pad) {
     int rcf = flush_pending(c);
     if (rcf != SAGE_OK) return rcf;
     if (c->new_block_ready || c->pre_stored) return SAGE_ERR_STATE;  // (never after flush_pending)
+    if (int rc = clear_top(c); rc != SAGE_OK) return rc;
     const bool one = c->fill_new > 0 && new_one(c, c->cur);
     HIPCHK(launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
     HIPCHK(launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial_new[c->cur], c->gp_new2_split, c->d, c->st, one));
