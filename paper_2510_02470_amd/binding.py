@@ -135,6 +135,11 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr()) if t is not None and t.numel() > 0 else C.c_void_p(0)
 
 
+def _stream(torch):
+    """torch's current stream on the current device (without the wrapper objects, which cost as much as a launch)."""
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+
+
 class Sage:
     """One sketch context on the current device and torch's current stream."""
 
@@ -365,10 +370,10 @@ def topm(alpha, m):
     import torch
 
     assert alpha.is_cuda and alpha.dtype == torch.float32 and alpha.is_contiguous()
-    out = torch.empty(max(int(m), 1), dtype=torch.int64, device="cuda")
-    stream = torch.cuda.current_stream().cuda_stream
-    _check(lib().sage_topm(_ptr(alpha), alpha.numel(), int(m), _ptr(out), C.c_void_p(stream)), "sage_topm")
-    return out[: int(m)]
+    m = int(m)
+    out = torch.empty(max(m, 1), dtype=torch.int64, device="cuda")
+    _check(lib().sage_topm(_ptr(alpha), alpha.numel(), m, _ptr(out), _stream(torch)), "sage_topm")
+    return out if m > 0 else out[:0]
 
 
 TOPM_STATIC_MAX_N = 16777216  # SAGE_TOPM_STATIC_MAX_N
@@ -379,8 +384,7 @@ def topm_static(alpha, m, out):
     import torch
 
     assert alpha.is_cuda and alpha.dtype == torch.float32 and alpha.is_contiguous()
-    assert out.is_cuda and out.dtype == torch.int64 and out.is_contiguous() and out.numel() >= int(m)
-    stream = torch.cuda.current_stream().cuda_stream
-    _check(lib().sage_topm_static(_ptr(alpha), alpha.numel(), int(m), _ptr(out), C.c_void_p(stream)),
-           "sage_topm_static")
-    return out[: int(m)]
+    m = int(m)
+    assert out.is_cuda and out.dtype == torch.int64 and out.is_contiguous() and out.numel() >= m
+    _check(lib().sage_topm_static(_ptr(alpha), alpha.numel(), m, _ptr(out), _stream(torch)), "sage_topm_static")
+    return out[:m]

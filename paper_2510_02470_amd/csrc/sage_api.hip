@@ -3,6 +3,7 @@
 #include <new>
 #include <stdlib.h>
 #include <string.h>
+#include <chrono>
 #include <mutex>
 #include <type_traits>
 #include <unistd.h>
@@ -25,7 +26,8 @@ enum { K_GRAM = 0, K_REDUCE, K_EIG, K_COEFF, K_REBUILD, K_INSERT, K_PROJECT, K_F
 struct SideKit {
     hipStream_t stream = nullptr;
     hipEvent_t mark = nullptr, side[2] = {nullptr, nullptr};
-    int* host = nullptr;  // pinned words: [0] a solve failed, [1], [2] report of the class-balanced selection
+    int* host = nullptr;  // pinned words: [0] a solve failed, [1], [2] report of the class-balanced selection, [16] signal
+    unsigned token = 0;   // of the last signal
 };
 
 // Where device memory comes from (sage_set_allocator); a context keeps the pair it was created with.
@@ -182,6 +184,49 @@ void dev_free(const Allocator& m, void* p) {
         (ptr) = nullptr;                \
     } while (0)
 
+// The end of the work that sets `done`: a short spin on the host's word, then (the stream has much to do before it, or
+// something failed) the runtime's own wait.
+hipError_t wait_signal(const HostSignal& done, hipStream_t st) {
+    using clock = std::chrono::steady_clock;
+    const auto until = clock::now() + std::chrono::microseconds(500);
+    do {
+        for (int i = 0; i < 64; ++i) {
+            if (__atomic_load_n(done.word, __ATOMIC_ACQUIRE) == done.token) return hipSuccess;
+            __builtin_ia32_pause();
+        }
+    } while (clock::now() < until);
+    return hipStreamSynchronize(st);
+}
+
+// Words for calls without a context: one pinned page for the process, at most 32 calls at a time (the others use the
+// runtime's wait).
+struct SignalPage {
+    std::mutex lock;
+    unsigned* words = nullptr;
+    unsigned used = 0, token = 0;
+    bool failed = false;
+} g_signals;
+bool signal_take(HostSignal& s) {
+    std::lock_guard<std::mutex> hold(g_signals.lock);
+    if (!g_signals.words && !g_signals.failed) {
+        g_signals.failed = hipHostMalloc((void**)&g_signals.words, 32 * 64, hipHostMallocPortable) != hipSuccess;
+        if (g_signals.failed) (void)hipGetLastError();
+        else memset(g_signals.words, 0, 32 * 64);
+    }
+    if (g_signals.failed || g_signals.used == 0xFFFFFFFFu) return false;
+    const int i = __builtin_ctz(~g_signals.used);
+    g_signals.used |= 1u << i;
+    s.word = g_signals.words + 16 * i;  // a line of its own
+    s.token = ++g_signals.token;
+    if (s.token == 0) s.token = ++g_signals.token;
+    return true;
+}
+void signal_give(const HostSignal& s) {
+    if (!s.word) return;
+    std::lock_guard<std::mutex> hold(g_signals.lock);
+    g_signals.used &= ~(1u << ((s.word - g_signals.words) / 16));
+}
+
 // run a launcher, optionally bracketed by events of kernel class `cls`
 template <typename F>
 int run(sage_ctx* c, int cls, F&& f) {
@@ -263,6 +308,14 @@ int widen(sage_ctx* c, int i) {
     return SAGE_OK;
 }
 
+HostSignal next_signal(sage_ctx* c) {
+    HostSignal s;
+    s.word = (unsigned*)c->kit.host + 16;
+    s.token = ++c->kit.token;
+    if (s.token == 0) s.token = ++c->kit.token;
+    return s;
+}
+
 // Rows of `s` are about to be stored in nw[i] from row row0 on (by the context stream unless row0 = 0).
 int note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
     const bool b = s.dtype == SAGE_BF16;  // factored rows of a bf16 context are rounded to bf16 when they are stored
@@ -314,7 +367,7 @@ bool kit_take(int device, SideKit& k) {
     bool ok = hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking) == hipSuccess;
     for (hipEvent_t* e : {&k.mark, &k.side[0], &k.side[1]})
         ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipHostMalloc((void**)&k.host, 4 * sizeof(int), hipHostMallocDefault) == hipSuccess;
+    ok = ok && hipHostMalloc((void**)&k.host, 32 * sizeof(int), hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         kit_destroy(k);
@@ -1181,8 +1234,9 @@ int sage_select(sage_ctx* c, double keep_rate, int64_t* out_idx, int64_t cap, in
     }
     if (c->store_zhat) RUN(K_SELECT, launch_cosine(c->zhat, N, c->k, c->ssum, c->alpha, c->st));
     c->alpha_n = N;
-    RUN(K_SELECT, launch_topm(c->alpha, N, m, out_idx, c->sw, c->st));
-    HIPCHK(hipStreamSynchronize(c->st));
+    const HostSignal done = next_signal(c);
+    RUN(K_SELECT, launch_topm(c->alpha, N, m, out_idx, c->sw, c->st, done));
+    HIPCHK(topm_signals(N, m) ? wait_signal(done, c->st) : hipStreamSynchronize(c->st));
     return SAGE_OK;
 }
 
@@ -1243,8 +1297,11 @@ int sage_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* 
         if (!dev_alloc(mem, st, &p, select_work_bytes(N))) return SAGE_ERR_ALLOC;
         w = select_work_layout(p, N);
     }
-    hipError_t e = launch_topm(alpha, N, m, out_idx, w, st);
-    hipError_t e2 = hipStreamSynchronize(st);
+    HostSignal done;
+    if (topm_signals(N, m)) (void)signal_take(done);
+    hipError_t e = launch_topm(alpha, N, m, out_idx, w, st, done);
+    hipError_t e2 = e == hipSuccess && done.word ? wait_signal(done, st) : hipStreamSynchronize(st);
+    signal_give(done);
     dev_free(mem, w.hist);
     if (e == hipSuccess && e2 == hipSuccess) return SAGE_OK;
     (void)hipGetLastError();
@@ -1291,6 +1348,12 @@ int sage_scores_export(sage_ctx* c, float* alpha_out) {
     ALIVE(c);
     if ((!alpha_out && c->n_scored > 0)) return SAGE_ERR_ARG;
     if (!c->has_basis || c->alpha_n != c->n_scored) return SAGE_ERR_STATE;
+    if (c->alpha_n > 0 && c->alpha_n <= COPY_SIGNAL_MAX) {
+        const HostSignal done = next_signal(c);
+        HIPCHK(launch_copy_signal(c->alpha, (int)c->alpha_n, alpha_out, done, c->st));
+        HIPCHK(wait_signal(done, c->st));
+        return SAGE_OK;
+    }
     if (c->alpha_n > 0)
         HIPCHK(hipMemcpyAsync(alpha_out, c->alpha, (size_t)c->alpha_n * sizeof(float), hipMemcpyDeviceToDevice, c->st));
     HIPCHK(hipStreamSynchronize(c->st));

@@ -268,8 +268,17 @@ struct SelectWork {
 constexpr int TOPM_HIST_WORDS = 4096 + 2 * 1024;
 constexpr int SELECT_BLOCK = 4096;  // keys per block in the compaction passes
 bool topm_needs_work(int64_t N);    // false: launch_topm uses no work space
+// A word of pinned host memory that the last kernel of a call sets to `token` once the call's results are in memory, for a
+// host that spins on it: 6.5 us from launch to answer where hipStreamSynchronize takes 11.5. null: no signal.
+struct HostSignal {
+    unsigned* word = nullptr;
+    unsigned token = 0;
+};
+bool topm_signals(int64_t N, int64_t m);  // launch_topm sets the word
 hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w,
-                       hipStream_t st);
+                       hipStream_t st, HostSignal done = HostSignal{});
+constexpr int COPY_SIGNAL_MAX = 32768;  // floats: 32 a thread of the one work-group; more is the copy engine's work
+hipError_t launch_copy_signal(const float* src, int n, float* dst, HostSignal done, hipStream_t st);
 
 // select_cb.hip: class-balanced selection (per-class centroid, cosine to it, top k_c of every class)
 struct CbWork {

@@ -58,7 +58,7 @@ constexpr int TOPM_T = 1024;  // threads of every kernel below
 // one work-group, N <= 1024 C
 template <int C>
 __global__ __launch_bounds__(TOPM_T) void topm_one_kernel(const float* __restrict__ alpha, int N, uint32_t m,
-                                                          int64_t* __restrict__ out_idx) {
+                                                          int64_t* __restrict__ out_idx, HostSignal done) {
     static_assert(C <= 32, "emit_keys packs counts of 16 bits");
     __shared__ uint32_t h[BINS1 + 2 * BINS2];
     __shared__ uint32_t cnt[16 * C], tot[16];
@@ -90,6 +90,7 @@ __global__ __launch_bounds__(TOPM_T) void topm_one_kernel(const float* __restric
     __syncthreads();
     pick_bin<TOPM_T, BINS2>(h + BINS1 + BINS2, rest, pw, d3, rest);
     emit_keys<TOPM_T, C>(key, 0, (p2 << 10) | d3, rest, 0u, 0u, cnt, tot, out_idx);
+    signal_host(done);
 }
 
 // hist: BINS1 + 2 BINS2 words
@@ -217,14 +218,27 @@ __global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restri
 // One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of six launches wins.
 constexpr int64_t TOPM_ONE = 32 * TOPM_T;
 
+// Small copies for a caller that waits: one work-group, then the signal.
+__global__ __launch_bounds__(TOPM_T) void copy_signal_kernel(const float* __restrict__ src, int n, float* __restrict__ dst,
+                                                             HostSignal done) {
+    for (int i = threadIdx.x; i < n; i += TOPM_T) dst[i] = src[i];
+    signal_host(done);
+}
+hipError_t launch_copy_signal(const float* src, int n, float* dst, HostSignal done, hipStream_t st) {
+    hipLaunchKernelGGL(copy_signal_kernel, dim3(1), dim3(TOPM_T), 0, st, src, n, dst, done);
+    return hipGetLastError();
+}
+
 bool topm_needs_work(int64_t N) { return N > TOPM_ONE; }
 
+bool topm_signals(int64_t N, int64_t m) { return m > 0 && N > 0 && N <= TOPM_ONE; }
+
 hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w,
-                       hipStream_t st) {
+                       hipStream_t st, HostSignal done) {
     if (m <= 0 || N <= 0) return hipSuccess;
     if (N <= TOPM_ONE) {
 #define SAGE_ONE(C) \
-    hipLaunchKernelGGL(topm_one_kernel<C>, dim3(1), dim3(TOPM_T), 0, st, alpha, (int)N, (uint32_t)m, out_idx)
+    hipLaunchKernelGGL(topm_one_kernel<C>, dim3(1), dim3(TOPM_T), 0, st, alpha, (int)N, (uint32_t)m, out_idx, done)
         if (N <= 2 * TOPM_T) SAGE_ONE(2);
         else if (N <= 4 * TOPM_T) SAGE_ONE(4);
         else if (N <= 8 * TOPM_T) SAGE_ONE(8);

@@ -101,4 +101,16 @@ __device__ __forceinline__ void emit_keys(const uint32_t (&key)[C], int64_t base
     }
 }
 
+// Called by every thread at the end of a kernel of ONE work-group: its stores are made visible to the whole system, then the
+// host's word is set.
+__device__ __forceinline__ void signal_host(const HostSignal& done) {
+    if (!done.word) return;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence_system();
+        __hip_atomic_store(done.word, done.token, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 }  // namespace sage

@@ -76,3 +76,42 @@ def test_projection_of_rows_of_any_alignment(dtype, D, k):
     assert ((got[:n] - Z / norm).abs() * norm / scale).max() <= 3e-7
     assert (got[n] - got[0]).abs().max() <= 1e-4  # (an aligned start may take the two-part basis)
     s.close()
+
+
+# the answer's signal: more callers than words, and the largest export that one work-group copies
+def test_topm_from_many_threads():
+    from concurrent.futures import ThreadPoolExecutor
+
+    import torch
+
+    from paper_2510_02470_amd.binding import topm
+
+    def calls(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            a = np.random.default_rng(i).standard_normal(500 + 37 * i).astype(np.float32)
+            ad = torch.from_numpy(a).cuda()
+            return all(topm(ad, m).cpu().tolist() == oracle.topm_f32(a, m).tolist() for m in (1, 7, 200, 499))
+
+    with ThreadPoolExecutor(40) as pool:
+        assert all(pool.map(calls, range(80)))
+
+
+@pytest.mark.parametrize("N", [1, 1025, 32_768, 32_769])
+def test_scores_export_at_the_edges_of_its_variants(N):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    rng = np.random.default_rng(N)
+    V, G = rng.standard_normal((2, 8)).astype(np.float32), (0.3 + rng.standard_normal((N, 8))).astype(np.float32)
+    s = Sage(4, 8)
+    s.set_basis(torch.from_numpy(V).cuda())
+    s.score(torch.from_numpy(G).cuda())
+    idx = s.select(0.5).cpu().numpy()
+    alpha = s.scores().cpu().numpy()
+    z = G.astype(np.float64) @ V.T.astype(np.float64)
+    z /= np.linalg.norm(z, axis=1, keepdims=True)
+    u = z.sum(0)
+    np.testing.assert_allclose(alpha, z @ (u / np.linalg.norm(u)), atol=2e-5)
+    assert idx.tolist() == oracle.topm_f32(alpha, len(idx)).tolist()
+    s.close()
