@@ -167,7 +167,7 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
 // 512 threads: 8 lanes per index, a sub-problem of M rows per 8 M threads. All arrays of the block in LDS; Q column-major.
 // A merge is a chain of short phases between barriers; half the time goes into the roots, which is why their loops are
 // unrolled to what M needs, and the products of 16 rows and more run on the matrix cores (in scalar code, bound by LDS
-// reads, the last product alone took 17 us). 45 us in all against 104 us for one loop over all sizes.
+// reads, the last product alone took 17 us). 37 us in all against 104 us for one loop over all sizes.
 constexpr int DCB_LD = 65;   // columns of Q
 constexpr int DCB_LDU = 68;  // columns of U: the 16 columns x 4 rows of a matrix-core operand fall on distinct banks
 struct DcBlockLds {

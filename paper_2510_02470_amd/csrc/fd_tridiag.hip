@@ -6,11 +6,12 @@
 // update of it, 2 flop per byte touched), so it is bound by the latency of a step, not by arithmetic. The matrix
 // therefore never leaves the registers: the work-groups own columns of the (symmetric) matrix, a wave's lanes the rows
 // lane, lane + 64, ..., and the rank-2 update of a step is applied in the same pass as the next step's product.
-//   n = 64, 128:  one work-group of 4 waves; the only exchange of a step goes through LDS (tri_one_kernel).
-//   n = 256, 512: n / 16 work-groups of 4 waves, one per CU of ONE XCD, which exchange two n-vectors per step through
-//                 the L2 they share (tri_many_kernel).
-// Every wave carries the vectors of the step (column, reflector, product) redundantly, so a step has one exchange and
-// no other synchronisation.
+//   n = 64:            one work-group; the exchanges of a step go through LDS (tri_one_kernel, 0.7 us a step).
+//   n = 128, 256, 512: 16, 16, 32 work-groups, one per CU of ONE XCD, which exchange two n-vectors per step through the L2
+//                      they share (tri_many_kernel, 0.9, 1.04, 1.45 us a step; every wave carries the vectors of the
+//                      step redundantly, so a step has one exchange and no other synchronisation).
+// One work-group issues the instructions of a 128-row reduction in 155 us, 16 of them take 116, so the exchange pays from there
+// on; where the work-groups cannot be relied on to share an XCD, 128 rows stay with one work-group.
 #include <mutex>
 #include <type_traits>
 
@@ -277,15 +278,15 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
     }
 }
 
-// ---- n = 64 J, J = 4, 8: n / 16 work-groups on one XCD ------------------------------------------------------------
-// As above, but a wave owns 4 whole columns, carries all vectors itself and sums its products over the lanes, and q and c go through the L2 the
-// work-groups share. An exchanged value is a 16-byte entry {low word, tag, high word, tag}; the tag (solve number and step)
+// ---- n = 64 J, J = 2, 4, 8: 16, 16 or 32 work-groups on one XCD ---------------------------------------------------
+// As above, but a wave owns 2 (n = 128) or 4 whole columns, carries all vectors itself and sums its products over the
+// lanes, and q and c go through the L2 the work-groups share. An exchanged value is a 16-byte entry {low word, tag, high word, tag}; the tag (solve number and step)
 // makes each 8-byte half carry its own validity, so there are no flags, no fences and nothing to clear: a reader polls an
 // entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough: once a
 // work-group has all of step k + 1, everyone has finished reading step k.
 // Stores: the L1 is write-through, so a plain store reaches the XCD's L2 (local = 1). Where the work-groups cannot be
 // relied on to sit on one XCD (launch_tridiag checks the mapping once) they are device-scope stores instead, which go on
-// to memory: 3.4 us per step instead of 1.9 us at n = 512.
+// to memory, which takes about twice as long a step.
 // Waves 0..3 compute and publish, waves 4..7 only poll and hand over through LDS: loads and stores of a wave retire in
 // order, so one that did both would wait, with every poll, for its own stores. They wait for c first, which is out before
 // the products are formed, then for q: a poll of one vector takes 550 cycles, of both 830.

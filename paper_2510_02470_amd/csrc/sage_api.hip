@@ -328,7 +328,7 @@ int note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
 // (at NP = 512 the kernels that take one part read pieces of bf16)
 bool new_one(const sage_ctx* c, int i) { return c->one_part && c->nw_bf16[i] && (c->d.NP < 512 || c->nw_half[i]); }
 
-// The reduction of a 256- or 512-row eigensolve keeps n / 16 work-groups of one XCD in step, so all of them must be
+// The reduction of a 128-, 256- or 512-row eigensolve keeps 16 or 32 work-groups of one XCD in step, so all of them must be
 // resident together. Contexts are spread over the XCDs; when two share one, their reductions are ordered by an event, so
 // that at most two (one launched before the second context appeared, one in the chain) are ever in flight on an XCD, and
 // two fit on its CUs side by side.
