@@ -208,7 +208,8 @@ def run_workload(torch, inputs, Sage, w, K, W, split=True, labels_classes=None, 
             "gram": ("mfma", gram_tiles * tile_flop, mm_peak_g, gram_products if split_gram else 1.0),
             "rebuild": ("mfma", rebuild_flop, mm_peak_r, rebuild_products if split_rebuild else 1.0),
             "project": ("hbm", w.batch * (esz * D + 4.0 * k) + 4.0 * k * D, PEAK_HBM, 1.0),
-            "insert": ("hbm", (esz + 4.0) * ell * D, PEAK_HBM, 1.0),
+            # (rows of a bf16 stream stay bf16 in the new half of a 512-row buffer under the split arithmetic)
+            "insert": ("hbm", (esz + (esz if one_part and split_gram else 4.0)) * ell * D, PEAK_HBM, 1.0),
         }
         s = Sage(ell, D, dtype=w.dtype, max_rows=(W + K) * w.batch)
         s.set_update_arithmetic(split)
