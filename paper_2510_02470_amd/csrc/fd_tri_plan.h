@@ -1,0 +1,45 @@
+// Who does what in a reduction by several work-groups (tri_many_kernel). Plain integer functions, so that the protocol can be
+// checked without a GPU (tests/tri_plan_check.cc).
+//
+// Step k of the reduction of n rows exchanges q and c at the rows above k: entry q[i] comes from the wave that owns column i,
+// all of c from the one that owns column k + 1. So a work-group has something to publish in the steps below its last column,
+// and it needs the entries of a step only to make those of the next. It leaves after its last entry; one without a column
+// below n has no part in the solve. Nobody then waits for a slot that others no longer wait for it to have read: slot
+// k & 1 is written again in step k + 2, by work-groups that have all of step k + 1, to which every reader of step k that is
+// not done contributed after it had read step k.
+#pragma once
+
+namespace sage {
+
+template <int J>
+struct TriPlan {
+    static constexpr int N = 64 * J;
+    static constexpr int CW = J >= 4 ? 4 : 2;   // columns of a wave
+    static constexpr int NW = N / CW;           // waves that hold columns
+    static constexpr int NWG = NW / 4;          // work-groups
+    static constexpr int ST = J / CW;           // columns of a wave are 64 ST apart
+
+    static constexpr int column(int wave, int s) { return (wave & 63) + 64 * ((wave >> 6) + ST * s); }
+    static constexpr int wave_of(int col) { return (col & 63) + 64 * ((col >> 6) & (ST - 1)); }
+
+    // of work-group wg, among the first n columns; -1: none
+    static constexpr int last_column(int wg, int n) {
+        int last = -1;
+        for (int s = 0; s < CW; ++s) {
+            const int first = column(4 * wg, s);  // its four waves own four neighbours
+            if (first < n) last = first + 3 < n ? first + 3 : n - 1;
+        }
+        return last;
+    }
+    // It takes part in steps 0 .. steps - 1 and waits for the entries of steps 0 .. waits - 1. The work-group of the last
+    // column goes on to the end: it alone is left in step n - 2, reads its own entries of it, and knows the last diagonal element.
+    static constexpr int steps(int wg, int n) { return last_column(wg, n) > 0 ? last_column(wg, n) : 0; }
+    static constexpr int waits(int wg, int n) {
+        return last_column(wg, n) == n - 1 ? n - 1 : (steps(wg, n) > 0 ? steps(wg, n) - 1 : 0);
+    }
+    // The wave that stores the reflector of step k: one that is still there, two work-groups on from the one that has c
+    // to publish.
+    static constexpr int storing_wave(int k, int n) { return wave_of(k + 9 < n ? k + 9 : n - 1); }
+};
+
+}  // namespace sage

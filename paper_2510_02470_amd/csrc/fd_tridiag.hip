@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "sage_internal.h"
+#include "fd_tri_plan.h"
 #include "fd_wy.h"
 #include "wave_ops.h"
 
@@ -282,8 +283,8 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 // As above, but a wave owns 2 (n = 128) or 4 whole columns, carries all vectors itself and sums its products over the
 // lanes, and q and c go through the L2 the work-groups share. An exchanged value is a 16-byte entry {low word, tag, high word, tag}; the tag (solve number and step)
 // makes each 8-byte half carry its own validity, so there are no flags, no fences and nothing to clear: a reader polls an
-// entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough: once a
-// work-group has all of step k + 1, everyone has finished reading step k.
+// entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough, because a
+// work-group leaves as soon as it has nothing left to publish (fd_tri_plan.h).
 // Stores: the L1 is write-through, so a plain store reaches the XCD's L2 (local = 1). Where the work-groups cannot be
 // relied on to sit on one XCD (launch_tridiag checks the mapping once) they are device-scope stores instead, which go on
 // to memory, which takes about twice as long a step.
@@ -312,15 +313,14 @@ __device__ __forceinline__ double entry_value(const u32x4& e) {
     return __longlong_as_double(((long long)e[2] << 32) | e[0]);
 }
 
-constexpr int many_columns(int J) { return J >= 4 ? 4 : 2; }
-
 template <int J, bool LOCAL>
 __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, u32x4* __restrict__ xch,
                                                           unsigned tag0, int xcd) {
-    constexpr int N = 64 * J, CW = many_columns(J), NW = N / CW, NWG = NW / 4;  // columns of a wave; waves, work-groups
+    using Plan = TriPlan<J>;
+    constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW;
     if ((LOCAL ? xcd_id() : (int)(blockIdx.x & 7)) != xcd) return;  // one of eight consecutive work-groups
     __builtin_amdgcn_s_setprio(3);
     __shared__ Pair qc[2][N];  // {q, c} by step parity
@@ -328,6 +328,8 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg = blockIdx.x >> 3;
+    if (Plan::last_column(wg, n) < 0) return;
+    const int steps = Plan::steps(wg, n), waits = Plan::waits(wg, n);  // waits >= steps - 1
 
     if (wave >= 4) {  // ---- pollers: entries t, t + 256, .. of c and q
         // J = 2: half the waves wait for c and half for q
@@ -335,15 +337,16 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         const int t = tid & (J >= 4 ? 255 : 127);
         const bool for_c = J >= 4 || wave < 6;
         int spins = SPIN_LIMIT;
-        for (int k = 0; k < n - 1; ++k) {
+        for (int k = 0; k < steps; ++k) {
             const int par = k & 1;
             const unsigned tag = tag0 + (unsigned)k;
             // all of this thread's entries of a vector in one round trip; it is done with the entries of rows <= k
+            // (in a last step that is not waited for, the waves that compute get zeros: nothing comes of it)
             auto poll = [&](const u32x4* src, double (&val)[PT]) __attribute__((always_inline)) {
                 u32x4 e[PT];
 #pragma unroll
                 for (int u = 0; u < PT; ++u) e[u] = u32x4{0u, 0u, 0u, 0u};
-                if (t + 256 * (PT - 1) > k && t < n) {
+                if (t + 256 * (PT - 1) > k && t < n && k < waits) {
                     bool more;
                     do {
                         if constexpr (PT == 2) {
@@ -407,7 +410,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
     if (wg == 0 && tid == 0) stat[0] = (double)ex;
 
     auto reduce = [&](auto hc) __attribute__((always_inline)) {
-        constexpr int H = decltype(hc)::value, ST = J / CW;  // register index of column s: H + ST * s
+        constexpr int H = decltype(hc)::value, ST = Plan::ST;  // register index of column s: H + ST * s
         double a[CW][J], x[J], v[J], w[J];
         {
             int mrow[J];
@@ -434,7 +437,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         double xk = C[(int64_t)active_index(0, m0, LP) * NP + active_index(0, m0, LP)] * sc0;
         double xk1 = n > 1 ? C[(int64_t)active_index(0, m0, LP) * NP + active_index(1, m0, LP)] * sc0 : 0.0;
 
-        for (int k = 0; k < n - 1; ++k) {
+        for (int k = 0; k < steps; ++k) {
             const int par = k & 1;
             const unsigned tag = tag0 + (unsigned)k;
             u32x4* const qx = xch + par * 2 * N;
@@ -529,12 +532,10 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             asm volatile("" ::: "memory");
             const int i2 = k + 2 < n ? k + 2 : k + 1;
             const double v2 = vs[wave][i2];
-            if (wg == (k & (NWG - 1))) {
-                if (wave == 0) {
+            if (Plan::storing_wave(k, n) == gw) {
 #pragma unroll
-                    for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = v[j];
-                }
-                if (tid == 64) {
+                for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = v[j];
+                if (lane == 0) {
                     dT[k] = xk;
                     eT[k] = beta;
                     tauT[k] = tau;
@@ -562,7 +563,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             xk = __builtin_fma(-2.0 * v1, w1, e1.b);
             xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, e2.b));
         }
-        if (wg == 0 && tid == 0) {
+        if (Plan::wave_of(n - 1) == gw && lane == 0) {  // (waits = n - 1: xk is the last step's)
             dT[n - 1] = xk;
             eT[n - 1] = 0.0;
             tauT[n - 1] = 0.0;
@@ -837,7 +838,7 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
 #define SAGE_TRI_ONE(J)                                                                                           \
     hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
 #define SAGE_TRI_MANY(J, L)                                                                                       \
-    hipLaunchKernelGGL((tri_many_kernel<J, L>), dim3(8 * (64 * J / many_columns(J) / 4)), dim3(512), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, \
+    hipLaunchKernelGGL((tri_many_kernel<J, L>), dim3(8 * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, \
                        w.V, w.stat, w.xch, w.epoch << 10, w.xcd)
     switch (NP / 64) {
         case 1: SAGE_TRI_ONE(1); break;

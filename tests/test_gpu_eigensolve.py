@@ -78,3 +78,67 @@ def test_contexts_in_several_streams_share_the_gpu():
         # one call or five: the same rows, the last bits of the Gram blocks may differ
         assert torch.allclose(got.T @ got, want.T @ want, rtol=0, atol=1e-5 * float((want.T @ want).abs().max()))
         c.close()
+
+
+@pytest.mark.parametrize("ell", [64, 128, 256])
+@pytest.mark.parametrize("rows", [1, 2, 5, 20, 60, 70, 131, 259])
+def test_basis_of_a_buffer_with_few_rows(ell, rows):
+    """A basis taken early: the reduction runs on the rows in use, so most of its work-groups have no column or leave it
+    before the end. Orthonormal to 1e-5, invariant under the rows' covariance and with all of its energy to 1e-6 (fp32 Gram)."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    if rows >= 2 * ell:
+        pytest.skip("that many rows shrink the buffer")
+    D = 700
+    G = np.random.default_rng(rows).standard_normal((rows, D)).astype(np.float32) * np.exp(np.linspace(0, -3, rows))[:, None].astype(np.float32)
+    s = Sage(ell, D)
+    s.fd_update(torch.from_numpy(G).cuda())
+    k = min(rows, ell - 1, 128)
+    s.fd_basis(k)
+    V = s.basis().cpu().numpy().astype(np.float64)
+    A = G.astype(np.float64)
+    fro, sig2 = (A ** 2).sum(), np.linalg.svd(A, compute_uv=False)[:k] ** 2
+    AV = A @ V.T
+    H = AV.T @ AV
+    assert np.abs(V @ V.T - np.eye(k)).max() <= 1e-5
+    assert np.abs(np.diag(H) - sig2).max() <= 1e-6 * fro
+    assert np.linalg.norm(A.T @ AV - V.T @ H, 2) <= 1e-6 * fro
+    assert abs(s.stats().frob2 - fro) <= 1e-6 * fro
+
+
+@pytest.mark.parametrize("ell", [64, 128, 256])
+def test_solves_beside_other_work_on_the_gpu(ell):
+    """A stream of copies and one of matrix products keep CUs of every XCD busy while a context works: same bits as alone."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(ell)
+    G = torch.randn((ell * 7 + 3, 1500), generator=g, device="cuda")
+
+    def stream_of_rows(s):
+        s.fd_update(G[:20])
+        s.fd_basis(4)                      # an early basis: few rows
+        for lo in range(20, G.shape[0], 3 * ell):
+            s.fd_update(G[lo:lo + 3 * ell])
+        s.fd_basis(ell // 2)
+
+    alone = Sage(ell, 1500)
+    stream_of_rows(alone)
+    want, basis = alone.sketch(), alone.basis()
+    src, dst = (torch.ones(1 << 26, device="cuda") for _ in range(2))
+    a = torch.randn((2048, 2048), generator=g, device="cuda")
+    torch.cuda.synchronize()
+    st = [torch.cuda.Stream() for _ in range(2)]
+    busy = Sage(ell, 1500)
+    for _ in range(40):
+        with torch.cuda.stream(st[0]):
+            dst.copy_(src)
+        with torch.cuda.stream(st[1]):
+            a @ a
+    stream_of_rows(busy)
+    assert torch.equal(busy.sketch(), want) and torch.equal(busy.basis(), basis)
+    torch.cuda.synchronize()
+    assert busy.stats().n_unconverged == 0

@@ -1,0 +1,27 @@
+"""Checks of the kernels' integer logic that need no GPU: the headers that hold it are compiled into small host programs."""
+import os
+import subprocess
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2510_02470_amd", "csrc")
+
+
+def _build(tmp_path, name):
+    exe = str(tmp_path / name)
+    b = subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, os.path.join(HERE, name + ".cc"), "-o", exe],
+                       capture_output=True, text=True)
+    assert b.returncode == 0, b.stderr
+    return exe
+
+
+def _run(*cmd):
+    return subprocess.run(cmd, capture_output=True, text=True, timeout=120)
+
+
+def test_reduction_protocol_overwrites_nothing_that_is_still_to_be_read(tmp_path):
+    """tri_plan_check.cc at every number of rows; and the check itself: it must refuse the protocol in which work-groups with
+    nothing left to publish go on reading."""
+    exe = _build(tmp_path, "tri_plan_check")
+    r = _run(exe)
+    assert r.returncode == 0 and "tri_plan_check ok" in r.stdout, r.stdout
+    assert _run(exe, "planted").returncode == 1
