@@ -59,8 +59,9 @@ typedef struct {
     double last_delta;   /* delta of the most recent shrink */
     int last_sweeps;     /* sweeps of an iterative eigensolver; 0: the eigensolve is direct */
     int fill;            /* buffer rows in use, 0..2*ell-1 */
-    int64_t n_unconverged; /* eigensolves so far (shrinks and bases) that could not be completed; 0 as long as the context
-                            works at all (the call after such a solve returns SAGE_ERR_HIP) */
+    int64_t n_unconverged; /* eigensolves so far that did not end the usual way: other work kept the cooperating work-groups
+                            of their reduction from running together, and one work-group repeated it alone. Such a solve
+                            takes milliseconds longer; its result is as good as any */
     double last_offdiag; /* largest |off-diagonal| / trace an iterative eigensolver left; 0: the eigensolve is direct, its
                             residual is a few 2*ell * 2^-52 of the trace */
 } sage_stats_t;
@@ -372,6 +373,12 @@ int sage_set_debug_checks(sage_ctx* ctx, int on);
  * after a real launch failure. Nothing faulty runs on the GPU. nth = 0 disarms the hook.
  */
 int sage_debug_fail_launch(sage_ctx* ctx, int nth);
+
+/*
+ * Test hook for solves that cannot be done by several work-groups together (see n_unconverged): with on != 0 those of the
+ * reduction give each other up after a single look. Everything ends normally.
+ */
+int sage_debug_impatient_solves(sage_ctx* ctx, int on);
 
 /* Static description of a status code (HOST string, never NULL). */
 const char* sage_strerror(int code);

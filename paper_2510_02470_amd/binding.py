@@ -21,7 +21,7 @@ EXPORTS = (
     "sage_set_allocator", "sage_fd_create", "sage_fd_create_ex", "sage_fd_update", "sage_fd_merge", "sage_set_update_arithmetic", "sage_probe_gram_split", "sage_fd_update_outer", "sage_score_outer", "sage_rescore_outer", "sage_set_score_store", "sage_rescore", "sage_fd_basis", "sage_fd_basis_weighted", "sage_score", "sage_select", "sage_score_labeled", "sage_select_cb", "sage_select_cb_ex",
     "sage_destroy", "sage_sync", "sage_set_projection_mode", "sage_fd_sketch_export", "sage_basis_export", "sage_set_basis", "sage_scores",
     "sage_scores_export", "sage_zhat_export", "sage_stats", "sage_topm", "sage_topm_static", "sage_probe_gram_eig", "sage_probe_eig_matrix",
-    "sage_profile_enable", "sage_copy_probe", "sage_set_debug_checks", "sage_debug_fail_launch", "sage_set_sweep_policy",
+    "sage_profile_enable", "sage_copy_probe", "sage_set_debug_checks", "sage_debug_fail_launch", "sage_debug_impatient_solves", "sage_set_sweep_policy",
     "sage_profile_read", "sage_strerror",
 )
 
@@ -114,6 +114,7 @@ def lib():
     L.sage_set_debug_checks.argtypes = [vp, i32]
     L.sage_set_sweep_policy.argtypes = [vp, i32]
     L.sage_debug_fail_launch.argtypes = [vp, i32]
+    L.sage_debug_impatient_solves.argtypes = [vp, i32]
     L.sage_profile_enable.argtypes = [vp, i32]
     L.sage_profile_read.argtypes = [vp, i32, C.POINTER(dbl), C.POINTER(i64)]
     L.sage_strerror.argtypes = [i32]
@@ -342,6 +343,9 @@ class Sage:
 
     def debug_fail_launch(self, nth):
         _check(self.L.sage_debug_fail_launch(self.h, int(nth)), "sage_debug_fail_launch")
+
+    def debug_impatient_solves(self, on=True):
+        _check(self.L.sage_debug_impatient_solves(self.h, 1 if on else 0), "sage_debug_impatient_solves")
 
     def profile_enable(self, on=True):
         _check(self.L.sage_profile_enable(self.h, 1 if on else 0), "sage_profile_enable")

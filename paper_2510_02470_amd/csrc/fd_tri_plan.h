@@ -37,9 +37,8 @@ struct TriPlan {
     static constexpr int waits(int wg, int n) {
         return last_column(wg, n) == n - 1 ? n - 1 : (steps(wg, n) > 0 ? steps(wg, n) - 1 : 0);
     }
-    // The wave that stores the reflector of step k: one that is still there, two work-groups on from the one that has c
-    // to publish.
-    static constexpr int storing_wave(int k, int n) { return wave_of(k + 9 < n ? k + 9 : n - 1); }
+    // It also sees every step, and stores the results: nothing that a delayed work-group does can reach them.
+    static constexpr bool closes(int wg, int n) { return last_column(wg, n) == n - 1; }
 };
 
 }  // namespace sage

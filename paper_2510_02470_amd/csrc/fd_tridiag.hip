@@ -291,9 +291,115 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 // Waves 0..3 compute and publish, waves 4..7 only poll and hand over through LDS: loads and stores of a wave retire in
 // order, so one that did both would wait, with every poll, for its own stores. They wait for c first, which is out before
 // the products are formed, then for q: a poll of one vector takes 550 cycles, of both 830.
-// A poll loop ends after SPIN_LIMIT rounds (seconds; the partners are resident or about to be, whatever else the GPU runs
-// ends by itself): the kernel then gives up, reports in stat[1], and every further wait returns at once.
-constexpr int SPIN_LIMIT = 1 << 22;
+// The work-groups must be resident together, which nothing guarantees: kernels of other streams and processes may hold the CUs
+// of the XCD. So a thread polls at most `polls` times in vain in all (SPIN_LIMIT: about 30 ms, where a whole reduction takes 0.8)
+// and then goes on with NaN for what did not come. NaN goes into everything it publishes from then on, so the others lose no time
+// waiting, and reaches the work-group of the last column, which finds it in the last diagonal element. That work-group is the only
+// one that writes results, and it then repeats the whole reduction alone (tri_alone): a solve never fails.
+constexpr int SPIN_LIMIT = 1 << 17;
+
+// The reduction by one work-group of 512 threads, with the matrix in V (its rows become the reflectors) and the vectors of a step
+// in LDS: every step reads and writes the trailing matrix once, through the L2. For solves that several work-groups could not
+// do together: 0.5, 2.2 and 12.8 ms at 128, 256 and 512 rows, where they take 0.12, 0.27 and 0.74. vec: 4 N words.
+template <int J>
+__device__ __forceinline__ void tri_alone(const double* __restrict__ C, int NP, int m0, int LP, int n, double* __restrict__ dT,
+                                          double* __restrict__ eT, double* __restrict__ tauT, double* V, double sc0,
+                                          double* vec) {
+    constexpr int N = 64 * J, T = 512;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = wave; i < n; i += T / 64)
+        for (int j = lane; j < N; j += 64)
+            V[(int64_t)i * N + j] = j < n ? C[(int64_t)active_index(i, m0, LP) * NP + active_index(j, m0, LP)] * sc0 : 0.0;
+    for (int j = tid; j < 4 * N; j += T) vec[j] = 0.0;
+    __syncthreads();
+    for (int k = 0; k < n; ++k) {
+        const double *v0 = vec + ((k + 1) & 1) * N, *w0 = v0 + 2 * N;  // of step k - 1 (v' and w' above)
+        double *v = vec + (k & 1) * N, *w = v + 2 * N;
+        // column k below the diagonal, with the update of step k - 1
+        for (int j = tid; j < N; j += T) {
+            const double a = V[(int64_t)k * N + j];
+            const double x = __builtin_fma(-v0[j], w0[k], __builtin_fma(-w0[j], v0[k], a));
+            v[j] = j > k && j < n ? x : 0.0;
+            w[j] = 0.0;
+            if (j == k) dT[k] = x;
+        }
+        __syncthreads();
+        if (k == n - 1) break;
+        double r2 = 0.0;
+        for (int j = lane; j < n; j += 64) r2 = j > k + 1 ? __builtin_fma(v[j], v[j], r2) : r2;
+        r2 = lane_sum<64>(r2);
+        double beta, tau, v1;
+        householder(v[k + 1], r2, beta, tau, v1);
+        __syncthreads();
+        for (int j = tid; j < N; j += T) {
+            const double x = j == k + 1 ? v1 : v[j];
+            if (j == k + 1) v[j] = x;
+            V[(int64_t)k * N + j] = x;
+        }
+        if (tid == 0) {
+            eT[k] = beta;
+            tauT[k] = tau;
+        }
+        __syncthreads();
+        const int c0 = (k + 1) & ~63;  // columns below are done with
+        // (four rows of a wave at a time, for their loads to be in flight together)
+        for (int i0 = k + 1 + wave; i0 < n; i0 += 4 * (T / 64)) {
+            double vi[4], wi[4], s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * (T / 64);
+                vi[u] = i < n ? v0[i] : 0.0;
+                wi[u] = i < n ? w0[i] : 0.0;
+            }
+            for (int j = c0 + lane; j < n; j += 64) {
+                const double vj = v0[j], wj = w0[j], xj = v[j];
+                double a[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u * (T / 64);
+                    a[u] = i < n ? V[(int64_t)i * N + j] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u * (T / 64);
+                    a[u] = __builtin_fma(-vj, wi[u], __builtin_fma(-wj, vi[u], a[u]));
+                    if (i < n) V[(int64_t)i * N + j] = a[u];
+                    s[u] = __builtin_fma(a[u], xj, s[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * (T / 64);
+                s[u] = lane_sum<64>(s[u]);
+                if (lane == 0 && i < n) w[i] = tau * s[u];
+            }
+        }
+        __syncthreads();
+        double dot = 0.0;
+        for (int j = lane; j < n; j += 64) dot = __builtin_fma(w[j], v[j], dot);
+        dot = lane_sum<64>(dot);
+        const double al = -0.5 * tau * dot;
+        __syncthreads();
+        for (int j = tid; j < N; j += T) w[j] = __builtin_fma(al, v[j], w[j]);
+        __syncthreads();
+    }
+}
+
+// The end of a reduction: what follows the last row in use. The rows of V that complete the last block of reflectors are zero; the
+// padding of T is decoupled and below every eigenvalue of a Gram matrix.
+template <int J>
+__device__ __forceinline__ void tri_finish(int n, double* __restrict__ dT, double* __restrict__ eT, double* __restrict__ tauT,
+                                           double* __restrict__ V) {
+    constexpr int N = 64 * J;
+    for (int i = n - 1 + (int)threadIdx.x; i < N; i += 512) {
+        if (i >= n) dT[i] = -1.0;
+        eT[i] = 0.0;
+        tauT[i] = 0.0;
+    }
+    for (int k = n - 1; k % WY != 0; ++k)
+        for (int i = threadIdx.x; i < N; i += 512) V[(int64_t)k * N + i] = 0.0;
+}
 
 template <bool LOCAL>
 __device__ __forceinline__ void put_entry(u32x4* p, double v, unsigned tag) {
@@ -318,30 +424,32 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, u32x4* __restrict__ xch,
-                                                          unsigned tag0, int xcd) {
+                                                          unsigned tag0, int xcd, int polls, double* __restrict__ redone) {
     using Plan = TriPlan<J>;
     constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW;
     if ((LOCAL ? xcd_id() : (int)(blockIdx.x & 7)) != xcd) return;  // one of eight consecutive work-groups
     __builtin_amdgcn_s_setprio(3);
     __shared__ Pair qc[2][N];  // {q, c} by step parity
     __shared__ double vs[4][N];
+    __shared__ bool gave_up;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg = blockIdx.x >> 3;
     if (Plan::last_column(wg, n) < 0) return;
     const int steps = Plan::steps(wg, n), waits = Plan::waits(wg, n);  // waits >= steps - 1
+    const bool closes = Plan::closes(wg, n);  // this work-group stores what the solve's next stages read
 
-    if (wave >= 4) {  // ---- pollers: entries t, t + 256, .. of c and q
+    auto wait_for_entries = [&]() __attribute__((always_inline)) {  // waves 4 ..: entries t, t + 256, .. of c and q
         // J = 2: half the waves wait for c and half for q
         constexpr int PT = J >= 4 ? N / 256 : 1;
         const int t = tid & (J >= 4 ? 255 : 127);
         const bool for_c = J >= 4 || wave < 6;
-        int spins = SPIN_LIMIT;
+        int spins = polls;
         for (int k = 0; k < steps; ++k) {
             const int par = k & 1;
             const unsigned tag = tag0 + (unsigned)k;
             // all of this thread's entries of a vector in one round trip; it is done with the entries of rows <= k
-            // (in a last step that is not waited for, the waves that compute get zeros: nothing comes of it)
+            // (in a last step that is not waited for, the waves that compute get NaN: nothing comes of it)
             auto poll = [&](const u32x4* src, double (&val)[PT]) __attribute__((always_inline)) {
                 u32x4 e[PT];
 #pragma unroll
@@ -372,7 +480,6 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                             more = more || (i > k && i < n && !fresh(e[u], tag));
                         }
                         if (more && --spins <= 0) {
-                            stat[1] = 1.0;
                             spins = 1;  // every further wait gives up after one round
                             more = false;
                         }
@@ -381,7 +488,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
 #pragma unroll
                 for (int u = 0; u < PT; ++u) {
                     const int i = t + 256 * u;
-                    val[u] = i > k && i < n ? entry_value(e[u]) : 0.0;
+                    val[u] = i > k && i < n ? (fresh(e[u], tag) ? entry_value(e[u]) : __builtin_nan("")) : 0.0;
                 }
             };
             const u32x4* const qx = xch + par * 2 * N + t;
@@ -398,20 +505,18 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             }
             lds_barrier();
         }
-        return;
-    }
+    };
 
     // Wave gw owns the columns of lane gw % 64: cl + 64 (H + s J / CW), s < CW, H = gw / 64 < J / CW. So the entries of v and w at
     // its own columns are in one lane of its own registers.
     const int gw = wg * 4 + wave, cl = gw & 63;
-    const double md = wave_max_diag(C, NP, lane);
-    const int ex = tri_exponent(md);
-    const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
-    if (wg == 0 && tid == 0) stat[0] = (double)ex;
-
     auto reduce = [&](auto hc) __attribute__((always_inline)) {
         constexpr int H = decltype(hc)::value, ST = Plan::ST;  // register index of column s: H + ST * s
         double a[CW][J], x[J], v[J], w[J];
+        const double md = wave_max_diag(C, NP, lane);
+        const int ex = tri_exponent(md);
+        const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
+        if (closes && tid == 0) stat[0] = (double)ex;
         {
             int mrow[J];
 #pragma unroll
@@ -532,10 +637,11 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             asm volatile("" ::: "memory");
             const int i2 = k + 2 < n ? k + 2 : k + 1;
             const double v2 = vs[wave][i2];
-            if (Plan::storing_wave(k, n) == gw) {
+            if (closes) {
 #pragma unroll
-                for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = v[j];
-                if (lane == 0) {
+                for (int j = 0; j < J; ++j)
+                    if ((j & 3) == wave) V[(int64_t)k * N + lane + 64 * j] = v[j];
+                if (tid == 64) {
                     dT[k] = xk;
                     eT[k] = beta;
                     tauT[k] = tau;
@@ -563,24 +669,24 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             xk = __builtin_fma(-2.0 * v1, w1, e1.b);
             xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, e2.b));
         }
-        if (Plan::wave_of(n - 1) == gw && lane == 0) {  // (waits = n - 1: xk is the last step's)
+        if (closes && tid == 0) {  // (waits = n - 1: xk is the last step's)
             dT[n - 1] = xk;
-            eT[n - 1] = 0.0;
-            tauT[n - 1] = 0.0;
+            gave_up = xk != xk;
         }
     };
     static_assert(NW == 64 || NW == 128, "one or two columns a lane");
-    if (NW == 64 || gw < 64) reduce(std::integral_constant<int, 0>{});
+    if (wave >= 4) wait_for_entries();
+    else if (NW == 64 || gw < 64) reduce(std::integral_constant<int, 0>{});
     else reduce(std::integral_constant<int, NW / 64 - 1>{});
-    if (wg == 0) {
-        for (int i = n + tid; i < N; i += 256) {
-            dT[i] = -1.0;
-            eT[i] = 0.0;
-            tauT[i] = 0.0;
-        }
-        for (int k = n - 1; k % WY != 0; ++k)  // the rows of V that complete the last block of reflectors
-            for (int i = tid; i < N; i += 256) V[(int64_t)k * N + i] = 0.0;
+    if (!closes) return;
+    __syncthreads();
+    if (gave_up) {  // (or the matrix is not finite: then so is this, and it does no harm)
+        if (tid == 0) *redone += 1.0;
+        const double sc = __builtin_amdgcn_ldexp(1.0, -tri_exponent(wave_max_diag(C, NP, lane)));
+        tri_alone<J>(C, NP, m0, LP, n, dT, eT, tauT, V, sc, &vs[0][0]);
+        __syncthreads();
     }
+    tri_finish<J>(n, dT, eT, tauT, V);
 }
 
 // ---- Y = H Z --------------------------------------------------------------------------------------------------------
@@ -661,11 +767,6 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
                 if (cf.mode == 0) {
                     cf.acc[0] += delta;
                     cf.acc[2] = delta;
-                }
-                if (stat[1] != 0.0) {  // the reduction gave up waiting: the host refuses the context from its next call on
-                    cf.acc[4] += 1.0;
-                    stat[1] = 0.0;
-                    *(volatile int*)cf.failed = 1;
                 }
             }
             return;
@@ -839,7 +940,7 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
     hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
 #define SAGE_TRI_MANY(J, L)                                                                                       \
     hipLaunchKernelGGL((tri_many_kernel<J, L>), dim3(8 * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, \
-                       w.V, w.stat, w.xch, w.epoch << 10, w.xcd)
+                       w.V, w.stat, w.xch, w.epoch << 10, w.xcd, w.impatient ? 1 : SPIN_LIMIT, w.redone)
     switch (NP / 64) {
         case 1: SAGE_TRI_ONE(1); break;
         case 2:

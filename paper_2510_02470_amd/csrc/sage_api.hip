@@ -26,7 +26,7 @@ enum { K_GRAM = 0, K_REDUCE, K_EIG, K_COEFF, K_REBUILD, K_INSERT, K_PROJECT, K_F
 struct SideKit {
     hipStream_t stream = nullptr;
     hipEvent_t mark = nullptr, side[2] = {nullptr, nullptr};
-    int* host = nullptr;  // pinned words: [0] a solve failed, [1], [2] report of the class-balanced selection, [16] signal
+    int* host = nullptr;  // pinned words: [1], [2] report of the class-balanced selection, [16] signal
     unsigned token = 0;   // of the last signal
 };
 
@@ -80,14 +80,13 @@ struct sage_ctx {
     bool nw_bf16[2] = {false, false};
     bool nw_half[2] = {false, false};  // nw[i] is kept in pieces of bf16 (half16), not as fp32
     bool one_part = true;
-    double* acc = nullptr;  // [0] sum_delta [1] frob2 [2] last_delta [4] failed solves
+    double* acc = nullptr;  // [0] sum_delta [1] frob2 [2] last_delta [4] EigWork::redone
 
     bool poisoned = false;   // a HIP call failed while work of a call was partly enqueued: the state is not trustworthy
     int fail_in = 0;         // test hook (sage_debug_fail_launch): the fail_in-th launch from now fails without running
     bool debug_checks = false;      // sage_set_debug_checks: scan caller batches for non-finite values
     unsigned* dbg_count = nullptr;  // device counter of that scan
 
-    int* h_failed = nullptr;  // pinned: set by the device when an eigensolve could not be completed (see ALIVE)
     int xcd_slot = -1;        // registered use of an XCD by this context's eigensolves (-1: they need none)
     int device = 0;
 
@@ -150,7 +149,6 @@ inline int hip_failed(sage_ctx* c) {
     do {                                                                               \
         if (!(c)) return SAGE_ERR_ARG;                                                 \
         if ((c)->poisoned) return SAGE_ERR_STATE;                                      \
-        if ((c)->h_failed && *(volatile int*)(c)->h_failed) return hip_failed(c);      \
     } while (0)
 
 std::mutex g_mem_lock;
@@ -329,7 +327,7 @@ int note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
 bool new_one(const sage_ctx* c, int i) { return c->one_part && c->nw_bf16[i] && (c->d.NP < 512 || c->nw_half[i]); }
 
 // The reduction of a 128-, 256- or 512-row eigensolve keeps 16 or 32 work-groups of one XCD in step, so all of them must be
-// resident together. Contexts are spread over the XCDs; when two share one, their reductions are ordered by an event, so
+// resident together (where they are not, the solve takes milliseconds longer). Contexts are spread over the XCDs; when two share one, their reductions are ordered by an event, so
 // that at most two (one launched before the second context appeared, one in the chain) are ever in flight on an XCD, and
 // two fit on its CUs side by side.
 struct XcdSlot {
@@ -359,7 +357,6 @@ bool kit_take(int device, SideKit& k) {
         std::lock_guard<std::mutex> hold(g_kit_lock);
         if (g_kits[device] > 0) {
             k = g_kit[device][--g_kits[device]];
-            *k.host = 0;
             return true;
         }
     }
@@ -373,7 +370,6 @@ bool kit_take(int device, SideKit& k) {
         kit_destroy(k);
         return false;
     }
-    *k.host = 0;
     return true;
 }
 // (everything enqueued with it is complete)
@@ -541,7 +537,7 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
     }
     const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3;
     const CoeffArgs cf{LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new, c->Mt,
-                       split_rb ? c->Mt3 : nullptr, c->acc, c->h_failed};  // (row ell - 1 of the result is zero)
+                       split_rb ? c->Mt3 : nullptr, c->acc};  // (row ell - 1 of the result is zero)
     RUN(K_EIG, eigensolve(c, ell, 2 * ell, cf.count, &cf));
     if (split_rb)
         RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], ell, c->Mt3, c->top, LP, LP, c->d, c->st,
@@ -725,7 +721,6 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     const int NP = c->d.NP;
     size_t hbytes = (size_t)c->d.S * c->d.LP * DC * sizeof(float);  // one half buffer
     if (!kit_take(dev, c->kit)) return fail(SAGE_ERR_HIP);
-    c->h_failed = c->kit.host;
 #define CALLOC(ptr, bytes)                                                        \
     do {                                                                          \
         if (!dev_alloc(c->mem, c->st, (void**)&(ptr), (bytes))) return fail(SAGE_ERR_ALLOC); \
@@ -778,6 +773,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
     CALLOC(c->acc, 8 * sizeof(double));
+    c->ew.redone = c->acc + 4;
 #undef CALLOC
     // Rows of the top half that the stream never fills are zero. (Those it has not filled yet are cleared when something
     // looks at them, see clear_top; rows of a new half beyond its fill are never used.)
@@ -937,7 +933,7 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     if (rc != SAGE_OK) return rc;
     const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3 && rebuild_split_ok(KP) && KP <= c->d.LP;
     const CoeffArgs cf{KP, k, weighted ? 2 : 1, c->d.n, c->d.ell, c->cnt_top, c->fill_top, c->d.LP + c->cnt_new,
-                       c->d.LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc, c->h_failed};
+                       c->d.LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc};
     rc = decompose(c, cf);
     if (rc != SAGE_OK) return rc;
     c->cnt_top = c->fill_top;
@@ -1490,6 +1486,12 @@ int sage_debug_fail_launch(sage_ctx* c, int nth) {
     ALIVE(c);
     if (nth < 0) return SAGE_ERR_ARG;
     c->fail_in = nth;
+    return SAGE_OK;
+}
+
+int sage_debug_impatient_solves(sage_ctx* c, int on) {
+    ALIVE(c);
+    c->ew.impatient = on != 0;
     return SAGE_OK;
 }
 

@@ -160,10 +160,12 @@ struct EigWork {
     double* eT;
     double* tauT;
     double* dI[2];  // NP: eigenvalues, ascending, in units of 2^stat[0]
-    double* stat;   // [0] exponent of the scaling, [1] set when the reduction gave up waiting for a work-group
+    double* stat;   // [0] exponent of the scaling
+    double* redone; // solves whose reduction one work-group repeated because the others were not there in time
+    bool impatient; // test hook: its work-groups wait for each other for one poll only
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
-    u32x4* xch;     // exchange buffers of the reduction (NP = 256, 512), 4 NP entries
-    int xcd;        // the XCD the reduction runs on (NP = 256, 512)
+    u32x4* xch;     // exchange buffers of the reduction (NP = 128, 256, 512), 4 NP entries
+    int xcd;        // the XCD the reduction runs on (NP = 128, 256, 512)
     bool local;     // work-groups with the same number modulo 8 share an XCD (tridiag_local_ok)
     unsigned epoch; // number of the solve, from 1 (tags of the exchange)
     DcWork dc;
@@ -177,14 +179,12 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
 // Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Mc3 (split
 // parts) if given, else into Mt. Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1)
-// and [rb0, rb1), the rows not yet counted), acc[2] last_delta, acc[4] failed solves; *failed (host memory) is set after a
-// failed solve.
+// and [rb0, rb1), the rows not yet counted), acc[2] last_delta. (acc[4]: EigWork::redone)
 struct CoeffArgs {
     int MP, count, mode, n, ell, ra0, ra1, rb0, rb1;
     float* Mt;
     void* Mc3;
     double* acc;
-    int* failed;
 };
 // the `count` leading eigenvectors into Yt, or (cf given) only the coefficients made from them
 hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st);

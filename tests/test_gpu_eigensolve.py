@@ -142,3 +142,51 @@ def test_solves_beside_other_work_on_the_gpu(ell):
     assert torch.equal(busy.sketch(), want) and torch.equal(busy.basis(), basis)
     torch.cuda.synchronize()
     assert busy.stats().n_unconverged == 0
+
+
+@pytest.mark.parametrize("ell", [64, 128, 256])
+def test_solves_that_their_work_groups_cannot_do_together(ell):
+    """The work-groups of the reduction give each other up after one look, as they do after a long wait where other work keeps
+    them from running together: every solve still succeeds (one work-group repeats it), to the bars of the usual way."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    s, n = Sage(ell, 64), 2 * ell
+    s.debug_impatient_solves()
+    solves = 0
+    for name, C in _matrices(n).items():
+        C = (C + C.T) / 2
+        Y, lam, _ = s.probe_eig_matrix(torch.from_numpy(C).cuda())
+        Y, lam = Y.cpu().numpy(), lam.cpu().numpy()
+        solves += 1
+        scale = max(np.abs(C).max(), 1e-300) * n
+        assert np.abs(Y.T @ Y - np.eye(n)).max() <= 1e-13, name
+        assert np.abs((Y * lam) @ Y.T - C).max() <= 1e-14 * scale, name
+        assert np.abs(np.sort(lam) - np.linalg.eigvalsh(C)).max() <= 1e-14 * scale, name
+    assert s.stats().n_unconverged == solves
+    s.debug_impatient_solves(False)
+    s.probe_eig_matrix(torch.eye(n, dtype=torch.float64, device="cuda"))
+    assert s.stats().n_unconverged == solves
+
+    # a whole round, with few rows first; the usual way for comparison
+    g = torch.Generator(device="cuda").manual_seed(ell)
+    G = torch.randn((ell * 4 + 3, 900), generator=g, device="cuda") * torch.linspace(1, 0.1, 900, device="cuda")
+    out = []
+    for impatient in (False, True):
+        c = Sage(ell, 900)
+        c.debug_impatient_solves(impatient)
+        for rows in (1, 2, 5, 19, ell):
+            c.fd_update(G[:rows])
+            c.fd_basis(1)
+        c.fd_update(G)
+        c.fd_basis(8)
+        c.score(G)
+        idx = c.select(0.1)
+        assert (c.stats().n_unconverged > 0) == impatient
+        B = c.sketch().double()
+        out.append((B.T @ B, c.scores(), idx, c.stats().sum_delta))
+    top = float(out[0][0].abs().max())
+    assert float((out[0][0] - out[1][0]).abs().max()) <= 1e-6 * top
+    assert abs(out[0][3] - out[1][3]) <= 1e-9 * out[0][3]
+    assert float((out[0][1] - out[1][1]).abs().max()) <= 1e-4
