@@ -344,8 +344,8 @@ class Sage:
     def debug_fail_launch(self, nth):
         _check(self.L.sage_debug_fail_launch(self.h, int(nth)), "sage_debug_fail_launch")
 
-    def debug_impatient_solves(self, on=True):
-        _check(self.L.sage_debug_impatient_solves(self.h, 1 if on else 0), "sage_debug_impatient_solves")
+    def debug_impatient_solves(self, on=1):
+        _check(self.L.sage_debug_impatient_solves(self.h, int(on)), "sage_debug_impatient_solves")
 
     def profile_enable(self, on=True):
         _check(self.L.sage_profile_enable(self.h, 1 if on else 0), "sage_profile_enable")

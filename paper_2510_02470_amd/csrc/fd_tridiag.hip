@@ -11,7 +11,8 @@
 //                      they share (tri_many_kernel, 0.9, 1.04, 1.45 us a step; every wave carries the vectors of the
 //                      step redundantly, so a step has one exchange and no other synchronisation).
 // One work-group issues the instructions of a 128-row reduction in 155 us, 16 of them take 116, so the exchange pays from there
-// on; where the work-groups cannot be relied on to share an XCD, 128 rows stay with one work-group.
+// on. Where work-groups cannot be placed on one XCD (xcd_map knows no period) one does it all: 128 rows by tri_one_kernel,
+// larger ones as after a wait in vain (see tri_many_kernel).
 #include <mutex>
 #include <type_traits>
 
@@ -285,9 +286,8 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 // makes each 8-byte half carry its own validity, so there are no flags, no fences and nothing to clear: a reader polls an
 // entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough, because a
 // work-group leaves as soon as it has nothing left to publish (fd_tri_plan.h).
-// Stores: the L1 is write-through, so a plain store reaches the XCD's L2 (local = 1). Where the work-groups cannot be
-// relied on to sit on one XCD (launch_tridiag checks the mapping once) they are device-scope stores instead, which go on
-// to memory, which takes about twice as long a step.
+// Stores: the L1 is write-through, so a plain store reaches the XCD's L2. Of the work-groups launched, one in `period` lands on
+// the XCD of the solve and stays, in the role of its number.
 // Waves 0..3 compute and publish, waves 4..7 only poll and hand over through LDS: loads and stores of a wave retire in
 // order, so one that did both would wait, with every poll, for its own stores. They wait for c first, which is out before
 // the products are formed, then for q: a poll of one vector takes 550 cycles, of both 830.
@@ -401,40 +401,33 @@ __device__ __forceinline__ void tri_finish(int n, double* __restrict__ dT, doubl
         for (int i = threadIdx.x; i < N; i += 512) V[(int64_t)k * N + i] = 0.0;
 }
 
-template <bool LOCAL>
 __device__ __forceinline__ void put_entry(u32x4* p, double v, unsigned tag) {
     const long long u = __double_as_longlong(v);
-    const u32x4 e = {(unsigned)u, tag, (unsigned)(u >> 32), tag};
-    if constexpr (LOCAL) {
-        *p = e;
-        asm volatile("" ::: "memory");  // stays here
-    } else {
-        // (s_nop: the data registers of a 16-byte store must not be written in the next cycle, which the compiler only
-        // takes care of for stores of its own)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(e) : "memory");
-    }
+    *p = u32x4{(unsigned)u, tag, (unsigned)(u >> 32), tag};
+    asm volatile("" ::: "memory");  // stays here
 }
 __device__ __forceinline__ bool fresh(const u32x4& e, unsigned tag) { return e[1] == tag && e[3] == tag; }
 __device__ __forceinline__ double entry_value(const u32x4& e) {
     return __longlong_as_double(((long long)e[2] << 32) | e[0]);
 }
 
-template <int J, bool LOCAL>
+template <int J>
 __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, u32x4* __restrict__ xch,
-                                                          unsigned tag0, int xcd, int polls, double* __restrict__ redone) {
+                                                          unsigned tag0, int xcd, int shift, int polls,
+                                                          double* __restrict__ redone) {
     using Plan = TriPlan<J>;
     constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW;
-    if ((LOCAL ? xcd_id() : (int)(blockIdx.x & 7)) != xcd) return;  // one of eight consecutive work-groups
+    if (xcd >= 0 && xcd_id() != xcd) return;
     __builtin_amdgcn_s_setprio(3);
     __shared__ Pair qc[2][N];  // {q, c} by step parity
     __shared__ double vs[4][N];
     __shared__ bool gave_up;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wg = blockIdx.x >> 3;
+    const int wg = xcd >= 0 ? blockIdx.x >> shift : Plan::wave_of(n - 1) >> 2;  // (xcd < 0: the only work-group)
     if (Plan::last_column(wg, n) < 0) return;
     const int steps = Plan::steps(wg, n), waits = Plan::waits(wg, n);  // waits >= steps - 1
     const bool closes = Plan::closes(wg, n);  // this work-group stores what the solve's next stages read
@@ -576,7 +569,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                             for (int j = J0; j < J; ++j) {
                                 double c = a[s][j];
                                 asm volatile("" : "+v"(c));  // keeps the cases apart (no run-time index into a[])
-                                put_entry<LOCAL>(cx + lane + 64 * j, c, tag);
+                                put_entry(cx + lane + 64 * j, c, tag);
                             }
                         }
                 }
@@ -605,7 +598,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                 swap_rows<32>(t, b0, b1);
                 t = b0 + b1;
                 const int col = cl + 64 * (H + ST * (lane & 3));
-                if (lane < 4 && col > k && col < n) put_entry<LOCAL>(qx + col, t, tag);
+                if (lane < 4 && col > k && col < n) put_entry(qx + col, t, tag);
             }
             else {  // two sums: one per lane of a pair
                 const bool odd = lane & 1;
@@ -619,7 +612,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                 swap_rows<32>(x, b0, b1);
                 x = b0 + b1;
                 const int col = cl + 64 * (H + ST * (lane & 1));
-                if (lane < 2 && col > k && col < n) put_entry<LOCAL>(qx + col, x, tag);
+                if (lane < 2 && col > k && col < n) put_entry(qx + col, x, tag);
             }
             // while the entries travel: the reflector
             double r2 = 0.0;
@@ -898,18 +891,18 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
     }
 }
 
-// Do eight consecutive work-groups run on the eight XCDs of the current device, in an order that repeats? Asked once per
-// device.
 __global__ void xcd_probe_kernel(int* __restrict__ out) {
     if (threadIdx.x == 0) out[blockIdx.x] = xcd_id();
 }
-static bool xcd_mapping_known() {
+const XcdMap& xcd_map() {
     static std::mutex lock;
-    static int known[64] = {0};  // 0: not asked yet, 1: yes, 2: no
+    static XcdMap known[64];
+    static bool asked[64] = {false};
+    static const XcdMap nothing{};
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nothing;
     std::lock_guard<std::mutex> hold(lock);
-    if (known[dev] == 0) {
+    if (!asked[dev]) {
         constexpr int B = 512;
         int* d = nullptr;
         int h[B];
@@ -925,41 +918,34 @@ static bool xcd_mapping_known() {
             }
             (void)hipFree(d);
         }
-        unsigned seen = 0;
-        for (int i = 0; ok && i < 8; ++i) seen |= 1u << h[i];
-        ok = ok && seen == 0xFF;
-        for (int i = 8; ok && i < B; ++i) ok = h[i] == h[i - 8];
-        known[dev] = ok ? 1 : 2;
+        if (ok) known[dev] = xcd_map_of(h, B);
+        asked[dev] = true;
     }
-    return known[dev] == 1;
+    return known[dev];
 }
 
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st) {
     const int LP = NP / 2;
 #define SAGE_TRI_ONE(J)                                                                                           \
     hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
-#define SAGE_TRI_MANY(J, L)                                                                                       \
-    hipLaunchKernelGGL((tri_many_kernel<J, L>), dim3(8 * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, \
-                       w.V, w.stat, w.xch, w.epoch << 10, w.xcd, w.impatient ? 1 : SPIN_LIMIT, w.redone)
+#define SAGE_TRI_MANY(J)                                                                                           \
+    hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, \
+                       w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, w.epoch << 10, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
+                       alone || w.impatient ? 1 : SPIN_LIMIT, w.redone)
+    const bool alone = w.period == 0;
     switch (NP / 64) {
         case 1: SAGE_TRI_ONE(1); break;
         case 2:
-            if (w.local) SAGE_TRI_MANY(2, true); else SAGE_TRI_ONE(2);
+            if (alone) SAGE_TRI_ONE(2); else SAGE_TRI_MANY(2);
             break;
-        case 4:
-            if (w.local) SAGE_TRI_MANY(4, true); else SAGE_TRI_MANY(4, false);
-            break;
-        case 8:
-            if (w.local) SAGE_TRI_MANY(8, true); else SAGE_TRI_MANY(8, false);
-            break;
+        case 4: SAGE_TRI_MANY(4); break;
+        case 8: SAGE_TRI_MANY(8); break;
         default: return hipErrorInvalidValue;
     }
 #undef SAGE_TRI_ONE
 #undef SAGE_TRI_MANY
     return hipGetLastError();
 }
-
-bool tridiag_local_ok() { return xcd_mapping_known(); }
 
 hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st) {
     const int LP = NP / 2;

@@ -386,18 +386,22 @@ void kit_give(int device, SideKit& k, bool reuse) {
     kit_destroy(k);
 }
 
-int xcd_take(sage_ctx* c) {
-    if (c->d.NP < 128 || c->device < 0 || c->device >= MAX_DEVICES) return 0;
+// The XCD for a context's reductions; where there is no telling which work-groups share one, it needs none.
+void xcd_take(sage_ctx* c) {
+    if (c->d.NP < 128 || c->device < 0 || c->device >= MAX_DEVICES) return;
+    const XcdMap& map = xcd_map();
+    c->ew.period = map.period;
+    if (map.period == 0) return;
     std::lock_guard<std::mutex> hold(g_xcd_lock);
-    const int first = (int)(getpid() & 7);  // other processes on the GPU most likely start at another one
+    const int first = (int)(getpid() % map.period);  // other processes on the GPU most likely start at another one
     int best = first;
-    for (int i = 1; i < 8; ++i) {
-        const int x = (first + i) & 7;
+    for (int i = 1; i < map.period; ++i) {
+        const int x = (first + i) % map.period;
         if (g_xcd[c->device][x].users < g_xcd[c->device][best].users) best = x;
     }
     g_xcd[c->device][best].users += 1;
     c->xcd_slot = best;
-    return best;
+    c->ew.xcd = map.id[best];
 }
 void xcd_release(sage_ctx* c) {
     if (c->xcd_slot < 0) return;
@@ -491,7 +495,7 @@ int side_ahead(sage_ctx* c, const RowSrc* next) {
     HIPCHK(hipEventRecord(c->ev_mark, c->st));
     HIPCHK(hipStreamWaitEvent(c->st2, c->ev_mark, 0));
     if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
-    const int skip = c->ew.local ? c->ew.xcd : -1;
+    const int skip = c->ew.period == 8 ? c->ew.xcd : -1;
     HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, skip));
     c->gp_side_used[o] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
     HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), skip));
@@ -767,8 +771,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.K, &w.dc.k1, &w.dc.dense}) take(*p, n1);
             if (pass == 0) CALLOC(c->eig_mem, bytes);
         }
-        c->ew.xcd = xcd_take(c);
-        c->ew.local = NP >= 128 && tridiag_local_ok();
+        xcd_take(c);
     }
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
@@ -1491,7 +1494,9 @@ int sage_debug_fail_launch(sage_ctx* c, int nth) {
 
 int sage_debug_impatient_solves(sage_ctx* c, int on) {
     ALIVE(c);
-    c->ew.impatient = on != 0;
+    if (on < 0 || on > 2) return SAGE_ERR_ARG;
+    c->ew.impatient = on == 1;
+    c->ew.period = on == 2 || c->xcd_slot < 0 ? 0 : xcd_map().period;
     return SAGE_OK;
 }
 

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "sage.h"
+#include "xcd_map.h"
 
 namespace sage {
 
@@ -80,8 +81,8 @@ __host__ __device__ inline const u32x4* half16(const float* half, int LP, int64_
 // ---- kernel launchers (each enqueues on `st` and returns hipGetLastError()) ---------------------------------
 // launch_util.hip: raise a kernel's dynamic LDS limit, once per (device, kernel); thread-safe
 hipError_t ensure_dynamic_lds(const void* kernel, int bytes);
-// The XCD this work-group runs on, 0..7. Eight consecutive work-groups run on eight different ones (checked once per device,
-// tridiag_local_ok); which of them the first gets differs from queue to queue, so nothing may be concluded from blockIdx alone.
+// The XCD this work-group runs on, 0..7. Nothing may be concluded from blockIdx alone: which XCD the first work-group gets
+// differs from queue to queue.
 __device__ __forceinline__ int xcd_id() {
     int id;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(id));
@@ -166,7 +167,7 @@ struct EigWork {
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
     u32x4* xch;     // exchange buffers of the reduction (NP = 128, 256, 512), 4 NP entries
     int xcd;        // the XCD the reduction runs on (NP = 128, 256, 512)
-    bool local;     // work-groups with the same number modulo 8 share an XCD (tridiag_local_ok)
+    int period;     // of the work-groups of a launch over the XCDs (XcdMap), 0: not known
     unsigned epoch; // number of the solve, from 1 (tags of the exchange)
     DcWork dc;
 };
@@ -174,7 +175,7 @@ struct EigWork {
 inline int dc_result(int NP) { return (NP == 128 || NP == 512) ? 1 : 0; }
 // Matrix indices in use: 0 .. m0-1 and LP .. LP + (n - m0) - 1, n in all (the others are zero rows and columns); the count
 // leading eigenvectors are formed.
-bool tridiag_local_ok();  // asks the current device (once)
+const XcdMap& xcd_map();  // asks the current device (once)
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
 // Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Mc3 (split

@@ -1,0 +1,36 @@
+// Which XCD the work-groups of a launch run on. Plain integer functions, so that they can be checked without a GPU
+// (tests/xcd_check.cc).
+#pragma once
+
+namespace sage {
+
+// Work-groups i and i + period of a launch run on the same XCD and `period` consecutive ones on different XCDs: those of
+// `id` (which of them the first gets differs from queue to queue). 8 on the whole chip, the number of XCDs of a
+// partition otherwise; 0: neither can be said.
+struct XcdMap {
+    int period = 0;
+    int id[8] = {};
+};
+
+// from the XCDs (0 .. 7) that the work-groups 0 .. count - 1 of one launch ran on
+inline XcdMap xcd_map_of(const int* on, int count) {
+    for (int p = 1; p <= 8; p *= 2) {
+        unsigned seen = 0;
+        XcdMap m;
+        bool ok = count >= 2 * p;
+        for (int i = 0; ok && i < count; ++i) {
+            if (i < p) {
+                ok = on[i] >= 0 && on[i] < 8 && !(seen >> on[i] & 1);
+                if (ok) seen |= 1u << on[i];
+                m.id[i] = on[i];
+            } else {
+                ok = on[i] == on[i - p];
+            }
+        }
+        m.period = p;
+        if (ok) return m;
+    }
+    return XcdMap{};
+}
+
+}  // namespace sage

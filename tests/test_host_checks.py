@@ -25,3 +25,9 @@ def test_reduction_protocol_overwrites_nothing_that_is_still_to_be_read(tmp_path
     r = _run(exe)
     assert r.returncode == 0 and "tri_plan_check ok" in r.stdout, r.stdout
     assert _run(exe, "planted").returncode == 1
+
+
+def test_placement_on_xcds(tmp_path):
+    """xcd_check.cc: which placements of work-groups on XCDs are taken for regular."""
+    r = _run(_build(tmp_path, "xcd_check"))
+    assert r.returncode == 0 and "xcd_check ok" in r.stdout, r.stdout
