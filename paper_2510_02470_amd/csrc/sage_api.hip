@@ -26,8 +26,10 @@ enum { K_GRAM = 0, K_REDUCE, K_EIG, K_COEFF, K_REBUILD, K_INSERT, K_PROJECT, K_F
 struct SideKit {
     hipStream_t stream = nullptr;
     hipEvent_t mark = nullptr, side[2] = {nullptr, nullptr};
-    int* host = nullptr;  // pinned words: [1], [2] report of the class-balanced selection, [16] signal
+    int* host = nullptr;  // pinned words: [1], [2] report of the class-balanced selection, [16] signal, [32] .. XCD probe
     unsigned token = 0;   // of the last signal
+    bool placed = false;  // place is known:
+    XcdMap place{};       // how the stream's launches lie on the XCDs
 };
 
 // Where device memory comes from (sage_set_allocator); a context keeps the pair it was created with.
@@ -55,6 +57,7 @@ struct sage_ctx {
     hipStream_t st2 = nullptr;                   // side stream (only when the Gram has >= 2 row panels)
     hipEvent_t ev_mark = nullptr;                // context stream: the Gram matrix of the current cycle is complete
     hipEvent_t ev_side[2] = {nullptr, nullptr};  // side stream: rows stored in nw[i] and their Gram block formed
+    int hole = -1;                               // ... whose launches leave the eigensolves' XCD alone (spare_unit)
     bool pending_shrink = false;   // the buffer is full, its shrink waits for the next update call (see sage_fd_update)
     bool pre_stored = false;       // the side stream has stored the next ell rows of the running call in nw[cur]
     bool new_block_ready = false;  // ... and their Gram block is (or will be, see ev_side) in gram_partial_new[cur]
@@ -282,9 +285,9 @@ struct RowSrc {
 };
 
 hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int half_rows, const Dims& d, bool to16,
-                       hipStream_t st, int skip = -1) {
-    if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, to16, skip, st);
-    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, to16, skip, st);
+                       hipStream_t st, int hole = -1) {
+    if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, to16, hole, st);
+    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, to16, hole, st);
 }
 
 // Before the top half is read while the stream has not filled it yet: its other rows count as zero.
@@ -340,6 +343,8 @@ std::mutex g_xcd_lock;
 XcdSlot g_xcd[MAX_DEVICES][8];
 
 constexpr int KITS_KEPT = 4;  // per device
+constexpr int PROBED = 512;   // work-groups of the XCD probe
+constexpr int KIT_WORDS = 32 + PROBED;
 std::mutex g_kit_lock;
 SideKit g_kit[MAX_DEVICES][KITS_KEPT];
 int g_kits[MAX_DEVICES] = {0};
@@ -364,7 +369,7 @@ bool kit_take(int device, SideKit& k) {
     bool ok = hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking) == hipSuccess;
     for (hipEvent_t* e : {&k.mark, &k.side[0], &k.side[1]})
         ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipHostMalloc((void**)&k.host, 32 * sizeof(int), hipHostMallocDefault) == hipSuccess;
+    ok = ok && hipHostMalloc((void**)&k.host, KIT_WORDS * sizeof(int), hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         kit_destroy(k);
@@ -387,21 +392,32 @@ void kit_give(int device, SideKit& k, bool reuse) {
 }
 
 // The XCD for a context's reductions; where there is no telling which work-groups share one, it needs none.
-void xcd_take(sage_ctx* c) {
-    if (c->d.NP < 128 || c->device < 0 || c->device >= MAX_DEVICES) return;
-    const XcdMap& map = xcd_map();
-    c->ew.period = map.period;
-    if (map.period == 0) return;
-    std::lock_guard<std::mutex> hold(g_xcd_lock);
-    const int first = (int)(getpid() % map.period);  // other processes on the GPU most likely start at another one
-    int best = first;
-    for (int i = 1; i < map.period; ++i) {
-        const int x = (first + i) % map.period;
-        if (g_xcd[c->device][x].users < g_xcd[c->device][best].users) best = x;
+int xcd_take(sage_ctx* c) {
+    if (c->d.NP < 128 || c->device < 0 || c->device >= MAX_DEVICES) return SAGE_OK;
+    SideKit& k = c->kit;
+    if (!k.placed) {
+        HIPCHK(launch_xcd_probe(k.host + 32, PROBED, k.stream));
+        HIPCHK(hipStreamSynchronize(k.stream));
+        k.place = xcd_map_of(k.host + 32, PROBED);
+        k.placed = true;
     }
+    const XcdMap& map = k.place;
+    c->ew.period = map.period;
+    if (map.period == 0) return SAGE_OK;
+    std::lock_guard<std::mutex> hold(g_xcd_lock);
+    int best = -1;
+    for (int i = 0; i < 8; ++i) {
+        const int x = ((int)(getpid() & 7) + i) & 7;  // other processes on the GPU most likely start at another one
+        bool there = false;
+        for (int p = 0; p < map.period; ++p) there = there || map.id[p] == x;
+        if (there && (best < 0 || g_xcd[c->device][x].users < g_xcd[c->device][best].users)) best = x;
+    }
+    for (int p = 0; p < 8 && map.period == 8; ++p)
+        if (map.id[p] == best) c->hole = p;
     g_xcd[c->device][best].users += 1;
     c->xcd_slot = best;
-    c->ew.xcd = map.id[best];
+    c->ew.xcd = best;
+    return SAGE_OK;
 }
 void xcd_release(sage_ctx* c) {
     if (c->xcd_slot < 0) return;
@@ -495,10 +511,10 @@ int side_ahead(sage_ctx* c, const RowSrc* next) {
     HIPCHK(hipEventRecord(c->ev_mark, c->st));
     HIPCHK(hipStreamWaitEvent(c->st2, c->ev_mark, 0));
     if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
-    const int skip = c->ew.period == 8 ? c->ew.xcd : -1;
-    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, skip));
+    const int hole = c->ew.period > 0 ? c->hole : -1;
+    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, hole));
     c->gp_side_used[o] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
-    HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), skip));
+    HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), hole));
     HIPCHK(hipEventRecord(c->ev_side[o], c->st2));
     return SAGE_OK;
 }
@@ -771,7 +787,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.K, &w.dc.k1, &w.dc.dense}) take(*p, n1);
             if (pass == 0) CALLOC(c->eig_mem, bytes);
         }
-        xcd_take(c);
+        if (int rc = xcd_take(c); rc != SAGE_OK) return fail(rc);
     }
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
@@ -1496,7 +1512,7 @@ int sage_debug_impatient_solves(sage_ctx* c, int on) {
     ALIVE(c);
     if (on < 0 || on > 2) return SAGE_ERR_ARG;
     c->ew.impatient = on == 1;
-    c->ew.period = on == 2 || c->xcd_slot < 0 ? 0 : xcd_map().period;
+    c->ew.period = on == 2 || c->xcd_slot < 0 ? 0 : c->kit.place.period;
     return SAGE_OK;
 }
 

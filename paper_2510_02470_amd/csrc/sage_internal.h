@@ -81,32 +81,22 @@ __host__ __device__ inline const u32x4* half16(const float* half, int LP, int64_
 // ---- kernel launchers (each enqueues on `st` and returns hipGetLastError()) ---------------------------------
 // launch_util.hip: raise a kernel's dynamic LDS limit, once per (device, kernel); thread-safe
 hipError_t ensure_dynamic_lds(const void* kernel, int bytes);
-// The XCD this work-group runs on, 0..7. Nothing may be concluded from blockIdx alone: which XCD the first work-group gets
-// differs from queue to queue.
+// The XCD this work-group runs on, 0..7.
 __device__ __forceinline__ int xcd_id() {
     int id;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(id));
     return id & 7;
 }
-// Work that runs beside an eigensolve keeps off the XCD the reduction has to itself: work-groups on XCD `skip` return at once
-// and the others take the work between them (skip = -1: all eight).
-// xcd_rank: this work-group's number among those that work, or -1.
-__device__ __forceinline__ int64_t xcd_rank(unsigned block, int skip) {
-    if (skip < 0) return block;
-    const int x = xcd_id();
-    if (x == skip) return -1;
-    return (int64_t)(block >> 3) * 7 + x - (x > skip);
-}
-inline int64_t xcd_grid(int64_t work, int skip) { return skip < 0 ? work : (work + 6) / 7 * 8; }  // work-groups to launch
+// Work that runs beside an eigensolve keeps off the XCD that the reduction has to itself: `hole`, see spare_unit.
 // fd_insert.hip
 // copy `rows` batch rows into rows row0.. of a half buffer (half_rows rows per slab)
 // (to16: in pieces of bf16, see half16; rows of bf16 only)
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         bool to16, int skip, hipStream_t st);
+                         bool to16, int hole, hipStream_t st);
 // factored rows (E: rows x C logit errors, H: rows x dh features, both of the row type): column c*dh + t = e_c * h_t
 // rounded as a stored row would be, column C*dh + c = e_c; requires D = C * (dh + 1)
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, bool to16, int skip, hipStream_t st);
+                               float* half, int half_rows, const Dims& d, bool to16, int hole, hipStream_t st);
 hipError_t launch_widen(float* half, const Dims& d, hipStream_t st);  // pieces of bf16 -> the fp32 half
 // ... written out row-major (rows x D of the row type)
 hipError_t launch_expand_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, void* out,
@@ -138,7 +128,7 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
 // new_one (split-arithmetic kernels): the new half is kept in pieces of bf16 (half16): one part instead of three, the result
 // has the same bits
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
-                       hipStream_t st, bool new_one = false, int skip = -1);
+                       hipStream_t st, bool new_one = false, int hole = -1);
 // C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
 // (the Gram matrix of the rows the last shrink wrote, see EigWork::known)
 hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const float* partial_b, const GramPlan* b,
@@ -175,7 +165,8 @@ struct EigWork {
 inline int dc_result(int NP) { return (NP == 128 || NP == 512) ? 1 : 0; }
 // Matrix indices in use: 0 .. m0-1 and LP .. LP + (n - m0) - 1, n in all (the others are zero rows and columns); the count
 // leading eigenvectors are formed.
-const XcdMap& xcd_map();  // asks the current device (once)
+// out (`count` words of host memory that the device can write) receives the XCD of every work-group
+hipError_t launch_xcd_probe(int* out, int count, hipStream_t st);
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
 // Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Mc3 (split

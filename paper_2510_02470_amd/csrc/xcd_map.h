@@ -4,9 +4,9 @@
 
 namespace sage {
 
-// Work-groups i and i + period of a launch run on the same XCD and `period` consecutive ones on different XCDs: those of
-// `id` (which of them the first gets differs from queue to queue). 8 on the whole chip, the number of XCDs of a
-// partition otherwise; 0: neither can be said.
+// Work-group i of a launch runs on XCD id[i % period], period different ones. 8 on the whole chip, the number of XCDs of a
+// partition otherwise; 0: it cannot be said. The first XCD differs from stream to stream and is the same for all launches on one
+// (tried on seven streams, 40 launches each of 1 to 1024 work-groups). Nothing that decides a result may rest on this.
 struct XcdMap {
     int period = 0;
     int id[8] = {};
@@ -32,5 +32,15 @@ inline XcdMap xcd_map_of(const int* on, int count) {
     }
     return XcdMap{};
 }
+
+// A launch that leaves one XCD alone: of eight work-groups the one at place `hole` has nothing to do and the others share
+// the units of work between them, in order. -1: all eight work. (Which work-groups these are is a matter of their numbers
+// only, so all units are done wherever they run.)
+constexpr long long spare_unit(unsigned block, int hole) {
+    if (hole < 0) return block;
+    const int place = (int)(block & 7u);
+    return place == hole ? -1 : (long long)(block >> 3) * 7 + place - (place > hole);
+}
+constexpr long long spare_grid(long long units, int hole) { return hole < 0 ? units : (units + 6) / 7 * 8; }  // work-groups
 
 }  // namespace sage

@@ -28,6 +28,7 @@ def test_reduction_protocol_overwrites_nothing_that_is_still_to_be_read(tmp_path
 
 
 def test_placement_on_xcds(tmp_path):
-    """xcd_check.cc: which placements of work-groups on XCDs are taken for regular."""
+    """xcd_check.cc: which placements of work-groups on XCDs are taken for regular; and a launch that leaves one XCD alone does
+    every unit of its work once, by the numbers of its work-groups alone, wherever they run."""
     r = _run(_build(tmp_path, "xcd_check"))
     assert r.returncode == 0 and "xcd_check ok" in r.stdout, r.stdout

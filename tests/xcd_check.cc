@@ -1,4 +1,4 @@
-// The placement of work-groups on XCDs (csrc/xcd_map.h).
+// The placement of work-groups on XCDs, and the work of launches that leave one alone (csrc/xcd_map.h).
 #include <cstdio>
 #include <vector>
 
@@ -29,8 +29,25 @@ static void check_map() {
     REQUIRE(xcd_map_of(on.data(), 512).period == 0);
 }
 
+// every unit once, whatever the number of units and the place left out
+static void check_spare() {
+    for (int hole = -1; hole < 8; ++hole)
+        for (long long units = 0; units <= 300; ++units) {
+            std::vector<int> done(units, 0);
+            const long long grid = spare_grid(units, hole);
+            REQUIRE(hole < 0 || grid % 8 == 0);
+            for (long long b = 0; b < grid; ++b) {
+                const long long u = spare_unit((unsigned)b, hole);
+                REQUIRE(u >= -1 && (u >= 0 || (int)(b & 7) == hole));
+                if (u >= 0 && u < units) ++done[u];
+            }
+            for (int d : done) REQUIRE(d == 1);
+        }
+}
+
 int main() {
     check_map();
+    check_spare();
     if (!failures) printf("xcd_check ok\n");
     return failures ? 1 : 0;
 }
