@@ -385,19 +385,19 @@ __device__ __forceinline__ void tri_alone(const double* __restrict__ C, int NP, 
     }
 }
 
-// The end of a reduction: what follows the last row in use. The rows of V that complete the last block of reflectors are zero; the
+// What follows the last row in use of a reduction's results, by threads 0 .. step - 1. The rows of V that complete the last block of reflectors are zero; the
 // padding of T is decoupled and below every eigenvalue of a Gram matrix.
 template <int J>
 __device__ __forceinline__ void tri_finish(int n, double* __restrict__ dT, double* __restrict__ eT, double* __restrict__ tauT,
-                                           double* __restrict__ V) {
+                                           double* __restrict__ V, int tid, int step) {
     constexpr int N = 64 * J;
-    for (int i = n - 1 + (int)threadIdx.x; i < N; i += 512) {
+    for (int i = n - 1 + tid; i < N; i += step) {
         if (i >= n) dT[i] = -1.0;
         eT[i] = 0.0;
         tauT[i] = 0.0;
     }
     for (int k = n - 1; k % WY != 0; ++k)
-        for (int i = threadIdx.x; i < N; i += 512) V[(int64_t)k * N + i] = 0.0;
+        for (int i = tid; i < N; i += step) V[(int64_t)k * N + i] = 0.0;
 }
 
 __device__ __forceinline__ void put_entry(u32x4* p, double v, unsigned tag) {
@@ -437,11 +437,12 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         const int t = tid & (J >= 4 ? 255 : 127);
         const bool for_c = J >= 4 || wave < 6;
         int spins = polls;
+        if (closes) tri_finish<J>(n, dT, eT, tauT, V, tid - 256, 256);
         for (int k = 0; k < steps; ++k) {
             const int par = k & 1;
             const unsigned tag = tag0 + (unsigned)k;
             // all of this thread's entries of a vector in one round trip; it is done with the entries of rows <= k
-            // (in a last step that is not waited for, the waves that compute get NaN: nothing comes of it)
+            // (in a last step that is not waited for, the waves that compute get zeros: nothing comes of it)
             auto poll = [&](const u32x4* src, double (&val)[PT]) __attribute__((always_inline)) {
                 u32x4 e[PT];
 #pragma unroll
@@ -474,13 +475,16 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                         if (more && --spins <= 0) {
                             spins = 1;  // every further wait gives up after one round
                             more = false;
+#pragma unroll
+                            for (int u = 0; u < PT; ++u)
+                                if (!fresh(e[u], tag)) e[u][2] = 0x7FF80000u;  // NaN
                         }
                     } while (more);
                 }
 #pragma unroll
                 for (int u = 0; u < PT; ++u) {
                     const int i = t + 256 * u;
-                    val[u] = i > k && i < n ? (fresh(e[u], tag) ? entry_value(e[u]) : __builtin_nan("")) : 0.0;
+                    val[u] = i > k && i < n ? entry_value(e[u]) : 0.0;
                 }
             };
             const u32x4* const qx = xch + par * 2 * N + t;
@@ -671,14 +675,15 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
     else if (NW == 64 || gw < 64) reduce(std::integral_constant<int, 0>{});
     else reduce(std::integral_constant<int, NW / 64 - 1>{});
     if (!closes) return;
-    __syncthreads();
+    lds_barrier();
     if (gave_up) {  // (or the matrix is not finite: then so is this, and it does no harm)
+        __syncthreads();
         if (tid == 0) *redone += 1.0;
         const double sc = __builtin_amdgcn_ldexp(1.0, -tri_exponent(wave_max_diag(C, NP, lane)));
         tri_alone<J>(C, NP, m0, LP, n, dT, eT, tauT, V, sc, &vs[0][0]);
         __syncthreads();
+        tri_finish<J>(n, dT, eT, tauT, V, tid, 512);
     }
-    tri_finish<J>(n, dT, eT, tauT, V);
 }
 
 // ---- Y = H Z --------------------------------------------------------------------------------------------------------
