@@ -377,7 +377,7 @@ int sage_debug_fail_launch(sage_ctx* ctx, int nth);
 /*
  * Test hook for solves that cannot be done by several work-groups together (see n_unconverged). on = 1: those of the
  * reduction give each other up after a single look; 2: one work-group does it all, as on a device where it cannot be told which
- * work-groups share an XCD; 0: the usual way. Everything ends normally.
+ * work-groups share an XCD; 3: none of them runs where it is expected; 0: the usual way. Everything ends normally.
  */
 int sage_debug_impatient_solves(sage_ctx* ctx, int on);
 

@@ -41,4 +41,15 @@ struct TriPlan {
     static constexpr bool closes(int wg, int n) { return last_column(wg, n) == n - 1; }
 };
 
+// Every role is given to `period` work-groups, of which one is expected on the XCD of the solve and the others leave. So that a
+// solve has its results whatever the placement, those of the closing role add to a word that is zero before: with `here`, on the
+// XCD. The first one there closes the solve; if none is, the last to come does all of it alone. The last one clears the word.
+enum TriClaim { CLAIM_LEAVE, CLAIM_CLOSE, CLAIM_ALONE };
+constexpr unsigned claim_add(bool here) { return here ? 0x101u : 1u; }
+constexpr bool claim_last(unsigned word, int period) { return (int)(word & 0xFFu) == period; }
+constexpr TriClaim claim_role(unsigned word, bool here, int period) {  // word: with one's own addition
+    if (here) return (word >> 8) == 1u ? CLAIM_CLOSE : CLAIM_LEAVE;
+    return claim_last(word, period) && (word >> 8) == 0u ? CLAIM_ALONE : CLAIM_LEAVE;
+}
+
 }  // namespace sage

@@ -286,7 +286,7 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 // entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough, because a
 // work-group leaves as soon as it has nothing left to publish (fd_tri_plan.h).
 // Stores: the L1 is write-through, so a plain store reaches the XCD's L2. Of the work-groups launched, one in `period` lands on
-// the XCD of the solve and stays, in the role of its number.
+// the XCD of the solve and stays, in the role of its number (see TriClaim for what happens if none does).
 // Waves 0..3 compute and publish, waves 4..7 only poll and hand over through LDS: loads and stores of a wave retire in
 // order, so one that did both would wait, with every poll, for its own stores. They wait for c first, which is out before
 // the products are formed, then for q: a poll of one vector takes 550 cycles, of both 830.
@@ -416,20 +416,32 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, u32x4* __restrict__ xch,
                                                           unsigned tag0, int xcd, int shift, int polls,
-                                                          double* __restrict__ redone) {
+                                                          double* __restrict__ redone, unsigned* __restrict__ claim) {
     using Plan = TriPlan<J>;
     constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW;
-    if (xcd >= 0 && xcd_id() != xcd) return;
-    __builtin_amdgcn_s_setprio(3);
+    // (xcd < 0: there is one work-group, in the closing role)
+    const int wg = xcd >= 0 ? blockIdx.x >> shift : Plan::wave_of(n - 1) >> 2;
+    const bool here = xcd < 0 || xcd_id() == xcd;
+    const bool closes = Plan::closes(wg, n);  // this work-group stores what the solve's next stages read
+    if (!here && !closes) return;
+    if (here) __builtin_amdgcn_s_setprio(3);
     __shared__ Pair qc[2][N];  // {q, c} by step parity
     __shared__ double vs[4][N];
     __shared__ bool gave_up;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wg = xcd >= 0 ? blockIdx.x >> shift : Plan::wave_of(n - 1) >> 2;  // (xcd < 0: the only work-group)
     if (Plan::last_column(wg, n) < 0) return;
     const int steps = Plan::steps(wg, n), waits = Plan::waits(wg, n);  // waits >= steps - 1
-    const bool closes = Plan::closes(wg, n);  // this work-group stores what the solve's next stages read
+    __shared__ TriClaim role;
+    if (closes && tid == 256) {  // (a thread that waits anyway)
+        role = CLAIM_CLOSE;
+        if (xcd >= 0) {
+            const unsigned mine = claim_add(here);
+            const unsigned word = mine + __hip_atomic_fetch_add(claim, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            role = claim_role(word, here, 1 << shift);
+            if (claim_last(word, 1 << shift)) __hip_atomic_store(claim, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
 
     auto wait_for_entries = [&]() __attribute__((always_inline)) {  // waves 4 ..: entries t, t + 256, .. of c and q
         // J = 2: half the waves wait for c and half for q
@@ -512,7 +524,6 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         const double md = wave_max_diag(C, NP, lane);
         const int ex = tri_exponent(md);
         const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
-        if (closes && tid == 0) stat[0] = (double)ex;
         {
             int mrow[J];
 #pragma unroll
@@ -666,21 +677,27 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, e2.b));
         }
         if (closes && tid == 0) {  // (waits = n - 1: xk is the last step's)
+            stat[0] = (double)ex;
             dT[n - 1] = xk;
             gave_up = xk != xk;
         }
     };
     static_assert(NW == 64 || NW == 128, "one or two columns a lane");
-    if (wave >= 4) wait_for_entries();
+    if (!here) gave_up = true;
+    else if (wave >= 4) wait_for_entries();
     else if (NW == 64 || gw < 64) reduce(std::integral_constant<int, 0>{});
     else reduce(std::integral_constant<int, NW / 64 - 1>{});
     if (!closes) return;
     lds_barrier();
+    if (role == CLAIM_LEAVE) return;
     if (gave_up) {  // (or the matrix is not finite: then so is this, and it does no harm)
         __syncthreads();
-        if (tid == 0) *redone += 1.0;
-        const double sc = __builtin_amdgcn_ldexp(1.0, -tri_exponent(wave_max_diag(C, NP, lane)));
-        tri_alone<J>(C, NP, m0, LP, n, dT, eT, tauT, V, sc, &vs[0][0]);
+        const int ex = tri_exponent(wave_max_diag(C, NP, lane));
+        if (tid == 0) {
+            *redone += 1.0;
+            stat[0] = (double)ex;
+        }
+        tri_alone<J>(C, NP, m0, LP, n, dT, eT, tauT, V, __builtin_amdgcn_ldexp(1.0, -ex), &vs[0][0]);
         __syncthreads();
         tri_finish<J>(n, dT, eT, tauT, V, tid, 512);
     }
@@ -910,7 +927,7 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
 #define SAGE_TRI_MANY(J)                                                                                           \
     hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, \
                        w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, w.epoch << 10, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
-                       alone || w.impatient ? 1 : SPIN_LIMIT, w.redone)
+                       alone || w.impatient ? 1 : SPIN_LIMIT, w.redone, w.claim)
     const bool alone = w.period == 0;
     switch (NP / 64) {
         case 1: SAGE_TRI_ONE(1); break;

@@ -793,6 +793,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
     CALLOC(c->acc, 8 * sizeof(double));
     c->ew.redone = c->acc + 4;
+    c->ew.claim = (unsigned*)(c->ew.stat + 16);
 #undef CALLOC
     // Rows of the top half that the stream never fills are zero. (Those it has not filled yet are cleared when something
     // looks at them, see clear_top; rows of a new half beyond its fill are never used.)
@@ -1510,8 +1511,9 @@ int sage_debug_fail_launch(sage_ctx* c, int nth) {
 
 int sage_debug_impatient_solves(sage_ctx* c, int on) {
     ALIVE(c);
-    if (on < 0 || on > 2) return SAGE_ERR_ARG;
+    if (on < 0 || on > 3) return SAGE_ERR_ARG;
     c->ew.impatient = on == 1;
+    if (c->xcd_slot >= 0) c->ew.xcd = on == 3 ? 8 : c->xcd_slot;
     c->ew.period = on == 2 || c->xcd_slot < 0 ? 0 : c->kit.place.period;
     return SAGE_OK;
 }

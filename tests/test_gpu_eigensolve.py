@@ -144,12 +144,12 @@ def test_solves_beside_other_work_on_the_gpu(ell):
     assert busy.stats().n_unconverged == 0
 
 
-@pytest.mark.parametrize("how", [1, 2])
+@pytest.mark.parametrize("how", [1, 2, 3])
 @pytest.mark.parametrize("ell", [64, 128, 256])
 def test_solves_that_their_work_groups_cannot_do_together(ell, how):
     """1: the work-groups of the reduction give each other up after one look, as they do after a long wait where other work keeps
     them from running together, and one repeats the solve. 2: one does it from the start (at ell = 64 a kernel of its own), as
-    where they cannot be placed on one XCD. Every solve succeeds, to the bars of the usual way."""
+    where they cannot be placed on one XCD. 3: none is on the XCD it is expected on. Every solve succeeds, to the bars of the usual way."""
     import torch
 
     from paper_2510_02470_amd.binding import Sage

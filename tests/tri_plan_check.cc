@@ -75,11 +75,33 @@ void check(int n) {
     REQUIRE(closing == 1, "%d work-groups store the results", closing);
 }
 
+// the work-groups of the closing role in every order of being on the XCD or not: one of them has the results to store
+static void check_claims() {
+    constexpr int J = 0;
+    for (int period = 1, n = 0; period <= 8; period *= 2)
+        for (unsigned on = 0; on < 1u << period; ++on) {
+            unsigned word = 0;
+            int closing = 0, alone = 0, last = 0;
+            for (int i = 0; i < period; ++i) {
+                const bool here = on >> i & 1u;
+                word += sage::claim_add(here);
+                const sage::TriClaim r = sage::claim_role(word, here, period);
+                closing += r == sage::CLAIM_CLOSE;
+                alone += r == sage::CLAIM_ALONE;
+                last += sage::claim_last(word, period);
+                REQUIRE(r != sage::CLAIM_CLOSE || here, "a work-group elsewhere closes");
+                REQUIRE(!sage::claim_last(word, period) || i == period - 1, "the word is cleared early");
+            }
+            REQUIRE(closing == (on != 0) && alone == (on == 0) && last == 1, "period %d, pattern %x", period, on);
+        }
+}
+
 int main(int argc, char** argv) {
     planted = argc > 1 && !strcmp(argv[1], "planted");
     for (int n = 1; n <= 128; ++n) check<2>(n);
     for (int n = 1; n <= 256; ++n) check<4>(n);
     for (int n = 1; n <= 512; ++n) check<8>(n);
+    check_claims();
     if (failures) printf("%d failures\n", failures);
     else printf("tri_plan_check ok\n");
     return failures ? 1 : 0;
