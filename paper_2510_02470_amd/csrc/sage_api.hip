@@ -330,13 +330,14 @@ int note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
 bool new_one(const sage_ctx* c, int i) { return c->one_part && c->nw_bf16[i] && (c->d.NP < 512 || c->nw_half[i]); }
 
 // The reduction of a 128-, 256- or 512-row eigensolve keeps 16 or 32 work-groups of one XCD in step, so all of them must be
-// resident together (where they are not, the solve takes milliseconds longer). Contexts are spread over the XCDs; when two share one, their reductions are ordered by an event, so
-// that at most two (one launched before the second context appeared, one in the chain) are ever in flight on an XCD, and
-// two fit on its CUs side by side.
+// resident together (where they are not, the solve takes milliseconds longer), and at 512 rows they fill the registers of
+// its 32 CUs. Contexts are spread over the XCDs; where two share one, each reduction waits for the one before it on that
+// XCD, by an event that is recorded after it, or, if the XCD was not shared yet, when the other context comes to wait.
 struct XcdSlot {
     int users = 0;
-    hipEvent_t last = nullptr;  // kept for the life of the process (at most 8 per device)
-    const void* owner = nullptr;
+    hipEvent_t last = nullptr;        // kept for the life of the process (at most 8 per device)
+    const sage_ctx* owner = nullptr;  // whose reduction was the last one
+    bool marked = false;              // ... and `last` is recorded after it
 };
 constexpr int MAX_DEVICES = 64;
 std::mutex g_xcd_lock;
@@ -438,18 +439,19 @@ hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf
     std::unique_lock<std::mutex> hold(g_xcd_lock);
     XcdSlot& x = g_xcd[c->device][c->xcd_slot];
     const bool shared = x.users > 1;
-    if (!shared) hold.unlock();
     if (shared) {
         if (!x.last && hipEventCreateWithFlags(&x.last, hipEventDisableTiming) != hipSuccess) return hipErrorUnknown;
-        if (x.owner && x.owner != c)
+        if (x.owner && x.owner != c) {
+            if (!x.marked)
+                if (hipError_t e = hipEventRecord(x.last, x.owner->st); e != hipSuccess) return e;
             if (hipError_t e = hipStreamWaitEvent(c->st, x.last, 0); e != hipSuccess) return e;
+        }
     }
     hipError_t e = launch_tridiag(c->ew, c->d.NP, m0, n, c->st);
-    if (shared) {
-        if (e == hipSuccess) e = hipEventRecord(x.last, c->st);
-        x.owner = c;
-        hold.unlock();
-    }
+    if (shared && e == hipSuccess) e = hipEventRecord(x.last, c->st);
+    x.owner = c;
+    x.marked = shared;
+    hold.unlock();
     if (e == hipSuccess) e = launch_dc(c->ew, c->d.NP, n, c->st);
     if (e == hipSuccess) e = launch_tri_back(c->ew, c->d.NP, m0, n, count, cf, c->st);
     return e;

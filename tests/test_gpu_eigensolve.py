@@ -77,7 +77,38 @@ def test_contexts_in_several_streams_share_the_gpu():
             st.synchronize()
         # one call or five: the same rows, the last bits of the Gram blocks may differ
         assert torch.allclose(got.T @ got, want.T @ want, rtol=0, atol=1e-5 * float((want.T @ want).abs().max()))
+        assert c.stats().n_unconverged == 0    # (nobody had to wait for work-groups that could not run beside another's)
         c.close()
+
+
+def test_a_context_joins_an_xcd_whose_reductions_are_in_flight():
+    """Eight contexts, one an XCD, have many solves enqueued when eight more are created and start theirs: each of those
+    comes after what is in flight on its XCD, and no solve is held up until it is given up."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(5)
+    G = torch.randn((256 * 12, 600), generator=g, device="cuda")
+    torch.cuda.synchronize()
+    st = [torch.cuda.Stream() for _ in range(16)]
+    ctx = []
+    for i, t in enumerate(st):
+        with torch.cuda.stream(t):
+            ctx.append(Sage(256, 600))
+            if i < 8:
+                ctx[i].fd_update(G)
+    for t, c in zip(st[8:], ctx[8:]):
+        with torch.cuda.stream(t):
+            c.fd_update(G)
+    want = None
+    for t, c in zip(st, ctx):
+        with torch.cuda.stream(t):
+            B = c.sketch()
+            assert c.stats().n_unconverged == 0
+            want = B if want is None else want
+            assert torch.equal(B, want)
+            c.close()
 
 
 @pytest.mark.parametrize("ell", [64, 128, 256])
