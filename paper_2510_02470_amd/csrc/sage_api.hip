@@ -376,6 +376,7 @@ bool kit_take(int device, SideKit& k) {
         kit_destroy(k);
         return false;
     }
+    memset(k.host, 0, KIT_WORDS * sizeof(int));  // (the signal word must not hold a token to come)
     return true;
 }
 // (everything enqueued with it is complete)
