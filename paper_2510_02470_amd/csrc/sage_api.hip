@@ -39,6 +39,13 @@ struct Allocator {
     void* user = nullptr;
 };
 
+// Chunk images of the basis for the bf16 projection (score_split.hip), built when rows first ask for them.
+struct BasisImages {
+    void* mem = nullptr;
+    size_t bytes = 0;
+    bool current = false;  // they are of the basis in Vblk
+};
+
 struct sage_ctx {
     Allocator mem{};
     Dims d{};
@@ -101,10 +108,8 @@ struct sage_ctx {
     int k = 0, KP = 0;
     float* Vblk = nullptr;
     int Vblk_KP = 0;
-    void* Vimg = nullptr;      // bf16 hi/lo chunk images of the basis (score_split.hip); built when the rows allow it
-    size_t Vimg_bytes = 0;
-    bool img_ok = false;       // ... and usable for row-major batches of this D
-    int img_parts = 0;         // the images hold the current basis in this many parts (0: they do not)
+    BasisImages img[2];        // in two and in three bf16 parts
+    bool img_ok = false;       // those of two parts serve row-major batches of this D
     void* stage = nullptr;     // factored rows written out, for shapes the factored projection does not take
     size_t stage_bytes = 0;
     int proj_mode = SAGE_PROJ_AUTO;
@@ -614,22 +619,29 @@ int ensure_vblk(sage_ctx* c, int KP) {
     return SAGE_OK;
 }
 
-// The bf16 hi/lo images of the basis in Vblk (score_split.hip).
+// The images of the basis in Vblk in so many bf16 parts (score_split.hip). Either number has memory of its own, so that a pass
+// that takes factored rows and row-major rows of another alignment in turn does not make them anew each time; where there is not
+// room for both, the other one's is given up.
 int ensure_images(sage_ctx* c, int parts) {
-    if (c->img_parts == parts) return SAGE_OK;
+    BasisImages& im = c->img[parts - 2];
+    if (im.current) return SAGE_OK;
     const size_t need = basis_image_bytes(c->KP, c->dtype, parts, c->d);
-    if (need > c->Vimg_bytes) {
-        if (c->Vimg) {
+    if (need > im.bytes) {
+        BasisImages& other = c->img[3 - parts];
+        if (im.mem) HIPCHK(hipStreamSynchronize(c->st));
+        FREE(im.mem);
+        im.bytes = 0;
+        if (!dev_alloc(c->mem, c->st, &im.mem, need)) {
+            if (!other.mem) return SAGE_ERR_ALLOC;
             HIPCHK(hipStreamSynchronize(c->st));
-            FREE(c->Vimg);
-            c->Vimg_bytes = 0;
+            FREE(other.mem);
+            other = BasisImages{};
+            ALLOC(im.mem, need);
         }
-        ALLOC(c->Vimg, need);
-        c->Vimg_bytes = need;
+        im.bytes = need;
     }
-    c->img_parts = 0;
-    RUN(K_REBUILD, launch_basis_split(c->Vblk, c->KP, c->dtype, parts, c->Vimg, c->d, c->st));
-    c->img_parts = parts;
+    RUN(K_REBUILD, launch_basis_split(c->Vblk, c->KP, c->dtype, parts, im.mem, c->d, c->st));
+    im.current = true;
     return SAGE_OK;
 }
 
@@ -637,7 +649,7 @@ int ensure_images(sage_ctx* c, int parts) {
 // this D (factored rows, and rows of other widths, build theirs on first use).
 int finish_basis(sage_ctx* c) {
     c->img_ok = false;
-    c->img_parts = 0;
+    for (BasisImages& im : c->img) im.current = false;
     if (c->proj_mode == SAGE_PROJ_F32) return SAGE_OK;
     if (!split_path_ok(nullptr, c->dtype, c->d)) return SAGE_OK;  // nullptr is "aligned": only D is judged here
     int rc = ensure_images(c, 2);
@@ -815,7 +827,7 @@ void sage_destroy(sage_ctx* c) {
     (void)hipStreamSynchronize(c->st);
     if (c->st2) (void)hipStreamSynchronize(c->st2);
     void* ptrs[] = {c->top,     c->nw[0],    c->nw[1],  c->gram_partial, c->gram_partial_new[0], c->gram_partial_new[1],
-                    c->eig_mem, c->Mt,       c->acc,    c->Vblk,         c->Vimg,
+                    c->eig_mem, c->Mt,       c->acc,    c->Vblk,         c->img[0].mem, c->img[1].mem,
                     c->zhat,    c->proj_partial, c->cons_partial, c->ssum, c->alpha, c->labels, c->cb_work, c->stage, c->Mt3, c->dbg_count};
     for (void* p : ptrs) dev_free(c->mem, p);
     xcd_release(c);
@@ -1052,7 +1064,7 @@ static int project_rows(sage_ctx* c, const RowSrc& src, int64_t R, int* slots) {
             ScorePlan p = score_outer_plan(R, src.dtype, src.C, src.dh, c->num_cu);
             rc = ensure_partial(c, (size_t)(p.splits + p.bias_slots) * R * c->KP);
             if (rc != SAGE_OK) return rc;
-            RUN(K_PROJECT, launch_project_outer(src.E, src.H, src.dtype, R, src.C, src.dh, c->stage, c->Vimg, c->Vblk,
+            RUN(K_PROJECT, launch_project_outer(src.E, src.H, src.dtype, R, src.C, src.dh, c->stage, c->img[0].mem, c->Vblk,
                                                 c->KP, c->proj_partial, p, c->st));
             *slots = p.splits + p.bias_slots;
             return SAGE_OK;
@@ -1072,7 +1084,7 @@ static int project_rows(sage_ctx* c, const RowSrc& src, int64_t R, int* slots) {
     int rc = ensure_partial(c, (size_t)p.splits * R * c->KP);
     if (rc != SAGE_OK) return rc;
     if (parts)
-        RUN(K_PROJECT, launch_project_split(g, c->dtype, R, parts, c->Vimg, c->KP, c->proj_partial, p, c->d, c->st));
+        RUN(K_PROJECT, launch_project_split(g, c->dtype, R, parts, c->img[parts - 2].mem, c->KP, c->proj_partial, p, c->d, c->st));
     else
         RUN(K_PROJECT, launch_project(g, c->dtype, R, c->Vblk, c->KP, c->proj_partial, p, c->d, c->st));
     *slots = p.splits;

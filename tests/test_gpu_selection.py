@@ -115,3 +115,37 @@ def test_scores_export_at_the_edges_of_its_variants(N):
     np.testing.assert_allclose(alpha, z @ (u / np.linalg.norm(u)), atol=2e-5)
     assert idx.tolist() == oracle.topm_f32(alpha, len(idx)).tolist()
     s.close()
+
+
+def test_factored_and_unaligned_rows_in_turn():
+    """A pass that takes factored rows (a basis of two parts) and row-major rows of an unaligned width (three parts) in turn:
+    the images of the basis are made once each, and a new basis replaces both."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    rng = np.random.default_rng(0)
+    C, dh, n = 3, 128, 200
+    D = C * (dh + 1)  # 387: rows start on no multiple of 16 bytes
+    E, H, G = (torch.from_numpy(rng.standard_normal((n, w)).astype(np.float32)).cuda() for w in (C, dh, D))
+    bases = [torch.from_numpy(rng.standard_normal((k, D)).astype(np.float32)).cuda() for k in (6, 6, 40)]
+
+    def alone(V, outer):
+        s = Sage(80, D)
+        s.set_basis(V)
+        s.score_outer(E, H) if outer else s.score(G)
+        return s.zhat()
+
+    s = Sage(80, D)
+    for V in bases:
+        want = torch.cat([alone(V, True), alone(V, False)] * 3)
+        s.set_basis(V)
+        s.score_outer(E, H)
+        s.score(G)
+        s.profile_enable(True)
+        for _ in range(2):
+            s.score_outer(E, H)
+            s.score(G)
+        assert s.profile_read()["rebuild"][1] == 0
+        s.profile_enable(False)
+        assert torch.equal(s.zhat(), want)
