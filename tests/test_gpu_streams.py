@@ -231,3 +231,32 @@ def test_one_part_shortcut_is_dropped_for_rows_that_are_not_bf16_values():
     st = out[0][2]
     assert st.n_shrinks == o.n_shrinks and st.fill == o.fill
     assert cov_diff_spec_norm(out[0][0].cpu().numpy(), o.B) / fro <= COV_TOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ell,rows,D", [(256, 511, 6001), (256, 300, 700), (200, 201, 1000), (193, 385, 2064), (256, 257, 65)])
+def test_first_gram_and_pending_norms_against_64_bits(dtype, ell, rows, D):
+    """Before the first shrink of a 512-row buffer the whole Gram matrix, and with it the norms of the rows sage_stats has not
+    counted yet, come from the split-arithmetic kernels (on the fp32 matrix cores under SAGE_MM_F32). Against 64 bits: a term
+    is good to 3 * 2^-26 (the products left out), a sum over a work-group's slabs (at most 8 here, a rounding each) to
+    8 * 2^-24 of the sum of magnitudes, which for the entries and eigenvalues below is at most ||A||_F^2."""
+    from paper_2510_02470_amd.binding import Sage
+
+    tol = 3 * 2.0 ** -26 + 8 * 2.0 ** -24
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    G = torch.randn((rows, D), generator=g, device="cuda") * torch.exp(0.5 * torch.randn((rows, 1), generator=g, device="cuda"))
+    G[:, 0] += 3.0
+    G = G.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    A = G.double().cpu()
+    fro, k = float((A ** 2).sum()), min(16, D)
+    sig2 = torch.linalg.eigvalsh(A @ A.T).flip(0)[:k]
+    for mode in (1, 2, 0):
+        s = Sage(ell, D, dtype=dtype)
+        s.set_update_arithmetic(mode)
+        s.fd_update(G[: rows - 7])
+        s.fd_update(G[rows - 7:])
+        assert abs(s.stats().frob2 - fro) <= tol * fro
+        s.fd_basis(k)
+        AV = A @ s.basis().double().cpu().T
+        assert float(((AV ** 2).sum(0) - sig2).abs().max()) <= tol * fro
+        assert abs(s.stats().frob2 - fro) <= tol * fro        # counted by the basis now
