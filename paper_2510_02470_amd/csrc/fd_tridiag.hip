@@ -291,11 +291,14 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 // order, so one that did both would wait, with every poll, for its own stores. They wait for c first, which is out before
 // the products are formed, then for q: a poll of one vector takes 550 cycles, of both 830.
 // The work-groups must be resident together, which nothing guarantees: kernels of other streams and processes may hold the CUs
-// of the XCD. So a thread polls at most `polls` times in vain in all (SPIN_LIMIT: about 30 ms, where a whole reduction takes 0.8)
-// and then goes on with NaN for what did not come. NaN goes into everything it publishes from then on, so the others lose no time
-// waiting, and reaches the work-group of the last column, which finds it in the last diagonal element. That work-group is the only
-// one that writes results, and it then repeats the whole reduction alone (tri_alone): a solve never fails.
-constexpr int SPIN_LIMIT = 1 << 17;
+// of the XCD. So a thread polls at most `polls` times in vain in all and then goes on with NaN for what did not come. NaN
+// goes into everything it publishes from then on, so the others lose no time waiting, and reaches the work-group of the
+// last column, which finds it in the last diagonal element. That work-group is the only one that writes results, and it
+// then repeats the whole reduction alone (tri_alone): a solve never fails. A work-group that starts when the others have
+// given up sees that in claim[1], which holds the tag of the last solve given up, and loses no time either.
+// poll_limit: to wait for as long as the repetition takes, 1.9, 3.8 and 15 ms (0.23 us a poll), costs at most twice what the better
+// of waiting and repeating would have. A reduction polls 500, 1100 and 3000 times in vain while it waits for its own steps.
+constexpr int poll_limit(int J) { return J == 2 ? 1 << 13 : J == 4 ? 1 << 14 : 1 << 16; }
 
 // The reduction by one work-group of 512 threads, with the matrix in V (its rows become the reflectors) and the vectors of a step
 // in LDS: every step reads and writes the trailing matrix once, through the L2. For solves that several work-groups could not
@@ -449,6 +452,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         const int t = tid & (J >= 4 ? 255 : 127);
         const bool for_c = J >= 4 || wave < 6;
         int spins = polls;
+        if (__hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag0) spins = 1;
         if (closes) tri_finish<J>(n, dT, eT, tauT, V, tid - 256, 256);
         for (int k = 0; k < steps; ++k) {
             const int par = k & 1;
@@ -487,6 +491,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                         if (more && --spins <= 0) {
                             spins = 1;  // every further wait gives up after one round
                             more = false;
+                            __hip_atomic_store(claim + 1, tag0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                             for (int u = 0; u < PT; ++u)
                                 if (!fresh(e[u], tag)) e[u][2] = 0x7FF80000u;  // NaN
@@ -927,7 +932,7 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
 #define SAGE_TRI_MANY(J)                                                                                           \
     hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, \
                        w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, w.epoch << 10, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
-                       alone || w.impatient ? 1 : SPIN_LIMIT, w.redone, w.claim)
+                       alone || w.impatient ? 1 : poll_limit(J), w.redone, w.claim)
     const bool alone = w.period == 0;
     switch (NP / 64) {
         case 1: SAGE_TRI_ONE(1); break;

@@ -153,7 +153,7 @@ struct EigWork {
     double* dI[2];  // NP: eigenvalues, ascending, in units of 2^stat[0]
     double* stat;   // [0] exponent of the scaling
     double* redone; // solves whose reduction one work-group repeated because the others were not there in time
-    unsigned* claim; // one word, zero before and after a reduction (TriClaim)
+    unsigned* claim; // [0] zero before and after a reduction (TriClaim), [1] tag of the last solve given up
     bool impatient; // test hook: its work-groups wait for each other for one poll only
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
     u32x4* xch;     // exchange buffers of the reduction (NP = 128, 256, 512), 4 NP entries
