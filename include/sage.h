@@ -101,9 +101,10 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
  * Pass 1 (Algorithm 1, Phase I): append `rows` rows to the sketch. Each row is copied into the next free buffer
  * row; whenever the buffer becomes full the shrink step runs: with sigma_j, v_j the singular values / right
  * singular vectors of the buffer, delta = sigma_ell^2 and row j becomes sqrt(max(sigma_j^2 - delta, 0)) v_j^T
- * (Method, FD paragraph). It is computed as: Gram C = B B^T (fp32 matrix cores, split over D, partial sums added
+ * (Method, FD paragraph). It is computed as: Gram C = B B^T (split over D, partial sums added
  * in fp64) -> eigensolve C = Y Lambda Y^T (fp64) -> B[0:ell] <- diag(w) Y^T B with
- * w_j = sqrt(max(lambda_j - delta, 0) / lambda_j) (fp32 matrix cores), rows ell.. zeroed.
+ * w_j = sqrt(max(lambda_j - delta, 0) / lambda_j), rows ell.. zeroed. (Arithmetic of the two dense products:
+ * sage_set_update_arithmetic.)
  * G_batch: DEVICE, rows x D of the context's dtype. rows >= 0 (0 is a no-op). Asynchronous on the context's
  * stream. Invalidates a basis made earlier. The host never reads device data in this call.
  * When a call ends exactly on a full buffer, that shrink is left for the next sage_fd_update (which can then overlap
@@ -252,8 +253,9 @@ int sage_set_basis(sage_ctx* ctx, const float* Vt, int k);
  * every row of a batch starts on a 16-byte boundary (D * element size a multiple of 16, batch pointer 16-byte
  * aligned, D >= 64 for bf16 / 32 for fp32 rows, D * element size < 16 MiB) the products run on the bf16 matrix cores
  * with every fp32 basis entry split as hi + lo (two bf16, relative error <= 2^-17) and fp32 rows split the same
- * way, accumulated in fp32; otherwise, and always under SAGE_PROJ_F32, on the fp32 matrix cores. Drops the current
- * basis: call before sage_fd_basis / sage_set_basis.
+ * way, accumulated in fp32. Rows of any other start run there with basis and fp32 rows in three bf16 parts (the fp32 result
+ * to within a few 2^-24 per term). Rows shorter than that, and everything under SAGE_PROJ_F32, run on the fp32 matrix cores.
+ * Drops the current basis: call before sage_fd_basis / sage_set_basis.
  */
 typedef enum { SAGE_PROJ_AUTO = 0, SAGE_PROJ_F32 = 1 } sage_proj_mode;
 int sage_set_projection_mode(sage_ctx* ctx, int mode);
@@ -264,7 +266,8 @@ int sage_set_projection_mode(sage_ctx* ctx, int mode);
  * parts (24 significant bits) and the six partial products that matter run on the bf16 matrix cores, accumulated in
  * fp32 -- the fp32 result to within a few 2^-24 per term, at a multiple of the fp32 matrix-core rate. It is used where
  * a kernel exists: the rebuild for ell >= 97 (padded sketch size 128 or 256), the Gram blocks of the steady state
- * (new rows x top rows, new rows x new rows) for ell >= 193 (padded size 256); everything else, and everything under
+ * (new rows x top rows, new rows x new rows) and the whole Gram matrix before the first shrink for ell >= 193 (padded size
+ * 256); everything else, and everything under
  * SAGE_MM_F32, runs on the fp32 matrix cores. Rows that arrive through sage_fd_update or sage_fd_update_outer in a bf16 context
  * are bf16 values kept as fp32: they have one part, not three, and the split kernels leave out the products with their (zero) second
  * and third parts -- three products instead of six wherever a buffered row of the stream is a factor, with the same
@@ -345,8 +348,8 @@ int sage_copy_probe(void* dst, const void* src, int64_t bytes, void* hip_stream)
  * Per-kernel timing for harnesses: when enabled, every kernel launch is bracketed by HIP events on the
  * context's stream (this serialises host and device, so whole-call timings taken while it is on are not
  * representative). sage_profile_read waits, then reports the accumulated milliseconds and launch count of
- * the kernel class `which` (0 gram, 1 gram reduce, 2 eigensolve, 3 coefficients, 4 rebuild/basis, 5 insert,
- * 6 project, 7 score finalise, 8 select) and clears that class.
+ * the kernel class `which` (0 gram, 1 gram reduce, 2 eigensolve with the rebuild's coefficients, 3 nothing, 4 rebuild/basis,
+ * 5 insert, 6 project, 7 score finalise, 8 select) and clears that class.
  */
 int sage_profile_enable(sage_ctx* ctx, int on);
 int sage_profile_read(sage_ctx* ctx, int which, double* ms, int64_t* launches);
@@ -368,7 +371,7 @@ int sage_set_debug_checks(sage_ctx* ctx, int on);
 
 /*
  * Test hook for the error path: the nth kernel launch from now that the context issues for its main sequence (Gram,
- * reduce, eigensolve, coefficients, rebuild, insert, projection, finalise, select) is not made and is reported as a
+ * reduce, eigensolve, rebuild, insert, projection, finalise, select) is not made and is reported as a
  * failed launch instead, so that the call in progress returns SAGE_ERR_HIP and the context becomes poisoned exactly as
  * after a real launch failure. Nothing faulty runs on the GPU. nth = 0 disarms the hook.
  */

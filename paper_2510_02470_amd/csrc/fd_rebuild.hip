@@ -168,7 +168,7 @@ hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const fl
 // Same decomposition as rebuild_kernel: a wave owns 32 columns for the whole product, its column operand comes from
 // global memory (8 rows of its k-half per stage of 16 buffer rows; k-slot (h, s) is buffer row 16*stage + 2s + h,
 // the order coeff_offset groups the coefficients in) and is split in registers; the coefficients come split
-// from coeffs_kernel in the order LDS holds them, [stage][part][h][m][8 k-slots], and streamed through a
+// from the back-transformation (tri_back_kernel) in the order LDS holds them, [stage][part][h][m][8 k-slots], and streamed through a
 // ring of three LDS buffers with direct global->LDS loads two stages ahead. The column operand is requested two
 // stages ahead as well.
 // NPT > 0: the buffer has NPT rows and the new rows in use hold bf16 values; their stages take the hi part alone and
