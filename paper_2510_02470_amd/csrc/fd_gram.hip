@@ -46,12 +46,13 @@ template <int P>
 __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ top, const float* __restrict__ nw,
                                                       int nfill, float* __restrict__ partial, int mode, int t0,
                                                       int tiles, int wg_per_group, int64_t slabs_total,
-                                                      int64_t slabs_per_group, int wgs, int hole) {
+                                                      int64_t slabs_per_group, int wgs,
+                                                      const int* __restrict__ hole) {
     constexpr int NP = P * 64;
     constexpr int STAGE = NP * 4;  // 16-byte pieces per stage
     extern __shared__ f32x4 lds[];
 
-    const int id = (int)spare_unit(blockIdx.x, hole);
+    const int id = (int)spare_unit_at(hole);
     if (id < 0 || id >= wgs) return;
     const int xcd = id & 7;  // consecutive block ids go to consecutive XCDs: keep a group on one XCD (shared L2)
     const int y = id >> 3;
@@ -698,9 +699,10 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
 
 __global__ __launch_bounds__(256, 2) void gram_new8_split_kernel(const float* __restrict__ nw, int nfill,
                                                                  float* __restrict__ partial, int64_t slabs_total,
-                                                                 int64_t slabs_per_group, int groups, int hole) {
+                                                                 int64_t slabs_per_group, int groups,
+                                                                 const int* __restrict__ hole) {
     extern __shared__ u32x4 ldsn[];
-    const int group = (int)spare_unit(blockIdx.x, hole);
+    const int group = (int)spare_unit_at(hole);
     if (group < 0 || group >= groups) return;
     int64_t s0 = (int64_t)group * slabs_per_group;
     int64_t s1 = s0 + slabs_per_group;
@@ -790,9 +792,10 @@ __device__ __forceinline__ void gram_new8_half_wave(const u32x4* __restrict__ N1
 template <bool FULL>
 __global__ __launch_bounds__(256, 2) void gram_new8_half_kernel(const float* __restrict__ nw, int nfill,
                                                                 float* __restrict__ partial, int64_t slabs_total,
-                                                                int64_t slabs_per_group, int groups, int hole) {
+                                                                int64_t slabs_per_group, int groups,
+                                                                const int* __restrict__ hole) {
     extern __shared__ u32x4 ldsh[];
-    const int group = (int)spare_unit(blockIdx.x, hole);
+    const int group = (int)spare_unit_at(hole);
     if (group < 0 || group >= groups) return;
     int64_t s0 = (int64_t)group * slabs_per_group;
     int64_t s1 = s0 + slabs_per_group;
@@ -874,7 +877,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, 
 }
 
 // wg_per_cu = 2 fills the chip. wg_per_cu = 1 is for the launch that shares the chip with the eigensolve (side stream): it
-// leaves an eighth of the CUs, an XCD, to the eigensolve's reduction (see spare_unit).
+// leaves an eighth of the CUs, an XCD, to the eigensolve's reduction (see spare_unit_at).
 GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_per_cu) {
     GramPlan p;
     const bool side = wg_per_cu == 1;
@@ -928,7 +931,7 @@ GramPlan gram_plan_split(const GramPlan& base, const Dims& d, int groups) {
 }
 
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
-                       hipStream_t st, bool new_one, int hole) {
+                       hipStream_t st, bool new_one, const int* hole) {
     if (p.tiles <= 0) return hipSuccess;
     dim3 grid((unsigned)(p.groups * p.wg_per_group));
     size_t lds = (size_t)2 * d.NP * 64;
@@ -950,7 +953,7 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
         return hipGetLastError();
     }
     if (p.mode == 2 && d.NP == 512 && p.split) {
-        const dim3 wgs((unsigned)spare_grid(p.groups, hole));
+        const dim3 wgs((unsigned)spare_grid_at(p.groups, hole));
         if (new_one) {
             constexpr int LDS = 3 * 3 * 2 * 256 * 16;  // three stages of three slabs
             const bool full = nfill >= 256;
@@ -978,7 +981,7 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
 #define SAGE_GRAM_CASE(PP)                                                                                          \
     case PP: {                                                                                                      \
         if (hipError_t ea = ensure_dynamic_lds((const void*)gram_kernel<PP>, 65536); ea != hipSuccess) return ea;   \
-        hipLaunchKernelGGL(gram_kernel<PP>, dim3((unsigned)spare_grid(grid.x, hole)), dim3(256), lds, st, top, nw, nfill,   \
+        hipLaunchKernelGGL(gram_kernel<PP>, dim3((unsigned)spare_grid_at(grid.x, hole)), dim3(256), lds, st, top, nw, nfill,   \
                            partial, p.mode, p.t0, p.tiles, p.wg_per_group, d.S, p.slabs_per_group, (int)grid.x, hole);  \
     } break;
         SAGE_GRAM_CASE(1)

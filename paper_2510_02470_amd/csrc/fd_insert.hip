@@ -8,11 +8,11 @@ namespace sage {
 // gap, and the four waves of a work-group store 64 rows. (A thread per piece along a row stored 64-byte pieces 16 KB apart:
 // 590 us for 256 fp32 rows of 1,048,576, 3.6 TB/s, and 1060 us for bf16 rows of 2,049,000.) The NS loads of a row are
 // neighbours and in flight together. Columns >= D are written as zero so that padding never carries data.
-// hole: see spare_unit.
+// hole: see spare_unit_at.
 template <int NS, typename Src>
 __global__ __launch_bounds__(256) void insert_kernel(Src src, int rows, int row0, float* __restrict__ B, int NP, int64_t D,
-                                                     int64_t S, int row_groups, int64_t units, int hole) {
-    const int64_t unit = spare_unit(blockIdx.x, hole);
+                                                     int64_t S, int row_groups, int64_t units, const int* __restrict__ hole) {
+    const int64_t unit = spare_unit_at(hole);
     if (unit < 0 || unit >= units) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = (int)((unsigned)unit % (unsigned)row_groups) * 64 + wave * 16 + (lane >> 2);
@@ -90,8 +90,8 @@ struct DenseRows {
 // rows, 256 bytes each, and a work-group's are 1 KB.
 template <int NS, typename Src>
 __global__ __launch_bounds__(256) void insert16_kernel(Src src, int rows, int row0, u32x4* __restrict__ B, int LP, int64_t D,
-                                                       int64_t Q, int row_groups, int64_t units, int hole) {
-    const int64_t unit = spare_unit(blockIdx.x, hole);
+                                                       int64_t Q, int row_groups, int64_t units, const int* __restrict__ hole) {
+    const int64_t unit = spare_unit_at(hole);
     if (unit < 0 || unit >= units) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = (int)((unsigned)unit % (unsigned)row_groups) * 64 + wave * 16 + (lane & 15);
@@ -107,13 +107,13 @@ __global__ __launch_bounds__(256) void insert16_kernel(Src src, int rows, int ro
 
 template <typename Src>
 static hipError_t launch_insert_src(const Src& src, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                                    bool to16, int hole, hipStream_t st) {
+                                    bool to16, const int* hole, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
     const int row_groups = (int)((rows + 63) / 64);
     if constexpr (Src::BF16) {
         if (to16) {
             const int64_t Q = 2 * d.S, units = (Q + 31) / 32 * row_groups;  // 8 loads a lane, 512 bytes of a row
-            hipLaunchKernelGGL((insert16_kernel<8, Src>), dim3((unsigned)spare_grid(units, hole)), dim3(256), 0, st, src, (int)rows,
+            hipLaunchKernelGGL((insert16_kernel<8, Src>), dim3((unsigned)spare_grid_at(units, hole)), dim3(256), 0, st, src, (int)rows,
                                row0, const_cast<u32x4*>(half16(half, half_rows, d.S)), half_rows, d.D, Q, row_groups, units, hole);
             return hipGetLastError();
         }
@@ -121,7 +121,7 @@ static hipError_t launch_insert_src(const Src& src, int64_t rows, int row0, floa
     // 16 slabs a wave, 16 KB of fp32 stores; 4 where that would leave the chip short of waves
     const int64_t wide = (d.S + 15) / 16 * row_groups;
     const int64_t units = wide >= 1024 ? wide : (d.S + 3) / 4 * row_groups;
-    const dim3 grid((unsigned)spare_grid(units, hole));
+    const dim3 grid((unsigned)spare_grid_at(units, hole));
     if (wide >= 1024)
         hipLaunchKernelGGL((insert_kernel<16, Src>), grid, dim3(256), 0, st, src, (int)rows, row0, half, half_rows, d.D, d.S,
                            row_groups, units, hole);
@@ -132,7 +132,7 @@ static hipError_t launch_insert_src(const Src& src, int64_t rows, int row0, floa
 }
 
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         bool to16, int hole, hipStream_t st) {
+                         bool to16, const int* hole, hipStream_t st) {
     const bool vec = d.D % 4 == 0 && (uintptr_t)G % (dtype == SAGE_BF16 ? 8 : 16) == 0;
 #define SAGE_INSERT(T, V) launch_insert_src(DenseRows<T, V>{(const T*)G}, rows, row0, half, half_rows, d, to16, hole, st)
     if (dtype == SAGE_BF16) return vec ? SAGE_INSERT(uint16_t, true) : SAGE_INSERT(uint16_t, false);
@@ -306,7 +306,7 @@ struct OuterRows {
 };
 
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, bool to16, int hole, hipStream_t st) {
+                               float* half, int half_rows, const Dims& d, bool to16, const int* hole, hipStream_t st) {
     if (dtype == SAGE_BF16)
         return launch_insert_src(OuterRows<uint16_t>{(const uint16_t*)E, (const uint16_t*)H, C, dh}, rows, row0, half,
                                  half_rows, d, to16, hole, st);

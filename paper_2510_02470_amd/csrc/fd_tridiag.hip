@@ -13,6 +13,7 @@
 // One work-group issues the instructions of a 128-row reduction in 155 us, 16 of them take 116, so the exchange pays from there
 // on. Where work-groups cannot be placed on one XCD (XcdMap without a period) one does it all: 128 rows by tri_one_kernel,
 // larger ones as after a wait in vain (see tri_many_kernel).
+#include <mutex>
 #include <type_traits>
 
 #include "sage_internal.h"
@@ -920,9 +921,42 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
 __global__ void xcd_probe_kernel(int* __restrict__ out) {
     if (threadIdx.x == 0) out[blockIdx.x] = xcd_id();
 }
-hipError_t launch_xcd_probe(int* out, int count, hipStream_t st) {
-    hipLaunchKernelGGL(xcd_probe_kernel, dim3(count), dim3(64), 0, st, out);
+// The place (spare_unit) of an XCD among the work-groups of the launches that follow on this stream.
+__global__ void xcd_place_kernel(int xcd, int* __restrict__ place) {
+    if (threadIdx.x == 0 && xcd_id() == xcd) *place = (int)blockIdx.x;
+}
+hipError_t launch_xcd_place(int xcd, int* place, hipStream_t st) {
+    hipLaunchKernelGGL(xcd_place_kernel, dim3(8), dim3(64), 0, st, xcd, place);
     return hipGetLastError();
+}
+const XcdMap& xcd_map() {
+    static std::mutex lock;
+    static XcdMap known[64];
+    static bool asked[64] = {false};
+    static const XcdMap nothing{};
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nothing;
+    std::lock_guard<std::mutex> hold(lock);
+    if (!asked[dev]) {
+        constexpr int B = 512;
+        int* d = nullptr;
+        int h[B];
+        bool ok = hipMalloc((void**)&d, sizeof(h)) == hipSuccess;
+        if (ok) {
+            hipStream_t st = nullptr;
+            ok = hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
+            if (ok) {
+                hipLaunchKernelGGL(xcd_probe_kernel, dim3(B), dim3(64), 0, st, d);
+                ok = hipMemcpyAsync(h, d, sizeof(h), hipMemcpyDeviceToHost, st) == hipSuccess &&
+                     hipStreamSynchronize(st) == hipSuccess;
+                (void)hipStreamDestroy(st);
+            }
+            (void)hipFree(d);
+        }
+        if (ok) known[dev] = xcd_map_of(h, B);
+        asked[dev] = true;
+    }
+    return known[dev];
 }
 
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st) {

@@ -26,10 +26,8 @@ enum { K_GRAM = 0, K_REDUCE, K_EIG, K_REBUILD = 4, K_INSERT, K_PROJECT, K_FINALI
 struct SideKit {
     hipStream_t stream = nullptr;
     hipEvent_t mark = nullptr, side[2] = {nullptr, nullptr};
-    int* host = nullptr;  // pinned words: [1], [2] report of the class-balanced selection, [16] signal, [32] .. XCD probe
+    int* host = nullptr;  // pinned words: [1], [2] report of the class-balanced selection, [16] signal
     unsigned token = 0;   // of the last signal
-    bool placed = false;  // place is known:
-    XcdMap place{};       // how the stream's launches lie on the XCDs
 };
 
 // Where device memory comes from (sage_set_allocator); a context keeps the pair it was created with.
@@ -64,7 +62,7 @@ struct sage_ctx {
     hipStream_t st2 = nullptr;                   // side stream (only when the Gram has >= 2 row panels)
     hipEvent_t ev_mark = nullptr;                // context stream: the Gram matrix of the current cycle is complete
     hipEvent_t ev_side[2] = {nullptr, nullptr};  // side stream: rows stored in nw[i] and their Gram block formed
-    int hole = -1;                               // ... whose launches leave the eigensolves' XCD alone (spare_unit)
+    int* side_hole = nullptr;                    // the place its launches leave out (spare_unit_at)
     bool pending_shrink = false;   // the buffer is full, its shrink waits for the next update call (see sage_fd_update)
     bool pre_stored = false;       // the side stream has stored the next ell rows of the running call in nw[cur]
     bool new_block_ready = false;  // ... and their Gram block is (or will be, see ev_side) in gram_partial_new[cur]
@@ -290,7 +288,7 @@ struct RowSrc {
 };
 
 hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int half_rows, const Dims& d, bool to16,
-                       hipStream_t st, int hole = -1) {
+                       hipStream_t st, const int* hole = nullptr) {
     if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, to16, hole, st);
     return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, to16, hole, st);
 }
@@ -349,8 +347,7 @@ std::mutex g_xcd_lock;
 XcdSlot g_xcd[MAX_DEVICES][8];
 
 constexpr int KITS_KEPT = 4;  // per device
-constexpr int PROBED = 512;   // work-groups of the XCD probe
-constexpr int KIT_WORDS = 32 + PROBED;
+constexpr int KIT_WORDS = 32;
 std::mutex g_kit_lock;
 SideKit g_kit[MAX_DEVICES][KITS_KEPT];
 int g_kits[MAX_DEVICES] = {0};
@@ -399,18 +396,11 @@ void kit_give(int device, SideKit& k, bool reuse) {
 }
 
 // The XCD for a context's reductions; where there is no telling which work-groups share one, it needs none.
-int xcd_take(sage_ctx* c) {
-    if (c->d.NP < 128 || c->device < 0 || c->device >= MAX_DEVICES) return SAGE_OK;
-    SideKit& k = c->kit;
-    if (!k.placed) {
-        HIPCHK(launch_xcd_probe(k.host + 32, PROBED, k.stream));
-        HIPCHK(hipStreamSynchronize(k.stream));
-        k.place = xcd_map_of(k.host + 32, PROBED);
-        k.placed = true;
-    }
-    const XcdMap& map = k.place;
+void xcd_take(sage_ctx* c) {
+    if (c->d.NP < 128 || c->device < 0 || c->device >= MAX_DEVICES) return;
+    const XcdMap& map = xcd_map();
     c->ew.period = map.period;
-    if (map.period == 0) return SAGE_OK;
+    if (map.period == 0) return;
     std::lock_guard<std::mutex> hold(g_xcd_lock);
     int best = -1;
     for (int i = 0; i < 8; ++i) {
@@ -419,12 +409,9 @@ int xcd_take(sage_ctx* c) {
         for (int p = 0; p < map.period; ++p) there = there || map.id[p] == x;
         if (there && (best < 0 || g_xcd[c->device][x].users < g_xcd[c->device][best].users)) best = x;
     }
-    for (int p = 0; p < 8 && map.period == 8; ++p)
-        if (map.id[p] == best) c->hole = p;
     g_xcd[c->device][best].users += 1;
     c->xcd_slot = best;
     c->ew.xcd = best;
-    return SAGE_OK;
 }
 void xcd_release(sage_ctx* c) {
     if (c->xcd_slot < 0) return;
@@ -519,7 +506,8 @@ int side_ahead(sage_ctx* c, const RowSrc* next) {
     HIPCHK(hipEventRecord(c->ev_mark, c->st));
     HIPCHK(hipStreamWaitEvent(c->st2, c->ev_mark, 0));
     if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
-    const int hole = c->ew.period > 0 ? c->hole : -1;
+    int* const hole = c->ew.period == 8 ? c->side_hole : nullptr;
+    if (hole) HIPCHK(launch_xcd_place(c->ew.xcd, hole, c->st2));
     HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, hole));
     c->gp_side_used[o] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
     HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), hole));
@@ -802,13 +790,14 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.K, &w.dc.k1, &w.dc.dense}) take(*p, n1);
             if (pass == 0) CALLOC(c->eig_mem, bytes);
         }
-        if (int rc = xcd_take(c); rc != SAGE_OK) return fail(rc);
+        xcd_take(c);
     }
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
     if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
     CALLOC(c->acc, 8 * sizeof(double));
     c->ew.redone = c->acc + 4;
     c->ew.claim = (unsigned*)(c->ew.stat + 16);
+    c->side_hole = (int*)(c->ew.stat + 24);
 #undef CALLOC
     // Rows of the top half that the stream never fills are zero. (Those it has not filled yet are cleared when something
     // looks at them, see clear_top; rows of a new half beyond its fill are never used.)
@@ -1529,7 +1518,7 @@ int sage_debug_impatient_solves(sage_ctx* c, int on) {
     if (on < 0 || on > 3) return SAGE_ERR_ARG;
     c->ew.impatient = on == 1;
     if (c->xcd_slot >= 0) c->ew.xcd = on == 3 ? 8 : c->xcd_slot;
-    c->ew.period = on == 2 || c->xcd_slot < 0 ? 0 : c->kit.place.period;
+    c->ew.period = on == 2 || c->xcd_slot < 0 ? 0 : xcd_map().period;
     return SAGE_OK;
 }
 

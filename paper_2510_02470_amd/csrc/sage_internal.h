@@ -87,16 +87,21 @@ __device__ __forceinline__ int xcd_id() {
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(id));
     return id & 7;
 }
-// Work that runs beside an eigensolve keeps off the XCD that the reduction has to itself: `hole`, see spare_unit.
+// Work that runs beside an eigensolve keeps off the XCD that the reduction has to itself: *hole is the place left out (spare_unit), set
+// by launch_xcd_place before it on the same stream; null: none is.
+__device__ __forceinline__ int64_t spare_unit_at(const int* __restrict__ hole) {
+    return spare_unit(blockIdx.x, hole ? *hole : -1);
+}
+inline int64_t spare_grid_at(int64_t units, const int* hole) { return spare_grid(units, hole ? 0 : -1); }
 // fd_insert.hip
 // copy `rows` batch rows into rows row0.. of a half buffer (half_rows rows per slab)
 // (to16: in pieces of bf16, see half16; rows of bf16 only)
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         bool to16, int hole, hipStream_t st);
+                         bool to16, const int* hole, hipStream_t st);
 // factored rows (E: rows x C logit errors, H: rows x dh features, both of the row type): column c*dh + t = e_c * h_t
 // rounded as a stored row would be, column C*dh + c = e_c; requires D = C * (dh + 1)
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, bool to16, int hole, hipStream_t st);
+                               float* half, int half_rows, const Dims& d, bool to16, const int* hole, hipStream_t st);
 hipError_t launch_widen(float* half, const Dims& d, hipStream_t st);  // pieces of bf16 -> the fp32 half
 // ... written out row-major (rows x D of the row type)
 hipError_t launch_expand_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, void* out,
@@ -128,7 +133,7 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
 // new_one (split-arithmetic kernels): the new half is kept in pieces of bf16 (half16): one part instead of three, the result
 // has the same bits
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
-                       hipStream_t st, bool new_one = false, int hole = -1);
+                       hipStream_t st, bool new_one = false, const int* hole = nullptr);
 // C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
 // (the Gram matrix of the rows the last shrink wrote, see EigWork::known)
 hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const float* partial_b, const GramPlan* b,
@@ -166,8 +171,8 @@ struct EigWork {
 inline int dc_result(int NP) { return (NP == 128 || NP == 512) ? 1 : 0; }
 // Matrix indices in use: 0 .. m0-1 and LP .. LP + (n - m0) - 1, n in all (the others are zero rows and columns); the count
 // leading eigenvectors are formed.
-// out (`count` words of host memory that the device can write) receives the XCD of every work-group
-hipError_t launch_xcd_probe(int* out, int count, hipStream_t st);
+hipError_t launch_xcd_place(int xcd, int* place, hipStream_t st);  // *place: 0 .. 7, device memory
+const XcdMap& xcd_map();  // of the launches on some stream of the current device; asked once per device
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
 // Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Mc3 (split

@@ -4,9 +4,10 @@
 
 namespace sage {
 
-// Work-group i of a launch runs on XCD id[i % period], period different ones. 8 on the whole chip, the number of XCDs of a
-// partition otherwise; 0: it cannot be said. The first XCD differs from stream to stream and is the same for all launches on one
-// (tried on seven streams, 40 launches each of 1 to 1024 work-groups). Nothing that decides a result may rest on this.
+// Work-groups i and i + period of a launch run on the same XCD and `period` consecutive ones on different XCDs, those of
+// `id`. 8 on the whole chip, the number of XCDs of a partition otherwise; 0: neither can be said. Which of them the first gets
+// differs from stream to stream, and for one stream when queues come and go (tried: another stream's first launch moved it
+// by one). Nothing that decides a result may rest on any of this.
 struct XcdMap {
     int period = 0;
     int id[8] = {};

@@ -111,8 +111,8 @@ def test_a_context_joins_an_xcd_whose_reductions_are_in_flight():
             c.close()
 
 
-@pytest.mark.parametrize("ell", [64, 128, 256])
-@pytest.mark.parametrize("rows", [1, 2, 5, 20, 60, 70, 131, 259])
+@pytest.mark.parametrize("ell,rows", [(ell, rows) for ell in (64, 128, 256) for rows in (1, 2, 5, 20, 60, 70, 131, 259)
+                                      if rows < 2 * ell])
 def test_basis_of_a_buffer_with_few_rows(ell, rows):
     """A basis taken early: the reduction runs on the rows in use, so most of its work-groups have no column or leave it
     before the end. Orthonormal to 1e-5, invariant under the rows' covariance and with all of its energy to 1e-6 (fp32 Gram)."""
@@ -120,8 +120,6 @@ def test_basis_of_a_buffer_with_few_rows(ell, rows):
 
     from paper_2510_02470_amd.binding import Sage
 
-    if rows >= 2 * ell:
-        pytest.skip("that many rows shrink the buffer")
     D = 700
     G = np.random.default_rng(rows).standard_normal((rows, D)).astype(np.float32) * np.exp(np.linspace(0, -3, rows))[:, None].astype(np.float32)
     s = Sage(ell, D)
