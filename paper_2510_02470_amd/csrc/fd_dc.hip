@@ -445,7 +445,12 @@ template <bool WITH_WY>
 __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const double* __restrict__ dT, const double* __restrict__ eT,
                                                           int N, double* __restrict__ dO, double* __restrict__ Z,
                                                           const double* __restrict__ V, const double* __restrict__ tauT,
-                                                          int n, double* __restrict__ Tw) {
+                                                          int n, double* __restrict__ Tw, u32x4* __restrict__ xch,
+                                                          unsigned* __restrict__ claim) {
+    if (!WITH_WY && blockIdx.x == 0) {  // the reduction before this is over: clear its exchange for the next
+        for (int e = threadIdx.x; e < 4 * N; e += 512) xch[e] = u32x4{0u, 0u, 0u, 0u};
+        if (threadIdx.x == 0) claim[1] = 0u;
+    }
     if (WITH_WY && blockIdx.x == 1) {
         const int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         if (b * WY <= n - 2) wy_factor<1>(V, tauT, b, n, threadIdx.x & 63, Tw);
@@ -828,10 +833,10 @@ hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
     if (hipError_t e = ensure_dynamic_lds(block, (int)sizeof(DcBlockLds)); e != hipSuccess) return e;
     if (N == 64)
         hipLaunchKernelGGL(dc_block_kernel<true>, dim3(2), dim3(512), sizeof(DcBlockLds), st, w.dT, w.eT, N, w.dI[0], w.Z[0],
-                           w.V, w.tauT, n, w.Tw);
+                           w.V, w.tauT, n, w.Tw, w.xch, w.claim);
     else
         hipLaunchKernelGGL(dc_block_kernel<false>, dim3(N / 64), dim3(512), sizeof(DcBlockLds), st, w.dT, w.eT, N, w.dI[0],
-                           w.Z[0], w.V, w.tauT, n, w.Tw);
+                           w.Z[0], w.V, w.tauT, n, w.Tw, w.xch, w.claim);
     int cur = 0;
     for (int m = 128; m <= N; m *= 2) {
         const int S = N / m;

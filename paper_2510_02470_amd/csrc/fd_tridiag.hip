@@ -282,10 +282,11 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 
 // ---- n = 64 J, J = 2, 4, 8: 16, 16 or 32 work-groups on one XCD ---------------------------------------------------
 // As above, but a wave owns 2 (n = 128) or 4 whole columns, carries all vectors itself and sums its products over the
-// lanes, and q and c go through the L2 the work-groups share. An exchanged value is a 16-byte entry {low word, tag, high word, tag}; the tag (solve number and step)
-// makes each 8-byte half carry its own validity, so there are no flags, no fences and nothing to clear: a reader polls an
+// lanes, and q and c go through the L2 the work-groups share. An exchanged value is a 16-byte entry {low word, tag, high word, tag}; the tag (the step, from 1)
+// makes each 8-byte half carry its own validity, so there are no flags and no fences: a reader polls an
 // entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough, because a
-// work-group leaves as soon as it has nothing left to publish (fd_tri_plan.h).
+// work-group leaves as soon as it has nothing left to publish (fd_tri_plan.h). The kernel after this one clears them
+// (dc_block_kernel), so that a solve needs no number of its own and a captured one can be replayed.
 // Stores: the L1 is write-through, so a plain store reaches the XCD's L2. Of the work-groups launched, one in `period` lands on
 // the XCD of the solve and stays, in the role of its number (see TriClaim for what happens if none does).
 // Waves 0..3 compute and publish, waves 4..7 only poll and hand over through LDS: loads and stores of a wave retire in
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 // goes into everything it publishes from then on, so the others lose no time waiting, and reaches the work-group of the
 // last column, which finds it in the last diagonal element. That work-group is the only one that writes results, and it
 // then repeats the whole reduction alone (tri_alone): a solve never fails. A work-group that starts when the others have
-// given up sees that in claim[1], which holds the tag of the last solve given up, and loses no time either.
+// given up sees that in claim[1] and loses no time either.
 // poll_limit: to wait for as long as the repetition takes, 1.9, 3.8 and 15 ms (0.23 us a poll), costs at most twice what the better
 // of waiting and repeating would have. A reduction polls 500, 1100 and 3000 times in vain while it waits for its own steps.
 constexpr int poll_limit(int J) { return J == 2 ? 1 << 13 : J == 4 ? 1 << 14 : 1 << 16; }
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, u32x4* __restrict__ xch,
-                                                          unsigned tag0, int xcd, int shift, int polls,
+                                                          int xcd, int shift, int polls,
                                                           double* __restrict__ redone, unsigned* __restrict__ claim) {
     using Plan = TriPlan<J>;
     constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW;
@@ -453,11 +454,11 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         const int t = tid & (J >= 4 ? 255 : 127);
         const bool for_c = J >= 4 || wave < 6;
         int spins = polls;
-        if (__hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag0) spins = 1;
+        if (__hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) spins = 1;
         if (closes) tri_finish<J>(n, dT, eT, tauT, V, tid - 256, 256);
         for (int k = 0; k < steps; ++k) {
             const int par = k & 1;
-            const unsigned tag = tag0 + (unsigned)k;
+            const unsigned tag = 1u + (unsigned)k;
             // all of this thread's entries of a vector in one round trip; it is done with the entries of rows <= k
             // (in a last step that is not waited for, the waves that compute get zeros: nothing comes of it)
             auto poll = [&](const u32x4* src, double (&val)[PT]) __attribute__((always_inline)) {
@@ -492,7 +493,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
                         if (more && --spins <= 0) {
                             spins = 1;  // every further wait gives up after one round
                             more = false;
-                            __hip_atomic_store(claim + 1, tag0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(claim + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                             for (int u = 0; u < PT; ++u)
                                 if (!fresh(e[u], tag)) e[u][2] = 0x7FF80000u;  // NaN
@@ -557,7 +558,7 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
 
         for (int k = 0; k < steps; ++k) {
             const int par = k & 1;
-            const unsigned tag = tag0 + (unsigned)k;
+            const unsigned tag = 1u + (unsigned)k;
             u32x4* const qx = xch + par * 2 * N;
             u32x4* const cx = qx + N;
 #pragma unroll
@@ -965,7 +966,7 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
     hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
 #define SAGE_TRI_MANY(J)                                                                                           \
     hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, \
-                       w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, w.epoch << 10, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
+                       w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
                        alone || w.impatient ? 1 : poll_limit(J), w.redone, w.claim)
     const bool alone = w.period == 0;
     switch (NP / 64) {

@@ -422,28 +422,37 @@ void xcd_release(sage_ctx* c) {
     c->xcd_slot = -1;
 }
 
+// What a captured stream holds runs later, if at all: it has no place in the order of reductions on an XCD.
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Eigensolve of the Gram matrix of fill_top + fill_new rows; the `count` leading eigenvectors are formed, or (cf given) the
 // coefficients made from its own count of them.
 hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf = nullptr) {
     if (n < 1) m0 = n = 1;  // an empty buffer: one zero row
-    c->ew.epoch = (c->ew.epoch + 1) & 0x3fffffu;
-    if (c->ew.epoch == 0) c->ew.epoch = 1;
     if (c->xcd_slot < 0) return launch_eig(c->ew, c->d.NP, m0, n, count, cf, c->st);
     std::unique_lock<std::mutex> hold(g_xcd_lock);
     XcdSlot& x = g_xcd[c->device][c->xcd_slot];
-    const bool shared = x.users > 1;
+    const bool shared = x.users > 1 && !capturing(c->st);
     if (shared) {
         if (!x.last && hipEventCreateWithFlags(&x.last, hipEventDisableTiming) != hipSuccess) return hipErrorUnknown;
         if (x.owner && x.owner != c) {
-            if (!x.marked)
+            if (!x.marked && !capturing(x.owner->st)) {
                 if (hipError_t e = hipEventRecord(x.last, x.owner->st); e != hipSuccess) return e;
-            if (hipError_t e = hipStreamWaitEvent(c->st, x.last, 0); e != hipSuccess) return e;
+                x.marked = true;
+            }
+            if (x.marked)
+                if (hipError_t e = hipStreamWaitEvent(c->st, x.last, 0); e != hipSuccess) return e;
         }
     }
     hipError_t e = launch_tridiag(c->ew, c->d.NP, m0, n, c->st);
     if (shared && e == hipSuccess) e = hipEventRecord(x.last, c->st);
     x.owner = c;
-    x.marked = shared;
+    x.marked = shared && e == hipSuccess;
     hold.unlock();
     if (e == hipSuccess) e = launch_dc(c->ew, c->d.NP, n, c->st);
     if (e == hipSuccess) e = launch_tri_back(c->ew, c->d.NP, m0, n, count, cf, c->st);

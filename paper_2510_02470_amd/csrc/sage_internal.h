@@ -158,13 +158,12 @@ struct EigWork {
     double* dI[2];  // NP: eigenvalues, ascending, in units of 2^stat[0]
     double* stat;   // [0] exponent of the scaling
     double* redone; // solves whose reduction one work-group repeated because the others were not there in time
-    unsigned* claim; // [0] zero before and after a reduction (TriClaim), [1] tag of the last solve given up
+    unsigned* claim; // [0] zero before and after a reduction (TriClaim), [1] set when the solve is given up
     bool impatient; // test hook: its work-groups wait for each other for one poll only
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
-    u32x4* xch;     // exchange buffers of the reduction (NP = 128, 256, 512), 4 NP entries
+    u32x4* xch;     // exchange buffers of the reduction (NP = 128, 256, 512), 4 NP entries, zero before it
     int xcd;        // the XCD the reduction runs on (NP = 128, 256, 512)
     int period;     // of the work-groups of a launch over the XCDs (XcdMap), 0: not known
-    unsigned epoch; // number of the solve, from 1 (tags of the exchange)
     DcWork dc;
 };
 // which of dI / Z the last merge of a solve of size NP writes
