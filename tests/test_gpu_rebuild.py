@@ -1,0 +1,43 @@
+"""The shrink's rebuild in two fp16 parts: rows of very different norms, zero rows, buffers of low rank, every padded size, both
+row types, against the shrink in 64 bits."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _shrink(A, ell, torch):
+    lam, Y = torch.linalg.eigh((A @ A.T).cpu())
+    lam, Y = lam.flip(0).cuda(), Y.flip(1).cuda()
+    keep = (lam[:ell] - lam[ell - 1]).clamp(min=0)
+    w = torch.where(keep > 0, (keep / lam[:ell].clamp(min=1e-300)).sqrt(), torch.zeros_like(keep))
+    return (w[:, None] * Y[:, :ell].T) @ A
+
+
+# decades: the rows' norms span so many of them (0: all alike); sizes just below and above a padding step
+@pytest.mark.parametrize("decades", [0, 6, 14])
+@pytest.mark.parametrize("ell,D,dtype", [(65, 1000, "f32"), (128, 4099, "bf16"), (128, 40, "f32"), (129, 1000, "bf16"),
+                                         (256, 4099, "f32"), (256, 2064, "bf16"), (256, 200, "bf16")])
+def test_shrink_against_64_bits(ell, D, dtype, decades):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(D + ell + decades)
+    n = 4 * ell
+    G = torch.randn(n, D, generator=g, device="cuda")
+    G *= 10.0 ** (-decades * torch.rand(n, 1, generator=g, device="cuda"))
+    G[3] = 0.0
+    G[ell + 5:ell + 9] = G[ell + 4]                      # rows the shrink's result has less rank for
+    G = G.to(torch.bfloat16 if dtype == "bf16" else torch.float32).contiguous()
+    s = Sage(ell, D, dtype=dtype)
+    s.fd_update(G[:2 * ell])
+    s.fd_update(G[2 * ell:])                             # three shrinks in all
+    B = s.sketch().double()[:ell]
+    A = G.double()
+    E = A[:ell]
+    for c in range(1, 4):
+        E = _shrink(torch.cat([E, A[c * ell:(c + 1) * ell]]), ell, torch)
+    assert bool(torch.isfinite(B).all())
+    # A Gram entry is a sum of D terms in fp32 (2^-24 sqrt(4099) = 4e-6 of its size at most, the terms being random), a rebuilt
+    # value one of 512 terms good to 2^-22 (5e-6).
+    assert float((B.T @ B - E.T @ E).norm()) <= 1e-5 * float((A * A).sum())
