@@ -445,10 +445,10 @@ template <bool WITH_WY>
 __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const double* __restrict__ dT, const double* __restrict__ eT,
                                                           int N, double* __restrict__ dO, double* __restrict__ Z,
                                                           const double* __restrict__ V, const double* __restrict__ tauT,
-                                                          int n, double* __restrict__ Tw, u32x4* __restrict__ xch,
+                                                          int n, double* __restrict__ Tw, double* __restrict__ xch,
                                                           unsigned* __restrict__ claim) {
-    if (!WITH_WY && blockIdx.x == 0) {  // the reduction before this is over: clear its exchange for the next
-        for (int e = threadIdx.x; e < 4 * N; e += 512) xch[e] = u32x4{0u, 0u, 0u, 0u};
+    if (!WITH_WY && blockIdx.x == 0) {  // the reduction before this is over: empty its exchange for the next
+        for (int e = threadIdx.x; e < 4 * N; e += 512) reinterpret_cast<u32x4*>(xch)[e] = u32x4{~0u, ~0u, ~0u, ~0u};
         if (threadIdx.x == 0) claim[1] = 0u;
     }
     if (WITH_WY && blockIdx.x == 1) {

@@ -4,9 +4,13 @@
 // Step k of the reduction of n rows exchanges q and c at the rows above k: entry q[i] comes from the wave that owns column i,
 // all of c from the one that owns column k + 1. So a work-group has something to publish in the steps below its last column,
 // and it needs the entries of a step only to make those of the next. It leaves after its last entry; one without a column
-// below n has no part in the solve. Nobody then waits for a slot that others no longer wait for it to have read: slot
-// k & 1 is written again in step k + 2, by work-groups that have all of step k + 1, to which every reader of step k that is
-// not done contributed after it had read step k.
+// below n has no part in the solve.
+//
+// An entry is the value itself, 8 bytes; a slot that holds no entry yet holds a pattern no result has (EMPTY, all ones). Step k uses
+// slot k & 3. The work-group of the last column, which takes part in every step, empties slot (k + 2) & 3 in step k, before
+// its barrier of that step: it has all of step k - 1 then, to which every reader of step k - 2 that is not done contributed
+// after it had read step k - 2. Who publishes or waits for entries of step k + 2 has that work-group's entry of step k + 1, which
+// it published after the slot was empty.
 #pragma once
 
 namespace sage {
@@ -14,10 +18,13 @@ namespace sage {
 template <int J>
 struct TriPlan {
     static constexpr int N = 64 * J;
-    static constexpr int CW = J >= 4 ? 4 : 2;   // columns of a wave
+    static constexpr int CW = J >= 8 ? 4 : 2;   // columns of a wave
     static constexpr int NW = N / CW;           // waves that hold columns
     static constexpr int NWG = NW / 4;          // work-groups
     static constexpr int ST = J / CW;           // columns of a wave are 64 ST apart
+    static constexpr int THREADS = 256 + N;     // of a work-group: four waves compute, a thread waits for two of 2 N entries
+    static constexpr int SLOTS = 4;
+    static constexpr int slot(int k) { return k & (SLOTS - 1); }
 
     static constexpr int column(int wave, int s) { return (wave & 63) + 64 * ((wave >> 6) + ST * s); }
     static constexpr int wave_of(int col) { return (col & 63) + 64 * ((col >> 6) & (ST - 1)); }

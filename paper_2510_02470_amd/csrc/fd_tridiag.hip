@@ -7,11 +7,11 @@
 // therefore never leaves the registers: the work-groups own columns of the (symmetric) matrix, a wave's lanes the rows
 // lane, lane + 64, ..., and the rank-2 update of a step is applied in the same pass as the next step's product.
 //   n = 64:            one work-group; the exchanges of a step go through LDS (tri_one_kernel, 0.7 us a step).
-//   n = 128, 256, 512: 16, 16, 32 work-groups, one per CU of ONE XCD, which exchange two n-vectors per step through the L2
-//                      they share (tri_many_kernel, 0.9, 1.04, 1.45 us a step; every wave carries the vectors of the
+//   n = 128, 256, 512: 16, 32, 32 work-groups, one per CU of ONE XCD, which exchange two n-vectors per step through the L2
+//                      they share (tri_many_kernel, 0.77, 0.83, 1.02 us a step; every wave carries the vectors of the
 //                      step redundantly, so a step has one exchange and no other synchronisation).
-// One work-group issues the instructions of a 128-row reduction in 155 us, 16 of them take 116, so the exchange pays from there
-// on. Where work-groups cannot be placed on one XCD (XcdMap without a period) one does it all: 128 rows by tri_one_kernel,
+// One work-group issues the instructions of a 128-row reduction in 144 us (110 with one barrier a step and every wave carrying
+// the vectors), 16 of them take 98, so the exchange pays from there on. Where work-groups cannot be placed on one XCD (XcdMap without a period) one does it all: 128 rows by tri_one_kernel,
 // larger ones as after a wait in vain (see tri_many_kernel).
 #include <mutex>
 #include <type_traits>
@@ -280,18 +280,22 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
     }
 }
 
-// ---- n = 64 J, J = 2, 4, 8: 16, 16 or 32 work-groups on one XCD ---------------------------------------------------
-// As above, but a wave owns 2 (n = 128) or 4 whole columns, carries all vectors itself and sums its products over the
-// lanes, and q and c go through the L2 the work-groups share. An exchanged value is a 16-byte entry {low word, tag, high word, tag}; the tag (the step, from 1)
-// makes each 8-byte half carry its own validity, so there are no flags and no fences: a reader polls an
-// entry, with loads that bypass its L1 (sc1), until both tags are the step's. Two slots by step parity are enough, because a
-// work-group leaves as soon as it has nothing left to publish (fd_tri_plan.h). The kernel after this one clears them
-// (dc_block_kernel), so that a solve needs no number of its own and a captured one can be replayed.
+// ---- n = 64 J, J = 2, 4, 8: 16, 32, 32 work-groups on one XCD -----------------------------------------------------
+// As above, but a wave owns 2 (n = 128, 256) or 4 whole columns, carries all vectors itself and sums its products over the
+// lanes, and q and c go through the L2 the work-groups share. An exchanged value is its own 8 bytes: a slot holds a pattern that
+// is no result until it is written, so there are no flags and no fences, and a reader polls, with loads that bypass its L1
+// (sc1), until it sees anything else. Four slots by step; the work-group of the last column, which sees every step, empties them
+// (fd_tri_plan.h). The kernel after this one empties them all (dc_block_kernel), so that a solve needs no number of its own
+// and a captured one can be replayed. (16-byte entries with a tag in each half, which need no emptying, moved twice the bytes and
+// took two loads a thread at 512 rows: 830 us beside the look-ahead work instead of 595.)
 // Stores: the L1 is write-through, so a plain store reaches the XCD's L2. Of the work-groups launched, one in `period` lands on
 // the XCD of the solve and stays, in the role of its number (see TriClaim for what happens if none does).
-// Waves 0..3 compute and publish, waves 4..7 only poll and hand over through LDS: loads and stores of a wave retire in
-// order, so one that did both would wait, with every poll, for its own stores. They wait for c first, which is out before
-// the products are formed, then for q: a poll of one vector takes 550 cycles, of both 830.
+// Waves 0..3 compute and publish, n / 64 more only poll and hand over through LDS, half of them q and half c: loads and stores of
+// a wave retire in order, so one that did both would wait, with every poll, for its own stores.
+// What a step costs (n = 256, cycles of 2.07 k): products and sums until q is out 600, until the last q is seen some 950 (a
+// store's way to L2, half a poll's period, a poll of 550), handing over 150, w and the next column 350. A branch costs a
+// wave 100 cycles, taken or not (an instruction about five), which is why the loop has as few as it has and
+// is written out per 64 steps: 264 -> 212 us at 256 rows and 740 -> 520 at 512 together with the smaller entries.
 // The work-groups must be resident together, which nothing guarantees: kernels of other streams and processes may hold the CUs
 // of the XCD. So a thread polls at most `polls` times in vain in all and then goes on with NaN for what did not come. NaN
 // goes into everything it publishes from then on, so the others lose no time waiting, and reaches the work-group of the
@@ -302,14 +306,14 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
 // of waiting and repeating would have. A reduction polls 500, 1100 and 3000 times in vain while it waits for its own steps.
 constexpr int poll_limit(int J) { return J == 2 ? 1 << 13 : J == 4 ? 1 << 14 : 1 << 16; }
 
-// The reduction by one work-group of 512 threads, with the matrix in V (its rows become the reflectors) and the vectors of a step
+// The reduction by one work-group of T threads, with the matrix in V (its rows become the reflectors) and the vectors of a step
 // in LDS: every step reads and writes the trailing matrix once, through the L2. For solves that several work-groups could not
 // do together: 0.5, 2.2 and 12.8 ms at 128, 256 and 512 rows, where they take 0.12, 0.27 and 0.74. vec: 4 N words.
-template <int J>
+template <int J, int T>
 __device__ __forceinline__ void tri_alone(const double* __restrict__ C, int NP, int m0, int LP, int n, double* __restrict__ dT,
                                           double* __restrict__ eT, double* __restrict__ tauT, double* V, double sc0,
                                           double* vec) {
-    constexpr int N = 64 * J, T = 512;
+    constexpr int N = 64 * J;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int i = wave; i < n; i += T / 64)
@@ -405,36 +409,35 @@ __device__ __forceinline__ void tri_finish(int n, double* __restrict__ dT, doubl
         for (int i = tid; i < N; i += step) V[(int64_t)k * N + i] = 0.0;
 }
 
-__device__ __forceinline__ void put_entry(u32x4* p, double v, unsigned tag) {
-    const long long u = __double_as_longlong(v);
-    *p = u32x4{(unsigned)u, tag, (unsigned)(u >> 32), tag};
+__device__ __forceinline__ void put_entry(double* p, double v) {
+    *p = v;
     asm volatile("" ::: "memory");  // stays here
-}
-__device__ __forceinline__ bool fresh(const u32x4& e, unsigned tag) { return e[1] == tag && e[3] == tag; }
-__device__ __forceinline__ double entry_value(const u32x4& e) {
-    return __longlong_as_double(((long long)e[2] << 32) | e[0]);
 }
 
 template <int J>
-__global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
+__global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
-                                                          double* __restrict__ stat, u32x4* __restrict__ xch,
+                                                          double* __restrict__ stat, double* __restrict__ xch,
                                                           int xcd, int shift, int polls,
                                                           double* __restrict__ redone, unsigned* __restrict__ claim) {
     using Plan = TriPlan<J>;
-    constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW;
+    constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW, T = Plan::THREADS;
     // (xcd < 0: there is one work-group, in the closing role)
     const int wg = xcd >= 0 ? blockIdx.x >> shift : Plan::wave_of(n - 1) >> 2;
     const bool here = xcd < 0 || xcd_id() == xcd;
     const bool closes = Plan::closes(wg, n);  // this work-group stores what the solve's next stages read
     if (!here && !closes) return;
-    if (here) __builtin_amdgcn_s_setprio(3);
-    __shared__ Pair qc[2][N];  // {q, c} by step parity
-    __shared__ double vs[4][N];
+    __shared__ __attribute__((aligned(16))) double qc[4][N + 2];  // q by step parity, then c
+    __shared__ __attribute__((aligned(16))) double vs[2][N];  // the closing work-group: the reflector, by step parity,
+    __shared__ double sc[2][64];                              // and {diagonal, off-diagonal element, tau}
     __shared__ bool gave_up;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (here) {  // waves that compute go before those that wait
+        if (wave < 4) __builtin_amdgcn_s_setprio(3);
+        else __builtin_amdgcn_s_setprio(1);
+    }
     if (Plan::last_column(wg, n) < 0) return;
     const int steps = Plan::steps(wg, n), waits = Plan::waits(wg, n);  // waits >= steps - 1
     __shared__ TriClaim role;
@@ -448,78 +451,65 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         }
     }
 
-    auto wait_for_entries = [&]() __attribute__((always_inline)) {  // waves 4 ..: entries t, t + 256, .. of c and q
-        // J = 2: half the waves wait for c and half for q
-        constexpr int PT = J >= 4 ? N / 256 : 1;
-        const int t = tid & (J >= 4 ? 255 : 127);
-        const bool for_c = J >= 4 || wave < 6;
+    auto wait_for_entries = [&]() __attribute__((always_inline)) {  // waves 4 ..: one half waits for q, the other for c
+        const int t = tid - 256;
+        const bool for_c = t >= N / 2;
+        const int i0 = 2 * (for_c ? t - N / 2 : t);  // this thread's entries: i0, i0 + 1
         int spins = polls;
         if (__hip_atomic_load(claim + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) spins = 1;
-        if (closes) tri_finish<J>(n, dT, eT, tauT, V, tid - 256, 256);
+        if (closes) tri_finish<J>(n, dT, eT, tauT, V, t, N);
+        auto store_reflector = [&](int k) __attribute__((always_inline)) {
+            *reinterpret_cast<Pair*>(V + (int64_t)k * N + i0) = *reinterpret_cast<const Pair*>(&vs[k & 1][i0]);
+            if (i0 < 6) (i0 == 0 ? dT : i0 == 2 ? eT : tauT)[k] = sc[k & 1][i0 / 2];
+        };
         for (int k = 0; k < steps; ++k) {
-            const int par = k & 1;
-            const unsigned tag = 1u + (unsigned)k;
-            // all of this thread's entries of a vector in one round trip; it is done with the entries of rows <= k
-            // (in a last step that is not waited for, the waves that compute get zeros: nothing comes of it)
-            auto poll = [&](const u32x4* src, double (&val)[PT]) __attribute__((always_inline)) {
-                u32x4 e[PT];
-#pragma unroll
-                for (int u = 0; u < PT; ++u) e[u] = u32x4{0u, 0u, 0u, 0u};
-                if (t + 256 * (PT - 1) > k && t < n && k < waits) {
-                    bool more;
-                    do {
-                        if constexpr (PT == 2) {
-                            asm volatile(
-                                "global_load_dwordx4 %0, %2, off sc1\n\t"
-                                "global_load_dwordx4 %1, %3, off sc1\n\t"
-                                "s_waitcnt vmcnt(0)"
-                                : "=&v"(e[0]), "=&v"(e[PT - 1])
-                                : "v"(src), "v"(src + 256)
-                                : "memory");
-                        } else {
-                            asm volatile(
-                                "global_load_dwordx4 %0, %1, off sc1\n\t"
-                                "s_waitcnt vmcnt(0)"
-                                : "=&v"(e[0])
-                                : "v"(src)
-                                : "memory");
-                        }
+            double* const dst = &qc[(k & 1) + (for_c ? 2 : 0)][i0];
+            if (closes) {
+                if (for_c) {  // (it has time: c comes long before q)
+                    if (k > 0) store_reflector(k - 1);
+                } else {      // empty the slot of step k + 2 (TriPlan)
+                    const u32x4 empty{~0u, ~0u, ~0u, ~0u};
+                    double* const slot = xch + Plan::slot(k + 2) * 2 * N + i0;
+                    *reinterpret_cast<u32x4*>(slot) = empty;
+                    *reinterpret_cast<u32x4*>(slot + N) = empty;
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // done before this step's barrier
+            }
+            // Both entries in one load; the thread is done with entries of rows <= k. What came goes to LDS before it is looked
+            // at: if it is there, so is its copy. (In a last step that is not waited for, the waves that compute get zeros: nothing
+            // comes of it.)
+            const bool on0 = i0 > k && i0 < n, on1 = i0 + 1 > k && i0 + 1 < n;
+            if ((on0 || on1) && k < waits) {
+                const double* const src = xch + (Plan::slot(k) * 2 + (for_c ? 1 : 0)) * N + i0;
+                bool more;
+                do {
+                    u32x4 e;
+                    asm volatile(
+                        "global_load_dwordx4 %0, %1, off sc1\n\t"
+                        "s_waitcnt vmcnt(0)"
+                        : "=&v"(e)
+                        : "v"(src)
+                        : "memory");
+                    const bool empty0 = on0 && (e[0] & e[1]) == ~0u, empty1 = on1 && (e[2] & e[3]) == ~0u;
+                    if (!on0) e[0] = e[1] = 0u;
+                    if (!on1) e[2] = e[3] = 0u;
+                    *reinterpret_cast<u32x4*>(dst) = e;
+                    more = empty0 || empty1;
+                    if (more && --spins <= 0) {
+                        spins = 1;  // every further wait gives up after one round
                         more = false;
-#pragma unroll
-                        for (int u = 0; u < PT; ++u) {
-                            const int i = t + 256 * u;
-                            more = more || (i > k && i < n && !fresh(e[u], tag));
-                        }
-                        if (more && --spins <= 0) {
-                            spins = 1;  // every further wait gives up after one round
-                            more = false;
-                            __hip_atomic_store(claim + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                            for (int u = 0; u < PT; ++u)
-                                if (!fresh(e[u], tag)) e[u][2] = 0x7FF80000u;  // NaN
-                        }
-                    } while (more);
-                }
-#pragma unroll
-                for (int u = 0; u < PT; ++u) {
-                    const int i = t + 256 * u;
-                    val[u] = i > k && i < n ? entry_value(e[u]) : 0.0;
-                }
-            };
-            const u32x4* const qx = xch + par * 2 * N + t;
-            double cv[PT], qv[PT];
-            if constexpr (J >= 4) {
-                poll(qx + N, cv);
-                poll(qx, qv);
-#pragma unroll
-                for (int u = 0; u < PT; ++u) qc[par][t + 256 * u] = Pair{qv[u], cv[u]};
+                        __hip_atomic_store(claim + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        const double nan = __longlong_as_double(0x7FF8000000000000ll);
+                        if (empty0) dst[0] = nan;
+                        if (empty1) dst[1] = nan;
+                    }
+                } while (more);
             } else {
-                poll(for_c ? qx + N : qx, cv);
-                if (for_c) qc[par][t].b = cv[0];
-                else qc[par][t].a = cv[0];
+                *reinterpret_cast<Pair*>(dst) = Pair{0.0, 0.0};
             }
             lds_barrier();
         }
+        if (closes && for_c && steps > 0) store_reflector(steps - 1);
     };
 
     // Wave gw owns the columns of lane gw % 64: cl + 64 (H + s J / CW), s < CW, H = gw / 64 < J / CW. So the entries of v and w at
@@ -556,132 +546,141 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
         double xk = C[(int64_t)active_index(0, m0, LP) * NP + active_index(0, m0, LP)] * sc0;
         double xk1 = n > 1 ? C[(int64_t)active_index(0, m0, LP) * NP + active_index(1, m0, LP)] * sc0 : 0.0;
 
-        for (int k = 0; k < steps; ++k) {
-            const int par = k & 1;
-            const unsigned tag = 1u + (unsigned)k;
-            u32x4* const qx = xch + par * 2 * N;
-            u32x4* const cx = qx + N;
+        // The steps whose column k + 1 lies in [64 B, 64 B + 64): rows and columns below 64 B are done with, and left out at
+        // compile time. A step is straight-line code but for the publishing of c: a branch costs a wave some 100 cycles, taken or
+        // not, an instruction five.
+        // Where the lane stores its column's sum; lanes beyond the wave's columns are out of the buffer's range, which the store
+        // leaves out (an exec-masked store would cost a branch).
+        const auto ring = __builtin_amdgcn_make_buffer_rsrc(xch, 0, Plan::SLOTS * 2 * N * 8, 0x00027000);
+        const int qofs = lane < CW ? (cl + 64 * (H + ST * lane)) * 8 : 0x40000000;
+        auto steps_of = [&](auto bc) __attribute__((always_inline)) {
+            constexpr int B = decltype(bc)::value;
+            constexpr int S0 = B > H ? (B - H + ST - 1) / ST : 0, NS = CW - S0;  // columns s < S0 are done with
+            if constexpr (NS > 0) {
+                const int end = 64 * B + 63 < steps ? 64 * B + 63 : steps;
+                for (int k = B > 0 ? 64 * B - 1 : 0; k < end; ++k) {
+                    double* const cx = xch + Plan::slot(k) * 2 * N + N;
+                    x[B] = lane + 64 * B > k + 1 ? x[B] : 0.0;  // (in steps before the last of the rows, all beyond are)
+                    double acc[CW];
+                    {
+                        double vcol[CW], wcol[CW];
 #pragma unroll
-            for (int j = 0; j < J; ++j) x[j] = lane + 64 * j > k + 1 ? x[j] : 0.0;
-            double acc[CW], vcol[CW], wcol[CW];
-#pragma unroll
-            for (int s = 0; s < CW; ++s) {
-                vcol[s] = read_lane(v[H + ST * s], cl);
-                wcol[s] = read_lane(w[H + ST * s], cl);
-            }
-            // Straight-line code over all four columns: finished ones are carried along (nothing reads them), because a
-            // branch per column or register leaves the fp64 pipeline waiting for every result. Rows below 64 J0 are done
-            // with.
-            auto pass = [&](auto j0c) __attribute__((always_inline)) {
-                constexpr int J0 = decltype(j0c)::value;
-#pragma unroll
-                for (int s = 0; s < CW; ++s)
-#pragma unroll
-                    for (int j = J0; j < J; ++j) a[s][j] = __builtin_fma(-w[j], vcol[s], a[s][j]);
-#pragma unroll
-                for (int s = 0; s < CW; ++s)
-#pragma unroll
-                    for (int j = J0; j < J; ++j) a[s][j] = __builtin_fma(-v[j], wcol[s], a[s][j]);
-                if (((k + 1) & 63) == cl && (((k + 1) >> 6) & (ST - 1)) == H) {  // column k + 1 is this wave's
-#pragma unroll
-                    for (int s = 0; s < CW; ++s)
-                        if ((k + 1) >> 6 == H + ST * s) {
-#pragma unroll
-                            for (int j = J0; j < J; ++j) {
-                                double c = a[s][j];
-                                asm volatile("" : "+v"(c));  // keeps the cases apart (no run-time index into a[])
-                                put_entry(cx + lane + 64 * j, c, tag);
-                            }
+                        for (int s = S0; s < CW; ++s) {
+                            vcol[s] = read_lane(v[H + ST * s], cl);
+                            wcol[s] = read_lane(w[H + ST * s], cl);
                         }
+#pragma unroll
+                        for (int s = S0; s < CW; ++s)
+#pragma unroll
+                            for (int j = B; j < J; ++j) a[s][j] = __builtin_fma(-w[j], vcol[s], a[s][j]);
+#pragma unroll
+                        for (int s = S0; s < CW; ++s)
+#pragma unroll
+                            for (int j = B; j < J; ++j) a[s][j] = __builtin_fma(-v[j], wcol[s], a[s][j]);
+                    }
+                    if constexpr ((B & (ST - 1)) == H) {  // column k + 1 may be this wave's
+                        if (((k + 1) & 63) == cl) {
+#pragma unroll
+                            for (int j = B; j < J; ++j) put_entry(cx + lane + 64 * j, a[(B - H) / ST][j]);
+                        }
+                    }
+#pragma unroll
+                    for (int s = S0; s < CW; ++s) acc[s] = a[s][B] * x[B];
+#pragma unroll
+                    for (int j = B + 1; j < J; ++j)
+#pragma unroll
+                        for (int s = S0; s < CW; ++s) acc[s] = __builtin_fma(a[s][j], x[j], acc[s]);
+                    // The sums over the wave, one column per lane of a quad (pair): two at a time per lane pair, then one. (What
+                    // goes to finished columns is not read.)
+                    double t;
+                    if constexpr (CW == 4) {
+                        const bool odd = lane & 1, hi = lane & 2;
+                        constexpr int S1 = S0 > 1 ? S0 : 1;
+                        const double a0 = acc[S0 > 0 ? S1 : 0], a1 = acc[S1], a2 = acc[S0 > 2 ? 3 : 2], a3 = acc[3];
+                        double t1 = odd ? a3 : a2, o1 = odd ? a2 : a3;
+                        t1 += dpp_move<DPP_XOR1>(o1);       // lane parity q: column 2 + q
+                        if constexpr (S0 < 2) {
+                            double t0 = odd ? a1 : a0, o0 = odd ? a0 : a1;
+                            t0 += dpp_move<DPP_XOR1>(o0);   // ... column q
+                            t = hi ? t1 : t0;
+                            const double o = hi ? t0 : t1;
+                            t += dpp_move<DPP_XOR2>(o);     // lane & 3 = column; sums over quads so far
+                        } else {
+                            t = t1 + dpp_move<DPP_XOR2>(t1);
+                        }
+                    } else {
+                        const bool odd = lane & 1;
+                        t = (odd ? acc[CW - 1] : acc[S0]) + dpp_move<DPP_XOR1>(odd ? acc[S0] : acc[CW - 1]);
+                        t += dpp_move<DPP_XOR2>(t);
+                    }
+                    t += dpp_move<0x124>(t);  // row_ror 4
+                    t += dpp_move<0x128>(t);  // row_ror 8: sums over rows of 16
+                    double b0, b1;
+                    swap_rows<16>(t, b0, b1);
+                    t = b0 + b1;
+                    swap_rows<32>(t, b0, b1);
+                    t = b0 + b1;
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, t), ring, qofs, Plan::slot(k) * 2 * N * 8, 0);
+                    asm volatile("" ::: "memory");  // stays here
+                    // while the entries travel: the reflector
+                    double r2 = 0.0;
+#pragma unroll
+                    for (int j = B; j < J; ++j) r2 = __builtin_fma(x[j], x[j], r2);
+                    r2 = lane_sum<64>(r2);
+                    double beta, tau, v1;
+                    householder(xk1, r2, beta, tau, v1);
+                    // (for the next step; after the last, nothing comes of it)
+                    const double v2 = read_lane((k + 2) >> 6 == B ? x[B] : x[B + 1 < J ? B + 1 : B], (k + 2) & 63);
+#pragma unroll
+                    for (int j = B; j < J; ++j) v[j] = j == B && lane + 64 * j == k + 1 ? v1 : x[j];
+                    if (closes) {
+#pragma unroll
+                        for (int g = 0; g < J; g += 4) {  // registers g + wave (the finished rows' are zero)
+                            double z[4];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) z[i] = g + i < B || g + i >= J ? 0.0 : v[g + i < J ? g + i : 0];
+                            const double lo = wave & 1 ? z[1] : z[0], up = wave & 1 ? z[3] : z[2];
+                            vs[k & 1][lane + 64 * (g + (J >= 4 ? wave : wave & 1))] = J >= 4 && (wave & 2) ? up : lo;
+                        }
+                        if (wave == 0) sc[k & 1][lane] = lane == 1 ? beta : lane == 2 ? tau : xk;
+                    }
+                    lds_barrier();
+                    const double *const ql = qc[k & 1], *const cl2 = qc[2 + (k & 1)];
+                    const Pair e1{ql[k + 1], cl2[k + 1]}, e2{ql[k + 2], cl2[k + 2]};
+                    double c[J], dot = 0.0, dot2 = 0.0;
+#pragma unroll
+                    for (int j = B; j < J; ++j) {
+                        const Pair e{ql[lane + 64 * j], cl2[lane + 64 * j]};  // (entries of rows <= k are zero)
+                        c[j] = e.b;
+                        w[j] = tau * __builtin_fma(v1, e.b, e.a);
+                        if ((j - B) & 1) dot2 = __builtin_fma(w[j], v[j], dot2);
+                        else dot = __builtin_fma(w[j], v[j], dot);
+                    }
+                    dot = lane_sum<64>(dot + dot2);
+                    const double al = -0.5 * tau * dot;
+                    const double w1 = __builtin_fma(al, v1, tau * __builtin_fma(v1, e1.b, e1.a));
+                    const double w2 = __builtin_fma(al, v2, tau * __builtin_fma(v1, e2.b, e2.a));
+#pragma unroll
+                    for (int j = B; j < J; ++j) {
+                        w[j] = __builtin_fma(al, v[j], w[j]);
+                        x[j] = __builtin_fma(-v[j], w1, __builtin_fma(-w[j], v1, c[j]));
+                    }
+                    xk = __builtin_fma(-2.0 * v1, w1, e1.b);
+                    xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, e2.b));
                 }
-#pragma unroll
-                for (int s = 0; s < CW; ++s) acc[s] = a[s][J0] * x[J0];
-#pragma unroll
-                for (int j = J0 + 1; j < J; ++j)
-#pragma unroll
-                    for (int s = 0; s < CW; ++s) acc[s] = __builtin_fma(a[s][j], x[j], acc[s]);
-            };
-            if (k < 32 * J) pass(std::integral_constant<int, 0>{});
-            else pass(std::integral_constant<int, J / 2>{});
-            if constexpr (CW == 4) {  // the four sums over the wave: two at a time per lane pair, then one per lane of a quad
-                const bool odd = lane & 1, hi = lane & 2;
-                double t0 = odd ? acc[1] : acc[0], o0 = odd ? acc[0] : acc[1];
-                double t1 = odd ? acc[3] : acc[2], o1 = odd ? acc[2] : acc[3];
-                t0 += dpp_move<DPP_XOR1>(o0);   // lane parity q: column q
-                t1 += dpp_move<DPP_XOR1>(o1);   // ... column 2 + q
-                double t = hi ? t1 : t0, o = hi ? t0 : t1;
-                t += dpp_move<DPP_XOR2>(o);     // lane & 3 = column; sums over quads so far
-                t += dpp_move<0x124>(t);        // row_ror 4
-                t += dpp_move<0x128>(t);        // row_ror 8: sums over rows of 16
-                double b0, b1;
-                swap_rows<16>(t, b0, b1);
-                t = b0 + b1;
-                swap_rows<32>(t, b0, b1);
-                t = b0 + b1;
-                const int col = cl + 64 * (H + ST * (lane & 3));
-                if (lane < 4 && col > k && col < n) put_entry(qx + col, t, tag);
             }
-            else {  // two sums: one per lane of a pair
-                const bool odd = lane & 1;
-                double x = (odd ? acc[1] : acc[0]) + dpp_move<DPP_XOR1>(odd ? acc[0] : acc[1]);
-                x += dpp_move<DPP_XOR2>(x);
-                x += dpp_move<0x124>(x);  // row_ror 4
-                x += dpp_move<0x128>(x);  // row_ror 8
-                double b0, b1;
-                swap_rows<16>(x, b0, b1);
-                x = b0 + b1;
-                swap_rows<32>(x, b0, b1);
-                x = b0 + b1;
-                const int col = cl + 64 * (H + ST * (lane & 1));
-                if (lane < 2 && col > k && col < n) put_entry(qx + col, x, tag);
-            }
-            // while the entries travel: the reflector
-            double r2 = 0.0;
-#pragma unroll
-            for (int j = 0; j < J; ++j) r2 = __builtin_fma(x[j], x[j], r2);
-            r2 = lane_sum<64>(r2);
-            double beta, tau, v1;
-            householder(xk1, r2, beta, tau, v1);
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int r = lane + 64 * j;
-                v[j] = r == k + 1 ? v1 : x[j];
-                vs[wave][r] = v[j];
-            }
-            asm volatile("" ::: "memory");
-            const int i2 = k + 2 < n ? k + 2 : k + 1;
-            const double v2 = vs[wave][i2];
-            if (closes) {
-#pragma unroll
-                for (int j = 0; j < J; ++j)
-                    if ((j & 3) == wave) V[(int64_t)k * N + lane + 64 * j] = v[j];
-                if (tid == 64) {
-                    dT[k] = xk;
-                    eT[k] = beta;
-                    tauT[k] = tau;
-                }
-            }
-            lds_barrier();
-            const Pair e1 = qc[par][k + 1], e2 = qc[par][i2];
-            double c[J], dot = 0.0;
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const Pair e = qc[par][lane + 64 * j];  // (entries of rows <= k are zero)
-                c[j] = e.b;
-                w[j] = tau * __builtin_fma(v1, e.b, e.a);
-                dot = __builtin_fma(w[j], v[j], dot);
-            }
-            dot = lane_sum<64>(dot);
-            const double al = -0.5 * tau * dot;
-            const double w1 = __builtin_fma(al, v1, tau * __builtin_fma(v1, e1.b, e1.a));
-            const double w2 = __builtin_fma(al, v2, tau * __builtin_fma(v1, e2.b, e2.a));
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                w[j] = __builtin_fma(al, v[j], w[j]);
-                x[j] = __builtin_fma(-v[j], w1, __builtin_fma(-w[j], v1, c[j]));
-            }
-            xk = __builtin_fma(-2.0 * v1, w1, e1.b);
-            xk1 = __builtin_fma(-v2, w1, __builtin_fma(-w2, v1, e2.b));
+        };
+        steps_of(std::integral_constant<int, 0>{});
+        steps_of(std::integral_constant<int, 1>{});
+        if constexpr (J >= 4) {
+            steps_of(std::integral_constant<int, 2>{});
+            steps_of(std::integral_constant<int, 3>{});
+        }
+        if constexpr (J >= 8) {
+            steps_of(std::integral_constant<int, 4>{});
+            steps_of(std::integral_constant<int, 5>{});
+            steps_of(std::integral_constant<int, 6>{});
+            steps_of(std::integral_constant<int, 7>{});
         }
         if (closes && tid == 0) {  // (waits = n - 1: xk is the last step's)
             stat[0] = (double)ex;
@@ -704,9 +703,9 @@ __global__ __launch_bounds__(512, 1) void tri_many_kernel(const double* __restri
             *redone += 1.0;
             stat[0] = (double)ex;
         }
-        tri_alone<J>(C, NP, m0, LP, n, dT, eT, tauT, V, __builtin_amdgcn_ldexp(1.0, -ex), &vs[0][0]);
+        tri_alone<J, T>(C, NP, m0, LP, n, dT, eT, tauT, V, __builtin_amdgcn_ldexp(1.0, -ex), &qc[0][0]);
         __syncthreads();
-        tri_finish<J>(n, dT, eT, tauT, V, tid, 512);
+        tri_finish<J>(n, dT, eT, tauT, V, tid, T);
     }
 }
 
@@ -985,7 +984,7 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
 #define SAGE_TRI_ONE(J)                                                                                           \
     hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
 #define SAGE_TRI_MANY(J)                                                                                           \
-    hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(512), 0, st, w.C, NP, m0, LP, n, \
+    hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(TriPlan<J>::THREADS), 0, st, w.C, NP, m0, LP, n, \
                        w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
                        alone || w.impatient ? 1 : poll_limit(J), w.redone, w.claim)
     const bool alone = w.period == 0;

@@ -786,7 +786,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             const size_t n1 = (size_t)NP, n2 = n1 * n1;
             EigWork& w = c->ew;
             bytes = 0;
-            take(w.xch, 4 * n1);
+            take(w.xch, 8 * n1);
             take(w.stat, 32);
             take(w.C, n2);
             take(w.Yt, n2);
@@ -818,7 +818,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     if (ell < c->d.LP && launch_zero_rows(c->top, c->d.LP, ell, c->d.LP, c->d, c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->acc, 0, 8 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     if (hipMemsetAsync(c->ew.stat, 0, 32 * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
-    if (hipMemsetAsync(c->ew.xch, 0, (size_t)4 * NP * sizeof(u32x4), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
+    if (hipMemsetAsync(c->ew.xch, 0xFF, (size_t)8 * NP * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     *out = c;
     return SAGE_OK;
 }

@@ -44,6 +44,7 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // v_mfma_f32_32x32x16_bf16: acc(32x32) += a(32x16) b(16x32). Lane l supplies a[l%32][8*(l/32) .. +8] and
 // b[8*(l/32) .. +8][l%32]; acc element i of lane l is row 8*(i/4) + 4*(l/32) + i%4, column l%32.
@@ -192,7 +193,7 @@ struct EigWork {
                     // (row_exponent of C's diagonal), in the order of scale_index
     float* unscale; // LP: inverse of the power of two each row of the split coefficients holds
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
-    u32x4* xch;     // exchange buffers of the reduction (NP = 128, 256, 512), 4 NP entries, zero before it
+    double* xch;    // exchange of the reduction (NP = 128, 256, 512): 4 slots of q and c, NP each; empty (all ones) before it
     int xcd;        // the XCD the reduction runs on (NP = 128, 256, 512)
     int period;     // of the work-groups of a launch over the XCDs (XcdMap), 0: not known
     DcWork dc;

@@ -261,3 +261,10 @@ def test_captured_update_replays(ell, dtype):
         want, got = want.T @ want, got.T @ got
         assert float((got - want).abs().max()) <= 1e-5 * float(want.abs().max())
         assert eager.stats().n_unconverged == 0 and s.stats().n_unconverged == 0
+
+
+@pytest.mark.parametrize("ell,rows", [(64, 64), (64, 65), (64, 66), (64, 127), (128, 64), (128, 65), (128, 129), (128, 194),
+                                      (256, 65), (256, 128), (256, 321), (256, 449), (256, 450), (256, 511)])
+def test_basis_where_the_reduction_ends_near_a_multiple_of_64_rows(ell, rows):
+    """The reduction's loop is written out per 64 steps: it ends just before, at and just after such a boundary."""
+    test_basis_of_a_buffer_with_few_rows(ell, rows)

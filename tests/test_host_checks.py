@@ -32,3 +32,11 @@ def test_placement_on_xcds(tmp_path):
     every unit of its work once, by the numbers of its work-groups alone, wherever they run."""
     r = _run(_build(tmp_path, "xcd_check"))
     assert r.returncode == 0 and "xcd_check ok" in r.stdout, r.stdout
+
+
+def test_slots_of_the_reduction_are_emptied_in_time(tmp_path):
+    """tri_slot_check.cc; and the check itself: it must refuse slots that are emptied a step early."""
+    exe = _build(tmp_path, "tri_slot_check")
+    r = _run(exe)
+    assert r.returncode == 0 and "tri_slot_check ok" in r.stdout, r.stdout
+    assert _run(exe, "planted").returncode == 1
