@@ -45,90 +45,76 @@ __device__ __forceinline__ double sqrt64(double x) {
     return x > 1e-290 ? r : 0.0;
 }
 
-// Root q of 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending): lambda = org + tau with org the
+// Root q of f = 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending): lambda = org + tau with org the
 // nearer of the poles around it. A group of L lanes works on a root; lane l holds the poles l + L e, e < E (z = 0 and
-// d = 1e30 beyond K). The interpolation converges quadratically: a step below 1e-9 of tau is the last one. About four
-// evaluations a root, six for the slowest of a wave. What counts is the number of fp64 instructions (4 cycles each on a
-// SIMD, 16 for the reciprocal estimate): a pole costs 11 of them, a root's step 45 and 12 per stage of the sums over L.
+// d = 1e30 beyond K). on: this group has a root (all lanes take part in the loop). The interpolation, which matches f, f' and
+// f'' by two poles and a constant, converges cubically: a step below 1e-7 of tau is the last one. About 3.4 evaluations a
+// root, six for the slowest of 64 (with f and the derivatives of the two sides, which converges quadratically, 4.3 and seven
+// and a half). An evaluation is a chain of some 500 cycles (reciprocal, sums over L, square root, reciprocal) and 11 fp64
+// instructions a pole; a branch costs 100 cycles, so there is none but the loop's.
 template <int L, int E>
-__device__ __forceinline__ void secular_root(int K, int q, int l, const double (&dj)[E], const double (&zj)[E], double dq,
+__device__ __forceinline__ void secular_root(bool on, int K, int q, int l, const double (&dj)[E], const double (&zj)[E], double dq,
                                              double dq1, double zsum, double& org, double& tau) {
-    const bool last = q == K - 1;
-    double lo = 0.0, hi = zsum * (1.0 + 4.0 * DC_EPS);
-    org = dq;
-    if (!last) {
-        const double mid = 0.5 * (dq1 - dq);
-        double f = 0.0;
+    const bool last = q >= K - 1;
+    double f0 = 0.0;
+    const double gap = dq1 - dq, mid = 0.5 * gap;
 #pragma unroll
-        for (int e = 0; e < E; ++e) f = __builtin_fma(zj[e], rcp64((dj[e] - dq) - mid), f);
-        f = 1.0 + lane_sum<L>(f);
-        if (f >= 0.0) {
-            hi = mid;
-        } else {
-            org = dq1;
-            lo = -mid;
-            hi = 0.0;
-        }
-    }
+    for (int e = 0; e < E; ++e) f0 = __builtin_fma(zj[e], rcp64((dj[e] - dq) - mid), f0);
+    f0 = 1.0 + lane_sum<L>(f0);
+    const bool left = last || f0 >= 0.0;
+    org = left ? dq : dq1;
+    double lo = left ? 0.0 : -mid;
+    double hi = last ? zsum * (1.0 + 4.0 * DC_EPS) : (left ? mid : 0.0);
     double t = 0.5 * (lo + hi);
-    double dl[E], zl[E], zr[E];  // distance of the poles; weights of those up to q, of those above
+    double dl[E];  // distance of the poles
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        dl[e] = dj[e] - org;
-        const bool low = l + L * e <= q;
-        zl[e] = low ? zj[e] : 0.0;
-        zr[e] = low ? 0.0 : zj[e];
-    }
-    const double dlq = dq - org, dlq1 = dq1 - org;
+    for (int e = 0; e < E; ++e) dl[e] = dj[e] - org;
+    const double dlq = dq - org, dlq1 = dq1 - org, tol = 0.0625 * DC_EPS * K;
+    const double rgap = rcp64(gap);
     for (int it = 0; it < 60; ++it) {
-        double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
+        double f = 0.0, f1 = 0.0, f2 = 0.0;  // f - 1, f', f'' / 2
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const double inv = rcp64(dl[e] - t), inv2 = inv * inv;
-            psi = __builtin_fma(zl[e], inv, psi);
-            phi = __builtin_fma(zr[e], inv, phi);
-            dpsi = __builtin_fma(zl[e], inv2, dpsi);
-            dphi = __builtin_fma(zr[e], inv2, dphi);
+            const double inv = rcp64(dl[e] - t), u = zj[e] * inv, u1 = u * inv;
+            f += u;
+            f1 += u1;
+            f2 = __builtin_fma(u1, inv, f2);
         }
-        psi = lane_sum<L>(psi);
-        dpsi = lane_sum<L>(dpsi);
-        phi = lane_sum<L>(phi);
-        dphi = lane_sum<L>(dphi);
-        const double f = 1.0 + psi + phi;
-        // psi < 0 < phi: phi - psi is the sum of the magnitudes
-        if (!(fabs(f) > 0.5 * DC_EPS * K * (1.0 + (phi - psi)))) break;
+        lane_sum3<L>(f, f1, f2);
+        f += 1.0;
         lo = f < 0.0 ? t : lo;  // (t lies inside the bracket)
         hi = f < 0.0 ? hi : t;
-        const double di = dlq - t;
-        // A step needs few digits: its error shrinks with the step, which is below 1e-9 of t when it is the last. So the
-        // square root is the hardware's estimate with one correction, and so is the quotient.
-        double num, den, off = 0.0, lim0 = di, lim1 = 1e300;
-        if (!last) {
-            const double dn = dlq1 - t;  // di < 0 < dn
-            const double p = di * di * dpsi, g = dn * dn * dphi;
-            const double c = 1.0 + __builtin_fma(-di, dpsi, psi) + __builtin_fma(-dn, dphi, phi);
-            // c + p / (di - x) + g / (dn - x) = 0, the root between the poles: c x^2 - a x + b = 0
-            const double a = __builtin_fma(c, di + dn, p + g), b = __builtin_fma(c * di, dn, __builtin_fma(p, dn, g * di));
-            const double disc = fmax(__builtin_fma(a, a, -4.0 * c * b), 1e-280);
-            const double y = __builtin_amdgcn_rsq(disc), r = disc * y;
-            const double sq = __builtin_fma(__builtin_fma(-r, r, disc), 0.5 * y, r);
-            const double h = 0.5 * (a + __builtin_copysign(sq, a));
-            num = a > 0.0 ? b : h;
-            den = a > 0.0 ? h : c;
-            lim1 = dn;
-        } else {
-            num = di * di * dpsi;
-            den = 1.0 + __builtin_fma(-di, dpsi, psi);  // (not positive: the step leaves the bracket, which is halved)
-            off = di;
-        }
+        // c + P di^2 / (di - x) + G dn^2 / (dn - x) = 0 with P + G = f', P / di + G / dn = f'' / 2, the root between the poles
+        // di < 0 < dn: c x^2 - a x + b = 0. The last root has no pole above it: x = di + f' di^2 / (f - di f') (if that is not
+        // positive the step leaves the bracket, which is halved). A step needs few digits: its error shrinks with the step,
+        // which is below 1e-7 of t when it is the last. So the square root is the hardware's estimate with one correction, and so
+        // is the quotient.
+        const double di = dlq - t, dn = dlq1 - t;
+        const double P = di * rgap * __builtin_fma(f2, dn, -f1), G = f1 - P;
+        const double Pd = P * di, Gd = G * dn, c = f - Pd - Gd;
+        const double p = Pd * di, g = Gd * dn;
+        const double a = __builtin_fma(c, di + dn, p + g), b = __builtin_fma(c * di, dn, __builtin_fma(p, dn, g * di));
+        const double disc = fmax(__builtin_fma(a, a, -4.0 * c * b), 1e-280);
+        const double ys = __builtin_amdgcn_rsq(disc), r = disc * ys;
+        const double sq = __builtin_fma(__builtin_fma(-r, r, disc), 0.5 * ys, r);
+        const double h = 0.5 * (a + __builtin_copysign(sq, a));
+        const double fd = f1 * di;
+        const double num = last ? fd * di : (a > 0.0 ? b : h), den = last ? f - fd : (a > 0.0 ? h : c);
         double y = __builtin_amdgcn_rcp(den);
         y = __builtin_fma(__builtin_fma(-den, y, 1.0), y, y);
-        const double x = __builtin_fma(num, y, off), step = t + x;
-        const bool in = x > lim0 && x < lim1 && step > lo && step < hi;  // (false for NaN)
-        const double tn = in ? step : 0.5 * (lo + hi);
-        const bool done = in ? fabs(x) <= 1e-9 * fabs(tn) : !(hi - lo > fabs(tn) * DC_EPS);
-        t = tn;
-        if (done) break;
+        const double x = __builtin_fma(num, y, last ? di : 0.0), step = t + x;
+        // (false for NaN; the bracket lies between the poles. A small step that leaves it is rounding: t is the root.)
+        const bool in = (step > lo) & (step < hi), small = fabs(x) <= 1e-7 * fabs(step);
+        const double half = 0.5 * (lo + hi);
+        const bool end = small | !(hi - lo > fabs(half) * DC_EPS);
+        // f is rounding: an eighth of what its terms may leave, their magnitudes taken from the two poles of the interpolation
+        const bool there = !(fabs(f) > tol * (1.0 + (fabs(Pd) + fabs(Gd))));
+        double tn = small ? t : half;
+        tn = in ? step : tn;
+        on = on & !there;
+        t = on ? tn : t;
+        on = on & !end;
+        if (!__any(on)) break;
     }
     tau = t;
 }
@@ -147,7 +133,7 @@ __device__ __forceinline__ double secular_z(int K, int j, int l, double dj, cons
         pr *= i < K ? f : 1.0;
     }
     pr = lane_product<L>(pr);
-    return __builtin_sqrt(fabs(pr));
+    return sqrt64(fabs(pr));
 }
 
 // Two neighbouring surviving poles (d0, z0), (d1, z1): is their coupling below tol after the rotation that zeroes z0?
@@ -167,7 +153,8 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
 // 512 threads: 8 lanes per index, a sub-problem of M rows per 8 M threads. All arrays of the block in LDS; Q column-major.
 // A merge is a chain of short phases between barriers; half the time goes into the roots, which is why their loops are
 // unrolled to what M needs, and the products of 16 rows and more run on the matrix cores (in scalar code, bound by LDS
-// reads, the last product alone took 17 us). 37 us in all against 104 us for one loop over all sizes.
+// reads, the last product alone took 17 us). 32 us in all (38 with the roots' cases told apart by branches and quadratic
+// steps), against 104 us for one loop over all sizes.
 constexpr int DCB_LD = 65;   // columns of Q
 constexpr int DCB_LDU = 68;  // columns of U: the 16 columns x 4 rows of a matrix-core operand fall on distinct banks
 struct DcBlockLds {
@@ -181,7 +168,7 @@ struct DcBlockLds {
     int any;
 };
 
-template <int M>
+template <int M, bool WIDE>
 __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
     constexpr int H = M / 2, E = M > 8 ? M / 8 : 1, EH = H > 8 ? H / 8 : 1;
     const int i = tid >> 3, l = tid & 7;
@@ -310,9 +297,9 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
         __syncthreads();
     }
     const double dki = S.dk[i];
-    // Four lanes a root up to 16 rows, where most of a step does not depend on the number of poles; eight above (two waves
-    // per SIMD, of which each issues an instruction every five cycles at best).
-    constexpr int LR = M >= 32 ? 8 : 4, ER = M / LR;
+    // Four lanes a root: half the instructions of a step do not depend on the number of poles, and two waves per SIMD issue no
+    // more of them than one. (64 rows: 9,850 cycles against 11,450 with eight lanes; those where registers are short.)
+    constexpr int LR = M >= 64 && !WIDE ? 8 : 4, ER = M / LR;
     if (LR == 8 || tid < 256) {
         const int ir = tid / LR, lr = tid & (LR - 1), br = ir & ~(M - 1), lir = ir & (M - 1);
         const int Kr = LR == 8 ? K : S.K[br];
@@ -328,11 +315,10 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
             zsum += zj[e];
         }
         zsum = lane_sum<LR>(zsum);
-        double org = 0.0, tau = 0.0, val = dkr;
-        if (lir < Kr) {
-            secular_root<LR, ER>(Kr, lir, lr, dj, zj, dkr, lir + 1 < Kr ? S.dk[ir + 1] : 0.0, zsum, org, tau);
-            val = finite_or_zero(org + tau);
-        }
+        double org, tau;
+        const bool has = lir < Kr;
+        secular_root<LR, ER>(has, Kr, lir, lr, dj, zj, dkr, lir + 1 < Kr ? S.dk[ir + 1] : dkr + 1.0, zsum, org, tau);
+        const double val = has ? finite_or_zero(org + tau) : dkr;
         if (lr == 0) {
             S.org[ir] = org;
             S.tau[ir] = tau;
@@ -376,7 +362,7 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
             nn = __builtin_fma(u[e], u[e], nn);
         }
         nn = lane_sum<8>(nn);
-        nn = rcp64(__builtin_sqrt(nn));
+        nn = rcp64(sqrt64(nn));
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int j = l + 8 * e;
@@ -470,12 +456,10 @@ __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const do
         const double a = finite_or_zero(dT[g0]) - (g0 > 0 ? fabs(finite_or_zero(eT[g0 - 1])) : 0.0);
         const double c = finite_or_zero(dT[g0 + 1]) - fabs(finite_or_zero(eT[g0 + 1]));
         const double b = finite_or_zero(eT[g0]);
-        double t = 0.0;
-        if (b != 0.0) {
-            const double z = (c - a) / (2.0 * b);
-            t = __builtin_copysign(1.0, z) / (fabs(z) + __builtin_sqrt(1.0 + z * z));
-        }
-        const double cc = 1.0 / __builtin_sqrt(1.0 + t * t), ss = t * cc;
+        const bool coupled = fabs(b) > 1e-290;  // (of a matrix of order one)
+        const double z = (c - a) * rcp64(coupled ? 2.0 * b : 1.0), za = fmin(fabs(z), 1e100);
+        const double t = coupled ? __builtin_copysign(rcp64(za + sqrt64(__builtin_fma(za, za, 1.0))), z) : 0.0;
+        const double cc = rcp64(sqrt64(__builtin_fma(t, t, 1.0))), ss = t * cc;
         const double l1 = a - t * b, l2 = c + t * b;  // vectors (cc, -ss) and (ss, cc)
         const bool first = ((i & 1) == 0) == (l1 <= l2);  // this index takes l1
         S.d[i] = first ? l1 : l2;
@@ -483,11 +467,11 @@ __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const do
         S.Q[i * DCB_LD + (i | 1)] = first ? -ss : cc;
     }
     __syncthreads();
-    dc_level<4>(S, tid, tol);
-    dc_level<8>(S, tid, tol);
-    dc_level<16>(S, tid, tol);
-    dc_level<32>(S, tid, tol);
-    dc_level<64>(S, tid, tol);
+    dc_level<4, WITH_WY>(S, tid, tol);
+    dc_level<8, WITH_WY>(S, tid, tol);
+    dc_level<16, WITH_WY>(S, tid, tol);
+    dc_level<32, WITH_WY>(S, tid, tol);
+    dc_level<64, WITH_WY>(S, tid, tol);
     if (l == 0) dO[b0 + i] = S.d[i];
     for (int c = tid >> 6; c < 64; c += 8) Z[(int64_t)(b0 + c) * N + b0 + (tid & 63)] = S.Q[c * DCB_LD + (tid & 63)];
 }
@@ -695,7 +679,8 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
             zsum += zj[e];
         }
         zsum = lane_sum<64>(zsum);
-        secular_root<64, E>(K, q, lane, dj, zj, w.dk[base + q], q + 1 < K ? w.dk[base + q + 1] : 0.0, zsum, org, tau);
+        secular_root<64, E>(true, K, q, lane, dj, zj, w.dk[base + q], q + 1 < K ? w.dk[base + q + 1] : w.dk[base + q] + 1.0, zsum, org,
+                            tau);
         val = finite_or_zero(org + tau);
     }
     if (lane == 0) {
@@ -796,7 +781,7 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(const double* __restric
                 n1 = __builtin_fma(u1, u1, n1);
             }
             const double nn = lane_sum<8>(n0 + n1);
-            if (l == 0) inv[c] = nn > 0.0 ? rcp64(__builtin_sqrt(nn)) : 0.0;
+            if (l == 0) inv[c] = nn > 0.0 ? rcp64(sqrt64(nn)) : 0.0;
         }
         const int l16 = lane & 15, lk = lane >> 4, bc = tid & 31;
         f64x4 acc[2] = {f64x4{0.0, 0.0, 0.0, 0.0}, f64x4{0.0, 0.0, 0.0, 0.0}};

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace sage {
 
 template <int CTRL>
@@ -53,6 +55,37 @@ __device__ __forceinline__ double lane_sum(double v) {
         v = a + b;
     }
     return v;
+}
+// Three sums at once: their stages alternate, so that none waits for its own result.
+template <int L>
+__device__ __forceinline__ void lane_sum3(double& a, double& b, double& c) {
+    auto stage = [&](auto ctrl) __attribute__((always_inline)) {
+        constexpr int CTRL = decltype(ctrl)::value;
+        const double x = dpp_move<CTRL>(a), y = dpp_move<CTRL>(b), z = dpp_move<CTRL>(c);
+        a += x;
+        b += y;
+        c += z;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto swap = [&](auto dist) __attribute__((always_inline)) {
+        constexpr int D = decltype(dist)::value;
+        double x0, x1, y0, y1, z0, z1;
+        swap_rows<D>(a, x0, x1);
+        swap_rows<D>(b, y0, y1);
+        swap_rows<D>(c, z0, z1);
+        a = x0 + x1;
+        b = y0 + y1;
+        c = z0 + z1;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    stage(std::integral_constant<int, DPP_XOR1>{});
+    stage(std::integral_constant<int, DPP_XOR2>{});
+    if constexpr (L >= 8) stage(std::integral_constant<int, DPP_HALF_MIRROR>{});
+    if constexpr (L >= 16) stage(std::integral_constant<int, DPP_MIRROR>{});
+    if constexpr (L == 64) {
+        swap(std::integral_constant<int, 16>{});
+        swap(std::integral_constant<int, 32>{});
+    }
 }
 template <int L>
 __device__ __forceinline__ double lane_product(double v) {
