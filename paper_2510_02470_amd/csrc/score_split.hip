@@ -9,12 +9,11 @@
 // v_mfma_f32_32x32x16_bf16. The error against an fp32 product is a few 2^-17 relative per term, below the fp32
 // accumulation error over D ~ 1e6 terms.
 //
-// Work-group = 256 threads = 4 waves, two work-groups per CU. A wave owns 64 batch rows x KP basis columns
-// (2 x KP/32 accumulator tiles). Its row operand comes straight from global memory into registers (nobody else
-// needs those rows; a lane reads 16-byte pieces and over one chunk consumes whole 128-byte lines); the basis
-// operand is shared by the 4 waves and is streamed through LDS with direct global->LDS loads, double buffered.
-// The basis is kept in HBM as "images": for each chunk of KC columns exactly the bytes LDS will hold, so staging
-// is a linear copy.
+// Work-group = 512 threads = 8 waves, one work-group per CU. A wave owns 64 batch rows x KP basis columns (2 x KP/32
+// accumulator tiles). Its rows are loaded whole memory lines at a time and turned to the matrix cores' order through LDS of
+// the wave's own (nobody else needs them); the basis operand is shared by the waves and is streamed through LDS with direct
+// global->LDS loads. The basis is kept in HBM as "images": for each chunk of KC columns exactly the bytes LDS will hold,
+// so staging is a linear copy.
 #include "sage_internal.h"
 
 namespace sage {
@@ -124,14 +123,52 @@ __device__ __forceinline__ void split8(const u32x4& x0, const u32x4& x1, u32x4& 
 // splits; those pieces of the row operand are zeroed.
 //
 // Work-group = 512 threads = 8 waves (two per SIMD), one per CU, 512 batch rows x KP basis columns; a wave owns 64
-// rows (2 accumulator row tiles) x KP columns. Row operands go straight from global memory to registers, the pieces
-// of window m+2 being requested at the start of window m; images are streamed with direct global->LDS loads, also
-// two windows ahead.
+// rows (2 accumulator row tiles) x KP columns. The rows of window m+2 are requested into registers during window m and
+// turned at the start of window m+2; images are streamed with direct global->LDS loads, also two windows ahead.
 template <typename T>
 struct RowOp {
     u32x4 v[4];  // bf16 rows: v[j] = k-step j; fp32 rows: v[2j], v[2j+1] = k-step j
 };
-
+// Rows are loaded eight lanes to the 128 bytes of a row, and turned to the matrix cores' order through LDS, 32 rows (4 KB) at a
+// time in memory of the wave's own. (Loaded in that order, a row a lane and 16 bytes at a time, a line was asked for in
+// four instructions while it was still on its way, which the vector cache waits for: it stalled 71% of the cycles at fp32
+// rows of 1,048,576 columns and 35% at bf16 rows of 2,049,000, and half of the former's lines were fetched from L2 twice. 512
+// such fp32 rows with 128 vectors: 945 us, now 629; 1024 such bf16 rows: 1073, now 1026, where the matrix cores' rate, as far
+// as the clock holds under this load, is the bound: 1.07 PFLOP.)
+struct RowRaw {
+    u32x4 v[4];  // v[x]: piece lane % 8 of row 8 x + lane / 8
+};
+// Piece p of row r lies at r * 8 + (p ^ (r / 2) % 8): the 16 lanes that are served together fall on all banks, both ways. The
+// addresses of a lane's accesses differ by constants (added, or xored in), so that only three are kept.
+struct TurnAt {
+    unsigned w0, w1, r;  // bytes: stores of even and odd x, loads
+};
+template <typename T>
+__device__ __forceinline__ TurnAt turn_at(int piece0, int lane) {
+    const int row = lane >> 3, s = lane & 7, n = lane & 31, h = lane >> 5;
+    TurnAt at;
+    at.w0 = (unsigned)(piece0 + row * 8 + (s ^ (row >> 1))) * 16;
+    at.w1 = (unsigned)(piece0 + row * 8 + (s ^ (4 + (row >> 1)))) * 16;
+    at.r = (unsigned)(piece0 + n * 8 + ((sizeof(T) == 2 ? h : 2 * h) ^ ((n >> 1) & 7))) * 16;
+    return at;
+}
+template <typename T>
+__device__ __forceinline__ void turn_rows(u32x4* lds, TurnAt at, const RowRaw (&raw)[2], RowOp<T> (&a)[2]) {
+    char* const m = reinterpret_cast<char*>(lds);
+    asm volatile("" : "+v"(at.r));  // (the loads' addresses are formed here, not kept)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) *reinterpret_cast<u32x4*>(m + (x & 1 ? at.w1 : at.w0) + x * 1024) = raw[t].v[x];
+        asm volatile("" ::: "memory");  // (a wave's LDS accesses keep their order)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const unsigned p = sizeof(T) == 2 ? 2 * x : 4 * (x >> 1) + (x & 1);
+            a[t].v[x] = *reinterpret_cast<const u32x4*>(m + (at.r ^ (p * 16)));
+        }
+        asm volatile("" ::: "memory");
+    }
+}
 template <int NT, typename T>  // NT = KP / 32
 __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restrict__ G, int64_t R,
                                                                const u32x4* __restrict__ img,
@@ -143,7 +180,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
     constexpr int PB = 8 * (int)sizeof(T);  // bytes of a piece in a row: 16 or 32
     constexpr int IMG = 2 * KP * PPR;  // 16-byte pieces per image
     constexpr int KS = KC / 16;        // matrix-core k-steps per window
-    extern __shared__ u32x4 lds[];     // 4 * IMG
+    extern __shared__ u32x4 lds[];     // 4 * IMG, then 256 pieces of each wave
 
     const int id = blockIdx.x;
     const int xcd = id & 7, y = id >> 3;
@@ -163,38 +200,27 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
     // phase of this wave's rows, in pieces
     const int phi = (int)(((reinterpret_cast<uintptr_t>(G) + (uintptr_t)((row0 + wave) * S)) & 127) / PB);
 
-    // Lane offsets are taken from gbase = (first row of the work-group) - 128 bytes, so that they are never negative;
-    // every offset is clamped to its own row, so no lane reads outside the batch (pieces outside the row meet zeros
-    // of the image or are zeroed below). Rows >= R repeat row R-1; their results are not written.
+    // A load takes eight rows, eight lanes the 128 bytes of each (load x of row tile t: rows 32 t + 8 x + lane / 8). Lane
+    // offsets are taken from gbase = (first row of the work-group) - 128 bytes, so that they are never negative; every offset is
+    // clamped to its own row, so no lane reads outside the batch (pieces outside the row meet zeros of the image or are
+    // zeroed below). Rows >= R repeat row R-1; their results are not written.
     const char* gbase = reinterpret_cast<const char*>(G) + row0 * S - 128;
-    unsigned lbase[2];
-    const unsigned back = (unsigned)(PB * phi) - (unsigned)(PB * h);  // lbase - back = offset of the row's first byte
+    const int64_t last = R - 1 - row0 < 511 ? R - 1 - row0 : 511;
+    const unsigned lrow = (unsigned)((wave + 8 * (lane >> 3)) * S), last_row = (unsigned)(last * S);
+    const unsigned lofs = 128u + 16u * (unsigned)(lane & 7) - (unsigned)(PB * phi);
+    auto load_rows = [&](RowRaw& a, int t, int64_t m) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        int64_t r = row0 + wave + 8 * (t * 32 + n);
-        if (r > R - 1) r = R - 1;
-        lbase[t] = (unsigned)((r - row0) * S) + 128u - back;
-    }
-    // piece x of window m for row tile t
-    auto load_piece = [&](RowOp<T>& a, int t, int64_t m, int x) __attribute__((always_inline)) {
-        const int xoff = sizeof(T) == 2 ? 32 * x : 64 * (x >> 1) + 16 * (x & 1);
-        const unsigned lo = lbase[t] + back, hi = lo + (unsigned)S - 16u;
-        unsigned o = lbase[t] + (unsigned)(m * 128) + (unsigned)xoff;
-        o = o < lo ? lo : o;
-        o = o > hi ? hi : o;
-        a.v[x] = *reinterpret_cast<const u32x4*>(gbase + o);
+        for (int x = 0; x < 4; ++x) {
+            unsigned r = lrow + (unsigned)((t * 32 + 8 * x) * 8) * (unsigned)S;
+            r = r > last_row ? last_row : r;
+            const unsigned lo = r + 128u, hi = lo + (unsigned)S - 16u;
+            unsigned o = r + lofs + (unsigned)(m * 128);
+            o = o < lo ? lo : o;
+            o = o > hi ? hi : o;
+            a.v[x] = *reinterpret_cast<const u32x4*>(gbase + o);
+        }
     };
-    // LDS piece index (inside one image, column tile 0) of this lane's basis operand for k-step j, and whether it
-    // lies in the previous image
-    int boff[KS];
-    bool prev[KS];
-#pragma unroll
-    for (int j = 0; j < KS; ++j) {
-        const int q = 2 * j + h;
-        prev[j] = q < phi;
-        boff[j] = img_piece<KC>(n, (q - phi) & (PPR - 1));
-    }
-
+    const TurnAt turn = turn_at<T>(4 * IMG + wave * 256, lane);
     f32x16 acc[2][NT];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -226,17 +252,17 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
     // One window. Step s = (k-step j, column tile ct) in order; the basis operand of step s + 1 is fetched from LDS
     // before the matrix-core instructions of step s are issued, and the scheduler may not move anything across a
     // step (left alone it hoists a whole window of LDS reads and spills). The ring has four slots, image c in slot
-    // c mod 4: m-1 and m are read, m+1 has landed or is landing, m+2 is requested now. a: row operand of this window;
-    // afar: buffer that receives window m+2.
-    auto visit = [&](RowOp<T> (&a)[2], RowOp<T> (&afar)[2], int64_t m) __attribute__((always_inline)) {
+    // c mod 4: m-1 and m are read, m+1 has landed or is landing, m+2 is requested now. raw: the rows of this window as they
+    // were loaded; it receives those of window m+2.
+    auto visit = [&](RowRaw (&raw)[2], int64_t m) __attribute__((always_inline)) {
         const int sp = (int)((m - 1) & 3), sc = (int)(m & 3);
+        RowOp<T> a[2];
+        turn_rows<T>(lds, turn, raw, a);
         stage(m + 2, (int)((m + 2) & 3));
-        // The row loads of window m+2 go out in two bursts, row tile 0 now and row tile 1 half way through the window
-        // (measured: 12% faster than one burst of 8). Within a burst the four pieces of a line are asked for back to
-        // back, while the line is still on its way or fresh in the vector cache.
+        // The row loads of window m+2 go out in two bursts, row tile 0 a quarter through the window, when the registers of
+        // the first operands are free again (the loads of this window's rows and accumulators fill the file otherwise: spills,
+        // whose reloads the count below would not know), row tile 1 half way.
         const int64_t m2 = m + 2 > c1 ? c1 : m + 2;  // beyond the last window: repeat it (never used)
-#pragma unroll
-        for (int x = 0; x < 4; ++x) load_piece(afar[0], 0, m2, x);
         if (m == c0 || m == c1) {
             const bool first = m == c0, last = m == c1;
 #pragma unroll
@@ -247,12 +273,18 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
                     if ((first && q < phi) || (last && q >= phi)) a[t].v[x] = u32x4{0u, 0u, 0u, 0u};
                 }
         }
-        int baddr[KS];
-#pragma unroll
-        for (int j = 0; j < KS; ++j) baddr[j] = boff[j] + (prev[j] ? sp : sc) * IMG;
+        // LDS piece (column tile 0) of this lane's basis operand for k-step j, which may lie in the previous image. Formed when
+        // it is needed: registers are short.
+        int hq = h;
+        asm volatile("" : "+v"(hq));
+        auto operand_at = [&](int j) __attribute__((always_inline)) {
+            const int q = 2 * j + hq;
+            return img_piece<KC>(n, (q - phi) & (PPR - 1)) + (q < phi ? sp : sc) * IMG;
+        };
         constexpr int STEPS = KS * 2 * NT;
         u32x4 b[2];
-        b[0] = lds[baddr[0]];
+        int at = operand_at(0);
+        b[0] = lds[at];
         u32x4 ahi[2], alo[2];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -269,12 +301,11 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
             }
             if (s + 1 < STEPS) {
                 const int j2 = (s + 1) / (2 * NT), ct2 = (s + 1) % (2 * NT);
-                b[(s + 1) % 2] = lds[baddr[j2] + ct2 * 32 * PPR];
+                if (ct2 == 0) at = operand_at(j2);
+                b[(s + 1) % 2] = lds[at + ct2 * 32 * PPR];
             }
-            if (s == STEPS / 2) {
-#pragma unroll
-                for (int x = 0; x < 4; ++x) load_piece(afar[1], 1, m2, x);
-            }
+            if (s == STEPS / 4) load_rows(raw[0], 0, m2);
+            if (s == STEPS / 2) load_rows(raw[1], 1, m2);
             const u32x4 bb = b[s % 2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) acc[t][ct % NT] = mfma_bf16(ahi[t], bb, acc[t][ct % NT]);
@@ -303,36 +334,31 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
     // some memory channels idle (5.1 TB/s for the row stream alone against 6.2 TB/s with rotated starts). The two row
     // tiles of a split keep the same start, so that they still share the basis images through L2. A run of
     // consecutive windows needs the ring primed with the images around its first window, so the walk is two runs.
-    RowOp<T> a0[2], a1[2], a2[2];
-    // (always_inline: called twice, the compiler otherwise makes the fp32-row instance a real function with the
-    // accumulators in scratch memory)
-    auto run = [&](int64_t ms, int64_t len) __attribute__((always_inline)) {
-        stage(ms - 1, (int)((ms - 1) & 3));
-        stage(ms, (int)(ms & 3));
-        stage(ms + 1, (int)((ms + 1) & 3));
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                load_piece(a0[t], t, ms, x);
-                load_piece(a1[t], t, ms + 1, x);
-            }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        // three windows per trip: the row buffers return to their roles
-        int64_t i = 0;
-        for (; i + 2 < len; i += 3) {
-            visit(a0, a2, ms + i);
-            visit(a1, a0, ms + i + 1);
-            visit(a2, a1, ms + i + 2);
-        }
-        if (i < len) visit(a0, a2, ms + i);
-        if (i + 1 < len) visit(a1, a0, ms + i + 1);
-    };
+    RowRaw a0[2], a1[2];
     if (nv > 0) {
         const int64_t rot = nv >= 8 ? (int64_t)(((unsigned)split * 37u) % (unsigned)(nv - 4)) + 2 : 0;  // 2 .. nv - 3
-        run(c0 + rot, nv - rot);
-        if (rot > 0) run(c0, rot);
+        int64_t ms = c0 + rot, me = c0 + nv;
+#pragma unroll 1
+        for (;;) {  // (one copy of the loop for both runs)
+            stage(ms - 1, (int)((ms - 1) & 3));
+            stage(ms, (int)(ms & 3));
+            stage(ms + 1, (int)((ms + 1) & 3));
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                load_rows(a0[t], t, ms);
+                load_rows(a1[t], t, ms + 1 > c1 ? c1 : ms + 1);
+            }
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+#pragma unroll 1
+            for (int64_t m = ms; m < me; m += 2) {  // two windows per trip: the row buffers return to their roles
+                visit(a0, m);
+                if (m + 1 < me) visit(a1, m + 1);
+            }
+            if (ms == c0) break;
+            ms = c0;
+            me = c0 + rot;
+        }
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS when the work-group ends
     }
 
@@ -592,7 +618,7 @@ template <int NT, typename T>
 static hipError_t launch_split_t(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
                                  const Dims& d, hipStream_t st) {
     constexpr int KC = 128 / (int)sizeof(T);
-    const int lds = (parts == 3 ? 3 * 3 : 4 * 2) * NT * 32 * (KC / 8) * 16;
+    const int lds = (parts == 3 ? 3 * 3 : 4 * 2) * NT * 32 * (KC / 8) * 16 + (parts == 3 ? 0 : 8 * 256 * 16);
     const void* kern = parts == 3 ? (const void*)project_any_kernel<NT, T> : (const void*)project_split_kernel<NT, T>;
     if (hipError_t ea = ensure_dynamic_lds(kern, lds); ea != hipSuccess) return ea;
     const int64_t chunks = (d.D + KC - 1) / KC;

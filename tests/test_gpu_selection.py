@@ -78,6 +78,36 @@ def test_projection_of_rows_of_any_alignment(dtype, D, k):
     s.close()
 
 
+# Rows on multiples of 8 columns: one window, partial ones, rows that start anywhere in a line, row counts that end inside a
+# wave's rows, several row tiles, a batch over 4 GiB (lane offsets have 32 bits).
+@pytest.mark.parametrize("n,D,k,dtype", [(n, D, k, t) for n in (1, 63, 700) for D in (64, 72, 1000) for k in (3, 40, 100)
+                                         for t in ("f32", "bf16")] + [(1100, 1_048_576, 100, "f32"), (1100, 2_049_000, 100, "bf16")])
+def test_projection_of_aligned_rows_at_the_edges_of_its_tiles(n, D, k, dtype):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    gen = torch.Generator(device="cuda").manual_seed(n + D + k)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    flat = torch.empty(n * D + 8, dtype=td, device="cuda")
+    for i in range(0, n * D + 8, 1 << 28):
+        part = flat[i:i + (1 << 28)]
+        part.copy_(torch.randn(part.numel(), generator=gen, device="cuda"))
+    G = flat[8:].view(n, D)
+    V = torch.randn(k, D, generator=gen, device="cuda")
+    s = Sage(max(2 * k, 2), D, dtype=dtype, max_rows=n)
+    s.set_basis(V)
+    s.score(G)
+    got = s.zhat().double()
+    Vd = V.double().T.contiguous()
+    Z = torch.cat([G[i:i + 32].double() @ Vd for i in range(0, n, 32)])
+    norm = Z.norm(dim=1, keepdim=True)
+    scale = torch.cat([G[i:i + 32].double().norm(dim=1, keepdim=True) for i in range(0, n, 32)]) * V.double().norm(dim=1).max()
+    # rows and basis in two bf16 parts: each good to 2^-17, and their low parts' product of 2^-18 is left out
+    assert float(((got - Z / norm).abs() * norm / scale).max()) <= 2.0 ** -16 + 2.0 ** -18
+    s.close()
+
+
 # the answer's signal: more callers than words, and the largest export that one work-group copies
 def test_topm_from_many_threads():
     from concurrent.futures import ThreadPoolExecutor
