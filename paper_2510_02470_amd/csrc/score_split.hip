@@ -14,6 +14,8 @@
 // the wave's own (nobody else needs them); the basis operand is shared by the waves and is streamed through LDS with direct
 // global->LDS loads. The basis is kept in HBM as "images": for each chunk of KC columns exactly the bytes LDS will hold,
 // so staging is a linear copy.
+#include <type_traits>
+
 #include "sage_internal.h"
 
 namespace sage {
@@ -380,13 +382,26 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
 // before (157 us for 2048 rows of 51,300 with 64 vectors), so here the basis has three bf16 parts (24 bits) and fp32 rows
 // are split the same way: six products (three for bf16 rows, which are exact), the fp32 result to a few 2^-24 per term.
 //
-// Shapes as in project_split_kernel: 512 threads, a wave owns 64 rows x KP columns, its row pieces come from global memory
-// two windows ahead (one with four column tiles, whose accumulators leave no room for a third set of row registers).
-// Every window is a whole image, so the ring has three slots. The last, partial window of the row is taken element by
-// element after the others, by the split that owns it.
+// Shapes as in project_split_kernel: 512 threads, a wave owns 64 rows x KP columns, rows are loaded eight lanes to 128 bytes, two
+// windows ahead, and turned through LDS. Every window is a whole image, so the ring has three slots (two where three do not
+// fit, four column tiles of bf16 rows: a window is long there, an image requested at its start lands within it). The last,
+// partial window of the row is taken after the others, by the split that owns it.
+//
+// With rows loaded in the matrix cores' order (the vector cache stalled four fifths of the time), and turned: 2048 rows of
+// 51,300 fp32, 64 vectors 121 and 113 us; 512 rows of 1,000,001 fp32, 128 vectors 965 and 825; 1024 such rows of bf16 1100 and
+// 715. The rows' loads remain the bound of the first: each takes two lines (103 us where rows start on a line), and with one
+// product instead of six it takes 104.
 template <typename T>
 struct __attribute__((packed, aligned(sizeof(T)))) AnyPiece {
     u32x4 v;
+};
+
+template <int NT, typename T>
+struct AnyShape {
+    static constexpr int IMG = 3 * NT * 32 * (16 / (int)sizeof(T));  // 16-byte pieces of an image
+    static constexpr int SLOTS = sizeof(T) == 2 && NT == 4 ? 2 : 3;
+    static constexpr int LDS = (SLOTS * IMG + 8 * 256) * 16;
+    static_assert(LDS <= 160 * 1024, "of one CU");
 };
 
 template <int NT, typename T>
@@ -397,10 +412,9 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     constexpr int KP = NT * 32;
     constexpr int KC = 128 / (int)sizeof(T);
     constexpr int PPR = KC / 8;
-    constexpr int IMG = 3 * KP * PPR;
+    constexpr int IMG = AnyShape<NT, T>::IMG, SLOTS = AnyShape<NT, T>::SLOTS;
     constexpr int KS = KC / 16;
-    constexpr int NB = NT == 4 ? 2 : 3;  // sets of row registers
-    extern __shared__ u32x4 lds[];       // 3 * IMG
+    extern __shared__ u32x4 lds[];  // SLOTS * IMG, then 256 pieces of each wave
 
     const int id = blockIdx.x;
     const int xcd = id & 7, y = id >> 3;
@@ -419,24 +433,18 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     const int64_t S = D * (int64_t)sizeof(T);
     const int64_t row0 = (int64_t)rt * 512;
     const char* gbase = reinterpret_cast<const char*>(G) + row0 * S;
-    unsigned lrow[2];  // rows >= R repeat row R - 1; their results are not written
+    // rows >= R repeat row R - 1; their results are not written
+    const int64_t last = R - 1 - row0 < 511 ? R - 1 - row0 : 511;
+    const unsigned lrow = (unsigned)((wave * 64 + (lane >> 3)) * S), last_row = (unsigned)(last * S);
+    auto load_rows = [&](RowRaw& a, int t, int64_t m) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        int64_t r = row0 + wave * 64 + t * 32 + n;
-        if (r > R - 1) r = R - 1;
-        lrow[t] = (unsigned)((r - row0) * S) + 8u * (unsigned)sizeof(T) * (unsigned)h;
-    }
-    // register x of a row operand: bf16: k-step x; fp32: half x & 1 of k-step x >> 1
-    auto piece_at = [](int x) { return sizeof(T) == 2 ? 32 * x : 64 * (x >> 1) + 16 * (x & 1); };
-    auto load_rows = [&](RowOp<T>& a, int t, int64_t m) __attribute__((always_inline)) {
-        const unsigned o = lrow[t] + (unsigned)(m * 128);
-#pragma unroll
-        for (int x = 0; x < 4; ++x) a.v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + o + piece_at(x))->v;
+        for (int x = 0; x < 4; ++x) {
+            unsigned r = lrow + (unsigned)(t * 32 + 8 * x) * (unsigned)S;
+            r = r > last_row ? last_row : r;
+            a.v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (r + 16u * (unsigned)(lane & 7) + (unsigned)(m * 128)))->v;
+        }
     };
-    int boff[KS];
-#pragma unroll
-    for (int j = 0; j < KS; ++j) boff[j] = img_piece<KC>(n, 2 * j + h);
-
+    const TurnAt turn = turn_at<T>(SLOTS * IMG + wave * 256, lane);
     f32x16 acc[2][NT];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -459,12 +467,15 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     };
 
     static_assert(8 + VL <= 15, "the low field of the count");
-    // the products of one window: row operands a, image in slot sc
-    auto multiply = [&](const RowOp<T> (&a)[2], int sc, auto&& half_way) __attribute__((always_inline)) {
+    int sc = 0;  // slot of the present window's image
+    // the products of one window: row operands a
+    auto multiply = [&](const RowOp<T> (&a)[2], auto&& between) __attribute__((always_inline)) {
         constexpr int STEPS = KS * 3 * NT;  // (k-step, part of the basis, column tile)
+        int hq = h;
+        asm volatile("" : "+v"(hq));  // (addresses are formed when they are needed: registers are short)
         auto addr = [&](int s) {
             const int j = s / (3 * NT), pt = (s / NT) % 3, ct = s % NT;
-            return boff[j] + sc * IMG + (pt * KP + ct * 32) * PPR;
+            return img_piece<KC>(n, 2 * j + hq) + sc * IMG + (pt * KP + ct * 32) * PPR;
         };
         u32x4 b[2];
         b[0] = lds[addr(0)];
@@ -492,7 +503,8 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
                 }
             }
             if (s + 1 < STEPS) b[(s + 1) % 2] = lds[addr(s + 1)];
-            if (s == STEPS / 2) half_way();
+            if (s == STEPS / 4) between(0);
+            if (s == STEPS / 2) between(1);
             const u32x4 bb = b[s % 2];
             constexpr int QS = sizeof(T) == 2 ? 1 : 3;
 #pragma unroll
@@ -504,70 +516,101 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // One window: its image is in slot sc; the image of m + 2 and the rows of m + NB - 1 are requested.
-    auto visit = [&](const RowOp<T> (&a)[2], RowOp<T> (&afar)[2], int64_t m, int sc) __attribute__((always_inline)) {
-        stage(m + 2, sc == 0 ? 2 : sc - 1);
-        const int64_t mf = m + NB - 1 > c1 - 1 ? c1 - 1 : m + NB - 1;  // beyond the last window: repeat it (never used)
-        load_rows(afar[0], 0, mf);
-        multiply(a, sc, [&]() __attribute__((always_inline)) { load_rows(afar[1], 1, mf); });
-        // at most this window's loads stay outstanding: image m + 1 (and rows m + 1) have landed
+    // One window: its image is in slot sc, its rows in raw as they were loaded, which receives the rows of window m + 2. The image
+    // requested is that of m + SLOTS - 1. more: false where the split has two windows at most, as those of small projections
+    // have, and nothing beyond them is requested (333 rows of 25,447 bf16: 22.2 us with such requests, 19.5
+    // without; 20.5 before rows were turned).
+    auto visit = [&](RowRaw (&raw)[2], int64_t m, auto more) __attribute__((always_inline)) {
+        constexpr bool MORE = decltype(more)::value;
+        const int64_t m2 = m + 2 > c1 - 1 ? c1 - 1 : m + 2;  // beyond the last window: repeat it (never used)
+        RowOp<T> a[2];
+        turn_rows<T>(lds, turn, raw, a);
+        if (MORE || SLOTS == 2) stage(m + SLOTS - 1, sc == 0 ? SLOTS - 1 : sc - 1);
+        multiply(a, [&](int t) __attribute__((always_inline)) {
+            if constexpr (MORE) load_rows(raw[t], t, m2);
+        });
+        // at most this window's row loads, with three slots its image loads too, stay outstanding: image m + 1 and rows m + 1
+        // have landed
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (8 + VL));
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (MORE ? 8 + (SLOTS == 3 ? VL : 0) : 0));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
+        sc = sc == SLOTS - 1 ? 0 : sc + 1;
     };
+    constexpr std::true_type MORE{};
+    constexpr std::false_type LAST{};
 
-    RowOp<T> a0[2], a1[2], a2[2];
     const int64_t len = c1 - c0;
-    if (len > 0) {
+    auto begin = [&](RowRaw (&a0)[2], RowRaw (&a1)[2]) __attribute__((always_inline)) {
         stage(c0, 0);
-        stage(c0 + 1, 1);
+        if (SLOTS == 3) stage(c0 + 1, 1);
         const int64_t m1 = len > 1 ? c0 + 1 : c0;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             load_rows(a0[t], t, c0);
-            if (NB == 3) load_rows(a1[t], t, m1);
+            load_rows(a1[t], t, m1);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        int64_t i = 0;
-        if constexpr (NB == 3) {
-            for (; i + 2 < len; i += 3) {
-                visit(a0, a2, c0 + i, 0);
-                visit(a1, a0, c0 + i + 1, 1);
-                visit(a2, a1, c0 + i + 2, 2);
-            }
-            if (i < len) visit(a0, a2, c0 + i, 0);
-            if (i + 1 < len) visit(a1, a0, c0 + i + 1, 1);
-        } else {
-            for (int sc = 0; i < len; i += 2) {
-                visit(a0, a1, c0 + i, sc);
-                sc = sc == 2 ? 0 : sc + 1;
-                if (i + 1 < len) visit(a1, a0, c0 + i + 1, sc);
-                sc = sc == 2 ? 0 : sc + 1;
-            }
+    };
+    if (len > 2) {
+        RowRaw a0[2], a1[2];
+        begin(a0, a1);
+#pragma unroll 1
+        for (int64_t m = c0; m < c1; m += 2) {  // two windows per trip: the row buffers return to their roles
+            visit(a0, m, MORE);
+            if (m + 1 < c1) visit(a1, m + 1, MORE);
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS any more
+    }
+    if (len == 1 || len == 2) {
+        RowRaw a0[2], a1[2];
+        begin(a0, a1);
+        visit(a0, c0, LAST);
+        if (len == 2) visit(a1, c0 + 1, LAST);
     }
     if (tail) {  // work-group uniform
         __syncthreads();
         stage(full, 0);
+        // The last 128 bytes of every row are loaded, and the columns beyond the whole windows picked out of them in LDS.
+        const int left = (int)(D - full * KC);
+        RowRaw raw[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
+                unsigned r = lrow + (unsigned)(t * 32 + 8 * x) * (unsigned)S;
+                r = r > last_row ? last_row : r;
+                raw[t].v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (r + (unsigned)S - 128u + 16u * (unsigned)(lane & 7)))->v;
+            }
+        RowOp<T> a[2];
+        char* const l = reinterpret_cast<char*>(lds);
+        const unsigned line = (unsigned)(SLOTS * IMG + wave * 256 + n * 8) * 16u, swz = (unsigned)((n >> 1) & 7) * 16u;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) *reinterpret_cast<u32x4*>(l + (x & 1 ? turn.w1 : turn.w0) + x * 1024) = raw[t].v[x];
+            asm volatile("" ::: "memory");  // (a wave's LDS accesses keep their order)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
                 constexpr int E = 16 / (int)sizeof(T);
-                const int64_t col = full * KC + (piece_at(x) + 8 * (int)sizeof(T) * h) / (int)sizeof(T);
-                const T* src = reinterpret_cast<const T*>(gbase + lrow[t] + (unsigned)(full * 128) + piece_at(x));
+                const int at = (sizeof(T) == 2 ? 16 * x : 16 * (x >> 1) + 4 * (x & 1)) + 8 * h;
                 T v[E];
 #pragma unroll
-                for (int e = 0; e < E; ++e) v[e] = col + e < D ? src[e] : (T)0;
-                __builtin_memcpy(&a0[t].v[x], v, 16);
+                for (int e = 0; e < E; ++e) {
+                    const int c = at + e < left ? KC - left + at + e : 0;  // column of the 128 bytes
+                    const T w = *reinterpret_cast<const T*>(l + line + (((unsigned)c * (unsigned)sizeof(T)) ^ swz));
+                    v[e] = at + e < left ? w : (T)0;
+                }
+                __builtin_memcpy(&a[t].v[x], v, 16);
             }
+            asm volatile("" ::: "memory");
+        }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        multiply(a0, 0, []() {});
+        sc = 0;
+        multiply(a, [](int) {});
     }
 
     float* out = partial + (int64_t)split * R * KP;
@@ -618,7 +661,7 @@ template <int NT, typename T>
 static hipError_t launch_split_t(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
                                  const Dims& d, hipStream_t st) {
     constexpr int KC = 128 / (int)sizeof(T);
-    const int lds = (parts == 3 ? 3 * 3 : 4 * 2) * NT * 32 * (KC / 8) * 16 + (parts == 3 ? 0 : 8 * 256 * 16);
+    const int lds = parts == 3 ? AnyShape<NT, T>::LDS : 4 * 2 * NT * 32 * (KC / 8) * 16 + 8 * 256 * 16;
     const void* kern = parts == 3 ? (const void*)project_any_kernel<NT, T> : (const void*)project_split_kernel<NT, T>;
     if (hipError_t ea = ensure_dynamic_lds(kern, lds); ea != hipSuccess) return ea;
     const int64_t chunks = (d.D + KC - 1) / KC;
