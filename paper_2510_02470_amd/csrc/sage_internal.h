@@ -294,13 +294,27 @@ hipError_t launch_project_outer(const void* E, const void* H, int dtype, int64_t
 hipError_t launch_cosine(const float* zhat, int64_t N, int k, const double* ssum, float* alpha, hipStream_t st);
 struct SelectWork {
     uint32_t* hist;      // TOPM_HIST_WORDS: one histogram per digit
-    uint32_t* state;     // 8: {prefix key, count left} after each digit
-    uint32_t* blk_gt;    // per block: count of keys > threshold
-    uint32_t* blk_eq;    // per block: count of keys == threshold
+    uint32_t* state;     // 4: {digits found, count left} after the first and the second digit
+    uint32_t* blk_gt;    // per block: keys above all that share the first two digits
+    uint32_t* blk_in;    // per block: keys that share them
+    uint16_t* table;     // per block, 1024: those with a third digit of at least the index
     int64_t nblk_cap;
 };
 constexpr int TOPM_HIST_WORDS = 4096 + 2 * 1024;
 constexpr int SELECT_BLOCK = 4096;  // keys per block in the compaction passes
+constexpr int SELECT_STATE_WORDS = 64;  // a 256-byte slot of its own
+constexpr int SELECT_BLOCK_WORDS = 2 + 1024 / 2;  // counters and table of a block
+// a work space of blocks blocks at p: TOPM_HIST_WORDS + SELECT_STATE_WORDS + blocks * SELECT_BLOCK_WORDS words
+inline SelectWork select_work_at(uint32_t* p, int64_t blocks) {
+    SelectWork w{};
+    w.hist = p;
+    w.state = w.hist + TOPM_HIST_WORDS;
+    w.blk_gt = w.state + SELECT_STATE_WORDS;
+    w.blk_in = w.blk_gt + blocks;
+    w.table = (uint16_t*)(w.blk_in + blocks);
+    w.nblk_cap = blocks;
+    return w;
+}
 bool topm_needs_work(int64_t N);    // false: launch_topm uses no work space
 // A word of pinned host memory that the last kernel of a call sets to `token` once the call's results are in memory, for a
 // host that spins on it: 6.5 us from launch to answer where hipStreamSynchronize takes 11.5. null: no signal.

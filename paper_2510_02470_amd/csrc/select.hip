@@ -46,8 +46,11 @@ hipError_t launch_cosine(const float* zhat, int64_t N, int k, const double* ssum
 // there is to move is 4 N bytes, so what counts is the number of launches (about 3 us each with its gap) and serial work
 // inside them:
 //   N <= TOPM_ONE: one work-group does everything, keys in registers, histograms in LDS; one launch, no work space;
-//   else: clear, three histograms, count, emit. Every work-group of the next kernel reads the histogram and finds the
-//         digit itself (a scan over the bins by 1024 threads), so there are no kernels between them.
+//   else: clear, two histograms, the third with a table for each block of keys, emit. Every work-group of the next kernel
+//         reads the histogram and finds the digit itself (a scan over the bins by 1024 threads), so there are no kernels
+//         between them. The tables answer, whatever the last digit turns out to be, how many keys of a block are above it and
+//         how many equal it, which took a kernel of its own between the last histogram and emit (a million keys: 24.2 us
+//         with it, 22.4 without, 19.9 with fewer work-groups for the histograms, see launch_topm).
 // The first digit has 12 bits because scores crowd into a few binary orders of magnitude: with 8 bits most lanes of a wave
 // add to one of two or three LDS words and the adds are done one after the other.
 // (One digit of 8 bits per launch with a one-thread pick kernel after each took 13 launches: 86 us at N = 2048 and 80 us at
@@ -98,9 +101,8 @@ __global__ __launch_bounds__(TOPM_T) void topm_clear_kernel(uint32_t* __restrict
     hist[blockIdx.x * TOPM_T + threadIdx.x] = 0;
 }
 
-// Histogram of digit P (0: bits 31..20, 1: bits 19..10, 2: bits 9..0) of the keys that share the digits found so far.
-// state[2 (P - 1)], state[2 (P - 1) + 1]: the prefix and the count left, found from the previous histogram, left for the
-// next kernel.
+// Histogram of digit P (0: bits 31..20, 1: bits 19..10) of the keys that share the digits found so far. state[0], state[1]: the
+// first digit and the count left, found from the first histogram, left for the next kernel.
 template <int P>
 __global__ __launch_bounds__(TOPM_T) void topm_hist_kernel(const float* __restrict__ alpha, int64_t N, uint32_t m,
                                                            uint32_t* __restrict__ hist, uint32_t* __restrict__ state) {
@@ -111,17 +113,11 @@ __global__ __launch_bounds__(TOPM_T) void topm_hist_kernel(const float* __restri
     for (int b = tid; b < BINS; b += TOPM_T) h[b] = 0;
     uint32_t prefix = 0;
     if constexpr (P > 0) {
-        uint32_t digit, rest;
-        if constexpr (P == 1) {
-            pick_bin<TOPM_T, BINS1>(hist, m, pw, digit, rest);
-            prefix = digit;
-        } else {
-            pick_bin<TOPM_T, BINS2>(hist + BINS1, state[1], pw, digit, rest);
-            prefix = (state[0] << 10) | digit;
-        }
+        uint32_t rest;
+        pick_bin<TOPM_T, BINS1>(hist, m, pw, prefix, rest);
         if (blockIdx.x == 0 && tid == 0) {
-            state[2 * (P - 1)] = prefix;
-            state[2 * (P - 1) + 1] = rest;
+            state[0] = prefix;
+            state[1] = rest;
         }
     } else {
         __syncthreads();
@@ -137,61 +133,73 @@ __global__ __launch_bounds__(TOPM_T) void topm_hist_kernel(const float* __restri
             if (i0 + u * stride >= N) continue;
             if (P == 0) atomicAdd(&h[key >> 20], 1u);
             if (P == 1 && (key >> 20) == prefix) atomicAdd(&h[(key >> 10) & 1023u], 1u);
-            if (P == 2 && (key >> 10) == prefix) atomicAdd(&h[key & 1023u], 1u);
         }
     }
     __syncthreads();
-    uint32_t* g = hist + (P == 0 ? 0 : P == 1 ? BINS1 : BINS1 + BINS2);
+    uint32_t* g = hist + (P == 0 ? 0 : BINS1);
     for (int b = tid; b < BINS; b += TOPM_T)
         if (const uint32_t v = h[b]) atomicAdd(&g[b], v);
 }
 
-// per block of SELECT_BLOCK keys: how many are above / equal to the threshold key, which goes to state[4], state[5]
-__global__ __launch_bounds__(TOPM_T) void topm_count_kernel(const float* __restrict__ alpha, int64_t N,
-                                                            const uint32_t* __restrict__ hist, uint32_t* __restrict__ state,
-                                                            uint32_t* __restrict__ blk_gt, uint32_t* __restrict__ blk_eq) {
-    constexpr int C = SELECT_BLOCK / TOPM_T;
+// Histogram of the last digit (bits 9..0), and for each block of 1024 C keys: blk_gt, how many are above all that share
+// the first 22 bits, blk_in, how many share them, and if any do, table[d], how many of those have a last digit of d or more.
+template <int C>
+__global__ __launch_bounds__(TOPM_T) void topm_table_kernel(const float* __restrict__ alpha, int64_t N,
+                                                            uint32_t* __restrict__ hist, uint32_t* __restrict__ state,
+                                                            uint32_t* __restrict__ blk_gt, uint32_t* __restrict__ blk_in,
+                                                            uint16_t* __restrict__ table) {
+    static_assert(BINS2 == TOPM_T && C * TOPM_T < 65536, "a bin a thread, counts of 16 bits");
+    __shared__ uint32_t h[BINS2], tot[16], sg, si;
     __shared__ PickWork pw;
-    __shared__ uint32_t sg, se;
-    const int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK + threadIdx.x;
+    const int tid = threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * (C * TOPM_T) + tid;
     uint32_t key[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) key[c] = base + c * TOPM_T < N ? score_key(alpha[base + c * TOPM_T]) : 0u;
-    if (threadIdx.x == 0) sg = se = 0;
+    h[tid] = 0;
+    if (tid == 0) sg = si = 0;
     uint32_t digit, rest;
-    pick_bin<TOPM_T, BINS2>(hist + BINS1 + BINS2, state[3], pw, digit, rest);
-    const uint32_t T = (state[2] << 10) | digit;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        state[4] = T;
-        state[5] = rest;
+    pick_bin<TOPM_T, BINS2>(hist + BINS1, state[1], pw, digit, rest);
+    const uint32_t prefix = (state[0] << 10) | digit;
+    if (blockIdx.x == 0 && tid == 0) {
+        state[2] = prefix;
+        state[3] = rest;
     }
-    uint32_t g = 0, e = 0;
+    uint32_t g = 0, i = 0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        const bool in = base + c * TOPM_T < N;
-        g += (uint32_t)__popcll(__ballot(in && key[c] > T));
-        e += (uint32_t)__popcll(__ballot(in && key[c] == T));
+        const bool in = base + c * TOPM_T < N, eq = in && (key[c] >> 10) == prefix;
+        g += (uint32_t)__popcll(__ballot(in && (key[c] >> 10) > prefix));
+        i += (uint32_t)__popcll(__ballot(eq));
+        if (eq) atomicAdd(&h[key[c] & 1023u], 1u);
     }
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&sg, g);
-        atomicAdd(&se, e);
+    if ((tid & 63) == 0) {
+        if (g) atomicAdd(&sg, g);
+        if (i) atomicAdd(&si, i);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         blk_gt[blockIdx.x] = sg;
-        blk_eq[blockIdx.x] = se;
+        blk_in[blockIdx.x] = si;
     }
+    if (si == 0) return;
+    const int d = BINS2 - 1 - tid;
+    const uint32_t v = h[d];
+    if (v) atomicAdd(&hist[BINS1 + BINS2 + d], v);
+    table[(int64_t)blockIdx.x * BINS2 + d] = (uint16_t)block_scan<TOPM_T>(v, tot);
 }
 
-// every work-group adds up the counts of the blocks before its own (at most 4096 of them for 16.7 million keys)
+// every work-group adds up the counts of the blocks before its own
+template <int C>
 __global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restrict__ alpha, int64_t N,
+                                                           const uint32_t* __restrict__ hist,
                                                            const uint32_t* __restrict__ state,
                                                            const uint32_t* __restrict__ blk_gt,
-                                                           const uint32_t* __restrict__ blk_eq,
-                                                           int64_t* __restrict__ out_idx) {
-    constexpr int C = SELECT_BLOCK / TOPM_T;
+                                                           const uint32_t* __restrict__ blk_in,
+                                                           const uint16_t* __restrict__ table, int64_t* __restrict__ out_idx) {
     __shared__ uint32_t cnt[16 * C], tot[16], sg, se;
-    const int64_t base = (int64_t)blockIdx.x * SELECT_BLOCK;
+    __shared__ PickWork pw;
+    const int64_t base = (int64_t)blockIdx.x * (C * TOPM_T);
     uint32_t key[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -199,23 +207,29 @@ __global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restri
         key[c] = i < N ? score_key(alpha[i]) : 0u;
     }
     if (threadIdx.x == 0) sg = se = 0;
+    uint32_t digit, rest;
+    pick_bin<TOPM_T, BINS2>(hist + BINS1 + BINS2, state[3], pw, digit, rest);
     uint32_t g = 0, e = 0;
     for (unsigned b = threadIdx.x; b < blockIdx.x; b += TOPM_T) {
         g += blk_gt[b];
-        e += blk_eq[b];
+        if (blk_in[b]) {
+            const uint16_t* t = table + (int64_t)b * BINS2 + digit;
+            const uint32_t above = digit + 1 < BINS2 ? t[1] : 0u;
+            g += above;
+            e += t[0] - above;
+        }
     }
     g = wave_scan(g);
     e = wave_scan(e);
-    __syncthreads();
     if ((threadIdx.x & 63) == 63 && (g | e)) {
         atomicAdd(&sg, g);
         atomicAdd(&se, e);
     }
     __syncthreads();
-    emit_keys<TOPM_T, C>(key, base, state[4], state[5], sg, se, cnt, tot, out_idx);
+    emit_keys<TOPM_T, C>(key, base, (state[2] << 10) | digit, rest, sg, se, cnt, tot, out_idx);
 }
 
-// One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of six launches wins.
+// One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of five launches wins.
 constexpr int64_t TOPM_ONE = 32 * TOPM_T;
 
 // Small copies for a caller that waits: one work-group, then the signal.
@@ -247,17 +261,30 @@ hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_id
 #undef SAGE_ONE
         return hipGetLastError();
     }
-    const int64_t nblk = (N + SELECT_BLOCK - 1) / SELECT_BLOCK;
-    if (nblk > w.nblk_cap) return hipErrorInvalidValue;
+    // Work-groups of the histograms: 16,384 keys each, 64 at least while there are as many blocks (their adds to the same few words
+    // of memory are done one after the other: a million keys 22.4 us with 244 work-groups, 19.9 with 64; 4 million, waiting
+    // included, 56.0 with 512, 49.8 with 244).
+    const int64_t blocks = (N + SELECT_BLOCK - 1) / SELECT_BLOCK, wide = blocks / 4;
+    const int64_t hw = wide < 64 ? (blocks < 64 ? blocks : 64) : wide < 512 ? wide : 512;
     hipLaunchKernelGGL(topm_clear_kernel, dim3(TOPM_HIST_WORDS / TOPM_T), dim3(TOPM_T), 0, st, w.hist);
-    const dim3 hb((unsigned)(nblk < 512 ? nblk : 512));
-    hipLaunchKernelGGL(topm_hist_kernel<0>, hb, dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
-    hipLaunchKernelGGL(topm_hist_kernel<1>, hb, dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
-    hipLaunchKernelGGL(topm_hist_kernel<2>, hb, dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
-    hipLaunchKernelGGL(topm_count_kernel, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.hist, w.state, w.blk_gt,
-                       w.blk_eq);
-    hipLaunchKernelGGL(topm_emit_kernel, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.state, w.blk_gt, w.blk_eq,
-                       out_idx);
+    hipLaunchKernelGGL(topm_hist_kernel<0>, dim3((unsigned)hw), dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
+    hipLaunchKernelGGL(topm_hist_kernel<1>, dim3((unsigned)hw), dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
+    // Blocks of 4096 keys; four times as long where every work-group would read the counts, and with many equal scores the
+    // tables, of more than 1024 blocks before it (16 million keys of seven values, waiting included: 166 us with short
+    // blocks, 111 with long ones; 2 million distinct keys 37.3 with short ones, 42.8 with long ones).
+    constexpr int CS = SELECT_BLOCK / TOPM_T, CL = 4 * CS;
+#define SAGE_TAIL(C)                                                                                                          \
+    do {                                                                                                                      \
+        const int64_t nblk = (N + C * TOPM_T - 1) / (C * TOPM_T);                                                             \
+        if (nblk > w.nblk_cap) return hipErrorInvalidValue;                                                                   \
+        hipLaunchKernelGGL(topm_table_kernel<C>, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.hist, w.state,         \
+                           w.blk_gt, w.blk_in, w.table);                                                                      \
+        hipLaunchKernelGGL(topm_emit_kernel<C>, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.hist, w.state,          \
+                           w.blk_gt, w.blk_in, w.table, out_idx);                                                             \
+    } while (0)
+    if (blocks <= 1024) SAGE_TAIL(CS);
+    else SAGE_TAIL(CL);
+#undef SAGE_TAIL
     return hipGetLastError();
 }
 

@@ -7,12 +7,11 @@
 
 namespace {
 
-// Work space of one top-m run over at most SAGE_TOPM_STATIC_MAX_N keys: the histograms, the state, and two per-block
-// counters for every block of SELECT_BLOCK keys.
+// Work space of one top-m run over at most SAGE_TOPM_STATIC_MAX_N keys: the histograms, the state, and two counters and a table
+// for every block of SELECT_BLOCK keys.
 constexpr int64_t MAX_N = SAGE_TOPM_STATIC_MAX_N;
 constexpr int64_t MAX_BLOCKS = (MAX_N + sage::SELECT_BLOCK - 1) / sage::SELECT_BLOCK;
-constexpr size_t HIST_WORDS = sage::TOPM_HIST_WORDS, STATE_WORDS = 64;  // the state gets a 256-byte slot of its own
-constexpr size_t SCRATCH_WORDS = HIST_WORDS + STATE_WORDS + 2 * (size_t)MAX_BLOCKS;
+constexpr size_t SCRATCH_WORDS = sage::TOPM_HIST_WORDS + sage::SELECT_STATE_WORDS + (size_t)MAX_BLOCKS * sage::SELECT_BLOCK_WORDS;
 
 // One copy per GPU, at that GPU's own address; host code never uses this name as a pointer (it is a host-side stand-in
 // there): it asks the runtime for the device address once per device and keeps it.
@@ -52,14 +51,9 @@ extern "C" int sage_topm_static(const float* alpha, int64_t N, int64_t m, int64_
     uint32_t* base = nullptr;
     int rc = scratch_ptr(&base);
     if (rc != SAGE_OK) return rc;
-    sage::SelectWork w{};
-    w.hist = base;
-    w.state = base + HIST_WORDS;
-    w.blk_gt = base + HIST_WORDS + STATE_WORDS;
-    w.blk_eq = w.blk_gt + MAX_BLOCKS;
-    w.nblk_cap = MAX_BLOCKS;
-    // the first kernel of the run clears the histograms; the state and every per-block counter that is read are
-    // written earlier in the same run, so nothing of the previous call's contents is used
+    const sage::SelectWork w = sage::select_work_at(base, MAX_BLOCKS);
+    // the first kernel of the run clears the histograms; the state, every per-block counter and every table that is read
+    // are written earlier in the same run, so nothing of the previous call's contents is used
     if (sage::launch_topm(alpha, N, m, out_idx, w, (hipStream_t)hip_stream) != hipSuccess) {
         (void)hipGetLastError();
         return SAGE_ERR_HIP;

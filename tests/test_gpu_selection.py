@@ -24,6 +24,23 @@ def test_topm_at_the_edges_of_its_variants(N, ties):
         assert topm_static(ad, m, torch.empty(m, dtype=torch.int64, device="cuda")).cpu().tolist() == want
 
 
+# work-groups of the histograms: one a block, 64, a quarter of the blocks; blocks of 4096 keys, then of 16,384
+@pytest.mark.parametrize("N", [65 * 4096, 257 * 4096 + 1, 4_194_304, 4_194_305, 5_000_003])
+@pytest.mark.parametrize("ties", [False, True])
+def test_topm_at_the_edges_of_its_blocks(N, ties):
+    import torch
+
+    from paper_2510_02470_amd.binding import topm, topm_static
+
+    rng = np.random.default_rng(N)
+    a = (rng.integers(-3, 4, size=N) / 4.0 if ties else np.tanh(0.1 + 0.3 * rng.standard_normal(N))).astype(np.float32)
+    ad = torch.from_numpy(a).cuda()
+    for m in (1, N // 100, N - 1):
+        want = oracle.topm_f32(a, m)
+        assert np.array_equal(topm(ad, m).cpu().numpy(), want)
+        assert np.array_equal(topm_static(ad, m, torch.empty(m, dtype=torch.int64, device="cuda")).cpu().numpy(), want)
+
+
 # class sizes: the rank select takes up to 256 rows; a mean above 256 rows takes the wider work-group; many classes leave
 # no room for counters in LDS
 @pytest.mark.parametrize("sizes", [(255, 256, 257, 0, 1, 30), (3000, 256, 257, 1025), (5000,), (2,) * 300 + (700,),
