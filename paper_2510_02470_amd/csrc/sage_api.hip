@@ -370,8 +370,9 @@ bool kit_take(int device, SideKit& k) {
     }
     k = SideKit{};
     bool ok = hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking) == hipSuccess;
+    // (no fence towards the host: what the events order is read by this device alone)
     for (hipEvent_t* e : {&k.mark, &k.side[0], &k.side[1]})
-        ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
+        ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&k.host, KIT_WORDS * sizeof(int), hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -462,14 +463,14 @@ hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf
 // The Gram matrix of a buffer of which no block is known, with the split-arithmetic kernels: new x top, new x new and, by
 // the latter's kernel, top x top (at D = 2,049,000 the fp32 kernel took 5.4 ms for it, this takes 2.6 for bf16 and 2.9 for fp32 rows). The side stream
 // is idle here.
-int gram_whole_split(sage_ctx* c) {
+int gram_whole_split(sage_ctx* c, hipEvent_t mark = nullptr) {
     const int i = c->cur, o = i ^ 1;
     const bool one = new_one(c, i);
     RUN(K_GRAM, launch_gram(c->top, c->top, c->fill_top, c->gram_partial_new[o], c->gp_new2_split, c->d, c->st));
     RUN(K_GRAM, launch_gram(c->top, c->nw[i], c->fill_new, c->gram_partial_new[i], c->gp_new2_split, c->d, c->st, one));
     RUN(K_GRAM, launch_gram(c->top, c->nw[i], c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
     RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, c->gp_cross_split, c->gram_partial_new[i], &c->gp_new2_split, c->ew.C,
-                                     false, c->ew.known, c->d, c->st, c->gram_partial_new[o], &c->gp_new2_split));
+                                     false, c->ew.known, c->d, c->st, c->gram_partial_new[o], &c->gp_new2_split, mark));
     return SAGE_OK;
 }
 
@@ -512,7 +513,7 @@ int decompose(sage_ctx* c, const CoeffArgs& cf) {
 int side_ahead(sage_ctx* c, const RowSrc* next) {
     // The other half was last read by the rebuild before last, which precedes the mark on the context stream.
     const int LP = c->d.LP, ell = c->d.ell, o = c->cur ^ 1;
-    HIPCHK(hipEventRecord(c->ev_mark, c->st));
+    if (capturing(c->st)) HIPCHK(hipEventRecord(c->ev_mark, c->st));  // (else the Gram reduction's launch recorded it)
     HIPCHK(hipStreamWaitEvent(c->st2, c->ev_mark, 0));
     if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
     int* const hole = c->ew.period == 8 ? c->side_hole : nullptr;
@@ -527,6 +528,7 @@ int side_ahead(sage_ctx* c, const RowSrc* next) {
 int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
     const int LP = c->d.LP, ell = c->d.ell;
     const bool ahead = use_side(c) && !c->prof && next && next_rows >= ell;
+    const hipEvent_t mark = ahead && !capturing(c->st) ? c->ev_mark : nullptr;
     if (c->new_block_ready || (c->top_shrunk && c->gp_cross.tiles > 0)) {
         // The top x top block is known. The new x new block came from the side stream, or is formed here when there
         // was nothing to look ahead to (first cycle of a call); then only new x top is left.
@@ -542,15 +544,15 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
         const GramPlan& gc = split && c->gp_cross_split.tiles > 0 ? c->gp_cross_split : c->gp_cross;
         RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial, gc, c->d, c->st, new_one(c, c->cur)));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gc, c->gram_partial_new[c->cur], gn, c->ew.C, true,
-                                         c->ew.known, c->d, c->st));
+                                         c->ew.known, c->d, c->st, nullptr, nullptr, mark));
     } else if (!c->top_shrunk && split_grams(c)) {
-        if (int rc = gram_whole_split(c); rc != SAGE_OK) return rc;
+        if (int rc = gram_whole_split(c, mark); rc != SAGE_OK) return rc;
     } else {
         const bool skip = c->top_shrunk && c->gp_skip.t0 > 0;
         const GramPlan& gp = skip ? c->gp_skip : c->gp;
         if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
         RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial, gp, c->d, c->st));
-        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st));
+        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st, nullptr, nullptr, mark));
     }
     c->new_block_ready = false;
     if (ahead) {

@@ -164,10 +164,11 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
                        hipStream_t st, bool new_one = false, const int* hole = nullptr);
 // C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
-// (the Gram matrix of the rows the last shrink wrote, see EigWork::known)
+// (the Gram matrix of the rows the last shrink wrote, see EigWork::known). done: recorded when C is complete (may be null; not
+// on a stream that is captured)
 hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const float* partial_b, const GramPlan* b,
                               double* C, bool known_top, const double* known, const Dims& d, hipStream_t st,
-                              const float* partial_top = nullptr, const GramPlan* top = nullptr);
+                              const float* partial_top = nullptr, const GramPlan* top = nullptr, hipEvent_t done = nullptr);
 
 // fd_tridiag.hip, fd_dc.hip, fd_eig.hip: the eigensolve
 struct DcWork {  // work arrays of the merges above 64 rows (see fd_dc.hip)
