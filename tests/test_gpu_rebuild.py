@@ -41,3 +41,37 @@ def test_shrink_against_64_bits(ell, D, dtype, decades):
     # A Gram entry is a sum of D terms in fp32 (2^-24 sqrt(4099) = 4e-6 of its size at most, the terms being random), a rebuilt
     # value one of 512 terms good to 2^-22 (5e-6).
     assert float((B.T @ B - E.T @ E).norm()) <= 1e-5 * float((A * A).sum())
+
+
+# Gram blocks in two scaled fp16 parts: fp32 rows from 131,072 columns on, in cycles that look ahead; rows of very different and
+# of extreme norms, zero rows, sketch sizes that fill their padding and do not.
+@pytest.mark.parametrize("ell,D", [(129, 131_071), (129, 131_072), (200, 131_077), (256, 200_001)])
+@pytest.mark.parametrize("decades,factor", [(0, 1.0), (8, 1e12), (14, 1e-9)])
+def test_wide_fp32_cycles_against_64_bits(ell, D, decades, factor):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(D + ell + decades)
+    n = 5 * ell
+    G = torch.randn(n, D, generator=g, device="cuda")
+    G *= factor * 10.0 ** (-decades * torch.rand(n, 1, generator=g, device="cuda"))
+    G[2 * ell + 3] = 0.0
+    G[3 * ell + 5:3 * ell + 9] = G[3 * ell + 4]
+    G[4 * ell, :D - 1] = 0.0                             # one element
+    s = Sage(ell, D)
+    s.fd_update(G)
+    B = s.sketch().double()[:ell]
+    E = G[:ell].double()
+    for c in range(1, 5):
+        E = _shrink(torch.cat([E, G[c * ell:(c + 1) * ell].double()]), ell, torch)
+    assert bool(torch.isfinite(B).all())
+    # As above: a Gram entry is good to 2^-22 (two parts) and to the fp32 sums' rounding (a few 1e-7), a rebuilt value to 2^-22.
+    # The covariances' distance on the span of both: || B^T B - E^T E || = || J (P P^T) || with P = [B; E], J = diag(1, -1).
+    P = torch.cat([B, E])
+    K = P @ P.T
+    J = torch.ones(2 * ell, 1, dtype=torch.float64, device="cuda")
+    J[ell:] = -1.0
+    err = float(((J * K) @ (J * K)).trace().clamp(min=0).sqrt())
+    assert err <= 1e-5 * float((G.double() ** 2).sum())
+    s.close()
