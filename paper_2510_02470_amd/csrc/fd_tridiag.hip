@@ -6,13 +6,13 @@
 // update of it, 2 flop per byte touched), so it is bound by the latency of a step, not by arithmetic. The matrix
 // therefore never leaves the registers: the work-groups own columns of the (symmetric) matrix, a wave's lanes the rows
 // lane, lane + 64, ..., and the rank-2 update of a step is applied in the same pass as the next step's product.
-//   n = 64:            one work-group; the exchanges of a step go through LDS (tri_one_kernel, 0.7 us a step).
+//   n = 64:            one work-group; the exchanges of a step go through LDS (tri_one_kernel, 0.65 us a step).
 //   n = 128, 256, 512: 16, 32, 32 work-groups, one per CU of ONE XCD, which exchange two n-vectors per step through the L2
 //                      they share (tri_many_kernel, 0.77, 0.83, 1.02 us a step; every wave carries the vectors of the
 //                      step redundantly, so a step has one exchange and no other synchronisation).
-// One work-group issues the instructions of a 128-row reduction in 144 us (110 with one barrier a step and every wave carrying
-// the vectors), 16 of them take 98, so the exchange pays from there on. Where work-groups cannot be placed on one XCD (XcdMap without a period) one does it all: 128 rows by tri_one_kernel,
-// larger ones as after a wait in vain (see tri_many_kernel).
+// One work-group takes 122 us for a 128-row reduction, 16 of them take 98, so the exchange pays from there on. Where work-groups
+// cannot be placed on one XCD (XcdMap without a period) one does it all: 128 rows by tri_one_kernel, larger ones as after a
+// wait in vain (see tri_many_kernel).
 #include <mutex>
 #include <type_traits>
 
@@ -70,13 +70,16 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // ---- n = 64 J, J = 1, 2: one work-group ---------------------------------------------------------------------------
-// Waves 0..3 hold the matrix as 16 x 16 threads of R x R elements (rows rs + 16 t, columns cs + 16 u); wave 4 carries the
-// vectors, wave 5 stores the reflectors. Step k, with x = column k below row k + 1 and v', w' of step k - 1 in LDS:
-//   waves 0..3: a -= v' w'^T + w' v'^T, q = a x (summed over the 16 lanes of a row), c = column k + 1;
-//   wave 4 meanwhile: the reflector (tau, v1);                                                                  barrier
-//   wave 4: p = tau (q + v1 c), w = p - tau/2 (p.v) v, next column c - v w_{k+1} - w v1;                        barrier
+// Waves 0..3 hold the matrix as 16 x 16 threads of R x R elements (rows rs + 16 t, columns cs + 16 u), wave 4 forms the
+// reflectors, wave 5 stores them; waves 0..4 carry the vectors, each its own copy, so that a step has one barrier. Step k,
+// with x = column k below row k + 1 and w' of step k - 1:
+//   waves 0..3: a -= v' w'^T + w' v'^T, q = a x (summed over the 16 lanes of a row), c = column k + 1, their part of x A x;
+//   wave 4 meanwhile: the reflector (tau, v1) from |x|;                                                      barrier
+//   all: v A v = x A x + 2 v1 q_{k+1} + v1^2 c_{k+1}, w = tau (q + v1 c) - tau^2/2 (v A v) v, next column c - v w_{k+1} - w v1.
 // A step is a chain of latencies (sum over a wave 160 cycles, LDS round trip 70, reductions over 16 lanes 105), at J = 2
-// also 3 x 64 fp64 operations a thread while nothing is done yet: finished rows and columns are left out in quarters.
+// also 3 x 64 fp64 operations a thread while nothing is done yet: finished rows and columns are left out at compile time, 16
+// steps at a time. n = 64: 43.5 us with the vectors on wave 4 alone and two barriers, 41.0 now; n = 128: 155
+// and 122.
 struct __attribute__((aligned(16))) Pair { double a, b; };
 
 template <int J>
@@ -84,200 +87,224 @@ __global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restric
                                                          double* __restrict__ dT, double* __restrict__ eT,
                                                          double* __restrict__ tauT, double* __restrict__ V,
                                                          double* __restrict__ stat) {
-    constexpr int N = 64 * J, R = N / 16;
-    __shared__ Pair vw[N], wx[N], qc[N];  // {v', w'}, {w', x} and {q, c}
-    __shared__ double vl[2][N];    // v, by step parity (for wave 5)
-    __shared__ double v1s;         // v1' of step k - 1: v' is the x before it with v1' in place k
-    __shared__ double dl[N], el[N], tl[N];
+    constexpr int W = 4, N = 64 * J, RG = 4 * W, RT = N / RG, CT = N / 16;
+    __shared__ Pair qc[2][N];       // {q, c} by step parity
+    __shared__ Pair wx[W + 1][N];   // {w', x}: every wave's own copy
+    __shared__ double pp[2][W];     // partial sums of x A x
+    __shared__ Pair prm[2];         // {tau, v1}
+    __shared__ double vl[2][N];     // the reflector, by step parity
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     const double md = wave_max_diag(C, NP, lane);
     const int ex = tri_exponent(md);
     const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
-    if (tid == 0) stat[0] = (double)ex;
     auto element = [&](int r, int c) __attribute__((always_inline)) {
         return (r < n && c < n) ? C[(int64_t)active_index(c, m0, LP) * NP + active_index(r, m0, LP)] * sc0 : 0.0;
     };
+    if (wave == W) __builtin_amdgcn_s_setprio(3);  // its chain is the longer one: 43.9 us without at n = 64
+    double x[J];  // column k below row k + 1, rows lane + 64 j
+    Pair* const own = wx[wave <= W ? wave : W];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int r = lane + 64 * j;
+        const double e = element(r, 0);
+        x[j] = r > 1 ? e : 0.0;
+        if (wave <= W) own[r] = Pair{0.0, x[j]};
+        if (wave == 0) qc[0][r] = qc[1][r] = Pair{0.0, 0.0};
+    }
 
-    if (wave < 4) {
-        const int rs = wave * 4 + (lane >> 4), cs = lane & 15;
-        double a[R][R], vc[R];  // vc: the x of the step before at the columns
+    // what all waves do after the barrier of step k: w of the step, the next x
+    struct Scal { double v1, w1, tau, al; Pair e1; };
+    auto vectors = [&](int k) __attribute__((always_inline)) {
+        const int par = k & 1;
+        const Pair tv = prm[par], e1 = qc[par][k + 1];
+        Pair e[J];
 #pragma unroll
-        for (int t = 0; t < R; ++t) {
+        for (int j = 0; j < J; ++j) e[j] = qc[par][lane + 64 * j];
+        double s = pp[par][0];
 #pragma unroll
-            for (int u = 0; u < R; ++u) a[t][u] = element(rs + 16 * t, cs + 16 * u);
-            vc[t] = 0.0;
+        for (int i = 1; i < W; ++i) s += pp[par][i];
+        const double tau = tv.a, v1 = tv.b;
+        const double g1 = __builtin_fma(v1, e1.b, e1.a);                      // q + v1 c at k + 1
+        s = __builtin_fma(v1, e1.a + g1, s);                                  // v A v = x A x + 2 v1 q + v1^2 c
+        const double al = -0.5 * tau * (tau * s);
+        const double w1 = __builtin_fma(al, v1, tau * g1);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int r = lane + 64 * j;
+            const double v = r == k + 1 ? v1 : x[j];
+            double w = __builtin_fma(al, v, tau * __builtin_fma(v1, e[j].b, e[j].a));
+            w = r > k ? w : 0.0;
+            const double xn = __builtin_fma(-v, w1, __builtin_fma(-w, v1, e[j].b));
+            x[j] = r > k + 2 ? xn : 0.0;
+            own[r] = Pair{w, x[j]};
         }
+        return Scal{v1, w1, tau, al, e1};
+    };
+
+    if (wave < W) {
+        const int rs = wave * 4 + (lane >> 4), cs = lane & 15;
+        double a[RT][CT], vr[RT], vc[CT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+#pragma unroll
+            for (int u = 0; u < CT; ++u) a[t][u] = element(rs + RG * t, cs + 16 * u);
+            vr[t] = 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < CT; ++u) vc[u] = 0.0;
         const bool odd = lane & 1, hi = lane & 2;
         lds_barrier();
-        for (int k = 0; k < n - 1; ++k) {
-            auto pass = [&](auto t0c) __attribute__((always_inline)) {
-                constexpr int T0 = decltype(t0c)::value;  // rows and columns below 16 T0 are done with
-                double q[R], wc[R], xc[R];
-                const double v1 = v1s;
+        // steps whose column k + 1 is 16 Q ..: rows below RG T0 and columns below 16 Q are done with
+        auto steps = [&](auto qcst) __attribute__((always_inline)) {
+            constexpr int Q = decltype(qcst)::value, T0 = 16 * Q / RG;
+            int k = 16 * Q - 1;
+            if (k < 0) k = 0;
+            const int end = 16 * Q + 15 < n - 1 ? 16 * Q + 15 : n - 1;
+            for (; k < end; ++k) {
+                const int par = k & 1;
+                double q[RT], xr[RT], xc[CT], wc[CT], p = 0.0;
 #pragma unroll
-                for (int u = T0; u < R; ++u) {
-                    const Pair e = wx[cs + 16 * u];
+                for (int u = Q; u < CT; ++u) {
+                    const Pair e = own[cs + 16 * u];
                     wc[u] = e.a;
                     xc[u] = e.b;
-                    vc[u] = cs + 16 * u == k ? v1 : vc[u];
                 }
 #pragma unroll
-                for (int t = T0; t < R; ++t) {
-                    const Pair e = vw[rs + 16 * t];
-                    double q0 = 0.0;
+                for (int t = T0; t < RT; ++t) {
+                    const Pair e = own[rs + RG * t];
+                    xr[t] = e.b;
 #pragma unroll
-                    for (int u = T0; u < R; ++u) a[t][u] = __builtin_fma(-e.b, vc[u], a[t][u]);
+                    for (int u = Q; u < CT; ++u) a[t][u] = __builtin_fma(-e.a, vc[u], a[t][u]);
 #pragma unroll
-                    for (int u = T0; u < R; ++u) a[t][u] = __builtin_fma(-e.a, wc[u], a[t][u]);
+                    for (int u = Q; u < CT; ++u) a[t][u] = __builtin_fma(-vr[t], wc[u], a[t][u]);
+                    double q0 = a[t][Q] * xc[Q];
 #pragma unroll
-                    for (int u = T0; u < R; ++u) q0 = __builtin_fma(a[t][u], xc[u], q0);
+                    for (int u = Q + 1; u < CT; ++u) q0 = __builtin_fma(a[t][u], xc[u], q0);
                     q[t] = q0;
+                    p = __builtin_fma(q0, xr[t], p);
                 }
-#pragma unroll
-                for (int u = T0; u < R; ++u) vc[u] = xc[u];
                 if (cs == ((k + 1) & 15)) {
 #pragma unroll
-                    for (int u = T0; u < R; ++u)
-                        if ((k + 1) >> 4 == u) {
-#pragma unroll
-                            for (int t = T0; t < R; ++t) {
-                                double c = a[t][u];
-                                asm volatile("" : "+v"(c));  // keeps the cases apart: merged, they index a[] by u at
-                                qc[rs + 16 * t].b = c;       // run time, which moves the matrix to scratch memory
-                            }
-                        }
+                    for (int t = T0; t < RT; ++t) qc[par][rs + RG * t].b = a[t][Q];
                 }
-                // over the 16 lanes of a row: four (two) rows at a time, told apart by the low bits of the lane, then the
-                // ring of what is left
-                constexpr int Q4 = (R - T0) / 4 * 4;
+                // q over the 16 lanes of a row (four rows at a time, told apart by the low bits of the lane), x A x over the wave
+                p = lane_sum<64>(p);
 #pragma unroll
-                for (int g = T0; g < T0 + Q4; g += 4) {
-                    double t0 = odd ? q[g + 1] : q[g], o0 = odd ? q[g] : q[g + 1];
-                    double t1 = odd ? q[g + 3] : q[g + 2], o1 = odd ? q[g + 2] : q[g + 3];
-                    t0 += dpp_move<DPP_XOR1>(o0);
-                    t1 += dpp_move<DPP_XOR1>(o1);
-                    double t = hi ? t1 : t0, o = hi ? t0 : t1;
-                    t += dpp_move<DPP_XOR2>(o);
-                    t += dpp_move<0x124>(t);  // row_ror 4
-                    t += dpp_move<0x128>(t);  // row_ror 8
-                    if (cs < 4) qc[rs + 16 * (g + cs)].a = t;
+                for (int g = T0; g < RT; g += 4) {
+                    const int left = RT - g;  // (compile time once unrolled)
+                    if (left >= 3) {
+                        const double q3 = left >= 4 ? q[g + 3 < RT ? g + 3 : RT - 1] : 0.0;
+                        double t0 = odd ? q[g + 1] : q[g], o0 = odd ? q[g] : q[g + 1];
+                        double t1 = odd ? q3 : q[g + 2 < RT ? g + 2 : RT - 1], o1 = odd ? q[g + 2 < RT ? g + 2 : RT - 1] : q3;
+                        t0 += dpp_move<DPP_XOR1>(o0);
+                        t1 += dpp_move<DPP_XOR1>(o1);
+                        double t = hi ? t1 : t0, o = hi ? t0 : t1;
+                        t += dpp_move<DPP_XOR2>(o);
+                        t += dpp_move<0x124>(t);  // row_ror 4
+                        t += dpp_move<0x128>(t);  // row_ror 8
+                        if (cs < (left >= 4 ? 4 : 3)) qc[par][rs + RG * (g + cs)].a = t;
+                    } else if (left == 2) {
+                        double t = odd ? q[g + 1 < RT ? g + 1 : RT - 1] : q[g], o = odd ? q[g] : q[g + 1 < RT ? g + 1 : RT - 1];
+                        t += dpp_move<DPP_XOR1>(o);
+                        t += dpp_move<DPP_XOR2>(t);
+                        t += dpp_move<0x124>(t);
+                        t += dpp_move<0x128>(t);
+                        if (cs < 2) qc[par][rs + RG * (g + cs)].a = t;
+                    } else {
+                        const double t = lane_sum<16>(q[g]);
+                        if (cs == 0) qc[par][rs + RG * g].a = t;
+                    }
                 }
+                if (lane == 0) pp[par][wave] = p;
 #pragma unroll
-                for (int g = T0 + Q4; g < R; g += 2) {
-                    double t = odd ? q[g + 1] : q[g], o = odd ? q[g] : q[g + 1];
-                    t += dpp_move<DPP_XOR1>(o);
-                    t += dpp_move<DPP_XOR2>(t);
-                    t += dpp_move<0x124>(t);
-                    t += dpp_move<0x128>(t);
-                    if (cs < 2) qc[rs + 16 * (g + cs)].a = t;
-                }
-            };
-            const int done = k / (N / 4);  // quarters of the matrix that are finished (rows and columns <= k - 1 are)
-            if constexpr (R == 8) {
-                if (done == 0) pass(std::integral_constant<int, 0>{});
-                else if (done == 1) pass(std::integral_constant<int, 2>{});
-                else if (done == 2) pass(std::integral_constant<int, 4>{});
-                else pass(std::integral_constant<int, 6>{});
-            } else {
-                if (done < 2) pass(std::integral_constant<int, 0>{});
-                else pass(std::integral_constant<int, 2>{});
+                for (int u = Q; u < CT; ++u) vc[u] = xc[u];
+#pragma unroll
+                for (int t = T0; t < RT; ++t) vr[t] = xr[t];
+                lds_barrier();
+                const Scal s = vectors(k);
+                vc[Q] = cs + 16 * Q == k + 1 ? s.v1 : vc[Q];
+#pragma unroll
+                for (int t = T0; t < RT; ++t)
+                    if (RG * t < 16 * Q + 16 && RG * t + RG > 16 * Q) vr[t] = rs + RG * t == k + 1 ? s.v1 : vr[t];
             }
-            lds_barrier();
-            lds_barrier();
+        };
+        steps(std::integral_constant<int, 0>{});
+        steps(std::integral_constant<int, 1>{});
+        steps(std::integral_constant<int, 2>{});
+        steps(std::integral_constant<int, 3>{});
+        if constexpr (J == 2) {
+            steps(std::integral_constant<int, 4>{});
+            steps(std::integral_constant<int, 5>{});
+            steps(std::integral_constant<int, 6>{});
+            steps(std::integral_constant<int, 7>{});
         }
         return;
     }
 
-    if (wave == 5) {
+    if (wave > W) {  // stores the reflectors
         lds_barrier();
         for (int k = 0; k < n - 1; ++k) {
             lds_barrier();
 #pragma unroll
             for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = vl[k & 1][lane + 64 * j];
-            lds_barrier();
         }
-        // the padding: decoupled, below every eigenvalue of a Gram matrix
-        for (int i = lane; i < N; i += 64) {
-            dT[i] = i < n - 1 ? dl[i] : -1.0;
-            eT[i] = i < n - 1 ? el[i] : 0.0;
-            tauT[i] = i < n - 1 ? tl[i] : 0.0;
-        }
-        if (lane == 0) dT[n - 1] = dl[n - 1];
         for (int k = n - 1; k % WY != 0; ++k)  // the rows of V that complete the last block of reflectors
 #pragma unroll
             for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = 0.0;
         return;
     }
-
-    // ---- wave 4
-    double x[J], vf[J];
+    // ---- the wave of the reflectors
+    double xk = element(0, 0), xk1 = element(1, 0);
+    double d[J], el[J], tl[J];  // of T, at lanes
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         const int r = lane + 64 * j;
-        x[j] = element(r, 0);
-        qc[r] = Pair{0.0, 0.0};
-        vw[r] = Pair{0.0, 0.0};
-        wx[r] = Pair{0.0, r > 1 ? x[j] : 0.0};
+        d[j] = r < n ? (n == 1 ? xk : 0.0) : -1.0;  // the padding: decoupled, below every eigenvalue of a Gram matrix
+        el[j] = tl[j] = 0.0;
     }
-    double xk = element(0, 0), xk1 = element(1, 0);
-    if (lane == 0) {
-        v1s = 0.0;
-        if (n == 1) dl[0] = xk;
-    }
-    lds_barrier();
-    for (int k = 0; k < n - 1; ++k) {
+    auto reflect = [&](int k, double& beta, double& tau, double& v1) __attribute__((always_inline)) {
         double r2 = 0.0;
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            vf[j] = lane + 64 * j > k + 1 ? x[j] : 0.0;
-            r2 = __builtin_fma(vf[j], vf[j], r2);
-        }
+        for (int j = 0; j < J; ++j) r2 = __builtin_fma(x[j], x[j], r2);
         r2 = lane_sum<64>(r2);
-        double beta, tau, v1;
         householder(xk1, r2, beta, tau, v1);
+        if (lane == 0) prm[k & 1] = Pair{tau, v1};
+    };
+    double beta, tau, v1;
+    reflect(0, beta, tau, v1);
+    lds_barrier();
+    for (int k = 0; k < n - 1; ++k) {
+        // (before the barrier of step k: v for the wave that stores it)
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = lane + 64 * j;
-            vf[j] = r == k + 1 ? v1 : vf[j];
-            vl[k & 1][r] = vf[j];
-        }
-        if (lane == 0) {
-            dl[k] = xk;
-            el[k] = beta;
-            tl[k] = tau;
-        }
+        for (int j = 0; j < J; ++j) vl[k & 1][lane + 64 * j] = lane + 64 * j == k + 1 ? v1 : x[j];
+        const int par = k & 1, i2 = k + 2 < N ? k + 2 : N - 1;
         lds_barrier();
-        double p[J], c[J], dot = 0.0;
+        const double v2 = own[i2].b;
+        const Pair e2 = qc[par][i2];
+        const Scal s = vectors(k);
+        const double w2 = __builtin_fma(s.al, v2, s.tau * __builtin_fma(s.v1, e2.b, e2.a));
+        xk1 = __builtin_fma(-v2, s.w1, __builtin_fma(-w2, s.v1, e2.b));
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            const int r = lane + 64 * j;
-            const Pair e = qc[r];
-            c[j] = e.b;
-            p[j] = r > k ? tau * __builtin_fma(v1, e.b, e.a) : 0.0;
-            dot = __builtin_fma(p[j], vf[j], dot);
+            const bool at = lane + 64 * j == k;
+            d[j] = at ? xk : d[j];
+            el[j] = at ? beta : el[j];
+            tl[j] = at ? tau : tl[j];
         }
-        const Pair e1 = qc[k + 1];
-        dot = lane_sum<64>(dot);
-        const double al = -0.5 * tau * dot;
-        const double w1 = __builtin_fma(al, v1, tau * __builtin_fma(v1, e1.b, e1.a));
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = lane + 64 * j;
-            const double w = __builtin_fma(al, vf[j], p[j]);
-            x[j] = __builtin_fma(-vf[j], w1, __builtin_fma(-w, v1, c[j]));
-            vw[r] = Pair{vf[j], w};
-            wx[r] = Pair{w, r > k + 2 ? x[j] : 0.0};
-        }
-        xk = __builtin_fma(-2.0 * v1, w1, e1.b);
-        if (lane == 0) {
-            v1s = v1;
-            if (k == n - 2) dl[n - 1] = xk;
-        }
-        lds_barrier();
-        xk1 = read_lane((J == 1 || k + 2 < 64) ? x[0] : x[J - 1], (k + 2) & 63);
+        xk = __builtin_fma(-2.0 * s.v1, s.w1, s.e1.b);
+        reflect(k + 1, beta, tau, v1);
     }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int r = lane + 64 * j;
+        if (r == n - 1) d[j] = xk;
+        dT[r] = d[j];
+        eT[r] = el[j];
+        tauT[r] = tl[j];
+    }
+    if (lane == 0) stat[0] = (double)ex;
 }
 
 // ---- n = 64 J, J = 2, 4, 8: 16, 32, 32 work-groups on one XCD -----------------------------------------------------

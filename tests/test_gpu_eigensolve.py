@@ -268,3 +268,9 @@ def test_captured_update_replays(ell, dtype):
 def test_basis_where_the_reduction_ends_near_a_multiple_of_64_rows(ell, rows):
     """The reduction's loop is written out per 64 steps: it ends just before, at and just after such a boundary."""
     test_basis_of_a_buffer_with_few_rows(ell, rows)
+
+
+@pytest.mark.parametrize("rows", [1, 2, 3, 15, 16, 17, 18, 31, 32, 33, 34, 47, 48, 49, 63])
+def test_basis_where_one_work_group_reduces(rows):
+    """64 rows: the loop is written out per 16 steps."""
+    test_basis_of_a_buffer_with_few_rows(32, rows)
