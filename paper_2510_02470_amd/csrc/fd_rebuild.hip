@@ -169,10 +169,11 @@ hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const fl
 //   taken out again when the result is stored. What falls below fp16's range is at most 2^-39 of the row's norm.
 // PARTS = 3, a basis: x = hi + mid + lo (three bf16 parts, 24 significant bits) and the six products whose weight is at least
 //   2^-16 of the leading one (hi*hi, hi*mid, mid*hi, hi*lo, lo*hi, mid*mid; the others are below 2^-24). A shrink done this
-//   way took 2.33 ms at D = 2,049,000 (256 fp32 and 256 bf16 rows; 1.59 in two parts) and 1.43 at 1,048,576 (512 fp32 rows).
+//   way took 2.33 ms at D = 2,049,000 (256 fp32 and 256 bf16 rows; 1.54 in two parts) and 1.43 at 1,048,576 (512 fp32 rows; 0.88).
 //   Against 64 bits over a stream's shrinks the covariance of a sketch made in two parts is as good (14 streams, sizes 100
 //   to 256: 1.56e-7 of ||A||_F^2 where three parts leave 1.67e-7) and so are its rows' products (1.42e-8, 1.50e-8); a single basis
 //   is less orthonormal in two (1.66e-7 a vector, 1.52e-7), and is made once, so it keeps the three.
+// W: waves of a work-group, see launch_rebuild_split.
 //
 // Same decomposition as rebuild_kernel: a wave owns 32 columns for the whole product, its column operand comes from
 // global memory (8 rows of its k-half per stage of 16 buffer rows; k-slot (h, s) is buffer row 16*stage + 2s + h,
@@ -189,23 +190,23 @@ __device__ __forceinline__ f32x16 mfma_part(u32x4 a, u32x4 b, f32x16 acc) {
     if constexpr (PARTS == 2) return mfma_f16(a, b, acc);
     else return mfma_bf16(a, b, acc);
 }
-template <int MT, int NPT, int PARTS>
-__global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top, const float* __restrict__ nw, int nfill,
+template <int MT, int NPT, int PARTS, int W>
+__global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(const float* top, const float* __restrict__ nw, int nfill,
                                                                const u32x4* __restrict__ Mc,
                                                                const float* __restrict__ scale,
                                                                const float* __restrict__ unscale, float* out, int NP,
                                                                int out_NP, int64_t Dp) {
     constexpr int MP = MT * 32;
     constexpr int STAGE16 = PARTS * 2 * MP;   // 16-byte pieces of coefficients per stage
-    constexpr int ML = STAGE16 / 256;     // direct-to-LDS loads per thread and stage
-    static_assert(STAGE16 % 256 == 0, "a stage must tile the work-group");
+    constexpr int ML = STAGE16 / (64 * W);  // direct-to-LDS loads per thread and stage
+    static_assert(STAGE16 % (64 * W) == 0, "a stage must tile the work-group");
     extern __shared__ u32x4 Ms[];         // 3 * STAGE16
     __shared__ f32x4 sc[128];             // the scales, four buffer rows each
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, h = lane >> 5;
-    const int64_t d = ((int64_t)blockIdx.x * 4 + wave) * 32 + c;  // this lane's column
+    const int64_t d = ((int64_t)blockIdx.x * W + wave) * 32 + c;  // this lane's column
     const bool live = d < Dp;  // Dp is a multiple of 16: the last 32-column group may overhang by 16
     const int64_t dc = live ? d : Dp - 1;
     const int LP = NP >> 1;
@@ -237,8 +238,8 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
         const u32x4* src = Mc + (int64_t)sg * STAGE16 + tid;
 #pragma unroll
         for (int q = 0; q < ML; ++q)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + q * 256),
-                                             (__attribute__((address_space(3))) void*)(Ms + buf * STAGE16 + q * 256 + wave * 64),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + q * 64 * W),
+                                             (__attribute__((address_space(3))) void*)(Ms + buf * STAGE16 + q * 64 * W + wave * 64),
                                              16, 0, 0);
     };
 
@@ -415,25 +416,32 @@ hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, co
                                 const float* unscale, float* out, int out_NP, int MP, const Dims& d, hipStream_t st,
                                 bool new_one) {
     if (nfill == 0) new_one = false;  // (no stages of the new half)
-    auto launch = [&](auto kernel) {
+    auto launch = [&](auto kernel, int W) {
         const size_t lds = (size_t)3 * parts * 2 * MP * 16;
         if (hipError_t e = ensure_dynamic_lds((const void*)kernel, (int)lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((d.Dp + 127) / 128)), dim3(256), lds, st, top, nw, nfill,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((d.Dp + 32 * W - 1) / (32 * W))), dim3(64 * W), lds, st, top, nw, nfill,
                            (const u32x4*)Msplit, scale, unscale, out, d.NP, out_NP, d.Dp);
         return hipGetLastError();
     };
     if (MP == 256 && parts == 2) {
-        if (new_one && d.NP == 512) return launch(rebuild_split_kernel<8, 512, 2>);
-        return launch(rebuild_split_kernel<8, 0, 2>);
+        // Eight waves to a work-group where that leaves two for each of 256 CUs: the two work-groups of four that share a CU both
+        // load all coefficients, at nearly the same time, and the vector cache makes one wait for the other's lines. 256 fp32
+        // and 256 bf16 rows of 2,049,000 columns: 1.61 ms with four, 1.54 with eight; 512 fp32 rows of 1,048,576: 0.89, 0.88.
+        if (d.D >= 131072) {
+            if (new_one && d.NP == 512) return launch(rebuild_split_kernel<8, 512, 2, 8>, 8);
+            return launch(rebuild_split_kernel<8, 0, 2, 8>, 8);
+        }
+        if (new_one && d.NP == 512) return launch(rebuild_split_kernel<8, 512, 2, 4>, 4);
+        return launch(rebuild_split_kernel<8, 0, 2, 4>, 4);
     }
     if (MP == 128 && parts == 2 && d.NP == 256) {  // (the shrink of 128 rows)
-        if (new_one) return launch(rebuild_split_kernel<4, 256, 2>);
-        return launch(rebuild_split_kernel<4, 0, 2>);
+        if (new_one) return launch(rebuild_split_kernel<4, 256, 2, 4>, 4);
+        return launch(rebuild_split_kernel<4, 0, 2, 4>, 4);
     }
     if (MP == 128 && parts == 3) {
-        if (new_one && d.NP == 512) return launch(rebuild_split_kernel<4, 512, 3>);
-        if (new_one && d.NP == 256) return launch(rebuild_split_kernel<4, 256, 3>);
-        return launch(rebuild_split_kernel<4, 0, 3>);
+        if (new_one && d.NP == 512) return launch(rebuild_split_kernel<4, 512, 3, 4>, 4);
+        if (new_one && d.NP == 256) return launch(rebuild_split_kernel<4, 256, 3, 4>, 4);
+        return launch(rebuild_split_kernel<4, 0, 3, 4>, 4);
     }
     return hipErrorInvalidValue;
 }

@@ -43,11 +43,13 @@ def test_shrink_against_64_bits(ell, D, dtype, decades):
     assert float((B.T @ B - E.T @ E).norm()) <= 1e-5 * float((A * A).sum())
 
 
-# Gram blocks in two scaled fp16 parts: fp32 rows from 131,072 columns on, in cycles that look ahead; rows of very different and
-# of extreme norms, zero rows, sketch sizes that fill their padding and do not.
-@pytest.mark.parametrize("ell,D", [(129, 131_071), (129, 131_072), (200, 131_077), (256, 200_001)])
+# From 131,072 columns on: Gram blocks in two scaled fp16 parts (fp32 rows, in cycles that look ahead), and the rebuild by
+# work-groups of eight waves; rows of very different and of extreme norms, zero rows, sketch sizes that fill their padding and
+# do not, column counts that end inside a wave's 32.
+@pytest.mark.parametrize("ell,D,dtype", [(129, 131_071, "f32"), (129, 131_072, "f32"), (200, 131_077, "f32"), (256, 200_001, "f32"),
+                                         (129, 131_072, "bf16"), (256, 131_077, "bf16")])
 @pytest.mark.parametrize("decades,factor", [(0, 1.0), (8, 1e12), (14, 1e-9)])
-def test_wide_fp32_cycles_against_64_bits(ell, D, decades, factor):
+def test_wide_cycles_against_64_bits(ell, D, dtype, decades, factor):
     import torch
 
     from paper_2510_02470_amd.binding import Sage
@@ -59,7 +61,8 @@ def test_wide_fp32_cycles_against_64_bits(ell, D, decades, factor):
     G[2 * ell + 3] = 0.0
     G[3 * ell + 5:3 * ell + 9] = G[3 * ell + 4]
     G[4 * ell, :D - 1] = 0.0                             # one element
-    s = Sage(ell, D)
+    G = G.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    s = Sage(ell, D, dtype=dtype)
     s.fd_update(G)
     B = s.sketch().double()[:ell]
     E = G[:ell].double()
