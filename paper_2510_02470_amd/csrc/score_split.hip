@@ -154,14 +154,14 @@ __device__ __forceinline__ TurnAt turn_at(int piece0, int lane) {
     at.r = (unsigned)(piece0 + n * 8 + ((sizeof(T) == 2 ? h : 2 * h) ^ ((n >> 1) & 7))) * 16;
     return at;
 }
-template <typename T>
-__device__ __forceinline__ void turn_rows(u32x4* lds, TurnAt at, const RowRaw (&raw)[2], RowOp<T> (&a)[2]) {
+template <int TILES, int LX, typename T>
+__device__ __forceinline__ void turn_rows(u32x4* lds, TurnAt at, const RowRaw (&raw)[TILES], RowOp<T> (&a)[TILES]) {
     char* const m = reinterpret_cast<char*>(lds);
     asm volatile("" : "+v"(at.r));  // (the loads' addresses are formed here, not kept)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < TILES; ++t) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) *reinterpret_cast<u32x4*>(m + (x & 1 ? at.w1 : at.w0) + x * 1024) = raw[t].v[x];
+        for (int x = 0; x < LX; ++x) *reinterpret_cast<u32x4*>(m + (x & 1 ? at.w1 : at.w0) + x * 1024) = raw[t].v[x];
         asm volatile("" ::: "memory");  // (a wave's LDS accesses keep their order)
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
@@ -171,12 +171,13 @@ __device__ __forceinline__ void turn_rows(u32x4* lds, TurnAt at, const RowRaw (&
         asm volatile("" ::: "memory");
     }
 }
-template <int NT, typename T>  // NT = KP / 32
+template <int NT, typename T, int NL>  // NT = KP / 32; NL: see loads_of
 __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restrict__ G, int64_t R,
                                                                const u32x4* __restrict__ img,
                                                                float* __restrict__ partial, int row_tiles, int64_t D,
                                                                int64_t chunks_total, int64_t chunks_per_split) {
     constexpr int KP = NT * 32;
+    constexpr int TILES = NL > 4 ? 2 : 1, LX = NL > 4 ? 4 : NL;  // row tiles of a wave, row loads of a tile and window
     constexpr int KC = 128 / (int)sizeof(T);
     constexpr int PPR = KC / 8;        // pieces (8 columns) per window
     constexpr int PB = 8 * (int)sizeof(T);  // bytes of a piece in a row: 16 or 32
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
     const unsigned lofs = 128u + 16u * (unsigned)(lane & 7) - (unsigned)(PB * phi);
     auto load_rows = [&](RowRaw& a, int t, int64_t m) __attribute__((always_inline)) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < LX; ++x) {
             unsigned r = lrow + (unsigned)((t * 32 + 8 * x) * 8) * (unsigned)S;
             r = r > last_row ? last_row : r;
             const unsigned lo = r + 128u, hi = lo + (unsigned)S - 16u;
@@ -223,9 +224,9 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
         }
     };
     const TurnAt turn = turn_at<T>(4 * IMG + wave * 256, lane);
-    f32x16 acc[2][NT];
+    f32x16 acc[TILES][NT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < TILES; ++t)
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
@@ -256,10 +257,10 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
     // step (left alone it hoists a whole window of LDS reads and spills). The ring has four slots, image c in slot
     // c mod 4: m-1 and m are read, m+1 has landed or is landing, m+2 is requested now. raw: the rows of this window as they
     // were loaded; it receives those of window m+2.
-    auto visit = [&](RowRaw (&raw)[2], int64_t m) __attribute__((always_inline)) {
+    auto visit = [&](RowRaw (&raw)[TILES], int64_t m) __attribute__((always_inline)) {
         const int sp = (int)((m - 1) & 3), sc = (int)(m & 3);
-        RowOp<T> a[2];
-        turn_rows<T>(lds, turn, raw, a);
+        RowOp<T> a[TILES];
+        turn_rows<TILES, LX, T>(lds, turn, raw, a);
         stage(m + 2, (int)((m + 2) & 3));
         // The row loads of window m+2 go out in two bursts, row tile 0 a quarter through the window, when the registers of
         // the first operands are free again (the loads of this window's rows and accumulators fill the file otherwise: spills,
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
         if (m == c0 || m == c1) {
             const bool first = m == c0, last = m == c1;
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < TILES; ++t)
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const int q = 2 * (sizeof(T) == 2 ? x : (x >> 1)) + h;
@@ -287,18 +288,18 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
         u32x4 b[2];
         int at = operand_at(0);
         b[0] = lds[at];
-        u32x4 ahi[2], alo[2];
+        u32x4 ahi[TILES], alo[TILES];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             const int j = s / (2 * NT), ct = s % (2 * NT);
             if (ct == 0) {
                 if constexpr (sizeof(T) == 2) {
-                    ahi[0] = a[0].v[j];
-                    ahi[1] = a[1].v[j];
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) ahi[t] = a[t].v[j];
                 } else {
-                    split8(a[0].v[2 * j], a[0].v[2 * j + 1], ahi[0], alo[0]);
-                    split8(a[1].v[2 * j], a[1].v[2 * j + 1], ahi[1], alo[1]);
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) split8(a[t].v[2 * j], a[t].v[2 * j + 1], ahi[t], alo[t]);
                 }
             }
             if (s + 1 < STEPS) {
@@ -307,25 +308,25 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
                 b[(s + 1) % 2] = lds[at + ct2 * 32 * PPR];
             }
             if (s == STEPS / 4) load_rows(raw[0], 0, m2);
-            if (s == STEPS / 2) load_rows(raw[1], 1, m2);
+            if (s == STEPS / 2 && TILES == 2) load_rows(raw[TILES - 1], 1, m2);
             const u32x4 bb = b[s % 2];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) acc[t][ct % NT] = mfma_bf16(ahi[t], bb, acc[t][ct % NT]);
+            for (int t = 0; t < TILES; ++t) acc[t][ct % NT] = mfma_bf16(ahi[t], bb, acc[t][ct % NT]);
             if constexpr (sizeof(T) == 4) {
                 if (ct < NT) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) acc[t][ct] = mfma_bf16(alo[t], bb, acc[t][ct]);
+                    for (int t = 0; t < TILES; ++t) acc[t][ct] = mfma_bf16(alo[t], bb, acc[t][ct]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        // This window requested VL image loads (image m+2) and 8 row loads (window m+2): once at most 8 + VL loads are
+        // This window requested VL image loads (image m+2) and NL row loads (window m+2): once at most NL + VL loads are
         // outstanding, image m+1 and the rows of window m+1 (and every older load) have landed; both were requested a
         // whole window earlier. A bare barrier: __syncthreads() carries a release fence, which on this target drains
         // every outstanding load and would throw the prefetch distance away. The LDS reads of this window have all
         // been consumed by matrix-core instructions above.
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (8 + VL));  // vmcnt(8 + VL); expcnt, lgkmcnt not waited for
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (NL + VL));  // vmcnt(NL + VL); expcnt, lgkmcnt not waited for
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
     // some memory channels idle (5.1 TB/s for the row stream alone against 6.2 TB/s with rotated starts). The two row
     // tiles of a split keep the same start, so that they still share the basis images through L2. A run of
     // consecutive windows needs the ring primed with the images around its first window, so the walk is two runs.
-    RowRaw a0[2], a1[2];
+    RowRaw a0[TILES], a1[TILES];
     if (nv > 0) {
         const int64_t rot = nv >= 8 ? (int64_t)(((unsigned)split * 37u) % (unsigned)(nv - 4)) + 2 : 0;  // 2 .. nv - 3
         int64_t ms = c0 + rot, me = c0 + nv;
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
             stage(ms, (int)(ms & 3));
             stage(ms + 1, (int)((ms + 1) & 3));
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < TILES; ++t) {
                 load_rows(a0[t], t, ms);
                 load_rows(a1[t], t, ms + 1 > c1 ? c1 : ms + 1);
             }
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
 
     float* out = partial + (int64_t)split * R * KP;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < TILES; ++t)
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
@@ -404,12 +405,13 @@ struct AnyShape {
     static_assert(LDS <= 160 * 1024, "of one CU");
 };
 
-template <int NT, typename T>
+template <int NT, typename T, int NL>
 __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict__ G, int64_t R,
                                                              const u32x4* __restrict__ img, float* __restrict__ partial,
                                                              int row_tiles, int64_t D, int64_t chunks_total,
                                                              int64_t chunks_per_split) {
     constexpr int KP = NT * 32;
+    constexpr int TILES = NL > 4 ? 2 : 1, LX = NL > 4 ? 4 : NL;
     constexpr int KC = 128 / (int)sizeof(T);
     constexpr int PPR = KC / 8;
     constexpr int IMG = AnyShape<NT, T>::IMG, SLOTS = AnyShape<NT, T>::SLOTS;
@@ -435,19 +437,19 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     const char* gbase = reinterpret_cast<const char*>(G) + row0 * S;
     // rows >= R repeat row R - 1; their results are not written
     const int64_t last = R - 1 - row0 < 511 ? R - 1 - row0 : 511;
-    const unsigned lrow = (unsigned)((wave * 64 + (lane >> 3)) * S), last_row = (unsigned)(last * S);
+    const unsigned lrow = (unsigned)((wave + 8 * (lane >> 3)) * S), last_row = (unsigned)(last * S);
     auto load_rows = [&](RowRaw& a, int t, int64_t m) __attribute__((always_inline)) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            unsigned r = lrow + (unsigned)(t * 32 + 8 * x) * (unsigned)S;
+        for (int x = 0; x < LX; ++x) {
+            unsigned r = lrow + (unsigned)((t * 32 + 8 * x) * 8) * (unsigned)S;
             r = r > last_row ? last_row : r;
             a.v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (r + 16u * (unsigned)(lane & 7) + (unsigned)(m * 128)))->v;
         }
     };
     const TurnAt turn = turn_at<T>(SLOTS * IMG + wave * 256, lane);
-    f32x16 acc[2][NT];
+    f32x16 acc[TILES][NT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < TILES; ++t)
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
@@ -466,10 +468,10 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
         }
     };
 
-    static_assert(8 + VL <= 15, "the low field of the count");
+    static_assert(NL + VL <= 15, "the low field of the count");
     int sc = 0;  // slot of the present window's image
     // the products of one window: row operands a
-    auto multiply = [&](const RowOp<T> (&a)[2], auto&& between) __attribute__((always_inline)) {
+    auto multiply = [&](const RowOp<T> (&a)[TILES], auto&& between) __attribute__((always_inline)) {
         constexpr int STEPS = KS * 3 * NT;  // (k-step, part of the basis, column tile)
         int hq = h;
         asm volatile("" : "+v"(hq));  // (addresses are formed when they are needed: registers are short)
@@ -479,14 +481,14 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
         };
         u32x4 b[2];
         b[0] = lds[addr(0)];
-        u32x4 ap[2][3];
+        u32x4 ap[TILES][3];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             const int j = s / (3 * NT), pt = (s / NT) % 3, ct = s % NT;
             if (s % (3 * NT) == 0) {
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
+                for (int t = 0; t < TILES; ++t) {
                     if constexpr (sizeof(T) == 2) {
                         ap[t][0] = a[t].v[j];
                     } else {
@@ -504,14 +506,14 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
             }
             if (s + 1 < STEPS) b[(s + 1) % 2] = lds[addr(s + 1)];
             if (s == STEPS / 4) between(0);
-            if (s == STEPS / 2) between(1);
+            if (s == STEPS / 2 && TILES == 2) between(1);
             const u32x4 bb = b[s % 2];
             constexpr int QS = sizeof(T) == 2 ? 1 : 3;
 #pragma unroll
             for (int q = 0; q < QS; ++q)
                 if (q + pt <= 2) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) acc[t][ct] = mfma_bf16(ap[t][q], bb, acc[t][ct]);
+                    for (int t = 0; t < TILES; ++t) acc[t][ct] = mfma_bf16(ap[t][q], bb, acc[t][ct]);
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -520,11 +522,11 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     // requested is that of m + SLOTS - 1. more: false where the split has two windows at most, as those of small projections
     // have, and nothing beyond them is requested (333 rows of 25,447 bf16: 22.2 us with such requests, 19.5
     // without; 20.5 before rows were turned).
-    auto visit = [&](RowRaw (&raw)[2], int64_t m, auto more) __attribute__((always_inline)) {
+    auto visit = [&](RowRaw (&raw)[TILES], int64_t m, auto more) __attribute__((always_inline)) {
         constexpr bool MORE = decltype(more)::value;
         const int64_t m2 = m + 2 > c1 - 1 ? c1 - 1 : m + 2;  // beyond the last window: repeat it (never used)
-        RowOp<T> a[2];
-        turn_rows<T>(lds, turn, raw, a);
+        RowOp<T> a[TILES];
+        turn_rows<TILES, LX, T>(lds, turn, raw, a);
         if (MORE || SLOTS == 2) stage(m + SLOTS - 1, sc == 0 ? SLOTS - 1 : sc - 1);
         multiply(a, [&](int t) __attribute__((always_inline)) {
             if constexpr (MORE) load_rows(raw[t], t, m2);
@@ -532,7 +534,7 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
         // at most this window's row loads, with three slots its image loads too, stay outstanding: image m + 1 and rows m + 1
         // have landed
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (MORE ? 8 + (SLOTS == 3 ? VL : 0) : 0));
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (MORE ? NL + (SLOTS == 3 ? VL : 0) : 0));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
@@ -542,12 +544,12 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     constexpr std::false_type LAST{};
 
     const int64_t len = c1 - c0;
-    auto begin = [&](RowRaw (&a0)[2], RowRaw (&a1)[2]) __attribute__((always_inline)) {
+    auto begin = [&](RowRaw (&a0)[TILES], RowRaw (&a1)[TILES]) __attribute__((always_inline)) {
         stage(c0, 0);
         if (SLOTS == 3) stage(c0 + 1, 1);
         const int64_t m1 = len > 1 ? c0 + 1 : c0;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < TILES; ++t) {
             load_rows(a0[t], t, c0);
             load_rows(a1[t], t, m1);
         }
@@ -555,7 +557,7 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
         __syncthreads();
     };
     if (len > 2) {
-        RowRaw a0[2], a1[2];
+        RowRaw a0[TILES], a1[TILES];
         begin(a0, a1);
 #pragma unroll 1
         for (int64_t m = c0; m < c1; m += 2) {  // two windows per trip: the row buffers return to their roles
@@ -565,7 +567,7 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS any more
     }
     if (len == 1 || len == 2) {
-        RowRaw a0[2], a1[2];
+        RowRaw a0[TILES], a1[TILES];
         begin(a0, a1);
         visit(a0, c0, LAST);
         if (len == 2) visit(a1, c0 + 1, LAST);
@@ -575,22 +577,22 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
         stage(full, 0);
         // The last 128 bytes of every row are loaded, and the columns beyond the whole windows picked out of them in LDS.
         const int left = (int)(D - full * KC);
-        RowRaw raw[2];
+        RowRaw raw[TILES];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < TILES; ++t)
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                unsigned r = lrow + (unsigned)(t * 32 + 8 * x) * (unsigned)S;
+            for (int x = 0; x < LX; ++x) {
+                unsigned r = lrow + (unsigned)((t * 32 + 8 * x) * 8) * (unsigned)S;
                 r = r > last_row ? last_row : r;
                 raw[t].v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (r + (unsigned)S - 128u + 16u * (unsigned)(lane & 7)))->v;
             }
-        RowOp<T> a[2];
+        RowOp<T> a[TILES];
         char* const l = reinterpret_cast<char*>(lds);
         const unsigned line = (unsigned)(SLOTS * IMG + wave * 256 + n * 8) * 16u, swz = (unsigned)((n >> 1) & 7) * 16u;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < TILES; ++t) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x) *reinterpret_cast<u32x4*>(l + (x & 1 ? turn.w1 : turn.w0) + x * 1024) = raw[t].v[x];
+            for (int x = 0; x < LX; ++x) *reinterpret_cast<u32x4*>(l + (x & 1 ? turn.w1 : turn.w0) + x * 1024) = raw[t].v[x];
             asm volatile("" ::: "memory");  // (a wave's LDS accesses keep their order)
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
@@ -615,12 +617,12 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
 
     float* out = partial + (int64_t)split * R * KP;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < TILES; ++t)
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int64_t r = row0 + wave * 64 + t * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+                const int64_t r = row0 + wave + 8 * (t * 32 + 8 * (i >> 2) + 4 * h + (i & 3));
                 if (r < R) out[r * KP + ct * 32 + n] = acc[t][ct][i];
             }
 }
@@ -657,22 +659,32 @@ ScorePlan score_split_plan(int64_t R, int dtype, const Dims& d, int num_cu) {
     return p;
 }
 
+// Row loads of a wave and window (eight rows each; the waves take the rows of a work-group in turn): as few as hold the batch.
+// (Eight whatever the batch: of 64 rows most loads ask for the last row again, a line that is on its way. 64 fp32 rows of 977,864
+// with 8 vectors: 183 us with eight, 101 with one; 128 bf16 rows of 200,001 with 100 vectors 67 and 41.)
+int loads_of(int64_t R) { return R > 256 ? 8 : R > 128 ? 4 : R > 64 ? 2 : 1; }
+
+template <int NT, typename T, int NL>
+static hipError_t launch_split_nl(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
+                                  const Dims& d, hipStream_t st) {
+    constexpr int KC = 128 / (int)sizeof(T);
+    const int lds = parts == 3 ? AnyShape<NT, T>::LDS : 4 * 2 * NT * 32 * (KC / 8) * 16 + 8 * 256 * 16;
+    void (*const kern)(const T*, int64_t, const u32x4*, float*, int, int64_t, int64_t, int64_t) =
+        parts == 3 ? project_any_kernel<NT, T, NL> : project_split_kernel<NT, T, NL>;
+    if (hipError_t ea = ensure_dynamic_lds((const void*)kern, lds); ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.row_tiles * p.splits)), dim3(512), lds, st, G, R, (const u32x4*)img, partial,
+                       p.row_tiles, d.D, (d.D + KC - 1) / KC, p.slabs_per_split);
+    return hipGetLastError();
+}
 template <int NT, typename T>
 static hipError_t launch_split_t(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
                                  const Dims& d, hipStream_t st) {
-    constexpr int KC = 128 / (int)sizeof(T);
-    const int lds = parts == 3 ? AnyShape<NT, T>::LDS : 4 * 2 * NT * 32 * (KC / 8) * 16 + 8 * 256 * 16;
-    const void* kern = parts == 3 ? (const void*)project_any_kernel<NT, T> : (const void*)project_split_kernel<NT, T>;
-    if (hipError_t ea = ensure_dynamic_lds(kern, lds); ea != hipSuccess) return ea;
-    const int64_t chunks = (d.D + KC - 1) / KC;
-    dim3 grid((unsigned)(p.row_tiles * p.splits));
-    if (parts == 3)
-        hipLaunchKernelGGL((project_any_kernel<NT, T>), grid, dim3(512), lds, st, G, R, (const u32x4*)img, partial,
-                           p.row_tiles, d.D, chunks, p.slabs_per_split);
-    else
-        hipLaunchKernelGGL((project_split_kernel<NT, T>), grid, dim3(512), lds, st, G, R, (const u32x4*)img, partial,
-                           p.row_tiles, d.D, chunks, p.slabs_per_split);
-    return hipGetLastError();
+    switch (loads_of(R)) {
+        case 1: return launch_split_nl<NT, T, 1>(G, R, parts, img, partial, p, d, st);
+        case 2: return launch_split_nl<NT, T, 2>(G, R, parts, img, partial, p, d, st);
+        case 4: return launch_split_nl<NT, T, 4>(G, R, parts, img, partial, p, d, st);
+        default: return launch_split_nl<NT, T, 8>(G, R, parts, img, partial, p, d, st);
+    }
 }
 
 template <int NT>

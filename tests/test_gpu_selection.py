@@ -96,10 +96,13 @@ def test_projection_of_rows_of_any_alignment(dtype, D, k):
 
 
 # Rows on multiples of 8 columns, and of 4 (a basis in three parts): one window to some, partial ones, rows that start anywhere
-# in a line, row counts that end inside a wave's rows, several row tiles, a batch over 4 GiB (lane offsets have 32 bits).
+# in a line, row counts that end inside a wave's rows and at each number of row loads, several row tiles, a batch over 4 GiB
+# (lane offsets have 32 bits).
 @pytest.mark.parametrize("n,D,k,dtype", [(n, D, k, t) for n in (1, 63, 700) for D in (64, 72, 1000) for k in (3, 40, 100)
                                          for t in ("f32", "bf16")]
                          + [(n, D, k, "f32") for n in (1, 63, 700) for D in (36, 68, 100, 1004) for k in (3, 40, 100)]
+                         + [(n, D, k, t) for n in (64, 65, 128, 129, 256, 257) for D, k in ((1000, 40), (1001, 100))
+                            for t in ("f32", "bf16")]
                          + [(1100, 1_048_576, 100, "f32"), (1100, 1_048_580, 100, "f32"), (1100, 2_049_000, 100, "bf16"),
                             (1100, 2_049_001, 100, "bf16")])
 def test_projection_of_aligned_rows_at_the_edges_of_its_tiles(n, D, k, dtype):
