@@ -171,10 +171,7 @@ def run_workload(torch, inputs, Sage, w, K, W, split=True, labels_classes=None, 
     # Gram blocks: three bf16 parts a value, 6 products; rows of a bf16 stream have one part, so 3 where such a row is one
     # factor and 1 where both are. Rebuild: two fp16 parts, 3 products, 2 for the rows of a bf16 stream. (The products left
     # out are exact zeros.)
-    # Wide fp32 rows: Gram blocks in two fp16 parts too, in the cycles that look ahead (those of the pass that is timed kernel
-    # by kernel do not: six products there).
     one_part = w.dtype == "bf16"
-    wide_f32 = not one_part and LP == 256 and D >= 131072
     rebuild_products = (3.0 + 2.0) / 2.0 if one_part else 3.0                  # top half 3, new half 2
     gram_products = (16 * 3.0 + 10 * 1.0) / 26.0 if one_part else 6.0          # 16 tiles new x top, 10 tiles new x new
     res.update({
@@ -192,9 +189,7 @@ def run_workload(torch, inputs, Sage, w, K, W, split=True, labels_classes=None, 
         "ms": {"update": ms_update, "basis": ms_basis, "score": ms_score, "select": ms_select, "wall": wall * 1e3},
         "selected": int(idx.numel()), "jacobi_sweeps_last": st.last_sweeps, "n_shrinks": int(st.n_shrinks),
         "unconverged_solves": int(st.n_unconverged),
-        "update_arithmetic": (("Gram and rebuild: fp32 values as two scaled fp16 parts, 3 products per fp32 product (fp32 accuracy)"
-                               if wide_f32 else
-                               "Gram: fp32 values as three bf16 parts, 6 bf16 MFMA products per fp32 product; rebuild: as two "
+        "update_arithmetic": (("Gram: fp32 values as three bf16 parts, 6 bf16 MFMA products per fp32 product; rebuild: as two "
                                "scaled fp16 parts, 3 products (fp32 accuracy)"
                                + ("; bf16 stream rows have one part: 3 (rebuild 2) products where one factor is such a row, "
                                   "1 where both are (same bits)" if one_part else ""))

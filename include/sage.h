@@ -266,8 +266,7 @@ int sage_set_projection_mode(sage_ctx* ctx, int mode);
  * partial products that matter run on the bf16 or fp16 matrix cores, accumulated in fp32 -- the fp32 result at a multiple of
  * the fp32 matrix-core rate. Gram blocks and the basis: three bf16 parts (24 significant bits), six products, good to a few
  * 2^-24 per term; the rebuild of a shrink: two fp16 parts of the scaled values (22 significant bits), three products, good to
- * 2^-22 per term, below what accumulating them in fp32 leaves; so are the Gram blocks of fp32 rows of 131,072 columns and more
- * in cycles whose rows were stored ahead. It is used where a kernel exists: the rebuild for ell >= 65
+ * 2^-22 per term, below what accumulating them in fp32 leaves. It is used where a kernel exists: the rebuild for ell >= 65
  * (padded sketch size 128 or 256), the Gram blocks of the steady state (new rows x top rows, new rows x new rows) and the
  * whole Gram matrix before the first shrink for ell >= 129 (padded size 256); everything else, and everything under
  * SAGE_MM_F32, runs on the fp32 matrix cores. Rows that arrive through sage_fd_update or sage_fd_update_outer in a bf16 context

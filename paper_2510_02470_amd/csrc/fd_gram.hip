@@ -331,37 +331,26 @@ __global__ __launch_bounds__(256, 2) void gram_cross8_kernel(const float* __rest
 // instructions (all waves of a work-group run in step: conversions done in one block would leave the matrix cores
 // idle), from registers that were loaded a stage earlier and are reloaded, for the slab after next, as soon as they
 // have been consumed.
-// MODE 1: the new half is kept in pieces of bf16 (half16): its mid and lo parts are zero, so only one part is staged, as it
+// NEW1: the new half is kept in pieces of bf16 (half16): its mid and lo parts are zero, so only one part is staged, as it
 // is, and only the three products with it are issued. The three left out would add exact
 // zeros: the result has the same bits either way.
-// MODE 2: fp32 rows in two fp16 parts (22 significant bits of a row scaled by a power of two: top rows by their norms, which the
-// shrink knows, new rows by their largest magnitudes, which were found when they were stored), three products, half the
-// matrix-core work. 256 + 256 rows of 1,048,576 columns: 680 us in six bf16 products, 455 in three, where memory is the bound
-// (2.1 GB, 4.7 TB/s). Fewer additions to the long sums are worth more than the two bits. Errors against 64 bits, in units of the
-// norms' product, root mean square of all elements, of this block and of new x new, at 131,072 / 1,048,576 columns: rows of
-// independent elements 0.95e-9 and 5.8e-9 / 1.2e-9 and 17e-9, in bf16 1.5e-9 and 17e-9 / 3.5e-9 and 180e-9; with a common
-// component 11e-9 and 14e-9 / 37e-9 and 90e-9, in bf16 17e-9 and 25e-9 / 64e-9 and 195e-9. At 65,536 columns the
-// triangle was no better (4.7e-9 against 3.5e-9 for independent elements), so shorter rows keep the bf16 parts, see side_ahead.
-template <int MODE>
+template <bool NEW1>
 __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* __restrict__ top,
                                                                    const float* __restrict__ nw, int nfill,
                                                                    float* __restrict__ partial, int64_t slabs_total,
-                                                                   int64_t slabs_per_group, const double* __restrict__ known,
-                                                                   const unsigned* __restrict__ maxima) {
-    constexpr bool NEW1 = MODE == 1, F16 = MODE == 2;
-    constexpr int NP = 512, LP = 256, PARTS = F16 ? 2 : 3;
+                                                                   int64_t slabs_per_group) {
+    constexpr int NP = 512, LP = 256;
     constexpr int HALF4 = LP * 4;        // 16-byte pieces of a half buffer per slab
     constexpr int HREG = NP + 8;         // pieces per k-half region: the rows plus 128 bytes, so that the two regions a
                                          // staging store touches fall on different banks
     constexpr int PART16 = 2 * HREG;     // pieces per part: [k-half][row]
-    constexpr int STAGE16 = PARTS * PART16;  // 48.4 KB
+    constexpr int STAGE16 = 3 * PART16;  // 48.4 KB
     extern __shared__ u32x4 ldsx[];      // 2 * STAGE16
-    __shared__ int ex[F16 ? NP : 1];     // exponents of the rows' scales
 
     const int id = blockIdx.x;
     const int xcd = id & 7;
     const int group = (id >> 3) * 8 + xcd;
-    int64_t s0 = (int64_t)group * slabs_per_group;
+    const int64_t s0 = (int64_t)group * slabs_per_group;
     int64_t s1 = s0 + slabs_per_group;
     if (s1 > slabs_total) s1 = slabs_total;
 
@@ -371,6 +360,14 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
     const int ag = wave >> 2, bg = wave & 3;  // new rows 128*ag .. + 128, top rows 64*bg .. + 64
     const int arow = LP + ag * 128 + l32;     // + 32 * i, i < 4
     const int brow = bg * 64 + l32;           // + 32 * cb
+
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][b][e] = 0.f;
 
     // staging: piece ps = it * 512 + tid is columns 4p .. 4p+3 of row ps >> 2 (rows >= LP: the new half)
     // (NEW1: the new rows' pieces are those of half16: piece tid is k-half tid >> 8 of row tid & 255)
@@ -385,20 +382,6 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
         const int hr = row >= LP ? row - LP : row;
         src[it] = (row >= LP && hr >= nfill) ? -1 : hr * 4 + p;
         dst8[it] = (((p >> 1) * HREG + row) << 1) + (p & 1);
-    }
-    float sc[4];
-    if constexpr (F16) {
-        if (tid < LP) {
-            double top2 = 0.0;
-#pragma unroll
-            for (int j = 0; j < LP; j += 64) top2 = fmax(top2, known[j + lane]);
-            for (int o = 32; o >= 1; o >>= 1) top2 = fmax(top2, __shfl_xor(top2, o));
-            ex[tid] = row_exponent(known[tid], top2);
-            ex[LP + tid] = max_exponent(maxima[tid]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < 4; ++it) sc[it] = __builtin_amdgcn_ldexpf(1.f, ex[it * 128 + (tid >> 2)]);
     }
     const bool used16 = (tid & 255) < nfill;
     const int dst16 = (tid >> 8) * HREG + LP + (tid & 255);
@@ -419,14 +402,6 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
             return;
         }
         uint2* d = reinterpret_cast<uint2*>(ldsx + buf * STAGE16) + dst8[it];
-        if constexpr (F16) {
-            unsigned a0, a1, b0, b1;
-            split2_f16(pre[it][0], pre[it][1], sc[it], sc[it], a0, a1);
-            split2_f16(pre[it][2], pre[it][3], sc[it], sc[it], b0, b1);
-            d[0] = make_uint2(a0, b0);
-            d[2 * PART16] = make_uint2(a1, b1);
-            return;
-        }
         unsigned a0, a1, a2, b0, b1, b2;
         split3_bf16(pre[it][0], pre[it][1], a0, a1, a2);
         split3_bf16(pre[it][2], pre[it][3], b0, b1, b2);
@@ -434,106 +409,73 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
         d[2 * PART16] = make_uint2(a1, b1);
         d[4 * PART16] = make_uint2(a2, b2);
     };
-    // MODE 2 sums its slabs in two halves: a long sum of one sign loses more to the fp16 cores' rounding (rows with a common
-    // component, 1,048,576 columns: 7.7e-8 of the norms' product in one, 3.7e-8 in two; 6.4e-8 in three bf16 parts).
-    const int64_t last = s1;
-    if (F16 && s1 - s0 >= 64) s1 = s0 + (s1 - s0) / 2;
-    bool second = false;
-#pragma unroll 1
-    for (;;) {
-        f32x16 acc[4][2];
+    if (s0 < s1) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int it = 0; it < IT; ++it) fetch1(it, s0);
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][b][e] = 0.f;
-
-        if (s0 < s1) {
-#pragma unroll
-            for (int it = 0; it < IT; ++it) fetch1(it, s0);
-#pragma unroll
-            for (int it = 0; it < IT; ++it) {
-                store1(it, 0);
-                fetch1(it, s0 + 1);
-            }
+        for (int it = 0; it < IT; ++it) {
+            store1(it, 0);
+            fetch1(it, s0 + 1);
         }
-        __syncthreads();
+    }
+    __syncthreads();
 
-        constexpr int AP = NEW1 ? 1 : PARTS;  // parts of a new row
-        constexpr int NQ = NEW1 || F16 ? 3 : 6;  // products
-        for (int64_t s = s0; s < s1; ++s) {
-            const int cur = (int)((s - s0) & 1);
-            const u32x4* st = ldsx + cur * STAGE16 + h * HREG;
-            u32x4 a[4][AP], b[2][PARTS];
+    constexpr int AP = NEW1 ? 1 : 3;  // parts of a new row
+    constexpr int NQ = NEW1 ? 3 : 6;  // products
+    for (int64_t s = s0; s < s1; ++s) {
+        const int cur = (int)((s - s0) & 1);
+        const u32x4* st = ldsx + cur * STAGE16 + h * HREG;
+        u32x4 a[4][AP], b[2][3];
 #pragma unroll
-            for (int p = 0; p < PARTS; ++p) {
-                if (p < AP) {
+        for (int p = 0; p < 3; ++p) {
+            if (p < AP) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) a[i][p] = st[p * PART16 + arow + 32 * i];
-                }
+                for (int i = 0; i < 4; ++i) a[i][p] = st[p * PART16 + arow + 32 * i];
+            }
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb) b[cb][p] = st[p * PART16 + brow + 32 * cb];
+            for (int cb = 0; cb < 2; ++cb) b[cb][p] = st[p * PART16 + brow + 32 * cb];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {  // in the order the parts were read: the first group needs the hi parts only
+            constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+            const int pa = NEW1 ? 0 : PA[q], pb = NEW1 ? q : PB[q];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) acc[i][cb] = mfma_bf16(a[i][pa], b[cb][pb], acc[i][cb]);
+            // slab s + 1 into the other buffer, slab s + 2 on its way
+            if (!NEW1 && q < 4) {
+                store1(q, cur ^ 1);
+                fetch1(q, s + 2);
+            }
+            if (NEW1) {
+                store1(q, cur ^ 1);
+                fetch1(q, s + 2);
             }
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {  // in the order the parts were read: the first group needs the hi parts only
-                constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
-                const int pa = NEW1 ? 0 : PA[q], pb = NEW1 ? q : PB[q];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
-                        acc[i][cb] = F16 ? mfma_f16(a[i][pa], b[cb][pb], acc[i][cb]) : mfma_bf16(a[i][pa], b[cb][pb], acc[i][cb]);
-                // slab s + 1 into the other buffer, slab s + 2 on its way
-                if (!NEW1 && q < (F16 ? 3 : 4)) {
-                    store1(q, cur ^ 1);
-                    fetch1(q, s + 2);
-                    if (F16 && q == 2) {
-                        store1(3, cur ^ 1);
-                        fetch1(3, s + 2);
-                    }
-                }
-                if (NEW1) {
-                    store1(q, cur ^ 1);
-                    fetch1(q, s + 2);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // the LDS stores above must be visible, the reads of this stage are consumed; the loads for slab s + 2 stay
-            // in flight (a bare barrier: __syncthreads() would wait for them)
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
         }
+        // the LDS stores above must be visible, the reads of this stage are consumed; the loads for slab s + 2 stay
+        // in flight (a bare barrier: __syncthreads() would wait for them)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
 
-        // tiles (ti - 4, tj) = (2*ag + i/2, bg); rows (i & 1) * 32 .. + 32 of the tile
-        int ho = h, lo = l32;
-        if (F16) asm volatile("" : "+v"(ho), "+v"(lo)::"memory");  // (nothing of this is formed before the loop and kept)
+    // tiles (ti - 4, tj) = (2*ag + i/2, bg); rows (i & 1) * 32 .. + 32 of the tile
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int tidx = (2 * ag + (i >> 1)) * 4 + bg;
-            float* out = partial + ((int64_t)group * 16 + tidx) * 4096 + (i & 1) * 2048;
+    for (int i = 0; i < 4; ++i) {
+        const int tidx = (2 * ag + (i >> 1)) * 4 + bg;
+        float* out = partial + ((int64_t)group * 16 + tidx) * 4096 + (i & 1) * 2048;
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
+        for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int r = 8 * (e >> 2) + 4 * ho + (e & 3);
-                    const int c = cb * 32 + lo;
-                    float x = acc[i][cb][e];
-                    if constexpr (F16) {
-                        x = __builtin_amdgcn_ldexpf(x, -(ex[bg * 64 + c] + ex[LP + ag * 128 + i * 32 + r]));
-                        if (second) x += out[r * 64 + c];
-                    }
-                    out[r * 64 + c] = x;
-                }
-        }
-        if (s1 == last) break;
-        s0 = s1;
-        s1 = last;
-        second = true;
-        __syncthreads();  // (the stages are free again)
+            for (int e = 0; e < 16; ++e) {
+                int r = 8 * (e >> 2) + 4 * h + (e & 3);
+                int c = cb * 32 + l32;
+                out[r * 64 + c] = acc[i][cb][e];
+            }
     }
 }
 
@@ -667,16 +609,15 @@ __global__ __launch_bounds__(256, 2) void gram_new8_kernel(const float* __restri
 // The same triangle on the bf16 matrix cores with three-way split values (see gram_cross8_split_kernel): the new rows
 // of a slab are split when they are staged ([part][k-half][row] pieces, 24 KB per stage), a wave's six operand row
 // blocks are 18 LDS reads per 54 matrix-core instructions, and the next slab is split and stored between the six
-// groups of matrix-core instructions. F16: two scaled fp16 parts, three products and on the diagonal blocks a fourth (beside
-// the eigensolve 460 us for 256 rows of 1,048,576 columns in bf16 parts, 400 now).
-template <int W, bool F16>
+// groups of matrix-core instructions.
+template <int W>
 __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ Nv, int nfill, float* __restrict__ partial,
-                                                     int group, int64_t s0, int64_t s1, u32x4* lds, const int* ex) {
+                                                     int group, int64_t s0, int64_t s1, u32x4* lds) {
     using M = New8Map<W>;
     constexpr int LP = 256, HALF4 = LP * 4;
     constexpr int HREG = LP + 8;         // pieces per k-half region (padded, see gram_cross8_split_kernel)
     constexpr int PART16 = 2 * HREG;     // pieces per part: [k-half][row]
-    constexpr int STAGE16 = (F16 ? 2 : 3) * PART16;  // 24.4 KB
+    constexpr int STAGE16 = 3 * PART16;  // 24.4 KB
     const int tid = threadIdx.x & 255, lane = tid & 63;
     const int l32 = lane & 31, h = lane >> 5;
 
@@ -693,11 +634,6 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
         src[it] = row >= nfill ? -1 : row * 4 + p;
         dst8[it] = (((p >> 1) * HREG + row) << 1) + (p & 1);
     }
-    float sc[4];
-    if constexpr (F16) {
-#pragma unroll
-        for (int it = 0; it < 4; ++it) sc[it] = __builtin_amdgcn_ldexpf(1.f, ex[it * 64 + (tid >> 2)]);
-    }
     f32x4 pre[4];
     auto fetch1 = [&](int it, int64_t sl) __attribute__((always_inline)) {
         const int64_t sc = sl < s1 ? sl : s1 - 1;  // beyond the end: repeat (never used)
@@ -705,14 +641,6 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
     };
     auto store1 = [&](int it, int buf) __attribute__((always_inline)) {
         uint2* d = reinterpret_cast<uint2*>(lds + buf * STAGE16) + dst8[it];
-        if constexpr (F16) {
-            unsigned a0, a1, b0, b1;
-            split2_f16(pre[it][0], pre[it][1], sc[it], sc[it], a0, a1);
-            split2_f16(pre[it][2], pre[it][3], sc[it], sc[it], b0, b1);
-            d[0] = make_uint2(a0, b0);
-            d[2 * PART16] = make_uint2(a1, b1);
-            return;
-        }
         unsigned a0, a1, a2, b0, b1, b2;
         split3_bf16(pre[it][0], pre[it][1], a0, a1, a2);
         split3_bf16(pre[it][2], pre[it][3], b0, b1, b2);
@@ -734,7 +662,7 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
     for (int64_t s = s0; s < s1; ++s) {
         const int cur = (int)((s - s0) & 1);
         const u32x4* st = lds + cur * STAGE16 + h * HREG + l32;
-        constexpr int NP3 = F16 ? 2 : 3, NQ = F16 ? 3 : 6;
+        constexpr int NP3 = 3, NQ = 6;
         u32x4 op[6][NP3];
 #pragma unroll
         for (int p = 0; p < NP3; ++p)
@@ -745,24 +673,12 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
         for (int k = 0; k < NQ; ++k) {  // in the order the parts were read
             constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                const u32x4 a = op[M::pa[q]][PA[k]], b = op[M::pb[q]][PB[k]];
-                acc[q] = F16 ? mfma_f16(a, b, acc[q]) : mfma_bf16(a, b, acc[q]);
-            }
-            if (k < (F16 ? 3 : 4)) {
+            for (int q = 0; q < 9; ++q) acc[q] = mfma_bf16(op[M::pa[q]][PA[k]], op[M::pb[q]][PB[k]], acc[q]);
+            if (k < 4) {
                 store1(k, cur ^ 1);
                 fetch1(k, s + 2);
-                if (F16 && k == 2) {
-                    store1(3, cur ^ 1);
-                    fetch1(3, s + 2);
-                }
             }
             __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (F16) {  // lo * lo: left out, the diagonal would always be too small
-#pragma unroll
-            for (int q = 0; q < 9; ++q)
-                if (M::pa[q] == M::pb[q]) acc[q] = mfma_f16(op[M::pa[q]][1], op[M::pb[q]][1], acc[q]);
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the LDS stores; the loads for slab s + 2 stay in flight
@@ -778,35 +694,28 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int r = 8 * (e >> 2) + 4 * h + (e & 3);
-            out[r * 64 + l32] = F16 ? __builtin_amdgcn_ldexpf(acc[q][e], -(ex[bi * 32 + r] + ex[bj * 32 + l32])) : acc[q][e];
+            out[r * 64 + l32] = acc[q][e];
         }
     }
 }
 
-template <bool F16>
 __global__ __launch_bounds__(256, 2) void gram_new8_split_kernel(const float* __restrict__ nw, int nfill,
                                                                  float* __restrict__ partial, int64_t slabs_total,
                                                                  int64_t slabs_per_group, int groups,
-                                                                 const int* __restrict__ hole,
-                                                                 const unsigned* __restrict__ maxima) {
+                                                                 const int* __restrict__ hole) {
     extern __shared__ u32x4 ldsn[];
-    __shared__ int ex[F16 ? 256 : 1];
     const int group = (int)spare_unit_at(hole);
     if (group < 0 || group >= groups) return;
     int64_t s0 = (int64_t)group * slabs_per_group;
     int64_t s1 = s0 + slabs_per_group;
     if (s1 > slabs_total) s1 = slabs_total;
     if (s0 > s1) s0 = s1;
-    if constexpr (F16) {
-        ex[threadIdx.x] = max_exponent(maxima[threadIdx.x]);
-        __syncthreads();
-    }
     const f32x4* Nv = reinterpret_cast<const f32x4*>(nw);
     switch (threadIdx.x >> 6) {  // wave-uniform
-        case 0: gram_new8_split_wave<0, F16>(Nv, nfill, partial, group, s0, s1, ldsn, ex); break;
-        case 1: gram_new8_split_wave<1, F16>(Nv, nfill, partial, group, s0, s1, ldsn, ex); break;
-        case 2: gram_new8_split_wave<2, F16>(Nv, nfill, partial, group, s0, s1, ldsn, ex); break;
-        default: gram_new8_split_wave<3, F16>(Nv, nfill, partial, group, s0, s1, ldsn, ex); break;
+        case 0: gram_new8_split_wave<0>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+        case 1: gram_new8_split_wave<1>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+        case 2: gram_new8_split_wave<2>(Nv, nfill, partial, group, s0, s1, ldsn); break;
+        default: gram_new8_split_wave<3>(Nv, nfill, partial, group, s0, s1, ldsn); break;
     }
 }
 
@@ -1024,18 +933,20 @@ GramPlan gram_plan_split(const GramPlan& base, const Dims& d, int groups) {
 }
 
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
-                       hipStream_t st, bool new_one, const int* hole, const GramScale& scale) {
+                       hipStream_t st, bool new_one, const int* hole) {
     if (p.tiles <= 0) return hipSuccess;
     dim3 grid((unsigned)(p.groups * p.wg_per_group));
     size_t lds = (size_t)2 * d.NP * 64;
     if (p.mode == 1 && d.NP == 512 && p.split) {
         constexpr int LDS_SPLIT = 2 * 3 * 2 * (512 + 8) * 16;  // two stages of [part][k-half][row + pad] pieces
-        void (*const kern)(const float*, const float*, int, float*, int64_t, int64_t, const double*, const unsigned*) =
-            new_one ? gram_cross8_split_kernel<1> : scale.maxima ? gram_cross8_split_kernel<2> : gram_cross8_split_kernel<0>;
-        if (hipError_t ea = ensure_dynamic_lds((const void*)kern, LDS_SPLIT); ea != hipSuccess) return ea;
-        const int lds2 = scale.maxima && !new_one ? LDS_SPLIT / 3 * 2 : LDS_SPLIT;
-        hipLaunchKernelGGL(kern, grid, dim3(512), lds2, st, top, nw, nfill, partial, d.S, p.slabs_per_group, scale.known,
-                           scale.maxima);
+        const void* kern = new_one ? (const void*)gram_cross8_split_kernel<true> : (const void*)gram_cross8_split_kernel<false>;
+        if (hipError_t ea = ensure_dynamic_lds(kern, LDS_SPLIT); ea != hipSuccess) return ea;
+        if (new_one)
+            hipLaunchKernelGGL(gram_cross8_split_kernel<true>, grid, dim3(512), LDS_SPLIT, st, top, nw, nfill, partial, d.S,
+                               p.slabs_per_group);
+        else
+            hipLaunchKernelGGL(gram_cross8_split_kernel<false>, grid, dim3(512), LDS_SPLIT, st, top, nw, nfill, partial,
+                               d.S, p.slabs_per_group);
         return hipGetLastError();
     }
     if (p.mode == 1 && d.NP == 512) {
@@ -1058,12 +969,8 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
                                    p.slabs_per_group, p.groups, hole);
         } else {
             constexpr int LDS = 2 * 3 * 2 * (256 + 8) * 16;  // two stages
-            if (scale.maxima)
-                hipLaunchKernelGGL(gram_new8_split_kernel<true>, wgs, dim3(256), LDS / 3 * 2, st, nw, nfill, partial, d.S,
-                                   p.slabs_per_group, p.groups, hole, scale.maxima);
-            else
-                hipLaunchKernelGGL(gram_new8_split_kernel<false>, wgs, dim3(256), LDS, st, nw, nfill, partial, d.S,
-                                   p.slabs_per_group, p.groups, hole, scale.maxima);
+            hipLaunchKernelGGL(gram_new8_split_kernel, wgs, dim3(256), LDS, st, nw, nfill, partial, d.S, p.slabs_per_group,
+                               p.groups, hole);
         }
         return hipGetLastError();
     }

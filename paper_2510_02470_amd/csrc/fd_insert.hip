@@ -11,8 +11,7 @@ namespace sage {
 // hole: see spare_unit_at.
 template <int NS, typename Src>
 __global__ __launch_bounds__(256) void insert_kernel(Src src, int rows, int row0, float* __restrict__ B, int NP, int64_t D,
-                                                     int64_t S, int row_groups, int64_t units, const int* __restrict__ hole,
-                                                     unsigned* __restrict__ maxima) {
+                                                     int64_t S, int row_groups, int64_t units, const int* __restrict__ hole) {
     const int64_t unit = spare_unit_at(hole);
     if (unit < 0 || unit >= units) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -26,15 +25,6 @@ __global__ __launch_bounds__(256) void insert_kernel(Src src, int rows, int row0
 #pragma unroll
     for (int i = 0; i < NS; ++i)
         if (s0 + i < S) dst[(int64_t)i * NP * (DC / 4)] = v[i];
-    if (maxima) {  // (a row's word is read first: of its thousands of parts few raise it)
-        float m = 0.f;
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-            m = fmaxf(m, fmaxf(fmaxf(fabsf(v[i].x), fabsf(v[i].y)), fmaxf(fabsf(v[i].z), fabsf(v[i].w))));
-        m = fmaxf(m, __shfl_xor(m, 1));
-        m = fmaxf(m, __shfl_xor(m, 2));
-        if (p == 0 && __float_as_uint(m) > maxima[row0 + r]) atomicMax(&maxima[row0 + r], __float_as_uint(m));
-    }
 }
 
 struct __attribute__((packed, aligned(2))) Eight {  // eight bf16 values at any element boundary
@@ -117,7 +107,7 @@ __global__ __launch_bounds__(256) void insert16_kernel(Src src, int rows, int ro
 
 template <typename Src>
 static hipError_t launch_insert_src(const Src& src, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                                    bool to16, const int* hole, hipStream_t st, unsigned* maxima) {
+                                    bool to16, const int* hole, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
     const int row_groups = (int)((rows + 63) / 64);
     if constexpr (Src::BF16) {
@@ -134,25 +124,17 @@ static hipError_t launch_insert_src(const Src& src, int64_t rows, int row0, floa
     const dim3 grid((unsigned)spare_grid_at(units, hole));
     if (wide >= 1024)
         hipLaunchKernelGGL((insert_kernel<16, Src>), grid, dim3(256), 0, st, src, (int)rows, row0, half, half_rows, d.D, d.S,
-                           row_groups, units, hole, maxima);
+                           row_groups, units, hole);
     else
         hipLaunchKernelGGL((insert_kernel<4, Src>), grid, dim3(256), 0, st, src, (int)rows, row0, half, half_rows, d.D, d.S,
-                           row_groups, units, hole, maxima);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void clear_words_kernel(unsigned* __restrict__ p, int n) {
-    for (int i = threadIdx.x; i < n; i += 256) p[i] = 0u;
-}
-hipError_t launch_clear_words(unsigned* p, int n, hipStream_t st) {
-    hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(256), 0, st, p, n);
+                           row_groups, units, hole);
     return hipGetLastError();
 }
 
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         bool to16, const int* hole, hipStream_t st, unsigned* maxima) {
+                         bool to16, const int* hole, hipStream_t st) {
     const bool vec = d.D % 4 == 0 && (uintptr_t)G % (dtype == SAGE_BF16 ? 8 : 16) == 0;
-#define SAGE_INSERT(T, V) launch_insert_src(DenseRows<T, V>{(const T*)G}, rows, row0, half, half_rows, d, to16, hole, st, maxima)
+#define SAGE_INSERT(T, V) launch_insert_src(DenseRows<T, V>{(const T*)G}, rows, row0, half, half_rows, d, to16, hole, st)
     if (dtype == SAGE_BF16) return vec ? SAGE_INSERT(uint16_t, true) : SAGE_INSERT(uint16_t, false);
     return vec ? SAGE_INSERT(float, true) : SAGE_INSERT(float, false);
 #undef SAGE_INSERT
@@ -324,13 +306,12 @@ struct OuterRows {
 };
 
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, bool to16, const int* hole, hipStream_t st,
-                               unsigned* maxima) {
+                               float* half, int half_rows, const Dims& d, bool to16, const int* hole, hipStream_t st) {
     if (dtype == SAGE_BF16)
         return launch_insert_src(OuterRows<uint16_t>{(const uint16_t*)E, (const uint16_t*)H, C, dh}, rows, row0, half,
-                                 half_rows, d, to16, hole, st, maxima);
+                                 half_rows, d, to16, hole, st);
     return launch_insert_src(OuterRows<float>{(const float*)E, (const float*)H, C, dh}, rows, row0, half, half_rows, d, false,
-                             hole, st, maxima);
+                             hole, st);
 }
 
 // The same rows written out row-major in their own type (for shapes the factored projection does not take).

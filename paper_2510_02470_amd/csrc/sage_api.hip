@@ -63,8 +63,6 @@ struct sage_ctx {
     hipEvent_t ev_mark = nullptr;                // context stream: the Gram matrix of the current cycle is complete
     hipEvent_t ev_side[2] = {nullptr, nullptr};  // side stream: rows stored in nw[i] and their Gram block formed
     int* side_hole = nullptr;                    // the place its launches leave out (spare_unit_at)
-    unsigned* row_max = nullptr;                 // 2 LP: bits of the largest magnitude in each row that it stored in nw[i]
-    bool row_max_known[2] = {false, false};      // the rows of nw[i] are those, of an fp32 stream
     bool pending_shrink = false;   // the buffer is full, its shrink waits for the next update call (see sage_fd_update)
     bool pre_stored = false;       // the side stream has stored the next ell rows of the running call in nw[cur]
     bool new_block_ready = false;  // ... and their Gram block is (or will be, see ev_side) in gram_partial_new[cur]
@@ -290,10 +288,9 @@ struct RowSrc {
 };
 
 hipError_t insert_rows(const RowSrc& s, int64_t rows, int row0, float* half, int half_rows, const Dims& d, bool to16,
-                       hipStream_t st, const int* hole = nullptr, unsigned* maxima = nullptr) {
-    if (s.outer())
-        return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, to16, hole, st, maxima);
-    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, to16, hole, st, maxima);
+                       hipStream_t st, const int* hole = nullptr) {
+    if (s.outer()) return launch_insert_outer(s.E, s.H, s.dtype, s.C, s.dh, rows, row0, half, half_rows, d, to16, hole, st);
+    return launch_insert(s.G, s.dtype, rows, row0, half, half_rows, d, to16, hole, st);
 }
 
 // Before the top half is read while the stream has not filled it yet: its other rows count as zero.
@@ -521,18 +518,9 @@ int side_ahead(sage_ctx* c, const RowSrc* next) {
     if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
     int* const hole = c->ew.period == 8 ? c->side_hole : nullptr;
     if (hole) HIPCHK(launch_xcd_place(c->ew.xcd, hole, c->st2));
-    const bool split = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0;
-    // Rows of fp32 in two fp16 parts from 131,072 columns on, where that is at least as exact as three bf16 parts (figures at
-    // gram_cross8_split_kernel). Rows of bf16 are exact in one bf16 part.
-    c->row_max_known[o] = split && !c->nw_bf16[o] && c->d.D >= 131072;
-    GramScale scale;
-    unsigned* const maxima = c->row_max_known[o] ? c->row_max + (size_t)o * LP : nullptr;
-    if (maxima) HIPCHK(launch_clear_words(maxima, LP, c->st2));
-    scale.maxima = maxima;
-    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, hole, maxima));
-    c->gp_side_used[o] = split ? &c->gp_new_split : &c->gp_new;
-    HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), hole,
-                       scale));
+    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, hole));
+    c->gp_side_used[o] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
+    HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), hole));
     HIPCHK(hipEventRecord(c->ev_side[o], c->st2));
     return SAGE_OK;
 }
@@ -554,9 +542,7 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
                                     new_one(c, c->cur)));
         }
         const GramPlan& gc = split && c->gp_cross_split.tiles > 0 ? c->gp_cross_split : c->gp_cross;
-        GramScale scale;
-        if (c->new_block_ready && c->row_max_known[c->cur]) scale = GramScale{c->ew.known, c->row_max + (size_t)c->cur * LP};
-        RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial, gc, c->d, c->st, new_one(c, c->cur), nullptr, scale));
+        RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial, gc, c->d, c->st, new_one(c, c->cur)));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gc, c->gram_partial_new[c->cur], gn, c->ew.C, true,
                                          c->ew.known, c->d, c->st, nullptr, nullptr, mark));
     } else if (!c->top_shrunk && split_grams(c)) {
@@ -808,7 +794,6 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             for (double** p : {&w.dT, &w.eT, &w.tauT, &w.known, &w.dc.dk, &w.dc.zk, &w.dc.org, &w.dc.tau, &w.dc.val, &w.dc.zh})
                 take(*p, n1);
             for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.K, &w.dc.k1, &w.dc.dense}) take(*p, n1);
-            take(c->row_max, n1);
             if (pass == 0) CALLOC(c->eig_mem, bytes);
         }
         xcd_take(c);

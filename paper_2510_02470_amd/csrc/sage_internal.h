@@ -95,12 +95,6 @@ __device__ __forceinline__ int row_exponent(double norm2, double norm2_max) {
     return 13 - ((e + 1) >> 1);
 }
 
-// The same for a row of which the largest magnitude is known (its bits): to less than 2^14.
-__device__ __forceinline__ int max_exponent(unsigned bits) {
-    const int e = bits > 0u && bits < 0x7f800000u ? 14 - __builtin_amdgcn_frexp_expf(__uint_as_float(bits)) : 0;
-    return e > 126 ? 126 : e;
-}
-
 // The upper halves of an fp32 pair as a bf16 pair: exact when both are bf16 values (rows of a bf16 stream kept as fp32).
 __device__ __forceinline__ unsigned hi_bf16(float x, float y) {
     return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
@@ -132,14 +126,11 @@ inline int64_t spare_grid_at(int64_t units, const int* hole) { return spare_grid
 // copy `rows` batch rows into rows row0.. of a half buffer (half_rows rows per slab)
 // (to16: in pieces of bf16, see half16; rows of bf16 only)
 hipError_t launch_insert(const void* G, int dtype, int64_t rows, int row0, float* half, int half_rows, const Dims& d,
-                         bool to16, const int* hole, hipStream_t st, unsigned* maxima = nullptr);
-// (maxima, for a half kept as fp32: half_rows words of zero, which receive the bits of the largest magnitude in each row)
+                         bool to16, const int* hole, hipStream_t st);
 // factored rows (E: rows x C logit errors, H: rows x dh features, both of the row type): column c*dh + t = e_c * h_t
 // rounded as a stored row would be, column C*dh + c = e_c; requires D = C * (dh + 1)
 hipError_t launch_insert_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, int row0,
-                               float* half, int half_rows, const Dims& d, bool to16, const int* hole, hipStream_t st,
-                               unsigned* maxima = nullptr);
-hipError_t launch_clear_words(unsigned* p, int n, hipStream_t st);
+                               float* half, int half_rows, const Dims& d, bool to16, const int* hole, hipStream_t st);
 hipError_t launch_widen(float* half, const Dims& d, hipStream_t st);  // pieces of bf16 -> the fp32 half
 // ... written out row-major (rows x D of the row type)
 hipError_t launch_expand_outer(const void* E, const void* H, int dtype, int64_t C, int64_t dh, int64_t rows, void* out,
@@ -170,14 +161,8 @@ GramPlan gram_plan_split(const GramPlan& base, const Dims& d, int groups);
 GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_per_cu);
 // new_one (split-arithmetic kernels): the new half is kept in pieces of bf16 (half16): one part instead of three, the result
 // has the same bits
-// scale (split-arithmetic kernels, new half kept as fp32): what is known of the rows' sizes, for the kernels in two scaled fp16
-// parts; without maxima, three bf16 parts
-struct GramScale {
-    const double* known = nullptr;     // LP squared norms of the top rows (EigWork::known); for the block new x top only
-    const unsigned* maxima = nullptr;  // LP: bits of the largest magnitude in each new row (launch_insert)
-};
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
-                       hipStream_t st, bool new_one = false, const int* hole = nullptr, const GramScale& scale = GramScale{});
+                       hipStream_t st, bool new_one = false, const int* hole = nullptr);
 // C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
 // (the Gram matrix of the rows the last shrink wrote, see EigWork::known). done: recorded when C is complete (may be null; not
 // on a stream that is captured)

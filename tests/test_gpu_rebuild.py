@@ -43,8 +43,7 @@ def test_shrink_against_64_bits(ell, D, dtype, decades):
     assert float((B.T @ B - E.T @ E).norm()) <= 1e-5 * float((A * A).sum())
 
 
-# From 131,072 columns on: Gram blocks in two scaled fp16 parts (fp32 rows, in cycles that look ahead), and the rebuild by
-# work-groups of eight waves; rows of very different and of extreme norms, zero rows, sketch sizes that fill their padding and
+# Rows of 131,072 columns and more, in cycles that look ahead, and the rebuild by work-groups of eight waves; rows of very different and of extreme norms, zero rows, sketch sizes that fill their padding and
 # do not, column counts that end inside a wave's 32.
 @pytest.mark.parametrize("ell,D,dtype", [(129, 131_071, "f32"), (129, 131_072, "f32"), (200, 131_077, "f32"), (256, 200_001, "f32"),
                                          (129, 131_072, "bf16"), (256, 131_077, "bf16")])
@@ -69,7 +68,7 @@ def test_wide_cycles_against_64_bits(ell, D, dtype, decades, factor):
     for c in range(1, 5):
         E = _shrink(torch.cat([E, G[c * ell:(c + 1) * ell].double()]), ell, torch)
     assert bool(torch.isfinite(B).all())
-    # As above: a Gram entry is good to 2^-22 (two parts) and to the fp32 sums' rounding (a few 1e-7), a rebuilt value to 2^-22.
+    # As above: a Gram entry is good to the fp32 sums' rounding (a few 1e-7), a rebuilt value to 2^-22.
     # The covariances' distance on the span of both: || B^T B - E^T E || = || J (P P^T) || with P = [B; E], J = diag(1, -1).
     P = torch.cat([B, E])
     K = P @ P.T
@@ -78,3 +77,26 @@ def test_wide_cycles_against_64_bits(ell, D, dtype, decades, factor):
     err = float(((J * K) @ (J * K)).trace().clamp(min=0).sqrt())
     assert err <= 1e-5 * float((G.double() ** 2).sum())
     s.close()
+
+
+@pytest.mark.parametrize("ell,D", [(129, 131_072), (256, 262_147)])
+def test_wide_rows_have_the_same_gram_blocks_however_the_stream_is_cut(ell, D):
+    """Rows stored ahead of their shrink and rows that are not go through the same arithmetic: with all that is not zero in 16
+    neighbouring columns, every Gram entry is one step of the matrix cores in either plan, and the sketches have the same bits."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(ell)
+    G = torch.zeros(4 * ell, D, device="cuda")
+    G[:, 65_536:65_552] = torch.randn(4 * ell, 16, generator=g, device="cuda") + 1.0
+    whole, parts = Sage(ell, D), Sage(ell, D)
+    whole.fd_update(G)                                   # looks ahead
+    for lo in range(0, 4 * ell, ell // 2):               # never does
+        parts.fd_update(G[lo:lo + ell // 2])
+    a, b = whole.sketch()[:ell], parts.sketch()[:ell]
+    # rank 16: nothing is shrunk away, the covariance is the rows'. fp32 sums of 4 ell terms after three roundings of a row.
+    want = G[:, 65_536:65_552].double()
+    want, got = want.T @ want, a[:, 65_536:65_552].double()
+    assert float((got.T @ got - want).abs().max()) <= 2e-6 * float(want.abs().max())
+    assert torch.equal(a, b)
