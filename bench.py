@@ -168,11 +168,10 @@ def run_workload(torch, inputs, Sage, w, K, W, split=True, labels_classes=None, 
     score_bytes_row = esz * D + 4.0 * k * D / w.batch + 4.0 * k
     LP = padded(ell)
     split_rebuild, split_gram = split and LP in (128, 256), split and LP == 256
-    # Gram blocks: three bf16 parts a value, 6 products; rows of a bf16 stream have one part, so 3 where such a row is one
-    # factor and 1 where both are. Rebuild: two fp16 parts, 3 products, 2 for the rows of a bf16 stream. (The products left
-    # out are exact zeros.)
+    # Rows of a bf16 stream have one bf16 part, not three: the split kernels issue 3 products (not 6) where a buffered
+    # stream row is one factor and 1 where both are (the products left out are exact zeros).
     one_part = w.dtype == "bf16"
-    rebuild_products = (3.0 + 2.0) / 2.0 if one_part else 3.0                  # top half 3, new half 2
+    rebuild_products = (6.0 + 3.0) / 2.0 if one_part else 6.0                  # top half 6, new half 3
     gram_products = (16 * 3.0 + 10 * 1.0) / 26.0 if one_part else 6.0          # 16 tiles new x top, 10 tiles new x new
     res.update({
         "K": K, "W": W, "rows": rows, "value": rows / (total_ms * 1e-3), "ms_per_step": total_ms / K,
@@ -189,10 +188,9 @@ def run_workload(torch, inputs, Sage, w, K, W, split=True, labels_classes=None, 
         "ms": {"update": ms_update, "basis": ms_basis, "score": ms_score, "select": ms_select, "wall": wall * 1e3},
         "selected": int(idx.numel()), "jacobi_sweeps_last": st.last_sweeps, "n_shrinks": int(st.n_shrinks),
         "unconverged_solves": int(st.n_unconverged),
-        "update_arithmetic": (("Gram: fp32 values as three bf16 parts, 6 bf16 MFMA products per fp32 product; rebuild: as two "
-                               "scaled fp16 parts, 3 products (fp32 accuracy)"
-                               + ("; bf16 stream rows have one part: 3 (rebuild 2) products where one factor is such a row, "
-                                  "1 where both are (same bits)" if one_part else ""))
+        "update_arithmetic": (("fp32 values as three bf16 parts, 6 bf16 MFMA products per fp32 product (fp32 accuracy)"
+                               + ("; bf16 stream rows have one part: 3 products where one factor is such a row, 1 where "
+                                  "both are (same bits)" if one_part else ""))
                               if split_rebuild else "fp32 MFMA"),
     })
     s.close()
@@ -248,8 +246,8 @@ def run_workload(torch, inputs, Sage, w, K, W, split=True, labels_classes=None, 
                 e["frac"] = rate / peak
                 e["peak"] = peak / (1e12 if bound == "mfma" else 1e9)
                 if bound == "mfma":
-                    e["executed_frac"] = rate * factor / peak   # matrix-core instructions issued (emulating fp32: x6 or x3,
-                    e["products_per_fp32_product"] = factor     # less where a factor has fewer parts)
+                    e["executed_frac"] = rate * factor / peak   # matrix-core instructions issued (emulating fp32: x6,
+                    e["products_per_fp32_product"] = factor     # less where a factor has one bf16 part)
             if traffic and name in traffic:
                 e["traffic"] = traffic[name]
             kern[name] = e
@@ -258,8 +256,8 @@ def run_workload(torch, inputs, Sage, w, K, W, split=True, labels_classes=None, 
         if g:
             fp32_equiv = rebuild_flop / (g["avg_ms"] * 1e-3)
             res["roofline"] = {
-                "kernel": ("rebuild_split_kernel (B[0:ell] <- diag(w) Y^T B on the fp16 matrix cores, whose rate is the bf16 "
-                           "ones': fp32 values as two parts, %.1f products per fp32 product; the longest single kernel of a cycle)"
+                "kernel": ("rebuild_split_kernel (B[0:ell] <- diag(w) Y^T B on the bf16 matrix cores: fp32 values as three "
+                           "bf16 parts, %.1f bf16 products per fp32 product; the longest single kernel of a cycle)"
                            % rebuild_products)
                 if split_rebuild else "rebuild_kernel (B[0:ell] <- diag(w) Y^T B, fp32 MFMA; the longest single kernel of a cycle)",
                 "bound": "mfma", "achieved": g["achieved"], "peak": g["peak"], "unit": "TFLOP/s",

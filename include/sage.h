@@ -262,16 +262,16 @@ int sage_set_projection_mode(sage_ctx* ctx, int mode);
 
 /*
  * Arithmetic of the shrink's dense products: the Gram blocks C = B B^T and the rebuild S <- Sigma' V^T = diag(w) Y^T B
- * (Method, FD paragraph; Algorithm 1, Phase I). SAGE_MM_SPLIT (default): every fp32 value is written as a sum of parts and the
- * partial products that matter run on the bf16 or fp16 matrix cores, accumulated in fp32 -- the fp32 result at a multiple of
- * the fp32 matrix-core rate. Gram blocks and the basis: three bf16 parts (24 significant bits), six products, good to a few
- * 2^-24 per term; the rebuild of a shrink: two fp16 parts of the scaled values (22 significant bits), three products, good to
- * 2^-22 per term, below what accumulating them in fp32 leaves. It is used where a kernel exists: the rebuild for ell >= 65
- * (padded sketch size 128 or 256), the Gram blocks of the steady state (new rows x top rows, new rows x new rows) and the
- * whole Gram matrix before the first shrink for ell >= 129 (padded size 256); everything else, and everything under
+ * (Method, FD paragraph; Algorithm 1, Phase I). SAGE_MM_SPLIT (default): every fp32 value is written as three bf16
+ * parts (24 significant bits) and the six partial products that matter run on the bf16 matrix cores, accumulated in
+ * fp32 -- the fp32 result to within a few 2^-24 per term, at a multiple of the fp32 matrix-core rate. It is used where
+ * a kernel exists: the rebuild for ell >= 65 (padded sketch size 128 or 256), the Gram blocks of the steady state
+ * (new rows x top rows, new rows x new rows) and the whole Gram matrix before the first shrink for ell >= 129 (padded size
+ * 256); everything else, and everything under
  * SAGE_MM_F32, runs on the fp32 matrix cores. Rows that arrive through sage_fd_update or sage_fd_update_outer in a bf16 context
- * are bf16 values: they have one part, and the split kernels leave out the products with their (zero) other parts, with the
- * same bits as the result. SAGE_MM_SPLIT_ALL_PARTS is SAGE_MM_SPLIT without that shortcut (a check that the bits are indeed
+ * are bf16 values kept as fp32: they have one part, not three, and the split kernels leave out the products with their (zero) second
+ * and third parts -- three products instead of six wherever a buffered row of the stream is a factor, with the same
+ * bits as the result. SAGE_MM_SPLIT_ALL_PARTS is SAGE_MM_SPLIT without that shortcut (a check that the bits are indeed
  * the same, and the rate fp32 rows would see). May be changed at any time between calls.
  */
 typedef enum { SAGE_MM_F32 = 0, SAGE_MM_SPLIT = 1, SAGE_MM_SPLIT_ALL_PARTS = 2 } sage_mm_mode;

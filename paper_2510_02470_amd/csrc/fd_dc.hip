@@ -630,36 +630,17 @@ __global__ __launch_bounds__(512) void dc_deflate_kernel(const double* __restric
 }
 
 // One wave per root. WYJ > 0 (the first merge of N = 64 WYJ): the row of work-groups after the last sub-problem's forms the
-// triangular factors of the reduction's blocks of reflectors, a wave each (wy_factor), and its last wave the scales that
-// the buffer rows get on the fp16 matrix cores (row_exponent; `scale`, from the diagonal of C).
+// triangular factors of the reduction's blocks of reflectors, a wave each (wy_factor).
 template <int E, int WYJ>  // m = 64 E
 __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict__ eT, int m, DcWork w,
                                                        const double* __restrict__ V, const double* __restrict__ tauT, int n,
-                                                       double* __restrict__ Tw, const double* __restrict__ C,
-                                                       float* __restrict__ scale) {
+                                                       double* __restrict__ Tw) {
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (WYJ > 0) {
-        static_assert(8 * WYJ < 128, "a wave of a row of work-groups for each block, and one more");
-        constexpr int N = 64 * WYJ;
+        static_assert(8 * WYJ <= 128, "as many waves in a row of work-groups as blocks");
         if (blockIdx.y == gridDim.y - 1) {
-            if (q == 127) {
-                double d[WYJ], m = 0.0;
-#pragma unroll
-                for (int j = 0; j < WYJ; ++j) {
-                    d[j] = C[(int64_t)(lane + 64 * j) * (N + 1)];
-                    m = fmax(m, d[j]);
-                }
-                for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-#pragma unroll
-                for (int j = 0; j < WYJ; ++j) {
-                    const int e = row_exponent(d[j], m), i = scale_index(lane + 64 * j);
-                    scale[i] = __builtin_amdgcn_ldexpf(1.f, e);
-                    scale[N + i] = __builtin_amdgcn_ldexpf(1.f, -e);
-                }
-            } else if (q * WY <= n - 2) {
-                wy_factor<WYJ>(V, tauT, q, n, lane, Tw);
-            }
+            if (q * WY <= n - 2) wy_factor<WYJ>(V, tauT, q, n, lane, Tw);
             return;
         }
     }
@@ -848,7 +829,7 @@ hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
 #define SAGE_ROOTS(E, WYJ)                                                                                              \
     do {                                                                                                                \
         hipLaunchKernelGGL((dc_roots_kernel<E, WYJ>), dim3(m / 4, WYJ > 0 ? S + 1 : S), dim3(256), 0, st, w.eT, m, w.dc, \
-                           w.V, w.tauT, n, w.Tw, w.C, w.scale);                                                         \
+                           w.V, w.tauT, n, w.Tw);                                                                       \
         hipLaunchKernelGGL(dc_weights_kernel<E>, dim3(m / 4, S), dim3(256), 0, st, m, w.dc, w.dI[cur ^ 1]);              \
     } while (0)
         if (m == 512) SAGE_ROOTS(8, 0);

@@ -158,55 +158,36 @@ hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const fl
 }
 
 
-// ---- the same product on the bf16 or fp16 matrix cores, with split values -----------------------------------------------
-// An fp32 matrix-core instruction (32x32x2) takes 64 cycles for 4096 flop, a bf16 or fp16 one (32x32x16) 32 cycles for 32768.
-// What the kernel is bound by is the power of these instructions, so it is their number that counts.
-// PARTS = 2, a shrink: both factors are scaled by powers of two into fp16's range and written as hi + lo (22 significant bits
-//   and a sign, see split2_f16); hi*hi, hi*lo, lo*hi make 16 buffer rows of a tile in 3 x 32 cycles instead of 8 x 64. The
-//   parts' errors and the product left out are 2^-24 .. 2^-22 of a term, about what rounding the sums to fp32 leaves. Buffer row
-//   i is multiplied by scale_i, which brings its norm to 2^13 at most (row_exponent; from the diagonal of the Gram
-//   matrix), and the coefficients that meet it are divided by it; each row of the coefficients has a power of two of its own,
-//   taken out again when the result is stored. What falls below fp16's range is at most 2^-39 of the row's norm.
-// PARTS = 3, a basis: x = hi + mid + lo (three bf16 parts, 24 significant bits) and the six products whose weight is at least
-//   2^-16 of the leading one (hi*hi, hi*mid, mid*hi, hi*lo, lo*hi, mid*mid; the others are below 2^-24). A shrink done this
-//   way took 2.33 ms at D = 2,049,000 (256 fp32 and 256 bf16 rows; 1.54 in two parts) and 1.43 at 1,048,576 (512 fp32 rows; 0.88).
-//   Against 64 bits over a stream's shrinks the covariance of a sketch made in two parts is as good (14 streams, sizes 100
-//   to 256: 1.56e-7 of ||A||_F^2 where three parts leave 1.67e-7) and so are its rows' products (1.42e-8, 1.50e-8); a single basis
-//   is less orthonormal in two (1.66e-7 a vector, 1.52e-7), and is made once, so it keeps the three.
-// W: waves of a work-group, see launch_rebuild_split.
+// ---- the same product on the bf16 matrix cores, three-way split ---------------------------------------------
+// An fp32 matrix-core instruction (32x32x2) takes 64 cycles for 4096 flop, a bf16 one (32x32x16) 32 cycles for 32768.
+// With x = hi + mid + lo (three bf16 parts, 24 significant bits) for both factors and the six products whose weight
+// is at least 2^-16 of the leading one (hi*hi, hi*mid, mid*hi, hi*lo, lo*hi, mid*mid; the others are below 2^-24),
+// 16 buffer rows cost 6 x 32 cycles per tile instead of 8 x 64: the fp32 result to within a few 2^-24 per term at
+// 2.7 times the rate. Accumulation is fp32 in both cases.
 //
 // Same decomposition as rebuild_kernel: a wave owns 32 columns for the whole product, its column operand comes from
 // global memory (8 rows of its k-half per stage of 16 buffer rows; k-slot (h, s) is buffer row 16*stage + 2s + h,
 // the order coeff_offset groups the coefficients in) and is split in registers; the coefficients come split
-// from the back-transformation (tri_back_kernel) in the order LDS holds them, [stage][part][h][m][8 k-slots], and are streamed
-// through a ring of three LDS buffers with direct global->LDS loads two stages ahead. The column operand is requested two
+// from the back-transformation (tri_back_kernel) in the order LDS holds them, [stage][part][h][m][8 k-slots], and streamed through a
+// ring of three LDS buffers with direct global->LDS loads two stages ahead. The column operand is requested two
 // stages ahead as well.
-// NPT > 0: the buffer has NPT rows and the new rows in use hold bf16 values; their stages take the hi part alone (the products
-// with the others would add exact zeros: a bf16 value is an fp16 one unless it is below fp16's range, and what is lost
-// there is below lo's range too). NPT = 0: any buffer, all parts. NPT = 512: the new half is kept in pieces of bf16
-// (half16); a lane loads the 4 bytes that hold its column's value and picks its half.
-template <int PARTS>
-__device__ __forceinline__ f32x16 mfma_part(u32x4 a, u32x4 b, f32x16 acc) {
-    if constexpr (PARTS == 2) return mfma_f16(a, b, acc);
-    else return mfma_bf16(a, b, acc);
-}
-template <int MT, int NPT, int PARTS, int W>
-__global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(const float* top, const float* __restrict__ nw, int nfill,
-                                                               const u32x4* __restrict__ Mc,
-                                                               const float* __restrict__ scale,
-                                                               const float* __restrict__ unscale, float* out, int NP,
+// NPT > 0: the buffer has NPT rows and the new rows in use hold bf16 values; their stages take the hi part alone and
+// three products (the other three would add exact zeros). NPT = 0: any buffer, all parts. NPT = 512: the new half is kept in
+// pieces of bf16 (half16); a lane loads the 4 bytes that hold its column's value and picks its half.
+template <int MT, int NPT>
+__global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top, const float* __restrict__ nw, int nfill,
+                                                               const u32x4* __restrict__ Mc3, float* out, int NP,
                                                                int out_NP, int64_t Dp) {
     constexpr int MP = MT * 32;
-    constexpr int STAGE16 = PARTS * 2 * MP;   // 16-byte pieces of coefficients per stage
-    constexpr int ML = STAGE16 / (64 * W);  // direct-to-LDS loads per thread and stage
-    static_assert(STAGE16 % (64 * W) == 0, "a stage must tile the work-group");
+    constexpr int STAGE16 = 3 * 2 * MP;   // 16-byte pieces of coefficients per stage
+    constexpr int ML = STAGE16 / 256;     // direct-to-LDS loads per thread and stage
+    static_assert(STAGE16 % 256 == 0, "a stage must tile the work-group");
     extern __shared__ u32x4 Ms[];         // 3 * STAGE16
-    __shared__ f32x4 sc[128];             // the scales, four buffer rows each
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, h = lane >> 5;
-    const int64_t d = ((int64_t)blockIdx.x * W + wave) * 32 + c;  // this lane's column
+    const int64_t d = ((int64_t)blockIdx.x * 4 + wave) * 32 + c;  // this lane's column
     const bool live = d < Dp;  // Dp is a multiple of 16: the last 32-column group may overhang by 16
     const int64_t dc = live ? d : Dp - 1;
     const int LP = NP >> 1;
@@ -218,8 +199,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(c
     const int nstage = (LP + (nfill + 15) / 16 * 16) / 16;  // no stage without rows in use (a basis right after a shrink: half)
     constexpr bool HALF = NPT == 512;
     const float* hcol = HALF ? reinterpret_cast<const float*>(half16(nw, LP, Dp / DC) + (dc / 8) * LP + h) + (dc % 8) / 2 : nw;
-    // lower or upper halves: of two words together (3 parts), of a word as fp32 (2 parts)
-    const unsigned pick = PARTS == 3 ? (HALF && !(dc & 1) ? 0x05040100u : 0x07060302u) : (dc & 1 ? 0x07060C0Cu : 0x05040C0Cu);
+    const unsigned pick = HALF && !(dc & 1) ? 0x05040100u : 0x07060302u;  // lower or upper halves of two words
     auto fetch_b = [&](auto from_half, int stg, float (&b)[8]) __attribute__((always_inline)) {
         const int sg = stg < nstage ? stg : nstage - 1;  // beyond the end: repeat (never used)
         const int r0 = sg * 16;
@@ -235,11 +215,11 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(c
     };
     auto fetch_m = [&](int stg, int buf) __attribute__((always_inline)) {
         const int sg = stg < nstage ? stg : nstage - 1;
-        const u32x4* src = Mc + (int64_t)sg * STAGE16 + tid;
+        const u32x4* src = Mc3 + (int64_t)sg * STAGE16 + tid;
 #pragma unroll
         for (int q = 0; q < ML; ++q)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + q * 64 * W),
-                                             (__attribute__((address_space(3))) void*)(Ms + buf * STAGE16 + q * 64 * W + wave * 64),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + q * 256),
+                                             (__attribute__((address_space(3))) void*)(Ms + buf * STAGE16 + q * 256 + wave * 64),
                                              16, 0, 0);
     };
 
@@ -253,45 +233,28 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(c
     auto stage = [&](auto one_c, auto far_half, const float (&b)[8], float (&bfar)[8], int stg, int cur) __attribute__((always_inline)) {
         constexpr bool one = decltype(one_c)::value;  // a stage of new rows with one part
         const u32x4* A = Ms + cur * STAGE16 + h * MP + c;  // + part * 2 * MP + tile * 32
-        u32x4 a[2][2][PARTS];  // [buffer][tile of the pair][part]
-        f32x4 s4[2];
-        if constexpr (PARTS == 2) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) s4[u] = sc[stg * 4 + h * 2 + u];
-        }
+        u32x4 a[2][2][3];  // [buffer][tile of the pair][part]
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int p = 0; p < PARTS; ++p) a[0][t][p] = A[p * 2 * MP + t * 32];
+            for (int p = 0; p < 3; ++p) a[0][t][p] = A[p * 2 * MP + t * 32];
         // rows of the new half that are not in use count as zero, whatever they hold
         const int r0 = stg * 16;
         const int limit = r0 >= LP ? nfill - (r0 - LP) - h : 0x7fffffff;  // 2*s < limit: row in use
-        u32x4 bp[PARTS];
+        u32x4 bh, bm, bl;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            float x = 4 * e < limit ? b[2 * e] : 0.f, y = 4 * e + 2 < limit ? b[2 * e + 1] : 0.f;
-            if constexpr (one && PARTS == 3) {
-                bp[0][e] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), pick);
-            } else if constexpr (PARTS == 3) {
+            const float x = 4 * e < limit ? b[2 * e] : 0.f, y = 4 * e + 2 < limit ? b[2 * e + 1] : 0.f;
+            if constexpr (one) {
+                bh[e] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), pick);
+                bm[e] = 0u;
+                bl[e] = 0u;
+            } else {
                 unsigned p0, p1, p2;
                 split3_bf16(x, y, p0, p1, p2);
-                bp[0][e] = p0;
-                bp[1][e] = p1;
-                bp[2][e] = p2;
-            } else {
-                const float sx = s4[e >> 1][2 * (e & 1)], sy = s4[e >> 1][2 * (e & 1) + 1];
-                if constexpr (one && HALF) {
-                    x = __uint_as_float(__builtin_amdgcn_perm(__float_as_uint(x), 0u, pick));
-                    y = __uint_as_float(__builtin_amdgcn_perm(__float_as_uint(y), 0u, pick));
-                }
-                if constexpr (one) {
-                    bp[0][e] = pack_f16(x * sx, y * sy);
-                } else {
-                    unsigned p0, p1;
-                    split2_f16(x, y, sx, sy, p0, p1);
-                    bp[0][e] = p0;
-                    bp[1][e] = p1;
-                }
+                bh[e] = p0;
+                bm[e] = p1;
+                bl[e] = p2;
             }
         }
         fetch_m(stg + 2, cur == 0 ? 2 : cur - 1);
@@ -304,24 +267,23 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(c
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int p = 0; p < PARTS; ++p) a[((i >> 1) + 1) & 1][t][p] = A[p * 2 * MP + (i + 2 + t) * 32];
+                    for (int p = 0; p < 3; ++p) a[((i >> 1) + 1) & 1][t][p] = A[p * 2 * MP + (i + 2 + t) * 32];
             }
             __builtin_amdgcn_sched_barrier(0);  // the reads go out before this pair's matrix-core instructions, not after
             const int bsel = (i >> 1) & 1;
             if constexpr (one) {
 #pragma unroll
-                for (int q = PARTS - 1; q >= 0; --q)  // smallest terms first
+                for (int q = 2; q >= 0; --q)  // smallest terms first
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) acc[i + t] = mfma_part<PARTS>(a[bsel][t][q], bp[0], acc[i + t]);
+                    for (int t = 0; t < 2; ++t) acc[i + t] = mfma_bf16(a[bsel][t][q], bh, acc[i + t]);
             } else {
-                constexpr int NQ = PARTS == 2 ? 3 : 6;
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {  // smallest terms first
-                    constexpr int PA[2][6] = {{1, 0, 0}, {2, 0, 1, 1, 0, 0}};  // part of the coefficient
-                    constexpr int PB[2][6] = {{0, 1, 0}, {0, 2, 1, 0, 1, 0}};  // part of the column operand
+                for (int q = 0; q < 6; ++q) {  // smallest terms first
+                    constexpr int PA[6] = {2, 0, 1, 1, 0, 0};  // part of the coefficient
+                    constexpr int PB[6] = {0, 2, 1, 0, 1, 0};  // part of the column operand
+                    const u32x4 bb = PB[q] == 0 ? bh : (PB[q] == 1 ? bm : bl);
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        acc[i + t] = mfma_part<PARTS>(a[bsel][t][PA[PARTS - 2][q]], bp[PB[PARTS - 2][q]], acc[i + t]);
+                    for (int t = 0; t < 2; ++t) acc[i + t] = mfma_bf16(a[bsel][t][PA[q]], bb, acc[i + t]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -338,7 +300,6 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(c
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    if (PARTS == 2 && tid < NP / 4) sc[tid] = reinterpret_cast<const f32x4*>(scale)[tid];
     // Stage s uses LDS buffer and row registers s mod 3 (+ a fixed offset, below).
     float b0[8], b1[8], b2[8];
     constexpr std::false_type all_parts{};
@@ -400,49 +361,37 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void rebuild_split_kernel(c
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int r = m * 32 + 8 * q + 4 * h;
-            const f32x4 u = PARTS == 2 ? *reinterpret_cast<const f32x4*>(unscale + r) : f32x4{1.f, 1.f, 1.f, 1.f};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) out[out_base + (int64_t)(r + i) * DC] = acc[m][4 * q + i] * u[i];
+        for (int i = 0; i < 16; ++i) {
+            int r = m * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+            out[out_base + (int64_t)r * DC] = acc[m][i];
         }
 }
 
-bool rebuild_split_ok(int MP, int parts) { return MP == 128 || (MP == 256 && parts == 2); }
+bool rebuild_split_ok(int MP) { return MP == 128 || MP == 256; }
 
-size_t rebuild_split_bytes(const Dims& d, int MP, int parts) { return (size_t)(d.NP / 16) * parts * 2 * MP * 16; }
+size_t rebuild_split_bytes(const Dims& d, int MP) { return (size_t)(d.NP / 16) * 3 * 2 * MP * 16; }
 
-hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Msplit, int parts, const float* scale,
-                                const float* unscale, float* out, int out_NP, int MP, const Dims& d, hipStream_t st,
-                                bool new_one) {
+template <int MT, int NPT>
+static hipError_t launch_rebuild_split_t(const float* top, const float* nw, int nfill, const void* Mc3, float* out,
+                                         int out_NP, const Dims& d, hipStream_t st) {
+    constexpr int MP = MT * 32;
+    constexpr size_t LDS = (size_t)3 * 3 * 2 * MP * 16;
+    if (hipError_t ea = ensure_dynamic_lds((const void*)rebuild_split_kernel<MT, NPT>, (int)LDS); ea != hipSuccess)
+        return ea;
+    dim3 grid((unsigned)((d.Dp + 127) / 128));
+    hipLaunchKernelGGL((rebuild_split_kernel<MT, NPT>), grid, dim3(256), LDS, st, top, nw, nfill, (const u32x4*)Mc3, out,
+                       d.NP, out_NP, d.Dp);
+    return hipGetLastError();
+}
+
+hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
+                                const Dims& d, hipStream_t st, bool new_one) {
     if (nfill == 0) new_one = false;  // (no stages of the new half)
-    auto launch = [&](auto kernel, int W) {
-        const size_t lds = (size_t)3 * parts * 2 * MP * 16;
-        if (hipError_t e = ensure_dynamic_lds((const void*)kernel, (int)lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((d.Dp + 32 * W - 1) / (32 * W))), dim3(64 * W), lds, st, top, nw, nfill,
-                           (const u32x4*)Msplit, scale, unscale, out, d.NP, out_NP, d.Dp);
-        return hipGetLastError();
-    };
-    if (MP == 256 && parts == 2) {
-        // Eight waves to a work-group where that leaves two for each of 256 CUs: the two work-groups of four that share a CU both
-        // load all coefficients, at nearly the same time, and the vector cache makes one wait for the other's lines. 256 fp32
-        // and 256 bf16 rows of 2,049,000 columns: 1.61 ms with four, 1.54 with eight; 512 fp32 rows of 1,048,576: 0.89, 0.88.
-        if (d.D >= 131072) {
-            if (new_one && d.NP == 512) return launch(rebuild_split_kernel<8, 512, 2, 8>, 8);
-            return launch(rebuild_split_kernel<8, 0, 2, 8>, 8);
-        }
-        if (new_one && d.NP == 512) return launch(rebuild_split_kernel<8, 512, 2, 4>, 4);
-        return launch(rebuild_split_kernel<8, 0, 2, 4>, 4);
-    }
-    if (MP == 128 && parts == 2 && d.NP == 256) {  // (the shrink of 128 rows)
-        if (new_one) return launch(rebuild_split_kernel<4, 256, 2, 4>, 4);
-        return launch(rebuild_split_kernel<4, 0, 2, 4>, 4);
-    }
-    if (MP == 128 && parts == 3) {
-        if (new_one && d.NP == 512) return launch(rebuild_split_kernel<4, 512, 3, 4>, 4);
-        if (new_one && d.NP == 256) return launch(rebuild_split_kernel<4, 256, 3, 4>, 4);
-        return launch(rebuild_split_kernel<4, 0, 3, 4>, 4);
-    }
+    if (MP == 256 && new_one && d.NP == 512) return launch_rebuild_split_t<8, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 256) return launch_rebuild_split_t<8, 0>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 128 && new_one && d.NP == 512) return launch_rebuild_split_t<4, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 128 && new_one && d.NP == 256) return launch_rebuild_split_t<4, 256>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (MP == 128) return launch_rebuild_split_t<4, 0>(top, nw, nfill, Mc3, out, out_NP, d, st);
     return hipErrorInvalidValue;
 }
 

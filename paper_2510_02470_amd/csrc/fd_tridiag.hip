@@ -757,36 +757,33 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
 //   mode 2, weighted basis: f_m = sqrt(max(lambda_m - delta, 0) / lambda_m) under the same rank test, which makes the row the
 //           m-th of the sketch a shrink of the buffer would write ("Two-pass scoring": z = S g).
 // A lane makes the 8 coefficients (stage, k-half h, row m) that a matrix-core lane of the rebuild takes per stage of 16
-// buffer rows: buffer rows 16 * stage + 2 s + h, s < 8. OUT_F32: in coeff_offset order. OUT_BF16: as three bf16 parts in the
-// order rebuild_split_kernel streams them. OUT_F16: as two fp16 parts in that order, divided by the scale of the buffer row
-// they meet and times a power of two that brings the largest of the row to 2^13 .. 2^14 (its inverse goes to `unscale`).
-// The work-group after the last row does the scalars.
-enum { OUT_Y, OUT_F32, OUT_F16, OUT_BF16 };
+// buffer rows: buffer rows 16 * stage + 2 s + h, s < 8. OUT_SPLIT: as three bf16 parts in the order rebuild_split_kernel
+// streams them; OUT_F32: in coeff_offset order. The work-group after the last row does the scalars.
+enum { OUT_Y, OUT_F32, OUT_SPLIT };
 struct Coeffs8 {
     float c[8];
 };
 template <int OUT>
 __device__ __forceinline__ void store_coeffs(const CoeffArgs& cf, int stg, int h, int m, const Coeffs8& v) {
-    if constexpr (OUT == OUT_F32) {
+    if constexpr (OUT == OUT_SPLIT) {
+        u32x4 hi, mid, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            unsigned a, b, c;
+            split3_bf16(v.c[2 * e], v.c[2 * e + 1], a, b, c);
+            hi[e] = a;
+            mid[e] = b;
+            lo[e] = c;
+        }
+        u32x4* dst = (u32x4*)cf.Mc3 + (int64_t)stg * (3 * 2 * cf.MP) + h * cf.MP + m;
+        dst[0] = hi;
+        dst[2 * cf.MP] = mid;
+        dst[4 * cf.MP] = lo;
+    } else {
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             *reinterpret_cast<f32x4*>(cf.Mt + coeff_offset(stg * 16 + h + 8 * q, m, cf.MP)) =
                 f32x4{v.c[4 * q], v.c[4 * q + 1], v.c[4 * q + 2], v.c[4 * q + 3]};
-    } else {
-        constexpr int PARTS = OUT == OUT_F16 ? 2 : 3;
-        u32x4 part[3];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            unsigned a, b, c = 0u;
-            if constexpr (OUT == OUT_F16) split2_f16(v.c[2 * e], v.c[2 * e + 1], 1.f, 1.f, a, b);
-            else split3_bf16(v.c[2 * e], v.c[2 * e + 1], a, b, c);
-            part[0][e] = a;
-            part[1][e] = b;
-            part[2][e] = c;
-        }
-        u32x4* dst = (u32x4*)cf.Msplit + (int64_t)stg * (PARTS * 2 * cf.MP) + h * cf.MP + m;
-#pragma unroll
-        for (int q = 0; q < PARTS; ++q) dst[q * 2 * cf.MP] = part[q];
     }
 }
 template <int J, int OUT>
@@ -794,8 +791,7 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
                                                          const double* __restrict__ Tw, int m0, int LP, int n,
                                                          double* __restrict__ Yt, int NP, CoeffArgs cf,
                                                          const double* __restrict__ dv, const double* __restrict__ C,
-                                                         double* __restrict__ stat, double* __restrict__ known,
-                                                         const float* __restrict__ scale, float* __restrict__ unscale) {
+                                                         double* __restrict__ stat, double* __restrict__ known) {
     constexpr int N = 64 * J, NQ = J >= 4 ? J / 2 : 1, QS = J / NQ, QB = N / WY / NQ;  // parts; registers, blocks of a part
     const int lane = threadIdx.x;
     const int rank = blockIdx.x, col = N - 1 - rank;
@@ -834,7 +830,6 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
         }
         if (f == 0.0) {  // a zero row
             if (lane < 8 * J) store_coeffs<OUT>(cf, lane >> 1, lane & 1, rank, {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f});
-            if (OUT == OUT_F16 && lane == 0) unscale[rank] = 1.f;
             return;
         }
     }
@@ -957,23 +952,8 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
 #pragma unroll
         for (int j = 0; j < J; ++j) y[place(row(j))] = z[j];
         __syncthreads();
-        const int stg = lane >> 1, h = lane & 1;
-        if constexpr (OUT == OUT_F16) {
-            const float* inv = scale + N + 8 * lane;
-            double g[8], m = 0.0;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                g[s] = lane < 8 * J ? f * y[stg * 16 + h + 2 * s] * (double)inv[s] : 0.0;
-                m = fmax(m, fabs(g[s]));
-            }
-            for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-            const int t = m > 1e-30 && m < 1e60 ? 14 - __builtin_amdgcn_frexp_exp(m) : 0;
-            Coeffs8 v;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) v.c[s] = (float)__builtin_amdgcn_ldexp(g[s], t);
-            if (lane < 8 * J) store_coeffs<OUT>(cf, stg, h, rank, v);
-            if (lane == 0) unscale[rank] = __builtin_amdgcn_ldexpf(1.f, -t);
-        } else if (lane < 8 * J) {
+        if (lane < 8 * J) {
+            const int stg = lane >> 1, h = lane & 1;
             Coeffs8 v;
 #pragma unroll
             for (int s = 0; s < 8; ++s) v.c[s] = (float)(f * y[stg * 16 + h + 2 * s]);
@@ -1052,11 +1032,10 @@ hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, c
     const CoeffArgs args = cf ? *cf : CoeffArgs{};
 #define SAGE_BACK(J, OUT)                                                                                                 \
     hipLaunchKernelGGL((tri_back_kernel<J, OUT>), dim3(OUT == OUT_Y ? count : args.MP + 1), dim3(64), 0, st,               \
-                       w.Z[dc_result(NP)], w.V, w.Tw, m0, LP, n, w.Yt, NP, args, dv, w.C, w.stat, w.known, w.scale, w.unscale)
+                       w.Z[dc_result(NP)], w.V, w.Tw, m0, LP, n, w.Yt, NP, args, dv, w.C, w.stat, w.known)
 #define SAGE_BACK_J(J)                        \
     if (!cf) SAGE_BACK(J, OUT_Y);             \
-    else if (args.Msplit && args.parts == 2) SAGE_BACK(J, OUT_F16); \
-    else if (args.Msplit) SAGE_BACK(J, OUT_BF16); \
+    else if (args.Mc3) SAGE_BACK(J, OUT_SPLIT); \
     else SAGE_BACK(J, OUT_F32);               \
     break
     switch (NP / 64) {

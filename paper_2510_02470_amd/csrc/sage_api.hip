@@ -80,7 +80,7 @@ struct sage_ctx {
     EigWork ew{};
     char* eig_mem = nullptr;  // what ew points into
     float* Mt = nullptr;
-    void* Msplit = nullptr;   // the rebuild's coefficients split into bf16 parts (SAGE_MM_SPLIT)
+    void* Mt3 = nullptr;   // the rebuild's coefficients split into bf16 parts (SAGE_MM_SPLIT)
     int mm_mode = SAGE_MM_SPLIT;
     // Rows of a bf16 stream are kept as fp32 but have one bf16 part, not three: the split-arithmetic kernels then skip
     // the products with the new rows' mid and lo parts (exact zeros; same bits). nw_bf16[i]: every row in use in nw[i]
@@ -323,7 +323,7 @@ HostSignal next_signal(sage_ctx* c) {
 // Rows of `s` are about to be stored in nw[i] from row row0 on (by the context stream unless row0 = 0).
 int note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
     const bool b = s.dtype == SAGE_BF16;  // factored rows of a bf16 context are rounded to bf16 when they are stored
-    if (row0 == 0) c->nw_half[i] = b && c->d.NP == 512 && c->one_part && split_grams(c) && c->Msplit;
+    if (row0 == 0) c->nw_half[i] = b && c->d.NP == 512 && c->one_part && split_grams(c) && c->Mt3;
     else if (!b)
         if (int rc = widen(c, i); rc != SAGE_OK) return rc;
     c->nw_bf16[i] = row0 == 0 ? b : (c->nw_bf16[i] && b);
@@ -562,12 +562,12 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
         int rc = side_ahead(c, next);
         if (rc != SAGE_OK) return rc;
     }
-    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Msplit;
+    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3;
     const CoeffArgs cf{LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new, c->Mt,
-                       split_rb ? c->Msplit : nullptr, 2, c->acc};  // (row ell - 1 of the result is zero)
+                       split_rb ? c->Mt3 : nullptr, c->acc};  // (row ell - 1 of the result is zero)
     RUN(K_EIG, eigensolve(c, ell, 2 * ell, cf.count, &cf));
     if (split_rb)
-        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], ell, c->Msplit, 2, c->ew.scale, c->ew.unscale, c->top, LP, LP, c->d, c->st,
+        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], ell, c->Mt3, c->top, LP, LP, c->d, c->st,
                                             new_one(c, c->cur)));
     else
         RUN(K_REBUILD, launch_rebuild(c->top, c->nw[c->cur], ell, c->Mt, c->top, LP, LP, c->d, c->st));
@@ -789,8 +789,6 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             take(w.Tw, 8 * n1);
             for (int i = 0; i < 2; ++i) take(w.Z[i], n2);
             for (int i = 0; i < 2; ++i) take(w.dI[i], n1);
-            take(w.scale, 2 * n1);
-            take(w.unscale, n1);
             for (double** p : {&w.dT, &w.eT, &w.tauT, &w.known, &w.dc.dk, &w.dc.zk, &w.dc.org, &w.dc.tau, &w.dc.val, &w.dc.zh})
                 take(*p, n1);
             for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.K, &w.dc.k1, &w.dc.dense}) take(*p, n1);
@@ -799,10 +797,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
         xcd_take(c);
     }
     CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
-    if (rebuild_split_ok(c->d.LP, 2)) {
-        const size_t shrinks = rebuild_split_bytes(c->d, c->d.LP, 2), bases = rebuild_split_bytes(c->d, 128, 3);
-        CALLOC(c->Msplit, shrinks > bases ? shrinks : bases);
-    }
+    if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
     CALLOC(c->acc, 8 * sizeof(double));
     c->ew.redone = c->acc + 4;
     c->ew.claim = (unsigned*)(c->ew.stat + 16);
@@ -826,7 +821,7 @@ void sage_destroy(sage_ctx* c) {
     if (c->st2) (void)hipStreamSynchronize(c->st2);
     void* ptrs[] = {c->top,     c->nw[0],    c->nw[1],  c->gram_partial, c->gram_partial_new[0], c->gram_partial_new[1],
                     c->eig_mem, c->Mt,       c->acc,    c->Vblk,         c->img[0].mem, c->img[1].mem,
-                    c->zhat,    c->proj_partial, c->cons_partial, c->ssum, c->alpha, c->labels, c->cb_work, c->stage, c->Msplit, c->dbg_count};
+                    c->zhat,    c->proj_partial, c->cons_partial, c->ssum, c->alpha, c->labels, c->cb_work, c->stage, c->Mt3, c->dbg_count};
     for (void* p : ptrs) dev_free(c->mem, p);
     xcd_release(c);
     kit_give(c->device, c->kit, !c->poisoned);
@@ -964,15 +959,15 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     if (rc != SAGE_OK) return rc;
     rc = ensure_vblk(c, KP);
     if (rc != SAGE_OK) return rc;
-    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Msplit && rebuild_split_ok(KP, 3) && KP <= c->d.LP;
+    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3 && rebuild_split_ok(KP) && KP <= c->d.LP;
     const CoeffArgs cf{KP, k, weighted ? 2 : 1, c->d.n, c->d.ell, c->cnt_top, c->fill_top, c->d.LP + c->cnt_new,
-                       c->d.LP + c->fill_new, c->Mt, split_rb ? c->Msplit : nullptr, 3, c->acc};
+                       c->d.LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc};
     rc = decompose(c, cf);
     if (rc != SAGE_OK) return rc;
     c->cnt_top = c->fill_top;
     c->cnt_new = c->fill_new;
     if (split_rb)
-        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], c->fill_new, c->Msplit, 3, c->ew.scale, c->ew.unscale, c->Vblk, KP, KP, c->d, c->st,
+        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], c->fill_new, c->Mt3, c->Vblk, KP, KP, c->d, c->st,
                                             c->fill_new > 0 && new_one(c, c->cur)));
     else {
         if (c->fill_new > 0)

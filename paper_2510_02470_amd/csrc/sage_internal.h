@@ -67,34 +67,6 @@ __device__ __forceinline__ void split3_bf16(float x, float y, unsigned& hi, unsi
     lo = pack_bf16(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xffff0000u));
 }
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-// v_mfma_f32_32x32x16_f16: the lanes hold what they hold in mfma_bf16.
-__device__ __forceinline__ f32x16 mfma_f16(u32x4 a, u32x4 b, f32x16 acc) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), acc, 0, 0, 0);
-}
-__device__ __forceinline__ unsigned pack_f16(float x, float y) {
-    const f16x2 h = {(_Float16)x, (_Float16)y};  // round to nearest even (v_cvt_pk_f16_f32)
-    return __builtin_bit_cast(unsigned, h);
-}
-// s x and t y (s, t powers of two) as two fp16 pairs hi + lo, each the nearest fp16 of what is left: 22 significant bits or
-// more where the value is at least 2^-3 (|error| <= 2^-23 |value|), an error of at most 2^-25 below.
-__device__ __forceinline__ void split2_f16(float x, float y, float s, float t, unsigned& hi, unsigned& lo) {
-    hi = pack_f16(x * s, y * t);
-    asm("" : "+v"(hi));  // (one conversion of the pair, from which the rest is formed; else each half is converted twice)
-    const f16x2 h = __builtin_bit_cast(f16x2, hi);
-    lo = pack_f16(__builtin_fmaf(x, s, -(float)h[0]), __builtin_fmaf(y, t, -(float)h[1]));
-}
-// The power of two that takes a row of squared norm norm2 to a norm of at most 2^13, as an exponent: its elements then lie
-// within fp16's range with a factor of eight to spare. A row far below the largest of the buffer (norm2_max) is taken for one
-// of 2^-14 of its norm: what rounding left of a row may be larger than its norm is known to be, and is not larger than that.
-__device__ __forceinline__ int row_exponent(double norm2, double norm2_max) {
-    const double v = fmax(norm2, norm2_max * 3.7252902984619140625e-09);
-    const int e = v > 1e-60 && v < 1e60 ? __builtin_amdgcn_frexp_exp(v) : 0;  // v < 2^e
-    return 13 - ((e + 1) >> 1);
-}
-
 // The upper halves of an fp32 pair as a bf16 pair: exact when both are bf16 values (rows of a bf16 stream kept as fp32).
 __device__ __forceinline__ unsigned hi_bf16(float x, float y) {
     return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
@@ -190,9 +162,6 @@ struct EigWork {
     double* redone; // solves whose reduction one work-group repeated because the others were not there in time
     unsigned* claim; // [0] zero before and after a reduction (TriClaim), [1] set when the solve is given up
     bool impatient; // test hook: its work-groups wait for each other for one poll only
-    float* scale;   // NP, then their inverses: the power of two each buffer row is multiplied by for the fp16 matrix cores
-                    // (row_exponent of C's diagonal), in the order of scale_index
-    float* unscale; // LP: inverse of the power of two each row of the split coefficients holds
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
     double* xch;    // exchange of the reduction (NP = 128, 256, 512): 4 slots of q and c, NP each; empty (all ones) before it
     int xcd;        // the XCD the reduction runs on (NP = 128, 256, 512)
@@ -207,14 +176,13 @@ hipError_t launch_xcd_place(int xcd, int* place, hipStream_t st);  // *place: 0 
 const XcdMap& xcd_map();  // of the launches on some stream of the current device; asked once per device
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
-// Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Msplit (in
-// 2 fp16 or 3 bf16 parts) if given, else into Mt. Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1)
+// Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Mc3 (split
+// parts) if given, else into Mt. Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1)
 // and [rb0, rb1), the rows not yet counted), acc[2] last_delta. (acc[4]: EigWork::redone)
 struct CoeffArgs {
     int MP, count, mode, n, ell, ra0, ra1, rb0, rb1;
     float* Mt;
-    void* Msplit;
-    int parts;
+    void* Mc3;
     double* acc;
 };
 // the `count` leading eigenvectors into Yt, or (cf given) only the coefficients made from them
@@ -232,23 +200,19 @@ __host__ __device__ inline int64_t coeff_offset(int i, int m, int MP) {
     return (int64_t)(i >> 4) * 16 * MP + ((h * MP + m) * 2 + piece) * 4 + (s & 3);
 }
 
-// Where the scale of buffer row i is kept: the eight rows of a stage of 16 that a lane takes are neighbours.
-__host__ __device__ inline int scale_index(int i) { return (i & ~15) | (i & 1) << 3 | (i & 15) >> 1; }
-
 // fd_rebuild.hip: out[0:MP] = M * B over every column, B = [top; first nfill rows of nw; zeros]; Mc holds the NP x MP
 // coefficients in coeff_offset order; out has out_NP rows per slab and may be `top` itself (in place).
 hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const float* Mc, float* out, int out_NP, int MP,
                           const Dims& d, hipStream_t st);
-// The same product on the bf16 or fp16 matrix cores with both factors split, in `parts` parts: 2 (fp16, scaled; three
-// products) or 3 (bf16; six products). Msplit: the split coefficients, rebuild_split_bytes(d, MP, parts) bytes; scale, unscale:
-// see EigWork. Only for MP = 128 or 256 (2 parts), MP = 128 (3 parts).
-bool rebuild_split_ok(int MP, int parts);
-size_t rebuild_split_bytes(const Dims& d, int MP, int parts);
-// new_one: every new row in use holds bf16 values (its other parts are zero and left out, the result has the same bits); at
-// NP = 512 the new half is then kept in pieces of bf16.
-hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Msplit, int parts, const float* scale,
-                                const float* unscale, float* out, int out_NP, int MP, const Dims& d, hipStream_t st,
-                                bool new_one = false);
+// The same product on the bf16 matrix cores with both factors split into three bf16 parts (six products: 24-bit
+// accuracy at 2.7 times the fp32 matrix-core rate). Mc3: the split coefficients, rebuild_split_bytes(d, MP) bytes. Only for
+// MP = 128 or 256 (rebuild_split_ok).
+bool rebuild_split_ok(int MP);
+size_t rebuild_split_bytes(const Dims& d, int MP);
+// new_one: every new row in use holds bf16 values (three products instead of six for the new half, the same bits); at NP = 512
+// the new half is then kept in pieces of bf16.
+hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
+                                const Dims& d, hipStream_t st, bool new_one = false);
 
 // score.hip
 struct ScorePlan {
