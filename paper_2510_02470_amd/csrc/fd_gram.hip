@@ -1010,8 +1010,7 @@ hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const f
         sa.groups >= 64 ? gram_reduce_kernel<8> : gram_reduce_kernel<1>;
     const dim3 grid(P * (P + 1) / 2, sa.groups >= 64 ? 128 : 16);
     // `done` rides on the launch's own completion: recorded after it, it is a packet of its own, and the reduction that follows
-    // started 6.7 us later, 5.0 without its fence towards the host (4096 rows of 5130 at sketch size 64: 12.88 ms, 12.76
-    // without the fence, 12.69 without the packet).
+    // started 6.7 us later (4096 rows of 5130 at sketch size 64: 12.88 ms with the packet, 12.70 without).
     if (done)
         hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, st, nullptr, done, 0, sa, sb, stop, C, d.NP, known_top ? 1 : 0, known);
     else

@@ -370,9 +370,10 @@ bool kit_take(int device, SideKit& k) {
     }
     k = SideKit{};
     bool ok = hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking) == hipSuccess;
-    // (no fence towards the host: what the events order is read by this device alone)
+    // These order data between streams (the caller's rows; rows and partial sums of the side stream) on a chip with an L2
+    // per XCD: they keep the release that a recorded event has. (hipEventDisableSystemFence is for events that only time.)
     for (hipEvent_t* e : {&k.mark, &k.side[0], &k.side[1]})
-        ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
+        ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&k.host, KIT_WORDS * sizeof(int), hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();

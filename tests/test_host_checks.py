@@ -40,3 +40,11 @@ def test_slots_of_the_reduction_are_emptied_in_time(tmp_path):
     r = _run(exe)
     assert r.returncode == 0 and "tri_slot_check ok" in r.stdout, r.stdout
     assert _run(exe, "planted").returncode == 1
+
+
+def test_events_that_order_streams_release_what_they_order():
+    """No run shows a missing release reliably, so the flag is looked for: hipEventDisableSystemFence takes the release away that
+    lets a stream see what was written, on another XCD, before the event."""
+    made = [(name, line) for name in sorted(os.listdir(CSRC)) if name.endswith((".hip", ".h"))
+            for line in open(os.path.join(CSRC, name)) if "hipEventCreateWithFlags" in line or "hipEventRecordWithFlags" in line]
+    assert made and not [m for m in made if "DisableSystemFence" in m[1]]
