@@ -36,15 +36,6 @@ __device__ __forceinline__ double dc_tolerance(const double* __restrict__ dT, co
     return 4.0 * DC_EPS * m;
 }
 
-// sqrt(x) for x >= 0 to about one unit in the last place (hardware estimate, two Newton steps)
-__device__ __forceinline__ double sqrt64(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
-    double r = x * y;
-    r = __builtin_fma(__builtin_fma(-r, r, x), 0.5 * y, r);
-    return x > 1e-290 ? r : 0.0;
-}
-
 // Root q of f = 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending): lambda = org + tau with org the
 // nearer of the poles around it. A group of L lanes works on a root; lane l holds the poles l + L e, e < E (z = 0 and
 // d = 1e30 beyond K). on: this group has a root (all lanes take part in the loop). The interpolation, which matches f, f' and
@@ -133,7 +124,7 @@ __device__ __forceinline__ double secular_z(int K, int j, int l, double dj, cons
         pr *= i < K ? f : 1.0;
     }
     pr = lane_product<L>(pr);
-    return sqrt64(fabs(pr));
+    return __builtin_sqrt(fabs(pr));
 }
 
 // Two neighbouring surviving poles (d0, z0), (d1, z1): is their coupling below tol after the rotation that zeroes z0?
@@ -362,7 +353,7 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
             nn = __builtin_fma(u[e], u[e], nn);
         }
         nn = lane_sum<8>(nn);
-        nn = rcp64(sqrt64(nn));
+        nn = rcp64(__builtin_sqrt(nn));
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int j = l + 8 * e;
@@ -456,10 +447,12 @@ __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const do
         const double a = finite_or_zero(dT[g0]) - (g0 > 0 ? fabs(finite_or_zero(eT[g0 - 1])) : 0.0);
         const double c = finite_or_zero(dT[g0 + 1]) - fabs(finite_or_zero(eT[g0 + 1]));
         const double b = finite_or_zero(eT[g0]);
-        const bool coupled = fabs(b) > 1e-290;  // (of a matrix of order one)
-        const double z = (c - a) * rcp64(coupled ? 2.0 * b : 1.0), za = fmin(fabs(z), 1e100);
-        const double t = coupled ? __builtin_copysign(rcp64(za + sqrt64(__builtin_fma(za, za, 1.0))), z) : 0.0;
-        const double cc = rcp64(sqrt64(__builtin_fma(t, t, 1.0))), ss = t * cc;
+        double t = 0.0;
+        if (b != 0.0) {
+            const double z = (c - a) / (2.0 * b);
+            t = __builtin_copysign(1.0, z) / (fabs(z) + __builtin_sqrt(1.0 + z * z));
+        }
+        const double cc = 1.0 / __builtin_sqrt(1.0 + t * t), ss = t * cc;
         const double l1 = a - t * b, l2 = c + t * b;  // vectors (cc, -ss) and (ss, cc)
         const bool first = ((i & 1) == 0) == (l1 <= l2);  // this index takes l1
         S.d[i] = first ? l1 : l2;
@@ -762,7 +755,7 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(const double* __restric
                 n1 = __builtin_fma(u1, u1, n1);
             }
             const double nn = lane_sum<8>(n0 + n1);
-            if (l == 0) inv[c] = nn > 0.0 ? rcp64(sqrt64(nn)) : 0.0;
+            if (l == 0) inv[c] = nn > 0.0 ? rcp64(__builtin_sqrt(nn)) : 0.0;
         }
         const int l16 = lane & 15, lk = lane >> 4, bc = tid & 31;
         f64x4 acc[2] = {f64x4{0.0, 0.0, 0.0, 0.0}, f64x4{0.0, 0.0, 0.0, 0.0}};
