@@ -302,7 +302,7 @@ int sage_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* 
 /*
  * sage_topm for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc. Same arguments and result as sage_topm, but the work space (histograms, the
- * select state, two counters and a table per block of 4096 keys, 8.4 MB in all) is a fixed array inside the library, one copy
+ * select state, two counters and a table per block of keys, 2.1 MB in all) is a fixed array inside the library, one copy
  * per GPU, held until the process ends; the call allocates and frees nothing and does not wait: the work is enqueued
  * on hip_stream and out_idx is complete when that stream reaches the end of it. N > SAGE_TOPM_STATIC_MAX_N gives
  * SAGE_ERR_CAPACITY. All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two

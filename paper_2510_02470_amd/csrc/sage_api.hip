@@ -667,10 +667,7 @@ int64_t keep_count(double keep_rate, int64_t N) {
 }
 
 // one allocation: histograms, state, counters and tables
-int64_t select_blocks(int64_t N) { return N > 0 ? (N + SELECT_BLOCK - 1) / SELECT_BLOCK : 1; }
-size_t select_work_bytes(int64_t N) {
-    return ((size_t)TOPM_HIST_WORDS + SELECT_STATE_WORDS + (size_t)SELECT_BLOCK_WORDS * (size_t)select_blocks(N)) * sizeof(uint32_t);
-}
+size_t select_work_bytes(int64_t N) { return topm_work_words(topm_work_blocks(N)) * sizeof(uint32_t); }
 
 }  // namespace
 
@@ -1194,7 +1191,7 @@ static int ensure_alpha(sage_ctx* c, int64_t N) {
         FREE(c->sw.hist);
     }
     c->alpha = na;
-    c->sw = select_work_at((uint32_t*)work, select_blocks(ncap));
+    c->sw = select_work_at((uint32_t*)work, topm_work_blocks(ncap));
     c->alpha_cap = ncap;
     return SAGE_OK;
 }
@@ -1320,7 +1317,7 @@ int sage_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* 
     if (topm_needs_work(N)) {
         void* p = nullptr;
         if (!dev_alloc(mem, st, &p, select_work_bytes(N))) return SAGE_ERR_ALLOC;
-        w = select_work_at((uint32_t*)p, select_blocks(N));
+        w = select_work_at((uint32_t*)p, topm_work_blocks(N));
     }
     HostSignal done;
     if (topm_signals(N, m)) (void)signal_take(done);

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "sage.h"
+#include "select_plan.h"
 #include "xcd_map.h"
 
 namespace sage {
@@ -265,11 +266,7 @@ struct SelectWork {
     uint16_t* table;     // per block, 1024: those with a third digit of at least the index
     int64_t nblk_cap;
 };
-constexpr int TOPM_HIST_WORDS = 4096 + 2 * 1024;
-constexpr int SELECT_BLOCK = 4096;  // keys per block in the compaction passes
-constexpr int SELECT_STATE_WORDS = 64;  // a 256-byte slot of its own
-constexpr int SELECT_BLOCK_WORDS = 2 + 1024 / 2;  // counters and table of a block
-// a work space of blocks blocks at p: TOPM_HIST_WORDS + SELECT_STATE_WORDS + blocks * SELECT_BLOCK_WORDS words
+// a work space of topm_work_words(blocks) words at p
 inline SelectWork select_work_at(uint32_t* p, int64_t blocks) {
     SelectWork w{};
     w.hist = p;

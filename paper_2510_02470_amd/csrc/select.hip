@@ -261,6 +261,8 @@ hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_id
 #undef SAGE_ONE
         return hipGetLastError();
     }
+    const int64_t nblk = topm_blocks(N);
+    if (nblk > w.nblk_cap) return hipErrorInvalidValue;
     // Work-groups of the histograms: 16,384 keys each, 64 at least while there are as many blocks (their adds to the same few words
     // of memory are done one after the other: a million keys 22.4 us with 244 work-groups, 19.9 with 64; 4 million, waiting
     // included, 56.0 with 512, 49.8 with 244).
@@ -269,21 +271,15 @@ hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_id
     hipLaunchKernelGGL(topm_clear_kernel, dim3(TOPM_HIST_WORDS / TOPM_T), dim3(TOPM_T), 0, st, w.hist);
     hipLaunchKernelGGL(topm_hist_kernel<0>, dim3((unsigned)hw), dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
     hipLaunchKernelGGL(topm_hist_kernel<1>, dim3((unsigned)hw), dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
-    // Blocks of 4096 keys; four times as long where every work-group would read the counts, and with many equal scores the
-    // tables, of more than 1024 blocks before it (16 million keys of seven values, waiting included: 166 us with short
-    // blocks, 111 with long ones; 2 million distinct keys 37.3 with short ones, 42.8 with long ones).
-    constexpr int CS = SELECT_BLOCK / TOPM_T, CL = 4 * CS;
 #define SAGE_TAIL(C)                                                                                                          \
     do {                                                                                                                      \
-        const int64_t nblk = (N + C * TOPM_T - 1) / (C * TOPM_T);                                                             \
-        if (nblk > w.nblk_cap) return hipErrorInvalidValue;                                                                   \
         hipLaunchKernelGGL(topm_table_kernel<C>, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.hist, w.state,         \
                            w.blk_gt, w.blk_in, w.table);                                                                      \
         hipLaunchKernelGGL(topm_emit_kernel<C>, dim3((unsigned)nblk), dim3(TOPM_T), 0, st, alpha, N, w.hist, w.state,          \
                            w.blk_gt, w.blk_in, w.table, out_idx);                                                             \
     } while (0)
-    if (blocks <= 1024) SAGE_TAIL(CS);
-    else SAGE_TAIL(CL);
+    if (topm_long(N)) SAGE_TAIL(SELECT_LONG / TOPM_T);
+    else SAGE_TAIL(SELECT_BLOCK / TOPM_T);
 #undef SAGE_TAIL
     return hipGetLastError();
 }

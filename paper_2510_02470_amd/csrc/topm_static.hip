@@ -8,10 +8,10 @@
 namespace {
 
 // Work space of one top-m run over at most SAGE_TOPM_STATIC_MAX_N keys: the histograms, the state, and two counters and a table
-// for every block of SELECT_BLOCK keys.
+// for every block of keys that such a run has.
 constexpr int64_t MAX_N = SAGE_TOPM_STATIC_MAX_N;
-constexpr int64_t MAX_BLOCKS = (MAX_N + sage::SELECT_BLOCK - 1) / sage::SELECT_BLOCK;
-constexpr size_t SCRATCH_WORDS = sage::TOPM_HIST_WORDS + sage::SELECT_STATE_WORDS + (size_t)MAX_BLOCKS * sage::SELECT_BLOCK_WORDS;
+constexpr int64_t MAX_BLOCKS = sage::topm_work_blocks(MAX_N);
+constexpr size_t SCRATCH_WORDS = sage::topm_work_words(MAX_BLOCKS);
 
 // One copy per GPU, at that GPU's own address; host code never uses this name as a pointer (it is a host-side stand-in
 // there): it asks the runtime for the device address once per device and keeps it.

@@ -42,6 +42,14 @@ def test_slots_of_the_reduction_are_emptied_in_time(tmp_path):
     assert _run(exe, "planted").returncode == 1
 
 
+def test_work_space_of_the_selection(tmp_path):
+    """select_plan_check.cc; and the check itself: it must refuse a work space for the longest call alone."""
+    exe = _build(tmp_path, "select_plan_check")
+    r = _run(exe)
+    assert r.returncode == 0 and "select_plan_check ok" in r.stdout, r.stdout
+    assert _run(exe, "planted").returncode == 1
+
+
 def test_events_that_order_streams_release_what_they_order():
     """No run shows a missing release reliably, so the flag is looked for: hipEventDisableSystemFence takes the release away that
     lets a stream see what was written, on another XCD, before the event."""
