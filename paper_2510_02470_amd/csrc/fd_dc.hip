@@ -5,8 +5,10 @@
 //   * entries with rho |z_i| below tol, and all but one of a group of equal poles (after a rotation of their columns),
 //     are deflated: they are eigenpairs already;
 //   * the other eigenvalues are the roots of the secular equation 1 + rho sum z_j^2 / (d_j - lambda) = 0, one in every
-//     gap, each kept as (nearest pole, distance): rational interpolation of the two sums on either side of the gap
-//     (J. Bunch, C. Nielsen, D. Sorensen, Numer. Math. 31, 1978), inside a bracket that is bisected when a step leaves it;
+//     gap, each kept as (nearest pole, distance): an interpolation with the gap's two poles and a constant that matches the
+//     function and two derivatives (C. Borges, W. Gragg, Numerical Linear Algebra and Scientific Computing, de Gruyter 1993;
+//     of two derivatives where J. Bunch, C. Nielsen, D. Sorensen, Numer. Math. 31, 1978, match one on either side of the gap),
+//     inside a bracket that is bisected when a step leaves it;
 //   * z is recomputed from the roots (M. Gu, S. Eisenstat, SIAM J. Matrix Anal. Appl. 16, 1995), which makes the
 //     eigenvectors z_j / (d_j - lambda_i) orthogonal to fp64 rounding however close the roots are.
 // Merges up to 64 rows run inside one work-group per 64 x 64 block (everything in LDS); the merges above it are four
@@ -39,7 +41,7 @@ __device__ __forceinline__ double dc_tolerance(const double* __restrict__ dT, co
 // Root q of f = 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending): lambda = org + tau with org the
 // nearer of the poles around it. A group of L lanes works on a root; lane l holds the poles l + L e, e < E (z = 0 and
 // d = 1e30 beyond K). on: this group has a root (all lanes take part in the loop). The interpolation, which matches f, f' and
-// f'' by two poles and a constant, converges cubically: a step below 1e-7 of tau is the last one. About 3.4 evaluations a
+// f'' by two poles and a constant (Borges and Gragg), converges cubically: a step below 1e-7 of tau is the last one. About 3.4 evaluations a
 // root, six for the slowest of 64 (with f and the derivatives of the two sides, which converges quadratically, 4.3 and seven
 // and a half). An evaluation is a chain of some 500 cycles (reciprocal, sums over L, square root, reciprocal) and 11 fp64
 // instructions a pole; a branch costs 100 cycles, so there is none but the loop's.
