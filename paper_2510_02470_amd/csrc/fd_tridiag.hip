@@ -81,7 +81,8 @@ __device__ __forceinline__ void lds_barrier() {
 // A step is a chain of latencies (sum over a wave 160 cycles, LDS round trip 70, reductions over 16 lanes 105), at J = 2
 // also 3 x 64 fp64 operations a thread while nothing is done yet: finished rows and columns are left out at compile time, 16
 // steps at a time. n = 64: 43.5 us with the vectors on wave 4 alone and two barriers, 41.0 now; n = 128: 155
-// and 122.
+// and 122. The sum v A v put together from parts leaves the solve's residual at 1.03 of what the sum over p v left (1500 matrices
+// of 64 rows, 1e-15 of the norm; orthogonality and eigenvalues as before).
 struct __attribute__((aligned(16))) Pair { double a, b; };
 
 template <int J>
