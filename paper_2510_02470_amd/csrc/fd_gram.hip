@@ -20,6 +20,11 @@ __device__ __forceinline__ void tile_coords(int t, int& ti, int& tj) {
     tj = t - i * (i + 1) / 2;
 }
 
+// Rows not in use are loaded like the others and dropped by a select: a predicate on the load is a branch, of which a wave paid one
+// per 16 bytes (cross block of 256 bf16 rows of 2,049,000: 716 us with it, 673 without; jobs of 128 and of 100 fp32 rows, 1,081,576
+// and 1,562,728 columns: 19.5 -> 18.6 and 26.1 -> 24.6 ms). What is loaded in their place is the last row in use, which is there anyway.
+__device__ __forceinline__ int row_in_use(int row, int rows) { return row < rows ? row : (rows > 0 ? rows - 1 : 0); }
+
 // P = NP / 64 row panels. Tiles t0 .. t0 + tiles - 1 of the row-major lower-triangle enumeration are computed (t0 > 0
 // leaves out the leading panels whose Gram block the caller already knows). 256 threads = 4 waves; the unit of work is half a tile (32 rows x 64 columns, two
 // 32x32 accumulators); a wave owns up to 3 units, a work-group 12 (6 tiles), and two work-groups share a CU so
@@ -44,7 +49,8 @@ __device__ __forceinline__ void gram_tile(int mode, int P, int t0, int idx, int&
     }
 }
 
-template <int P>
+// FRESH: mode 2, which needs no top rows.
+template <int P, bool FRESH>
 __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ top, const float* __restrict__ nw,
                                                       int nfill, float* __restrict__ partial, int mode, int t0,
                                                       int tiles, int wg_per_group, int64_t slabs_total,
@@ -94,8 +100,8 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
     // the top half, the new half, or is zero
     constexpr int LP = NP / 2;
     constexpr int HALF4 = LP * 4;  // 16-byte pieces of one half buffer per slab
-    int src[P];                    // piece index inside the half's slab, -1: zero row
-    bool isnew[P];
+    int src[P];                    // piece index inside the half's slab
+    bool isnew[P], used[P];
 #pragma unroll
     for (int it = 0; it < P; ++it) {
         int ps = it * 256 + tid;
@@ -103,8 +109,11 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
         int p = (ps & 3) ^ ((row >> 2) & 3);
         isnew[it] = row >= LP;
         int hr = isnew[it] ? row - LP : row;
-        src[it] = ((isnew[it] && hr >= nfill) || (mode == 2 && !isnew[it])) ? -1 : hr * 4 + p;  // mode 2 never reads top rows
+        const int rows = isnew[it] ? nfill : LP;
+        src[it] = row_in_use(hr, rows) * 4 + p;
+        used[it] = hr < rows && (isnew[it] || !FRESH);
     }
+    constexpr int IT0 = FRESH && P > 1 ? P / 2 : 0;  // the first with new rows, where the others are not needed
     const f32x4* Tv = reinterpret_cast<const f32x4*>(top);
     const f32x4* Nv = reinterpret_cast<const f32x4*>(nw);
     // Slabs are requested two stages before they are used: one set of registers goes to LDS while the other fills (with P = 8
@@ -114,17 +123,17 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
     auto fetch = [&](int64_t sl, f32x4 (&pre)[P]) __attribute__((always_inline)) {
         const int64_t sc = sl < s1 ? sl : s1 - 1;  // beyond the end: repeat (never used)
 #pragma unroll
-        for (int it = 0; it < P; ++it) {
-            const f32x4* base = (isnew[it] ? Nv : Tv) + sc * HALF4;
-            pre[it] = src[it] >= 0 ? base[src[it]] : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int it = IT0; it < P; ++it) pre[it] = ((isnew[it] ? Nv : Tv) + sc * HALF4)[src[it]];
+    };
+    auto store = [&](const f32x4 (&pre)[P], f32x4* dst) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = IT0; it < P; ++it) dst[it * 256 + tid] = used[it] ? pre[it] : f32x4{0.f, 0.f, 0.f, 0.f};
     };
 
     if (s0 < s1) {
         fetch(s0, pre0);
         if constexpr (TWO) fetch(s0 + 1, pre1);
-#pragma unroll
-        for (int it = 0; it < P; ++it) lds[it * 256 + tid] = pre0[it];
+        store(pre0, lds);
     }
     __syncthreads();
 
@@ -166,9 +175,7 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
         if (on[2]) products(std::integral_constant<int, 3>{});
         else if (on[1]) products(std::integral_constant<int, 2>{});
         else if (on[0]) products(std::integral_constant<int, 1>{});
-        f32x4* nx = lds + (cur ^ 1) * STAGE;
-#pragma unroll
-        for (int it = 0; it < P; ++it) nx[it * 256 + tid] = next[it];
+        store(next, lds + (cur ^ 1) * STAGE);
         // a bare barrier after the LDS traffic: __syncthreads() would also wait for the loads of the slab after next
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
@@ -375,26 +382,29 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
     const f32x4* Nv = reinterpret_cast<const f32x4*>(nw);
     const u32x4* N16 = half16(nw, LP, slabs_total);
     constexpr int IT = NEW1 ? 3 : 4;
-    int src[4], dst8[4];  // source piece in the half buffer (-1: a new row not in use), LDS offset in 8-byte units
+    int src[4], dst8[4];  // source piece in the half buffer, LDS offset in 8-byte units
+    bool used[4];         // (see row_in_use)
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int ps = it * 512 + tid, row = ps >> 2, p = ps & 3;
-        const int hr = row >= LP ? row - LP : row;
-        src[it] = (row >= LP && hr >= nfill) ? -1 : hr * 4 + p;
+        const int hr = row & (LP - 1);
+        const int rows = it >= 2 ? nfill : LP;
+        src[it] = row_in_use(hr, rows) * 4 + p;
+        used[it] = hr < rows;
         dst8[it] = (((p >> 1) * HREG + row) << 1) + (p & 1);
     }
     const bool used16 = (tid & 255) < nfill;
+    const int src16 = (tid & 256) + row_in_use(tid & 255, nfill);
     const int dst16 = (tid >> 8) * HREG + LP + (tid & 255);
     f32x4 pre[4];
     u32x4 pre16;
     auto fetch1 = [&](int it, int64_t sl) __attribute__((always_inline)) {
         const int64_t sc = sl < s1 ? sl : s1 - 1;  // beyond the end: repeat (never used)
         if (NEW1 && it == 2) {
-            pre16 = N16[sc * 512 + tid];
+            pre16 = N16[sc * 512 + src16];
             return;
         }
-        const f32x4* base = (it >= 2 ? Nv : Tv) + sc * HALF4;
-        pre[it] = src[it] >= 0 ? base[src[it]] : f32x4{0.f, 0.f, 0.f, 0.f};
+        pre[it] = ((it >= 2 ? Nv : Tv) + sc * HALF4)[src[it]];
     };
     auto store1 = [&](int it, int buf) __attribute__((always_inline)) {
         if (NEW1 && it == 2) {
@@ -403,6 +413,7 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
         }
         uint2* d = reinterpret_cast<uint2*>(ldsx + buf * STAGE16) + dst8[it];
         unsigned a0, a1, a2, b0, b1, b2;
+        if (!used[it]) pre[it] = f32x4{0.f, 0.f, 0.f, 0.f};
         split3_bf16(pre[it][0], pre[it][1], a0, a1, a2);
         split3_bf16(pre[it][2], pre[it][3], b0, b1, b2);
         d[0] = make_uint2(a0, b0);
@@ -628,20 +639,23 @@ __device__ __forceinline__ void gram_new8_split_wave(const f32x4* __restrict__ N
         for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
 
     int src[4], dst8[4];
+    bool used[4];  // (see row_in_use)
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int ps = it * 256 + tid, row = ps >> 2, p = ps & 3;
-        src[it] = row >= nfill ? -1 : row * 4 + p;
+        src[it] = row_in_use(row, nfill) * 4 + p;
+        used[it] = row < nfill;
         dst8[it] = (((p >> 1) * HREG + row) << 1) + (p & 1);
     }
     f32x4 pre[4];
     auto fetch1 = [&](int it, int64_t sl) __attribute__((always_inline)) {
         const int64_t sc = sl < s1 ? sl : s1 - 1;  // beyond the end: repeat (never used)
-        pre[it] = src[it] >= 0 ? Nv[sc * HALF4 + src[it]] : f32x4{0.f, 0.f, 0.f, 0.f};
+        pre[it] = Nv[sc * HALF4 + src[it]];
     };
     auto store1 = [&](int it, int buf) __attribute__((always_inline)) {
         uint2* d = reinterpret_cast<uint2*>(lds + buf * STAGE16) + dst8[it];
         unsigned a0, a1, a2, b0, b1, b2;
+        if (!used[it]) pre[it] = f32x4{0.f, 0.f, 0.f, 0.f};
         split3_bf16(pre[it][0], pre[it][1], a0, a1, a2);
         split3_bf16(pre[it][2], pre[it][3], b0, b1, b2);
         d[0] = make_uint2(a0, b0);
@@ -732,6 +746,8 @@ __device__ __forceinline__ void gram_new8_half_wave(const u32x4* __restrict__ N1
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
 
+    const int row = FULL ? tid : row_in_use(tid, nfill);
+
     f32x16 acc[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q)
@@ -744,7 +760,7 @@ __device__ __forceinline__ void gram_new8_half_wave(const u32x4* __restrict__ N1
             const int64_t s = sl + q / 2;  // (512 pieces a slab, two loads of 256)
             const int64_t sc = s < s1 ? s : s1 - 1;  // beyond the end: repeat (never used)
             __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(N16 + sc * (2 * LP) + (q & 1) * 256 + tid),
+                (const __attribute__((address_space(1))) void*)(N16 + sc * (2 * LP) + (q & 1) * 256 + row),
                 (__attribute__((address_space(3))) void*)(lds + buf * STAGE + q * 256 + wave * 64), 16, 0, 0);
         }
     };
@@ -982,8 +998,9 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
     switch (d.NP / 64) {
 #define SAGE_GRAM_CASE(PP)                                                                                          \
     case PP: {                                                                                                      \
-        if (hipError_t ea = ensure_dynamic_lds((const void*)gram_kernel<PP>, 65536); ea != hipSuccess) return ea;   \
-        hipLaunchKernelGGL(gram_kernel<PP>, dim3((unsigned)spare_grid_at(grid.x, hole)), dim3(256), lds, st, top, nw, nfill,   \
+        const auto kern = p.mode == 2 ? gram_kernel<PP, true> : gram_kernel<PP, false>;                             \
+        if (hipError_t ea = ensure_dynamic_lds((const void*)kern, 65536); ea != hipSuccess) return ea;              \
+        hipLaunchKernelGGL(kern, dim3((unsigned)spare_grid_at(grid.x, hole)), dim3(256), lds, st, top, nw, nfill,   \
                            partial, p.mode, p.t0, p.tiles, p.wg_per_group, d.S, p.slabs_per_group, (int)grid.x, hole);  \
     } break;
         SAGE_GRAM_CASE(1)
