@@ -49,13 +49,16 @@ __device__ __forceinline__ void gram_tile(int mode, int P, int t0, int idx, int&
     }
 }
 
+// The launch's row of work-groups y takes tops.p[y] for the top half and has its partial tiles y * stride floats further on.
 // FRESH: mode 2, which needs no top rows.
 template <int P, bool FRESH>
-__global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ top, const float* __restrict__ nw,
+__global__ __launch_bounds__(256, 2) void gram_kernel(GramTops tops, const float* __restrict__ nw,
                                                       int nfill, float* __restrict__ partial, int mode, int t0,
                                                       int tiles, int wg_per_group, int64_t slabs_total,
                                                       int64_t slabs_per_group, int wgs,
                                                       const int* __restrict__ hole) {
+    const float* __restrict__ top = tops.p[blockIdx.y];
+    partial += blockIdx.y * tops.stride;
     constexpr int NP = P * 64;
     constexpr int STAGE = NP * 4;  // 16-byte pieces per stage
     extern __shared__ f32x4 lds[];
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
     constexpr int LP = NP / 2;
     constexpr int HALF4 = LP * 4;  // 16-byte pieces of one half buffer per slab
     int src[P];                    // piece index inside the half's slab
-    bool isnew[P], used[P];
+    bool isnew[P], used[P];        // (see row_in_use)
 #pragma unroll
     for (int it = 0; it < P; ++it) {
         int ps = it * 256 + tid;
@@ -109,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(const float* __restrict__ 
         int p = (ps & 3) ^ ((row >> 2) & 3);
         isnew[it] = row >= LP;
         int hr = isnew[it] ? row - LP : row;
-        const int rows = isnew[it] ? nfill : LP;
+        const int rows = isnew[it] ? nfill : tops.rows;
         src[it] = row_in_use(hr, rows) * 4 + p;
         used[it] = hr < rows && (isnew[it] || !FRESH);
     }
@@ -342,10 +345,11 @@ __global__ __launch_bounds__(256, 2) void gram_cross8_kernel(const float* __rest
 // is, and only the three products with it are issued. The three left out would add exact
 // zeros: the result has the same bits either way.
 template <bool NEW1>
-__global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* __restrict__ top,
+__global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(GramTops tops,
                                                                    const float* __restrict__ nw, int nfill,
                                                                    float* __restrict__ partial, int64_t slabs_total,
-                                                                   int64_t slabs_per_group) {
+                                                                   int64_t slabs_per_group, int groups,
+                                                                   const int* __restrict__ hole) {
     constexpr int NP = 512, LP = 256;
     constexpr int HALF4 = LP * 4;        // 16-byte pieces of a half buffer per slab
     constexpr int HREG = NP + 8;         // pieces per k-half region: the rows plus 128 bytes, so that the two regions a
@@ -354,9 +358,10 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
     constexpr int STAGE16 = 3 * PART16;  // 48.4 KB
     extern __shared__ u32x4 ldsx[];      // 2 * STAGE16
 
-    const int id = blockIdx.x;
-    const int xcd = id & 7;
-    const int group = (id >> 3) * 8 + xcd;
+    const int group = (int)spare_unit_at(hole);
+    if (group < 0 || group >= groups) return;
+    const float* __restrict__ top = tops.p[blockIdx.y];
+    partial += blockIdx.y * tops.stride;
     const int64_t s0 = (int64_t)group * slabs_per_group;
     int64_t s1 = s0 + slabs_per_group;
     if (s1 > slabs_total) s1 = slabs_total;
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
     for (int it = 0; it < 4; ++it) {
         const int ps = it * 512 + tid, row = ps >> 2, p = ps & 3;
         const int hr = row & (LP - 1);
-        const int rows = it >= 2 ? nfill : LP;
+        const int rows = it >= 2 ? nfill : tops.rows;
         src[it] = row_in_use(hr, rows) * 4 + p;
         used[it] = hr < rows;
         dst8[it] = (((p >> 1) * HREG + row) << 1) + (p & 1);
@@ -487,6 +492,98 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(const float* 
                 int c = cb * 32 + l32;
                 out[r * 64 + c] = acc[i][cb][e];
             }
+    }
+}
+
+// The same rectangle of two blocks kept in pieces of bf16 (half16), the top rows being an earlier block's: one part each, one
+// product (the bits of the kernel above, whose other products add exact zeros), nothing to convert. Bound by memory: the pieces
+// go straight to LDS, three slabs (48 KB) at a time into a ring of three, two of them on their way (144 KB of a CU's 160).
+__global__ __launch_bounds__(512, 1) void gram_cross8_half_kernel(GramTops tops, const float* __restrict__ nw, int nfill,
+                                                                  float* __restrict__ partial, int64_t slabs_total,
+                                                                  int64_t slabs_per_group, int groups,
+                                                                  const int* __restrict__ hole) {
+    constexpr int LP = 256, SL = 3, SLAB = 2 * 2 * LP, STAGE = SL * SLAB, ML = STAGE / 512;  // SLAB: [top, new][k-half][row]
+    extern __shared__ u32x4 ldsc[];  // 3 * STAGE
+    const int group = (int)spare_unit_at(hole);
+    if (group < 0 || group >= groups) return;
+    partial += blockIdx.y * tops.stride;
+    const int64_t s0 = (int64_t)group * slabs_per_group;
+    int64_t s1 = s0 + slabs_per_group;
+    if (s1 > slabs_total) s1 = slabs_total;
+    const u32x4* T16 = half16(tops.p[blockIdx.y], LP, slabs_total);
+    const u32x4* N16 = half16(nw, LP, slabs_total);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    const int ag = wave >> 2, bg = wave & 3;  // new rows 128*ag .. + 128, top rows 64*bg .. + 64
+
+    const int trow = (tid & 256) + row_in_use(tid & 255, tops.rows), nrow = (tid & 256) + row_in_use(tid & 255, nfill);
+
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][b][e] = 0.f;
+
+    auto stage = [&](int64_t sl, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < ML; ++q) {  // 512 pieces of a slab's top rows, then of its new rows
+            const int64_t s = sl + q / 2;
+            const int64_t sc = s < s1 ? s : s1 - 1;  // beyond the end: repeat (never used)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)((q & 1 ? N16 + nrow : T16 + trow) + sc * (2 * LP)),
+                (__attribute__((address_space(3))) void*)(ldsc + buf * STAGE + q * 512 + wave * 64), 16, 0, 0);
+        }
+    };
+    if (s0 < s1) {
+        stage(s0, 0);
+        stage(s0 + SL, 1);
+    }
+    int buf = 0;
+    for (int64_t s = s0; s < s1; s += SL) {
+        // all but the last stage's loads have landed; everyone is done with the buffer of the stage before
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0F70 | ML);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        stage(s + 2 * SL, buf == 0 ? 2 : buf - 1);
+        const u32x4* st = ldsc + buf * STAGE + h * LP + l32;
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            if (s + u >= s1) break;  // (uniform)
+            u32x4 a[4], b[2];
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const int r = bg * 64 + 32 * cb;
+                b[cb] = st[u * SLAB + r];
+                if (r + l32 >= tops.rows) b[cb] = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = ag * 128 + 32 * i;
+                a[i] = st[u * SLAB + 2 * LP + r];
+                if (r + l32 >= nfill) a[i] = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) acc[i][cb] = mfma_bf16(a[i], b[cb], acc[i][cb]);
+        }
+        buf = buf == 2 ? 0 : buf + 1;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS when the work-group ends
+
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int tidx = (2 * ag + (i >> 1)) * 4 + bg;
+        float* out = partial + ((int64_t)group * 16 + tidx) * 4096 + (i & 1) * 2048;
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) out[(8 * (e >> 2) + 4 * h + (e & 3)) * 64 + cb * 32 + l32] = acc[i][cb][e];
     }
 }
 
@@ -950,19 +1047,36 @@ GramPlan gram_plan_split(const GramPlan& base, const Dims& d, int groups) {
 
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
                        hipStream_t st, bool new_one, const int* hole) {
-    if (p.tiles <= 0) return hipSuccess;
+    return launch_gram_tops(GramTops{{top}, 0, d.LP}, 1, nw, nfill, partial, p, d, st, new_one, hole);
+}
+
+hipError_t launch_gram_blocks(const GramTops& tops, int count, const float* nw, int nfill, float* partial, const GramPlan& p,
+                              const Dims& d, hipStream_t st, const int* hole) {
+    constexpr int LDS = 3 * 3 * 2 * 2 * 256 * 16;  // three stages of three slabs
+    if (count <= 0) return hipSuccess;
+    if (hipError_t ea = ensure_dynamic_lds((const void*)gram_cross8_half_kernel, LDS); ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(gram_cross8_half_kernel, dim3((unsigned)spare_grid_at(p.groups, hole), count), dim3(512), LDS, st, tops,
+                       nw, nfill, partial, d.S, p.slabs_per_group, p.groups, hole);
+    return hipGetLastError();
+}
+
+hipError_t launch_gram_tops(const GramTops& tops, int count, const float* nw, int nfill, float* partial, const GramPlan& p,
+                            const Dims& d, hipStream_t st, bool new_one, const int* hole) {
+    if (p.tiles <= 0 || count <= 0) return hipSuccess;
+    const float* const top = tops.p[0];
     dim3 grid((unsigned)(p.groups * p.wg_per_group));
     size_t lds = (size_t)2 * d.NP * 64;
     if (p.mode == 1 && d.NP == 512 && p.split) {
         constexpr int LDS_SPLIT = 2 * 3 * 2 * (512 + 8) * 16;  // two stages of [part][k-half][row + pad] pieces
         const void* kern = new_one ? (const void*)gram_cross8_split_kernel<true> : (const void*)gram_cross8_split_kernel<false>;
         if (hipError_t ea = ensure_dynamic_lds(kern, LDS_SPLIT); ea != hipSuccess) return ea;
+        const dim3 wgs((unsigned)spare_grid_at(p.groups, hole), count);
         if (new_one)
-            hipLaunchKernelGGL(gram_cross8_split_kernel<true>, grid, dim3(512), LDS_SPLIT, st, top, nw, nfill, partial, d.S,
-                               p.slabs_per_group);
+            hipLaunchKernelGGL(gram_cross8_split_kernel<true>, wgs, dim3(512), LDS_SPLIT, st, tops, nw, nfill, partial, d.S,
+                               p.slabs_per_group, p.groups, hole);
         else
-            hipLaunchKernelGGL(gram_cross8_split_kernel<false>, grid, dim3(512), LDS_SPLIT, st, top, nw, nfill, partial,
-                               d.S, p.slabs_per_group);
+            hipLaunchKernelGGL(gram_cross8_split_kernel<false>, wgs, dim3(512), LDS_SPLIT, st, tops, nw, nfill, partial,
+                               d.S, p.slabs_per_group, p.groups, hole);
         return hipGetLastError();
     }
     if (p.mode == 1 && d.NP == 512) {
@@ -1000,7 +1114,7 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
     case PP: {                                                                                                      \
         const auto kern = p.mode == 2 ? gram_kernel<PP, true> : gram_kernel<PP, false>;                             \
         if (hipError_t ea = ensure_dynamic_lds((const void*)kern, 65536); ea != hipSuccess) return ea;              \
-        hipLaunchKernelGGL(kern, dim3((unsigned)spare_grid_at(grid.x, hole)), dim3(256), lds, st, top, nw, nfill,   \
+        hipLaunchKernelGGL(kern, dim3((unsigned)spare_grid_at(grid.x, hole), count), dim3(256), lds, st, tops, nw, nfill,   \
                            partial, p.mode, p.t0, p.tiles, p.wg_per_group, d.S, p.slabs_per_group, (int)grid.x, hole);  \
     } break;
         SAGE_GRAM_CASE(1)

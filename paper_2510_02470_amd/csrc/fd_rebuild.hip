@@ -4,8 +4,9 @@
 // Phase I, "S <- Sigma' V^T"), in place on the sketch, and the scoring basis V_k^T = diag(1/sigma) Y_k^T B
 // (Algorithm 1, "Freeze S for scoring"), written to its own buffer.
 //
-// The buffer is two half buffers of LP = NP/2 rows (same slab layout): `top` = matrix rows 0 .. LP-1, `nw` = matrix rows
-// LP .. NP-1 of which the first nfill hold data (the others count as zero, whatever they hold).
+// The buffer is half buffers of LP rows (same slab layout): `top` = rows 0 .. LP-1, then one or, for shrinks that were put
+// together (sage_api.hip), several blocks of LP rows of which the first nfill hold data (the others count as zero, whatever
+// they hold). Stages of 16 rows without any are left out.
 // A wave owns 32 columns for the whole product: it reads all NP buffer rows of those columns (its B operand comes
 // straight from global memory, one 128 B line per row pair), keeps the MP x 32 result in accumulators, and only
 // then writes. Nobody else touches those columns, so the update is safely in place (out == top, which is why neither
@@ -19,10 +20,38 @@
 
 namespace sage {
 
-template <int MT>  // MT = MP / 32 accumulator tiles per wave
-__global__ __launch_bounds__(256, 2) void rebuild_kernel(const float* top, const float* __restrict__ nw, int nfill,
-                                                         const float* __restrict__ Mc, float* out, int NP, int out_NP,
-                                                         int64_t Dp) {
+// Where a stage of 16 buffer rows lies: LP / 16 of the top, then `per` of every block (those with rows in use). By selections, not
+// by branches: a branch costs a wave some 100 cycles, and there is nobody to hide them behind in these loops. MANY: there may be
+// several blocks (with one, the divisions took 0.5 us of 5 at 64 rows of 512).
+template <bool MANY>
+struct BlockMap {
+    NewBlocks nw;
+    int per;         // stages of a block, (nfill + 15) / 16
+    unsigned magic;  // s / per = s * magic >> 16 (s < 128, per <= 16)
+    struct Place {
+        int block, row;  // row: first of the stage, in its half
+        bool fresh;      // a block's
+    };
+    __device__ __forceinline__ Place place(int stg, int ntop) const {
+        const bool fresh = stg >= ntop;
+        if constexpr (!MANY) return {0, (fresh ? stg - ntop : stg) * 16, fresh};
+        const int s = fresh ? stg - ntop : 0, b = (int)((unsigned)s * magic >> 16);
+        return {b, (fresh ? s - b * per : stg) * 16, fresh};
+    }
+    // the stage's chunk of coefficients: there the blocks are ntop stages apart
+    __device__ __forceinline__ int chunk(int stg, int ntop) const { return MANY ? stg + place(stg, ntop).block * (ntop - per) : stg; }
+};
+template <bool MANY>
+static BlockMap<MANY> block_map(const NewBlocks& nw, int nfill) {
+    BlockMap<MANY> m{nw, nfill > 0 ? (nfill + 15) / 16 : 1, 0};
+    m.magic = 65536u / (unsigned)m.per + 1u;
+    return m;
+}
+
+template <int MT, bool MANY>  // MT = MP / 32 accumulator tiles per wave
+__global__ __launch_bounds__(256, 2) void rebuild_kernel(const float* top, BlockMap<MANY> blocks, int nfill,
+                                                         const float* __restrict__ Mc, float* out, int LP, int out_NP,
+                                                         int64_t Dp, int units, const int* __restrict__ hole) {
     constexpr int MP = MT * 32;
     constexpr int CHUNK4 = 16 * MP / 4;  // 16-byte pieces per stage (16 buffer rows x MP coefficients)
     constexpr int PER = CHUNK4 / 256;    // pieces per thread per stage (MT / 2 ... at least 1)
@@ -30,29 +59,32 @@ __global__ __launch_bounds__(256, 2) void rebuild_kernel(const float* top, const
     constexpr int PERC = PER > 0 ? PER : 1;
     __shared__ f32x4 Ms[3][CHUNK4];
 
+    const int64_t unit = spare_unit_at(hole);
+    if (unit < 0 || unit >= units) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int c = lane & 31, h = lane >> 5;
-    const int64_t d = ((int64_t)blockIdx.x * 4 + wave) * 32 + c;  // this lane's column
+    const int64_t d = (unit * 4 + wave) * 32 + c;  // this lane's column
     const bool live = d < Dp;  // Dp is a multiple of 16: the last 32-column group may overhang by 16
     const int64_t dc = live ? d : Dp - 1;
-    const int LP = NP >> 1;
     const int64_t coff = ((dc / DC) * LP) * (int64_t)DC + (dc % DC) + (int64_t)h * DC;  // row h of this column, either half
-    // lanes beyond the last column compute nothing that is stored; they read the new half only, which this kernel never
+    // lanes beyond the last column compute nothing that is stored; they read a block only, which this kernel never
     // writes (out may be top: top and out are the same memory then, hence not declared restrict)
-    const float* tcol = (live ? top : nw) + coff;
-    const float* ncol = nw + coff;
-    // rows 16*stg + 2*s + h of the matrix: stage stg lies in the top half when stg < LP/16. Rows of the new half are
+    const float* tcol = (live ? top : blocks.nw.at(0)) + coff;
+    const int64_t away = blocks.nw.ring + coff - tcol;  // from there to the ring
+    // rows 16*stg + 2*s + h of the matrix: stage stg lies in the top half when stg < LP/16. Rows of a block are
     // always loaded (they exist); those not in use are zeroed when the stage consumes them (use_b), not here, so
     // that nothing waits for a load right after issuing it.
+    const int ntop = LP >> 4;
     auto fetch_b = [&](int stg, float (&b)[8]) {
-        const int r0 = stg * 16;
-        const float* bn = r0 >= LP ? ncol + (int64_t)(r0 - LP) * DC : tcol + (int64_t)r0 * DC;
+        const typename BlockMap<MANY>::Place p = blocks.place(stg, ntop);
+        const int64_t ofs = away + blocks.nw.offset(p.block);
+        const float* bn = tcol + (p.fresh ? ofs : 0) + (int64_t)p.row * DC;
 #pragma unroll
         for (int s = 0; s < 8; ++s) b[s] = bn[(int64_t)(2 * s) * DC];
     };
     auto use_b = [&](int stg, const float (&b)[8], float (&o)[8]) {
-        const int r0 = stg * 16;
-        const int limit = r0 >= LP ? nfill - (r0 - LP) - h : 0x7fffffff;  // 2*s < limit: row in use
+        const typename BlockMap<MANY>::Place p = blocks.place(stg, ntop);
+        const int limit = p.fresh ? nfill - p.row - h : 0x7fffffff;  // 2*s < limit: row in use
 #pragma unroll
         for (int s = 0; s < 8; ++s) o[s] = 2 * s < limit ? b[s] : 0.f;
     };
@@ -67,7 +99,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_kernel(const float* top, const
     float bpre[8];
     f32x4 mpre[PERC];
     // prologue: coefficients of stages 0 and 1 into LDS, row operand of stage 0 on its way
-    const int nstage = (LP + (nfill + 15) / 16 * 16) / 16;  // no stage without rows in use
+    const int nstage = ntop + (nfill > 0 ? blocks.per * blocks.nw.count : 0);  // no stage without rows in use
     fetch_b(0, bpre);
 #pragma unroll
     for (int u = 0; u < PERC; ++u)
@@ -99,7 +131,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_kernel(const float* top, const
         if (more2) {
 #pragma unroll
             for (int u = 0; u < PERC; ++u)
-                if (u * 256 + tid < CHUNK4) mpre[u] = Mv[(int64_t)(stg + 2) * CHUNK4 + u * 256 + tid];
+                if (u * 256 + tid < CHUNK4) mpre[u] = Mv[(int64_t)blocks.chunk(stg + 2, ntop) * CHUNK4 + u * 256 + tid];
         }
         if (more) fetch_b(stg + 1, bpre);
         __builtin_amdgcn_sched_barrier(0);
@@ -141,16 +173,22 @@ __global__ __launch_bounds__(256, 2) void rebuild_kernel(const float* top, const
         }
 }
 
-hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const float* Mc, float* out, int out_NP, int MP,
-                          const Dims& d, hipStream_t st) {
-    dim3 grid((unsigned)((d.Dp + 127) / 128));
-#define SAGE_RB(MT)                                                                                                  \
-    hipLaunchKernelGGL(rebuild_kernel<MT>, grid, dim3(256), 0, st, top, nw, nfill, Mc, out, d.NP, out_NP, d.Dp)
+hipError_t launch_rebuild(const float* top, const NewBlocks& nw, int nfill, const float* Mc, float* out, int out_NP, int MP,
+                          const Dims& d, hipStream_t st, const int* hole) {
+    const int units = (int)((d.Dp + 127) / 128);
+    dim3 grid((unsigned)spare_grid_at(units, hole));
+#define SAGE_RB(MT, MANY)                                                                                              \
+    hipLaunchKernelGGL((rebuild_kernel<MT, MANY>), grid, dim3(256), 0, st, top, block_map<MANY>(nw, nfill), nfill, Mc, out, d.LP, \
+                       out_NP, d.Dp, units, hole)
+    if (nw.count > 1 && MP != 64) return hipErrorInvalidValue;  // (larger ones have split coefficients, of smaller ones none is deferred)
     switch (MP / 32) {
-        case 1: SAGE_RB(1); break;
-        case 2: SAGE_RB(2); break;
-        case 4: SAGE_RB(4); break;
-        case 8: SAGE_RB(8); break;
+        case 1: SAGE_RB(1, false); break;
+        case 2:
+            if (nw.count > 1) SAGE_RB(2, true);
+            else SAGE_RB(2, false);
+            break;
+        case 4: SAGE_RB(4, false); break;
+        case 8: SAGE_RB(8, false); break;
         default: return hipErrorInvalidValue;
     }
 #undef SAGE_RB
@@ -174,48 +212,50 @@ hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const fl
 // NPT > 0: the buffer has NPT rows and the new rows in use hold bf16 values; their stages take the hi part alone and
 // three products (the other three would add exact zeros). NPT = 0: any buffer, all parts. NPT = 512: the new half is kept in
 // pieces of bf16 (half16); a lane loads the 4 bytes that hold its column's value and picks its half.
-template <int MT, int NPT>
-__global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top, const float* __restrict__ nw, int nfill,
-                                                               const u32x4* __restrict__ Mc3, float* out, int NP,
-                                                               int out_NP, int64_t Dp) {
+template <int MT, int NPT, bool MANY>
+__global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top, BlockMap<MANY> blocks, int nfill,
+                                                               const u32x4* __restrict__ Mc3, float* out, int LP,
+                                                               int out_NP, int64_t Dp, int units,
+                                                               const int* __restrict__ hole) {
     constexpr int MP = MT * 32;
     constexpr int STAGE16 = 3 * 2 * MP;   // 16-byte pieces of coefficients per stage
     constexpr int ML = STAGE16 / 256;     // direct-to-LDS loads per thread and stage
     static_assert(STAGE16 % 256 == 0, "a stage must tile the work-group");
     extern __shared__ u32x4 Ms[];         // 3 * STAGE16
 
+    const int64_t unit = spare_unit_at(hole);
+    if (unit < 0 || unit >= units) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, h = lane >> 5;
-    const int64_t d = ((int64_t)blockIdx.x * 4 + wave) * 32 + c;  // this lane's column
+    const int64_t d = (unit * 4 + wave) * 32 + c;  // this lane's column
     const bool live = d < Dp;  // Dp is a multiple of 16: the last 32-column group may overhang by 16
     const int64_t dc = live ? d : Dp - 1;
-    const int LP = NP >> 1;
     const int64_t coff = ((dc / DC) * LP) * (int64_t)DC + (dc % DC) + (int64_t)h * DC;  // row h of this column, either half
-    // lanes beyond the last column compute nothing that is stored; they read the new half only, which this kernel never
+    // lanes beyond the last column compute nothing that is stored; they read a block only, which this kernel never
     // writes (out may be top: top and out are the same memory then, hence not declared restrict)
-    const float* tcol = (live ? top : nw) + coff;
-    const float* ncol = nw + coff;
-    const int nstage = (LP + (nfill + 15) / 16 * 16) / 16;  // no stage without rows in use (a basis right after a shrink: half)
+    const float* tcol = (live ? top : blocks.nw.at(0)) + coff;
+    const int64_t away = blocks.nw.ring + coff - tcol;  // from there to the ring
+    const int ntop = LP >> 4;
+    const int nstage = ntop + (nfill > 0 ? blocks.per * blocks.nw.count : 0);  // no stage without rows in use (a basis right after a shrink: half)
     constexpr bool HALF = NPT == 512;
-    const float* hcol = HALF ? reinterpret_cast<const float*>(half16(nw, LP, Dp / DC) + (dc / 8) * LP + h) + (dc % 8) / 2 : nw;
+    const int64_t hoff = HALF ? ((dc / 8) * LP + h) * 4 + (dc % 8) / 2 : 0;  // in words, from the start of a block's pieces
     const unsigned pick = HALF && !(dc & 1) ? 0x05040100u : 0x07060302u;  // lower or upper halves of two words
     auto fetch_b = [&](auto from_half, int stg, float (&b)[8]) __attribute__((always_inline)) {
-        const int sg = stg < nstage ? stg : nstage - 1;  // beyond the end: repeat (never used)
-        const int r0 = sg * 16;
-        if constexpr (decltype(from_half)::value) {
-            const float* bn = hcol + (r0 > LP ? r0 - LP : 0) * 4;
+        const typename BlockMap<MANY>::Place p = blocks.place(stg < nstage ? stg : nstage - 1, ntop);  // beyond the end: repeat (never used)
+        if constexpr (decltype(from_half)::value) {  // (of a block: or, without any, never used)
+            const float* bn = reinterpret_cast<const float*>(half16(blocks.nw.at(p.block), LP, Dp / DC)) + hoff + (p.fresh ? p.row : 0) * 4;
 #pragma unroll
             for (int s = 0; s < 8; ++s) b[s] = bn[2 * s * 4];
         } else {
-            const float* bn = r0 >= LP ? ncol + (int64_t)(r0 - LP) * DC : tcol + (int64_t)r0 * DC;
+            const int64_t ofs = away + blocks.nw.offset(p.block);
+            const float* bn = tcol + (p.fresh ? ofs : 0) + (int64_t)p.row * DC;
 #pragma unroll
             for (int s = 0; s < 8; ++s) b[s] = bn[(int64_t)(2 * s) * DC];
         }
     };
     auto fetch_m = [&](int stg, int buf) __attribute__((always_inline)) {
-        const int sg = stg < nstage ? stg : nstage - 1;
-        const u32x4* src = Mc3 + (int64_t)sg * STAGE16 + tid;
+        const u32x4* src = Mc3 + (int64_t)blocks.chunk(stg < nstage ? stg : nstage - 1, ntop) * STAGE16 + tid;
 #pragma unroll
         for (int q = 0; q < ML; ++q)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + q * 256),
@@ -239,8 +279,8 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
 #pragma unroll
             for (int p = 0; p < 3; ++p) a[0][t][p] = A[p * 2 * MP + t * 32];
         // rows of the new half that are not in use count as zero, whatever they hold
-        const int r0 = stg * 16;
-        const int limit = r0 >= LP ? nfill - (r0 - LP) - h : 0x7fffffff;  // 2*s < limit: row in use
+        const typename BlockMap<MANY>::Place here = blocks.place(stg, ntop);
+        const int limit = here.fresh ? nfill - here.row - h : 0x7fffffff;  // 2*s < limit: row in use
         u32x4 bh, bm, bl;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -369,29 +409,37 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
 
 bool rebuild_split_ok(int MP) { return MP == 128 || MP == 256; }
 
-size_t rebuild_split_bytes(const Dims& d, int MP) { return (size_t)(d.NP / 16) * 3 * 2 * MP * 16; }
+size_t rebuild_split_bytes(int rows, int MP) { return (size_t)(rows / 16) * 3 * 2 * MP * 16; }
 
-template <int MT, int NPT>
-static hipError_t launch_rebuild_split_t(const float* top, const float* nw, int nfill, const void* Mc3, float* out,
-                                         int out_NP, const Dims& d, hipStream_t st) {
+template <int MT, int NPT, bool MANY = false>
+static hipError_t launch_rebuild_split_t(const float* top, const NewBlocks& nw, int nfill, const void* Mc3, float* out,
+                                         int out_NP, const Dims& d, hipStream_t st, const int* hole) {
     constexpr int MP = MT * 32;
     constexpr size_t LDS = (size_t)3 * 3 * 2 * MP * 16;
-    if (hipError_t ea = ensure_dynamic_lds((const void*)rebuild_split_kernel<MT, NPT>, (int)LDS); ea != hipSuccess)
+    if (hipError_t ea = ensure_dynamic_lds((const void*)rebuild_split_kernel<MT, NPT, MANY>, (int)LDS); ea != hipSuccess)
         return ea;
-    dim3 grid((unsigned)((d.Dp + 127) / 128));
-    hipLaunchKernelGGL((rebuild_split_kernel<MT, NPT>), grid, dim3(256), LDS, st, top, nw, nfill, (const u32x4*)Mc3, out,
-                       d.NP, out_NP, d.Dp);
+    const int units = (int)((d.Dp + 127) / 128);
+    dim3 grid((unsigned)spare_grid_at(units, hole));
+    hipLaunchKernelGGL((rebuild_split_kernel<MT, NPT, MANY>), grid, dim3(256), LDS, st, top, block_map<MANY>(nw, nfill), nfill,
+                       (const u32x4*)Mc3, out, d.LP, out_NP, d.Dp, units, hole);
     return hipGetLastError();
 }
 
-hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
-                                const Dims& d, hipStream_t st, bool new_one) {
+hipError_t launch_rebuild_split(const float* top, const NewBlocks& nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
+                                const Dims& d, hipStream_t st, bool new_one, const int* hole) {
     if (nfill == 0) new_one = false;  // (no stages of the new half)
-    if (MP == 256 && new_one && d.NP == 512) return launch_rebuild_split_t<8, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);
-    if (MP == 256) return launch_rebuild_split_t<8, 0>(top, nw, nfill, Mc3, out, out_NP, d, st);
-    if (MP == 128 && new_one && d.NP == 512) return launch_rebuild_split_t<4, 512>(top, nw, nfill, Mc3, out, out_NP, d, st);
-    if (MP == 128 && new_one && d.NP == 256) return launch_rebuild_split_t<4, 256>(top, nw, nfill, Mc3, out, out_NP, d, st);
-    if (MP == 128) return launch_rebuild_split_t<4, 0>(top, nw, nfill, Mc3, out, out_NP, d, st);
+    if (nw.count > 1) {
+        if (MP == 256 && new_one) return launch_rebuild_split_t<8, 512, true>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+        if (MP == 256) return launch_rebuild_split_t<8, 0, true>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+        if (MP == 128 && d.NP == 256 && new_one) return launch_rebuild_split_t<4, 256, true>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+        if (MP == 128 && d.NP == 256) return launch_rebuild_split_t<4, 0, true>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+        return hipErrorInvalidValue;
+    }
+    if (MP == 256 && new_one && d.NP == 512) return launch_rebuild_split_t<8, 512>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+    if (MP == 256) return launch_rebuild_split_t<8, 0>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+    if (MP == 128 && new_one && d.NP == 512) return launch_rebuild_split_t<4, 512>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+    if (MP == 128 && new_one && d.NP == 256) return launch_rebuild_split_t<4, 256>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
+    if (MP == 128) return launch_rebuild_split_t<4, 0>(top, nw, nfill, Mc3, out, out_NP, d, st, hole);
     return hipErrorInvalidValue;
 }
 

@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "sage_internal.h"
+#include "fd_coeffs.h"
 #include "fd_tri_plan.h"
 #include "fd_wy.h"
 #include "wave_ops.h"
@@ -757,36 +758,9 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
 //   mode 1, basis: f_m = 1 / sqrt(lambda_m), or 0 when lambda_m <= n 2^-23 lambda_1.
 //   mode 2, weighted basis: f_m = sqrt(max(lambda_m - delta, 0) / lambda_m) under the same rank test, which makes the row the
 //           m-th of the sketch a shrink of the buffer would write ("Two-pass scoring": z = S g).
-// A lane makes the 8 coefficients (stage, k-half h, row m) that a matrix-core lane of the rebuild takes per stage of 16
-// buffer rows: buffer rows 16 * stage + 2 s + h, s < 8. OUT_SPLIT: as three bf16 parts in the order rebuild_split_kernel
-// streams them; OUT_F32: in coeff_offset order. The work-group after the last row does the scalars.
-enum { OUT_Y, OUT_F32, OUT_SPLIT };
-struct Coeffs8 {
-    float c[8];
-};
-template <int OUT>
-__device__ __forceinline__ void store_coeffs(const CoeffArgs& cf, int stg, int h, int m, const Coeffs8& v) {
-    if constexpr (OUT == OUT_SPLIT) {
-        u32x4 hi, mid, lo;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            unsigned a, b, c;
-            split3_bf16(v.c[2 * e], v.c[2 * e + 1], a, b, c);
-            hi[e] = a;
-            mid[e] = b;
-            lo[e] = c;
-        }
-        u32x4* dst = (u32x4*)cf.Mc3 + (int64_t)stg * (3 * 2 * cf.MP) + h * cf.MP + m;
-        dst[0] = hi;
-        dst[2 * cf.MP] = mid;
-        dst[4 * cf.MP] = lo;
-    } else {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            *reinterpret_cast<f32x4*>(cf.Mt + coeff_offset(stg * 16 + h + 8 * q, m, cf.MP)) =
-                f32x4{v.c[4 * q], v.c[4 * q + 1], v.c[4 * q + 2], v.c[4 * q + 3]};
-    }
-}
+// OUT_SPLIT, OUT_F32: in the orders of the rebuild (fd_coeffs.h). OUT_M: in fp64, row m of M in matrix indices, for a rebuild that
+// comes later (fd_defer.hip). The work-group after the last row does the scalars.
+enum { OUT_Y, OUT_F32, OUT_SPLIT, OUT_M };
 template <int J, int OUT>
 __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restrict__ Z, const double* __restrict__ V,
                                                          const double* __restrict__ Tw, int m0, int LP, int n,
@@ -830,7 +804,11 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
             }
         }
         if (f == 0.0) {  // a zero row
-            if (lane < 8 * J) store_coeffs<OUT>(cf, lane >> 1, lane & 1, rank, {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f});
+            if constexpr (OUT == OUT_M) {
+                for (int i = lane; i < N; i += 64) cf.M[(int64_t)rank * N + i] = 0.0;
+            } else if (lane < 8 * J) {
+                store_coeffs<OUT == OUT_SPLIT>(cf.Mt, cf.Mc3, cf.MP, lane >> 1, lane & 1, rank, {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f});
+            }
             return;
         }
     }
@@ -948,6 +926,10 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
         double* out = Yt + (int64_t)rank * NP;
 #pragma unroll
         for (int j = 0; j < J; ++j) out[place(row(j))] = z[j];
+    } else if constexpr (OUT == OUT_M) {
+        double* out = cf.M + (int64_t)rank * N;
+#pragma unroll
+        for (int j = 0; j < J; ++j) out[place(row(j))] = f * z[j];
     } else {
         __shared__ double y[N];
 #pragma unroll
@@ -958,7 +940,7 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
             Coeffs8 v;
 #pragma unroll
             for (int s = 0; s < 8; ++s) v.c[s] = (float)(f * y[stg * 16 + h + 2 * s]);
-            store_coeffs<OUT>(cf, stg, h, rank, v);
+            store_coeffs<OUT == OUT_SPLIT>(cf.Mt, cf.Mc3, cf.MP, stg, h, rank, v);
         }
     }
 }
@@ -1036,6 +1018,7 @@ hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, c
                        w.Z[dc_result(NP)], w.V, w.Tw, m0, LP, n, w.Yt, NP, args, dv, w.C, w.stat, w.known)
 #define SAGE_BACK_J(J)                        \
     if (!cf) SAGE_BACK(J, OUT_Y);             \
+    else if (args.M) SAGE_BACK(J, OUT_M);       \
     else if (args.Mc3) SAGE_BACK(J, OUT_SPLIT); \
     else SAGE_BACK(J, OUT_F32);               \
     break

@@ -8,6 +8,7 @@
 #include <type_traits>
 #include <unistd.h>
 
+#include "fd_defer_plan.h"
 #include "sage_internal.h"
 
 using namespace sage;
@@ -15,6 +16,7 @@ using namespace sage;
 namespace {
 
 constexpr int NCLASS = 9;
+constexpr int MAX_HALVES = GRAM_TOPS - 1;  // of the ring of new rows; a block's products are with all but one of them and the top
 constexpr int64_t SCORE_CHUNK = 2048;  // rows per projection launch
 enum { K_GRAM = 0, K_REDUCE, K_EIG, K_REBUILD = 4, K_INSERT, K_PROJECT, K_FINALIZE, K_SELECT };
 
@@ -52,26 +54,41 @@ struct sage_ctx {
     int num_cu = 256;
 
     // The 2*ell-row buffer is kept as two half buffers of LP rows each (column-slab layout): `top` holds buffer rows
-    // 0 .. ell-1 (after a shrink: the rows it wrote), nw[cur] holds buffer rows ell .. 2*ell-1 as they arrive. Two new
-    // halves alternate so that the rows of the next cycle can be stored, and their own Gram block formed, on a side
-    // stream while the eigensolve of the current cycle runs.
+    // 0 .. ell-1 (after a shrink: the rows it wrote), half df.cur of the ring holds buffer rows ell .. 2*ell-1 as they arrive.
+    // Two of the ring's halves alternate so that the rows of the next cycle can be stored, and their own Gram block formed, on a
+    // side stream while the eigensolve of the current cycle runs; the others hold blocks whose shrink is deferred (see below).
     float* top = nullptr;
-    float* nw[2] = {nullptr, nullptr};
-    int cur = 0;
+    float* ring = nullptr;
+    int64_t half_floats = 0;
+    int halves = 0;
+    float* nw(int i) const { return ring + i * half_floats; }
+    DeferPlan df{};  // df.cur: the current half
+    int par = 0;                       // of the cycle: which of gram_partial_new, ev_side and gp_side_used are those of half cur
     SideKit kit{};                               // the stream, events and host word the next five name
     hipStream_t st2 = nullptr;                   // side stream (only when the Gram has >= 2 row panels)
     hipEvent_t ev_mark = nullptr;                // context stream: the Gram matrix of the current cycle is complete
-    hipEvent_t ev_side[2] = {nullptr, nullptr};  // side stream: rows stored in nw[i] and their Gram block formed
+    hipEvent_t ev_side[2] = {nullptr, nullptr};  // side stream: rows stored ahead and their Gram block formed, by par
     int* side_hole = nullptr;                    // the place its launches leave out (spare_unit_at)
     bool pending_shrink = false;   // the buffer is full, its shrink waits for the next update call (see sage_fd_update)
-    bool pre_stored = false;       // the side stream has stored the next ell rows of the running call in nw[cur]
-    bool new_block_ready = false;  // ... and their Gram block is (or will be, see ev_side) in gram_partial_new[cur]
+    bool pre_stored = false;       // the side stream has stored the next ell rows of the running call in half cur
+    bool new_block_ready = false;  // ... and their Gram block is (or will be, see ev_side) in gram_partial_new[par]
+    // Deferred shrinks (fd_defer.hip). The buffer's top rows are W [top; the blocks of df], with blocks only inside an update call: it
+    // ends with the rows written, so that everything else finds them in `top`.
+    bool folded = true;         // W includes the last shrink's M
+    double* M[2] = {nullptr, nullptr};  // M[mi]: the last shrink's coefficients
+    double* Wb[2] = {nullptr, nullptr};
+    const double* W = nullptr;
+    int mi = 0, wi = 0, ldw = 0, ldk = 0;
+    double* K = nullptr;        // products of the next block's rows with [W [top; blocks]; cur], then those with top and blocks
+    double* C_next = nullptr;   // the Gram matrix of the next cycle, as far as it is known
+    bool C_ready = false;       // ew.C is the whole Gram matrix of the coming shrink
+    bool marked = false;        // ev_mark is recorded after the last work of the context stream that the side stream must wait for
     GramPlan gp{};        // whole lower triangle
     GramPlan gp_skip{};   // without the top x top block (known after a shrink)
     GramPlan gp_cross{};  // new rows x top rows
     // ... and their counterparts for the split-arithmetic kernels (tiles = 0: not available for this sketch size)
     GramPlan gp_cross_split{}, gp_new_split{}, gp_new2_split{};
-    const GramPlan* gp_side_used[2] = {nullptr, nullptr};  // the plan the side stream's launch into gram_partial_new[i] used
+    const GramPlan* gp_side_used[2] = {nullptr, nullptr};  // the plan the launch into gram_partial_new[i] used
     GramPlan gp_new{};    // new rows x new rows, one work-group per CU (it shares the chip with the eigensolve)
     GramPlan gp_new2{};   // the same block with the chip to itself (context stream, when there was nothing to look ahead to)
     bool top_shrunk = false;  // top holds exactly what the last shrink wrote
@@ -83,10 +100,10 @@ struct sage_ctx {
     void* Mt3 = nullptr;   // the rebuild's coefficients split into bf16 parts (SAGE_MM_SPLIT)
     int mm_mode = SAGE_MM_SPLIT;
     // Rows of a bf16 stream are kept as fp32 but have one bf16 part, not three: the split-arithmetic kernels then skip
-    // the products with the new rows' mid and lo parts (exact zeros; same bits). nw_bf16[i]: every row in use in nw[i]
+    // the products with the new rows' mid and lo parts (exact zeros; same bits). nw_bf16[i]: every row in use in half i
     // came from a bf16 batch (row-major or factored; not sage_fd_merge's fp32 rows). one_part: the shortcut is allowed (off under SAGE_MM_SPLIT_ALL_PARTS).
-    bool nw_bf16[2] = {false, false};
-    bool nw_half[2] = {false, false};  // nw[i] is kept in pieces of bf16 (half16), not as fp32
+    bool nw_bf16[MAX_HALVES] = {};
+    bool nw_half[MAX_HALVES] = {};  // half i is kept in pieces of bf16 (half16), not as fp32
     bool one_part = true;
     double* acc = nullptr;  // [0] sum_delta [1] frob2 [2] last_delta [4] EigWork::redone
 
@@ -303,11 +320,11 @@ bool split_grams(const sage_ctx* c) {
     return c->mm_mode == SAGE_MM_SPLIT && c->gp_cross_split.tiles > 0 && c->gp_new2_split.tiles > 0;
 }
 
-// The new half nw[i] as fp32 (on the context stream; the side stream is done with it): for the kernels that know no other form.
+// Half i of the ring as fp32 (on the context stream; the side stream is done with it): for the kernels that know no other form.
 int widen(sage_ctx* c, int i) {
     if (!c->nw_half[i]) return SAGE_OK;
-    if (c->st2) HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[i], 0));  // (never recorded: nothing to wait for)
-    HIPCHK(launch_widen(c->nw[i], c->d, c->st));
+    if (c->st2 && i == c->df.cur) HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[c->par], 0));  // (never recorded: nothing to wait for)
+    HIPCHK(launch_widen(c->nw(i), c->d, c->st));
     c->nw_half[i] = false;
     return SAGE_OK;
 }
@@ -320,7 +337,7 @@ HostSignal next_signal(sage_ctx* c) {
     return s;
 }
 
-// Rows of `s` are about to be stored in nw[i] from row row0 on (by the context stream unless row0 = 0).
+// Rows of `s` are about to be stored in half i from row row0 on (by the context stream unless row0 = 0).
 int note_new_rows(sage_ctx* c, int i, int row0, const RowSrc& s) {
     const bool b = s.dtype == SAGE_BF16;  // factored rows of a bf16 context are rounded to bf16 when they are stored
     if (row0 == 0) c->nw_half[i] = b && c->d.NP == 512 && c->one_part && split_grams(c) && c->Mt3;
@@ -465,11 +482,11 @@ hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf
 // the latter's kernel, top x top (at D = 2,049,000 the fp32 kernel took 5.4 ms for it, this takes 2.6 for bf16 and 2.9 for fp32 rows). The side stream
 // is idle here.
 int gram_whole_split(sage_ctx* c, hipEvent_t mark = nullptr) {
-    const int i = c->cur, o = i ^ 1;
-    const bool one = new_one(c, i);
+    const int i = c->par, o = i ^ 1;
+    const bool one = new_one(c, c->df.cur);
     RUN(K_GRAM, launch_gram(c->top, c->top, c->fill_top, c->gram_partial_new[o], c->gp_new2_split, c->d, c->st));
-    RUN(K_GRAM, launch_gram(c->top, c->nw[i], c->fill_new, c->gram_partial_new[i], c->gp_new2_split, c->d, c->st, one));
-    RUN(K_GRAM, launch_gram(c->top, c->nw[i], c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
+    RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial_new[i], c->gp_new2_split, c->d, c->st, one));
+    RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
     RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, c->gp_cross_split, c->gram_partial_new[i], &c->gp_new2_split, c->ew.C,
                                      false, c->ew.known, c->d, c->st, c->gram_partial_new[o], &c->gp_new2_split, mark));
     return SAGE_OK;
@@ -490,89 +507,246 @@ int decompose(sage_ctx* c, const CoeffArgs& cf) {
     } else if (skip && split_grams(c) && !c->new_block_ready && !c->pre_stored) {
         // the two blocks that are not known, with the split-arithmetic kernels (the side stream is idle here: its
         // partial buffer of the current half is free)
-        const bool one = new_one(c, c->cur);
-        RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
-        RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial_new[c->cur], c->gp_new2_split, c->d,
+        const bool one = new_one(c, c->df.cur);
+        RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
+        RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial_new[c->par], c->gp_new2_split, c->d,
                                 c->st, one));
-        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, c->gp_cross_split, c->gram_partial_new[c->cur], &c->gp_new2_split,
+        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, c->gp_cross_split, c->gram_partial_new[c->par], &c->gp_new2_split,
                                          c->ew.C, true, c->ew.known, c->d, c->st));
     } else {
         const GramPlan& gp = skip ? c->gp_skip : c->gp;
-        if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
-        RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, gp, c->d, c->st));
+        if (int rc = widen(c, c->df.cur); rc != SAGE_OK) return rc;
+        RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial, gp, c->d, c->st));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st));
     }
     RUN(K_EIG, eigensolve(c, c->fill_top, c->fill_top + c->fill_new, cf.count, &cf));
     return SAGE_OK;
 }
 
-// The buffer is full: shrink it (Method, FD paragraph). Leaves top = the ell new rows and the other new half current.
-// next / next_rows: what is left of the running update call after this buffer. If a whole further cycle of rows is
-// there, they are stored in the other new half and their own Gram block is formed on the side stream while the
-// eigensolve runs on the context stream (neither needs its result, and the eigensolve leaves most of the chip idle).
-// The next ell rows of the running call into the other new half and their own Gram block, on the side stream.
-int side_ahead(sage_ctx* c, const RowSrc* next) {
-    // The other half was last read by the rebuild before last, which precedes the mark on the context stream.
-    const int LP = c->d.LP, ell = c->d.ell, o = c->cur ^ 1;
-    if (capturing(c->st)) HIPCHK(hipEventRecord(c->ev_mark, c->st));  // (else the Gram reduction's launch recorded it)
+// The side stream goes on after what the context stream has been given so far.
+int side_follow(sage_ctx* c) {
+    if (!c->marked || capturing(c->st)) HIPCHK(hipEventRecord(c->ev_mark, c->st));  // (else it rode on the last launch)
     HIPCHK(hipStreamWaitEvent(c->st2, c->ev_mark, 0));
-    if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
-    int* const hole = c->ew.period == 8 ? c->side_hole : nullptr;
-    if (hole) HIPCHK(launch_xcd_place(c->ew.xcd, hole, c->st2));
-    HIPCHK(insert_rows(*next, ell, 0, c->nw[o], LP, c->d, c->nw_half[o], c->st2, hole));
-    c->gp_side_used[o] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
-    HIPCHK(launch_gram(c->top, c->nw[o], ell, c->gram_partial_new[o], *c->gp_side_used[o], c->d, c->st2, new_one(c, o), hole));
-    HIPCHK(hipEventRecord(c->ev_side[o], c->st2));
     return SAGE_OK;
 }
 
+// The next ell rows of the running call into another half and their own Gram block, on the side stream.
+int side_ahead(sage_ctx* c, const RowSrc* next, const int* hole) {
+    const int LP = c->d.LP, ell = c->d.ell, o = c->df.next = c->df.free_half(), pn = c->par ^ 1;
+    if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
+    HIPCHK(insert_rows(*next, ell, 0, c->nw(o), LP, c->d, c->nw_half[o], c->st2, hole));
+    c->gp_side_used[pn] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
+    HIPCHK(launch_gram(c->top, c->nw(o), ell, c->gram_partial_new[pn], *c->gp_side_used[pn], c->d, c->st2, new_one(c, o), hole));
+    return SAGE_OK;
+}
+
+// Whether this shrink may leave its rows unwritten: the block and the next one are kept in the same form.
+bool may_defer(const sage_ctx* c, const RowSrc& next) {
+    return c->df.max > 0 && c->mm_mode == SAGE_MM_SPLIT && next.dtype == c->dtype &&
+           c->nw_bf16[c->df.cur] == (c->dtype == SAGE_BF16) &&
+           (c->d.NP < 512 || (c->Mt3 && split_grams(c) && c->nw_half[c->df.cur] == (c->one_part && c->dtype == SAGE_BF16)));
+}
+// (the blocks are all in the form that may_defer asks for)
+bool blocks_one_part(const sage_ctx* c) { return c->one_part && c->dtype == SAGE_BF16; }
+
+// W takes in the last shrink's M.
+hipError_t fold_shrink(sage_ctx* c, hipStream_t st) {
+    const int LP = c->d.LP, n = c->df.count;
+    if (n < 1 || n > c->df.max) return hipErrorInvalidValue;  // (what the buffers are made for)
+    c->folded = true;
+    if (n == 1) {
+        c->W = c->M[c->mi];
+        c->ldw = c->d.NP;
+        return hipSuccess;
+    }
+    const double* const W = c->W;
+    const int ldw = c->ldw;
+    c->W = c->Wb[c->wi ^= 1];
+    c->ldw = (1 + c->df.max) * LP;
+    return launch_defer_compose(c->M[c->mi], W, ldw, n * LP, c->Wb[c->wi], c->ldw, c->d, st);
+}
+
+// The rows of the deferred shrinks: top <- W [top; blocks].
+hipError_t write_rows(sage_ctx* c, hipStream_t st, const int* hole) {
+    const int LP = c->d.LP;
+    if (!c->folded)
+        if (hipError_t e = fold_shrink(c, st); e != hipSuccess) return e;
+    const NewBlocks b{c->ring, c->half_floats, c->df.slots, c->df.count};
+    if (b.count < 1 || b.count > c->df.max) return hipErrorInvalidValue;
+    c->df.written();
+    if (hipError_t e = launch_defer_coeffs(c->W, c->ldw, (1 + b.count) * LP, c->Mt, c->Mt3, c->d, st); e != hipSuccess) return e;
+    if (c->Mt3) return launch_rebuild_split(c->top, b, c->d.ell, c->Mt3, c->top, LP, LP, c->d, st, blocks_one_part(c), hole);
+    return launch_rebuild(c->top, b, c->d.ell, c->Mt, c->top, LP, LP, c->d, st, hole);
+}
+
+// Products of the rows of half o with `top` and with the blocks b, partial tiles one after the other.
+const GramPlan& cross_plan(const sage_ctx* c) { return c->gp_cross_split.tiles > 0 ? c->gp_cross_split : c->gp_cross; }
+hipError_t cross_top(sage_ctx* c, int o, hipStream_t st, const int* hole) {
+    return launch_gram_tops(GramTops{{c->top}, 0, c->d.ell}, 1, c->nw(o), c->d.ell, c->gram_partial, cross_plan(c), c->d, st,
+                            new_one(c, o), hole);
+}
+hipError_t cross_blocks(sage_ctx* c, int o, const NewBlocks& b, hipStream_t st, const int* hole) {
+    const GramPlan& gp = cross_plan(c);
+    GramTops tops{};
+    tops.rows = c->d.ell;
+    tops.stride = (int64_t)gp.partial_floats;
+    for (int j = 0; j < b.count; ++j) tops.p[j] = b.at(j);
+    if (c->d.NP == 512 && blocks_one_part(c))
+        return launch_gram_blocks(tops, b.count, c->nw(o), c->d.ell, c->gram_partial + tops.stride, gp, c->d, st, hole);
+    return launch_gram_tops(tops, b.count, c->nw(o), c->d.ell, c->gram_partial + tops.stride, gp, c->d, st, false, hole);
+}
+// ... with both, in one launch where their rows have the same form
+hipError_t cross_all(sage_ctx* c, int o, const NewBlocks& b, hipStream_t st, const int* hole) {
+    if (c->d.NP == 512 && blocks_one_part(c)) {
+        if (hipError_t e = cross_top(c, o, st, hole); e != hipSuccess) return e;
+        return cross_blocks(c, o, b, st, hole);
+    }
+    GramTops tops{};
+    tops.rows = c->d.ell;
+    tops.stride = (int64_t)cross_plan(c).partial_floats;
+    tops.p[0] = c->top;
+    for (int j = 0; j < b.count; ++j) tops.p[1 + j] = b.at(j);
+    return launch_gram_tops(tops, 1 + b.count, c->nw(o), c->d.ell, c->gram_partial, cross_plan(c), c->d, st, false, hole);
+}
+hipError_t cross_reduce(sage_ctx* c, int sources, const int* col, hipStream_t st) {
+    const GramPlan& gp = cross_plan(c);
+    const int pn = c->par ^ 1;
+    return launch_defer_reduce(c->gram_partial, (int64_t)gp.partial_floats, sources, col, gp, c->gram_partial_new[pn],
+                               *c->gp_side_used[pn], c->K, c->ldk, c->C_next, c->d, st);
+}
+
+// The blocks whose shrink is deferred, with the current one.
+NewBlocks blocks_and_cur(const sage_ctx* c) { return NewBlocks{c->ring, c->half_floats, c->df.slots_with_cur(), c->df.count + 1}; }
+
+// Beside the eigensolve of a shrink that will be deferred, on the side stream: the rows of earlier ones where it is time, the
+// next block, and its products with the buffer of the running shrink (columns 0 .. 2 LP - 1 of K).
+int side_defer(sage_ctx* c, const RowSrc* next, bool write_first, const int* hole) {
+    const int LP = c->d.LP;
+    if (!c->folded) HIPCHK(fold_shrink(c, c->st2));
+    if (write_first) HIPCHK(write_rows(c, c->st2, hole));
+    if (int rc = side_ahead(c, next, hole); rc != SAGE_OK) return rc;
+    const int n = c->df.count;
+    HIPCHK(cross_all(c, c->df.next, blocks_and_cur(c), c->st2, hole));
+    int col[GRAM_TOPS];
+    col[0] = n > 0 ? 2 * LP : 0;
+    for (int j = 0; j < n; ++j) col[1 + j] = (3 + j) * LP;
+    col[n + 1] = LP;
+    HIPCHK(cross_reduce(c, n + 2, col, c->st2));
+    if (n > 0) HIPCHK(launch_defer_fold(c->K + 2 * LP, c->ldk, c->W, c->ldw, (1 + n) * LP, c->K, c->ldk, c->d, c->st2));
+    return SAGE_OK;
+}
+
+// The buffer is full: shrink it (Method, FD paragraph). Leaves top = the ell new rows and another new half current.
+// next / next_rows: what is left of the running update call after this buffer. If a whole further cycle of rows is
+// there, they are stored in another new half and their own Gram block is formed on the side stream while the
+// eigensolve runs on the context stream (neither needs its result, and the eigensolve leaves most of the chip idle). Where
+// shrinks are deferred (fd_defer.hip), so are the products with the buffer, and the rows may stay unwritten.
 int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
     const int LP = c->d.LP, ell = c->d.ell;
     const bool ahead = use_side(c) && !c->prof && next && next_rows >= ell;
-    const hipEvent_t mark = ahead && !capturing(c->st) ? c->ev_mark : nullptr;
-    if (c->new_block_ready || (c->top_shrunk && c->gp_cross.tiles > 0)) {
+    const bool cap = capturing(c->st);
+    // (a captured update must find and leave the rows written)
+    const DeferPlan::Step step = c->df.step(ahead, !cap && ahead && may_defer(c, *next), next_rows, ell);
+    const hipEvent_t mark = ahead && !cap ? c->ev_mark : nullptr;
+    const bool have_C = c->C_ready && !cap;
+    c->C_ready = false;
+    if (have_C) {
+        // formed after the last eigensolve
+    } else if (c->new_block_ready || (c->top_shrunk && c->gp_cross.tiles > 0)) {
         // The top x top block is known. The new x new block came from the side stream, or is formed here when there
         // was nothing to look ahead to (first cycle of a call); then only new x top is left.
         const bool split = c->mm_mode == SAGE_MM_SPLIT;
-        const GramPlan* gn = c->gp_side_used[c->cur];
+        const GramPlan* gn = c->gp_side_used[c->par];
         if (c->new_block_ready) {
-            HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[c->cur], 0));
+            HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[c->par], 0));
         } else {
             gn = split && c->gp_new2_split.tiles > 0 ? &c->gp_new2_split : &c->gp_new2;
-            RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial_new[c->cur], *gn, c->d, c->st,
-                                    new_one(c, c->cur)));
+            RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), ell, c->gram_partial_new[c->par], *gn, c->d, c->st,
+                                    new_one(c, c->df.cur)));
         }
         const GramPlan& gc = split && c->gp_cross_split.tiles > 0 ? c->gp_cross_split : c->gp_cross;
-        RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial, gc, c->d, c->st, new_one(c, c->cur)));
-        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gc, c->gram_partial_new[c->cur], gn, c->ew.C, true,
+        RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), ell, c->gram_partial, gc, c->d, c->st, new_one(c, c->df.cur)));
+        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gc, c->gram_partial_new[c->par], gn, c->ew.C, true,
                                          c->ew.known, c->d, c->st, nullptr, nullptr, mark));
+        c->marked = mark != nullptr;
     } else if (!c->top_shrunk && split_grams(c)) {
         if (int rc = gram_whole_split(c, mark); rc != SAGE_OK) return rc;
+        c->marked = mark != nullptr;
     } else {
         const bool skip = c->top_shrunk && c->gp_skip.t0 > 0;
         const GramPlan& gp = skip ? c->gp_skip : c->gp;
-        if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
-        RUN(K_GRAM, launch_gram(c->top, c->nw[c->cur], ell, c->gram_partial, gp, c->d, c->st));
+        if (int rc = widen(c, c->df.cur); rc != SAGE_OK) return rc;
+        RUN(K_GRAM, launch_gram(c->top, c->nw(c->df.cur), ell, c->gram_partial, gp, c->d, c->st));
         RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, gp, nullptr, nullptr, c->ew.C, skip, c->ew.known, c->d, c->st, nullptr, nullptr, mark));
+        c->marked = mark != nullptr;
     }
     c->new_block_ready = false;
     if (ahead) {
         // after the Gram launches of this cycle: started beside them, the side stream's work (all of it, or the insert
         // alone) slowed the cross block more than it gained under the eigensolve (28.4 k against 29.7 k rows/s at
         // D = 2,049,000, both ways)
-        int rc = side_ahead(c, next);
-        if (rc != SAGE_OK) return rc;
+        if (int rc = side_follow(c); rc != SAGE_OK) return rc;
+        int* const hole = c->ew.period == 8 ? c->side_hole : nullptr;
+        if (hole) HIPCHK(launch_xcd_place(c->ew.xcd, hole, c->st2));
+        if (int rc = step.defer && c->df.beside ? side_defer(c, next, step.write_first, hole) : side_ahead(c, next, hole); rc != SAGE_OK) return rc;
+        if (step.defer && !c->df.beside && !step.last) HIPCHK(cross_blocks(c, c->df.next, blocks_and_cur(c), c->st2, hole));
+        HIPCHK(hipEventRecord(c->ev_side[c->par ^ 1], c->st2));
+    } else if (step.write_first) {
+        RUN(K_REBUILD, write_rows(c, c->st, nullptr));
+    } else if (c->df.count > 0 && !c->folded) {
+        RUN(K_REDUCE, fold_shrink(c, c->st));  // (the eigensolve writes the other M)
     }
-    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3;
-    const CoeffArgs cf{LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new, c->Mt,
-                       split_rb ? c->Mt3 : nullptr, c->acc};  // (row ell - 1 of the result is zero)
+    const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3, write_now = !step.defer && c->df.count == 0;
+    CoeffArgs cf{LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new, c->Mt,
+                 split_rb ? c->Mt3 : nullptr, c->acc};  // (row ell - 1 of the result is zero)
+    if (!write_now) cf.M = c->M[c->mi ^ 1];
     RUN(K_EIG, eigensolve(c, ell, 2 * ell, cf.count, &cf));
-    if (split_rb)
-        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], ell, c->Mt3, c->top, LP, LP, c->d, c->st,
-                                            new_one(c, c->cur)));
-    else
-        RUN(K_REBUILD, launch_rebuild(c->top, c->nw[c->cur], ell, c->Mt, c->top, LP, LP, c->d, c->st));
-    if (use_side(c)) c->cur ^= 1;  // two new halves alternate; with a single Gram panel there is only nw[0]
+    const NewBlocks one{c->ring, c->half_floats, (unsigned)c->df.cur, 1};
+    c->marked = false;
+    if (write_now) {
+        if (split_rb)
+            RUN(K_REBUILD, launch_rebuild_split(c->top, one, ell, c->Mt3, c->top, LP, LP, c->d, c->st, new_one(c, c->df.cur)));
+        else
+            RUN(K_REBUILD, launch_rebuild(c->top, one, ell, c->Mt, c->top, LP, LP, c->d, c->st));
+    } else {
+        c->mi ^= 1;
+        c->df.push();
+        c->folded = false;
+        const double* W = c->M[c->mi];
+        int ldw = c->d.NP, len = 2 * LP;
+        if (step.defer && !c->df.beside) {
+            RUN(K_REDUCE, fold_shrink(c, c->st));
+            if (!step.last) {
+                HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[c->par ^ 1], 0));
+                RUN(K_GRAM, cross_top(c, c->df.next, c->st, nullptr));
+                int col[GRAM_TOPS];
+                for (int j = 0; j <= c->df.count; ++j) col[j] = j * LP;
+                RUN(K_REDUCE, cross_reduce(c, 1 + c->df.count, col, c->st));
+                W = c->W;
+                ldw = c->ldw;
+                len = (1 + c->df.count) * LP;
+                c->C_ready = true;
+            }
+        } else if (step.defer) {
+            HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[c->par ^ 1], 0));
+            c->C_ready = true;
+        }
+        if (c->C_ready) {
+            RUN(K_REDUCE, launch_defer_cross(c->K, c->ldk, W, ldw, len, c->C_next, c->ew.known, c->d, c->st, c->ev_mark));
+            double* const C = c->ew.C;
+            c->ew.C = c->C_next;
+            c->C_next = C;
+            c->marked = true;
+        }
+        if (!step.defer || step.last) {
+            RUN(K_REBUILD, write_rows(c, c->st, nullptr));
+            c->marked = false;
+        }
+    }
+    if (use_side(c)) {  // (with a single Gram panel there is one new half only)
+        c->df.advance(ahead);
+        c->par ^= 1;
+    }
     c->fill_top = ell;
     c->cnt_top = ell;
     c->fill_new = 0;
@@ -656,6 +830,24 @@ int finish_basis(sage_ctx* c) {
     if (rc != SAGE_OK) return rc;
     c->img_ok = true;
     return SAGE_OK;
+}
+
+// Which contexts defer shrinks (fd_defer.hip). Us a cycle, at once / deferred, for calls of four cycles:
+// Beside the eigensolves while all work on the rows of a cycle is done before an eigensolve is; it then takes the insert, rectangles,
+// a triangle and the rebuild on seven XCDs instead of one rectangle and the rebuild in series. ell = 64, fp32 rows: 227 / 200 (D =
+// 51,300), 239 / 210 (131,072), 285 / 314 (262,144); 128: 424 / 392, 462 / 414, 571 / 639; 256, bf16: 965 / 853 (131,072), 1562 / 1412
+// (524,288), 2332 / 2564 (1,048,576). Three blocks where that costs next to nothing: the rows are rounded to fp32 a third as often. At 512
+// buffer rows it would cost a tenth (bf16, 131,072: 946 where one block takes 853). Wide fp32 rows gain 4% there (131,072: 1050 / 1009)
+// and stay as they are: their Gram blocks have the same bits however a stream is cut into calls.
+// Beyond, two at a time where that is less work: rows with one part cost three products per element in a rebuild, the top's six,
+// so two shrinks at once take 12 where one by one they take 18, for one more rectangle of one product (1,048,576: 2332 / 1994; four
+// at once 1998). For rows of three parts it would be as much work as before.
+void defer_plan(sage_ctx* c) {
+    const int64_t D = c->d.D;
+    if (c->d.NP < 128) return;
+    const bool one = c->dtype == SAGE_BF16 && c->d.NP == 512;
+    c->df.beside = D <= (c->d.NP < 512 ? 196608 : one ? 589824 : 131071);
+    c->df.max = c->df.beside ? (c->d.NP < 512 ? 3 : 1) : one ? 2 : 0;
 }
 
 int64_t keep_count(double keep_rate, int64_t N) {
@@ -750,16 +942,20 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     do {                                                                          \
         if (!dev_alloc(c->mem, c->st, (void**)&(ptr), (bytes))) return fail(SAGE_ERR_ALLOC); \
     } while (0)
+    defer_plan(c);
+    c->half_floats = (int64_t)(hbytes / sizeof(float));
+    c->halves = P < 2 ? 1 : c->df.halves();
     CALLOC(c->top, hbytes);
-    CALLOC(c->nw[0], hbytes);
+    CALLOC(c->ring, (size_t)c->halves * hbytes);
     {
         size_t pf = c->gp.partial_floats;
         if (c->gp_skip.partial_floats > pf) pf = c->gp_skip.partial_floats;
-        if (c->gp_cross.partial_floats > pf) pf = c->gp_cross.partial_floats;
+        // deferred shrinks: a block's products with the top and up to defer_max blocks
+        const size_t pc = c->gp_cross.partial_floats * (1 + c->df.max);
+        if (pc > pf) pf = pc;
         CALLOC(c->gram_partial, pf * sizeof(float));
     }
     if (P >= 2) {
-        CALLOC(c->nw[1], hbytes);
         const size_t pn = c->gp_new.partial_floats > c->gp_new2.partial_floats ? c->gp_new.partial_floats
                                                                                 : c->gp_new2.partial_floats;
         CALLOC(c->gram_partial_new[0], pn * sizeof(float));
@@ -782,6 +978,14 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             take(w.xch, 8 * n1);
             take(w.stat, 32);
             take(w.C, n2);
+            if (c->df.max > 0) {
+                const size_t lp = (size_t)c->d.LP;
+                c->ldk = (c->df.max + 2) * c->d.LP;
+                take(c->C_next, n2);
+                for (int i = 0; i < 2; ++i) take(c->M[i], lp * n1);
+                for (int i = 0; i < 2; ++i) take(c->Wb[i], lp * lp * (1 + c->df.max));
+                take(c->K, lp * c->ldk);
+            }
             take(w.Yt, n2);
             take(w.V, n2);
             take(w.Tw, 8 * n1);
@@ -794,8 +998,9 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
         }
         xcd_take(c);
     }
-    CALLOC(c->Mt, (size_t)NP * c->d.LP * sizeof(float));
-    if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(c->d, c->d.LP));
+    const int brows = (c->df.max > 1 ? 1 + c->df.max : 2) * c->d.LP;
+    CALLOC(c->Mt, (size_t)brows * c->d.LP * sizeof(float));
+    if (rebuild_split_ok(c->d.LP)) CALLOC(c->Mt3, rebuild_split_bytes(brows, c->d.LP));
     CALLOC(c->acc, 8 * sizeof(double));
     c->ew.redone = c->acc + 4;
     c->ew.claim = (unsigned*)(c->ew.stat + 16);
@@ -817,7 +1022,7 @@ void sage_destroy(sage_ctx* c) {
     if (!c) return;
     (void)hipStreamSynchronize(c->st);
     if (c->st2) (void)hipStreamSynchronize(c->st2);
-    void* ptrs[] = {c->top,     c->nw[0],    c->nw[1],  c->gram_partial, c->gram_partial_new[0], c->gram_partial_new[1],
+    void* ptrs[] = {c->top,     c->ring,     c->gram_partial, c->gram_partial_new[0], c->gram_partial_new[1],
                     c->eig_mem, c->Mt,       c->acc,    c->Vblk,         c->img[0].mem, c->img[1].mem,
                     c->zhat,    c->proj_partial, c->cons_partial, c->ssum, c->alpha, c->labels, c->cb_work, c->stage, c->Mt3, c->dbg_count};
     for (void* p : ptrs) dev_free(c->mem, p);
@@ -863,8 +1068,8 @@ static int update_rows(sage_ctx* c, RowSrc g, int64_t rows) {
             c->fill_new = ell;
         } else {
             take = (int)((int64_t)(ell - c->fill_new) < rows ? (ell - c->fill_new) : rows);
-            if (int rc = note_new_rows(c, c->cur, c->fill_new, g); rc != SAGE_OK) return rc;
-            RUN(K_INSERT, insert_rows(g, take, c->fill_new, c->nw[c->cur], LP, c->d, c->nw_half[c->cur], c->st));
+            if (int rc = note_new_rows(c, c->df.cur, c->fill_new, g); rc != SAGE_OK) return rc;
+            RUN(K_INSERT, insert_rows(g, take, c->fill_new, c->nw(c->df.cur), LP, c->d, c->nw_half[c->df.cur], c->st));
             c->fill_new += take;
         }
         c->rows_seen += take;
@@ -877,7 +1082,7 @@ static int update_rows(sage_ctx* c, RowSrc g, int64_t rows) {
                 // the half just completed: the context stream waits for it, so that the batch is free once this
                 // call's work is complete there.
                 c->pending_shrink = true;
-                if (c->new_block_ready) HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[c->cur], 0));
+                if (c->new_block_ready) HIPCHK(hipStreamWaitEvent(c->st, c->ev_side[c->par], 0));
             } else {
                 int rc = shrink(c, &g, rows);
                 if (rc != SAGE_OK) return rc;
@@ -964,13 +1169,14 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     if (rc != SAGE_OK) return rc;
     c->cnt_top = c->fill_top;
     c->cnt_new = c->fill_new;
+    const NewBlocks rows{c->ring, c->half_floats, (unsigned)c->df.cur, 1};
     if (split_rb)
-        RUN(K_REBUILD, launch_rebuild_split(c->top, c->nw[c->cur], c->fill_new, c->Mt3, c->Vblk, KP, KP, c->d, c->st,
-                                            c->fill_new > 0 && new_one(c, c->cur)));
+        RUN(K_REBUILD, launch_rebuild_split(c->top, rows, c->fill_new, c->Mt3, c->Vblk, KP, KP, c->d, c->st,
+                                            c->fill_new > 0 && new_one(c, c->df.cur)));
     else {
         if (c->fill_new > 0)
-            if (int rcw = widen(c, c->cur); rcw != SAGE_OK) return rcw;
-        RUN(K_REBUILD, launch_rebuild(c->top, c->nw[c->cur], c->fill_new, c->Mt, c->Vblk, KP, KP, c->d, c->st));
+            if (int rcw = widen(c, c->df.cur); rcw != SAGE_OK) return rcw;
+        RUN(K_REBUILD, launch_rebuild(c->top, rows, c->fill_new, c->Mt, c->Vblk, KP, KP, c->d, c->st));
     }
     c->k = k;
     c->KP = KP;
@@ -994,8 +1200,9 @@ int sage_set_update_arithmetic(sage_ctx* c, int mode) {
     if (mode != SAGE_MM_F32 && mode != SAGE_MM_SPLIT && mode != SAGE_MM_SPLIT_ALL_PARTS) return SAGE_ERR_ARG;
     c->mm_mode = mode == SAGE_MM_F32 ? SAGE_MM_F32 : SAGE_MM_SPLIT;
     c->one_part = mode != SAGE_MM_SPLIT_ALL_PARTS;
+    c->C_ready = false;  // a shrink that is pending forms its products in the new arithmetic
     if (mode != SAGE_MM_SPLIT)
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < c->halves; ++i)
             if (int rc = widen(c, i); rc != SAGE_OK) return rc;
     return SAGE_OK;
 }
@@ -1338,9 +1545,9 @@ int sage_fd_sketch_export(sage_ctx* c, float* B_out) {
     const int ell = c->d.ell;
     if (int rc = clear_top(c); rc != SAGE_OK) return rc;
     if (c->fill_new > 0)
-        if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
+        if (int rc = widen(c, c->df.cur); rc != SAGE_OK) return rc;
     HIPCHK(launch_export_rows(c->top, c->d.LP, ell, B_out, c->d, c->st));
-    HIPCHK(launch_export_rows(c->nw[c->cur], c->d.LP, c->fill_new, B_out + (size_t)ell * c->d.D, c->d, c->st));
+    HIPCHK(launch_export_rows(c->nw(c->df.cur), c->d.LP, c->fill_new, B_out + (size_t)ell * c->d.D, c->d, c->st));
     if (c->fill_new < ell)
         HIPCHK(hipMemsetAsync(B_out + (size_t)(ell + c->fill_new) * c->d.D, 0,
                               (size_t)(ell - c->fill_new) * c->d.D * sizeof(float), c->st));
@@ -1409,8 +1616,8 @@ int sage_stats(sage_ctx* c, sage_stats_t* out) {
         if (split_grams(c) && !c->new_block_ready && !c->pre_stored) {
             if (int rc = gram_whole_split(c); rc != SAGE_OK) return rc;
         } else {
-            if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
-            e = launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp, c->d, c->st);
+            if (int rc = widen(c, c->df.cur); rc != SAGE_OK) return rc;
+            e = launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial, c->gp, c->d, c->st);
             if (e == hipSuccess)
                 e = launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st);
             if (e != hipSuccess) return hip_failed(c);
@@ -1450,8 +1657,8 @@ int sage_probe_gram_eig(sage_ctx* c, double* C_out, int eig, double* Y_out, doub
     int rcf = flush_pending(c);
     if (rcf != SAGE_OK) return rcf;
     if (int rc = clear_top(c); rc != SAGE_OK) return rc;
-    if (int rc = widen(c, c->cur); rc != SAGE_OK) return rc;
-    HIPCHK(launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp, c->d, c->st));
+    if (int rc = widen(c, c->df.cur); rc != SAGE_OK) return rc;
+    HIPCHK(launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial, c->gp, c->d, c->st));
     HIPCHK(launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st));
     // Inside the library matrix index LP + j stands for buffer row ell + j; the probe reports buffer-row order
     // (rows 0 .. 2*ell-1, padding last).
@@ -1475,10 +1682,10 @@ int sage_probe_gram_split(sage_ctx* c, double* C_out, int* n_pad) {
     if (rcf != SAGE_OK) return rcf;
     if (c->new_block_ready || c->pre_stored) return SAGE_ERR_STATE;  // (never after flush_pending)
     if (int rc = clear_top(c); rc != SAGE_OK) return rc;
-    const bool one = c->fill_new > 0 && new_one(c, c->cur);
-    HIPCHK(launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
-    HIPCHK(launch_gram(c->top, c->nw[c->cur], c->fill_new, c->gram_partial_new[c->cur], c->gp_new2_split, c->d, c->st, one));
-    HIPCHK(launch_gram_reduce(c->gram_partial, c->gp_cross_split, c->gram_partial_new[c->cur], &c->gp_new2_split, c->ew.C,
+    const bool one = c->fill_new > 0 && new_one(c, c->df.cur);
+    HIPCHK(launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial, c->gp_cross_split, c->d, c->st, one));
+    HIPCHK(launch_gram(c->top, c->nw(c->df.cur), c->fill_new, c->gram_partial_new[c->par], c->gp_new2_split, c->d, c->st, one));
+    HIPCHK(launch_gram_reduce(c->gram_partial, c->gp_cross_split, c->gram_partial_new[c->par], &c->gp_new2_split, c->ew.C,
                               false, c->ew.known, c->d, c->st));
     HIPCHK(launch_probe_permute(c->ew.C, C_out, NP, LP, ell, true, c->st));
     HIPCHK(hipStreamSynchronize(c->st));

@@ -136,6 +136,19 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
 // has the same bits
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
                        hipStream_t st, bool new_one = false, const int* hole = nullptr);
+// Mode 1 with several half buffers for the top rows: the partial tiles of p[j] are `stride` floats after those of p[j - 1]. (NP <= 256
+// or a split plan.)
+constexpr int GRAM_TOPS = 6;
+struct GramTops {
+    const float* p[GRAM_TOPS];
+    int64_t stride;
+    int rows;  // of each; what a half holds beyond counts as zero
+};
+hipError_t launch_gram_tops(const GramTops& tops, int count, const float* nw, int nfill, float* partial, const GramPlan& p,
+                            const Dims& d, hipStream_t st, bool new_one, const int* hole);
+// ... all of them and the new half kept in pieces of bf16 (half16; NP = 512, a split plan)
+hipError_t launch_gram_blocks(const GramTops& tops, int count, const float* nw, int nfill, float* partial, const GramPlan& p,
+                              const Dims& d, hipStream_t st, const int* hole);
 // C = sum of the partial tiles of launch a and (if given) launch b; known_top: the top x top block is diag(known)
 // (the Gram matrix of the rows the last shrink wrote, see EigWork::known). done: recorded when C is complete (may be null; not
 // on a stream that is captured)
@@ -177,19 +190,37 @@ hipError_t launch_xcd_place(int xcd, int* place, hipStream_t st);  // *place: 0 
 const XcdMap& xcd_map();  // of the launches on some stream of the current device; asked once per device
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
-// Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into Mc3 (split
-// parts) if given, else into Mt. Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1)
+// Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into M if given, else into
+// Mc3 (split parts) if given, else into Mt. Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1)
 // and [rb0, rb1), the rows not yet counted), acc[2] last_delta. (acc[4]: EigWork::redone)
 struct CoeffArgs {
     int MP, count, mode, n, ell, ra0, ra1, rb0, rb1;
     float* Mt;
     void* Mc3;
     double* acc;
+    double* M = nullptr;  // given: the coefficients go here in fp64, MP x NP in matrix indices, and to neither of the above
 };
 // the `count` leading eigenvectors into Yt, or (cf given) only the coefficients made from them
 hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st);
 hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st);
 hipError_t launch_eig_export(const EigWork& w, int NP, double* Y, double* lam, double* record, hipStream_t st);
+
+// fd_defer.hip: shrinks whose rows are written later. LP = 64, 128, 256; all in fp64.
+// Partial tiles of `sources` rectangles (launch_gram_tops with plan pc, `stride` floats apart) into K, source s from column col[s]
+// on, and of the new x new triangle (plan pn) into C.
+hipError_t launch_defer_reduce(const float* cross, int64_t stride, int sources, const int* col, const GramPlan& pc, const float* fresh,
+                               const GramPlan& pn, double* K, int ldk, double* C, const Dims& d, hipStream_t st);
+// out (LP x LP) = K W^T over `len` columns
+hipError_t launch_defer_fold(const double* K, int ldk, const double* W, int ldw, int len, double* out, int ldo, const Dims& d,
+                             hipStream_t st);
+// ... into the new x top rectangle of C; its top x top block becomes diag(known)
+hipError_t launch_defer_cross(const double* K, int ldk, const double* W, int ldw, int len, double* C, const double* known,
+                              const Dims& d, hipStream_t st, hipEvent_t done);
+// out = [M_top W, M_new], W of `cols` columns
+hipError_t launch_defer_compose(const double* M, const double* W, int ldw, int cols, double* out, int ldo, const Dims& d,
+                                hipStream_t st);
+// the rebuild's coefficients of W's first `rows` columns, into Mc3 if given, else into Mt
+hipError_t launch_defer_coeffs(const double* W, int ldw, int rows, float* Mt, void* Mc3, const Dims& d, hipStream_t st);
 
 // Where the coefficient M[m][i] (output row m < MP, buffer row i < NP) is stored for the rebuild kernel: chunks of
 // 16 buffer rows; inside a chunk [i & 1][m][(i & 15) >> 1], i.e. the 8 values a matrix-core lane needs are
@@ -201,19 +232,28 @@ __host__ __device__ inline int64_t coeff_offset(int i, int m, int MP) {
     return (int64_t)(i >> 4) * 16 * MP + ((h * MP + m) * 2 + piece) * 4 + (s & 3);
 }
 
-// fd_rebuild.hip: out[0:MP] = M * B over every column, B = [top; first nfill rows of nw; zeros]; Mc holds the NP x MP
-// coefficients in coeff_offset order; out has out_NP rows per slab and may be `top` itself (in place).
-hipError_t launch_rebuild(const float* top, const float* nw, int nfill, const float* Mc, float* out, int out_NP, int MP,
-                          const Dims& d, hipStream_t st);
+// Blocks of new rows that lie in one ring of half buffers: block b is slot (slots >> 4 b) & 15 of it.
+struct NewBlocks {
+    const float* ring = nullptr;
+    int64_t stride = 0;  // floats
+    unsigned slots = 0;
+    int count = 0;
+    __host__ __device__ __forceinline__ int64_t offset(int b) const { return (int64_t)(slots >> (4 * b) & 15u) * stride; }
+    __host__ __device__ __forceinline__ const float* at(int b) const { return ring + offset(b); }
+};
+// fd_rebuild.hip: out[0:MP] = M * B over every column, B = [top; the blocks, the first nfill rows of each in use]; Mc holds the
+// coefficients, LP (1 + blocks) x MP, in coeff_offset order; out has out_NP rows per slab and may be `top` itself (in place).
+hipError_t launch_rebuild(const float* top, const NewBlocks& nw, int nfill, const float* Mc, float* out, int out_NP, int MP,
+                          const Dims& d, hipStream_t st, const int* hole = nullptr);
 // The same product on the bf16 matrix cores with both factors split into three bf16 parts (six products: 24-bit
-// accuracy at 2.7 times the fp32 matrix-core rate). Mc3: the split coefficients, rebuild_split_bytes(d, MP) bytes. Only for
-// MP = 128 or 256 (rebuild_split_ok).
+// accuracy at 2.7 times the fp32 matrix-core rate). Mc3: the split coefficients of `rows` buffer rows, rebuild_split_bytes(rows, MP)
+// bytes. Only for MP = 128 or 256 (rebuild_split_ok).
 bool rebuild_split_ok(int MP);
-size_t rebuild_split_bytes(const Dims& d, int MP);
-// new_one: every new row in use holds bf16 values (three products instead of six for the new half, the same bits); at NP = 512
-// the new half is then kept in pieces of bf16.
-hipError_t launch_rebuild_split(const float* top, const float* nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
-                                const Dims& d, hipStream_t st, bool new_one = false);
+size_t rebuild_split_bytes(int rows, int MP);
+// new_one: every new row in use holds bf16 values (three products instead of six for the blocks, the same bits); at NP = 512
+// the blocks are then kept in pieces of bf16.
+hipError_t launch_rebuild_split(const float* top, const NewBlocks& nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
+                                const Dims& d, hipStream_t st, bool new_one = false, const int* hole = nullptr);
 
 // score.hip
 struct ScorePlan {

@@ -1,0 +1,73 @@
+"""Shrinks whose rows are written later (csrc/fd_defer.hip) against Frequent Directions in 64 bits, for streams cut into calls in the
+ways that take different paths through it."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _shrink(A, ell):
+    import torch
+
+    lam, Y = torch.linalg.eigh((A @ A.T).cpu())
+    lam, Y = lam.flip(0)[:ell].to(A.device), Y.flip(1)[:, :ell].to(A.device)
+    keep = (lam - lam[ell - 1]).clamp(min=0)
+    w = torch.where(keep > 0, (keep / lam.clamp(min=1e-300)).sqrt(), torch.zeros_like(keep))
+    return (w[:, None] * Y.T) @ A, float(lam[ell - 1])
+
+
+def _sketch64(G, ell):
+    """What is in the buffer after all rows: at least ell - 1 rows of a sketch and those that came after its last shrink."""
+    import torch
+
+    B, delta = G[:ell].double(), 0.0
+    for lo in range(ell, len(G), ell):
+        B = torch.cat([B, G[lo:lo + ell].double()])
+        if len(B) == 2 * ell:
+            B, d = _shrink(B, ell)
+            delta += d
+    return B, delta
+
+
+def _cov_diff(A, B):
+    """|A^T A - B^T B|_F without forming either: by the Gram matrix of all rows with signs."""
+    import torch
+
+    P = torch.cat([A, B])
+    K = P @ P.T
+    K[:, len(A):] *= -1.0
+    return float((K @ K).trace().clamp(min=0).sqrt())
+
+
+# 128, 256 and 512 buffer rows with and without padding, row types, widths that are a multiple of nothing; the last two widths are those
+# from which two shrinks at a time are put together, and beyond which wide fp32 rows do as before
+@pytest.mark.parametrize("ell,dtype,D", [(33, "f32", 701), (64, "f32", 5130), (64, "bf16", 2113), (65, "f32", 1300), (100, "bf16", 25447),
+                                         (128, "f32", 3001), (129, "bf16", 1999), (200, "f32", 2050), (256, "bf16", 4097),
+                                         (129, "bf16", 589_825), (129, "f32", 131_071)])
+def test_streams_in_calls_of_many_few_and_part_cycles(ell, dtype, D):
+    """The covariance is held to 1e-6 of |A|_F^2: nine cycles whose Gram entries carry fp32 sums of their slabs (a few 2^-24 of the rows'
+    norms) and whose rows are rounded to fp32 at most once each; 6e-8 is what such streams leave."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(ell + D)
+    N = 9 * ell + ell // 3
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    k = ell // 2
+    signal = torch.randn((N, k), generator=g, device="cuda") * torch.arange(1, k + 1, device="cuda") ** -0.5
+    G = (signal @ torch.randn((k, D), generator=g, device="cuda") + 0.1 * torch.randn((N, D), generator=g, device="cuda")).to(td)
+    want, delta = _sketch64(G, ell)
+    fro = float((G.double() ** 2).sum())
+    cuts = {"one call": [N], "whole cycles": [ell] * 9 + [ell // 3], "calls of several": [4 * ell, 3 * ell, 2 * ell, ell // 3],
+            "part cycles": [2 * ell + ell // 2, 3 * ell + 1, ell - 1, 2 * ell, N - 8 * ell - ell // 2]}
+    for name, sizes in cuts.items():
+        assert sum(sizes) == N
+        s, lo = Sage(ell, D, dtype=dtype), 0
+        for n in sizes:
+            s.fd_update(G[lo:lo + n].contiguous())
+            lo += n
+        st = s.stats()
+        assert st.rows_seen == N and st.n_unconverged == 0, name
+        assert abs(st.frob2 - fro) <= 1e-6 * fro and abs(st.sum_delta - delta) <= 1e-6 * fro, name
+        assert _cov_diff(s.sketch().double(), want) <= 1e-6 * fro, name
+        s.close()

@@ -42,6 +42,14 @@ def test_slots_of_the_reduction_are_emptied_in_time(tmp_path):
     assert _run(exe, "planted").returncode == 1
 
 
+def test_deferred_shrinks_leave_no_rows_behind(tmp_path):
+    """defer_check.cc; and the check itself: it must refuse blocks that are not written when there is room for no more."""
+    exe = _build(tmp_path, "defer_check")
+    r = _run(exe)
+    assert r.returncode == 0 and "defer_check ok" in r.stdout, r.stdout
+    assert _run(exe, "planted").returncode == 1
+
+
 def test_work_space_of_the_selection(tmp_path):
     """select_plan_check.cc; and the check itself: it must refuse a work space for the longest call alone."""
     exe = _build(tmp_path, "select_plan_check")
