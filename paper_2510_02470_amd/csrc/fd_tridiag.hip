@@ -64,6 +64,10 @@ __device__ __forceinline__ void householder(double alpha, double rest2, double& 
 }
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
+// Loads before it are made where they stand: the compiler would move each to the place where its value is known to be wanted, behind
+// a branch and with a wait of its own (16 elements of a matrix: 5 us).
+__device__ __forceinline__ void loads_go_out() { asm volatile("" ::: "memory"); }
+
 // Orders this wave's LDS traffic before the barrier and nothing else: __syncthreads() would also wait for the global
 // stores in flight.
 __device__ __forceinline__ void lds_barrier() {
@@ -73,242 +77,288 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // ---- n = 64 J, J = 1, 2: one work-group ---------------------------------------------------------------------------
-// Waves 0..3 hold the matrix as 16 x 16 threads of R x R elements (rows rs + 16 t, columns cs + 16 u), wave 4 forms the
-// reflectors, wave 5 stores them; waves 0..4 carry the vectors, each its own copy, so that a step has one barrier. Step k,
+// Waves 0 .. W - 1 hold the matrix, wave I its rows 16 I .. 16 I + 15: lane 16 g + r row 16 I + r of the columns 16 (g + 4 u) .. + 15, u < J.
+// So the 16 lanes of a row of the register file hold, at their own places 16 g + r + 64 u, the 16 entries of a vector that go with
+// its columns, and v_fmac_f64 with row_newbcast:c takes entry c for column c: the update and the product of a step are three
+// instructions per element, without a broadcast and without sums over lanes but for the four groups g. Wave W forms the
+// reflectors, wave W + 1 stores the results; all carry the vectors, each its own copy, so that a step has one barrier. Step k,
 // with x = column k below row k + 1 and w' of step k - 1:
-//   waves 0..3: a -= v' w'^T + w' v'^T, q = a x (summed over the 16 lanes of a row), c = column k + 1, their part of x A x;
-//   wave 4 meanwhile: the reflector (tau, v1) from |x|;                                                      barrier
+//   waves 0 .. W - 1: a -= v' w'^T + w' v'^T, q = a x, c = column k + 1, their part of x A x;
+//   wave W meanwhile: the reflector (tau, v1) from |x|;                                                      barrier
 //   all: v A v = x A x + 2 v1 q_{k+1} + v1^2 c_{k+1}, w = tau (q + v1 c) - tau^2/2 (v A v) v, next column c - v w_{k+1} - w v1.
-// A step is a chain of latencies (sum over a wave 160 cycles, LDS round trip 70, reductions over 16 lanes 105), at J = 2
-// also 3 x 64 fp64 operations a thread while nothing is done yet: finished rows and columns are left out at compile time, 16
-// steps at a time. n = 64: 43.5 us with the vectors on wave 4 alone and two barriers, 41.0 now; n = 128: 155
-// and 122. The sum v A v put together from parts leaves the solve's residual at 1.03 of what the sum over p v left (1500 matrices
-// of 64 rows, 1e-15 of the norm; orthogonality and eigenvalues as before).
+// A step is a chain of latencies (LDS round trip 110 cycles, sum over a wave 120) and of instructions of four cycles each, dependent
+// or not: 1,000 cycles where a SIMD has one of the waves, 2,050 where it has two (n = 128, first half: half the rows to a wave more, on
+// four waves, took 2,430). Steps come in sixteens, written out, so that column k + 1 is a register; those beyond the last row change
+// nothing. A wave whose rows are finished only keeps the barriers.
 struct __attribute__((aligned(16))) Pair { double a, b; };
 
+// a[c] += x(lane c of the row) s, c < 16. A DPP operand must not have been written by the two instructions before it, and the compiler
+// does not look into these: hence the waits, at the end for what follows. (An instruction that needs the result of the one before it
+// costs no more than another one, four cycles.)
+__device__ __forceinline__ void row_update(double (&a)[16], double x, double s) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %16, %17 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %16, %17 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %16, %17 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %16, %17 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %4, %16, %17 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %5, %16, %17 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %6, %16, %17 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %7, %16, %17 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %8, %16, %17 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %9, %16, %17 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %10, %16, %17 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %11, %16, %17 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %12, %16, %17 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %13, %16, %17 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %14, %16, %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %15, %16, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15])
+        : "v"(x), "v"(s));
+}
+// q += the sum over c of x(lane c of the row) a[c]
+__device__ __forceinline__ void row_product(double& q, double x, const double (&a)[16]) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(q)
+        : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9]), "v"(a[10]), "v"(a[11]), "v"(a[12]), "v"(a[13]), "v"(a[14]), "v"(a[15]));
+}
+// the value of the given lane (4 * lane in `at`)
+__device__ __forceinline__ double from_lane(double v, int at) {
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_ds_bpermute(at, (int)u), hi = __builtin_amdgcn_ds_bpermute(at, (int)(u >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 template <int J>
-__global__ __launch_bounds__(384, 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
-                                                         double* __restrict__ dT, double* __restrict__ eT,
-                                                         double* __restrict__ tauT, double* __restrict__ V,
-                                                         double* __restrict__ stat) {
-    constexpr int W = 4, N = 64 * J, RG = 4 * W, RT = N / RG, CT = N / 16;
-    __shared__ Pair qc[2][N];       // {q, c} by step parity
-    __shared__ Pair wx[W + 1][N];   // {w', x}: every wave's own copy
-    __shared__ double pp[2][W];     // partial sums of x A x
-    __shared__ Pair prm[2];         // {tau, v1}
-    __shared__ double vl[2][N];     // the reflector, by step parity
+__global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
+                                                                      double* __restrict__ dT, double* __restrict__ eT,
+                                                                      double* __restrict__ tauT, double* __restrict__ V,
+                                                                      double* __restrict__ stat) {
+    constexpr int W = 4 * J, N = 64 * J;
+    __shared__ Pair qc[2][N + 64];  // {q, c} by step parity; what is not wanted goes beyond them
+    __shared__ __attribute__((aligned(16))) double prm[2][2 * W];  // waves' sums of x A x, then tau, v1, off-diagonal element
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int blocks = (n + 15) >> 4, steps = 16 * blocks - 1;  // of all waves: one barrier each
 
     const double md = wave_max_diag(C, NP, lane);
     const int ex = tri_exponent(md);
     const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
-    auto element = [&](int r, int c) __attribute__((always_inline)) {
-        return (r < n && c < n) ? C[(int64_t)active_index(c, m0, LP) * NP + active_index(r, m0, LP)] * sc0 : 0.0;
+    auto inside = [&](int r, int c) __attribute__((always_inline)) { return r < n && c < n; };
+    auto load = [&](int r, int c) __attribute__((always_inline)) {
+        const bool in = inside(r, c);
+        return C[(int64_t)(in ? active_index(c, m0, LP) : 0) * NP + (in ? active_index(r, m0, LP) : 0)];
     };
-    if (wave == W) __builtin_amdgcn_s_setprio(3);  // its chain is the longer one: 43.9 us without at n = 64
-    double x[J];  // column k below row k + 1, rows lane + 64 j
-    Pair* const own = wx[wave <= W ? wave : W];
+    double x[J], v[J], nw[J];  // column k below row k + 1; v and -w of the step before: rows lane + 64 j
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        x[j] = load(lane + 64 * j, 0);
+        v[j] = nw[j] = 0.0;
+    }
+    double xk = load(0, 0), xk1 = load(1, 0);  // column k at rows k and k + 1, where it is wanted
+    loads_go_out();
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         const int r = lane + 64 * j;
-        const double e = element(r, 0);
-        x[j] = r > 1 ? e : 0.0;
-        if (wave <= W) own[r] = Pair{0.0, x[j]};
-        if (wave == 0) qc[0][r] = qc[1][r] = Pair{0.0, 0.0};
+        x[j] = r > 1 && inside(r, 0) ? x[j] * sc0 : 0.0;
+    }
+    xk = inside(0, 0) ? xk * sc0 : 0.0;
+    xk1 = inside(1, 0) ? xk1 * sc0 : 0.0;
+
+    // what the waves do after the barrier of step k, whose column k + 1 is in registers J0 .. : v, -w and the next x. xn: the next column
+    // with row k + 2, which x leaves out. (One read for all that is the same in all lanes: six waves' reads come at once.)
+    struct Scal { double v1, w1, tau, c1, beta; };
+    auto vectors = [&](auto uc, int k, double (&xn)[J]) __attribute__((always_inline)) {
+        constexpr int J0 = decltype(uc)::value;
+        const int par = k & 1;
+        const double z = prm[par][lane & (2 * W - 1)];
+        double q[J], c[J];
+#pragma unroll
+        for (int j = J0; j < J; ++j) {
+            const Pair e = qc[par][lane + 64 * j];
+            q[j] = e.a;
+            c[j] = e.b;
+        }
+        const double tau = read_lane(z, W), v1 = read_lane(z, W + 1), beta = read_lane(z, W + 2);
+        double s = read_lane(lane_sum<W>(z), 0);
+        const double q1 = read_lane(q[J0], (k + 1) & 63), c1 = read_lane(c[J0], (k + 1) & 63);
+        const double g1 = __builtin_fma(v1, c1, q1);                          // q + v1 c at k + 1
+        s = __builtin_fma(v1, q1 + g1, s);                                    // v A v = x A x + 2 v1 q + v1^2 c
+        const double nal = 0.5 * tau * (tau * s);
+        const double w1 = __builtin_fma(-nal, v1, tau * g1);
+#pragma unroll
+        for (int j = J0; j < J; ++j) {
+            const int r = lane + 64 * j;
+            v[j] = r == k + 1 ? v1 : x[j];
+            // (rows that are finished need no care: H leaves next to nothing of them, and x is zero there)
+            nw[j] = __builtin_fma(nal, v[j], -tau * __builtin_fma(v1, c[j], q[j]));
+            xn[j] = __builtin_fma(-v[j], w1, __builtin_fma(nw[j], v1, c[j]));
+            x[j] = r > k + 2 ? xn[j] : 0.0;
+        }
+        return Scal{v1, w1, tau, c1, beta};
+    };
+    constexpr std::integral_constant<int, 0> first{};
+    constexpr std::integral_constant<int, J - 1> second{};
+
+    if (wave < W) {
+        const int r16 = lane & 15, g = lane >> 4, row = 16 * wave + r16;
+        double a[J][16];
+#pragma unroll
+        for (int u = 0; u < J; ++u)
+#pragma unroll
+            for (int c = 0; c < 16; ++c) a[u][c] = load(row, 16 * (g + 4 * u) + c);
+        loads_go_out();
+#pragma unroll
+        for (int u = 0; u < J; ++u)
+#pragma unroll
+            for (int c = 0; c < 16; ++c) a[u][c] = inside(row, 16 * (g + 4 * u) + c) ? a[u][c] * sc0 : 0.0;
+        // the vectors at this lane's row, which lane `row` of a register has
+        const bool upper = J > 1 && wave >= 4;
+        auto at_row = [&](const double (&y)[J]) __attribute__((always_inline)) { return from_lane(upper ? y[J - 1] : y[0], 4 * (row & 63)); };
+        double vr = 0.0, nwr = 0.0, xr = at_row(x);
+        if (lane < 2) prm[lane][wave] = 0.0;
+        if (g < 2) qc[g][row] = Pair{0.0, 0.0};
+        const int qat = g == 0 ? row : N + lane;
+        lds_barrier();
+        if (wave >= blocks) {  // no rows: what it would add is zero
+            for (int k = 0; k < steps; ++k) lds_barrier();
+            return;
+        }
+        const int mine = wave + 1;  // column blocks before this wave's rows are finished
+        auto step = [&](auto uc, auto cc, int b, int cat) __attribute__((always_inline)) {
+            constexpr int U = decltype(uc)::value, CC = decltype(cc)::value;
+            const int k = 16 * b + CC - 1;
+            constexpr int par = (CC + 1) & 1;  // of k
+#pragma unroll
+            for (int u = U; u < J; ++u) row_update(a[u], nw[u], vr);
+#pragma unroll
+            for (int u = U; u < J; ++u) row_update(a[u], v[u], nwr);
+            qc[par][cat].b = a[U][CC];
+            double q = 0.0, b0, b1;
+#pragma unroll
+            for (int u = U; u < J; ++u) row_product(q, x[u], a[u]);
+            swap_rows<16>(q, b0, b1);
+            q = b0 + b1;
+            swap_rows<32>(q, b0, b1);
+            q = b0 + b1;
+            qc[par][qat].a = q;
+            const double p = lane_sum<16>(q * xr);
+            if (lane == 0) prm[par][wave] = p;
+            lds_barrier();
+            double xn[J];
+            const Scal s = vectors(uc, k, xn);
+            vr = row == k + 1 ? s.v1 : xr;
+            xr = at_row(x);
+            nwr = at_row(nw);
+        };
+        auto sixteen = [&](auto uc, int b) __attribute__((always_inline)) {
+            constexpr int U = decltype(uc)::value;
+            const int cat = g == b - 4 * U ? row : N + lane;
+            if (b > 0) step(uc, std::integral_constant<int, 0>{}, b, cat);
+            step(uc, std::integral_constant<int, 1>{}, b, cat);
+            step(uc, std::integral_constant<int, 2>{}, b, cat);
+            step(uc, std::integral_constant<int, 3>{}, b, cat);
+            step(uc, std::integral_constant<int, 4>{}, b, cat);
+            step(uc, std::integral_constant<int, 5>{}, b, cat);
+            step(uc, std::integral_constant<int, 6>{}, b, cat);
+            step(uc, std::integral_constant<int, 7>{}, b, cat);
+            step(uc, std::integral_constant<int, 8>{}, b, cat);
+            step(uc, std::integral_constant<int, 9>{}, b, cat);
+            step(uc, std::integral_constant<int, 10>{}, b, cat);
+            step(uc, std::integral_constant<int, 11>{}, b, cat);
+            step(uc, std::integral_constant<int, 12>{}, b, cat);
+            step(uc, std::integral_constant<int, 13>{}, b, cat);
+            step(uc, std::integral_constant<int, 14>{}, b, cat);
+            step(uc, std::integral_constant<int, 15>{}, b, cat);
+        };
+        int b = 0;
+        for (; b < (mine < 4 ? mine : 4); ++b) sixteen(first, b);
+        if constexpr (J == 2) {
+            for (; b < mine; ++b) sixteen(second, b);
+        }
+        // Its rows are finished: x and so its part of x A x is zero from here on. (The sum of the step before last is still there.)
+        if (lane == 0) prm[1][wave] = 0.0;
+        for (int k = 16 * mine - 1; k < steps; ++k) lds_barrier();
+        return;
     }
 
-    // what all waves do after the barrier of step k: w of the step, the next x
-    struct Scal { double v1, w1, tau, al; Pair e1; };
-    auto vectors = [&](int k) __attribute__((always_inline)) {
-        const int par = k & 1;
-        const Pair tv = prm[par], e1 = qc[par][k + 1];
-        Pair e[J];
+    if (wave > W) {  // stores the results
+        if (lane == 0) stat[0] = (double)ex;
+        lds_barrier();
+        auto steps_of = [&](auto uc, int k, int end) __attribute__((always_inline)) {
+            constexpr int U = decltype(uc)::value;
+            for (; k < end; ++k) {
+                lds_barrier();
+                double xn[J];
+                const Scal s = vectors(uc, k, xn);
 #pragma unroll
-        for (int j = 0; j < J; ++j) e[j] = qc[par][lane + 64 * j];
-        double s = pp[par][0];
+                for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = j >= U ? v[j] : 0.0;
+                if (lane < 3) (lane == 0 ? dT : lane == 1 ? eT : tauT)[k] = lane == 0 ? xk : lane == 1 ? s.beta : s.tau;
+                xk = __builtin_fma(-2.0 * s.v1, s.w1, s.c1);
+            }
+            return k;
+        };
+        const int k63 = steps_of(first, 0, steps < 63 ? steps : 63);
+        if constexpr (J == 2) steps_of(second, k63, steps);
+        // (rows of V beyond n - 2 that complete the last block of reflectors are zero: those steps' reflectors)
+        if (n - 1 >= steps && steps % WY != 0)
 #pragma unroll
-        for (int i = 1; i < W; ++i) s += pp[par][i];
-        const double tau = tv.a, v1 = tv.b;
-        const double g1 = __builtin_fma(v1, e1.b, e1.a);                      // q + v1 c at k + 1
-        s = __builtin_fma(v1, e1.a + g1, s);                                  // v A v = x A x + 2 v1 q + v1^2 c
-        const double al = -0.5 * tau * (tau * s);
-        const double w1 = __builtin_fma(al, v1, tau * g1);
+            for (int j = 0; j < J; ++j) V[(int64_t)steps * N + lane + 64 * j] = 0.0;
+        // the padding: decoupled, below every eigenvalue of a Gram matrix
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int r = lane + 64 * j;
-            const double v = r == k + 1 ? v1 : x[j];
-            double w = __builtin_fma(al, v, tau * __builtin_fma(v1, e[j].b, e[j].a));
-            w = r > k ? w : 0.0;
-            const double xn = __builtin_fma(-v, w1, __builtin_fma(-w, v1, e[j].b));
-            x[j] = r > k + 2 ? xn : 0.0;
-            own[r] = Pair{w, x[j]};
+            if (r == steps || r >= n) dT[r] = r < n ? xk : -1.0;
+            if (r >= n || r >= steps) eT[r] = tauT[r] = 0.0;
         }
-        return Scal{v1, w1, tau, al, e1};
-    };
-
-    if (wave < W) {
-        const int rs = wave * 4 + (lane >> 4), cs = lane & 15;
-        double a[RT][CT], vr[RT], vc[CT];
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-#pragma unroll
-            for (int u = 0; u < CT; ++u) a[t][u] = element(rs + RG * t, cs + 16 * u);
-            vr[t] = 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < CT; ++u) vc[u] = 0.0;
-        const bool odd = lane & 1, hi = lane & 2;
-        lds_barrier();
-        // steps whose column k + 1 is 16 Q ..: rows below RG T0 and columns below 16 Q are done with
-        auto steps = [&](auto qcst) __attribute__((always_inline)) {
-            constexpr int Q = decltype(qcst)::value, T0 = 16 * Q / RG;
-            int k = 16 * Q - 1;
-            if (k < 0) k = 0;
-            const int end = 16 * Q + 15 < n - 1 ? 16 * Q + 15 : n - 1;
-            for (; k < end; ++k) {
-                const int par = k & 1;
-                double q[RT], xr[RT], xc[CT], wc[CT], p = 0.0;
-#pragma unroll
-                for (int u = Q; u < CT; ++u) {
-                    const Pair e = own[cs + 16 * u];
-                    wc[u] = e.a;
-                    xc[u] = e.b;
-                }
-#pragma unroll
-                for (int t = T0; t < RT; ++t) {
-                    const Pair e = own[rs + RG * t];
-                    xr[t] = e.b;
-#pragma unroll
-                    for (int u = Q; u < CT; ++u) a[t][u] = __builtin_fma(-e.a, vc[u], a[t][u]);
-#pragma unroll
-                    for (int u = Q; u < CT; ++u) a[t][u] = __builtin_fma(-vr[t], wc[u], a[t][u]);
-                    double q0 = a[t][Q] * xc[Q];
-#pragma unroll
-                    for (int u = Q + 1; u < CT; ++u) q0 = __builtin_fma(a[t][u], xc[u], q0);
-                    q[t] = q0;
-                    p = __builtin_fma(q0, xr[t], p);
-                }
-                if (cs == ((k + 1) & 15)) {
-#pragma unroll
-                    for (int t = T0; t < RT; ++t) qc[par][rs + RG * t].b = a[t][Q];
-                }
-                // q over the 16 lanes of a row (four rows at a time, told apart by the low bits of the lane), x A x over the wave
-                p = lane_sum<64>(p);
-#pragma unroll
-                for (int g = T0; g < RT; g += 4) {
-                    const int left = RT - g;  // (compile time once unrolled)
-                    if (left >= 3) {
-                        const double q3 = left >= 4 ? q[g + 3 < RT ? g + 3 : RT - 1] : 0.0;
-                        double t0 = odd ? q[g + 1] : q[g], o0 = odd ? q[g] : q[g + 1];
-                        double t1 = odd ? q3 : q[g + 2 < RT ? g + 2 : RT - 1], o1 = odd ? q[g + 2 < RT ? g + 2 : RT - 1] : q3;
-                        t0 += dpp_move<DPP_XOR1>(o0);
-                        t1 += dpp_move<DPP_XOR1>(o1);
-                        double t = hi ? t1 : t0, o = hi ? t0 : t1;
-                        t += dpp_move<DPP_XOR2>(o);
-                        t += dpp_move<0x124>(t);  // row_ror 4
-                        t += dpp_move<0x128>(t);  // row_ror 8
-                        if (cs < (left >= 4 ? 4 : 3)) qc[par][rs + RG * (g + cs)].a = t;
-                    } else if (left == 2) {
-                        double t = odd ? q[g + 1 < RT ? g + 1 : RT - 1] : q[g], o = odd ? q[g] : q[g + 1 < RT ? g + 1 : RT - 1];
-                        t += dpp_move<DPP_XOR1>(o);
-                        t += dpp_move<DPP_XOR2>(t);
-                        t += dpp_move<0x124>(t);
-                        t += dpp_move<0x128>(t);
-                        if (cs < 2) qc[par][rs + RG * (g + cs)].a = t;
-                    } else {
-                        const double t = lane_sum<16>(q[g]);
-                        if (cs == 0) qc[par][rs + RG * g].a = t;
-                    }
-                }
-                if (lane == 0) pp[par][wave] = p;
-#pragma unroll
-                for (int u = Q; u < CT; ++u) vc[u] = xc[u];
-#pragma unroll
-                for (int t = T0; t < RT; ++t) vr[t] = xr[t];
-                lds_barrier();
-                const Scal s = vectors(k);
-                vc[Q] = cs + 16 * Q == k + 1 ? s.v1 : vc[Q];
-#pragma unroll
-                for (int t = T0; t < RT; ++t)
-                    if (RG * t < 16 * Q + 16 && RG * t + RG > 16 * Q) vr[t] = rs + RG * t == k + 1 ? s.v1 : vr[t];
-            }
-        };
-        steps(std::integral_constant<int, 0>{});
-        steps(std::integral_constant<int, 1>{});
-        steps(std::integral_constant<int, 2>{});
-        steps(std::integral_constant<int, 3>{});
-        if constexpr (J == 2) {
-            steps(std::integral_constant<int, 4>{});
-            steps(std::integral_constant<int, 5>{});
-            steps(std::integral_constant<int, 6>{});
-            steps(std::integral_constant<int, 7>{});
-        }
-        return;
-    }
-
-    if (wave > W) {  // stores the reflectors
-        lds_barrier();
-        for (int k = 0; k < n - 1; ++k) {
-            lds_barrier();
-#pragma unroll
-            for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = vl[k & 1][lane + 64 * j];
-        }
-        for (int k = n - 1; k % WY != 0; ++k)  // the rows of V that complete the last block of reflectors
-#pragma unroll
-            for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = 0.0;
         return;
     }
     // ---- the wave of the reflectors
-    double xk = element(0, 0), xk1 = element(1, 0);
-    double d[J], el[J], tl[J];  // of T, at lanes
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int r = lane + 64 * j;
-        d[j] = r < n ? (n == 1 ? xk : 0.0) : -1.0;  // the padding: decoupled, below every eigenvalue of a Gram matrix
-        el[j] = tl[j] = 0.0;
-    }
-    auto reflect = [&](int k, double& beta, double& tau, double& v1) __attribute__((always_inline)) {
-        double r2 = 0.0;
+    __builtin_amdgcn_s_setprio(3);
+    auto reflect = [&](int k) __attribute__((always_inline)) {
+        double r2 = 0.0, beta, tau, v1;
 #pragma unroll
         for (int j = 0; j < J; ++j) r2 = __builtin_fma(x[j], x[j], r2);
         r2 = lane_sum<64>(r2);
         householder(xk1, r2, beta, tau, v1);
-        if (lane == 0) prm[k & 1] = Pair{tau, v1};
-    };
-    double beta, tau, v1;
-    reflect(0, beta, tau, v1);
-    lds_barrier();
-    for (int k = 0; k < n - 1; ++k) {
-        // (before the barrier of step k: v for the wave that stores it)
-#pragma unroll
-        for (int j = 0; j < J; ++j) vl[k & 1][lane + 64 * j] = lane + 64 * j == k + 1 ? v1 : x[j];
-        const int par = k & 1, i2 = k + 2 < N ? k + 2 : N - 1;
-        lds_barrier();
-        const double v2 = own[i2].b;
-        const Pair e2 = qc[par][i2];
-        const Scal s = vectors(k);
-        const double w2 = __builtin_fma(s.al, v2, s.tau * __builtin_fma(s.v1, e2.b, e2.a));
-        xk1 = __builtin_fma(-v2, s.w1, __builtin_fma(-w2, s.v1, e2.b));
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const bool at = lane + 64 * j == k;
-            d[j] = at ? xk : d[j];
-            el[j] = at ? beta : el[j];
-            tl[j] = at ? tau : tl[j];
+        if (lane == 0) {
+            *reinterpret_cast<Pair*>(&prm[k & 1][W]) = Pair{tau, v1};
+            prm[k & 1][W + 2] = beta;
         }
-        xk = __builtin_fma(-2.0 * s.v1, s.w1, s.e1.b);
-        reflect(k + 1, beta, tau, v1);
-    }
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int r = lane + 64 * j;
-        if (r == n - 1) d[j] = xk;
-        dT[r] = d[j];
-        eT[r] = el[j];
-        tauT[r] = tl[j];
-    }
-    if (lane == 0) stat[0] = (double)ex;
+    };
+    reflect(0);
+    lds_barrier();
+    auto steps_of = [&](auto uc, int k, int end) __attribute__((always_inline)) {
+        constexpr int U = decltype(uc)::value;
+        for (; k < end; ++k) {
+            lds_barrier();
+            double xn[J];
+            vectors(uc, k, xn);
+            xk1 = read_lane(k + 2 < 64 * (U + 1) || U + 1 >= J ? xn[U] : xn[U + 1 < J ? U + 1 : U], (k + 2) & 63);
+            reflect(k + 1);
+        }
+        return k;
+    };
+    const int k63 = steps_of(first, 0, steps < 63 ? steps : 63);
+    if constexpr (J == 2) steps_of(second, k63, steps);
 }
 
 // ---- n = 64 J, J = 2, 4, 8: 16, 32, 32 work-groups on one XCD -----------------------------------------------------
@@ -564,12 +614,21 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
                 const int col = cl + 64 * (H + ST * s);
                 const double* src = C + (int64_t)active_index(col < n ? col : 0, m0, LP) * NP;
 #pragma unroll
-                for (int j = 0; j < J; ++j) a[s][j] = (col < n && mrow[j] >= 0) ? src[mrow[j]] * sc0 : 0.0;
+                for (int j = 0; j < J; ++j) a[s][j] = src[mrow[j] >= 0 ? mrow[j] : 0];
             }
             const double* src = C + (int64_t)active_index(0, m0, LP) * NP;
 #pragma unroll
+            for (int j = 0; j < J; ++j) x[j] = src[mrow[j] >= 0 ? mrow[j] : 0];
+            loads_go_out();
+#pragma unroll
+            for (int s = 0; s < CW; ++s) {
+                const int col = cl + 64 * (H + ST * s);
+#pragma unroll
+                for (int j = 0; j < J; ++j) a[s][j] = col < n && mrow[j] >= 0 ? a[s][j] * sc0 : 0.0;
+            }
+#pragma unroll
             for (int j = 0; j < J; ++j) {
-                x[j] = mrow[j] >= 0 ? src[mrow[j]] * sc0 : 0.0;
+                x[j] = mrow[j] >= 0 ? x[j] * sc0 : 0.0;
                 v[j] = 0.0;
                 w[j] = 0.0;
             }
@@ -989,7 +1048,7 @@ const XcdMap& xcd_map() {
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st) {
     const int LP = NP / 2;
 #define SAGE_TRI_ONE(J)                                                                                           \
-    hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(384), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
+    hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(64 * (4 * J + 2)), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
 #define SAGE_TRI_MANY(J)                                                                                           \
     hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(TriPlan<J>::THREADS), 0, st, w.C, NP, m0, LP, n, \
                        w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
