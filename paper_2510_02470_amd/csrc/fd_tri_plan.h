@@ -44,6 +44,10 @@ struct TriPlan {
     static constexpr int waits(int wg, int n) {
         return last_column(wg, n) == n - 1 ? n - 1 : (steps(wg, n) > 0 ? steps(wg, n) - 1 : 0);
     }
+    // The same where the reduction ends after `until` steps, 0 < until < n, and leaves the columns from `until` on: whoever owns one of them
+    // waits for every step.
+    static constexpr int steps_until(int wg, int n, int until) { return steps(wg, n) < until ? steps(wg, n) : until; }
+    static constexpr int waits_until(int wg, int n, int until) { return last_column(wg, n) >= until ? until : waits(wg, n); }
     // It also sees every step, and stores the results: nothing that a delayed work-group does can reach them.
     static constexpr bool closes(int wg, int n) { return last_column(wg, n) == n - 1; }
 };

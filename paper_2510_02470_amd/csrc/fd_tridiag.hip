@@ -6,13 +6,13 @@
 // update of it, 2 flop per byte touched), so it is bound by the latency of a step, not by arithmetic. The matrix
 // therefore never leaves the registers: the work-groups own columns of the (symmetric) matrix, a wave's lanes the rows
 // lane, lane + 64, ..., and the rank-2 update of a step is applied in the same pass as the next step's product.
-//   n = 64:            one work-group; the exchanges of a step go through LDS (tri_one_kernel, 0.65 us a step).
+//   n = 64:            one work-group; the exchanges of a step go through LDS (tri_one_kernel, 0.44 us a step).
 //   n = 128, 256, 512: 16, 32, 32 work-groups, one per CU of ONE XCD, which exchange two n-vectors per step through the L2
 //                      they share (tri_many_kernel, 0.77, 0.83, 1.02 us a step; every wave carries the vectors of the
-//                      step redundantly, so a step has one exchange and no other synchronisation).
-// One work-group takes 122 us for a 128-row reduction, 16 of them take 98, so the exchange pays from there on. Where work-groups
-// cannot be placed on one XCD (XcdMap without a period) one does it all: 128 rows by tri_one_kernel, larger ones as after a
-// wait in vain (see tri_many_kernel).
+//                      step redundantly, so a step has one exchange and no other synchronisation), until 64 rows are left;
+//                      those are the work of one work-group again (n = 128: 98 -> 55 + 32 us, 256: 206 -> 175 + 35).
+// One work-group takes 92 us for the whole of 128 rows, which is what is done where work-groups cannot be placed on one XCD (XcdMap
+// without a period); larger ones are then done as after a wait in vain (see tri_many_kernel).
 #include <mutex>
 #include <type_traits>
 
@@ -74,6 +74,109 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// The reduction by one work-group of T threads, with the matrix in V (its rows become the reflectors) and the vectors of a step
+// in LDS: every step reads and writes the trailing matrix once, through the L2. For solves that several work-groups could not
+// do together: 0.5, 2.2 and 12.8 ms at 128, 256 and 512 rows, where they take 0.12, 0.27 and 0.74. vec: 4 N words.
+template <int J, int T>
+__device__ __forceinline__ void tri_alone(const double* __restrict__ C, int NP, int m0, int LP, int n, double* __restrict__ dT,
+                                          double* __restrict__ eT, double* __restrict__ tauT, double* V, double sc0,
+                                          double* vec) {
+    constexpr int N = 64 * J;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = wave; i < n; i += T / 64)
+        for (int j = lane; j < N; j += 64)
+            V[(int64_t)i * N + j] = j < n ? C[(int64_t)active_index(i, m0, LP) * NP + active_index(j, m0, LP)] * sc0 : 0.0;
+    for (int j = tid; j < 4 * N; j += T) vec[j] = 0.0;
+    __syncthreads();
+    for (int k = 0; k < n; ++k) {
+        const double *v0 = vec + ((k + 1) & 1) * N, *w0 = v0 + 2 * N;  // of step k - 1 (v' and w' above)
+        double *v = vec + (k & 1) * N, *w = v + 2 * N;
+        // column k below the diagonal, with the update of step k - 1
+        for (int j = tid; j < N; j += T) {
+            const double a = V[(int64_t)k * N + j];
+            const double x = __builtin_fma(-v0[j], w0[k], __builtin_fma(-w0[j], v0[k], a));
+            v[j] = j > k && j < n ? x : 0.0;
+            w[j] = 0.0;
+            if (j == k) dT[k] = x;
+        }
+        __syncthreads();
+        if (k == n - 1) break;
+        double r2 = 0.0;
+        for (int j = lane; j < n; j += 64) r2 = j > k + 1 ? __builtin_fma(v[j], v[j], r2) : r2;
+        r2 = lane_sum<64>(r2);
+        double beta, tau, v1;
+        householder(v[k + 1], r2, beta, tau, v1);
+        __syncthreads();
+        for (int j = tid; j < N; j += T) {
+            const double x = j == k + 1 ? v1 : v[j];
+            if (j == k + 1) v[j] = x;
+            V[(int64_t)k * N + j] = x;
+        }
+        if (tid == 0) {
+            eT[k] = beta;
+            tauT[k] = tau;
+        }
+        __syncthreads();
+        const int c0 = (k + 1) & ~63;  // columns below are done with
+        // (four rows of a wave at a time, for their loads to be in flight together)
+        for (int i0 = k + 1 + wave; i0 < n; i0 += 4 * (T / 64)) {
+            double vi[4], wi[4], s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * (T / 64);
+                vi[u] = i < n ? v0[i] : 0.0;
+                wi[u] = i < n ? w0[i] : 0.0;
+            }
+            for (int j = c0 + lane; j < n; j += 64) {
+                const double vj = v0[j], wj = w0[j], xj = v[j];
+                double a[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u * (T / 64);
+                    a[u] = i < n ? V[(int64_t)i * N + j] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u * (T / 64);
+                    a[u] = __builtin_fma(-vj, wi[u], __builtin_fma(-wj, vi[u], a[u]));
+                    if (i < n) V[(int64_t)i * N + j] = a[u];
+                    s[u] = __builtin_fma(a[u], xj, s[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * (T / 64);
+                s[u] = lane_sum<64>(s[u]);
+                if (lane == 0 && i < n) w[i] = tau * s[u];
+            }
+        }
+        __syncthreads();
+        double dot = 0.0;
+        for (int j = lane; j < n; j += 64) dot = __builtin_fma(w[j], v[j], dot);
+        dot = lane_sum<64>(dot);
+        const double al = -0.5 * tau * dot;
+        __syncthreads();
+        for (int j = tid; j < N; j += T) w[j] = __builtin_fma(al, v[j], w[j]);
+        __syncthreads();
+    }
+}
+
+// What follows the last row in use of a reduction's results, by threads 0 .. step - 1. The rows of V that complete the last block of reflectors are zero; the
+// padding of T is decoupled and below every eigenvalue of a Gram matrix.
+template <int J>
+__device__ __forceinline__ void tri_finish(int n, double* __restrict__ dT, double* __restrict__ eT, double* __restrict__ tauT,
+                                           double* __restrict__ V, int tid, int step) {
+    constexpr int N = 64 * J;
+    for (int i = n - 1 + tid; i < N; i += step) {
+        if (i >= n) dT[i] = -1.0;
+        eT[i] = 0.0;
+        tauT[i] = 0.0;
+    }
+    for (int k = n - 1; k % WY != 0; ++k)
+        for (int i = tid; i < N; i += step) V[(int64_t)k * N + i] = 0.0;
 }
 
 // ---- n = 64 J, J = 1, 2: one work-group ---------------------------------------------------------------------------
@@ -147,23 +250,27 @@ __device__ __forceinline__ double from_lane(double v, int at) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-template <int J>
-__global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n,
-                                                                      double* __restrict__ dT, double* __restrict__ eT,
-                                                                      double* __restrict__ tauT, double* __restrict__ V,
-                                                                      double* __restrict__ stat) {
-    constexpr int W = 4 * J, N = 64 * J;
+// The reduction of rows off .. off + n - 1 (see the kernel). bad: set if the diagonal has a NaN.
+template <int J, int JN>
+__device__ __forceinline__ void tri_one(const double* __restrict__ C, int NP, int m0, int LP, int n, int off,
+                                        const double* __restrict__ rest, double* __restrict__ dT, double* __restrict__ eT,
+                                        double* __restrict__ tauT, double* __restrict__ V, double* __restrict__ stat, bool* bad) {
+    constexpr int W = 4 * J, N = 64 * J, NV = 64 * JN;  // NV: columns of V
+    constexpr bool TAIL = JN > J;
     __shared__ Pair qc[2][N + 64];  // {q, c} by step parity; what is not wanted goes beyond them
     __shared__ __attribute__((aligned(16))) double prm[2][2 * W];  // waves' sums of x A x, then tau, v1, off-diagonal element
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blocks = (n + 15) >> 4, steps = 16 * blocks - 1;  // of all waves: one barrier each
-
-    const double md = wave_max_diag(C, NP, lane);
-    const int ex = tri_exponent(md);
-    const double sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
+    int ex = 0;
+    double sc0 = 1.0;
+    if (!TAIL || !rest) {
+        ex = tri_exponent(wave_max_diag(C, NP, lane));
+        sc0 = __builtin_amdgcn_ldexp(1.0, -ex);
+    }
     auto inside = [&](int r, int c) __attribute__((always_inline)) { return r < n && c < n; };
     auto load = [&](int r, int c) __attribute__((always_inline)) {
+        if (TAIL && rest) return rest[c * 64 + r];
         const bool in = inside(r, c);
         return C[(int64_t)(in ? active_index(c, m0, LP) : 0) * NP + (in ? active_index(r, m0, LP) : 0)];
     };
@@ -301,34 +408,38 @@ __global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const doub
     }
 
     if (wave > W) {  // stores the results
-        if (lane == 0) stat[0] = (double)ex;
+        if (lane == 0 && !(TAIL && rest)) stat[0] = (double)ex;
         lds_barrier();
+        double* const Vo = V + (int64_t)off * NV;
+        bool nan = xk != xk;
         auto steps_of = [&](auto uc, int k, int end) __attribute__((always_inline)) {
             constexpr int U = decltype(uc)::value;
             for (; k < end; ++k) {
                 lds_barrier();
                 double xn[J];
                 const Scal s = vectors(uc, k, xn);
+                double* const row = Vo + (int64_t)k * NV;
+                if constexpr (TAIL) {  // (one register, its entries at columns off ..)
 #pragma unroll
-                for (int j = 0; j < J; ++j) V[(int64_t)k * N + lane + 64 * j] = j >= U ? v[j] : 0.0;
-                if (lane < 3) (lane == 0 ? dT : lane == 1 ? eT : tauT)[k] = lane == 0 ? xk : lane == 1 ? s.beta : s.tau;
+                    for (int j = 0; j < JN; ++j)
+                        if (lane + 64 * j < off || lane + 64 * j >= off + 64) row[lane + 64 * j] = 0.0;
+                    row[off + lane] = v[0];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < J; ++j) row[lane + 64 * j] = j >= U ? v[j] : 0.0;
+                }
+                if (lane < 3) (lane == 0 ? dT : lane == 1 ? eT : tauT)[off + k] = lane == 0 ? xk : lane == 1 ? s.beta : s.tau;
                 xk = __builtin_fma(-2.0 * s.v1, s.w1, s.c1);
+                nan = nan || xk != xk;
             }
             return k;
         };
         const int k63 = steps_of(first, 0, steps < 63 ? steps : 63);
         if constexpr (J == 2) steps_of(second, k63, steps);
-        // (rows of V beyond n - 2 that complete the last block of reflectors are zero: those steps' reflectors)
-        if (n - 1 >= steps && steps % WY != 0)
-#pragma unroll
-            for (int j = 0; j < J; ++j) V[(int64_t)steps * N + lane + 64 * j] = 0.0;
-        // the padding: decoupled, below every eigenvalue of a Gram matrix
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = lane + 64 * j;
-            if (r == steps || r >= n) dT[r] = r < n ? xk : -1.0;
-            if (r >= n || r >= steps) eT[r] = tauT[r] = 0.0;
-        }
+        if (lane == 0 && steps == n - 1) dT[off + steps] = xk;
+        // what follows the last row, with the steps beyond it (tri_many_kernel has done so where it began)
+        if (!(TAIL && rest)) tri_finish<JN>(n, dT, eT, tauT, V, lane, 64);
+        if (TAIL && lane == 0) *bad = nan;
         return;
     }
     // ---- the wave of the reflectors
@@ -361,6 +472,49 @@ __global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const doub
     if constexpr (J == 2) steps_of(second, k63, steps);
 }
 
+// JN > J: the last rows of a solve of 64 JN buffer rows. rest: what tri_many_kernel leaves of the matrix after `off` steps, 64 x 64 and scaled;
+// null: it is C's, and there are no more than 64 rows. Where that kernel gave up (stat[1], or NaN that its work-groups left), and with
+// `all`, the whole reduction is done here.
+template <int J, int JN>
+__global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int nall, int off,
+                                                                      const double* __restrict__ rest, bool all,
+                                                                      double* __restrict__ dT, double* __restrict__ eT,
+                                                                      double* __restrict__ tauT, double* __restrict__ V,
+                                                                      double* __restrict__ stat, double* __restrict__ redone) {
+    constexpr int W = 4 * J, N = 64 * J, NV = 64 * JN;  // NV: columns of V
+    constexpr bool TAIL = JN > J;
+    const int n = nall - off;
+    const int tid = threadIdx.x, lane = tid & 63;
+
+    if constexpr (TAIL) {
+        __shared__ bool bad;
+        bool redo = all;
+        if (!redo) {
+            if (rest) redo = stat[1] != 0.0;
+            if (!redo) {
+                tri_one<J, JN>(C, NP, m0, LP, n, off, rest, dT, eT, tauT, V, stat, &bad);
+                lds_barrier();
+                redo = rest && bad;
+            }
+        }
+        if (!redo) return;
+        // (or the matrix is not finite: then so is this, and it does no harm)
+        constexpr int T = 64 * (W + 2);
+        __shared__ double vec[4 * NV];
+        __syncthreads();
+        const int ex = tri_exponent(wave_max_diag(C, NP, lane));
+        if (tid == 0) {
+            *redone += 1.0;
+            stat[0] = (double)ex;
+        }
+        tri_alone<JN, T>(C, NP, m0, LP, nall, dT, eT, tauT, V, __builtin_amdgcn_ldexp(1.0, -ex), vec);
+        __syncthreads();
+        tri_finish<JN>(nall, dT, eT, tauT, V, tid, T);
+    } else {
+        tri_one<J, JN>(C, NP, m0, LP, n, off, rest, dT, eT, tauT, V, stat, nullptr);
+    }
+}
+
 // ---- n = 64 J, J = 2, 4, 8: 16, 32, 32 work-groups on one XCD -----------------------------------------------------
 // As above, but a wave owns 2 (n = 128, 256) or 4 whole columns, carries all vectors itself and sums its products over the
 // lanes, and q and c go through the L2 the work-groups share. An exchanged value is its own 8 bytes: a slot holds a pattern that
@@ -380,115 +534,12 @@ __global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const doub
 // The work-groups must be resident together, which nothing guarantees: kernels of other streams and processes may hold the CUs
 // of the XCD. So a thread polls at most `polls` times in vain in all and then goes on with NaN for what did not come. NaN
 // goes into everything it publishes from then on, so the others lose no time waiting, and reaches the work-group of the
-// last column, which finds it in the last diagonal element. That work-group is the only one that writes results, and it
+// last column, which says so in stat[1], or what a work-group leaves of the matrix, where the kernel that goes on finds it. That one
 // then repeats the whole reduction alone (tri_alone): a solve never fails. A work-group that starts when the others have
 // given up sees that in claim[1] and loses no time either.
 // poll_limit: to wait for as long as the repetition takes, 1.9, 3.8 and 15 ms (0.23 us a poll), costs at most twice what the better
 // of waiting and repeating would have. A reduction polls 500, 1100 and 3000 times in vain while it waits for its own steps.
 constexpr int poll_limit(int J) { return J == 2 ? 1 << 13 : J == 4 ? 1 << 14 : 1 << 16; }
-
-// The reduction by one work-group of T threads, with the matrix in V (its rows become the reflectors) and the vectors of a step
-// in LDS: every step reads and writes the trailing matrix once, through the L2. For solves that several work-groups could not
-// do together: 0.5, 2.2 and 12.8 ms at 128, 256 and 512 rows, where they take 0.12, 0.27 and 0.74. vec: 4 N words.
-template <int J, int T>
-__device__ __forceinline__ void tri_alone(const double* __restrict__ C, int NP, int m0, int LP, int n, double* __restrict__ dT,
-                                          double* __restrict__ eT, double* __restrict__ tauT, double* V, double sc0,
-                                          double* vec) {
-    constexpr int N = 64 * J;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int i = wave; i < n; i += T / 64)
-        for (int j = lane; j < N; j += 64)
-            V[(int64_t)i * N + j] = j < n ? C[(int64_t)active_index(i, m0, LP) * NP + active_index(j, m0, LP)] * sc0 : 0.0;
-    for (int j = tid; j < 4 * N; j += T) vec[j] = 0.0;
-    __syncthreads();
-    for (int k = 0; k < n; ++k) {
-        const double *v0 = vec + ((k + 1) & 1) * N, *w0 = v0 + 2 * N;  // of step k - 1 (v' and w' above)
-        double *v = vec + (k & 1) * N, *w = v + 2 * N;
-        // column k below the diagonal, with the update of step k - 1
-        for (int j = tid; j < N; j += T) {
-            const double a = V[(int64_t)k * N + j];
-            const double x = __builtin_fma(-v0[j], w0[k], __builtin_fma(-w0[j], v0[k], a));
-            v[j] = j > k && j < n ? x : 0.0;
-            w[j] = 0.0;
-            if (j == k) dT[k] = x;
-        }
-        __syncthreads();
-        if (k == n - 1) break;
-        double r2 = 0.0;
-        for (int j = lane; j < n; j += 64) r2 = j > k + 1 ? __builtin_fma(v[j], v[j], r2) : r2;
-        r2 = lane_sum<64>(r2);
-        double beta, tau, v1;
-        householder(v[k + 1], r2, beta, tau, v1);
-        __syncthreads();
-        for (int j = tid; j < N; j += T) {
-            const double x = j == k + 1 ? v1 : v[j];
-            if (j == k + 1) v[j] = x;
-            V[(int64_t)k * N + j] = x;
-        }
-        if (tid == 0) {
-            eT[k] = beta;
-            tauT[k] = tau;
-        }
-        __syncthreads();
-        const int c0 = (k + 1) & ~63;  // columns below are done with
-        // (four rows of a wave at a time, for their loads to be in flight together)
-        for (int i0 = k + 1 + wave; i0 < n; i0 += 4 * (T / 64)) {
-            double vi[4], wi[4], s[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = i0 + u * (T / 64);
-                vi[u] = i < n ? v0[i] : 0.0;
-                wi[u] = i < n ? w0[i] : 0.0;
-            }
-            for (int j = c0 + lane; j < n; j += 64) {
-                const double vj = v0[j], wj = w0[j], xj = v[j];
-                double a[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = i0 + u * (T / 64);
-                    a[u] = i < n ? V[(int64_t)i * N + j] : 0.0;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = i0 + u * (T / 64);
-                    a[u] = __builtin_fma(-vj, wi[u], __builtin_fma(-wj, vi[u], a[u]));
-                    if (i < n) V[(int64_t)i * N + j] = a[u];
-                    s[u] = __builtin_fma(a[u], xj, s[u]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = i0 + u * (T / 64);
-                s[u] = lane_sum<64>(s[u]);
-                if (lane == 0 && i < n) w[i] = tau * s[u];
-            }
-        }
-        __syncthreads();
-        double dot = 0.0;
-        for (int j = lane; j < n; j += 64) dot = __builtin_fma(w[j], v[j], dot);
-        dot = lane_sum<64>(dot);
-        const double al = -0.5 * tau * dot;
-        __syncthreads();
-        for (int j = tid; j < N; j += T) w[j] = __builtin_fma(al, v[j], w[j]);
-        __syncthreads();
-    }
-}
-
-// What follows the last row in use of a reduction's results, by threads 0 .. step - 1. The rows of V that complete the last block of reflectors are zero; the
-// padding of T is decoupled and below every eigenvalue of a Gram matrix.
-template <int J>
-__device__ __forceinline__ void tri_finish(int n, double* __restrict__ dT, double* __restrict__ eT, double* __restrict__ tauT,
-                                           double* __restrict__ V, int tid, int step) {
-    constexpr int N = 64 * J;
-    for (int i = n - 1 + tid; i < N; i += step) {
-        if (i >= n) dT[i] = -1.0;
-        eT[i] = 0.0;
-        tauT[i] = 0.0;
-    }
-    for (int k = n - 1; k % WY != 0; ++k)
-        for (int i = tid; i < N; i += step) V[(int64_t)k * N + i] = 0.0;
-}
 
 __device__ __forceinline__ void put_entry(double* p, double v) {
     *p = v;
@@ -500,13 +551,12 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
                                                           double* __restrict__ dT, double* __restrict__ eT,
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, double* __restrict__ xch,
-                                                          int xcd, int shift, int polls,
-                                                          double* __restrict__ redone, unsigned* __restrict__ claim) {
+                                                          int xcd, int shift, int polls, double* __restrict__ rest,
+                                                          unsigned* __restrict__ claim) {
     using Plan = TriPlan<J>;
     constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW, T = Plan::THREADS;
-    // (xcd < 0: there is one work-group, in the closing role)
-    const int wg = xcd >= 0 ? blockIdx.x >> shift : Plan::wave_of(n - 1) >> 2;
-    const bool here = xcd < 0 || xcd_id() == xcd;
+    const int wg = blockIdx.x >> shift, last = n - 64;  // steps 0 .. last - 1
+    const bool here = xcd_id() == xcd;
     const bool closes = Plan::closes(wg, n);  // this work-group stores what the solve's next stages read
     if (!here && !closes) return;
     __shared__ __attribute__((aligned(16))) double qc[4][N + 2];  // q by step parity, then c
@@ -520,16 +570,13 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
         else __builtin_amdgcn_s_setprio(1);
     }
     if (Plan::last_column(wg, n) < 0) return;
-    const int steps = Plan::steps(wg, n), waits = Plan::waits(wg, n);  // waits >= steps - 1
+    const int steps = Plan::steps_until(wg, n, last), waits = Plan::waits_until(wg, n, last);  // waits >= steps - 1
     __shared__ TriClaim role;
     if (closes && tid == 256) {  // (a thread that waits anyway)
-        role = CLAIM_CLOSE;
-        if (xcd >= 0) {
-            const unsigned mine = claim_add(here);
-            const unsigned word = mine + __hip_atomic_fetch_add(claim, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            role = claim_role(word, here, 1 << shift);
-            if (claim_last(word, 1 << shift)) __hip_atomic_store(claim, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        const unsigned mine = claim_add(here);
+        const unsigned word = mine + __hip_atomic_fetch_add(claim, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        role = claim_role(word, here, 1 << shift);
+        if (claim_last(word, 1 << shift)) __hip_atomic_store(claim, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 
     auto wait_for_entries = [&]() __attribute__((always_inline)) {  // waves 4 ..: one half waits for q, the other for c
@@ -772,9 +819,24 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
             steps_of(std::integral_constant<int, 6>{});
             steps_of(std::integral_constant<int, 7>{});
         }
-        if (closes && tid == 0) {  // (waits = n - 1: xk is the last step's)
+        // What is left of this wave's columns, with the update of the last step; NaN if anything of it did not come.
+        if (waits == last) {
+#pragma unroll
+            for (int s = 0; s < CW; ++s) {
+                const int col = cl + 64 * (H + ST * s);
+                const double vcol = read_lane(v[H + ST * s], cl), wcol = read_lane(w[H + ST * s], cl);
+                if (col >= last && col < n) {
+#pragma unroll
+                    for (int j = 0; j < J; ++j) {
+                        const int r = lane + 64 * j;
+                        const double e = __builtin_fma(-v[j], wcol, __builtin_fma(-w[j], vcol, a[s][j]));
+                        if (r >= last && r < n) rest[(col - last) * 64 + r - last] = e;
+                    }
+                }
+            }
+        }
+        if (closes && tid == 0) {  // (xk: of row `last`)
             stat[0] = (double)ex;
-            dT[n - 1] = xk;
             gave_up = xk != xk;
         }
     };
@@ -786,17 +848,7 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
     if (!closes) return;
     lds_barrier();
     if (role == CLAIM_LEAVE) return;
-    if (gave_up) {  // (or the matrix is not finite: then so is this, and it does no harm)
-        __syncthreads();
-        const int ex = tri_exponent(wave_max_diag(C, NP, lane));
-        if (tid == 0) {
-            *redone += 1.0;
-            stat[0] = (double)ex;
-        }
-        tri_alone<J, T>(C, NP, m0, LP, n, dT, eT, tauT, V, __builtin_amdgcn_ldexp(1.0, -ex), &qc[0][0]);
-        __syncthreads();
-        tri_finish<J>(n, dT, eT, tauT, V, tid, T);
-    }
+    if (tid == 0) stat[1] = gave_up ? 1.0 : 0.0;
 }
 
 // ---- Y = H Z --------------------------------------------------------------------------------------------------------
@@ -1047,17 +1099,23 @@ const XcdMap& xcd_map() {
 
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st) {
     const int LP = NP / 2;
-#define SAGE_TRI_ONE(J)                                                                                           \
-    hipLaunchKernelGGL(tri_one_kernel<J>, dim3(1), dim3(64 * (4 * J + 2)), 0, st, w.C, NP, m0, LP, n, w.dT, w.eT, w.tauT, w.V, w.stat)
-#define SAGE_TRI_MANY(J)                                                                                           \
-    hipLaunchKernelGGL(tri_many_kernel<J>, dim3(alone ? 1 : w.period * TriPlan<J>::NWG), dim3(TriPlan<J>::THREADS), 0, st, w.C, NP, m0, LP, n, \
-                       w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, alone ? -1 : w.xcd, alone ? 0 : __builtin_ctz(w.period), \
-                       alone || w.impatient ? 1 : poll_limit(J), w.redone, w.claim)
     const bool alone = w.period == 0;
+#define SAGE_TRI_ONE(J, JN, OFF, REST, ALL)                                                                           \
+    hipLaunchKernelGGL((tri_one_kernel<J, JN>), dim3(1), dim3(64 * (4 * J + 2)), 0, st, w.C, NP, m0, LP, n, OFF, REST, ALL, w.dT, w.eT, \
+                       w.tauT, w.V, w.stat, w.redone)
+#define SAGE_TRI_MANY(J)                                                                                           \
+    do {                                                                                                           \
+        if (n > 64 && !alone)                                                                                      \
+            hipLaunchKernelGGL(tri_many_kernel<J>, dim3(w.period * TriPlan<J>::NWG), dim3(TriPlan<J>::THREADS), 0, st, w.C, NP, m0, LP, \
+                               n, w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, w.xcd, __builtin_ctz(w.period),           \
+                               w.impatient ? 1 : poll_limit(J), w.Yt, w.claim);                                    \
+        SAGE_TRI_ONE(1, J, n > 64 && !alone ? n - 64 : 0, n > 64 && !alone ? w.Yt : nullptr, n > 64 && alone);      \
+    } while (0)
     switch (NP / 64) {
-        case 1: SAGE_TRI_ONE(1); break;
+        case 1: SAGE_TRI_ONE(1, 1, 0, nullptr, false); break;
         case 2:
-            if (alone) SAGE_TRI_ONE(2); else SAGE_TRI_MANY(2);
+            if (alone) SAGE_TRI_ONE(2, 2, 0, nullptr, false);
+            else SAGE_TRI_MANY(2);
             break;
         case 4: SAGE_TRI_MANY(4); break;
         case 8: SAGE_TRI_MANY(8); break;

@@ -50,6 +50,14 @@ def test_deferred_shrinks_leave_no_rows_behind(tmp_path):
     assert _run(exe, "planted").returncode == 1
 
 
+def test_a_reduction_that_leaves_64_rows_has_all_it_stores(tmp_path):
+    """tri_tail_check.cc; and the check itself: it must refuse a plan where nobody waits for the last step."""
+    exe = _build(tmp_path, "tri_tail_check")
+    r = _run(exe)
+    assert r.returncode == 0 and "tri_tail_check ok" in r.stdout, r.stdout
+    assert _run(exe, "planted").returncode == 1
+
+
 def test_work_space_of_the_selection(tmp_path):
     """select_plan_check.cc; and the check itself: it must refuse a work space for the longest call alone."""
     exe = _build(tmp_path, "select_plan_check")
