@@ -428,13 +428,14 @@ __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const do
                                                           unsigned* __restrict__ claim) {
     if (!WITH_WY && blockIdx.x == 0) {  // the reduction before this is over: empty its exchange for the next
         for (int e = threadIdx.x; e < 4 * N; e += 512) reinterpret_cast<u32x4*>(xch)[e] = u32x4{~0u, ~0u, ~0u, ~0u};
-        if (threadIdx.x == 0) claim[1] = 0u;
+        if (threadIdx.x >= 1 && threadIdx.x <= 3) claim[threadIdx.x] = 0u;
     }
     if (WITH_WY && blockIdx.x == 1) {
         const int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         if (b * WY <= n - 2) wy_factor<1>(V, tauT, b, n, threadIdx.x & 63, Tw);
         return;
     }
+    __builtin_amdgcn_s_setprio(3);  // (96 rows beside a Gram launch of the side stream: 53 -> 43 us)
     extern __shared__ char dc_lds[];
     DcBlockLds& S = *reinterpret_cast<DcBlockLds*>(dc_lds);
     const int tid = threadIdx.x, i = tid >> 3, l = tid & 7;

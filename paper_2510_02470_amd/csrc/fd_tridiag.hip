@@ -10,7 +10,8 @@
 //   n = 128, 256, 512: 16, 32, 32 work-groups, one per CU of ONE XCD, which exchange two n-vectors per step through the L2
 //                      they share (tri_many_kernel, 0.77, 0.83, 1.02 us a step; every wave carries the vectors of the
 //                      step redundantly, so a step has one exchange and no other synchronisation), until 64 rows are left;
-//                      those are the work of one work-group again (n = 128: 98 -> 55 + 32 us, 256: 206 -> 175 + 35).
+//                      one of them goes on with those as if there were no others (n = 128: 98 -> 85 us, 256: 206 -> 205 to
+//                      212, 512: 585 -> 545, the latter two beside the side stream's work).
 // One work-group takes 92 us for the whole of 128 rows, which is what is done where work-groups cannot be placed on one XCD (XcdMap
 // without a period); larger ones are then done as after a wait in vain (see tri_many_kernel).
 #include <mutex>
@@ -250,7 +251,8 @@ __device__ __forceinline__ double from_lane(double v, int at) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// The reduction of rows off .. off + n - 1 (see the kernel). bad: set if the diagonal has a NaN.
+// The reduction by 4 J + 2 waves of rows off .. off + n - 1, the last of a solve of 64 JN buffer rows if JN > J. rest: what several
+// work-groups leave of the matrix after `off` steps, 64 x 64 and scaled, with bad set if the diagonal has a NaN; null: it is C's.
 template <int J, int JN>
 __device__ __forceinline__ void tri_one(const double* __restrict__ C, int NP, int m0, int LP, int n, int off,
                                         const double* __restrict__ rest, double* __restrict__ dT, double* __restrict__ eT,
@@ -270,7 +272,7 @@ __device__ __forceinline__ void tri_one(const double* __restrict__ C, int NP, in
     }
     auto inside = [&](int r, int c) __attribute__((always_inline)) { return r < n && c < n; };
     auto load = [&](int r, int c) __attribute__((always_inline)) {
-        if (TAIL && rest) return rest[c * 64 + r];
+        if (TAIL && rest) return __hip_atomic_load(rest + c * 64 + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // (past the L1)
         const bool in = inside(r, c);
         return C[(int64_t)(in ? active_index(c, m0, LP) : 0) * NP + (in ? active_index(r, m0, LP) : 0)];
     };
@@ -437,9 +439,9 @@ __device__ __forceinline__ void tri_one(const double* __restrict__ C, int NP, in
         const int k63 = steps_of(first, 0, steps < 63 ? steps : 63);
         if constexpr (J == 2) steps_of(second, k63, steps);
         if (lane == 0 && steps == n - 1) dT[off + steps] = xk;
-        // what follows the last row, with the steps beyond it (tri_many_kernel has done so where it began)
+        // what follows the last row, with the steps beyond it (where there is a rest, that has been done)
         if (!(TAIL && rest)) tri_finish<JN>(n, dT, eT, tauT, V, lane, 64);
-        if (TAIL && lane == 0) *bad = nan;
+        if (TAIL && rest && lane == 0) *bad = nan;
         return;
     }
     // ---- the wave of the reflectors
@@ -472,47 +474,37 @@ __device__ __forceinline__ void tri_one(const double* __restrict__ C, int NP, in
     if constexpr (J == 2) steps_of(second, k63, steps);
 }
 
-// JN > J: the last rows of a solve of 64 JN buffer rows. rest: what tri_many_kernel leaves of the matrix after `off` steps, 64 x 64 and scaled;
-// null: it is C's, and there are no more than 64 rows. Where that kernel gave up (stat[1], or NaN that its work-groups left), and with
-// `all`, the whole reduction is done here.
+// The whole reduction by T threads of one work-group, for solves that several could not do together, or where one of them found NaN. (If
+// that is the matrix's, so is what comes of this, and it does no harm.)
+template <int JN, int T>
+__device__ __forceinline__ void tri_redo(const double* __restrict__ C, int NP, int m0, int LP, int n, double* __restrict__ dT,
+                                         double* __restrict__ eT, double* __restrict__ tauT, double* __restrict__ V,
+                                         double* __restrict__ stat, double* __restrict__ redone) {
+    __shared__ double vec[4 * 64 * JN];
+    const int tid = threadIdx.x;
+    const int ex = tri_exponent(wave_max_diag(C, NP, tid & 63));
+    if (tid == 0) {
+        *redone += 1.0;
+        stat[0] = (double)ex;
+    }
+    tri_alone<JN, T>(C, NP, m0, LP, n, dT, eT, tauT, V, __builtin_amdgcn_ldexp(1.0, -ex), vec);
+    __syncthreads();
+    tri_finish<JN>(n, dT, eT, tauT, V, tid, T);
+}
+
+// JN > J: no more than 64 J rows of a solve of 64 JN buffer rows; more of them, with `all`, are done as after a wait in vain.
 template <int J, int JN>
-__global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int nall, int off,
-                                                                      const double* __restrict__ rest, bool all,
+__global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const double* __restrict__ C, int NP, int m0, int LP, int n, bool all,
                                                                       double* __restrict__ dT, double* __restrict__ eT,
                                                                       double* __restrict__ tauT, double* __restrict__ V,
                                                                       double* __restrict__ stat, double* __restrict__ redone) {
-    constexpr int W = 4 * J, N = 64 * J, NV = 64 * JN;  // NV: columns of V
-    constexpr bool TAIL = JN > J;
-    const int n = nall - off;
-    const int tid = threadIdx.x, lane = tid & 63;
-
-    if constexpr (TAIL) {
-        __shared__ bool bad;
-        bool redo = all;
-        if (!redo) {
-            if (rest) redo = stat[1] != 0.0;
-            if (!redo) {
-                tri_one<J, JN>(C, NP, m0, LP, n, off, rest, dT, eT, tauT, V, stat, &bad);
-                lds_barrier();
-                redo = rest && bad;
-            }
+    if constexpr (JN > J) {
+        if (all) {
+            tri_redo<JN, 64 * (4 * J + 2)>(C, NP, m0, LP, n, dT, eT, tauT, V, stat, redone);
+            return;
         }
-        if (!redo) return;
-        // (or the matrix is not finite: then so is this, and it does no harm)
-        constexpr int T = 64 * (W + 2);
-        __shared__ double vec[4 * NV];
-        __syncthreads();
-        const int ex = tri_exponent(wave_max_diag(C, NP, lane));
-        if (tid == 0) {
-            *redone += 1.0;
-            stat[0] = (double)ex;
-        }
-        tri_alone<JN, T>(C, NP, m0, LP, nall, dT, eT, tauT, V, __builtin_amdgcn_ldexp(1.0, -ex), vec);
-        __syncthreads();
-        tri_finish<JN>(nall, dT, eT, tauT, V, tid, T);
-    } else {
-        tri_one<J, JN>(C, NP, m0, LP, n, off, rest, dT, eT, tauT, V, stat, nullptr);
     }
+    tri_one<J, JN>(C, NP, m0, LP, n, 0, nullptr, dT, eT, tauT, V, stat, nullptr);
 }
 
 // ---- n = 64 J, J = 2, 4, 8: 16, 32, 32 work-groups on one XCD -----------------------------------------------------
@@ -520,7 +512,10 @@ __global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const doub
 // lanes, and q and c go through the L2 the work-groups share. An exchanged value is its own 8 bytes: a slot holds a pattern that
 // is no result until it is written, so there are no flags and no fences, and a reader polls, with loads that bypass its L1
 // (sc1), until it sees anything else. Four slots by step; the work-group of the last column, which sees every step, empties them
-// (fd_tri_plan.h). The kernel after this one empties them all (dc_block_kernel), so that a solve needs no number of its own
+// (fd_tri_plan.h). When 64 rows are left, their columns' owners store them and say so, a bit of a word for each column, and the
+// work-group of the last one, which has the most to do with them, goes on alone (tri_one). A kernel of its own for that took 34 us
+// where the chip was idle, but 49 to 73 at 512 rows and 57 at 96 beside the side stream's work: that keeps off the XCD of the solve only,
+// and a launch's one work-group goes anywhere. The kernel after this one empties the slots and the word (dc_block_kernel), so that a solve needs no number of its own
 // and a captured one can be replayed. (16-byte entries with a tag in each half, which need no emptying, moved twice the bytes and
 // took two loads a thread at 512 rows: 830 us beside the look-ahead work instead of 595.)
 // Stores: the L1 is write-through, so a plain store reaches the XCD's L2. Of the work-groups launched, one in `period` lands on
@@ -534,8 +529,8 @@ __global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const doub
 // The work-groups must be resident together, which nothing guarantees: kernels of other streams and processes may hold the CUs
 // of the XCD. So a thread polls at most `polls` times in vain in all and then goes on with NaN for what did not come. NaN
 // goes into everything it publishes from then on, so the others lose no time waiting, and reaches the work-group of the
-// last column, which says so in stat[1], or what a work-group leaves of the matrix, where the kernel that goes on finds it. That one
-// then repeats the whole reduction alone (tri_alone): a solve never fails. A work-group that starts when the others have
+// last column or what is left of the matrix, where that one finds it. It then repeats the whole reduction alone (tri_redo): a
+// solve never fails. A work-group that starts when the others have
 // given up sees that in claim[1] and loses no time either.
 // poll_limit: to wait for as long as the repetition takes, 1.9, 3.8 and 15 ms (0.23 us a poll), costs at most twice what the better
 // of waiting and repeating would have. A reduction polls 500, 1100 and 3000 times in vain while it waits for its own steps.
@@ -552,9 +547,9 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
                                                           double* __restrict__ tauT, double* __restrict__ V,
                                                           double* __restrict__ stat, double* __restrict__ xch,
                                                           int xcd, int shift, int polls, double* __restrict__ rest,
-                                                          unsigned* __restrict__ claim) {
+                                                          unsigned* __restrict__ claim, double* __restrict__ redone) {
     using Plan = TriPlan<J>;
-    constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW, T = Plan::THREADS;
+    constexpr int N = Plan::N, CW = Plan::CW, NW = Plan::NW, T = Plan::THREADS, T1 = 384;  // (T1: see tri_one)
     const int wg = blockIdx.x >> shift, last = n - 64;  // steps 0 .. last - 1
     const bool here = xcd_id() == xcd;
     const bool closes = Plan::closes(wg, n);  // this work-group stores what the solve's next stages read
@@ -562,7 +557,8 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
     __shared__ __attribute__((aligned(16))) double qc[4][N + 2];  // q by step parity, then c
     __shared__ __attribute__((aligned(16))) double vs[2][N];  // the closing work-group: the reflector, by step parity,
     __shared__ double sc[2][64];                              // and {diagonal, off-diagonal element, tau}
-    __shared__ bool gave_up;
+    __shared__ bool gave_up, bad;
+    unsigned long long* const left = reinterpret_cast<unsigned long long*>(claim + 2);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (here) {  // waves that compute go before those that wait
@@ -832,6 +828,8 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
                         const double e = __builtin_fma(-v[j], wcol, __builtin_fma(-w[j], vcol, a[s][j]));
                         if (r >= last && r < n) rest[(col - last) * 64 + r - last] = e;
                     }
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // there before the column counts as there
+                    if (lane == 0) __hip_atomic_fetch_or(left, 1ull << (col - last), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         }
@@ -847,8 +845,26 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
     else reduce(std::integral_constant<int, NW / 64 - 1>{});
     if (!closes) return;
     lds_barrier();
-    if (role == CLAIM_LEAVE) return;
-    if (tid == 0) stat[1] = gave_up ? 1.0 : 0.0;
+    if (role == CLAIM_LEAVE || wave >= T1 / 64) return;  // (barriers are those of the waves that are left)
+    // ---- the rows that are left
+    if (!gave_up) {
+        __builtin_amdgcn_s_setprio(3);
+        if (tid == 0) {
+            int spins = polls;
+            while (__hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ~0ull && --spins > 0) {}
+            bad = spins <= 0;
+        }
+        lds_barrier();
+        const bool missing = bad;
+        lds_barrier();
+        if (!missing) {
+            tri_one<1, J>(C, NP, m0, LP, 64, last, rest, dT, eT, tauT, V, stat, &bad);
+            lds_barrier();
+            if (!bad) return;
+        }
+    }
+    __syncthreads();
+    tri_redo<J, T1>(C, NP, m0, LP, n, dT, eT, tauT, V, stat, redone);
 }
 
 // ---- Y = H Z --------------------------------------------------------------------------------------------------------
@@ -1100,21 +1116,22 @@ const XcdMap& xcd_map() {
 hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st) {
     const int LP = NP / 2;
     const bool alone = w.period == 0;
-#define SAGE_TRI_ONE(J, JN, OFF, REST, ALL)                                                                           \
-    hipLaunchKernelGGL((tri_one_kernel<J, JN>), dim3(1), dim3(64 * (4 * J + 2)), 0, st, w.C, NP, m0, LP, n, OFF, REST, ALL, w.dT, w.eT, \
-                       w.tauT, w.V, w.stat, w.redone)
+#define SAGE_TRI_ONE(J, JN, ALL)                                                                                       \
+    hipLaunchKernelGGL((tri_one_kernel<J, JN>), dim3(1), dim3(64 * (4 * J + 2)), 0, st, w.C, NP, m0, LP, n, ALL, w.dT, w.eT, w.tauT, \
+                       w.V, w.stat, w.redone)
 #define SAGE_TRI_MANY(J)                                                                                           \
     do {                                                                                                           \
         if (n > 64 && !alone)                                                                                      \
             hipLaunchKernelGGL(tri_many_kernel<J>, dim3(w.period * TriPlan<J>::NWG), dim3(TriPlan<J>::THREADS), 0, st, w.C, NP, m0, LP, \
                                n, w.dT, w.eT, w.tauT, w.V, w.stat, w.xch, w.xcd, __builtin_ctz(w.period),           \
-                               w.impatient ? 1 : poll_limit(J), w.Yt, w.claim);                                    \
-        SAGE_TRI_ONE(1, J, n > 64 && !alone ? n - 64 : 0, n > 64 && !alone ? w.Yt : nullptr, n > 64 && alone);      \
+                               w.impatient ? 1 : poll_limit(J), w.Yt, w.claim, w.redone);                          \
+        else                                                                                                       \
+            SAGE_TRI_ONE(1, J, n > 64);                                                                            \
     } while (0)
     switch (NP / 64) {
-        case 1: SAGE_TRI_ONE(1, 1, 0, nullptr, false); break;
+        case 1: SAGE_TRI_ONE(1, 1, false); break;
         case 2:
-            if (alone) SAGE_TRI_ONE(2, 2, 0, nullptr, false);
+            if (alone) SAGE_TRI_ONE(2, 2, false);
             else SAGE_TRI_MANY(2);
             break;
         case 4: SAGE_TRI_MANY(4); break;

@@ -174,7 +174,8 @@ struct EigWork {
     double* dI[2];  // NP: eigenvalues, ascending, in units of 2^stat[0]
     double* stat;   // [0] exponent of the scaling
     double* redone; // solves whose reduction one work-group repeated because the others were not there in time
-    unsigned* claim; // [0] zero before and after a reduction (TriClaim), [1] set when the solve is given up
+    unsigned* claim; // [0] zero before and after a reduction (TriClaim), [1] set when the solve is given up, [2], [3] bits of the
+                     // columns that are left of it (zero before it)
     bool impatient; // test hook: its work-groups wait for each other for one poll only
     double* known;  // LP: Gram matrix of the rows the last shrink wrote (diagonal): max(lambda_j - delta, 0)
     double* xch;    // exchange of the reduction (NP = 128, 256, 512): 4 slots of q and c, NP each; empty (all ones) before it
