@@ -38,31 +38,53 @@ __device__ __forceinline__ double dc_tolerance(const double* __restrict__ dT, co
     return 4.0 * DC_EPS * m;
 }
 
-// Root q of f = 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending): lambda = org + tau with org the
-// nearer of the poles around it. A group of L lanes works on a root; lane l holds the poles l + L e, e < E (z = 0 and
-// d = 1e30 beyond K). on: this group has a root (all lanes take part in the loop). The interpolation, which matches f, f' and
-// f'' by two poles and a constant (Borges and Gragg), converges cubically: a step below 1e-7 of tau is the last one. About 3.4 evaluations a
-// root, six for the slowest of 64 (with f and the derivatives of the two sides, which converges quadratically, 4.3 and seven
-// and a half). An evaluation is a chain of some 500 cycles (reciprocal, sums over L, square root, reciprocal) and 11 fp64
-// instructions a pole; a branch costs 100 cycles, so there is none but the loop's.
+// A root of f = 1 + sum_j z_j / (d_j - lambda) (z_j = rho z_j^2 > 0, K poles ascending), the one between the neighbouring poles pi and
+// pn, of weights zi and zn, or (last) the one above pn, the last: lambda = org + tau with org the nearer of the poles around it. A
+// group of L lanes works on a root; lane l holds the poles l + L e, e < E (z = 0 and d = 1e30 beyond K). on: this group has a
+// root (all lanes take part in the loop). It starts from the root of the two poles and a constant that stands for the others, their
+// sum at the middle of the bracket (R.-C. Li, LAPACK Working Note 89, 1993). The interpolation, which matches f, f' and f'' by two poles
+// and a constant (Borges and Gragg), converges cubically: a step below 1e-7 of tau is the last one. About 2.8 evaluations a root,
+// 4.8 for the slowest of 64 (started at a quarter of the gap and with one pole for the last root, which came in slowest most times,
+// 3.6 and 7.5). An evaluation is a chain of some 700 cycles (reciprocal, sums over L, square root, reciprocal) and 11 fp64 instructions
+// a pole; a branch costs 100 cycles, so there is none but the loop's. 64 rows in all: 32 -> 30 us.
 template <int L, int E>
-__device__ __forceinline__ void secular_root(bool on, int K, int q, int l, const double (&dj)[E], const double (&zj)[E], double dq,
-                                             double dq1, double zsum, double& org, double& tau) {
-    const bool last = q >= K - 1;
+__device__ __forceinline__ void secular_root(bool on, bool last, int K, const double (&dj)[E], const double (&zj)[E], double pi, double pn,
+                                             double zi, double zn, double zsum, double& org, double& tau) {
+    // The root of c + p / (di - x) + g / (dn - x), di < dn: c x^2 - a x + b = 0. Its error shrinks with the step, which is below 1e-7
+    // of t when it is the last, so a step needs few digits: the square root is the hardware's estimate with one correction, and so is
+    // the quotient. (A fraction, num / den.)
+    auto interpolate = [last](double c, double di, double dn, double p, double g, double& num, double& den) __attribute__((always_inline)) {
+        const double a = __builtin_fma(c, di + dn, p + g), b = __builtin_fma(c * di, dn, __builtin_fma(p, dn, g * di));
+        const double disc = fmax(__builtin_fma(a, a, -4.0 * c * b), 1e-280);
+        const double ys = __builtin_amdgcn_rsq(disc), r = disc * ys;
+        const double sq = __builtin_fma(__builtin_fma(-r, r, disc), 0.5 * ys, r);
+        const double h = 0.5 * (a + __builtin_copysign(sq, a));
+        const bool first = (a > 0.0) != last;  // of the two roots, the one between the poles or the one above them
+        num = first ? b : h;
+        den = first ? h : c;
+    };
+    auto inverse = [](double x) __attribute__((always_inline)) {
+        const double y = __builtin_amdgcn_rcp(x);
+        return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    };
+    double num, den;
+    const double gap = pn - pi, mid = 0.5 * (last ? zsum : gap), base = last ? pn : pi;
     double f0 = 0.0;
-    const double gap = dq1 - dq, mid = 0.5 * gap;
 #pragma unroll
-    for (int e = 0; e < E; ++e) f0 = __builtin_fma(zj[e], rcp64((dj[e] - dq) - mid), f0);
+    for (int e = 0; e < E; ++e) f0 = __builtin_fma(zj[e], rcp64((dj[e] - base) - mid), f0);
     f0 = 1.0 + lane_sum<L>(f0);
-    const bool left = last || f0 >= 0.0;
-    org = left ? dq : dq1;
-    double lo = left ? 0.0 : -mid;
-    double hi = last ? zsum * (1.0 + 4.0 * DC_EPS) : (left ? mid : 0.0);
-    double t = 0.5 * (lo + hi);
+    const bool left = f0 >= 0.0;
+    org = left ? base : pn;
+    double lo = left ? 0.0 : (last ? mid : -mid);
+    double hi = left ? mid : (last ? zsum * (1.0 + 4.0 * DC_EPS) : 0.0);
+    const double dli = pi - org, dln = pn - org, tol = 0.0625 * DC_EPS * K;
+    const double c0 = __builtin_fma(-zi, rcp64((pi - base) - mid), __builtin_fma(-zn, rcp64((pn - base) - mid), f0));
+    interpolate(c0, dli, dln, zi, zn, num, den);
+    const double t0 = num * inverse(den);
+    double t = (t0 > lo) & (t0 < hi) ? t0 : 0.5 * (lo + hi);
     double dl[E];  // distance of the poles
 #pragma unroll
     for (int e = 0; e < E; ++e) dl[e] = dj[e] - org;
-    const double dlq = dq - org, dlq1 = dq1 - org, tol = 0.0625 * DC_EPS * K;
     const double rgap = rcp64(gap);
     for (int it = 0; it < 60; ++it) {
         double f = 0.0, f1 = 0.0, f2 = 0.0;  // f - 1, f', f'' / 2
@@ -77,40 +99,37 @@ __device__ __forceinline__ void secular_root(bool on, int K, int q, int l, const
         f += 1.0;
         lo = f < 0.0 ? t : lo;  // (t lies inside the bracket)
         hi = f < 0.0 ? hi : t;
-        // c + P di^2 / (di - x) + G dn^2 / (dn - x) = 0 with P + G = f', P / di + G / dn = f'' / 2, the root between the poles
-        // di < 0 < dn: c x^2 - a x + b = 0. The last root has no pole above it: x = di + f' di^2 / (f - di f') (if that is not
-        // positive the step leaves the bracket, which is halved). A step needs few digits: its error shrinks with the step,
-        // which is below 1e-7 of t when it is the last. So the square root is the hardware's estimate with one correction, and so
-        // is the quotient.
-        const double di = dlq - t, dn = dlq1 - t;
+        // c + P di^2 / (di - x) + G dn^2 / (dn - x) = 0 with P + G = f', P / di + G / dn = f'' / 2. The last root is above both poles,
+        // where the difference of P and G leaves less of the digits: once f is small its steps are those of one pole, pn, x = dn +
+        // f' dn^2 / (f - dn f') (last roots of 4 to 64 poles: mean error 0.76 ulp against 1.24, for 0.1 evaluations).
+        const double di = dli - t, dn = dln - t;
         const double P = di * rgap * __builtin_fma(f2, dn, -f1), G = f1 - P;
-        const double Pd = P * di, Gd = G * dn, c = f - Pd - Gd;
-        const double p = Pd * di, g = Gd * dn;
-        const double a = __builtin_fma(c, di + dn, p + g), b = __builtin_fma(c * di, dn, __builtin_fma(p, dn, g * di));
-        const double disc = fmax(__builtin_fma(a, a, -4.0 * c * b), 1e-280);
-        const double ys = __builtin_amdgcn_rsq(disc), r = disc * ys;
-        const double sq = __builtin_fma(__builtin_fma(-r, r, disc), 0.5 * ys, r);
-        const double h = 0.5 * (a + __builtin_copysign(sq, a));
-        const double fd = f1 * di;
-        const double num = last ? fd * di : (a > 0.0 ? b : h), den = last ? f - fd : (a > 0.0 ? h : c);
-        double y = __builtin_amdgcn_rcp(den);
-        y = __builtin_fma(__builtin_fma(-den, y, 1.0), y, y);
-        const double x = __builtin_fma(num, y, last ? di : 0.0), step = t + x;
+        const double Pd = P * di, Gd = G * dn;
+        interpolate(f - Pd - Gd, di, dn, Pd * di, Gd * dn, num, den);
+        const double fd = f1 * dn;
+        const bool one = last & !(fabs(f) > 0.01);
+        num = one ? fd * dn : num;
+        den = one ? f - fd : den;
+        const double x = __builtin_fma(num, inverse(den), one ? dn : 0.0), step = t + x;
         // (false for NaN; the bracket lies between the poles. A small step that leaves it is rounding: t is the root.)
         const bool in = (step > lo) & (step < hi), small = fabs(x) <= 1e-7 * fabs(step);
         const double half = 0.5 * (lo + hi);
         const bool end = small | !(hi - lo > fabs(half) * DC_EPS);
-        // f is rounding: an eighth of what its terms may leave, their magnitudes taken from the two poles of the interpolation
-        const bool there = !(fabs(f) > tol * (1.0 + (fabs(Pd) + fabs(Gd))));
-        double tn = small ? t : half;
+        // f is rounding: an eighth of what its terms may leave, their magnitudes taken from the two poles of the interpolation (of
+        // the last root's they sum up to 1)
+        const bool there = !(fabs(f) > tol * (1.0 + (last ? 1.0 : fabs(Pd) + fabs(Gd))));
+        double tn = small | there ? t : half;
         tn = in ? step : tn;
-        on = on & !there;
         t = on ? tn : t;
-        on = on & !end;
+        on = on & !(end | there);
         if (!__any(on)) break;
     }
     tau = t;
 }
+
+// The lower one of the two poles next to root q of K: those around it, or the last two. (If there is one only, it is the upper one, with
+// none of weight below it.)
+__device__ __forceinline__ int lower_pole(int q, int K) { return max(min(q, K - 2), 0); }
 
 // |z_j| of the rank-one problem whose eigenvalues are exactly the computed roots: the product over i != j of
 // (lambda_i - d_j) / (d_i - d_j), times (lambda_j - d_j). Lane l holds roots l + L e.
@@ -147,7 +166,7 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
 // A merge is a chain of short phases between barriers; half the time goes into the roots, which is why their loops are
 // unrolled to what M needs, and the products of 16 rows and more run on the matrix cores (in scalar code, bound by LDS
 // reads, the last product alone took 17 us). 32 us in all (38 with the roots' cases told apart by branches and quadratic
-// steps), against 104 us for one loop over all sizes.
+// steps; 30 with the roots started nearby), against 104 us for one loop over all sizes.
 constexpr int DCB_LD = 65;   // columns of Q
 constexpr int DCB_LDU = 68;  // columns of U: the 16 columns x 4 rows of a matrix-core operand fall on distinct banks
 struct DcBlockLds {
@@ -310,7 +329,10 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
         zsum = lane_sum<LR>(zsum);
         double org, tau;
         const bool has = lir < Kr;
-        secular_root<LR, ER>(has, Kr, lir, lr, dj, zj, dkr, lir + 1 < Kr ? S.dk[ir + 1] : dkr + 1.0, zsum, org, tau);
+        const int ip = br + lower_pole(lir, Kr);
+        const double pn = S.dk[ip + (Kr > 1)], zi = S.zk[ip], zn = S.zk[ip + (Kr > 1)];
+        secular_root<LR, ER>(has, lir >= Kr - 1, Kr, dj, zj, Kr > 1 ? S.dk[ip] : pn - 1.0, pn, Kr > 1 ? rhor * zi * zi : 0.0, rhor * zn * zn,
+                             zsum, org, tau);
         const double val = has ? finite_or_zero(org + tau) : dkr;
         if (lr == 0) {
             S.org[ir] = org;
@@ -656,7 +678,9 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
             zsum += zj[e];
         }
         zsum = lane_sum<64>(zsum);
-        secular_root<64, E>(true, K, q, lane, dj, zj, w.dk[base + q], q + 1 < K ? w.dk[base + q + 1] : w.dk[base + q] + 1.0, zsum, org,
+        const int ip = base + lower_pole(q, K);
+        const double pn = w.dk[ip + (K > 1)], zi = w.zk[ip], zn = w.zk[ip + (K > 1)];
+        secular_root<64, E>(true, q >= K - 1, K, dj, zj, K > 1 ? w.dk[ip] : pn - 1.0, pn, K > 1 ? rho * zi * zi : 0.0, rho * zn * zn, zsum, org,
                             tau);
         val = finite_or_zero(org + tau);
     }
