@@ -11,8 +11,8 @@
 //     inside a bracket that is bisected when a step leaves it;
 //   * z is recomputed from the roots (M. Gu, S. Eisenstat, SIAM J. Matrix Anal. Appl. 16, 1995), which makes the
 //     eigenvectors z_j / (d_j - lambda_i) orthogonal to fp64 rounding however close the roots are.
-// Merges up to 64 rows run inside one work-group per 64 x 64 block (everything in LDS); the merges above it are four
-// kernels each: deflation, roots (a wave per root), z and the order of the new eigenvalues, and the products of the
+// Merges up to 64 rows run inside one work-group per 64 x 64 block (everything in LDS); the merges above it are three
+// kernels each: deflation and roots (a wave per root), z and the order of the new eigenvalues, and the products of the
 // halves' eigenvectors with the merge's on the fp64 matrix cores.
 // Every size, index and count derived here is clamped by construction (counts of comparisons between finite numbers), so
 // non-finite input gives wrong numbers but no access out of bounds.
@@ -81,7 +81,7 @@ __device__ __forceinline__ void secular_root(bool on, bool last, int K, const do
     const double c0 = __builtin_fma(-zi, rcp64((pi - base) - mid), __builtin_fma(-zn, rcp64((pn - base) - mid), f0));
     interpolate(c0, dli, dln, zi, zn, num, den);
     const double t0 = num * inverse(den);
-    double t = (t0 > lo) & (t0 < hi) ? t0 : 0.5 * (lo + hi);
+    double t = ((t0 > lo) & (t0 < hi)) ? t0 : 0.5 * (lo + hi);
     double dl[E];  // distance of the poles
 #pragma unroll
     for (int e = 0; e < E; ++e) dl[e] = dj[e] - org;
@@ -118,7 +118,7 @@ __device__ __forceinline__ void secular_root(bool on, bool last, int K, const do
         // f is rounding: an eighth of what its terms may leave, their magnitudes taken from the two poles of the interpolation (of
         // the last root's they sum up to 1)
         const bool there = !(fabs(f) > tol * (1.0 + (last ? 1.0 : fabs(Pd) + fabs(Gd))));
-        double tn = small | there ? t : half;
+        double tn = (small | there) ? t : half;
         tn = in ? step : tn;
         t = on ? tn : t;
         on = on & !(end | there);
@@ -494,77 +494,117 @@ __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const do
     for (int c = tid >> 6; c < 64; c += 8) Z[(int64_t)(b0 + c) * N + b0 + (tid & 63)] = S.Q[c * DCB_LD + (tid & 63)];
 }
 
-// ---- merges of m = 128, 256, 512 rows -----------------------------------------------------------------------------
+// ---- merges of M = 128, 256, 512 rows -----------------------------------------------------------------------------
 // Work arrays (N each, sub-problem at its base): dk, zk (poles and z of the survivors, then the deflated), col (their
 // columns of Z), half (indices of the survivors that live in the left half, then those in the right half), org, tau,
-// zh, val, npos; per sub-problem: K, k1 (survivors in the left half), dense (rotations mixed the halves).
-// One work-group of 512 threads per sub-problem: order the poles, deflate.
-__global__ __launch_bounds__(512) void dc_deflate_kernel(const double* __restrict__ dT, const double* __restrict__ eT, int N,
-                                                         int m, const double* __restrict__ dI, double* __restrict__ Z,
-                                                         DcWork w) {
-    __shared__ double d[512], ds[512], zs[512];
-    __shared__ int cs[512], sv[512], col[512];
-    __shared__ double rc[512], rs[512];
-    __shared__ int ra[512], rb[512];
+// zh, val, npos; ra, rb, rc, rs (rotations); per sub-problem: K, k1 (survivors in the left half), dense (rotations mixed the
+// halves), nrot.
+
+// Order of the poles, deflation, and one wave per root. Every work-group of a sub-problem orders and deflates for itself: a chain of
+// some 2 us, whereas a launch that did it for all of them took 5 to 6, of which 3 to 4 pass before its first instruction. (Jobs of 128,
+// 200 and 256 buffer rows: 10.84 -> 10.55, 9.21 -> 8.90 and 11.16 -> 10.79 ms, of 512: 29.44 -> 29.35.) The work-group after the
+// last root's leaves the records for the kernels that follow. Columns that are rotated are rotated by dc_weights_kernel: here other work-groups still read them. WYJ > 0 (the first
+// merge of N = 64 WYJ): the row of work-groups after the last sub-problem's forms the triangular factors of the
+// reduction's blocks of reflectors, a wave each (wy_factor).
+template <int M, int WYJ>
+__global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict__ dT, const double* __restrict__ eT, int N,
+                                                       const double* __restrict__ dI, const double* __restrict__ Z, DcWork w,
+                                                       const double* __restrict__ V, const double* __restrict__ tauT, int n,
+                                                       double* __restrict__ Tw) {
+    constexpr int E = M / 64, half = M / 2, P = M > 256 ? M / 256 : 1;  // entries a lane of a root's wave, a thread
+    __shared__ double d[M], ds[M], zs[M];
+    __shared__ int cs[M], sv[M], col[M];
     __shared__ int sK, snr, sany;
-    __shared__ int wsum[8], wsum2[8];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int base = blockIdx.x * m, half = m >> 1;
-    const double tol = dc_tolerance(dT, eT, N, lane);
+    __shared__ int wsum[E], wsum2[E];  // per 64 entries
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if constexpr (WYJ > 0) {
+        static_assert(8 * WYJ <= M, "as many waves in a row of work-groups as blocks");
+        if (blockIdx.y == gridDim.y - 1) {
+            const int q = blockIdx.x * 4 + wave;
+            if (q * WY <= n - 2) wy_factor<WYJ>(V, tauT, q, n, lane, Tw);
+            return;
+        }
+    }
+    const int base = blockIdx.y * M;
+    const bool records = blockIdx.x == M / 4;
+    const bool on = M >= 256 || tid < M;  // this thread has entries tid + 256 p
     const double ec = finite_or_zero(eT[base + half - 1]), rho = fabs(ec);
-    const bool on = tid < m;
-    double di = 0.0, zi = 0.0;
-    if (on) {
-        di = dI[base + tid];
-        d[tid] = di;
-        const double* zc = Z + (int64_t)(base + tid) * N;
-        zi = finite_or_zero(tid < half ? zc[base + half - 1] : (ec < 0.0 ? -zc[base + half] : zc[base + half]));
-    }
-    if (tid == 0) sany = 0;
-    __syncthreads();
-    if (on) {
-        // both halves are sorted: rank = own position + position in the other half
-        const int o0 = tid < half ? half : 0;
-        int a = 0, b = half;  // number of entries of the other half that go before this one
-        while (a < b) {
-            const int mid = (a + b) >> 1;
-            const double x = d[o0 + mid];
-            const bool pre = x < di || (x == di && o0 == 0);
-            if (pre) a = mid + 1;
-            else b = mid;
-        }
-        const int r = (tid < half ? tid : tid - half) + a;
-        ds[r] = di;
-        zs[r] = zi;
-        cs[r] = tid;
-    }
-    __syncthreads();
-    const bool live = on && rho * fabs(zs[tid]) > tol;
-    {
-        const unsigned long long mask = __ballot(live);
-        const int pre = __popcll(mask & ((1ull << lane) - 1ull));
-        if (lane == 0) wsum[wave] = __popcll(mask);
-        __syncthreads();
-        int off = 0, tot = 0;
-        for (int q = 0; q < 8; ++q) {
-            off += q < wave ? wsum[q] : 0;
-            tot += wsum[q];
-        }
-        if (on) sv[live ? off + pre : tot + tid - (off + pre)] = tid;
-        if (tid == 0) {
-            sK = tot;
-            snr = 0;
+    double di[P], zi[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int t = tid + 256 * p;
+        if (on) {
+            const double* zc = Z + (int64_t)(base + t) * N;
+            di[p] = dI[base + t];
+            zi[p] = t < half ? zc[base + half - 1] : zc[base + half];
         }
     }
+    const double tol = dc_tolerance(dT, eT, N, lane);
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (on) {
+            const int t = tid + 256 * p;
+            d[t] = di[p];
+            zi[p] = finite_or_zero(t >= half && ec < 0.0 ? -zi[p] : zi[p]);
+        }
+    if (tid == 0) {
+        sany = 0;
+        snr = 0;
+    }
     __syncthreads();
-    if (tid + 1 < sK) {
-        const int s0 = sv[tid], s1 = sv[tid + 1];
-        if (poles_equal(ds[s0], zs[s0], ds[s1], zs[s1], tol)) sany = 1;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (on) {
+            // both halves are sorted: rank = own position + position in the other half
+            const int t = tid + 256 * p, o0 = t < half ? half : 0;
+            int a = 0, b = half;  // number of entries of the other half that go before this one
+            while (a < b) {
+                const int mid = (a + b) >> 1;
+                const double x = d[o0 + mid];
+                const bool pre = x < di[p] || (x == di[p] && o0 == 0);
+                if (pre) a = mid + 1;
+                else b = mid;
+            }
+            const int r = (t < half ? t : t - half) + a;
+            ds[r] = di[p];
+            zs[r] = zi[p];
+            cs[r] = t;
+        }
+    __syncthreads();
+    unsigned long long mask[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int t = tid + 256 * p;
+        mask[p] = __ballot(on && rho * fabs(zs[t & (M - 1)]) > tol);
+        if (on && lane == 0) wsum[t >> 6] = __popcll(mask[p]);
+    }
+    __syncthreads();
+    int tot = 0;
+#pragma unroll
+    for (int g = 0; g < E; ++g) tot += wsum[g];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (on) {
+            const int t = tid + 256 * p;
+            int off = __popcll(mask[p] & ((1ull << lane) - 1ull));
+#pragma unroll
+            for (int g = 0; g < E; ++g) off += g < (t >> 6) ? wsum[g] : 0;
+            sv[(mask[p] >> lane) & 1ull ? off : tot + t - off] = t;
+        }
+    if (tid == 0) sK = tot;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int t = tid + 256 * p;
+        if (on && t + 1 < tot) {
+            const int s0 = sv[t], s1 = sv[t + 1];
+            if (poles_equal(ds[s0], zs[s0], ds[s1], zs[s1], tol)) sany = 1;
+        }
     }
     __syncthreads();
     if (sany) {  // rare: walk the survivors in order, rotate equal poles together
         if (tid == 0) {
-            const int Kb = sK;
+            const int Kb = tot;
             int nk = 0, nr = 0, nd = 0, pj = -1;
             for (int q = 0; q < Kb; ++q) {
                 const int nj = sv[q];
@@ -580,12 +620,14 @@ __global__ __launch_bounds__(512) void dc_deflate_kernel(const double* __restric
                     zs[pj] = 0.0;
                     ds[pj] = d0 * c * c + d1 * s * s;
                     ds[nj] = d0 * s * s + d1 * c * c;
-                    ra[nr] = cs[pj];
-                    rb[nr] = cs[nj];
-                    rc[nr] = c;
-                    rs[nr] = s;
+                    if (records) {
+                        w.ra[base + nr] = cs[pj];
+                        w.rb[base + nr] = cs[nj];
+                        w.rc[base + nr] = c;
+                        w.rs[base + nr] = s;
+                    }
                     ++nr;
-                    col[m - 1 - nd++] = pj;
+                    col[M - 1 - nd++] = pj;
                     pj = nj;
                 } else {
                     col[nk++] = pj;
@@ -594,93 +636,74 @@ __global__ __launch_bounds__(512) void dc_deflate_kernel(const double* __restric
             }
             if (pj >= 0) col[nk++] = pj;
             for (int q = 0; q < nk; ++q) sv[q] = col[q];
-            for (int q = 0; q < nd; ++q) sv[nk + q] = col[m - 1 - q];
+            for (int q = 0; q < nd; ++q) sv[nk + q] = col[M - 1 - q];
             sK = nk;
             snr = nr;
         }
         __syncthreads();
-        // the columns become dense: clear what was not stored of them, then rotate (a thread per row)
-        if (on) {
-            for (int c = 0; c < m; ++c)
-                if ((c < half) != (tid < half)) Z[(int64_t)(base + c) * N + base + tid] = 0.0;
-            const int nr = snr;
-            for (int q = 0; q < nr; ++q) {
-                double* A = Z + (int64_t)(base + ra[q]) * N + base + tid;
-                double* B = Z + (int64_t)(base + rb[q]) * N + base + tid;
-                const double a = *A, b = *B;
-                *A = rc[q] * a + rs[q] * b;
-                *B = rc[q] * b - rs[q] * a;
+    }
+    const int K = sK;
+    if (records) {
+        const bool dense = snr > 0;
+        int cq[P];
+        unsigned long long ml[P], mr[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const int t = tid + 256 * p;
+            cq[p] = on ? cs[sv[t]] : 0;
+            ml[p] = __ballot(on && t < K && !dense && cq[p] < half);
+            mr[p] = __ballot(on && t < K && !dense && cq[p] >= half);
+            if (on && lane == 0) {
+                wsum[t >> 6] = __popcll(ml[p]);
+                wsum2[t >> 6] = __popcll(mr[p]);
             }
         }
         __syncthreads();
-    }
-    const int K = sK;
-    const bool dense = snr > 0;
-    const int cq = on ? cs[sv[tid]] : 0;
-    const bool inl = tid < K && !dense && cq < half, inr = tid < K && !dense && cq >= half;
-    {
-        const unsigned long long ml = __ballot(inl), mr = __ballot(inr);
-        if (lane == 0) {
-            wsum[wave] = __popcll(ml);
-            wsum2[wave] = __popcll(mr);
-        }
-        __syncthreads();
-        int ol = __popcll(ml & ((1ull << lane) - 1ull)), orr = __popcll(mr & ((1ull << lane) - 1ull)), tl = 0;
-        for (int q = 0; q < 8; ++q) {
-            ol += q < wave ? wsum[q] : 0;
-            orr += q < wave ? wsum2[q] : 0;
-            tl += wsum[q];
-        }
-        if (inl) w.half[base + ol] = tid;
-        if (inr) w.half[base + tl + orr] = tid;
-        if (dense && tid < K) w.half[base + tid] = tid;
+        int tl = 0;
+#pragma unroll
+        for (int g = 0; g < E; ++g) tl += wsum[g];
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (on) {
+                const int t = tid + 256 * p;
+                int ol = __popcll(ml[p] & ((1ull << lane) - 1ull)), orr = __popcll(mr[p] & ((1ull << lane) - 1ull));
+#pragma unroll
+                for (int g = 0; g < E; ++g) {
+                    ol += g < (t >> 6) ? wsum[g] : 0;
+                    orr += g < (t >> 6) ? wsum2[g] : 0;
+                }
+                if ((ml[p] >> lane) & 1ull) w.half[base + ol] = t;
+                if ((mr[p] >> lane) & 1ull) w.half[base + tl + orr] = t;
+                if (dense && t < K) w.half[base + t] = t;
+                w.dk[base + t] = ds[sv[t]];
+                w.zk[base + t] = zs[sv[t]];
+                w.col[base + t] = base + cq[p];
+            }
         if (tid == 0) {
-            w.K[blockIdx.x] = K;
-            w.k1[blockIdx.x] = tl;
-            w.dense[blockIdx.x] = dense ? 1 : 0;
+            w.K[blockIdx.y] = K;
+            w.k1[blockIdx.y] = tl;
+            w.dense[blockIdx.y] = dense ? 1 : 0;
+            w.nrot[blockIdx.y] = snr;
         }
+        return;
     }
-    if (on) {
-        w.dk[base + tid] = ds[sv[tid]];
-        w.zk[base + tid] = zs[sv[tid]];
-        w.col[base + tid] = base + cq;
-    }
-}
-
-// One wave per root. WYJ > 0 (the first merge of N = 64 WYJ): the row of work-groups after the last sub-problem's forms the
-// triangular factors of the reduction's blocks of reflectors, a wave each (wy_factor).
-template <int E, int WYJ>  // m = 64 E
-__global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict__ eT, int m, DcWork w,
-                                                       const double* __restrict__ V, const double* __restrict__ tauT, int n,
-                                                       double* __restrict__ Tw) {
-    const int lane = threadIdx.x & 63;
-    const int q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if constexpr (WYJ > 0) {
-        static_assert(8 * WYJ <= 128, "as many waves in a row of work-groups as blocks");
-        if (blockIdx.y == gridDim.y - 1) {
-            if (q * WY <= n - 2) wy_factor<WYJ>(V, tauT, q, n, lane, Tw);
-            return;
-        }
-    }
-    const int base = blockIdx.y * m;
-    const int K = w.K[blockIdx.y];
-    double org = 0.0, tau = 0.0, val = w.dk[base + q];
+    const int q = blockIdx.x * 4 + wave;
+    double org = 0.0, tau = 0.0, val = ds[sv[q]];
     if (q < K) {
-        const double rho = fabs(finite_or_zero(eT[base + (m >> 1) - 1]));
         double dj[E], zj[E], zsum = 0.0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int j = lane + 64 * e;
-            const bool on = j < K;
-            dj[e] = on ? w.dk[base + j] : 1e30;
-            const double z = on ? w.zk[base + j] : 0.0;
+            const int j = lane + 64 * e, s = sv[j];
+            const bool live = j < K;
+            dj[e] = live ? ds[s] : 1e30;
+            const double z = live ? zs[s] : 0.0;
             zj[e] = rho * z * z;
             zsum += zj[e];
         }
         zsum = lane_sum<64>(zsum);
-        const int ip = base + lower_pole(q, K);
-        const double pn = w.dk[ip + (K > 1)], zi = w.zk[ip], zn = w.zk[ip + (K > 1)];
-        secular_root<64, E>(true, q >= K - 1, K, dj, zj, K > 1 ? w.dk[ip] : pn - 1.0, pn, K > 1 ? rho * zi * zi : 0.0, rho * zn * zn, zsum, org,
+        const int ip = lower_pole(q, K), si = sv[ip], sn = sv[ip + (K > 1)];
+        const double pn = ds[sn], z0 = zs[si], z1 = zs[sn];
+        secular_root<64, E>(true, q >= K - 1, K, dj, zj, K > 1 ? ds[si] : pn - 1.0, pn, K > 1 ? rho * z0 * z0 : 0.0, rho * z1 * z1, zsum, org,
                             tau);
         val = finite_or_zero(org + tau);
     }
@@ -691,12 +714,31 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
     }
 }
 
-// one wave per index: z of the merge, and the place of its eigenvalue among all
-template <int E>  // m = 64 E
-__global__ __launch_bounds__(256) void dc_weights_kernel(int m, DcWork w, double* __restrict__ dO) {
+// one wave per index: z of the merge, and the place of its eigenvalue among all. The work-group after the last index's rotates
+// columns of Z where that is called for.
+template <int M>
+__global__ __launch_bounds__(256) void dc_weights_kernel(DcWork w, double* __restrict__ dO, double* __restrict__ Z, int N) {
+    constexpr int E = M / 64, m = M;
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int base = blockIdx.y * m;
+    if (blockIdx.x == M / 4) {
+        const int nr = w.nrot[blockIdx.y];
+        if (nr == 0) return;
+        // the columns become dense: clear what was not stored of them, then rotate (a thread per row)
+        for (int r = threadIdx.x; r < m; r += 256) {
+            for (int c = 0; c < m; ++c)
+                if ((c < m / 2) != (r < m / 2)) Z[(int64_t)(base + c) * N + base + r] = 0.0;
+            for (int i = 0; i < nr; ++i) {
+                double* A = Z + (int64_t)(base + w.ra[base + i]) * N + base + r;
+                double* B = Z + (int64_t)(base + w.rb[base + i]) * N + base + r;
+                const double a = *A, b = *B, c = w.rc[base + i], s = w.rs[base + i];
+                *A = c * a + s * b;
+                *B = c * b - s * a;
+            }
+        }
+        return;
+    }
     const int K = w.K[blockIdx.y];
     const double val = w.val[base + q];
     int np = 0;
@@ -845,18 +887,17 @@ hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
     int cur = 0;
     for (int m = 128; m <= N; m *= 2) {
         const int S = N / m;
-        hipLaunchKernelGGL(dc_deflate_kernel, dim3(S), dim3(512), 0, st, w.dT, w.eT, N, m, w.dI[cur], w.Z[cur], w.dc);
-#define SAGE_ROOTS(E, WYJ)                                                                                              \
+#define SAGE_ROOTS(M, WYJ)                                                                                               \
     do {                                                                                                                \
-        hipLaunchKernelGGL((dc_roots_kernel<E, WYJ>), dim3(m / 4, WYJ > 0 ? S + 1 : S), dim3(256), 0, st, w.eT, m, w.dc, \
-                           w.V, w.tauT, n, w.Tw);                                                                       \
-        hipLaunchKernelGGL(dc_weights_kernel<E>, dim3(m / 4, S), dim3(256), 0, st, m, w.dc, w.dI[cur ^ 1]);              \
+        hipLaunchKernelGGL((dc_roots_kernel<M, WYJ>), dim3(M / 4 + 1, WYJ > 0 ? S + 1 : S), dim3(256), 0, st, w.dT, w.eT, N, w.dI[cur], \
+                           w.Z[cur], w.dc, w.V, w.tauT, n, w.Tw);                                                       \
+        hipLaunchKernelGGL(dc_weights_kernel<M>, dim3(M / 4 + 1, S), dim3(256), 0, st, w.dc, w.dI[cur ^ 1], w.Z[cur], N); \
     } while (0)
-        if (m == 512) SAGE_ROOTS(8, 0);
-        else if (m == 256) SAGE_ROOTS(4, 0);
-        else if (N == 128) SAGE_ROOTS(2, 2);
-        else if (N == 256) SAGE_ROOTS(2, 4);
-        else SAGE_ROOTS(2, 8);
+        if (m == 512) SAGE_ROOTS(512, 0);
+        else if (m == 256) SAGE_ROOTS(256, 0);
+        else if (N == 128) SAGE_ROOTS(128, 2);
+        else if (N == 256) SAGE_ROOTS(128, 4);
+        else SAGE_ROOTS(128, 8);
 #undef SAGE_ROOTS
         hipLaunchKernelGGL(dc_vectors_kernel, dim3(m / 32, m / 64, S), dim3(256), 0, st, w.Z[cur], w.Z[cur ^ 1], N, m, w.dc);
         cur ^= 1;
