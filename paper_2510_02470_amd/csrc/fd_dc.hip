@@ -497,7 +497,7 @@ __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const do
 // ---- merges of M = 128, 256, 512 rows -----------------------------------------------------------------------------
 // Work arrays (N each, sub-problem at its base): dk, zk (poles and z of the survivors, then the deflated), col (their
 // columns of Z), half (indices of the survivors that live in the left half, then those in the right half), org, tau,
-// zh, val, npos; ra, rb, rc, rs (rotations); per sub-problem: K, k1 (survivors in the left half), dense (rotations mixed the
+// zh, val, npos (place of its eigenvalue), from (the inverse); ra, rb, rc, rs (rotations); per sub-problem: K, k1 (survivors in the left half), dense (rotations mixed the
 // halves), nrot.
 
 // Order of the poles, deflation, and one wave per root. Every work-group of a sub-problem orders and deflates for itself: a chain of
@@ -512,10 +512,12 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
                                                        const double* __restrict__ V, const double* __restrict__ tauT, int n,
                                                        double* __restrict__ Tw) {
     constexpr int E = M / 64, half = M / 2, P = M > 256 ? M / 256 : 1;  // entries a lane of a root's wave, a thread
+    // (14.5 KB at 512 rows: it goes beside a Gram work-group of the side stream, of 144. With 18.5 KB it waited for that, 309 us.)
     __shared__ double d[M], ds[M], zs[M];
-    __shared__ int cs[M], sv[M], col[M];
+    __shared__ unsigned short cs[M], sv[M];
     __shared__ int sK, snr, sany;
     __shared__ int wsum[E], wsum2[E];  // per 64 entries
+    int* const col = reinterpret_cast<int*>(d);  // (once the ranks are known)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if constexpr (WYJ > 0) {
         static_assert(8 * WYJ <= M, "as many waves in a row of work-groups as blocks");
@@ -568,7 +570,7 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
             const int r = (t < half ? t : t - half) + a;
             ds[r] = di[p];
             zs[r] = zi[p];
-            cs[r] = t;
+            cs[r] = (unsigned short)t;
         }
     __syncthreads();
     unsigned long long mask[P];
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
             int off = __popcll(mask[p] & ((1ull << lane) - 1ull));
 #pragma unroll
             for (int g = 0; g < E; ++g) off += g < (t >> 6) ? wsum[g] : 0;
-            sv[(mask[p] >> lane) & 1ull ? off : tot + t - off] = t;
+            sv[(mask[p] >> lane) & 1ull ? off : tot + t - off] = (unsigned short)t;
         }
     if (tid == 0) sK = tot;
     __syncthreads();
@@ -635,8 +637,8 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(const double* __restrict_
                 }
             }
             if (pj >= 0) col[nk++] = pj;
-            for (int q = 0; q < nk; ++q) sv[q] = col[q];
-            for (int q = 0; q < nd; ++q) sv[nk + q] = col[M - 1 - q];
+            for (int q = 0; q < nk; ++q) sv[q] = (unsigned short)col[q];
+            for (int q = 0; q < nd; ++q) sv[nk + q] = (unsigned short)col[M - 1 - q];
             sK = nk;
             snr = nr;
         }
@@ -766,6 +768,7 @@ __global__ __launch_bounds__(256) void dc_weights_kernel(DcWork w, double* __res
     if (lane == 0) {
         w.zh[base + q] = zz;
         w.npos[base + q] = np;
+        w.from[base + np] = q;
         dO[base + np] = val;
     }
 }
@@ -872,8 +875,8 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(const double* __restric
     }
 }
 
-// T = Z D Z^T: eigenvalues ascending in dI, eigenvectors in the columns of Z (buffer dc_result(N) of either), and the
-// triangular factors of the reflectors in Tw. n: rows in use.
+// T = Z D Z^T: eigenvalues ascending in dI[dc_result(N)], the triangular factors of the reflectors in Tw. The eigenvectors are the
+// columns of Z[0] (N = 64), or what the last merge makes of those of Z[dc_result(N) ^ 1] by `dc`. n: rows in use.
 hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
     if (N != 64 && N != 128 && N != 256 && N != 512) return hipErrorInvalidValue;
     const void* block = N == 64 ? (const void*)dc_block_kernel<true> : (const void*)dc_block_kernel<false>;
@@ -899,6 +902,7 @@ hipError_t launch_dc(const EigWork& w, int N, int n, hipStream_t st) {
         else if (N == 256) SAGE_ROOTS(128, 4);
         else SAGE_ROOTS(128, 8);
 #undef SAGE_ROOTS
+        if (m == N) break;  // (the last merge's vectors are formed where they are used: tri_back_kernel)
         hipLaunchKernelGGL(dc_vectors_kernel, dim3(m / 32, m / 64, S), dim3(256), 0, st, w.Z[cur], w.Z[cur ^ 1], N, m, w.dc);
         cur ^= 1;
     }

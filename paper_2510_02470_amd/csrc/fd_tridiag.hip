@@ -888,8 +888,116 @@ __global__ __launch_bounds__(TriPlan<J>::THREADS, 1) void tri_many_kernel(const 
 // OUT_SPLIT, OUT_F32: in the orders of the rebuild (fd_coeffs.h). OUT_M: in fp64, row m of M in matrix indices, for a rebuild that
 // comes later (fd_defer.hip). The work-group after the last row does the scalars.
 enum { OUT_Y, OUT_F32, OUT_SPLIT, OUT_M };
+
+// Eigenvector `col` of the last merge of N = 64 J rows, rows 2 lane, 2 lane + 1 of each 128, by one wave: u_j = zh_j / (d_j - lambda),
+// normalised, and the sum of u_j times the survivors' columns of Z, of which those of the left (right) half have rows in that half
+// only. A kernel on the matrix cores for all of them, one launch more, took 10 us at N = 128 and 14 at 256, and formed those that
+// nobody wants too; here they cost 6.5 and 8 (jobs of 128, 200 and 256 buffer rows: 10.62 -> 10.30, 8.93 -> 8.71 and 10.85 -> 10.67
+// ms; at 512, where the side stream or the rebuild is what a cycle waits for, 29.4 as before).
+template <int J>
+__device__ __forceinline__ void merged_vector(const double* __restrict__ Z, const DcWork& dc, int col, int lane, double (&z)[J]) {
+    constexpr int N = 64 * J, half = N / 2, PAIRS = J / 2, U = 16 / PAIRS;  // steps requested together
+    static_assert(half % (2 * U) == 0, "two sets of steps at a time");
+    __shared__ double us[N], lu[N];
+    __shared__ int lc[N];  // survivors' columns and entries of u in the order they are taken
+    const int q = dc.from[col] & (N - 1), K = dc.K[0], k1 = dc.k1[0];  // (an index whatever the input was)
+    const bool dense = dc.dense[0] != 0;
+    auto left_pair = [&](int p) { return N == 128 ? lane < 32 : p < PAIRS / 2; };
+    if (q >= K) {  // deflated: a column as it is
+        const int src = dc.col[q];
+        const double* c = Z + (int64_t)src * N + 2 * lane;
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const f64x2 x = *reinterpret_cast<const f64x2*>(c + 128 * p);
+            const bool own = dense || (src < half) == left_pair(p);  // (what else is stored there is stale)
+            z[2 * p] = own ? x[0] : 0.0;
+            z[2 * p + 1] = own ? x[1] : 0.0;
+        }
+        return;
+    }
+    const double org = dc.org[q], tau = dc.tau[q];
+    double u[J], nn = 0.0;
+    int list[J];
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+        const int j = lane + 64 * e;
+        list[e] = j < K ? dc.half[j] : 0;
+        u[e] = j < K ? dc.zh[j] * rcp64((dc.dk[j] - org) - tau) : 0.0;
+        nn = __builtin_fma(u[e], u[e], nn);
+        // fill: entries of zero with a column that is finite in its half
+        lu[j] = 0.0;
+        lc[j] = dense || j < half ? 0 : half;
+    }
+    nn = lane_sum<64>(nn);
+    const double inv = nn > 0.0 ? rcp64(__builtin_sqrt(nn)) : 0.0;
+#pragma unroll
+    for (int e = 0; e < J; ++e) us[lane + 64 * e] = u[e] * inv;
+    __syncthreads();
+    // (not dense: at most `half` of either half, the left one's first)
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+        const int s = lane + 64 * e;
+        if (s < K) {
+            const int to = dense || s < k1 ? s : half + s - k1;
+            lu[to] = us[list[e]];
+            lc[to] = dc.col[list[e]];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < J; ++j) z[j] = 0.0;
+    const double* const zl = Z + 2 * lane;
+    if (dense) {
+        for (int s = 0; s < K; ++s) {
+            const double us_ = lu[s];
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+                const f64x2 x = *reinterpret_cast<const f64x2*>(zl + (int64_t)lc[s] * N + 128 * p);
+                z[2 * p] = __builtin_fma(us_, x[0], z[2 * p]);
+                z[2 * p + 1] = __builtin_fma(us_, x[1], z[2 * p + 1]);
+            }
+        }
+        return;
+    }
+    struct Steps {
+        f64x2 x[U][PAIRS];
+        double u[U][2];
+    };
+    auto fetch = [&](int s0, Steps& t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int s = s0 + i;
+            const int cl = lc[s], cr = lc[half + s];
+            t.u[i][0] = lu[s];
+            t.u[i][1] = lu[half + s];
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p)
+                t.x[i][p] = *reinterpret_cast<const f64x2*>(zl + (left_pair(p) ? cl : cr) * N + 128 * p);
+        }
+    };
+    auto add = [&](const Steps& t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+                const double w = left_pair(p) ? t.u[i][0] : t.u[i][1];
+                z[2 * p] = __builtin_fma(w, t.x[i][p][0], z[2 * p]);
+                z[2 * p + 1] = __builtin_fma(w, t.x[i][p][1], z[2 * p + 1]);
+            }
+    };
+    const int steps = max(k1, K - k1);  // <= half
+    Steps ta, tb;
+    fetch(0, ta);
+    for (int s = 0; s < steps; s += 2 * U) {
+        fetch(s + U, tb);  // (s + 2 U <= half)
+        add(ta);
+        fetch(s + 2 * U < half ? s + 2 * U : 0, ta);  // (beyond the end: repeated, not used)
+        add(tb);
+    }
+}
+
 template <int J, int OUT>
-__global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restrict__ Z, const double* __restrict__ V,
+__global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restrict__ Z, DcWork dc, const double* __restrict__ V,
                                                          const double* __restrict__ Tw, int m0, int LP, int n,
                                                          double* __restrict__ Yt, int NP, CoeffArgs cf,
                                                          const double* __restrict__ dv, const double* __restrict__ C,
@@ -953,8 +1061,8 @@ __global__ __launch_bounds__(64, 1) void tri_back_kernel(const double* __restric
         }
     };
     double z[J];
-#pragma unroll
-    for (int j = 0; j < J; j += JW) load_rows(Z + (int64_t)col * N + JW * lane + 64 * j, z, j);
+    if constexpr (J == 1) z[0] = Z[(int64_t)col * N + lane];
+    else merged_vector<J>(Z, dc, col, lane, z);
     struct Block {
         double v[WY][J], t;  // t: entry (lane >> 3, lane & 7) of T
     };
@@ -1149,7 +1257,7 @@ hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, c
     const CoeffArgs args = cf ? *cf : CoeffArgs{};
 #define SAGE_BACK(J, OUT)                                                                                                 \
     hipLaunchKernelGGL((tri_back_kernel<J, OUT>), dim3(OUT == OUT_Y ? count : args.MP + 1), dim3(64), 0, st,               \
-                       w.Z[dc_result(NP)], w.V, w.Tw, m0, LP, n, w.Yt, NP, args, dv, w.C, w.stat, w.known)
+                       w.Z[NP == 64 ? 0 : dc_result(NP) ^ 1], w.dc, w.V, w.Tw, m0, LP, n, w.Yt, NP, args, dv, w.C, w.stat, w.known)
 #define SAGE_BACK_J(J)                        \
     if (!cf) SAGE_BACK(J, OUT_Y);             \
     else if (args.M) SAGE_BACK(J, OUT_M);       \

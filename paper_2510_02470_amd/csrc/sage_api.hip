@@ -993,7 +993,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
             for (int i = 0; i < 2; ++i) take(w.dI[i], n1);
             for (double** p : {&w.dT, &w.eT, &w.tauT, &w.known, &w.dc.dk, &w.dc.zk, &w.dc.org, &w.dc.tau, &w.dc.val, &w.dc.zh, &w.dc.rc, &w.dc.rs})
                 take(*p, n1);
-            for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.ra, &w.dc.rb, &w.dc.K, &w.dc.k1, &w.dc.dense, &w.dc.nrot}) take(*p, n1);
+            for (int** p : {&w.dc.col, &w.dc.half, &w.dc.npos, &w.dc.from, &w.dc.ra, &w.dc.rb, &w.dc.K, &w.dc.k1, &w.dc.dense, &w.dc.nrot}) take(*p, n1);
             if (pass == 0) CALLOC(c->eig_mem, bytes);
         }
         xcd_take(c);

@@ -159,7 +159,7 @@ hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const f
 // fd_tridiag.hip, fd_dc.hip, fd_eig.hip: the eigensolve
 struct DcWork {  // work arrays of the merges above 64 rows (see fd_dc.hip)
     double *dk, *zk, *org, *tau, *val, *zh, *rc, *rs;  // NP each
-    int *col, *half, *npos, *ra, *rb;                  // NP each
+    int *col, *half, *npos, *from, *ra, *rb;           // NP each
     int *K, *k1, *dense, *nrot;                        // per sub-problem
 };
 struct EigWork {
