@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void defer_coeffs_kernel(const double* __restr
 struct DeferReduce {
     const float* cross;
     int64_t stride;  // between the sources' partial tiles
-    int sources, cross_groups;
+    int sources, top_groups, cross_groups;  // groups of the first source, of the others
     int col[GRAM_TOPS];
     const float* fresh;  // the triangle's
     int fresh_tiles, fresh_groups;
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void defer_reduce_kernel(DeferReduce g, double
     const int s = cross ? t / (q * q) : 0, idx = cross ? t - s * q * q : t - g.sources * q * q;
     const float* p0 = (cross ? g.cross + s * g.stride : g.fresh) + (int64_t)idx * 4096 + e;
     const int64_t gstride = (int64_t)(cross ? q * q : g.fresh_tiles) * 4096;
-    const int groups = cross ? g.cross_groups : g.fresh_groups, per = (groups + SEG - 1) / SEG;
+    const int groups = cross ? (s == 0 ? g.top_groups : g.cross_groups) : g.fresh_groups, per = (groups + SEG - 1) / SEG;
     int k = seg * per;
     const int k1 = k + per < groups ? k + per : groups;
     double sum = 0.0;
@@ -142,12 +142,12 @@ __global__ __launch_bounds__(256) void defer_reduce_kernel(DeferReduce g, double
     C[gc * NP + gr] = sum;
 }
 
-hipError_t launch_defer_reduce(const float* cross, int64_t stride, int sources, const int* col, const GramPlan& pc, const float* fresh,
+hipError_t launch_defer_reduce(const float* cross, int64_t stride, int sources, const int* col, int top_groups, int groups, const float* fresh,
                                const GramPlan& pn, double* K, int ldk, double* C, const Dims& d, hipStream_t st) {
-    DeferReduce g{cross, stride, sources, pc.groups, {}, fresh, pn.tiles, pn.groups};
+    DeferReduce g{cross, stride, sources, top_groups, groups, {}, fresh, pn.tiles, pn.groups};
     for (int s = 0; s < sources; ++s) g.col[s] = col[s];
     const int q = d.NP / 128, tiles = sources * q * q + q * (q + 1) / 2;
-    if (pc.groups >= 64)
+    if (groups >= 64)
         hipLaunchKernelGGL(defer_reduce_kernel<8>, dim3(tiles, 128), dim3(256), 0, st, g, K, ldk, C, d.NP);
     else
         hipLaunchKernelGGL(defer_reduce_kernel<1>, dim3(tiles, 16), dim3(256), 0, st, g, K, ldk, C, d.NP);

@@ -497,12 +497,13 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(GramTops tops
 
 // The same rectangle of two blocks kept in pieces of bf16 (half16), the top rows being an earlier block's: one part each, one
 // product (the bits of the kernel above, whose other products add exact zeros), nothing to convert. Bound by memory: the pieces
-// go straight to LDS, three slabs (48 KB) at a time into a ring of three, two of them on their way (144 KB of a CU's 160).
+// go straight to LDS, two slabs (32 KB) at a time into a ring of three, two of them on their way. (With three slabs at a time, 144 KB of
+// a CU's 160, the merges of the eigensolve beside it waited for it, 230 us.)
 __global__ __launch_bounds__(512, 1) void gram_cross8_half_kernel(GramTops tops, const float* __restrict__ nw, int nfill,
                                                                   float* __restrict__ partial, int64_t slabs_total,
                                                                   int64_t slabs_per_group, int groups,
                                                                   const int* __restrict__ hole) {
-    constexpr int LP = 256, SL = 3, SLAB = 2 * 2 * LP, STAGE = SL * SLAB, ML = STAGE / 512;  // SLAB: [top, new][k-half][row]
+    constexpr int LP = 256, SL = 2, SLAB = 2 * 2 * LP, STAGE = SL * SLAB, ML = STAGE / 512;  // SLAB: [top, new][k-half][row]
     extern __shared__ u32x4 ldsc[];  // 3 * STAGE
     const int group = (int)spare_unit_at(hole);
     if (group < 0 || group >= groups) return;
@@ -925,6 +926,128 @@ __global__ __launch_bounds__(256, 2) void gram_new8_half_kernel(const float* __r
     }
 }
 
+struct __attribute__((packed, aligned(2))) Piece8 {  // eight bf16 values at any element boundary
+    u32x4 v;
+};
+
+// ... of rows on their way from the caller's batch into the half, which saves reading them a second time: a stage is four slabs, 128 bytes of every row, loaded as insert16_kernel
+// does (lane = (row, piece of four neighbours), the two halves of a line one after the other), two stages ahead, and goes from the
+// registers to LDS and to the half. 256 rows of 2,049,000 beside an eigensolve: 490 us (4.3 TB/s), stored and multiplied by a kernel each
+// 480 + 240. (Fp32 rows, six products a pair and no registers for a second slab ahead, took 1090 us where two kernels take 1010.)
+template <int W>
+__device__ __forceinline__ void gram_new8_rows16_wave(u32x4* __restrict__ N16, const uint16_t* __restrict__ G, int64_t D, int nfill,
+                                                      float* __restrict__ partial, int group, int64_t s0, int64_t s1, u32x4* lds) {
+    using M = New8Map<W>;
+    constexpr int LP = 256, SL = 4, STAGE = SL * 2 * LP, KC = SL * DC;  // KC: columns of a stage
+    const int lane = threadIdx.x & 63;
+    const int l32 = lane & 31, h = lane >> 5;
+    const int row = W * 64 + (lane & 15), piece = lane >> 4;  // (wave W loads rows 64 W .. + 63)
+
+    f32x16 acc[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+    unsigned src[4];  // bytes from the first column of a stage in row 0
+#pragma unroll
+    for (int g = 0; g < 4; ++g) src[g] = (unsigned)row_in_use(row + 16 * g, nfill) * (unsigned)D * 2u + 16u * piece;
+
+    // (a stage that ends beyond the range of the work-group reads columns of the next one's, or none)
+    auto fetch = [&](int64_t sl, u32x4 (&v)[8]) __attribute__((always_inline)) {
+        const int64_t c = (sl < s1 ? sl : s1 - 1) * DC;
+        const char* g0 = reinterpret_cast<const char*>(G + c);
+        if (c + KC <= D) {  // (uniform)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const Piece8*>(g0 + src[q >> 1] + 64 * (q & 1))->v;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int left = (int)(D - c) - 8 * piece - 32 * (q & 1);
+                const uint16_t* g = reinterpret_cast<const uint16_t*>(g0 + src[q >> 1] + 64 * (q & 1));
+                u32x4 x = {0u, 0u, 0u, 0u};
+                if (left >= 8) {
+                    x = reinterpret_cast<const Piece8*>(g)->v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e >> 1] |= e < left ? (unsigned)g[e] << (16 * (e & 1)) : 0u;
+                }
+                v[q] = x;
+            }
+        }
+    };
+    auto store = [&](int64_t sl, int buf, const u32x4 (&v)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int at = (4 * (q & 1) + piece) * LP + row + 16 * (q >> 1);
+            lds[buf * STAGE + at] = v[q];
+            if (sl + 2 * (q & 1) + (piece >> 1) < s1) N16[sl * (2 * LP) + at] = v[q];
+        }
+    };
+    u32x4 va[8], vb[8];
+    if (s0 < s1) {
+        fetch(s0, va);
+        fetch(s0 + SL, vb);
+    }
+    auto step = [&](int64_t s, int buf, u32x4 (&v)[8]) __attribute__((always_inline)) {
+        if (s >= s1) return;  // (uniform)
+        store(s, buf, v);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); the loads stay in flight
+        __builtin_amdgcn_s_barrier();        // (whoever stores into this buffer next has been past the other one's barrier)
+        asm volatile("" ::: "memory");
+        fetch(s + 2 * SL, v);
+        const u32x4* st = lds + buf * STAGE + h * LP + l32;
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            if (s + u >= s1) break;  // (uniform)
+            u32x4 op[6];
+#pragma unroll
+            for (int o = 0; o < 6; ++o) {
+                op[o] = st[u * 2 * LP + M::rows[o] * 32];
+                if (M::rows[o] * 32 + l32 >= nfill) op[o] = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int q = 0; q < 9; ++q) acc[q] = mfma_bf16(op[M::pa[q]], op[M::pb[q]], acc[q]);
+        }
+    };
+    for (int64_t s = s0; s < s1; s += 2 * SL) {
+        step(s, 0, va);
+        step(s + SL, 1, vb);
+    }
+
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        const int bi = M::rows[M::pa[q]], bj = M::rows[M::pb[q]];
+        const int ti = bi >> 1, tj = bj >> 1;
+        float* out = partial + ((int64_t)group * 10 + ti * (ti + 1) / 2 + tj) * 4096 + (bi & 1) * 2048 + (bj & 1) * 32;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int r = 8 * (e >> 2) + 4 * h + (e & 3);
+            out[r * 64 + l32] = acc[q][e];
+        }
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void gram_new8_rows16_kernel(float* __restrict__ nw, const uint16_t* __restrict__ G, int64_t D,
+                                                                  int nfill, float* __restrict__ partial, int64_t slabs_total,
+                                                                  int64_t slabs_per_group, int groups,
+                                                                  const int* __restrict__ hole) {
+    extern __shared__ u32x4 ldsr[];
+    const int group = (int)spare_unit_at(hole);
+    if (group < 0 || group >= groups) return;
+    int64_t s0 = (int64_t)group * slabs_per_group;
+    int64_t s1 = s0 + slabs_per_group;
+    if (s1 > slabs_total) s1 = slabs_total;
+    if (s0 > s1) s0 = s1;
+    u32x4* N16 = const_cast<u32x4*>(half16(nw, 256, slabs_total));
+    switch (threadIdx.x >> 6) {  // wave-uniform
+        case 0: gram_new8_rows16_wave<0>(N16, G, D, nfill, partial, group, s0, s1, ldsr); break;
+        case 1: gram_new8_rows16_wave<1>(N16, G, D, nfill, partial, group, s0, s1, ldsr); break;
+        case 2: gram_new8_rows16_wave<2>(N16, G, D, nfill, partial, group, s0, s1, ldsr); break;
+        default: gram_new8_rows16_wave<3>(N16, G, D, nfill, partial, group, s0, s1, ldsr); break;
+    }
+}
+
 // C (NP x NP, fp64, both triangles) = sum over groups of the partial tiles, in group order. With q = P/2:
 // known_top: tiles with ti < q are not summed, their block is diag(known) (the top rows are the rows the last shrink
 // wrote, whose Gram matrix it recorded). Otherwise tile (ti, tj) comes from the first of the sources whose mode covers it
@@ -1045,6 +1168,19 @@ GramPlan gram_plan_split(const GramPlan& base, const Dims& d, int groups) {
     return p;
 }
 
+// Lane offsets are 32-bit, over 256 rows.
+bool gram_rows_ok(const GramPlan& p, const Dims& d) {
+    return p.mode == 2 && p.split && d.NP == 512 && d.D * 2 * 256 + 256 < ((int64_t)1 << 32);
+}
+hipError_t launch_gram_rows16(const void* G, int rows, float* nw, float* partial, const GramPlan& p, const Dims& d, const int* hole,
+                              hipStream_t st) {
+    constexpr int LDS = 2 * 4 * 2 * 256 * 16;  // two stages of four slabs
+    if (hipError_t ea = ensure_dynamic_lds((const void*)gram_new8_rows16_kernel, LDS); ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(gram_new8_rows16_kernel, dim3((unsigned)spare_grid_at(p.groups, hole)), dim3(256), LDS, st, nw,
+                       (const uint16_t*)G, d.D, rows, partial, d.S, p.slabs_per_group, p.groups, hole);
+    return hipGetLastError();
+}
+
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
                        hipStream_t st, bool new_one, const int* hole) {
     return launch_gram_tops(GramTops{{top}, 0, d.LP}, 1, nw, nfill, partial, p, d, st, new_one, hole);
@@ -1052,7 +1188,7 @@ hipError_t launch_gram(const float* top, const float* nw, int nfill, float* part
 
 hipError_t launch_gram_blocks(const GramTops& tops, int count, const float* nw, int nfill, float* partial, const GramPlan& p,
                               const Dims& d, hipStream_t st, const int* hole) {
-    constexpr int LDS = 3 * 3 * 2 * 2 * 256 * 16;  // three stages of three slabs
+    constexpr int LDS = 3 * 2 * 2 * 2 * 256 * 16;  // three stages of two slabs
     if (count <= 0) return hipSuccess;
     if (hipError_t ea = ensure_dynamic_lds((const void*)gram_cross8_half_kernel, LDS); ea != hipSuccess) return ea;
     hipLaunchKernelGGL(gram_cross8_half_kernel, dim3((unsigned)spare_grid_at(p.groups, hole), count), dim3(512), LDS, st, tops,

@@ -88,6 +88,7 @@ struct sage_ctx {
     GramPlan gp_cross{};  // new rows x top rows
     // ... and their counterparts for the split-arithmetic kernels (tiles = 0: not available for this sketch size)
     GramPlan gp_cross_split{}, gp_new_split{}, gp_new2_split{};
+    GramPlan gp_cross_side{};  // (that on the side stream)
     const GramPlan* gp_side_used[2] = {nullptr, nullptr};  // the plan the launch into gram_partial_new[i] used
     GramPlan gp_new{};    // new rows x new rows, one work-group per CU (it shares the chip with the eigensolve)
     GramPlan gp_new2{};   // the same block with the chip to itself (context stream, when there was nothing to look ahead to)
@@ -534,8 +535,12 @@ int side_follow(sage_ctx* c) {
 int side_ahead(sage_ctx* c, const RowSrc* next, const int* hole) {
     const int LP = c->d.LP, ell = c->d.ell, o = c->df.next = c->df.free_half(), pn = c->par ^ 1;
     if (int rc = note_new_rows(c, o, 0, *next); rc != SAGE_OK) return rc;
-    HIPCHK(insert_rows(*next, ell, 0, c->nw(o), LP, c->d, c->nw_half[o], c->st2, hole));
     c->gp_side_used[pn] = c->mm_mode == SAGE_MM_SPLIT && c->gp_new_split.tiles > 0 ? &c->gp_new_split : &c->gp_new;
+    if (c->nw_half[o] && !next->outer() && gram_rows_ok(*c->gp_side_used[pn], c->d)) {
+        HIPCHK(launch_gram_rows16(next->G, ell, c->nw(o), c->gram_partial_new[pn], *c->gp_side_used[pn], c->d, hole, c->st2));
+        return SAGE_OK;
+    }
+    HIPCHK(insert_rows(*next, ell, 0, c->nw(o), LP, c->d, c->nw_half[o], c->st2, hole));
     HIPCHK(launch_gram(c->top, c->nw(o), ell, c->gram_partial_new[pn], *c->gp_side_used[pn], c->d, c->st2, new_one(c, o), hole));
     return SAGE_OK;
 }
@@ -580,16 +585,20 @@ hipError_t write_rows(sage_ctx* c, hipStream_t st, const int* hole) {
 }
 
 // Products of the rows of half o with `top` and with the blocks b, partial tiles one after the other.
-const GramPlan& cross_plan(const sage_ctx* c) { return c->gp_cross_split.tiles > 0 ? c->gp_cross_split : c->gp_cross; }
+const GramPlan& cross_plan(const sage_ctx* c, hipStream_t st) {
+    if (c->gp_cross_split.tiles == 0) return c->gp_cross;
+    return st == c->st2 ? c->gp_cross_side : c->gp_cross_split;
+}
+int64_t cross_stride(const sage_ctx* c) { return (int64_t)c->gp_cross.partial_floats; }  // (no plan has more)
 hipError_t cross_top(sage_ctx* c, int o, hipStream_t st, const int* hole) {
-    return launch_gram_tops(GramTops{{c->top}, 0, c->d.ell}, 1, c->nw(o), c->d.ell, c->gram_partial, cross_plan(c), c->d, st,
+    return launch_gram_tops(GramTops{{c->top}, 0, c->d.ell}, 1, c->nw(o), c->d.ell, c->gram_partial, cross_plan(c, st), c->d, st,
                             new_one(c, o), hole);
 }
 hipError_t cross_blocks(sage_ctx* c, int o, const NewBlocks& b, hipStream_t st, const int* hole) {
-    const GramPlan& gp = cross_plan(c);
+    const GramPlan& gp = cross_plan(c, st);
     GramTops tops{};
     tops.rows = c->d.ell;
-    tops.stride = (int64_t)gp.partial_floats;
+    tops.stride = cross_stride(c);
     for (int j = 0; j < b.count; ++j) tops.p[j] = b.at(j);
     if (c->d.NP == 512 && blocks_one_part(c))
         return launch_gram_blocks(tops, b.count, c->nw(o), c->d.ell, c->gram_partial + tops.stride, gp, c->d, st, hole);
@@ -603,16 +612,16 @@ hipError_t cross_all(sage_ctx* c, int o, const NewBlocks& b, hipStream_t st, con
     }
     GramTops tops{};
     tops.rows = c->d.ell;
-    tops.stride = (int64_t)cross_plan(c).partial_floats;
+    tops.stride = cross_stride(c);
     tops.p[0] = c->top;
     for (int j = 0; j < b.count; ++j) tops.p[1 + j] = b.at(j);
-    return launch_gram_tops(tops, 1 + b.count, c->nw(o), c->d.ell, c->gram_partial, cross_plan(c), c->d, st, false, hole);
+    return launch_gram_tops(tops, 1 + b.count, c->nw(o), c->d.ell, c->gram_partial, cross_plan(c, st), c->d, st, false, hole);
 }
+// (the products with the blocks were formed on the side stream, those with the top by the same stream as this)
 hipError_t cross_reduce(sage_ctx* c, int sources, const int* col, hipStream_t st) {
-    const GramPlan& gp = cross_plan(c);
     const int pn = c->par ^ 1;
-    return launch_defer_reduce(c->gram_partial, (int64_t)gp.partial_floats, sources, col, gp, c->gram_partial_new[pn],
-                               *c->gp_side_used[pn], c->K, c->ldk, c->C_next, c->d, st);
+    return launch_defer_reduce(c->gram_partial, cross_stride(c), sources, col, cross_plan(c, st).groups, cross_plan(c, c->st2).groups,
+                               c->gram_partial_new[pn], *c->gp_side_used[pn], c->K, c->ldk, c->C_next, c->d, st);
 }
 
 // The blocks whose shrink is deferred, with the current one.
@@ -926,7 +935,12 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
         c->gp_new2_split = gram_plan_split(c->gp_new2, c->d, 0);
         // beside the eigensolve: one work-group per CU of the seven XCDs that it leaves alone, so that the kernels after
         // the reduction find room beside them
-        c->gp_new_split = gram_plan_split(c->gp_new2, c->d, c->num_cu > 32 ? c->num_cu / 8 * 7 : 8);
+        const int side = c->num_cu > 32 ? c->num_cu / 8 * 7 : 8;
+        c->gp_new_split = gram_plan_split(c->gp_new2, c->d, side);
+        // The new x top kernels fill a CU, and the kernels after the reduction that do not fit beside them (divide and conquer's
+        // blocks: 77 KB of LDS) come to all XCDs: one CU of each is left to them (those blocks of 512 rows 290 -> 60 us). As many
+        // work-groups as the whole chip holds took two rounds of the 224 CUs.
+        c->gp_cross_side = gram_plan_split(c->gp_cross, c->d, side > 56 ? side - 7 : side);
     }
     c->fixed_cap = max_rows > 0;
     c->cap_rows = max_rows > 0 ? max_rows : 65536;

@@ -136,6 +136,10 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
 // has the same bits
 hipError_t launch_gram(const float* top, const float* nw, int nfill, float* partial, const GramPlan& p, const Dims& d,
                        hipStream_t st, bool new_one = false, const int* hole = nullptr);
+// Mode 2 of row-major bf16 rows that are stored into the half `nw`, in pieces of bf16, on the way (from its row 0 on).
+bool gram_rows_ok(const GramPlan& p, const Dims& d);
+hipError_t launch_gram_rows16(const void* G, int rows, float* nw, float* partial, const GramPlan& p, const Dims& d, const int* hole,
+                              hipStream_t st);
 // Mode 1 with several half buffers for the top rows: the partial tiles of p[j] are `stride` floats after those of p[j - 1]. (NP <= 256
 // or a split plan.)
 constexpr int GRAM_TOPS = 6;
@@ -209,7 +213,7 @@ hipError_t launch_eig_export(const EigWork& w, int NP, double* Y, double* lam, d
 // fd_defer.hip: shrinks whose rows are written later. LP = 64, 128, 256; all in fp64.
 // Partial tiles of `sources` rectangles (launch_gram_tops with plan pc, `stride` floats apart) into K, source s from column col[s]
 // on, and of the new x new triangle (plan pn) into C.
-hipError_t launch_defer_reduce(const float* cross, int64_t stride, int sources, const int* col, const GramPlan& pc, const float* fresh,
+hipError_t launch_defer_reduce(const float* cross, int64_t stride, int sources, const int* col, int top_groups, int groups, const float* fresh,
                                const GramPlan& pn, double* K, int ldk, double* C, const Dims& d, hipStream_t st);
 // out (LP x LP) = K W^T over `len` columns
 hipError_t launch_defer_fold(const double* K, int ldk, const double* W, int ldw, int len, double* out, int ldo, const Dims& d,

@@ -37,6 +37,30 @@ def test_same_bits_as_with_all_parts(D, ell):
     assert out[0][2].frob2 == out[1][2].frob2
 
 
+# The kernel that stores rows and forms their Gram block (four slabs of 16 columns at a time): rows that end within a slab, with one, in
+# the middle of a stage and with it; one, several and no whole stages a work-group; rows on any element. All parts: two kernels.
+@pytest.mark.parametrize("ell,D,shift", [(129, 257, 0), (256, 320, 1), (256, 336, 0), (200, 14_400, 0), (256, 14_401, 1), (256, 28_672, 0),
+                                         (131, 57_391, 1), (256, 57_344, 0)])
+def test_same_bits_where_rows_are_stored_and_multiplied_in_one_go(ell, D, shift):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    n = 4 * ell + 5
+    mem = torch.empty(n * D + 8, dtype=torch.bfloat16, device="cuda")
+    G = mem[shift:shift + n * D].view(n, D)
+    G.copy_(_rows(n, D, D + ell))
+    out = []
+    for mode in (1, 2):
+        s = Sage(ell, D, dtype="bf16")
+        s.set_update_arithmetic(mode)
+        s.fd_update(G)
+        out.append((s.sketch(), s.stats()))
+        s.close()
+    assert torch.equal(out[0][0], out[1][0])
+    assert out[0][1].frob2 == out[1][1].frob2 and out[0][1].sum_delta == out[1][1].sum_delta
+
+
 def test_fp32_rows_and_readers_in_the_middle_of_a_half():
     import torch
 
