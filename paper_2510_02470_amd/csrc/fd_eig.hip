@@ -10,8 +10,8 @@
 
 namespace sage {
 
-hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st) {
-    if (hipError_t e = launch_tridiag(w, NP, m0, n, st); e != hipSuccess) return e;
+hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st, const RowJob* job) {
+    if (hipError_t e = launch_tridiag(w, NP, m0, n, st, job); e != hipSuccess) return e;
     if (hipError_t e = launch_dc(w, NP, n, st); e != hipSuccess) return e;
     return launch_tri_back(w, NP, m0, n, count, cf, st);
 }

@@ -19,6 +19,7 @@
 
 #include "sage_internal.h"
 #include "fd_coeffs.h"
+#include "fd_rows.h"
 #include "fd_tri_plan.h"
 #include "fd_wy.h"
 #include "wave_ops.h"
@@ -505,6 +506,54 @@ __global__ __launch_bounds__(64 * (4 * J + 2), 1) void tri_one_kernel(const doub
         }
     }
     tri_one<J, JN>(C, NP, m0, LP, n, 0, nullptr, dT, eT, tauT, V, stat, nullptr);
+}
+
+// 64 rows, and beside them the next rows of a stream into another half (insert_kernel's work, 16 rows x 8 slabs a wave): as a launch
+// of its own that took 4.7 us of a cycle of 85 (512 columns), and the chip is idle here but for one CU.
+template <typename Src>
+__global__ __launch_bounds__(384, 1) void tri_one_insert_kernel(const double* __restrict__ C, int m0, int n, double* __restrict__ dT,
+                                                                double* __restrict__ eT, double* __restrict__ tauT,
+                                                                double* __restrict__ V, double* __restrict__ stat, Src src, int rows,
+                                                                float* __restrict__ half, int64_t D, int64_t S, int row_groups,
+                                                                int64_t units) {
+    constexpr int LP = 32, NS = 8;
+    if (blockIdx.x == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        tri_one<1, 1>(C, 2 * LP, m0, LP, n, 0, nullptr, dT, eT, tauT, V, stat, nullptr);
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const int64_t unit = (int64_t)(blockIdx.x - 1) * 6 + (threadIdx.x >> 6);
+    if (unit >= units) return;
+    const int r = (int)((unsigned)unit % (unsigned)row_groups) * 16 + (lane >> 2), p = lane & 3;
+    if (r >= rows) return;
+    const int64_t s0 = (int64_t)((unsigned)unit / (unsigned)row_groups) * NS;
+    float4 v[NS];
+    src.template load<NS>(r, s0 * DC + p * 4, D, v);
+    float4* dst = reinterpret_cast<float4*>(half + (s0 * LP + r) * DC) + p;
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+        if (s0 + i < S) dst[(int64_t)i * LP * (DC / 4)] = v[i];
+}
+template <typename Src>
+static void launch_tri_one_insert(const EigWork& w, int m0, int n, const Src& src, const RowJob& job, hipStream_t st) {
+    const int row_groups = (job.rows + 15) / 16;
+    const int64_t units = (job.d.S + 7) / 8 * row_groups;
+    hipLaunchKernelGGL(tri_one_insert_kernel<Src>, dim3((unsigned)(1 + (units + 5) / 6)), dim3(384), 0, st, w.C, m0, n, w.dT, w.eT, w.tauT,
+                       w.V, w.stat, src, job.rows, job.half, job.d.D, job.d.S, row_groups, units);
+}
+static void launch_tri_one_insert(const EigWork& w, int m0, int n, const RowJob& job, hipStream_t st) {
+    const bool bf16 = job.dtype == SAGE_BF16;
+    if (!job.G) {
+        if (bf16) launch_tri_one_insert(w, m0, n, OuterRows<uint16_t>{(const uint16_t*)job.E, (const uint16_t*)job.H, job.C, job.dh}, job, st);
+        else launch_tri_one_insert(w, m0, n, OuterRows<float>{(const float*)job.E, (const float*)job.H, job.C, job.dh}, job, st);
+        return;
+    }
+    const bool vec = rows_start_on_four(job.G, job.dtype, job.d);
+    if (bf16 && vec) launch_tri_one_insert(w, m0, n, DenseRows<uint16_t, true>{(const uint16_t*)job.G}, job, st);
+    else if (bf16) launch_tri_one_insert(w, m0, n, DenseRows<uint16_t, false>{(const uint16_t*)job.G}, job, st);
+    else if (vec) launch_tri_one_insert(w, m0, n, DenseRows<float, true>{(const float*)job.G}, job, st);
+    else launch_tri_one_insert(w, m0, n, DenseRows<float, false>{(const float*)job.G}, job, st);
 }
 
 // ---- n = 64 J, J = 2, 4, 8: 16, 32, 32 work-groups on one XCD -----------------------------------------------------
@@ -1221,8 +1270,9 @@ const XcdMap& xcd_map() {
     return known[dev];
 }
 
-hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st) {
+hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st, const RowJob* job) {
     const int LP = NP / 2;
+    if (job && NP != 64) return hipErrorInvalidValue;
     const bool alone = w.period == 0;
 #define SAGE_TRI_ONE(J, JN, ALL)                                                                                       \
     hipLaunchKernelGGL((tri_one_kernel<J, JN>), dim3(1), dim3(64 * (4 * J + 2)), 0, st, w.C, NP, m0, LP, n, ALL, w.dT, w.eT, w.tauT, \
@@ -1237,7 +1287,10 @@ hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t s
             SAGE_TRI_ONE(1, J, n > 64);                                                                            \
     } while (0)
     switch (NP / 64) {
-        case 1: SAGE_TRI_ONE(1, 1, false); break;
+        case 1:
+            if (job) launch_tri_one_insert(w, m0, n, *job, st);
+            else SAGE_TRI_ONE(1, 1, false);
+            break;
         case 2:
             if (alone) SAGE_TRI_ONE(2, 2, false);
             else SAGE_TRI_MANY(2);

@@ -70,7 +70,7 @@ struct sage_ctx {
     hipEvent_t ev_side[2] = {nullptr, nullptr};  // side stream: rows stored ahead and their Gram block formed, by par
     int* side_hole = nullptr;                    // the place its launches leave out (spare_unit_at)
     bool pending_shrink = false;   // the buffer is full, its shrink waits for the next update call (see sage_fd_update)
-    bool pre_stored = false;       // the side stream has stored the next ell rows of the running call in half cur
+    bool pre_stored = false;       // the next ell rows of the running call are stored in half cur already
     bool new_block_ready = false;  // ... and their Gram block is (or will be, see ev_side) in gram_partial_new[par]
     // Deferred shrinks (fd_defer.hip). The buffer's top rows are W [top; the blocks of df], with blocks only inside an update call: it
     // ends with the rows written, so that everything else finds them in `top`.
@@ -452,9 +452,9 @@ bool capturing(hipStream_t st) {
 
 // Eigensolve of the Gram matrix of fill_top + fill_new rows; the `count` leading eigenvectors are formed, or (cf given) the
 // coefficients made from its own count of them.
-hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf = nullptr) {
+hipError_t eigensolve(sage_ctx* c, int m0, int n, int count, const CoeffArgs* cf = nullptr, const RowJob* job = nullptr) {
     if (n < 1) m0 = n = 1;  // an empty buffer: one zero row
-    if (c->xcd_slot < 0) return launch_eig(c->ew, c->d.NP, m0, n, count, cf, c->st);
+    if (c->xcd_slot < 0) return launch_eig(c->ew, c->d.NP, m0, n, count, cf, c->st, job);
     std::unique_lock<std::mutex> hold(g_xcd_lock);
     XcdSlot& x = g_xcd[c->device][c->xcd_slot];
     const bool shared = x.users > 1 && !capturing(c->st);
@@ -709,7 +709,14 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
     CoeffArgs cf{LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new, c->Mt,
                  split_rb ? c->Mt3 : nullptr, c->acc};  // (row ell - 1 of the result is zero)
     if (!write_now) cf.M = c->M[c->mi ^ 1];
-    RUN(K_EIG, eigensolve(c, ell, 2 * ell, cf.count, &cf));
+    // At 64 buffer rows the reduction's launch stores them (`inline_rows`), into the half that is not in use.
+    const bool inline_rows = c->d.NP == 64 && !c->prof && next && next_rows >= ell && !cap;
+    RowJob job{};
+    if (inline_rows) {
+        job = RowJob{next->G, next->E, next->H, next->C, next->dh, next->dtype, ell, c->nw(c->df.cur ^ 1), c->d};
+        if (int rc = note_new_rows(c, c->df.cur ^ 1, 0, *next); rc != SAGE_OK) return rc;
+    }
+    RUN(K_EIG, eigensolve(c, ell, 2 * ell, cf.count, &cf, inline_rows ? &job : nullptr));
     const NewBlocks one{c->ring, c->half_floats, (unsigned)c->df.cur, 1};
     c->marked = false;
     if (write_now) {
@@ -752,15 +759,17 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
             c->marked = false;
         }
     }
-    if (use_side(c)) {  // (with a single Gram panel there is one new half only)
+    if (use_side(c)) {
         c->df.advance(ahead);
         c->par ^= 1;
+    } else {
+        c->df.cur = inline_rows ? c->df.cur ^ 1 : 0;  // (0 whenever a call ends, so that a captured one can be replayed)
     }
     c->fill_top = ell;
     c->cnt_top = ell;
     c->fill_new = 0;
     c->cnt_new = 0;
-    c->pre_stored = ahead;
+    c->pre_stored = ahead || inline_rows;
     c->new_block_ready = ahead;
     c->n_shrinks += 1;
     c->top_shrunk = true;
@@ -958,7 +967,7 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     } while (0)
     defer_plan(c);
     c->half_floats = (int64_t)(hbytes / sizeof(float));
-    c->halves = P < 2 ? 1 : c->df.halves();
+    c->halves = c->df.halves();
     CALLOC(c->top, hbytes);
     CALLOC(c->ring, (size_t)c->halves * hbytes);
     {
@@ -1076,7 +1085,7 @@ static int update_rows(sage_ctx* c, RowSrc g, int64_t rows) {
             RUN(K_INSERT, insert_rows(g, take, c->fill_top, c->top, LP, c->d, false, c->st));
             c->fill_top += take;
         } else if (c->pre_stored) {
-            // the previous shrink of this call has had these ell rows stored already (side stream)
+            // the previous shrink of this call has had these ell rows stored already
             take = ell;
             c->pre_stored = false;
             c->fill_new = ell;

@@ -160,6 +160,14 @@ hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const f
                               double* C, bool known_top, const double* known, const Dims& d, hipStream_t st,
                               const float* partial_top = nullptr, const GramPlan* top = nullptr, hipEvent_t done = nullptr);
 
+// Rows to be stored into a half, from its row 0 on, as fp32, by a launch of the eigensolve (NP = 64): a row-major batch G, or factors.
+struct RowJob {
+    const void *G, *E, *H;
+    int64_t C, dh;
+    int dtype, rows;
+    float* half;
+    Dims d;
+};
 // fd_tridiag.hip, fd_dc.hip, fd_eig.hip: the eigensolve
 struct DcWork {  // work arrays of the merges above 64 rows (see fd_dc.hip)
     double *dk, *zk, *org, *tau, *val, *zh, *rc, *rs;  // NP each
@@ -193,7 +201,7 @@ inline int dc_result(int NP) { return (NP == 128 || NP == 512) ? 1 : 0; }
 // leading eigenvectors are formed.
 hipError_t launch_xcd_place(int xcd, int* place, hipStream_t st);  // *place: 0 .. 7, device memory
 const XcdMap& xcd_map();  // of the launches on some stream of the current device; asked once per device
-hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st);
+hipError_t launch_tridiag(const EigWork& w, int NP, int m0, int n, hipStream_t st, const RowJob* job = nullptr);  // (job: NP = 64)
 hipError_t launch_dc(const EigWork& w, int NP, int n, hipStream_t st);
 // Coefficients of a shrink (mode 0), a basis (1) or a weighted basis (2), MP rows of which `count` are not zero; into M if given, else into
 // Mc3 (split parts) if given, else into Mt. Scalars on device: acc[0] sum_delta, acc[1] frob2 (+= diag(C) over matrix indices [ra0, ra1)
@@ -207,7 +215,7 @@ struct CoeffArgs {
 };
 // the `count` leading eigenvectors into Yt, or (cf given) only the coefficients made from them
 hipError_t launch_tri_back(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st);
-hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st);
+hipError_t launch_eig(const EigWork& w, int NP, int m0, int n, int count, const CoeffArgs* cf, hipStream_t st, const RowJob* job = nullptr);
 hipError_t launch_eig_export(const EigWork& w, int NP, double* Y, double* lam, double* record, hipStream_t st);
 
 // fd_defer.hip: shrinks whose rows are written later. LP = 64, 128, 256; all in fp64.

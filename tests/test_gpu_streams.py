@@ -260,3 +260,51 @@ def test_first_gram_and_pending_norms_against_64_bits(dtype, ell, rows, D):
         AV = A @ s.basis().double().cpu().T
         assert float(((AV ** 2).sum(0) - sig2).abs().max()) <= tol * fro
         assert abs(s.stats().frob2 - fro) <= tol * fro        # counted by the basis now
+
+
+# 64 buffer rows: the rows of a cycle to come are stored by the launch of a reduction, 16 rows x 8 slabs of 16 columns a wave, six waves a
+# work-group. Sketches below, at and above one of 16 rows; widths below and above a wave's columns, ragged; batches on any element.
+@pytest.mark.parametrize("ell,dtype,D,shift", [(2, "f32", 40, 0), (16, "f32", 128, 0), (17, "bf16", 129, 1), (32, "f32", 801, 0), (32, "bf16", 2052, 0),
+                                               (31, "f32", 516, 1), (32, "bf16", 5130, 1), (32, "f32", 100_004, 0)])
+def test_rows_stored_by_the_reduction_are_those_of_separate_calls(ell, dtype, D, shift):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    n = 6 * ell + ell // 2
+    g = torch.Generator(device="cuda").manual_seed(ell * D)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    G = torch.empty(n * D + 8, dtype=td, device="cuda")[shift:shift + n * D].view(n, D)
+    G.copy_(torch.randn((n, D), generator=g, device="cuda"))
+    out = []
+    for sizes in ([n], [ell] * 6 + [n - 6 * ell], [2 * ell + 1, 3 * ell, n - 5 * ell - 1]):
+        s, lo = Sage(ell, D, dtype=dtype), 0
+        for m in sizes:
+            if m:
+                s.fd_update(G[lo:lo + m])
+            lo += m
+        out.append((s.sketch(), s.stats()))
+        s.close()
+    for o in out[1:]:
+        assert torch.equal(o[0], out[0][0]) and o[1].frob2 == out[0][1].frob2 and o[1].sum_delta == out[0][1].sum_delta
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_factored_rows_stored_by_the_reduction(dtype):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    ell, C, dh = 24, 7, 37
+    g = torch.Generator(device="cuda").manual_seed(3)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    E = torch.randn((5 * ell + 3, C), generator=g, device="cuda").to(td)
+    H = torch.randn((5 * ell + 3, dh), generator=g, device="cuda").to(td)
+    out = []
+    for step in (len(E), ell):
+        s = Sage(ell, C * (dh + 1), dtype=dtype)
+        for lo in range(0, len(E), step):
+            s.fd_update_outer(E[lo:lo + step].contiguous(), H[lo:lo + step].contiguous())
+        out.append(s.sketch())
+        s.close()
+    assert torch.equal(out[0], out[1])
