@@ -84,8 +84,9 @@ int sage_set_allocator(sage_alloc_fn alloc, sage_free_fn free, void* user);
  * Create a context for an FD sketch of fp32 rows on the default stream: a zeroed buffer of 2*ell rows by D
  * columns, fill pointer 0 (Algorithm 1, "Initialize S <- 0, row counter r <- 0"; the buffer has 2*ell rows so
  * that new rows only ever land in zero rows, Liberty's form of FD).
- * out: HOST pointer receiving the handle. 2 <= ell <= 256, D >= 1. Device memory: about 2*ell*D*4 bytes for the
- * sketch plus work space; SAGE_ERR_ALLOC if it does not fit.
+ * out: HOST pointer receiving the handle. 2 <= ell <= 256, D >= 1. Device memory: three to five halves of L*D*4 bytes, L =
+ * ell padded to 32, 64, 128 or 256, for the sketch, the rows to come and those whose shrink is deferred, plus work space.
+ * Where that does not fit, two (L = 32) or three halves will do; SAGE_ERR_ALLOC if those do not fit either.
  */
 int sage_fd_create(sage_ctx** out, int ell, int64_t D);
 

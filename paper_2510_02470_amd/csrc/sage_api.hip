@@ -710,7 +710,7 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
                  split_rb ? c->Mt3 : nullptr, c->acc};  // (row ell - 1 of the result is zero)
     if (!write_now) cf.M = c->M[c->mi ^ 1];
     // At 64 buffer rows the reduction's launch stores them (`inline_rows`), into the half that is not in use.
-    const bool inline_rows = c->d.NP == 64 && !c->prof && next && next_rows >= ell && !cap;
+    const bool inline_rows = c->d.NP == 64 && c->halves > 1 && !c->prof && next && next_rows >= ell && !cap;
     RowJob job{};
     if (inline_rows) {
         job = RowJob{next->G, next->E, next->H, next->C, next->dh, next->dtype, ell, c->nw(c->df.cur ^ 1), c->d};
@@ -906,8 +906,8 @@ int sage_set_allocator(sage_alloc_fn alloc, sage_free_fn free_, void* user) {
     return SAGE_OK;
 }
 
-int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64_t max_rows, void* hip_stream) {
-    if (!out) return SAGE_ERR_ARG;
+// lean: the halves that storing rows ahead (64 buffer rows) and deferring shrinks take are left out, where there is no memory for them.
+static int create(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64_t max_rows, void* hip_stream, bool lean) {
     *out = nullptr;
     if (ell < 2 || ell > 256 || D < 1 || max_rows < 0) return SAGE_ERR_ARG;
     if (in_dtype != SAGE_F32 && in_dtype != SAGE_BF16) return SAGE_ERR_ARG;
@@ -967,9 +967,9 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     do {                                                                          \
         if (!dev_alloc(c->mem, c->st, (void**)&(ptr), (bytes))) return fail(SAGE_ERR_ALLOC); \
     } while (0)
-    defer_plan(c);
+    if (!lean) defer_plan(c);
     c->half_floats = (int64_t)(hbytes / sizeof(float));
-    c->halves = c->df.halves();
+    c->halves = lean && c->d.NP == 64 ? 1 : c->df.halves();
     CALLOC(c->top, hbytes);
     CALLOC(c->ring, (size_t)c->halves * hbytes);
     {
@@ -1039,6 +1039,12 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
     if (hipMemsetAsync(c->ew.xch, 0xFF, (size_t)8 * NP * sizeof(double), c->st) != hipSuccess) return fail(SAGE_ERR_HIP);
     *out = c;
     return SAGE_OK;
+}
+
+int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64_t max_rows, void* hip_stream) {
+    if (!out) return SAGE_ERR_ARG;
+    const int rc = create(out, ell, D, in_dtype, max_rows, hip_stream, false);
+    return rc == SAGE_ERR_ALLOC ? create(out, ell, D, in_dtype, max_rows, hip_stream, true) : rc;
 }
 
 int sage_fd_create(sage_ctx** out, int ell, int64_t D) { return sage_fd_create_ex(out, ell, D, SAGE_F32, 0, nullptr); }

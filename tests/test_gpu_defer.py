@@ -71,3 +71,50 @@ def test_streams_in_calls_of_many_few_and_part_cycles(ell, dtype, D):
         assert abs(st.frob2 - fro) <= 1e-6 * fro and abs(st.sum_delta - delta) <= 1e-6 * fro, name
         assert _cov_diff(s.sketch().double(), want) <= 1e-6 * fro, name
         s.close()
+
+
+@pytest.mark.parametrize("ell,dtype,D,ring", [(20, "f32", 3001, 2), (64, "f32", 5130, 4), (256, "bf16", 270_000, 3)])
+def test_contexts_where_memory_is_short(ell, dtype, D, ring):
+    """Where the halves for rows ahead and deferred shrinks do not fit, a context does with those it needs and shrinks at once: the
+    same covariance up to what rounding leaves (as above)."""
+    import torch
+
+    from paper_2510_02470_amd import binding
+
+    L, lp = binding.lib(), max(32, 1 << (ell - 1).bit_length())
+    half = (D + 15) // 16 * 16 * lp * 4
+    held, refused = {}, []
+
+    def take(size, stream, user):
+        if size == ring * half:
+            refused.append(size)
+            return None
+        t = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+        p = (t.data_ptr() + 255) // 256 * 256
+        held[p] = t
+        return p
+
+    def give(p, user):
+        torch.cuda.synchronize()
+        held.pop(p, None)
+
+    fns = binding._ALLOC_FN(take), binding._FREE_FN(give)
+    G = torch.randn((7 * ell + 3, D), device="cuda", generator=torch.Generator(device="cuda").manual_seed(D))
+    G = G.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    out = []
+    for short in (False, True):
+        if short:
+            L.sage_set_allocator(fns[0], fns[1], None)
+        try:
+            s = binding.Sage(ell, D, dtype=dtype)
+            s.fd_update(G)
+            s.fd_update(G[:2 * ell])
+            out.append((s.sketch(), s.stats()))
+            s.close()
+        finally:
+            if short:
+                binding._torch_memory(L)
+    assert refused and not held
+    fro = out[0][1].frob2
+    assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
+    assert _cov_diff(out[0][0].double(), out[1][0].double()) <= 1e-6 * fro
