@@ -1,5 +1,5 @@
-// Which halves of the ring of new rows hold what, and which shrinks leave their rows unwritten (fd_defer.hip). Plain integer
-// functions, so that they can be checked without a GPU (tests/defer_check.cc).
+// Which halves of the ring of new rows hold what, which shrinks leave their rows unwritten, and which buffers their coefficients go
+// through (fd_defer.hip). Plain integer functions, so that they can be checked without a GPU (tests/defer_check.cc).
 #pragma once
 #include <stdint.h>
 
@@ -14,6 +14,12 @@ struct DeferPlan {
     int cur = 0, next = 1, spare = 1, count = 0;
     unsigned slots = 0;
     int group = 0;  // not beside: shrinks that are put together this time
+    // The coefficients: a shrink whose rows are not written by itself leaves M in buffer m; after it the rows of the `count` deferred
+    // ones are W [top; blocks], W in buffer w (MS, MS + 1: its own two) once M is folded into it. With one block W is M, without a copy, so
+    // the next fold, on the side stream, reads the last two M's while the eigensolve beside it writes the one after: three in turn.
+    int MS = 3;
+    int m = 0, w = 0;
+    bool folded = true;
 
     int halves() const { return max > 1 ? max + 1 : 2; }
     int free_half() const {
@@ -49,6 +55,20 @@ struct DeferPlan {
     void written() {
         slots = 0;
         count = 0;
+    }
+    int next_m() const { return m + 1 < MS ? m + 1 : 0; }  // where the running shrink's M goes
+    void made_m() {
+        m = next_m();
+        folded = false;
+    }
+    struct Fold {
+        int from, out;  // out <- [M_top from, M_new]; out < 0: W is M itself, nothing to do
+    };
+    Fold fold() {
+        folded = true;
+        const int from = w;
+        w = count == 1 ? m : from == MS ? MS + 1 : MS;
+        return Fold{from, count == 1 ? -1 : w};
     }
     void advance(bool ahead) {
         const int old = cur;

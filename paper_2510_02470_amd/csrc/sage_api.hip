@@ -74,11 +74,11 @@ struct sage_ctx {
     bool new_block_ready = false;  // ... and their Gram block is (or will be, see ev_side) in gram_partial_new[par]
     // Deferred shrinks (fd_defer.hip). The buffer's top rows are W [top; the blocks of df], with blocks only inside an update call: it
     // ends with the rows written, so that everything else finds them in `top`.
-    bool folded = true;         // W includes the last shrink's M
-    double* M[2] = {nullptr, nullptr};  // M[mi]: the last shrink's coefficients
-    double* Wb[2] = {nullptr, nullptr};
-    const double* W = nullptr;
-    int mi = 0, wi = 0, ldw = 0, ldk = 0;
+    double* coef[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};  // M and W, by the numbers of df
+    const double* last_M() const { return coef[df.m]; }
+    const double* W() const { return coef[df.w]; }
+    int ldw() const { return df.w < df.MS ? d.NP : (1 + df.max) * d.LP; }
+    int ldk = 0;
     double* K = nullptr;        // products of the next block's rows with [W [top; blocks]; cur], then those with top and blocks
     double* C_next = nullptr;   // the Gram matrix of the next cycle, as far as it is known
     bool C_ready = false;       // ew.C is the whole Gram matrix of the coming shrink
@@ -556,30 +556,24 @@ bool blocks_one_part(const sage_ctx* c) { return c->one_part && c->dtype == SAGE
 
 // W takes in the last shrink's M.
 hipError_t fold_shrink(sage_ctx* c, hipStream_t st) {
-    const int LP = c->d.LP, n = c->df.count;
+    const int n = c->df.count;
     if (n < 1 || n > c->df.max) return hipErrorInvalidValue;  // (what the buffers are made for)
-    c->folded = true;
-    if (n == 1) {
-        c->W = c->M[c->mi];
-        c->ldw = c->d.NP;
-        return hipSuccess;
-    }
-    const double* const W = c->W;
-    const int ldw = c->ldw;
-    c->W = c->Wb[c->wi ^= 1];
-    c->ldw = (1 + c->df.max) * LP;
-    return launch_defer_compose(c->M[c->mi], W, ldw, n * LP, c->Wb[c->wi], c->ldw, c->d, st);
+    const double* const from = c->W();
+    const int ldf = c->ldw();
+    const DeferPlan::Fold f = c->df.fold();
+    if (f.out < 0) return hipSuccess;
+    return launch_defer_compose(c->last_M(), from, ldf, n * c->d.LP, c->coef[f.out], c->ldw(), c->d, st);
 }
 
 // The rows of the deferred shrinks: top <- W [top; blocks].
 hipError_t write_rows(sage_ctx* c, hipStream_t st, const int* hole) {
     const int LP = c->d.LP;
-    if (!c->folded)
+    if (!c->df.folded)
         if (hipError_t e = fold_shrink(c, st); e != hipSuccess) return e;
     const NewBlocks b{c->ring, c->half_floats, c->df.slots, c->df.count};
     if (b.count < 1 || b.count > c->df.max) return hipErrorInvalidValue;
     c->df.written();
-    if (hipError_t e = launch_defer_coeffs(c->W, c->ldw, (1 + b.count) * LP, c->Mt, c->Mt3, c->d, st); e != hipSuccess) return e;
+    if (hipError_t e = launch_defer_coeffs(c->W(), c->ldw(), (1 + b.count) * LP, c->Mt, c->Mt3, c->d, st); e != hipSuccess) return e;
     if (c->Mt3) return launch_rebuild_split(c->top, b, c->d.ell, c->Mt3, c->top, LP, LP, c->d, st, blocks_one_part(c), hole);
     return launch_rebuild(c->top, b, c->d.ell, c->Mt, c->top, LP, LP, c->d, st, hole);
 }
@@ -631,7 +625,7 @@ NewBlocks blocks_and_cur(const sage_ctx* c) { return NewBlocks{c->ring, c->half_
 // next block, and its products with the buffer of the running shrink (columns 0 .. 2 LP - 1 of K).
 int side_defer(sage_ctx* c, const RowSrc* next, bool write_first, const int* hole) {
     const int LP = c->d.LP;
-    if (!c->folded) HIPCHK(fold_shrink(c, c->st2));
+    if (!c->df.folded) HIPCHK(fold_shrink(c, c->st2));
     if (write_first) HIPCHK(write_rows(c, c->st2, hole));
     if (int rc = side_ahead(c, next, hole); rc != SAGE_OK) return rc;
     const int n = c->df.count;
@@ -641,7 +635,7 @@ int side_defer(sage_ctx* c, const RowSrc* next, bool write_first, const int* hol
     for (int j = 0; j < n; ++j) col[1 + j] = (3 + j) * LP;
     col[n + 1] = LP;
     HIPCHK(cross_reduce(c, n + 2, col, c->st2));
-    if (n > 0) HIPCHK(launch_defer_fold(c->K + 2 * LP, c->ldk, c->W, c->ldw, (1 + n) * LP, c->K, c->ldk, c->d, c->st2));
+    if (n > 0) HIPCHK(launch_defer_fold(c->K + 2 * LP, c->ldk, c->W(), c->ldw(), (1 + n) * LP, c->K, c->ldk, c->d, c->st2));
     return SAGE_OK;
 }
 
@@ -702,13 +696,13 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
         HIPCHK(hipEventRecord(c->ev_side[c->par ^ 1], c->st2));
     } else if (step.write_first) {
         RUN(K_REBUILD, write_rows(c, c->st, nullptr));
-    } else if (c->df.count > 0 && !c->folded) {
-        RUN(K_REDUCE, fold_shrink(c, c->st));  // (the eigensolve writes the other M)
+    } else if (c->df.count > 0 && !c->df.folded) {
+        RUN(K_REDUCE, fold_shrink(c, c->st));  // (with the count it was made for)
     }
     const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3, write_now = !step.defer && c->df.count == 0;
     CoeffArgs cf{LP, ell - 1, 0, c->d.n, ell, c->cnt_top, c->fill_top, LP + c->cnt_new, LP + c->fill_new, c->Mt,
                  split_rb ? c->Mt3 : nullptr, c->acc};  // (row ell - 1 of the result is zero)
-    if (!write_now) cf.M = c->M[c->mi ^ 1];
+    if (!write_now) cf.M = c->coef[c->df.next_m()];
     // At 64 buffer rows the reduction's launch stores them (`inline_rows`), into the half that is not in use.
     const bool inline_rows = c->d.NP == 64 && c->halves > 1 && !c->prof && next && next_rows >= ell && !cap;
     RowJob job{};
@@ -725,10 +719,9 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
         else
             RUN(K_REBUILD, launch_rebuild(c->top, one, ell, c->Mt, c->top, LP, LP, c->d, c->st));
     } else {
-        c->mi ^= 1;
         c->df.push();
-        c->folded = false;
-        const double* W = c->M[c->mi];
+        c->df.made_m();
+        const double* W = c->last_M();
         int ldw = c->d.NP, len = 2 * LP;
         if (step.defer && !c->df.beside) {
             RUN(K_REDUCE, fold_shrink(c, c->st));
@@ -738,8 +731,8 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
                 int col[GRAM_TOPS];
                 for (int j = 0; j <= c->df.count; ++j) col[j] = j * LP;
                 RUN(K_REDUCE, cross_reduce(c, 1 + c->df.count, col, c->st));
-                W = c->W;
-                ldw = c->ldw;
+                W = c->W();
+                ldw = c->ldw();
                 len = (1 + c->df.count) * LP;
                 c->C_ready = true;
             }
@@ -1007,8 +1000,8 @@ static int create(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64
                 const size_t lp = (size_t)c->d.LP;
                 c->ldk = (c->df.max + 2) * c->d.LP;
                 take(c->C_next, n2);
-                for (int i = 0; i < 2; ++i) take(c->M[i], lp * n1);
-                for (int i = 0; i < 2; ++i) take(c->Wb[i], lp * lp * (1 + c->df.max));
+                for (int i = 0; i < c->df.MS; ++i) take(c->coef[i], lp * n1);
+                for (int i = 0; i < 2; ++i) take(c->coef[c->df.MS + i], lp * lp * (1 + c->df.max));
                 take(c->K, lp * c->ldk);
             }
             take(w.Yt, n2);

@@ -1,10 +1,14 @@
 // Deferred shrinks (csrc/fd_defer_plan.h): streams cut into calls at random, with every half's rows followed by their numbers. What is
 // written and what is left unwritten must together be the stream, no half may be stored to while it holds rows that are still
-// needed, and no more blocks may come together than the buffers are made for.
-// Argument "planted": the same with the rows of a full set of blocks not written first, which must fail.
+// needed, and no more blocks may come together than the buffers are made for. The buffers of the coefficients are followed too, by the
+// numbers of the shrinks that are in them: what the side stream does between the mark and the join is done before or after what the
+// context stream does there, at random, and must find what it was enqueued for either way.
+// Arguments: "planted", the same with the rows of a full set of blocks not written first; "two", with two buffers for the M's. Both
+// must fail.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <vector>
 
 #include "fd_defer_plan.h"
@@ -12,7 +16,7 @@
 using sage::DeferPlan;
 typedef std::vector<int> Rows;
 
-static bool planted = false;
+static bool planted = false, two = false;
 static int failures = 0;
 #define REQUIRE(cond, what)                                                                      \
     do {                                                                                         \
@@ -24,10 +28,41 @@ struct Stream {
     int ell, fill_top = 0, fill_new = 0, rows = 0;
     bool pending = false, stored = false, shrunk = false, ready = false;
     Rows top, half[16];
+    int shrinks = 0;
+    Rows coef[5], due;                       // shrinks whose coefficients a buffer holds; those whose rows are not written
+    std::vector<std::function<void()>> side;  // enqueued there, not done yet
+    bool on_side = false;
 
     static void add(Rows& a, const Rows& b) { a.insert(a.end(), b.begin(), b.end()); }
-    void write() {
+    void enqueue(std::function<void()> f) {
+        if (on_side) side.push_back(f);
+        else f();
+    }
+    void join() {
+        for (auto& f : side) f();
+        side.clear();
+    }
+    void holds(int buffer, const Rows& want, const char* what) {
+        enqueue([=] { REQUIRE(coef[buffer] == want, what); });
+    }
+    void fold() {
         REQUIRE(p.count >= 1 && p.count <= p.max, "blocks beyond what W is made for");
+        const DeferPlan::Fold f = p.fold();
+        const int m = p.m;
+        if (f.out < 0) return;
+        holds(f.from, Rows(due.begin(), due.end() - 1), "W is not that of the shrinks before the last");
+        holds(m, Rows(1, due.back()), "M is not the last shrink's");
+        enqueue([=] {
+            Rows w = coef[f.from];
+            add(w, coef[m]);
+            coef[f.out] = w;
+        });
+    }
+    void write() {
+        if (!p.folded) fold();
+        REQUIRE(p.count >= 1 && p.count <= p.max, "blocks beyond what W is made for");
+        holds(p.w, due, "rows are written with another W than theirs");
+        due.clear();
         for (int b = 0; b < p.count; ++b) add(top, half[p.slots >> (4 * b) & 15]);
         p.written();
     }
@@ -38,8 +73,15 @@ struct Stream {
         REQUIRE((int)half[p.cur].size() == ell, "a shrink of a half that is not full");
         REQUIRE(p.count == 0 || (ready && !captured), "the products of unwritten rows are not there");
         ready = false;
+        const bool write_now = !s.defer && p.count == 0, last = rand() & 1;  // last: the side stream comes late
         if (ahead) {
-            if (s.defer && p.beside && s.write_first) write();
+            if (s.defer && p.beside) {
+                on_side = true;
+                if (p.count > 0 && !p.folded) fold();
+                if (s.write_first) write();
+                if (p.count > 0) holds(p.w, due, "the rectangle is taken through another W than the rows'");
+                on_side = false;
+            }
             REQUIRE(s.defer || p.count == 0, "stored ahead for a shrink that comes after unwritten ones");
             const int o = p.next = p.free_half();
             REQUIRE(o >= 0 && o < p.halves() && o != p.cur, "no such half");
@@ -48,11 +90,24 @@ struct Stream {
             half[o].assign(next, next + ell);
         } else if (s.write_first) {
             write();
+        } else if (p.count > 0 && !p.folded) {
+            fold();
         }
-        if (!s.defer && p.count == 0) {
+        if (!last) join();
+        if (!write_now) coef[p.next_m()] = Rows(1, shrinks);  // the eigensolve
+        join();
+        if (write_now) {
             add(top, half[p.cur]);
         } else {
             p.push();
+            p.made_m();
+            due.push_back(shrinks);
+            if (s.defer && !p.beside) {
+                fold();
+                holds(p.w, due, "the rectangle is taken through another W than the rows'");
+            } else if (s.defer) {
+                holds(p.m, Rows(1, shrinks), "the rectangle is taken through another M than the last shrink's");
+            }
             ready = s.defer && (p.beside || !s.last);
             if (!s.defer || s.last) write();
         }
@@ -63,6 +118,7 @@ struct Stream {
         fill_new = 0;
         stored = ahead;
         shrunk = true;
+        ++shrinks;
     }
     void update(int n, bool captured) {
         Rows r(n);
@@ -111,12 +167,14 @@ struct Stream {
 
 int main(int argc, char** argv) {
     planted = argc > 1 && !strcmp(argv[1], "planted");
+    two = argc > 1 && !strcmp(argv[1], "two");
     srand(1);
     for (int trial = 0; trial < 40000; ++trial) {
         Stream s;
         s.ell = 2 + rand() % 4;
         s.p.max = rand() % 5;
         s.p.beside = rand() & 1;
+        if (two) s.p.MS = 2;
         for (int calls = 1 + rand() % 9; calls > 0; --calls) {
             s.update(rand() % 5 < 3 ? 1 + rand() % (6 * s.ell) : s.ell * (1 + rand() % 5), false);
             if (rand() % 6 == 0) s.look();
