@@ -1720,6 +1720,7 @@ int sage_probe_eig_matrix(sage_ctx* c, const double* C_in, double* Y_out, double
     ALIVE(c);
     if (!C_in) return SAGE_ERR_ARG;
     const int NP = c->d.NP;
+    c->C_ready = false;  // (C_in takes its place: a shrink that is pending forms the products again)
     HIPCHK(hipMemcpyAsync(c->ew.C, C_in, (size_t)NP * NP * sizeof(double), hipMemcpyDeviceToDevice, c->st));
     HIPCHK(eigensolve(c, NP / 2, NP, NP));
     HIPCHK(launch_eig_export(c->ew, NP, Y_out, lam_out, sweep_stat_out, c->st));

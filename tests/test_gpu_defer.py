@@ -118,3 +118,29 @@ def test_contexts_where_memory_is_short(ell, dtype, D, ring):
     fro = out[0][1].frob2
     assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
     assert _cov_diff(out[0][0].double(), out[1][0].double()) <= 1e-6 * fro
+
+
+@pytest.mark.parametrize("ell,dtype,D", [(64, "f32", 5130), (100, "bf16", 2113), (256, "bf16", 4097)])
+def test_probe_of_a_matrix_leaves_a_pending_shrink_alone(ell, dtype, D):
+    """A call of several cycles that ends on a full buffer has the Gram matrix of the pending shrink already; the eigensolve of another
+    matrix (sage_probe_eig_matrix: "the sketch is not modified") must not take its place. The sketches differ by the Gram matrix formed
+    anew, in other partial sums: bar as above."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(D)
+    G = torch.randn((6 * ell, D), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    n = 2 * max(32, 1 << (ell - 1).bit_length())
+    X = torch.randn((n, n), generator=g, device="cuda", dtype=torch.float64)
+    out = []
+    for probe in (False, True):
+        s = Sage(ell, D, dtype=dtype)
+        s.fd_update(G)
+        if probe:
+            s.probe_eig_matrix(X @ X.T)
+        out.append((s.sketch().double(), s.stats()))
+        s.close()
+    fro = out[0][1].frob2
+    assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
+    assert _cov_diff(out[0][0], out[1][0]) <= 1e-6 * fro
