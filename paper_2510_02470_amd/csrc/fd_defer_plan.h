@@ -14,6 +14,9 @@ struct DeferPlan {
     int cur = 0, next = 1, spare = 1, count = 0;
     unsigned slots = 0;
     int group = 0;  // not beside: shrinks that are put together this time
+    // A call was captured: a graph holds the halves cur and spare by their addresses, and replays of it may stand between other
+    // calls. So those two alone take turns from then on (no shrink is deferred): calls of an even number of cycles end where they began.
+    bool captured = false;
     // The coefficients: a shrink whose rows are not written by itself leaves M in buffer m; after it the rows of the `count` deferred
     // ones are W [top; blocks], W in buffer w (MS, MS + 1: its own two) once M is folded into it. With one block W is M, without a copy, so
     // the next fold, on the side stream, reads the last two M's while the eigensolve beside it writes the one after: three in turn.
@@ -37,7 +40,7 @@ struct DeferPlan {
     // The shrink of the full half cur. next_rows: rows of the running call after it; ahead: the next ell of them are stored ahead;
     // allowed: the block and the next one can be deferred. An update call never ends with blocks.
     Step step(bool ahead, bool allowed, int64_t next_rows, int ell) {
-        Step s{ahead && allowed && max > 0, count > 0 && count == max, false};
+        Step s{ahead && allowed && !captured && max > 0, count > 0 && count == max, false};
         if (s.defer && !beside && count == 0) {
             // the shrinks left in this call, this one included, in equal groups
             const int64_t left = next_rows / ell + (next_rows % ell ? 1 : 0), groups = (left + max - 1) / max;

@@ -449,6 +449,13 @@ bool capturing(hipStream_t st) {
     (void)hipGetLastError();
     return false;
 }
+// A call that stores to the halves or reads them: if it is captured, they must be found where they are now by every replay. (And what
+// is known of a pending shrink here is not what a replay leaves.)
+void note_capture(sage_ctx* c) {
+    if (c->df.captured || !capturing(c->st)) return;
+    c->df.captured = true;
+    c->C_ready = false;
+}
 
 // Eigensolve of the Gram matrix of fill_top + fill_new rows; the `count` leading eigenvectors are formed, or (cf given) the
 // coefficients made from its own count of them.
@@ -648,10 +655,9 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
     const int LP = c->d.LP, ell = c->d.ell;
     const bool ahead = use_side(c) && !c->prof && next && next_rows >= ell;
     const bool cap = capturing(c->st);
-    // (a captured update must find and leave the rows written)
-    const DeferPlan::Step step = c->df.step(ahead, !cap && ahead && may_defer(c, *next), next_rows, ell);
+    const DeferPlan::Step step = c->df.step(ahead, ahead && may_defer(c, *next), next_rows, ell);
     const hipEvent_t mark = ahead && !cap ? c->ev_mark : nullptr;
-    const bool have_C = c->C_ready && !cap;
+    const bool have_C = c->C_ready;
     c->C_ready = false;
     if (have_C) {
         // formed after the last eigensolve
@@ -1070,6 +1076,7 @@ static int update_rows(sage_ctx* c, RowSrc g, int64_t rows) {
     if (rows < 0) return SAGE_ERR_ARG;
     if (rows == 0) return SAGE_OK;
     c->has_basis = false;
+    note_capture(c);
     const int ell = c->d.ell, LP = c->d.LP;
     if (c->pending_shrink) {
         // the buffer filled up exactly at the end of the previous call: with this call's rows at hand the shrink can
@@ -1182,6 +1189,7 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     ALIVE(c);
     if (k < 1 || k > c->d.ell - 1 || k > 128) return SAGE_ERR_ARG;
     const int KP = pad_pow2_32(k);
+    note_capture(c);
     int rc = flush_pending(c);
     if (rc != SAGE_OK) return rc;
     rc = ensure_vblk(c, KP);

@@ -3,8 +3,8 @@
 // needed, and no more blocks may come together than the buffers are made for. The buffers of the coefficients are followed too, by the
 // numbers of the shrinks that are in them: what the side stream does between the mark and the join is done before or after what the
 // context stream does there, at random, and must find what it was enqueued for either way.
-// Arguments: "planted", the same with the rows of a full set of blocks not written first; "two", with two buffers for the M's. Both
-// must fail.
+// Arguments: "planted", the same with the rows of a full set of blocks not written first; "two", with two buffers for the M's;
+// "forgets", with shrinks deferred after a captured call as before it. All must fail.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -16,7 +16,7 @@
 using sage::DeferPlan;
 typedef std::vector<int> Rows;
 
-static bool planted = false, two = false;
+static bool planted = false, two = false, forgets = false;
 static int failures = 0;
 #define REQUIRE(cond, what)                                                                      \
     do {                                                                                         \
@@ -68,7 +68,8 @@ struct Stream {
     }
     void shrink(const int* next, int64_t n, bool captured) {
         const bool ahead = n >= ell;
-        DeferPlan::Step s = p.step(ahead, !captured, n, ell);
+        if (captured) p.captured = true;
+        DeferPlan::Step s = p.step(ahead, true, n, ell);
         if (planted) s.write_first = false;
         REQUIRE((int)half[p.cur].size() == ell, "a shrink of a half that is not full");
         REQUIRE(p.count == 0 || (ready && !captured), "the products of unwritten rows are not there");
@@ -168,6 +169,7 @@ struct Stream {
 int main(int argc, char** argv) {
     planted = argc > 1 && !strcmp(argv[1], "planted");
     two = argc > 1 && !strcmp(argv[1], "two");
+    forgets = argc > 1 && !strcmp(argv[1], "forgets");
     srand(1);
     for (int trial = 0; trial < 40000; ++trial) {
         Stream s;
@@ -179,7 +181,7 @@ int main(int argc, char** argv) {
             s.update(rand() % 5 < 3 ? 1 + rand() % (6 * s.ell) : s.ell * (1 + rand() % 5), false);
             if (rand() % 6 == 0) s.look();
         }
-        // two cycles of a captured call end where they began
+        // two cycles of a captured call end where they began, and so does an even number of cycles after it
         while (!s.pending || s.shrunk == false) s.update(s.ell - s.fill_new % s.ell, false);
         const int cur = s.p.cur;
         s.ready = false;
@@ -187,6 +189,11 @@ int main(int argc, char** argv) {
         DeferPlan& p = s.p;
         const int ell = s.ell;
         REQUIRE(p.cur == cur, "a captured call of two cycles ends on another half");
+        for (int calls = rand() % 4; calls > 0; --calls) {
+            if (forgets) p.captured = false;
+            s.update(2 * s.ell * (1 + rand() % 3), false);
+            REQUIRE(p.cur == cur, "later calls of whole pairs of cycles end on another half than the captured one");
+        }
         s.look();
     }
     if (failures) printf("%d failures\n", failures);

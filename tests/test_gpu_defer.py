@@ -144,3 +144,40 @@ def test_probe_of_a_matrix_leaves_a_pending_shrink_alone(ell, dtype, D):
     fro = out[0][1].frob2
     assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
     assert _cov_diff(out[0][0], out[1][0]) <= 1e-6 * fro
+
+
+@pytest.mark.parametrize("ell,dtype,D", [(64, "f32", 1200), (128, "bf16", 1200), (256, "bf16", 1200), (256, "f32", 1200), (130, "bf16", 300_000)])
+def test_eager_calls_between_replays_of_a_captured_one(ell, dtype, D):
+    """A graph holds the halves that were in use when it was captured: eager calls of an even number of cycles leave the rows in them, as
+    the captured call does. Against all calls made one by one, bar as above."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(ell)
+    G = [torch.randn((n * ell, D), generator=g, device="cuda").to(td) for n in (2, 1, 2, 4, 2, 2, 2, 6, 2)]
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(st):
+        eager, s = Sage(ell, D, dtype=dtype), Sage(ell, D, dtype=dtype)
+        for c in (eager, s):
+            c.fd_update(G[0])
+            c.fd_update(G[1])          # ends on a full buffer, nothing stored ahead
+        rows = G[2].clone()
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        graph.capture_begin(capture_error_mode="thread_local")
+        s.fd_update(rows)
+        graph.capture_end()
+        for i, B in enumerate(G[2:]):
+            if i % 2 == 0:
+                rows.copy_(B)
+                graph.replay()
+            else:
+                s.fd_update(B)
+            eager.fd_update(B)
+        st.synchronize()
+        want, got = eager.sketch().double(), s.sketch().double()
+        fro = eager.stats().frob2
+        assert _cov_diff(want, got) <= 1e-6 * fro

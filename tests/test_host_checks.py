@@ -44,13 +44,16 @@ def test_slots_of_the_reduction_are_emptied_in_time(tmp_path):
 
 def test_deferred_shrinks_leave_no_rows_behind(tmp_path):
     """defer_check.cc; and the check itself: it must refuse blocks that are not written when there is room for no more, and
-    coefficients in two buffers, of which the side stream reads one while the eigensolve beside it writes it."""
+    coefficients in two buffers, of which the side stream reads one while the eigensolve beside it writes it, and halves that move
+    on after a captured call, whose replays find them where they were."""
     exe = _build(tmp_path, "defer_check")
     r = _run(exe)
     assert r.returncode == 0 and "defer_check ok" in r.stdout, r.stdout
     assert _run(exe, "planted").returncode == 1
     r = _run(exe, "two")
     assert r.returncode == 1 and "W is not that of the shrinks before the last" in r.stdout, r.stdout
+    r = _run(exe, "forgets")
+    assert r.returncode == 1 and "another half than the captured one" in r.stdout, r.stdout
 
 
 def test_a_reduction_that_leaves_64_rows_has_all_it_stores(tmp_path):
