@@ -86,7 +86,8 @@ int sage_set_allocator(sage_alloc_fn alloc, sage_free_fn free, void* user);
  * that new rows only ever land in zero rows, Liberty's form of FD).
  * out: HOST pointer receiving the handle. 2 <= ell <= 256, D >= 1. Device memory: three to five halves of L*D*4 bytes, L =
  * ell padded to 32, 64, 128 or 256, for the sketch, the rows to come and those whose shrink is deferred, plus work space.
- * Where that does not fit, two (L = 32) or three halves will do; SAGE_ERR_ALLOC if those do not fit either.
+ * Where that does not fit, two (L = 32) or three halves will do; SAGE_ERR_ALLOC if those do not fit either. The others are given
+ * back, too, when something that a later call needs does not fit beside them (not by a context whose update or basis was captured in a graph).
  */
 int sage_fd_create(sage_ctx** out, int ell, int64_t D);
 

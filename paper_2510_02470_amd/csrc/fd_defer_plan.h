@@ -25,6 +25,12 @@ struct DeferPlan {
     bool folded = true;
 
     int halves() const { return max > 1 ? max + 1 : 2; }
+    // Between calls: two halves remain, the current rows in the first (which is all that 64 buffer rows need).
+    void give_up() {
+        max = 0;
+        cur = 0;
+        next = spare = 1;
+    }
     int free_half() const {
         if (count == 0 && spare != cur) return spare;
         unsigned used = 1u << cur;

@@ -195,16 +195,67 @@ void dev_free(const Allocator& m, void* p) {
     else (void)hipFree(p);
 }
 
+int give_up_halves(sage_ctx* c);
+// ... for what a context comes to need after its creation
+bool late_alloc(sage_ctx* c, void** p, size_t bytes) {
+    if (dev_alloc(c->mem, c->st, p, bytes)) return true;
+    return give_up_halves(c) == SAGE_OK && dev_alloc(c->mem, c->st, p, bytes);
+}
+#define NO_MEMORY(c) ((c)->poisoned ? SAGE_ERR_HIP : SAGE_ERR_ALLOC)
 // (`c` must be in scope)
-#define ALLOC(ptr, bytes)                                                                    \
-    do {                                                                                     \
-        if (!dev_alloc(c->mem, c->st, (void**)&(ptr), (bytes))) return SAGE_ERR_ALLOC;       \
+#define ALLOC(ptr, bytes)                                                      \
+    do {                                                                       \
+        if (!late_alloc(c, (void**)&(ptr), (bytes))) return NO_MEMORY(c);      \
     } while (0)
 #define FREE(ptr)                       \
     do {                                \
         dev_free(c->mem, (void*)(ptr)); \
         (ptr) = nullptr;                \
     } while (0)
+
+// The halves that only rows stored ahead (64 buffer rows) and deferred shrinks take, given back where memory is short after all:
+// between calls none of them is in use but, perhaps, the current one. The ring is one allocation, so what remains takes the place of
+// it, by way of the host where the two do not fit side by side. SAGE_ERR_ALLOC: there is nothing to give.
+bool capturing(hipStream_t st);
+int give_up_halves(sage_ctx* c) {
+    const int keep = c->d.NP == 64 ? 1 : 2;
+    if (c->halves <= keep || c->df.count > 0 || c->df.captured || capturing(c->st)) return SAGE_ERR_ALLOC;
+    HIPCHK(hipStreamSynchronize(c->st));
+    if (c->st2) HIPCHK(hipStreamSynchronize(c->st2));
+    const size_t half = (size_t)c->half_floats * sizeof(float);
+    const int cur = c->df.cur;
+    const bool rows = c->fill_new > 0;
+    auto copy = [&](void* dst, const void* src, hipMemcpyKind kind) {
+        return !rows || (hipMemcpyAsync(dst, src, half, kind, c->st) == hipSuccess && hipStreamSynchronize(c->st) == hipSuccess);
+    };
+    float* ring = nullptr;
+    bool ok;
+    if (dev_alloc(c->mem, c->st, (void**)&ring, keep * half)) {
+        ok = copy(ring, c->nw(cur), hipMemcpyDeviceToDevice);
+        if (ok) FREE(c->ring);
+    } else {
+        void* const host = rows ? malloc(half) : nullptr;
+        if (rows && !host) return SAGE_ERR_ALLOC;
+        ok = copy(host, c->nw(cur), hipMemcpyDeviceToHost);
+        if (ok) {
+            FREE(c->ring);
+            ok = dev_alloc(c->mem, c->st, (void**)&ring, keep * half) &&  // (no more than what has just been given back)
+                 copy(ring, host, hipMemcpyHostToDevice);
+        }
+        free(host);
+    }
+    if (!ok) {
+        FREE(ring);
+        return hip_failed(c);
+    }
+    c->ring = ring;
+    c->halves = keep;
+    c->nw_bf16[0] = c->nw_bf16[cur];
+    c->nw_half[0] = c->nw_half[cur];
+    for (int i = 1; i < MAX_HALVES; ++i) c->nw_bf16[i] = c->nw_half[i] = false;
+    c->df.give_up();
+    return SAGE_OK;
+}
 
 // The end of the work that sets `done`: a short spin on the host's word, then (the stream has much to do before it, or
 // something failed) the runtime's own wait.
@@ -822,8 +873,8 @@ int ensure_images(sage_ctx* c, int parts) {
         if (im.mem) HIPCHK(hipStreamSynchronize(c->st));
         FREE(im.mem);
         im.bytes = 0;
-        if (!dev_alloc(c->mem, c->st, &im.mem, need)) {
-            if (!other.mem) return SAGE_ERR_ALLOC;
+        if (!late_alloc(c, &im.mem, need)) {
+            if (!other.mem || c->poisoned) return NO_MEMORY(c);
             HIPCHK(hipStreamSynchronize(c->st));
             FREE(other.mem);
             other = BasisImages{};
@@ -1414,9 +1465,9 @@ static int ensure_alpha(sage_ctx* c, int64_t N) {
     void* work = nullptr;
     int64_t ncap = N > c->cap_rows ? N : c->cap_rows;
     ALLOC(na, (size_t)ncap * sizeof(float));
-    if (!dev_alloc(c->mem, c->st, &work, select_work_bytes(ncap))) {
+    if (!late_alloc(c, &work, select_work_bytes(ncap))) {
         FREE(na);
-        return SAGE_ERR_ALLOC;
+        return NO_MEMORY(c);
     }
     if (c->alpha) {
         // keep what a running rescoring pass has written

@@ -181,3 +181,64 @@ def test_eager_calls_between_replays_of_a_captured_one(ell, dtype, D):
         want, got = eager.sketch().double(), s.sketch().double()
         fro = eager.stats().frob2
         assert _cov_diff(want, got) <= 1e-6 * fro
+
+
+@pytest.mark.parametrize("ell,dtype,D,keep,halves,rest", [(20, "f32", 30_001, 1, 2, 3), (64, "f32", 51_300, 2, 4, 64), (64, "f32", 51_300, 2, 4, 0),
+                                                          (100, "bf16", 20_003, 2, 4, 33), (256, "bf16", 400_000, 2, 3, 100)])
+def test_contexts_where_memory_gets_short_later(ell, dtype, D, keep, halves, rest):
+    """A context that was created with the halves for rows ahead and deferred shrinks gives them back when something else it needs does not
+    fit, so that the job goes through in the memory it took without them: the same scores, and the same covariance after further rows (bar
+    as above). rest = 0: against a basis of the caller's, with a shrink pending whose Gram matrix is there."""
+    import torch
+
+    from paper_2510_02470_amd import binding
+
+    L, lp = binding.lib(), max(32, 1 << (ell - 1).bit_length())
+    extra = (halves - keep) * ((D + 15) // 16 * 16 * lp * 4)
+    held, limit, refused, peak = {}, [None], [], [0]
+
+    def take(size, stream, user):
+        used = sum(t.numel() for t in held.values())
+        if limit[0] is not None and used + size > limit[0]:
+            refused.append(size)
+            return None
+        peak[0] = max(peak[0], used + size)
+        t = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+        p = (t.data_ptr() + 255) // 256 * 256
+        held[p] = t[:size]
+        return p
+
+    def give(p, user):
+        torch.cuda.synchronize()
+        held.pop(p, None)
+
+    fns = binding._ALLOC_FN(take), binding._FREE_FN(give)
+    N, k = 7 * ell + rest, ell // 2
+    g = torch.Generator(device="cuda").manual_seed(D)
+    G = (torch.randn((N, k), generator=g, device="cuda") @ torch.randn((k, D), generator=g, device="cuda")
+         + 0.1 * torch.randn((N, D), generator=g, device="cuda")).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    out = []
+    L.sage_set_allocator(fns[0], fns[1], None)
+    try:
+        for short in (False, True):
+            s = binding.Sage(ell, D, dtype=dtype, max_rows=N)
+            s.fd_update(G)
+            if short:
+                limit[0] = peak[0] - extra
+            if rest:
+                s.fd_basis(min(k, 128))
+            else:
+                s.set_basis(G[:k].float())
+            s.score(G)
+            s.select(0.1)
+            alpha = s.scores()
+            s.fd_update(G[:3 * ell])
+            out.append((s.sketch().double(), s.stats(), alpha))
+            s.close()
+    finally:
+        binding._torch_memory(L)
+    assert refused and not held
+    fro = out[0][1].frob2
+    assert torch.equal(out[0][2], out[1][2])
+    assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
+    assert _cov_diff(out[0][0], out[1][0]) <= 1e-6 * fro
