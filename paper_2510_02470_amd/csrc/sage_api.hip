@@ -900,23 +900,27 @@ int finish_basis(sage_ctx* c) {
     return SAGE_OK;
 }
 
-// Which contexts defer shrinks (fd_defer.hip). Us a cycle, at once / deferred, for calls of four cycles:
+// Which contexts defer shrinks (fd_defer.hip). Us a cycle, at once / deferred, for calls of four cycles, medians of seven in turn; runs of
+// one side differ by 3%.
 // Beside the eigensolves while all work on the rows of a cycle is done before an eigensolve is; it then takes the insert, rectangles,
-// a triangle and the rebuild on seven XCDs instead of one rectangle and the rebuild in series. ell = 64, fp32 rows: 227 / 200 (D =
-// 51,300), 239 / 210 (131,072), 285 / 314 (262,144); 128: 424 / 392, 462 / 414, 571 / 639. Three blocks where that costs next to
-// nothing: the rows are rounded to fp32 a third as often. At 512 buffer rows it would cost a tenth (bf16, 131,072: 946 where one block
-// takes 853). Wide fp32 rows gain 4% there (131,072: 1050 / 1009) and stay as they are: their Gram blocks have the same bits however a
-// stream is cut into calls.
+// a triangle and the rebuild on seven XCDs instead of one rectangle and the rebuild in series. The lines lie where the two cross:
+//   ell = 64, fp32 rows:  216 / 200 (D = 131,072), 228 / 222 (163,840), 240 / 250 (196,608), 262 / 306 (262,144)
+//   ell = 100:            368 / 342, 395 / 390, 410 / 435, 451 / 544        ell = 128: 414 / 369, 436 / 402, 457 / 450, 496 / 560
+//   (bf16 rows the same within 3%)
+//   ell = 256, fp32 rows: 863 / 835 (65,536), 931 / 914 (98,304), 945 / 961 (114,688), 967 / 1071 (131,071)
+//   ell = 200:            718 / 695, 795 / 761, 807 / 798, 809 / 878        ell = 136: 540 / 521, 611 / 593, 624 / 618, 642 / 683
+// Three blocks where that costs next to nothing: the rows are rounded to fp32 a third as often. At 512 buffer rows it would cost a tenth
+// (bf16, 131,072: 946 where one block takes 853).
 // Beyond, two at a time where that is less work: rows with one part cost three products per element in a rebuild, the top's six,
 // so two shrinks at once take 12 where one by one they take 18, for one more rectangle of one product (1,048,576: 2332 / 1994; four
-// at once 1998). Against one beside each eigensolve (ell = 256, bf16, beside / two at a time; runs differ by 4%): 916 / 898 (131,072),
-// 1100 / 1090 (262,144), 1345 / 1238 (393,216), 1606 / 1385 (524,288), 1876 / 1500 (655,360). For rows of three parts it would be as
-// much work as before.
+// at once 1998). Against one beside each eigensolve (bf16, beside / two at a time): ell = 256, 852 / 864 (131,072), 910 / 929 (163,840),
+// 954 / 939 (196,608), 1082 / 1034 (262,144), 1189 / 1069 (327,680); ell = 200, 725 / 735, 762 / 775, 786 / 781, 886 / 835, 992 / 911. For
+// rows of three parts it would be as much work as before.
 void defer_plan(sage_ctx* c) {
     const int64_t D = c->d.D;
     if (c->d.NP < 128) return;
     const bool one = c->dtype == SAGE_BF16 && c->d.NP == 512;
-    c->df.beside = D <= (c->d.NP < 512 ? 196608 : one ? 262144 : 131071);
+    c->df.beside = D <= (c->d.NP < 512 ? 196608 : one ? 180224 : 98304);
     c->df.max = c->df.beside ? (c->d.NP < 512 ? 3 : 1) : one ? 2 : 0;
 }
 

@@ -38,11 +38,13 @@ def _cov_diff(A, B):
     return float((K @ K).trace().clamp(min=0).sqrt())
 
 
-# 128, 256 and 512 buffer rows with and without padding, row types, widths that are a multiple of nothing; the last three widths: two
-# shrinks at a time are put together, wide fp32 rows at the last one where they are deferred, the first with two shrinks at a time
+# 128, 256 and 512 buffer rows with and without padding, row types, widths that are a multiple of nothing; then both sides of the widths
+# where a plan ends: one beside each eigensolve, or two at a time (bf16 at 512 buffer rows), or all at once
 @pytest.mark.parametrize("ell,dtype,D", [(33, "f32", 701), (64, "f32", 5130), (64, "bf16", 2113), (65, "f32", 1300), (100, "bf16", 25447),
                                          (128, "f32", 3001), (129, "bf16", 1999), (200, "f32", 2050), (256, "bf16", 4097),
-                                         (129, "bf16", 589_825), (129, "f32", 131_071), (200, "bf16", 262_145)])
+                                         (129, "bf16", 589_825), (129, "f32", 131_071), (200, "bf16", 262_145),
+                                         (129, "f32", 98_304), (129, "f32", 98_305), (136, "bf16", 180_224), (136, "bf16", 180_225),
+                                         (40, "f32", 196_608), (40, "f32", 196_609)])
 def test_streams_in_calls_of_many_few_and_part_cycles(ell, dtype, D):
     """The covariance is held to 1e-6 of |A|_F^2: nine cycles whose Gram entries carry fp32 sums of their slabs (a few 2^-24 of the rows'
     norms) and whose rows are rounded to fp32 at most once each; 6e-8 is what such streams leave."""
