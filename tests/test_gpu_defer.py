@@ -4,6 +4,11 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+# Of |A|_F^2, for the covariance after some nine cycles, whose Gram entries are fp32 sums over slabs and whose rows are rounded to fp32 once
+# for every rebuild. Such streams leave 1.2e-7 to 2.3e-7 (18 sizes, four cuts, three seeds each). With the third bf16 part of the
+# coefficients or of the rows left out of the rebuild it would be 9e-7 to 2.6e-6 (a model in 64 bits, six sizes).
+BAR = 4e-7
+
 
 def _shrink(A, ell):
     import torch
@@ -46,8 +51,8 @@ def _cov_diff(A, B):
                                          (129, "f32", 98_304), (129, "f32", 98_305), (136, "bf16", 180_224), (136, "bf16", 180_225),
                                          (40, "f32", 196_608), (40, "f32", 196_609)])
 def test_streams_in_calls_of_many_few_and_part_cycles(ell, dtype, D):
-    """The covariance is held to 1e-6 of |A|_F^2: nine cycles whose Gram entries carry fp32 sums of their slabs (a few 2^-24 of the rows'
-    norms) and whose rows are rounded to fp32 at most once each; 6e-8 is what such streams leave."""
+    """Against |A|_F^2, ||A||_F^2 itself and the covariance to BAR and the sum of the deltas to 5e-9, of which 1.3e-9 is the most (fp32 sums
+    over D of squares of one sign are off by up to 2e-7, the deltas' errors are of either sign)."""
     import torch
 
     from paper_2510_02470_amd.binding import Sage
@@ -70,8 +75,8 @@ def test_streams_in_calls_of_many_few_and_part_cycles(ell, dtype, D):
             lo += n
         st = s.stats()
         assert st.rows_seen == N and st.n_unconverged == 0, name
-        assert abs(st.frob2 - fro) <= 1e-6 * fro and abs(st.sum_delta - delta) <= 1e-6 * fro, name
-        assert _cov_diff(s.sketch().double(), want) <= 1e-6 * fro, name
+        assert abs(st.frob2 - fro) <= BAR * fro and abs(st.sum_delta - delta) <= 5e-9 * fro, name
+        assert _cov_diff(s.sketch().double(), want) <= BAR * fro, name
         s.close()
 
 
@@ -118,8 +123,8 @@ def test_contexts_where_memory_is_short(ell, dtype, D, ring):
                 binding._torch_memory(L)
     assert refused and not held
     fro = out[0][1].frob2
-    assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
-    assert _cov_diff(out[0][0].double(), out[1][0].double()) <= 1e-6 * fro
+    assert abs(out[1][1].frob2 - fro) <= BAR * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= BAR * fro
+    assert _cov_diff(out[0][0].double(), out[1][0].double()) <= BAR * fro
 
 
 @pytest.mark.parametrize("ell,dtype,D", [(64, "f32", 5130), (100, "bf16", 2113), (256, "bf16", 4097)])
@@ -144,8 +149,8 @@ def test_probe_of_a_matrix_leaves_a_pending_shrink_alone(ell, dtype, D):
         out.append((s.sketch().double(), s.stats()))
         s.close()
     fro = out[0][1].frob2
-    assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
-    assert _cov_diff(out[0][0], out[1][0]) <= 1e-6 * fro
+    assert abs(out[1][1].frob2 - fro) <= BAR * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= BAR * fro
+    assert _cov_diff(out[0][0], out[1][0]) <= BAR * fro
 
 
 @pytest.mark.parametrize("ell,dtype,D", [(64, "f32", 1200), (128, "bf16", 1200), (256, "bf16", 1200), (256, "f32", 1200), (130, "bf16", 300_000)])
@@ -182,7 +187,7 @@ def test_eager_calls_between_replays_of_a_captured_one(ell, dtype, D):
         st.synchronize()
         want, got = eager.sketch().double(), s.sketch().double()
         fro = eager.stats().frob2
-        assert _cov_diff(want, got) <= 1e-6 * fro
+        assert _cov_diff(want, got) <= BAR * fro
 
 
 @pytest.mark.parametrize("ell,dtype,D,keep,halves,rest", [(20, "f32", 30_001, 1, 2, 3), (64, "f32", 51_300, 2, 4, 64), (64, "f32", 51_300, 2, 4, 0),
@@ -242,5 +247,5 @@ def test_contexts_where_memory_gets_short_later(ell, dtype, D, keep, halves, res
     assert refused and not held
     fro = out[0][1].frob2
     assert torch.equal(out[0][2], out[1][2])
-    assert abs(out[1][1].frob2 - fro) <= 1e-6 * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= 1e-6 * fro
-    assert _cov_diff(out[0][0], out[1][0]) <= 1e-6 * fro
+    assert abs(out[1][1].frob2 - fro) <= BAR * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= BAR * fro
+    assert _cov_diff(out[0][0], out[1][0]) <= BAR * fro
