@@ -8,6 +8,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "fd_rows.h"
 #include "sage_internal.h"
 
 namespace sage {
@@ -926,10 +927,6 @@ __global__ __launch_bounds__(256, 2) void gram_new8_half_kernel(const float* __r
     }
 }
 
-struct __attribute__((packed, aligned(2))) Piece8 {  // eight bf16 values at any element boundary
-    u32x4 v;
-};
-
 // ... of rows on their way from the caller's batch into the half, which saves reading them a second time: a stage is four slabs, 128 bytes of every row, loaded as insert16_kernel
 // does (lane = (row, piece of four neighbours), the two halves of a line one after the other), two stages ahead, and goes from the
 // registers to LDS and to the half. 256 rows of 2,049,000 beside an eigensolve: 490 us (4.3 TB/s), stored and multiplied by a kernel each
@@ -958,7 +955,7 @@ __device__ __forceinline__ void gram_new8_rows16_wave(u32x4* __restrict__ N16, c
         const char* g0 = reinterpret_cast<const char*>(G + c);
         if (c + KC <= D) {  // (uniform)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const Piece8*>(g0 + src[q >> 1] + 64 * (q & 1))->v;
+            for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const Eight*>(g0 + src[q >> 1] + 64 * (q & 1))->v;
         } else {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
@@ -966,7 +963,7 @@ __device__ __forceinline__ void gram_new8_rows16_wave(u32x4* __restrict__ N16, c
                 const uint16_t* g = reinterpret_cast<const uint16_t*>(g0 + src[q >> 1] + 64 * (q & 1));
                 u32x4 x = {0u, 0u, 0u, 0u};
                 if (left >= 8) {
-                    x = reinterpret_cast<const Piece8*>(g)->v;
+                    x = reinterpret_cast<const Eight*>(g)->v;
                 } else {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[e >> 1] |= e < left ? (unsigned)g[e] << (16 * (e & 1)) : 0u;
