@@ -111,8 +111,12 @@ int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, i
  * stream. Invalidates a basis made earlier. The host never reads device data in this call.
  * When a call ends exactly on a full buffer, that shrink is left for the next sage_fd_update (which can then overlap
  * part of it with the storing of its own first rows) or for the first call that looks at the sketch (sage_fd_basis,
- * sage_stats, the exports and probes); results are the same either way. Part of the work runs on a second stream
+ * sage_stats, the exports and probes); the result is as good either way. Equal calls on equal rows give equal bits; how a stream is
+ * cut into calls decides the order of some sums and how often rows are rounded to fp32, so the last bits depend on it. Part of the work runs on a second stream
  * owned by the context; the batch is free for reuse once the call's work is complete on the context's stream.
+ * A call captured in a graph works on the memory that holds the buffer's rows then, also when it is replayed. It can be replayed
+ * after itself, and after other update calls in between, if all of them bring ell rows an even number of times (any number for ell <= 32). The
+ * counters of sage_stats that the host keeps (rows_seen, n_shrinks) know nothing of replays.
  */
 int sage_fd_update(sage_ctx* ctx, const void* G_batch, int64_t rows);
 

@@ -80,7 +80,7 @@ __device__ __forceinline__ void lds_barrier() {
 
 // The reduction by one work-group of T threads, with the matrix in V (its rows become the reflectors) and the vectors of a step
 // in LDS: every step reads and writes the trailing matrix once, through the L2. For solves that several work-groups could not
-// do together: 0.5, 2.2 and 12.8 ms at 128, 256 and 512 rows, where they take 0.12, 0.27 and 0.74. vec: 4 N words.
+// do together: 0.5, 2.2 and 12.8 ms at 128, 256 and 512 rows, where they take 0.085, 0.21 and 0.55. vec: 4 N words.
 template <int J, int T>
 __device__ __forceinline__ void tri_alone(const double* __restrict__ C, int NP, int m0, int LP, int n, double* __restrict__ dT,
                                           double* __restrict__ eT, double* __restrict__ tauT, double* V, double sc0,
