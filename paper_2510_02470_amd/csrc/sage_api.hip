@@ -1551,7 +1551,7 @@ int sage_select(sage_ctx* c, double keep_rate, int64_t* out_idx, int64_t cap, in
     if (c->store_zhat) RUN(K_SELECT, launch_cosine(c->zhat, N, c->k, c->ssum, c->alpha, c->st));
     c->alpha_n = N;
     const HostSignal done = next_signal(c);
-    RUN(K_SELECT, launch_topm(c->alpha, N, m, out_idx, c->sw, c->st, done));
+    RUN(K_SELECT, launch_topm(c->alpha, N, m, out_idx, c->sw, false, c->st, done));
     HIPCHK(topm_signals(N, m) ? wait_signal(done, c->st) : hipStreamSynchronize(c->st));
     return SAGE_OK;
 }
@@ -1615,7 +1615,7 @@ int sage_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* 
     }
     HostSignal done;
     if (topm_signals(N, m)) (void)signal_take(done);
-    hipError_t e = launch_topm(alpha, N, m, out_idx, w, st, done);
+    hipError_t e = launch_topm(alpha, N, m, out_idx, w, false, st, done);
     hipError_t e2 = e == hipSuccess && done.word ? wait_signal(done, st) : hipStreamSynchronize(st);
     signal_give(done);
     dev_free(mem, w.hist);

@@ -338,7 +338,8 @@ struct HostSignal {
     unsigned token = 0;
 };
 bool topm_signals(int64_t N, int64_t m);  // launch_topm sets the word
-hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w,
+// clear: the histograms of w are zero, as every run leaves them; otherwise one launch more makes them so.
+hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w, bool clear,
                        hipStream_t st, HostSignal done = HostSignal{});
 constexpr int COPY_SIGNAL_MAX = 32768;  // floats: 32 a thread of the one work-group; more is the copy engine's work
 hipError_t launch_copy_signal(const float* src, int n, float* dst, HostSignal done, hipStream_t st);

@@ -46,9 +46,11 @@ hipError_t launch_cosine(const float* zhat, int64_t N, int k, const double* ssum
 // there is to move is 4 N bytes, so what counts is the number of launches (about 3 us each with its gap) and serial work
 // inside them:
 //   N <= TOPM_ONE: one work-group does everything, keys in registers, histograms in LDS; one launch, no work space;
-//   else: clear, two histograms, the third with a table for each block of keys, emit. Every work-group of the next kernel
+//   else: two histograms, the third with a table for each block of keys, emit. Every work-group of the next kernel
 //         reads the histogram and finds the digit itself (a scan over the bins by 1024 threads), so there are no kernels
-//         between them. The tables answer, whatever the last digit turns out to be, how many keys of a block are above it and
+//         between them. Each run clears a histogram after its last reader, so that work space that is kept is clear for the
+//         next run, and only new work space takes a launch for that (a million keys in kept work space: 20.0 us with it, 18.1
+//         without). The tables answer, whatever the last digit turns out to be, how many keys of a block are above it and
 //         how many equal it, which took a kernel of its own between the last histogram and emit (a million keys: 24.2 us
 //         with it, 22.4 without, 19.9 with fewer work-groups for the histograms, see launch_topm).
 // The first digit has 12 bits because scores crowd into a few binary orders of magnitude: with 8 bits most lanes of a wave
@@ -96,13 +98,13 @@ __global__ __launch_bounds__(TOPM_T) void topm_one_kernel(const float* __restric
     signal_host(done);
 }
 
-// hist: BINS1 + 2 BINS2 words
+// hist: BINS1 + 2 BINS2 words. (The third part needs no clearing here, but new work space is all the same to this launch.)
 __global__ __launch_bounds__(TOPM_T) void topm_clear_kernel(uint32_t* __restrict__ hist) {
     hist[blockIdx.x * TOPM_T + threadIdx.x] = 0;
 }
 
 // Histogram of digit P (0: bits 31..20, 1: bits 19..10) of the keys that share the digits found so far. state[0], state[1]: the
-// first digit and the count left, found from the first histogram, left for the next kernel.
+// first digit and the count left, found from the first histogram, left for the next kernel. P = 0 also clears the third histogram.
 template <int P>
 __global__ __launch_bounds__(TOPM_T) void topm_hist_kernel(const float* __restrict__ alpha, int64_t N, uint32_t m,
                                                            uint32_t* __restrict__ hist, uint32_t* __restrict__ state) {
@@ -120,6 +122,7 @@ __global__ __launch_bounds__(TOPM_T) void topm_hist_kernel(const float* __restri
             state[1] = rest;
         }
     } else {
+        if (blockIdx.x == 0) hist[BINS1 + BINS2 + tid] = 0;
         __syncthreads();
     }
     const int64_t stride = (int64_t)gridDim.x * TOPM_T;
@@ -142,7 +145,8 @@ __global__ __launch_bounds__(TOPM_T) void topm_hist_kernel(const float* __restri
 }
 
 // Histogram of the last digit (bits 9..0), and for each block of 1024 C keys: blk_gt, how many are above all that share
-// the first 22 bits, blk_in, how many share them, and if any do, table[d], how many of those have a last digit of d or more.
+// the first 22 bits, blk_in, how many share them, and if any do, table[d], how many of those have a last digit of d or more. Clears
+// the first histogram, which has been read.
 template <int C>
 __global__ __launch_bounds__(TOPM_T) void topm_table_kernel(const float* __restrict__ alpha, int64_t N,
                                                             uint32_t* __restrict__ hist, uint32_t* __restrict__ state,
@@ -158,6 +162,7 @@ __global__ __launch_bounds__(TOPM_T) void topm_table_kernel(const float* __restr
     for (int c = 0; c < C; ++c) key[c] = base + c * TOPM_T < N ? score_key(alpha[base + c * TOPM_T]) : 0u;
     h[tid] = 0;
     if (tid == 0) sg = si = 0;
+    if (blockIdx.x < BINS1 / TOPM_T) hist[blockIdx.x * TOPM_T + tid] = 0;
     uint32_t digit, rest;
     pick_bin<TOPM_T, BINS2>(hist + BINS1, state[1], pw, digit, rest);
     const uint32_t prefix = (state[0] << 10) | digit;
@@ -189,11 +194,10 @@ __global__ __launch_bounds__(TOPM_T) void topm_table_kernel(const float* __restr
     table[(int64_t)blockIdx.x * BINS2 + d] = (uint16_t)block_scan<TOPM_T>(v, tot);
 }
 
-// every work-group adds up the counts of the blocks before its own
+// every work-group adds up the counts of the blocks before its own; the second histogram, which has been read, is cleared
 template <int C>
 __global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restrict__ alpha, int64_t N,
-                                                           const uint32_t* __restrict__ hist,
-                                                           const uint32_t* __restrict__ state,
+                                                           uint32_t* __restrict__ hist, const uint32_t* __restrict__ state,
                                                            const uint32_t* __restrict__ blk_gt,
                                                            const uint32_t* __restrict__ blk_in,
                                                            const uint16_t* __restrict__ table, int64_t* __restrict__ out_idx) {
@@ -207,6 +211,7 @@ __global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restri
         key[c] = i < N ? score_key(alpha[i]) : 0u;
     }
     if (threadIdx.x == 0) sg = se = 0;
+    if (blockIdx.x == 0) hist[BINS1 + threadIdx.x] = 0;
     uint32_t digit, rest;
     pick_bin<TOPM_T, BINS2>(hist + BINS1 + BINS2, state[3], pw, digit, rest);
     uint32_t g = 0, e = 0;
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restri
     emit_keys<TOPM_T, C>(key, base, (state[2] << 10) | digit, rest, sg, se, cnt, tot, out_idx);
 }
 
-// One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of five launches wins.
+// One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of four launches wins.
 constexpr int64_t TOPM_ONE = 32 * TOPM_T;
 
 // Small copies for a caller that waits: one work-group, then the signal.
@@ -247,7 +252,7 @@ bool topm_needs_work(int64_t N) { return N > TOPM_ONE; }
 
 bool topm_signals(int64_t N, int64_t m) { return m > 0 && N > 0 && N <= TOPM_ONE; }
 
-hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w,
+hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, const SelectWork& w, bool clear,
                        hipStream_t st, HostSignal done) {
     if (m <= 0 || N <= 0) return hipSuccess;
     if (N <= TOPM_ONE) {
@@ -268,7 +273,8 @@ hipError_t launch_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_id
     // included, 56.0 with 512, 49.8 with 244).
     const int64_t blocks = (N + SELECT_BLOCK - 1) / SELECT_BLOCK, wide = blocks / 4;
     const int64_t hw = wide < 64 ? (blocks < 64 ? blocks : 64) : wide < 512 ? wide : 512;
-    hipLaunchKernelGGL(topm_clear_kernel, dim3(TOPM_HIST_WORDS / TOPM_T), dim3(TOPM_T), 0, st, w.hist);
+    static_assert(BINS2 == TOPM_T && BINS1 / TOPM_T <= TOPM_ONE / SELECT_BLOCK, "a bin a thread; as many blocks as clear bins");
+    if (!clear) hipLaunchKernelGGL(topm_clear_kernel, dim3(TOPM_HIST_WORDS / TOPM_T), dim3(TOPM_T), 0, st, w.hist);
     hipLaunchKernelGGL(topm_hist_kernel<0>, dim3((unsigned)hw), dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
     hipLaunchKernelGGL(topm_hist_kernel<1>, dim3((unsigned)hw), dim3(TOPM_T), 0, st, alpha, N, (uint32_t)m, w.hist, w.state);
 #define SAGE_TAIL(C)                                                                                                          \

@@ -1,6 +1,7 @@
 // Top-m selection for callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses that
 // forbid hipMalloc): the radix-select work space lives in a file-scope device array instead of a per-call allocation.
 // See sage_topm_static in include/sage.h.
+#include <atomic>
 #include <mutex>
 
 #include "sage_internal.h"
@@ -20,10 +21,12 @@ static __device__ __align__(256) uint32_t scratch[SCRATCH_WORDS];
 constexpr int MAX_DEVICES = 64;
 std::mutex g_lock;
 uint32_t* g_ptr[MAX_DEVICES] = {nullptr};
+// A run of several launches of which one was refused may have left its histograms as they were: the next call clears them.
+std::atomic<bool> g_cut_short[MAX_DEVICES];
 
 // Device address of `scratch` on the current device (looked up on the first call per device).
-int scratch_ptr(uint32_t** out) {
-    int dev = -1;
+int scratch_ptr(uint32_t** out, int& dev) {
+    dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
         return SAGE_ERR_HIP;
@@ -49,14 +52,18 @@ extern "C" int sage_topm_static(const float* alpha, int64_t N, int64_t m, int64_
     if (N > MAX_N) return SAGE_ERR_CAPACITY;
     if (m == 0) return SAGE_OK;
     uint32_t* base = nullptr;
-    int rc = scratch_ptr(&base);
+    int dev = -1, rc = scratch_ptr(&base, dev);
     if (rc != SAGE_OK) return rc;
     const sage::SelectWork w = sage::select_work_at(base, MAX_BLOCKS);
-    // the first kernel of the run clears the histograms; the state, every per-block counter and every table that is read
-    // are written earlier in the same run, so nothing of the previous call's contents is used
-    if (sage::launch_topm(alpha, N, m, out_idx, w, (hipStream_t)hip_stream) != hipSuccess) {
+    // The histograms are zero when the module is loaded and when a run is over (two that overlapped too, once both are: each
+    // clears them after its own additions); the state, every per-block counter and every table that is read are written earlier in
+    // the same run. So nothing of the previous call's contents is used.
+    const bool clear = !g_cut_short[dev].load();
+    if (sage::launch_topm(alpha, N, m, out_idx, w, clear, (hipStream_t)hip_stream) != hipSuccess) {
         (void)hipGetLastError();
+        g_cut_short[dev].store(true);
         return SAGE_ERR_HIP;
     }
+    if (!clear && sage::topm_needs_work(N)) g_cut_short[dev].store(false);
     return SAGE_OK;
 }

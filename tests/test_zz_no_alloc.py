@@ -54,3 +54,30 @@ def test_static_topm_rejects_what_it_cannot_hold():
     assert L.sage_topm_static(p, 16, 17, q, None) == binding.SAGE_ERR_ARG
     assert L.sage_topm_static(None, 16, 1, q, None) == binding.SAGE_ERR_ARG
     assert L.sage_topm_static(p, 16, 0, None, None) == 0
+
+
+def test_static_topm_leaves_its_work_space_clear():
+    """Runs that take several launches clear their histograms behind them: calls and replays in any order, at the smallest such
+    size, at both block lengths and at the most keys there may be, give what a sort gives."""
+    import torch
+
+    from paper_2510_02470_amd import binding
+
+    def check(a, m, got):
+        order = torch.sort(a + 0.0, descending=True, stable=True).indices[:m]
+        assert torch.equal(torch.sort(order).values, got)
+
+    a = _scores(300_001, 11, torch)
+    out = torch.empty(20_000, dtype=torch.int64, device="cuda")
+    binding.topm_static(a, 20_000, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        binding.topm_static(a, 20_000, out)
+    for i, (n, m) in enumerate([(32_769, 1), (4_194_305, 70_000), (binding.TOPM_STATIC_MAX_N, 5), (1000, 10), (40_000, 40_000)]):
+        a.copy_(_scores(300_001, 20 + i, torch))
+        out.fill_(-1)
+        graph.replay()
+        check(a, 20_000, out)
+        b = _scores(n, 30 + i, torch)
+        check(b, m, binding.topm_static(b, m, torch.empty(m, dtype=torch.int64, device="cuda")))
