@@ -499,20 +499,23 @@ __global__ __launch_bounds__(512, 1) void gram_cross8_split_kernel(GramTops tops
 // The same rectangle of two blocks kept in pieces of bf16 (half16), the top rows being an earlier block's: one part each, one
 // product (the bits of the kernel above, whose other products add exact zeros), nothing to convert. Bound by memory: the pieces
 // go straight to LDS, two slabs (32 KB) at a time into a ring of three, two of them on their way. (With three slabs at a time, 144 KB of
-// a CU's 160, the merges of the eigensolve beside it waited for it, 230 us.)
+// a CU's 160, the merges of the eigensolve beside it waited for it, 230 us.) Several earlier blocks: the new rows of a range come from
+// the L2 for all but one of them (three blocks of 256 rows of 2,049,000: 1100 us, 1270 one block after the other).
 __global__ __launch_bounds__(512, 1) void gram_cross8_half_kernel(GramTops tops, const float* __restrict__ nw, int nfill,
                                                                   float* __restrict__ partial, int64_t slabs_total,
-                                                                  int64_t slabs_per_group, int groups,
+                                                                  int64_t slabs_per_group, int groups, int count,
                                                                   const int* __restrict__ hole) {
     constexpr int LP = 256, SL = 2, SLAB = 2 * 2 * LP, STAGE = SL * SLAB, ML = STAGE / 512;  // SLAB: [top, new][k-half][row]
     extern __shared__ u32x4 ldsc[];  // 3 * STAGE
-    const int group = (int)spare_unit_at(hole);
-    if (group < 0 || group >= groups) return;
-    partial += blockIdx.y * tops.stride;
+    const int at = hole ? *hole : -1, unit = (int)spare_unit(blockIdx.x, at);
+    if (unit < 0) return;
+    const int group = range_unit(unit, count, at).range, block = range_unit(unit, count, at).part;
+    if (group >= groups) return;
+    partial += block * tops.stride;
     const int64_t s0 = (int64_t)group * slabs_per_group;
     int64_t s1 = s0 + slabs_per_group;
     if (s1 > slabs_total) s1 = slabs_total;
-    const u32x4* T16 = half16(tops.p[blockIdx.y], LP, slabs_total);
+    const u32x4* T16 = half16(tops.p[block], LP, slabs_total);
     const u32x4* N16 = half16(nw, LP, slabs_total);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1188,8 +1191,8 @@ hipError_t launch_gram_blocks(const GramTops& tops, int count, const float* nw, 
     constexpr int LDS = 3 * 2 * 2 * 2 * 256 * 16;  // three stages of two slabs
     if (count <= 0) return hipSuccess;
     if (hipError_t ea = ensure_dynamic_lds((const void*)gram_cross8_half_kernel, LDS); ea != hipSuccess) return ea;
-    hipLaunchKernelGGL(gram_cross8_half_kernel, dim3((unsigned)spare_grid_at(p.groups, hole), count), dim3(512), LDS, st, tops,
-                       nw, nfill, partial, d.S, p.slabs_per_group, p.groups, hole);
+    hipLaunchKernelGGL(gram_cross8_half_kernel, dim3((unsigned)spare_grid_at(range_units(p.groups, count, hole ? 0 : -1), hole)), dim3(512), LDS, st, tops, nw, nfill,
+                       partial, d.S, p.slabs_per_group, p.groups, count, hole);
     return hipGetLastError();
 }
 

@@ -911,17 +911,20 @@ int finish_basis(sage_ctx* c) {
 //   ell = 200:            718 / 695, 795 / 761, 807 / 798, 809 / 878        ell = 136: 540 / 521, 611 / 593, 624 / 618, 642 / 683
 // Three blocks where that costs next to nothing: the rows are rounded to fp32 a third as often. At 512 buffer rows it would cost a tenth
 // (bf16, 131,072: 946 where one block takes 853).
-// Beyond, two at a time where that is less work: rows with one part cost three products per element in a rebuild, the top's six,
-// so two shrinks at once take 12 where one by one they take 18, for one more rectangle of one product (1,048,576: 2332 / 1994; four
-// at once 1998). Against one beside each eigensolve (bf16, beside / two at a time): ell = 256, 852 / 864 (131,072), 910 / 929 (163,840),
+// Beyond, several at a time where that is less work: rows with one part cost three products per element in a rebuild, the top's six,
+// so two shrinks at once take 12 where one by one they take 18, for one more rectangle of one product (1,048,576: 2332 / 1994).
+// Against one beside each eigensolve (bf16, beside / two at a time): ell = 256, 852 / 864 (131,072), 910 / 929 (163,840),
 // 954 / 939 (196,608), 1082 / 1034 (262,144), 1189 / 1069 (327,680); ell = 200, 725 / 735, 762 / 775, 786 / 781, 886 / 835, 992 / 911. For
-// rows of three parts it would be as much work as before.
+// rows of three parts it would be as much work as before. Up to four at once take 18 where two by two they take 24, for three rectangles
+// more, which are formed beside the eigensolves as long as these last; and two halves more of memory. Two / up to four at a time, calls
+// of 4 cycles: ell = 256, 942 / 945 (190,000), 1081 / 1075 (300,000), 1424 / 1372 (600,000), 3190 / 3100 (2,049,000); ell = 200, 852 / 837
+// (260,000), 1644 / 1500 (1,000,000); calls of 3 and of 5 cycles gain more (an odd one is not left alone).
 void defer_plan(sage_ctx* c) {
     const int64_t D = c->d.D;
     if (c->d.NP < 128) return;
     const bool one = c->dtype == SAGE_BF16 && c->d.NP == 512;
     c->df.beside = D <= (c->d.NP < 512 ? 196608 : one ? 180224 : 98304);
-    c->df.max = c->df.beside ? (c->d.NP < 512 ? 3 : 1) : one ? 2 : 0;
+    c->df.max = c->df.beside ? (c->d.NP < 512 ? 3 : 1) : one ? (D < 524288 ? 2 : 4) : 0;
 }
 
 int64_t keep_count(double keep_rate, int64_t N) {

@@ -44,4 +44,19 @@ constexpr long long spare_unit(unsigned block, int hole) {
 }
 constexpr long long spare_grid(long long units, int hole) { return hole < 0 ? units : (units + 6) / 7 * 8; }  // work-groups
 
+
+// Units that read a range in common, `count` to a range: of such a launch they are neighbours on one XCD, whose L2 they share.
+struct RangeUnit {
+    int range, part;
+};
+constexpr int range_stride(int hole) { return hole < 0 ? 8 : 7; }  // units that are this far apart
+constexpr RangeUnit range_unit(int unit, int count, int hole) {
+    const int w = range_stride(hole);
+    return RangeUnit{unit / (w * count) * w + unit % w, unit / w % count};
+}
+constexpr int range_units(int ranges, int count, int hole) {  // (those of ranges beyond the last have nothing to do)
+    const int w = range_stride(hole);
+    return (ranges + w - 1) / w * w * count;
+}
+
 }  // namespace sage

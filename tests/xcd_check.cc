@@ -45,9 +45,31 @@ static void check_spare() {
         }
 }
 
+// every part of every range once, the parts of a range on one XCD
+static void check_ranges() {
+    for (int hole = -1; hole < 8; ++hole)
+        for (int count = 1; count <= 5; ++count)
+            for (int ranges = 1; ranges <= 230; ranges += ranges < 20 ? 1 : 7) {
+                std::vector<int> done(ranges * count, 0), place(ranges, -1);
+                const long long grid = spare_grid(range_units(ranges, count, hole), hole);
+                for (long long b = 0; b < grid; ++b) {
+                    const long long u = spare_unit((unsigned)b, hole);
+                    if (u < 0) continue;
+                    const RangeUnit r = range_unit((int)u, count, hole);
+                    REQUIRE(r.range >= 0 && r.part >= 0 && r.part < count);
+                    if (r.range >= ranges) continue;
+                    ++done[r.range * count + r.part];
+                    REQUIRE(place[r.range] < 0 || place[r.range] == (int)(b & 7));
+                    place[r.range] = (int)(b & 7);
+                }
+                for (int d : done) REQUIRE(d == 1);
+            }
+}
+
 int main() {
     check_map();
     check_spare();
+    check_ranges();
     if (!failures) printf("xcd_check ok\n");
     return failures ? 1 : 0;
 }
