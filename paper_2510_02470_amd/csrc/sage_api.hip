@@ -551,17 +551,14 @@ int gram_whole_split(sage_ctx* c, hipEvent_t mark = nullptr) {
     return SAGE_OK;
 }
 
-// Gram + eigensolve of the buffer as it stands, and the coefficients of a basis. After a shrink the Gram matrix of the top rows
-// is known (diagonal lambda_j - delta, recorded by the shrink), so their block is not recomputed.
+// After a shrink the Gram matrix of the top rows is known (diagonal lambda_j - delta, recorded by the shrink).
+bool top_known(const sage_ctx* c) { return c->top_shrunk && c->gp_skip.t0 > 0; }
+
+// Gram + eigensolve of the buffer as it stands, and the coefficients of a basis. A block that is known is not recomputed.
 int decompose(sage_ctx* c, const CoeffArgs& cf) {
     if (int rc = clear_top(c); rc != SAGE_OK) return rc;
-    const bool skip = c->top_shrunk && c->gp_skip.t0 > 0;
-    if (skip && c->fill_new == 0) {
-        // only the rows the last shrink wrote are there: nothing to compute
-        GramPlan none = c->gp_skip;
-        none.tiles = 0;
-        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, none, nullptr, nullptr, c->ew.C, true, c->ew.known, c->d, c->st));
-    } else if (!skip && split_grams(c) && !c->new_block_ready && !c->pre_stored) {
+    const bool skip = top_known(c);
+    if (!skip && split_grams(c) && !c->new_block_ready && !c->pre_stored) {
         if (int rc = gram_whole_split(c); rc != SAGE_OK) return rc;
     } else if (skip && split_grams(c) && !c->new_block_ready && !c->pre_stored) {
         // the two blocks that are not known, with the split-arithmetic kernels (the side stream is idle here: its
@@ -1252,15 +1249,20 @@ static int basis_impl(sage_ctx* c, int k, bool weighted) {
     if (rc != SAGE_OK) return rc;
     rc = ensure_vblk(c, KP);
     if (rc != SAGE_OK) return rc;
+    const bool shrunk = top_known(c) && c->fill_new == 0;  // only the rows the last shrink wrote are there: nothing to decompose
     const bool split_rb = c->mm_mode == SAGE_MM_SPLIT && c->Mt3 && rebuild_split_ok(KP) && KP <= c->d.LP;
     const CoeffArgs cf{KP, k, weighted ? 2 : 1, c->d.n, c->d.ell, c->cnt_top, c->fill_top, c->d.LP + c->cnt_new,
                        c->d.LP + c->fill_new, c->Mt, split_rb ? c->Mt3 : nullptr, c->acc};
-    rc = decompose(c, cf);
-    if (rc != SAGE_OK) return rc;
+    if (!shrunk) {  // (of a shrunk buffer's rows all are counted in ||A||_F^2)
+        rc = decompose(c, cf);
+        if (rc != SAGE_OK) return rc;
+    }
     c->cnt_top = c->fill_top;
     c->cnt_new = c->fill_new;
     const NewBlocks rows{c->ring, c->half_floats, (unsigned)c->df.cur, 1};
-    if (split_rb)
+    if (shrunk)
+        RUN(K_REBUILD, launch_basis_rows(c->top, c->ew.known, k, cf.mode, c->Vblk, KP, c->d, c->st));
+    else if (split_rb)
         RUN(K_REBUILD, launch_rebuild_split(c->top, rows, c->fill_new, c->Mt3, c->Vblk, KP, KP, c->d, c->st,
                                             c->fill_new > 0 && new_one(c, c->df.cur)));
     else {

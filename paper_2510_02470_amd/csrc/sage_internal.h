@@ -267,6 +267,8 @@ size_t rebuild_split_bytes(int rows, int MP);
 // the blocks are then kept in pieces of bf16.
 hipError_t launch_rebuild_split(const float* top, const NewBlocks& nw, int nfill, const void* Mc3, float* out, int out_NP, int MP,
                                 const Dims& d, hipStream_t st, bool new_one = false, const int* hole = nullptr);
+// KP rows of a basis (mode: CoeffArgs) from those that the last shrink wrote, nothing else being in the buffer
+hipError_t launch_basis_rows(const float* top, const double* known, int k, int mode, float* out, int KP, const Dims& d, hipStream_t st);
 
 // score.hip
 struct ScorePlan {
