@@ -1114,6 +1114,134 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, 
     C[(int64_t)gc * NP + gr] = s;
 }
 
+// ---- 64 buffer rows: the Gram matrix, and with it the rebuild of the shrink before ---------------------------------
+// top x top, new x top and new x new of [top; next], or (REBUILD, where the next block's rows are in the other half already: the
+// reduction's launch has stored them) of [M [top; nw]; next], whose first rows are formed and stored on the way: the wave that forms the
+// new top rows of 32 columns multiplies them there and then. Their product is formed transposed, which leaves a lane row l % 32 of the
+// result at the columns 8 q + 4 h + j, q, j < 4: four stores of 16 bytes, and, one column of either h a step, the operand that a contraction
+// over the columns takes; rows that are loaded come in the same order. No LDS but for the sums at the end, the coefficients stay in
+// registers, and a wave goes through its units with the next one's rows on their way. The bits of the Gram matrix are the same
+// either way. HS: stages of 16 rows of a half in use.
+// Bound by memory where rows are long: with the rebuild 1.05 GB at 2,049,000 columns in 215 us, where a kernel for each took 130 and (all
+// four blocks, through LDS) 190; by the launch where they are short (512 columns: 6.2 us, were 5.2 and 4.9). In between the two are
+// even (51,300: a unit for each wave, 12.8 us for 7.5 and 6.3). 17 blocks of 32 rows: 11.1 -> 8.1 ms at 2,049,000, 3.85 -> 3.30 at
+// 524,288; 64 of 512 columns: 5.39 -> 5.24.
+template <int HS, bool REBUILD>
+__global__ __launch_bounds__(256, 2) void gram64_kernel(std::conditional_t<REBUILD, float, const float>* top, int top_rows,
+                                                        const float* __restrict__ nw, const float* __restrict__ next, int rows,
+                                                        const float* __restrict__ Mc, float* __restrict__ partial, int64_t S, int64_t units) {
+    constexpr int LP = 32, K = REBUILD ? 8 * HS : 1;  // steps of two rows of a half
+    __shared__ float sums[4][48][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, h = lane >> 5;
+    f32x4 m[2][HS][2];  // coefficients of the top's and of the block's stages for row c of the result (see coeff_offset)
+    if constexpr (REBUILD) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int g = 0; g < HS; ++g)
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+                    m[b][g][p] = reinterpret_cast<const f32x4*>(Mc)[(2 * b + g) * (16 * LP / 4) + (h * LP + c) * 2 + (p ^ ((c >> 3) & 1))];
+    }
+    struct Rows {
+        float t[K], b[K];  // REBUILD: rows 2 s + h of column c of the unit: top, block;
+        f32x4 o[4];        // otherwise row c of the top at columns 8 q + 4 h ..
+        f32x4 n[4];        // row c of the next block there
+    };
+    const int nrow = row_in_use(c, rows), trow = row_in_use(c, top_rows);
+    auto fetch = [&](int64_t u, Rows& r) __attribute__((always_inline)) {
+        const int64_t s0 = 2 * (u < units ? u : units - 1), s1 = s0 + 1 < S ? s0 + 1 : s0;  // (beyond the end: repeated, not used)
+        if constexpr (REBUILD) {
+            const int64_t col = ((c < 16 ? s0 : s1) * LP + h) * DC + (c & 15);
+#pragma unroll
+            for (int s = 0; s < K; ++s) r.t[s] = top[col + 2 * s * DC];
+#pragma unroll
+            for (int s = 0; s < K; ++s) r.b[s] = nw[col + 2 * s * DC];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t at = (q < 2 ? s0 : s1) * LP * DC + 8 * (q & 1) + 4 * h;
+            if constexpr (!REBUILD) r.o[q] = *reinterpret_cast<const f32x4*>(top + at + trow * DC);
+            r.n[q] = *reinterpret_cast<const f32x4*>(next + at + nrow * DC);
+        }
+    };
+    f32x16 tt, nt, nn;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tt[i] = nt[i] = nn[i] = 0.f;
+    auto unit = [&](int64_t u, Rows& r) __attribute__((always_inline)) {
+        const bool both = 2 * u + 1 < S;  // (wave-uniform) the second slab is there
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = REBUILD || c >= top_rows ? 0.f : r.o[i >> 2][i & 3];
+        if constexpr (REBUILD) {
+#pragma unroll
+            for (int s = 0; s < K; ++s) acc = mfma32(r.t[s], m[0][s >> 3][s >> 2 & 1][s & 3], acc);
+#pragma unroll
+            for (int s = 0; s < K; ++s) acc = mfma32(2 * s + h < rows ? r.b[s] : 0.f, m[1][s >> 3][s >> 2 & 1][s & 3], acc);
+        }
+        float x[16];  // of the next block
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const bool there = i < 8 || both;
+            x[i] = there && c < rows ? r.n[i >> 2][i & 3] : 0.f;
+            acc[i] = there ? acc[i] : 0.f;
+        }
+        if constexpr (REBUILD) {
+            if (c < 16 * HS) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (q < 2 || both)
+                        *reinterpret_cast<f32x4*>(top + ((2 * u + (q >> 1)) * LP + c) * DC + 8 * (q & 1) + 4 * h) =
+                            f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            nn = mfma32(x[i], x[i], nn);
+            nt = mfma32(x[i], acc[i], nt);
+            tt = mfma32(acc[i], acc[i], tt);
+        }
+    };
+    const int64_t stride = (int64_t)gridDim.x * 4, u0 = (int64_t)blockIdx.x * 4 + wave;
+    if (u0 < units) {
+        Rows ra, rb;
+        fetch(u0, ra);
+        for (int64_t u = u0; u < units; u += 2 * stride) {
+            fetch(u + stride, rb);
+            unit(u, ra);
+            if (u + stride >= units) break;
+            fetch(u + 2 * stride, ra);
+            unit(u + stride, rb);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        sums[wave][i][lane] = tt[i];
+        sums[wave][16 + i][lane] = nt[i];
+        sums[wave][32 + i][lane] = nn[i];
+    }
+    __syncthreads();
+    float* const out = partial + (int64_t)blockIdx.x * 4096;  // a 64 x 64 tile, of which the reduction reads the lower triangle
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        const int i = 4 * k + wave, e = i & 15;
+        const float s = (float)(((double)sums[0][i][lane] + (double)sums[1][i][lane]) +
+                                ((double)sums[2][i][lane] + (double)sums[3][i][lane]));  // (rounded once)
+        const int row = 8 * (e >> 2) + 4 * h + (e & 3) + (i < 16 ? 0 : LP), col = c + (i < 32 ? 0 : LP);
+        out[row * 64 + col] = s;
+    }
+}
+
+hipError_t launch_rebuild_gram(float* top, const float* nw, const float* next, const float* Mc, float* partial, const GramPlan& p,
+                               const Dims& d, hipStream_t st) {
+    if (d.NP != 64 || p.mode != 0 || p.t0 != 0) return hipErrorInvalidValue;
+    const auto kern = d.ell <= 16 ? gram64_kernel<1, true> : gram64_kernel<2, true>;
+    hipLaunchKernelGGL(kern, dim3(p.groups), dim3(256), 0, st, top, d.LP, nw, next, d.ell, Mc, partial, d.S, (d.S + 1) / 2);
+    return hipGetLastError();
+}
+
 // wg_per_cu = 2 fills the chip. wg_per_cu = 1 is for the launch that shares the chip with the eigensolve (side stream): it
 // leaves an eighth of the CUs, an XCD, to the eigensolve's reduction (see spare_unit_at).
 GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_per_cu) {
@@ -1138,11 +1266,15 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
     int g = (wg_per_cu * cus / p.wg_per_group) / 8 * 8;
     if (g < 8) g = 8;
     // At least 4 slabs per group so that small problems do not drown in partial tiles; 2 where there are so few slabs that
-    // the chain of loads of a group is what counts (64 rows x 512 columns: 9.3 us -> 5).
+    // the chain of loads of a group is what counts.
     const int64_t least = d.S <= 256 ? 2 : 4;
     int64_t gmax = ((d.S + least - 1) / least + 7) / 8 * 8;
     if (gmax < 8) gmax = 8;
     if (g > gmax) g = (int)gmax;
+    if (P == 1) {  // gram64_kernel: a wave takes units of two slabs
+        const int64_t wgs = ((d.S + 1) / 2 + 3) / 4;
+        g = wgs < (int64_t)wg_per_cu * num_cu ? (int)wgs : wg_per_cu * num_cu;
+    }
     p.groups = g;
     p.slabs_per_group = (d.S + g - 1) / g;
     p.partial_floats = (size_t)g * p.tiles * 4096;
@@ -1245,6 +1377,12 @@ hipError_t launch_gram_tops(const GramTops& tops, int count, const float* nw, in
         hipLaunchKernelGGL(gram_new8_kernel, grid, dim3(256), 32768, st, nw, nfill, partial, d.S, p.slabs_per_group);
         return hipGetLastError();
     }
+    if (d.NP == 64) {
+        if (p.mode != 0 || count != 1 || hole) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((gram64_kernel<2, false>), grid, dim3(256), 0, st, top, tops.rows, nullptr, nw, nfill, nullptr, partial, d.S,
+                           (d.S + 1) / 2);
+        return hipGetLastError();
+    }
     switch (d.NP / 64) {
 #define SAGE_GRAM_CASE(PP)                                                                                          \
     case PP: {                                                                                                      \
@@ -1253,7 +1391,6 @@ hipError_t launch_gram_tops(const GramTops& tops, int count, const float* nw, in
         hipLaunchKernelGGL(kern, dim3((unsigned)spare_grid_at(grid.x, hole), count), dim3(256), lds, st, tops, nw, nfill,   \
                            partial, p.mode, p.t0, p.tiles, p.wg_per_group, d.S, p.slabs_per_group, (int)grid.x, hole);  \
     } break;
-        SAGE_GRAM_CASE(1)
         SAGE_GRAM_CASE(2)
         SAGE_GRAM_CASE(4)
         SAGE_GRAM_CASE(8)

@@ -160,6 +160,10 @@ hipError_t launch_gram_reduce(const float* partial_a, const GramPlan& a, const f
                               double* C, bool known_top, const double* known, const Dims& d, hipStream_t st,
                               const float* partial_top = nullptr, const GramPlan* top = nullptr, hipEvent_t done = nullptr);
 
+// NP = 64: top <- M [top; nw], and the partial tiles of the Gram matrix of [top; next], ell rows each, by the plan of the whole triangle.
+hipError_t launch_rebuild_gram(float* top, const float* nw, const float* next, const float* Mc, float* partial, const GramPlan& p,
+                               const Dims& d, hipStream_t st);
+
 // Rows to be stored into a half, from its row 0 on, as fp32, by a launch of the eigensolve (NP = 64): a row-major batch G, or factors.
 struct RowJob {
     const void *G, *E, *H;

@@ -84,6 +84,43 @@ def test_wide_cycles_against_64_bits(ell, D, dtype, decades, factor):
     s.close()
 
 
+# 64 buffer rows: the rebuild forms the next shrink's Gram matrix as well. Sketch sizes that fill one or both stages of 16 rows and that
+# do not; one column, a wave's 32 with and without a second slab, more units than waves.
+@pytest.mark.parametrize("ell,D,dtype", [(2, 1, "f32"), (16, 16, "f32"), (16, 4099, "bf16"), (17, 33, "f32"), (17, 48, "bf16"), (31, 1040, "f32"),
+                                         (32, 65, "bf16"), (32, 131_089, "f32"), (15, 200_007, "f32"), (32, 262_144, "bf16")])
+@pytest.mark.parametrize("decades,factor", [(0, 1.0), (14, 1e-9)])
+def test_cycles_of_64_buffer_rows_against_64_bits(ell, D, dtype, decades, factor):
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(D + ell + decades)
+    n = 5 * ell
+    G = torch.randn(n, D, generator=g, device="cuda")
+    G *= factor * 10.0 ** (-decades * torch.rand(n, 1, generator=g, device="cuda"))
+    G[2 * ell + 1] = 0.0
+    G[4 * ell, :D - 1] = 0.0
+    G = G.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    E = G[:ell].double()
+    for c in range(1, 5):
+        E = _shrink(torch.cat([E, G[c * ell:(c + 1) * ell].double()]), ell, torch)
+    J = torch.ones(2 * ell, 1, dtype=torch.float64, device="cuda")
+    J[ell:] = -1.0
+    for cuts in ([n], [ell + ell // 2, n - ell - ell // 2], [2 * ell, 2 * ell, ell]):
+        s = Sage(ell, D, dtype=dtype)
+        lo = 0
+        for rows in cuts:
+            s.fd_update(G[lo:lo + rows])
+            lo += rows
+        B = s.sketch().double()[:ell]
+        assert bool(torch.isfinite(B).all())
+        P = torch.cat([B, E])                            # (as above)
+        K = P @ P.T
+        err = float(((J * K) @ (J * K)).trace().clamp(min=0).sqrt())
+        assert err <= _bar(ell, D, decades) * float((G.double() ** 2).sum())
+        s.close()
+
+
 @pytest.mark.parametrize("ell,D", [(129, 131_072), (256, 262_147)])
 def test_wide_rows_have_the_same_gram_blocks_however_the_stream_is_cut(ell, D):
     """Rows stored ahead of their shrink and rows that are not go through the same arithmetic: with all that is not zero in 16
