@@ -162,11 +162,13 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
 }
 
 // ---- pairs in closed form and merges of 4 .. 64 rows, one work-group per 64 x 64 diagonal block ----------------------
-// 512 threads: 8 lanes per index, a sub-problem of M rows per 8 M threads. All arrays of the block in LDS; Q column-major.
-// A merge is a chain of short phases between barriers; half the time goes into the roots, which is why their loops are
+// Merges up to 16 rows: 16 rows and four lanes per index to each of the first four waves, no barrier (dc_level_wave). Those of 32
+// and 64: 512 threads, 8 lanes per index, a sub-problem of M rows per 8 M threads. All arrays of the block in LDS; Q column-major.
+// A merge is a chain of short phases; half the time goes into the roots, which is why their loops are
 // unrolled to what M needs, and the products of 16 rows and more run on the matrix cores (in scalar code, bound by LDS
-// reads, the last product alone took 17 us). 32 us in all (38 with the roots' cases told apart by branches and quadratic
-// steps; 30 with the roots started nearby), against 104 us for one loop over all sizes.
+// reads, the last product alone took 17 us). A merge of 4, 8, 16, 32, 64 rows takes 6.0, 6.7, 8.5, 13 and 15 thousand cycles (the first three
+// with barriers between their phases: 8.3, 9.4 and 11.5). 28 us in all (38 with the roots' cases told apart by branches and quadratic
+// steps; 30.7 with barriers in all merges), against 104 us for one loop over all sizes.
 constexpr int DCB_LD = 65;   // columns of Q
 constexpr int DCB_LDU = 68;  // columns of U: the 16 columns x 4 rows of a matrix-core operand fall on distinct banks
 struct DcBlockLds {
@@ -180,9 +182,67 @@ struct DcBlockLds {
     int any;
 };
 
+// The K survivors of the sub-problem at bb, in order: equal poles are rotated together, one of each group stays. nrot rotations are left to be
+// applied to the columns.
+__device__ __forceinline__ void rotate_equal_poles(DcBlockLds& S, int bb, int K, double tol) {
+    int nk = 0, nr = 0, pc = -1;
+    double pd = 0.0, pz = 0.0;
+    for (int q = 0; q < K; ++q) {
+        double nd = S.dk[bb + q], nz = S.zk[bb + q];
+        const int nc = S.col[bb + q];
+        if (pc >= 0) {
+            if (poles_equal(pd, pz, nd, nz, tol)) {
+                const double t = __builtin_sqrt(pz * pz + nz * nz), c = nz / t, s = -pz / t;
+                S.td[bb + nr] = pd * c * c + nd * s * s;
+                S.tc[bb + nr] = pc;
+                nd = pd * s * s + nd * c * c;
+                nz = t;
+                S.ra[bb + nr] = pc;
+                S.rb[bb + nr] = nc;
+                S.rc[bb + nr] = c;
+                S.rs[bb + nr] = s;
+                ++nr;
+            } else {
+                S.dk[bb + nk] = pd;
+                S.zk[bb + nk] = pz;
+                S.col[bb + nk] = pc;
+                ++nk;
+            }
+        }
+        pd = nd;
+        pz = nz;
+        pc = nc;
+    }
+    if (pc >= 0) {
+        S.dk[bb + nk] = pd;
+        S.zk[bb + nk] = pz;
+        S.col[bb + nk] = pc;
+        ++nk;
+    }
+    for (int q = 0; q < nr; ++q) {  // nk + nr == K
+        S.dk[bb + nk + q] = S.td[bb + q];
+        S.zk[bb + nk + q] = 0.0;
+        S.col[bb + nk + q] = S.tc[bb + q];
+    }
+    S.K[bb] = nk;
+    S.nrot[bb] = nr;
+}
+// ... and they are, in row i
+__device__ __forceinline__ void rotate_columns(DcBlockLds& S, int bb, int i) {
+    const int nr = S.nrot[bb];
+    for (int q = 0; q < nr; ++q) {
+        double* A = S.Q + S.ra[bb + q] * DCB_LD + i;
+        double* B = S.Q + S.rb[bb + q] * DCB_LD + i;
+        const double a = *A, b = *B, c = S.rc[bb + q], s = S.rs[bb + q];
+        *A = c * a + s * b;
+        *B = c * b - s * a;
+    }
+}
+
 template <int M, bool WIDE>
 __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
-    constexpr int H = M / 2, E = M > 8 ? M / 8 : 1, EH = H > 8 ? H / 8 : 1;
+    static_assert(M == 32 || M == 64, "smaller ones: dc_level_wave");
+    constexpr int H = M / 2, E = M / 8, EH = H / 8;
     const int i = tid >> 3, l = tid & 7;
     const int base = i & ~(M - 1), li = i & (M - 1);
     const double ec = S.e[base + H - 1], rho = fabs(ec);
@@ -196,8 +256,8 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
 #pragma unroll
         for (int e = 0; e < EH; ++e) {
             const int j = l + 8 * e;
-            const double x = S.d[o + (j & (H - 1))];
-            cnt += j < H && (x < di || (x == di && li >= H)) ? 1 : 0;
+            const double x = S.d[o + j];
+            cnt += (x < di || (x == di && li >= H)) ? 1 : 0;
         }
         cnt = lane_sum_i<8>(cnt) + (li < H ? li : li - H);
         if (l == 0) {
@@ -227,7 +287,7 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
     {
         const int before = __popcll(sub & ((1ull << li) - 1ull));
         const int pos = live ? before : K + li - before;
-        if (M >= 32 && l == 1) {
+        if (l == 1) {
             const unsigned long long alll = *reinterpret_cast<const unsigned long long*>(S.maskl);
             const unsigned long long ones = M == 64 ? ~0ull : (1ull << (M & 63)) - 1ull, below = (1ull << li) - 1ull;
             const unsigned long long subl = (M == 64 ? alll : alll >> base) & ones;
@@ -250,61 +310,9 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
     }
     __syncthreads();
     if (S.any) {  // rare: walk the survivors in order, rotate equal poles together
-        if (tid < 64 && (tid & (M - 1)) == 0) {
-            const int bb = tid, Kb = S.K[bb];
-            int nk = 0, nr = 0, pc = -1;
-            double pd = 0.0, pz = 0.0;
-            for (int q = 0; q < Kb; ++q) {
-                double nd = S.dk[bb + q], nz = S.zk[bb + q];
-                const int nc = S.col[bb + q];
-                if (pc >= 0) {
-                    if (poles_equal(pd, pz, nd, nz, tol)) {
-                        const double t = __builtin_sqrt(pz * pz + nz * nz), c = nz / t, s = -pz / t;
-                        S.td[bb + nr] = pd * c * c + nd * s * s;
-                        S.tc[bb + nr] = pc;
-                        nd = pd * s * s + nd * c * c;
-                        nz = t;
-                        S.ra[bb + nr] = pc;
-                        S.rb[bb + nr] = nc;
-                        S.rc[bb + nr] = c;
-                        S.rs[bb + nr] = s;
-                        ++nr;
-                    } else {
-                        S.dk[bb + nk] = pd;
-                        S.zk[bb + nk] = pz;
-                        S.col[bb + nk] = pc;
-                        ++nk;
-                    }
-                }
-                pd = nd;
-                pz = nz;
-                pc = nc;
-            }
-            if (pc >= 0) {
-                S.dk[bb + nk] = pd;
-                S.zk[bb + nk] = pz;
-                S.col[bb + nk] = pc;
-                ++nk;
-            }
-            for (int q = 0; q < nr; ++q) {  // nk + nr == Kb
-                S.dk[bb + nk + q] = S.td[bb + q];
-                S.zk[bb + nk + q] = 0.0;
-                S.col[bb + nk + q] = S.tc[bb + q];
-            }
-            S.K[bb] = nk;
-            S.nrot[bb] = nr;
-        }
+        if (tid < 64 && (tid & (M - 1)) == 0) rotate_equal_poles(S, tid, S.K[tid], tol);
         __syncthreads();
-        if (l == 0) {
-            const int nr = S.nrot[base];
-            for (int q = 0; q < nr; ++q) {
-                double* A = S.Q + S.ra[base + q] * DCB_LD + i;
-                double* B = S.Q + S.rb[base + q] * DCB_LD + i;
-                const double a = *A, b = *B, c = S.rc[base + q], s = S.rs[base + q];
-                *A = c * a + s * b;
-                *B = c * b - s * a;
-            }
-        }
+        if (l == 0) rotate_columns(S, base, i);
         K = S.K[base];
         __syncthreads();
     }
@@ -346,18 +354,18 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int j = l + 8 * e;
-        dj[e] = j < K ? S.dk[base + (j & (M - 1))] : 1e30;
+        dj[e] = j < K ? S.dk[base + j] : 1e30;
     }
     {
         double og[E], ta[E];
         int np = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int j = l + 8 * e, jj = base + (j & (M - 1));
+            const int j = l + 8 * e, jj = base + j;
             og[e] = S.org[jj];
             ta[e] = S.tau[jj];
             const double x = S.val[jj];
-            np += j < M && (x < val || (x == val && j < li)) ? 1 : 0;
+            np += x < val || (x == val && j < li) ? 1 : 0;
         }
         np = lane_sum_i<8>(np);
         const double zz = secular_z<8, E>(K, li, l, dki, dj, og, ta);
@@ -373,7 +381,7 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int j = l + 8 * e;
-            u[e] = j < K ? S.zh[base + (j & (M - 1))] * rcp64((dj[e] - org) - tau) : 0.0;
+            u[e] = j < K ? S.zh[base + j] * rcp64((dj[e] - org) - tau) : 0.0;
             nn = __builtin_fma(u[e], u[e], nn);
         }
         nn = lane_sum<8>(nn);
@@ -381,61 +389,206 @@ __device__ __forceinline__ void dc_level(DcBlockLds& S, int tid, double tol) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int j = l + 8 * e;
-            if (j < M) S.U[i * DCB_LDU + j] = li < K ? u[e] * nn : (j == li ? 1.0 : 0.0);
+            S.U[i * DCB_LDU + j] = li < K ? u[e] * nn : (j == li ? 1.0 : 0.0);
         }
     }
     __syncthreads();
-    if constexpr (M >= 16) {
-        constexpr int T = M / 16, TILES = (64 / M) * T * T, PER = TILES > 8 ? TILES / 8 : 1;
-        // The columns of Q are still those of the halves: a row tile meets the H of its own half, unless rotations mixed them.
-        const bool dense = M == 16 || S.any != 0;  // (a tile of 16 rows spans both halves of 16)
-        const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lk = lane >> 4;
-        f64x4 acc[PER];
+    constexpr int T = M / 16, TILES = (64 / M) * T * T, PER = TILES > 8 ? TILES / 8 : 1;
+    // The columns of Q are still those of the halves: a row tile meets the H of its own half, unless rotations mixed them.
+    const bool dense = S.any != 0;
+    const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lk = lane >> 4;
+    f64x4 acc[PER];
 #pragma unroll
-        for (int g = 0; g < PER; ++g) {
-            acc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
-            const int t = wave + 8 * g;
-            if (t < TILES) {
-                const int sb = (t / (T * T)) * M, r0 = sb + ((t / T) % T) * 16, c0 = sb + (t % T) * 16;
-                if (!dense) {
-                    const int half = (r0 - sb) & H;
+    for (int g = 0; g < PER; ++g) {
+        acc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
+        const int t = wave + 8 * g;
+        if (t < TILES) {
+            const int sb = (t / (T * T)) * M, r0 = sb + ((t / T) % T) * 16, c0 = sb + (t % T) * 16;
+            if (!dense) {
+                const int half = (r0 - sb) & H;
 #pragma unroll
-                    for (int k = 0; k < H; k += 4) {
-                        const int j = S.lst[sb + half + k + lk];
-                        const double av = S.Q[S.col[sb + j] * DCB_LD + r0 + l16];
-                        acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + j], acc[g]);
-                    }
-                } else {
+                for (int k = 0; k < H; k += 4) {
+                    const int j = S.lst[sb + half + k + lk];
+                    const double av = S.Q[S.col[sb + j] * DCB_LD + r0 + l16];
+                    acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + j], acc[g]);
+                }
+            } else {
 #pragma unroll 4
-                    for (int k = 0; k < M; k += 4) {
-                        const double av = S.Q[S.col[sb + k + lk] * DCB_LD + r0 + l16];
-                        acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + k + lk], acc[g]);
-                    }
+                for (int k = 0; k < M; k += 4) {
+                    const double av = S.Q[S.col[sb + k + lk] * DCB_LD + r0 + l16];
+                    acc[g] = mfma64(av, S.U[(c0 + l16) * DCB_LDU + k + lk], acc[g]);
                 }
             }
         }
-        __syncthreads();
-#pragma unroll
-        for (int g = 0; g < PER; ++g) {
-            const int t = wave + 8 * g;
-            if (t < TILES) {
-                const int sb = (t / (T * T)) * M, r0 = sb + ((t / T) % T) * 16, c0 = sb + (t % T) * 16;
-                double* o = S.Q + S.np[c0 + l16] * DCB_LD + r0 + lk;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) o[4 * v] = acc[g][v];
-            }
-        }
-    } else {
-        double out = 0.0;
-        if (l < M) {
-#pragma unroll
-            for (int j = 0; j < M; ++j)
-                out = __builtin_fma(S.Q[S.col[base + j] * DCB_LD + base + l], S.U[i * DCB_LDU + j], out);
-        }
-        __syncthreads();
-        if (l < M) S.Q[S.np[i] * DCB_LD + base + l] = out;
     }
     __syncthreads();
+#pragma unroll
+    for (int g = 0; g < PER; ++g) {
+        const int t = wave + 8 * g;
+        if (t < TILES) {
+            const int sb = (t / (T * T)) * M, r0 = sb + ((t / T) % T) * 16, c0 = sb + (t % T) * 16;
+            double* o = S.Q + S.np[c0 + l16] * DCB_LD + r0 + lk;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o[4 * v] = acc[g][v];
+        }
+    }
+    __syncthreads();
+}
+
+// A merge of 4, 8 or 16 rows by a wave, the first four waves 16 rows of the block each, four lanes an index: the steps of dc_level, but
+// nothing goes from wave to wave, so there is no barrier. (The LDS takes a wave's instructions in their order.) Rotations are rare.
+__device__ __forceinline__ void wave_order() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+template <int M>
+__device__ __forceinline__ void dc_level_wave(DcBlockLds& S, int tid, double tol) {
+    static_assert(M == 4 || M == 8 || M == 16, "no more than a wave's rows");
+    constexpr int H = M / 2, E = M / 4, EH = H > 4 ? H / 4 : 1;
+    const int i = tid >> 2, l = tid & 3;
+    const int base = i & ~(M - 1), li = i & (M - 1);
+    const double ec = S.e[base + H - 1], rho = fabs(ec);
+    {
+        const double di = S.d[i];
+        double zi = li < H ? S.Q[i * DCB_LD + base + H - 1] : S.Q[i * DCB_LD + base + H];
+        zi = finite_or_zero(li >= H && ec < 0.0 ? -zi : zi);
+        const int o = base + (li < H ? H : 0);
+        int cnt = 0;
+#pragma unroll
+        for (int e = 0; e < EH; ++e) {
+            const int j = l + 4 * e;
+            const double x = S.d[o + (j & (H - 1))];
+            cnt += j < H && (x < di || (x == di && li >= H)) ? 1 : 0;
+        }
+        cnt = lane_sum_i<4>(cnt) + (li < H ? li : li - H);
+        if (l == 0) {
+            S.ds[base + cnt] = di;
+            S.zs[base + cnt] = zi;
+            S.cs[base + cnt] = i;
+        }
+    }
+    wave_order();
+    const double dsi = S.ds[i], zsi = S.zs[i];
+    const int csi = S.cs[i];
+    const bool live = rho * fabs(zsi) > tol;
+    const unsigned long long all = __ballot(live) & 0x1111111111111111ull;  // bit 4 q: index 16 wave + q
+    const unsigned long long sub = M == 16 ? all : (all >> (4 * (base & 15))) & ((1ull << ((4 * M) & 63)) - 1ull);
+    int K = __popcll(sub);
+    bool equal = false;
+    {
+        const int before = __popcll(sub & ((1ull << (4 * li)) - 1ull));
+        const int pos = live ? before : K + li - before;
+        const unsigned long long after = li == 15 ? 0ull : sub >> (4 * (li + 1));
+        if (live && after) {
+            const int nx = base + li + 1 + (__builtin_ctzll(after) >> 2);
+            equal = poles_equal(dsi, zsi, S.ds[nx], S.zs[nx], tol);
+        }
+        if (l == 0) {
+            S.dk[base + pos] = dsi;
+            S.zk[base + pos] = zsi;
+            S.col[base + pos] = csi;
+        }
+    }
+    wave_order();
+    if (__any(equal)) {
+        if (l == 0 && li == 0) rotate_equal_poles(S, base, K, tol);
+        wave_order();
+        if (l == 0) rotate_columns(S, base, i);
+        K = S.K[base];
+        wave_order();
+    }
+    double org, tau, val, dj[E];
+    const double dki = S.dk[i];
+    {
+        double rj[E], zj[E], zsum = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = l + 4 * e;
+            const bool on = j < K;
+            dj[e] = rj[e] = on ? S.dk[base + j] : 1e30;
+            const double z = on ? S.zk[base + j] : 0.0;
+            zj[e] = rho * z * z;
+            zsum += zj[e];
+        }
+        zsum = lane_sum<4>(zsum);
+        const bool has = li < K;
+        const int ip = base + lower_pole(li, K);
+        const double pn = S.dk[ip + (K > 1)], zi = S.zk[ip], zn = S.zk[ip + (K > 1)];
+        secular_root<4, E>(has, li >= K - 1, K, rj, zj, K > 1 ? S.dk[ip] : pn - 1.0, pn, K > 1 ? rho * zi * zi : 0.0, rho * zn * zn, zsum, org, tau);
+        val = has ? finite_or_zero(org + tau) : dki;
+        if (l == 0) {
+            S.org[i] = org;
+            S.tau[i] = tau;
+            S.val[i] = val;
+        }
+    }
+    wave_order();
+    {
+        double og[E], ta[E];
+        int np = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = l + 4 * e;
+            og[e] = S.org[base + j];
+            ta[e] = S.tau[base + j];
+            const double x = S.val[base + j];
+            np += x < val || (x == val && j < li) ? 1 : 0;
+        }
+        np = lane_sum_i<4>(np);
+        const double zz = secular_z<4, E>(K, li, l, dki, dj, og, ta);
+        if (l == 0) {
+            S.zh[i] = __builtin_copysign(zz, S.zk[i]);
+            S.np[i] = base + np;
+            S.d[base + np] = val;
+        }
+    }
+    wave_order();
+    {
+        double u[E], nn = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = l + 4 * e;
+            u[e] = j < K ? S.zh[base + j] * rcp64((dj[e] - org) - tau) : 0.0;
+            nn = __builtin_fma(u[e], u[e], nn);
+        }
+        nn = lane_sum<4>(nn);
+        nn = rcp64(__builtin_sqrt(nn));
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = l + 4 * e;
+            S.U[i * DCB_LDU + j] = li < K ? u[e] * nn : (j == li ? 1.0 : 0.0);
+        }
+    }
+    wave_order();
+    if constexpr (M == 16) {
+        const int lane = tid & 63, l16 = lane & 15, lk = lane >> 4;
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < M; k += 4) {
+            const double av = S.Q[S.col[(tid >> 6) * 16 + k + lk] * DCB_LD + (tid >> 6) * 16 + l16];
+            acc = mfma64(av, S.U[((tid >> 6) * 16 + l16) * DCB_LDU + k + lk], acc);
+        }
+        wave_order();
+        double* o = S.Q + S.np[(tid >> 6) * 16 + l16] * DCB_LD + (tid >> 6) * 16 + lk;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[4 * v] = acc[v];
+    } else {
+        double out[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) out[e] = 0.0;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const double uj = S.U[i * DCB_LDU + j];
+            const double* q = S.Q + S.col[base + j] * DCB_LD + base + l;
+#pragma unroll
+            for (int e = 0; e < E; ++e) out[e] = __builtin_fma(q[4 * e], uj, out[e]);
+        }
+        wave_order();
+        double* o = S.Q + S.np[i] * DCB_LD + base + l;
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[4 * e] = out[e];
+    }
+    wave_order();
 }
 
 // A work-group per diagonal block of 64. WITH_WY (N = 64): the work-group after it forms the triangular factors of the
@@ -485,9 +638,12 @@ __global__ __launch_bounds__(512, WITH_WY ? 1 : 4) void dc_block_kernel(const do
         S.Q[i * DCB_LD + (i | 1)] = first ? -ss : cc;
     }
     __syncthreads();
-    dc_level<4, WITH_WY>(S, tid, tol);
-    dc_level<8, WITH_WY>(S, tid, tol);
-    dc_level<16, WITH_WY>(S, tid, tol);
+    if (tid < 256) {
+        dc_level_wave<4>(S, tid, tol);
+        dc_level_wave<8>(S, tid, tol);
+        dc_level_wave<16>(S, tid, tol);
+    }
+    __syncthreads();
     dc_level<32, WITH_WY>(S, tid, tol);
     dc_level<64, WITH_WY>(S, tid, tol);
     if (l == 0) dO[b0 + i] = S.d[i];

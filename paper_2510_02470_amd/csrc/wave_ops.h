@@ -91,7 +91,7 @@ template <int L>
 __device__ __forceinline__ double lane_product(double v) {
     v *= dpp_move<DPP_XOR1>(v);
     v *= dpp_move<DPP_XOR2>(v);
-    v *= dpp_move<DPP_HALF_MIRROR>(v);
+    if constexpr (L >= 8) v *= dpp_move<DPP_HALF_MIRROR>(v);
     if constexpr (L >= 16) v *= dpp_move<DPP_MIRROR>(v);
     if constexpr (L == 64) {
         double a, b;
@@ -110,7 +110,7 @@ template <int L>
 __device__ __forceinline__ int lane_sum_i(int v) {
     v += dpp_move_i<DPP_XOR1>(v);
     v += dpp_move_i<DPP_XOR2>(v);
-    v += dpp_move_i<DPP_HALF_MIRROR>(v);
+    if constexpr (L >= 8) v += dpp_move_i<DPP_HALF_MIRROR>(v);
     if constexpr (L >= 16) v += dpp_move_i<DPP_MIRROR>(v);
     if constexpr (L == 64)
         v = (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
