@@ -49,6 +49,38 @@ def test_eigensolve_at_every_padded_size(ell):
         assert np.abs(np.sort(lam) - np.linalg.eigvalsh(C)).max() <= 1e-14 * scale, name
 
 
+@pytest.mark.parametrize("m", [4, 8, 16])
+@pytest.mark.parametrize("ell", [32, 64, 256])
+def test_small_merges_of_different_kinds_side_by_side(ell, m):
+    """Merges of 4, 8 and 16 rows share a wave: those that rotate equal poles together (a segment with one value on its diagonal and one
+    beside it: its halves have the same poles), those without survivors (nothing beside the diagonal) and ordinary ones, in every
+    order. The reduction leaves a tridiagonal matrix one. Bars as above."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    n = 2 * ell
+    rng = np.random.default_rng(n + m)
+    s = Sage(ell, 64)
+    for joined in (False, True):
+        d, e = 10.0 + rng.standard_normal(n), rng.standard_normal(n - 1)
+        for j in range(n // m):
+            kind, lo = rng.integers(3), j * m
+            if kind < 2:
+                d[lo:lo + m] = 10.0
+                e[lo:lo + m - 1] = kind
+            if not joined and lo:
+                e[lo - 1] = 0.0
+        C = np.diag(d) + np.diag(e, 1) + np.diag(e, -1)
+        Y, lam, _ = s.probe_eig_matrix(torch.from_numpy(C).cuda())
+        Y, lam = Y.cpu().numpy(), lam.cpu().numpy()
+        scale = np.abs(C).max() * n
+        assert np.abs(Y.T @ Y - np.eye(n)).max() <= 1e-13
+        assert np.abs((Y * lam) @ Y.T - C).max() <= 1e-14 * scale
+        assert np.abs(np.sort(lam) - np.linalg.eigvalsh(C)).max() <= 1e-14 * scale
+    s.close()
+
+
 def test_contexts_in_several_streams_share_the_gpu():
     """More contexts than XCDs, each on a stream of its own with work in flight at the same time: the reductions that keep
     work-groups of one XCD in step must not starve each other."""
