@@ -186,8 +186,7 @@ int sage_select_cb_ex(sage_ctx* ctx, double keep_rate, int n_classes, int rule, 
  * store_zhat = 0, sage_score only accumulates the consensus sum (rows are counted, nothing per row is kept), and a
  * further pass over the same rows in the same order, sage_rescore, recomputes zhat_i and writes alpha_i =
  * clamp(<zhat_i, u>, -1, 1) (4 bytes per row); sage_select then selects from those. The scores are bit-equal to the
- * stored run's where both passes cut the stream into the same batches (the size of a batch decides the order of a row's sums in
- * wide rows, and with it the last bits). store_zhat = 1 (the default) is the two-pass run. Either call resets the scoring pass.
+ * stored run's. store_zhat = 1 (the default) is the two-pass run. Either call resets the scoring pass.
  * In the store-free run: sage_score after the first sage_rescore, sage_rescore of more rows than were scored,
  * sage_select before every row has been rescored, sage_score_labeled / sage_select_cb and sage_zhat_export return
  * SAGE_ERR_STATE. G_batch: DEVICE, as for sage_score. Asynchronous on the context stream.

@@ -380,8 +380,6 @@ struct __attribute__((packed, aligned(sizeof(T)))) AnyPiece {
     u32x4 v;
 };
 
-// three parts: is memory the bound?
-constexpr bool any_wide(int dtype, int KP) { return KP <= (dtype == SAGE_BF16 ? 32 : 64); }
 template <int NT, typename T, int PARTS>
 struct AnyShape {
     static constexpr int IMG = PARTS * NT * 32 * (16 / (int)sizeof(T));  // 16-byte pieces of an image
@@ -474,9 +472,7 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     // own there, which the others, each a 256th of them or less, no longer round (zhat of 2048 rows of 51,300 fp32, 64 vectors, against
     // 64 bits: 3.9e-7 with sums half as long, 5.5e-7, 1.7e-7 with these; two parts, 512 of 1,048,576, 128 vectors: 2.06e-6, 2.17e-6,
     // 1.97e-6).
-    // (So have the batches of up to 256 rows of such shapes: where a split has no more than three windows, a row's sums have the same bits
-    // whatever the batch.)
-    constexpr int SETS = PARTS == 2 || any_wide(sizeof(T) == 2 ? SAGE_BF16 : SAGE_F32, 32 * NT) ? 2 : 1;
+    constexpr int SETS = CH;
     f32x16 acc[TILES][SETS][NT];
 #pragma unroll
     for (int t = 0; t < TILES; ++t)
@@ -659,6 +655,8 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
                 if (r < R) out[r * KP + ct * 32 + n] = SETS == 2 ? acc[t][0][ct][i] + acc[t][SETS - 1][ct][i] : acc[t][0][ct][i];
             }
 }
+// three parts: is memory the bound?
+constexpr bool any_wide(int dtype, int KP) { return KP <= (dtype == SAGE_BF16 ? 32 : 64); }
 
 // Any row start that is a multiple of the element, a row of at least one window, lane offsets of 32 bits.
 bool any_path_ok(const void* G, int dtype, const Dims& d) {
