@@ -279,7 +279,6 @@ struct ScorePlan {
     int row_tiles;    // ceil(R / 128)
     int splits;       // split-K over D
     int64_t slabs_per_split;
-    bool lines = false;  // project_split_kernel, whose windows are lines of memory
     // factored rows only: the splits form a grid of class groups x feature-window groups
     int class_groups = 0, classes_per_group = 0, window_groups = 0, windows_per_group = 0;
     int bias_slots = 0, classes_per_bias_slot = 0;  // ... followed by the slots of the bias columns

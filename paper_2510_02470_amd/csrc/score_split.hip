@@ -9,7 +9,8 @@
 // v_mfma_f32_32x32x16_bf16. The error against an fp32 product is a few 2^-17 relative per term, below the fp32
 // accumulation error over D ~ 1e6 terms.
 //
-// Work-group = 512 threads = 8 waves, one work-group per CU. A wave owns 32 or 64 batch rows x KP basis columns. Its rows are loaded whole memory lines at a time and turned to the matrix cores' order through LDS of
+// Work-group = 512 threads = 8 waves, one work-group per CU. A wave owns 64 batch rows x KP basis columns (2 x KP/32
+// accumulator tiles). Its rows are loaded whole memory lines at a time and turned to the matrix cores' order through LDS of
 // the wave's own (nobody else needs them); the basis operand is shared by the waves and is streamed through LDS with direct
 // global->LDS loads. The basis is kept in HBM as "images": for each chunk of KC columns exactly the bytes LDS will hold,
 // so staging is a linear copy.
@@ -112,13 +113,9 @@ __device__ __forceinline__ void split8(const u32x4& x0, const u32x4& x1, u32x4& 
     }
 }
 
-// Batches of more than 256 bf16 rows with more than 64 vectors, of many windows to a split: the matrix cores, as far as the clock holds
-// under this load, and the reads of the basis operands from LDS are the bound there, and a wave has 64 rows for each of these
-// (1024 rows of 1,000,000: 520 us; 560 with project_any_kernel, which is better everywhere else, see score_split_plan).
-//
-// Rows of a batch are 2 D bytes apart, which in general is not a multiple of the 128-byte memory line, so a
+// Rows of a batch are D * sizeof(T) bytes apart, which in general is not a multiple of the 128-byte memory line, so a
 // row's k-th 128 bytes straddle two lines and a kernel that walks every row in steps of 128 bytes from the row
-// start fetches many lines twice. Here a wave only holds rows whose start addresses are congruent modulo 128 (rows
+// start fetches most lines twice. Here a wave only holds rows whose start addresses are congruent modulo 128 (rows
 // w, w + 8, w + 16, ... of the work-group's 512: 8 * pitch is a multiple of 128 because the pitch is a multiple of 16)
 // and walks them in line-aligned windows: with phi = (row address mod 128) / (bytes of 8 columns), window m of the
 // wave is the 128 bytes that start 8*phi columns before column m*KC. Its basis operand is then the last phi pieces
@@ -130,13 +127,16 @@ __device__ __forceinline__ void split8(const u32x4& x0, const u32x4& x1, u32x4& 
 // Work-group = 512 threads = 8 waves (two per SIMD), one per CU, 512 batch rows x KP basis columns; a wave owns 64
 // rows (2 accumulator row tiles) x KP columns. The rows of window m+2 are requested into registers during window m and
 // turned at the start of window m+2; images are streamed with direct global->LDS loads, also two windows ahead.
+template <typename T>
 struct RowOp {
-    u32x4 v[4];  // v[j] = k-step j
+    u32x4 v[4];  // bf16 rows: v[j] = k-step j; fp32 rows: v[2j], v[2j+1] = k-step j
 };
 // Rows are loaded eight lanes to the 128 bytes of a row, and turned to the matrix cores' order through LDS, 32 rows (4 KB) at a
 // time in memory of the wave's own. (Loaded in that order, a row a lane and 16 bytes at a time, a line was asked for in
-// four instructions while it was still on its way, which the vector cache waits for: it stalled 35% of the cycles; 1024 rows of
-// 2,049,000: 1073 us, now 1026.)
+// four instructions while it was still on its way, which the vector cache waits for: it stalled 71% of the cycles at fp32
+// rows of 1,048,576 columns and 35% at bf16 rows of 2,049,000, and half of the former's lines were fetched from L2 twice. 512
+// such fp32 rows with 128 vectors: 945 us, now 629; 1024 such bf16 rows: 1073, now 1026, where the matrix cores' rate, as far
+// as the clock holds under this load, is the bound: 1.07 PFLOP.)
 struct RowRaw {
     u32x4 v[4];  // v[x]: piece lane % 8 of row 8 x + lane / 8
 };
@@ -145,37 +145,42 @@ struct RowRaw {
 struct TurnAt {
     unsigned w0, w1, r;  // bytes: stores of even and odd x, loads
 };
+template <typename T>
 __device__ __forceinline__ TurnAt turn_at(int piece0, int lane) {
     const int row = lane >> 3, s = lane & 7, n = lane & 31, h = lane >> 5;
     TurnAt at;
     at.w0 = (unsigned)(piece0 + row * 8 + (s ^ (row >> 1))) * 16;
     at.w1 = (unsigned)(piece0 + row * 8 + (s ^ (4 + (row >> 1)))) * 16;
-    at.r = (unsigned)(piece0 + n * 8 + (h ^ ((n >> 1) & 7))) * 16;
+    at.r = (unsigned)(piece0 + n * 8 + ((sizeof(T) == 2 ? h : 2 * h) ^ ((n >> 1) & 7))) * 16;
     return at;
 }
-template <int TILES>
-__device__ __forceinline__ void turn_rows(u32x4* lds, TurnAt at, const RowRaw (&raw)[TILES], RowOp (&a)[TILES]) {
+template <int TILES, int LX, typename T>
+__device__ __forceinline__ void turn_rows(u32x4* lds, TurnAt at, const RowRaw (&raw)[TILES], RowOp<T> (&a)[TILES]) {
     char* const m = reinterpret_cast<char*>(lds);
     asm volatile("" : "+v"(at.r));  // (the loads' addresses are formed here, not kept)
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) *reinterpret_cast<u32x4*>(m + (x & 1 ? at.w1 : at.w0) + x * 1024) = raw[t].v[x];
+        for (int x = 0; x < LX; ++x) *reinterpret_cast<u32x4*>(m + (x & 1 ? at.w1 : at.w0) + x * 1024) = raw[t].v[x];
         asm volatile("" ::: "memory");  // (a wave's LDS accesses keep their order)
 #pragma unroll
-        for (int x = 0; x < 4; ++x) a[t].v[x] = *reinterpret_cast<const u32x4*>(m + (at.r ^ (unsigned)(2 * x * 16)));
+        for (int x = 0; x < 4; ++x) {
+            const unsigned p = sizeof(T) == 2 ? 2 * x : 4 * (x >> 1) + (x & 1);
+            a[t].v[x] = *reinterpret_cast<const u32x4*>(m + (at.r ^ (p * 16)));
+        }
         asm volatile("" ::: "memory");
     }
 }
-__global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* __restrict__ G, int64_t R,
+template <int NT, typename T, int NL>  // NT = KP / 32; NL: see loads_of
+__global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restrict__ G, int64_t R,
                                                                const u32x4* __restrict__ img,
                                                                float* __restrict__ partial, int row_tiles, int64_t D,
                                                                int64_t chunks_total, int64_t chunks_per_split) {
-    constexpr int NT = 4, KP = NT * 32;
-    constexpr int TILES = 2, LX = 4, NL = TILES * LX;  // row tiles of a wave, row loads of a tile and window
-    constexpr int KC = 64;
+    constexpr int KP = NT * 32;
+    constexpr int TILES = NL > 4 ? 2 : 1, LX = NL > 4 ? 4 : NL;  // row tiles of a wave, row loads of a tile and window
+    constexpr int KC = 128 / (int)sizeof(T);
     constexpr int PPR = KC / 8;        // pieces (8 columns) per window
-    constexpr int PB = 16;             // bytes of a piece in a row
+    constexpr int PB = 8 * (int)sizeof(T);  // bytes of a piece in a row: 16 or 32
     constexpr int IMG = 2 * KP * PPR;  // 16-byte pieces per image
     constexpr int KS = KC / 16;        // matrix-core k-steps per window
     extern __shared__ u32x4 lds[];     // 4 * IMG, then 256 pieces of each wave
@@ -193,7 +198,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
-    const int64_t S = D * 2;  // row pitch in bytes
+    const int64_t S = D * (int64_t)sizeof(T);  // row pitch in bytes
     const int64_t row0 = (int64_t)rt * 512;
     // phase of this wave's rows, in pieces
     const int phi = (int)(((reinterpret_cast<uintptr_t>(G) + (uintptr_t)((row0 + wave) * S)) & 127) / PB);
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
             a.v[x] = *reinterpret_cast<const u32x4*>(gbase + o);
         }
     };
-    const TurnAt turn = turn_at(4 * IMG + wave * 256, lane);
+    const TurnAt turn = turn_at<T>(4 * IMG + wave * 256, lane);
     f32x16 acc[TILES][NT];
 #pragma unroll
     for (int t = 0; t < TILES; ++t)
@@ -237,9 +242,15 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + q * 512),
                                              (__attribute__((address_space(3))) void*)(lds + slot * IMG + q * 512 + wave * 64),
                                              16, 0, 0);
+        if constexpr (IMG % 512 != 0) {  // IMG = 256 (KP = 32, fp32 rows): half a round; waves 4..7 repeat it, so that
+                                         // every wave has the same number of loads in flight (the wait below counts)
+            const u32x4* src2 = img + image_of(c) * IMG + (tid & 255);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src2),
+                                             (__attribute__((address_space(3))) void*)(lds + slot * IMG + (wave & 3) * 64), 16,
+                                             0, 0);
+        }
     };
-    static_assert(IMG % 512 == 0, "every wave has as many loads in flight");
-    constexpr int VL = IMG / 512;  // image loads per wave and window
+    constexpr int VL = (IMG + 511) / 512;  // image loads per wave and window
 
     // One window. Step s = (k-step j, column tile ct) in order; the basis operand of step s + 1 is fetched from LDS
     // before the matrix-core instructions of step s are issued, and the scheduler may not move anything across a
@@ -248,8 +259,8 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
     // were loaded; it receives those of window m+2.
     auto visit = [&](RowRaw (&raw)[TILES], int64_t m) __attribute__((always_inline)) {
         const int sp = (int)((m - 1) & 3), sc = (int)(m & 3);
-        RowOp a[TILES];
-        turn_rows<TILES>(lds, turn, raw, a);
+        RowOp<T> a[TILES];
+        turn_rows<TILES, LX, T>(lds, turn, raw, a);
         stage(m + 2, (int)((m + 2) & 3));
         // The row loads of window m+2 go out in two bursts, row tile 0 a quarter through the window, when the registers of
         // the first operands are free again (the loads of this window's rows and accumulators fill the file otherwise: spills,
@@ -261,7 +272,7 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
             for (int t = 0; t < TILES; ++t)
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    const int q = 2 * x + h;
+                    const int q = 2 * (sizeof(T) == 2 ? x : (x >> 1)) + h;
                     if ((first && q < phi) || (last && q >= phi)) a[t].v[x] = u32x4{0u, 0u, 0u, 0u};
                 }
         }
@@ -277,14 +288,19 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
         u32x4 b[2];
         int at = operand_at(0);
         b[0] = lds[at];
-        u32x4 ahi[TILES];
+        u32x4 ahi[TILES], alo[TILES];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             const int j = s / (2 * NT), ct = s % (2 * NT);
             if (ct == 0) {
+                if constexpr (sizeof(T) == 2) {
 #pragma unroll
-                for (int t = 0; t < TILES; ++t) ahi[t] = a[t].v[j];
+                    for (int t = 0; t < TILES; ++t) ahi[t] = a[t].v[j];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) split8(a[t].v[2 * j], a[t].v[2 * j + 1], ahi[t], alo[t]);
+                }
             }
             if (s + 1 < STEPS) {
                 const int j2 = (s + 1) / (2 * NT), ct2 = (s + 1) % (2 * NT);
@@ -292,10 +308,16 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
                 b[(s + 1) % 2] = lds[at + ct2 * 32 * PPR];
             }
             if (s == STEPS / 4) load_rows(raw[0], 0, m2);
-            if (s == STEPS / 2) load_rows(raw[TILES - 1], 1, m2);
+            if (s == STEPS / 2 && TILES == 2) load_rows(raw[TILES - 1], 1, m2);
             const u32x4 bb = b[s % 2];
 #pragma unroll
             for (int t = 0; t < TILES; ++t) acc[t][ct % NT] = mfma_bf16(ahi[t], bb, acc[t][ct % NT]);
+            if constexpr (sizeof(T) == 4) {
+                if (ct < NT) {
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) acc[t][ct] = mfma_bf16(alo[t], bb, acc[t][ct]);
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
         // This window requested VL image loads (image m+2) and NL row loads (window m+2): once at most NL + VL loads are
@@ -356,53 +378,50 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const uint16_t* _
 }
 
 // ---- projection of rows of any width and alignment ---------------------------------------------------------------
-// Windows are counted from the row's first column, wherever that lies in a memory line, and a piece is loaded at any element
-// boundary. Rows that start on a multiple of 8 columns' bytes take a basis of two parts, the others one of three (24 bits, and fp32
-// rows are split the same way: six products, three for bf16 rows, which are exact): these went through the fp32 matrix cores before
-// (157 us for 2048 rows of 51,300 with 64 vectors) and are as accurate here, to a few 2^-24 per term.
+// Where rows do not start on a multiple of 8 columns' bytes, windows are counted from the row's first column, wherever that
+// lies in a memory line, and a piece is loaded at any element boundary. Such rows went through the fp32 matrix cores
+// before (157 us for 2048 rows of 51,300 with 64 vectors), so here the basis has three bf16 parts (24 bits) and fp32 rows
+// are split the same way: six products (three for bf16 rows, which are exact), the fp32 result to a few 2^-24 per term.
 //
-// Where memory is the bound, a wave takes 32 rows (256 a work-group) and 256 bytes of each at a time. A window's first and last line
-// are shared with its neighbours, and half of the times such a line has left the L2 when the next window asks for it: 256 bytes lie
-// in three lines where 128 lie in two (604 MB fetched for 440, now 478; 2048 rows of 51,300 fp32, 64 vectors: 108 us, now 100). Rows
-// whose pitch is a large power of two fall on the same memory channels, of which they leave fewer idle this way (512 fp32 rows of
-// 1,048,576, 128 vectors: 632 us, now 500; 1024 with 64 vectors 1150, now 800). And there are half as many partial sums to write and to
-// add up, which is what counts where rows are short (1024 bf16 rows of 32,768, 128 vectors: 62 us with their finish, now 47).
-// The basis operands are then read from LDS for 32 rows instead of 64. Where that, or the products, is the bound (three parts: fp32
-// rows with four column tiles, bf16 rows, which have one product for three, with two or four; two parts: project_split_kernel), a
-// window is 128 bytes of 64 rows, and of 32 rows in batches of up to 256.
+// With few basis vectors what bounds it is memory: a window's first and last line are shared with its neighbours, and half of the
+// times such a line has left the L2 when the next window asks for it. So there a wave takes 32 rows (256 a work-group) and 256 bytes
+// of each at a time, which lie in three lines; with 64 rows and 128 bytes, which lie in two, 604 MB were fetched for 440 (now 478;
+// 2048 rows of 51,300 fp32, 64 vectors: 108 us, now 102), and there were twice as many partial sums to write and to add up (12.0 us,
+// now 9.8). The basis operands are then read from LDS for 32 rows instead of 64. Where that, or the products, is the bound (fp32 rows
+// with four column tiles, bf16 rows, which have one product for three, with two or four), a window is 128 bytes of 64 rows (1024 rows
+// of 1,000,001 bf16, 128 vectors: 715 us, 790 with 256 bytes of 32 rows), or of 32 rows in batches of up to 256.
 //
 // A window is one or two chunks of the basis (CH), each with an image of its own. Rows are requested two windows ahead, in the
 // registers in which they come, and turned to the matrix cores' order through LDS of the wave's own (as in
-// project_split_kernel). The ring of images has three slots, by chunk (two where three do not fit, four column tiles of bf16 rows in
-// three parts: a chunk is long there, an image requested at its start lands within it).
+// project_split_kernel). The ring of images has three slots, by chunk (two where three do not fit, four column tiles of bf16 rows: a
+// chunk is long there, an image requested at its start lands within it).
 template <typename T>
 struct __attribute__((packed, aligned(sizeof(T)))) AnyPiece {
     u32x4 v;
 };
 
-template <int NT, typename T, int PARTS>
+template <int NT, typename T>
 struct AnyShape {
-    static constexpr int IMG = PARTS * NT * 32 * (16 / (int)sizeof(T));  // 16-byte pieces of an image
-    static constexpr int SLOTS = sizeof(T) == 2 && NT == 4 && PARTS == 3 ? 2 : 3;
+    static constexpr int IMG = 3 * NT * 32 * (16 / (int)sizeof(T));  // 16-byte pieces of an image
+    static constexpr int SLOTS = sizeof(T) == 2 && NT == 4 ? 2 : 3;
     static constexpr int lds(int pieces) { return (SLOTS * IMG + 8 * pieces) * 16; }  // bytes, with pieces of each wave's
 };
 
 // NL: row loads of a wave and window (64 / LPR rows each; the waves take the rows of a work-group in turn), as few as hold the batch
-template <int NT, typename T, int NL, int TILES, int CH, int PARTS>
+template <int NT, typename T, int NL, int TILES, int CH>
 __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict__ G, int64_t R,
                                                              const u32x4* __restrict__ img, float* __restrict__ partial,
                                                              int row_tiles, int64_t D, int64_t per, int last_split) {
     constexpr int KP = NT * 32;
     constexpr int KC = 128 / (int)sizeof(T);
     constexpr int PPR = KC / 8;
-    using Shape = AnyShape<NT, T, PARTS>;
-    constexpr int IMG = Shape::IMG, SLOTS = Shape::SLOTS;
+    constexpr int IMG = AnyShape<NT, T>::IMG, SLOTS = AnyShape<NT, T>::SLOTS;
     constexpr int KS = KC / 16;
     constexpr int ROWS = 256 * TILES;              // of a work-group
     constexpr int LPR = 8 * CH;                    // lanes (pieces) to a row's bytes of a window
     constexpr int NA = CH == 2 ? (NL + 1) / 2 : NL;  // row loads that a window's first chunk requests
     constexpr int MINE = 256 * TILES * CH;         // pieces of a window of a wave's rows
-    static_assert(NL <= 4 * TILES * CH && Shape::lds(MINE) <= 160 * 1024, "rows of a wave; LDS of a CU");
+    static_assert(NL <= 4 * TILES * CH && AnyShape<NT, T>::lds(MINE) <= 160 * 1024, "rows of a wave; LDS of a CU");
     extern __shared__ u32x4 lds[];                 // SLOTS * IMG, then MINE of each wave
 
     const int id = blockIdx.x;
@@ -427,13 +446,10 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
         const unsigned r = (unsigned)(wave + 8 * (64 / LPR * x + lane / LPR)) * (unsigned)S;
         return r > last_row ? last_row : r;
     };
-    // Whole windows are walked from a start of the split's own and wrap around (as in project_split_kernel): window(w) is the w-th.
-    const int whole = len / CH, rot = whole > 3 ? (int)((unsigned)split * 37u % (unsigned)whole) : 0;
-    auto window = [&](int w) { return w >= whole ? w : w + rot < whole ? w + rot : w + rot - whole; };
     const unsigned end = (unsigned)(c1 * 128) - 16u;  // the last piece of this split's whole chunks
     u32x4 raw0[NL], raw1[NL];  // [x]: piece lane % LPR of that row
     auto load_rows = [&](u32x4 (&raw)[NL], int w, int from, int to) __attribute__((always_inline)) {
-        w = window(w < windows - 1 ? w : windows - 1);  // beyond the last window: repeat it (never used)
+        w = w < windows - 1 ? w : windows - 1;  // beyond the last window: repeat it (never used)
         unsigned o = (unsigned)(c0 * 128) + 16u * LPR * (unsigned)w + 16u * (unsigned)(lane % LPR);
         o = o > end ? end : o;  // (a window of one chunk)
 #pragma unroll
@@ -470,8 +486,7 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     };
     // Splits of 256 bytes of fewer rows are half as many and sums twice as long. So the leading parts' products have accumulators of their
     // own there, which the others, each a 256th of them or less, no longer round (zhat of 2048 rows of 51,300 fp32, 64 vectors, against
-    // 64 bits: 3.9e-7 with sums half as long, 5.5e-7, 1.7e-7 with these; two parts, 512 of 1,048,576, 128 vectors: 2.06e-6, 2.17e-6,
-    // 1.97e-6).
+    // 64 bits: 3.9e-7 with sums half as long, 5.5e-7, 1.7e-7 with these).
     constexpr int SETS = CH;
     f32x16 acc[TILES][SETS][NT];
 #pragma unroll
@@ -484,7 +499,7 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
                 for (int i = 0; i < 16; ++i) acc[t][u][ct][i] = 0.f;
 
     constexpr int VL = (IMG + 511) / 512;
-    auto chunk = [&](int i) { return c0 + (i < len ? CH * window(i / CH) + i % CH : 0); };  // the i-th; beyond the last: any (never used)
+    auto chunk = [&](int i) { return c0 + (i < len ? i : len - 1); };  // beyond the split's: the last one again (never used)
     auto stage = [&](int64_t c, int slot) __attribute__((always_inline)) {
         const u32x4* src = img + c * IMG;
 #pragma unroll
@@ -500,27 +515,25 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     int sc = 0;  // slot of the present chunk's image
     // the products of one chunk: row operands a
     auto multiply = [&](const Op (&a)[TILES], auto&& between) __attribute__((always_inline)) {
-        constexpr int STEPS = KS * PARTS * NT;  // (k-step, part of the basis, column tile)
+        constexpr int STEPS = KS * 3 * NT;  // (k-step, part of the basis, column tile)
         int hq = h;
         asm volatile("" : "+v"(hq));  // (addresses are formed when they are needed: registers are short)
         auto addr = [&](int s) {
-            const int j = s / (PARTS * NT), pt = (s / NT) % PARTS, ct = s % NT;
+            const int j = s / (3 * NT), pt = (s / NT) % 3, ct = s % NT;
             return img_piece<KC>(n, 2 * j + hq) + sc * IMG + (pt * KP + ct * 32) * PPR;
         };
         u32x4 b[2];
         b[0] = lds[addr(0)];
-        u32x4 ap[TILES][PARTS];
+        u32x4 ap[TILES][3];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
-            const int j = s / (PARTS * NT), pt = (s / NT) % PARTS, ct = s % NT;
-            if (s % (PARTS * NT) == 0) {
+            const int j = s / (3 * NT), pt = (s / NT) % 3, ct = s % NT;
+            if (s % (3 * NT) == 0) {
 #pragma unroll
                 for (int t = 0; t < TILES; ++t) {
                     if constexpr (sizeof(T) == 2) {
                         ap[t][0] = a[t].v[j];
-                    } else if constexpr (PARTS == 2) {
-                        split8(a[t].v[2 * j], a[t].v[2 * j + 1], ap[t][0], ap[t][1]);
                     } else {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
@@ -538,10 +551,10 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
             if (s == STEPS / 4) between(0);
             if (s == STEPS / 2) between(1);
             const u32x4 bb = b[s % 2];
-            constexpr int QS = sizeof(T) == 2 ? 1 : PARTS;
+            constexpr int QS = sizeof(T) == 2 ? 1 : 3;
 #pragma unroll
             for (int q = 0; q < QS; ++q)
-                if (q + pt < PARTS) {
+                if (q + pt <= 2) {
                     const int u = SETS == 2 && q + pt > 0 ? 1 : 0;
 #pragma unroll
                     for (int t = 0; t < TILES; ++t) acc[t][u][ct] = mfma_bf16(ap[t][q], bb, acc[t][u][ct]);
@@ -579,7 +592,7 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     constexpr std::false_type NO{};
 
     if (len > 0) {
-        stage(chunk(0), 0);
+        stage(c0, 0);
         if (SLOTS == 3) stage(chunk(1), 1);
         load_rows(raw0, 0, 0, NL);
         if (windows > 1) {  // (begins before window 1 is there: 256 rows of 200,001 bf16, 128 vectors: 80 -> 74 us)
@@ -655,8 +668,9 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
                 if (r < R) out[r * KP + ct * 32 + n] = SETS == 2 ? acc[t][0][ct][i] + acc[t][SETS - 1][ct][i] : acc[t][0][ct][i];
             }
 }
-// three parts: is memory the bound?
+// is memory the bound? (rows of a work-group; which shape is taken)
 constexpr bool any_wide(int dtype, int KP) { return KP <= (dtype == SAGE_BF16 ? 32 : 64); }
+int any_rows(int64_t R, int dtype, int KP) { return !any_wide(dtype, KP) && R > 256 ? 512 : 256; }
 
 // Any row start that is a multiple of the element, a row of at least one window, lane offsets of 32 bits.
 bool any_path_ok(const void* G, int dtype, const Dims& d) {
@@ -674,22 +688,11 @@ bool split_path_ok(const void* G, int dtype, const Dims& d) {
 
 ScorePlan score_split_plan(int64_t R, int dtype, int parts, int KP, const Dims& d, int num_cu) {
     ScorePlan p;
-    const int KC = dtype == SAGE_BF16 ? 64 : 32;
+    const int KC = dtype == SAGE_BF16 ? 64 : 32, rows = parts == 3 ? any_rows(R, dtype, KP) : 512;
     const int64_t chunks = (d.D + KC - 1) / KC;
-    // project_split_kernel's part: where it has more than some 40 chunks to a work-group, what it gains is more than the partial sums it
-    // has more of cost (bf16 rows, 128 vectors, us a pass of 4096 rows, project_any_kernel / project_split_kernel: batches of 1024, D =
-    // 200,008 616 / 660, 300,008 846 / 843, 400,008 1070 / 1028, 600,008 1540 / 1430; of 512, 400,008 1240 / 1388, 800,008 2230 / 2265; of
-    // 2048, 300,008 766 / 720), unless the rows fall on the same memory channels (1024 of 1,048,576 1360 / 1430 for two batches).
-    p.lines = parts == 2 && dtype == SAGE_BF16 && KP == 128 && R > 256 && chunks * ((R + 511) / 512) > (int64_t)40 * num_cu &&
-              d.D % (1 << 19) != 0;
-    const int rows = p.lines || (parts == 3 && !any_wide(dtype, KP) && R > 256) ? 512 : 256;
     p.row_tiles = (int)((R + rows - 1) / rows);
-    // A work-group per CU and no more: those too many are a second round of the chip (three row tiles in 88 splits, 264 work-groups,
-    // against 80: 615 fp32 rows of 1,267,880, 64 vectors 986 us a pass, now 822; 1300 of 300,008 in 48 and 40 splits 513 and 378 a
-    // batch). Two rounds of half the size only where one would leave a fifth of the CUs idle (seven row tiles, 32 splits of 256 CUs or
-    // 72: 1700 rows of 100,008 369 us for two batches against 381).
-    const int64_t one = num_cu / p.row_tiles / 8 * 8, two = 2 * (int64_t)num_cu / p.row_tiles / 8 * 8;
-    int64_t s = two * 10 > one * 24 ? two : one;
+    int64_t want = ((int64_t)num_cu + p.row_tiles - 1) / p.row_tiles;  // one work-group per CU
+    int64_t s = (want + 7) / 8 * 8;
     // At least ~2 chunks per split: a small projection is a chain of loads, 1 us per chunk and more (1024 rows of 5136 fp32:
     // 25.7 us at 8 chunks, 16.2 at 2, with the finish of the more numerous partial sums as fast)
     int64_t smax = ((chunks + 1) / 2 + 7) / 8 * 8;
@@ -697,49 +700,61 @@ ScorePlan score_split_plan(int64_t R, int dtype, int parts, int KP, const Dims& 
     if (s < 8) s = 8;
     if (s > 512) s = 512;
     p.splits = (int)s;
-    p.slabs_per_split = p.lines ? (chunks + s - 1) / s : (d.D / KC + s - 1) / s;  // chunks per split on this path (whole ones)
+    p.slabs_per_split = (chunks + s - 1) / s;  // chunks per split on this path (three parts: shared out evenly)
     return p;
 }
 
-static hipError_t launch_lines(const uint16_t* G, int64_t R, const void* img, float* partial, const ScorePlan& p, const Dims& d,
-                               hipStream_t st) {
-    constexpr int lds = 4 * 2 * 128 * 8 * 16 + 8 * 256 * 16;
-    if (hipError_t ea = ensure_dynamic_lds((const void*)project_split_kernel, lds); ea != hipSuccess) return ea;
-    hipLaunchKernelGGL(project_split_kernel, dim3((unsigned)(p.row_tiles * p.splits)), dim3(512), lds, st, G, R, (const u32x4*)img, partial,
-                       p.row_tiles, d.D, (d.D + 63) / 64, p.slabs_per_split);
+template <int NT, typename T, int NL>
+static hipError_t launch_split_nl(const T* G, int64_t R, const void* img, float* partial, const ScorePlan& p, const Dims& d,
+                                  hipStream_t st) {
+    constexpr int KC = 128 / (int)sizeof(T), lds = 4 * 2 * NT * 32 * (KC / 8) * 16 + 8 * 256 * 16;
+    const auto kern = project_split_kernel<NT, T, NL>;
+    if (hipError_t ea = ensure_dynamic_lds((const void*)kern, lds); ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.row_tiles * p.splits)), dim3(512), lds, st, G, R, (const u32x4*)img, partial,
+                       p.row_tiles, d.D, (d.D + KC - 1) / KC, p.slabs_per_split);
     return hipGetLastError();
 }
-template <int NT, typename T, int NL, int TILES, int CH, int PARTS>
+template <int NT, typename T, int NL, int TILES, int CH>
 static hipError_t launch_any_nl(const T* G, int64_t R, const void* img, float* partial, const ScorePlan& p, const Dims& d,
                                 hipStream_t st) {
-    constexpr int lds = AnyShape<NT, T, PARTS>::lds(256 * TILES * CH);
-    const auto kern = project_any_kernel<NT, T, NL, TILES, CH, PARTS>;
-    if (hipError_t ea = ensure_dynamic_lds((const void*)kern, lds); ea != hipSuccess) return ea;
+    constexpr int lds = AnyShape<NT, T>::lds(256 * TILES * CH);
     // The last split, which has no more whole chunks than the others, takes the partial one. (Whole chunks shared out evenly, 36 or 37
     // to a split instead of 37: 256 rows of 300,001 fp32, 64 vectors took 100 us instead of 94; 333 of 20,001 bf16, 50 vectors, with
     // the partial chunk after a whole one, 15.6 instead of 14.2.)
+    const int64_t full = d.D * (int64_t)sizeof(T) / 128;
+    const auto kern = project_any_kernel<NT, T, NL, TILES, CH>;
+    if (hipError_t ea = ensure_dynamic_lds((const void*)kern, lds); ea != hipSuccess) return ea;
     hipLaunchKernelGGL(kern, dim3((unsigned)(p.row_tiles * p.splits)), dim3(512), lds, st, G, R, (const u32x4*)img, partial,
-                       p.row_tiles, d.D, p.slabs_per_split, p.splits - 1);
+                       p.row_tiles, d.D, (full + p.splits - 1) / p.splits, p.splits - 1);
     return hipGetLastError();
 }
-// Row loads of a wave and window (eight rows each in batches of up to 256; the waves take the rows of a work-group in turn): as few as
-// hold the batch. (Eight whatever the batch: of 64 rows most loads ask for the last row again, a line that is on its way. 64 fp32
-// rows of 977,864 with 8 vectors: 183 us with eight, 101 with one; 128 bf16 rows of 200,001 with 100 vectors 67 and 41.)
-template <int NT, typename T, int PARTS>
-static hipError_t launch_any_t(const T* G, int64_t R, const void* img, float* partial, const ScorePlan& p, const Dims& d, hipStream_t st) {
-    constexpr bool wide = PARTS == 2 || any_wide(sizeof(T) == 2 ? SAGE_BF16 : SAGE_F32, 32 * NT);
-    if (R > 256) return launch_any_nl<NT, T, 8, wide ? 1 : 2, wide ? 2 : 1, PARTS>(G, R, img, partial, p, d, st);
-    if (R > 128) return launch_any_nl<NT, T, 4, 1, 1, PARTS>(G, R, img, partial, p, d, st);
-    if (R > 64) return launch_any_nl<NT, T, 2, 1, 1, PARTS>(G, R, img, partial, p, d, st);
-    return launch_any_nl<NT, T, 1, 1, 1, PARTS>(G, R, img, partial, p, d, st);
-}
+// Row loads of a wave and window (eight rows each; the waves take the rows of a work-group in turn): as few as hold the batch.
+// (Eight whatever the batch: of 64 rows most loads ask for the last row again, a line that is on its way. 64 fp32 rows of 977,864
+// with 8 vectors: 183 us with eight, 101 with one; 128 bf16 rows of 200,001 with 100 vectors 67 and 41.)
+int loads_of(int64_t R) { return R > 256 ? 8 : R > 128 ? 4 : R > 64 ? 2 : 1; }
+
 template <int NT, typename T>
 static hipError_t launch_split_t(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
                                  const Dims& d, hipStream_t st) {
-    if constexpr (NT == 4 && sizeof(T) == 2)
-        if (p.lines) return launch_lines(G, R, img, partial, p, d, st);
-    if (parts == 3) return launch_any_t<NT, T, 3>(G, R, img, partial, p, d, st);
-    return launch_any_t<NT, T, 2>(G, R, img, partial, p, d, st);
+    if (parts == 3) {
+        if (R > 256) {
+            if constexpr (any_wide(sizeof(T) == 2 ? SAGE_BF16 : SAGE_F32, 32 * NT))
+                return launch_any_nl<NT, T, 8, 1, 2>(G, R, img, partial, p, d, st);
+            else
+                return launch_any_nl<NT, T, 8, 2, 1>(G, R, img, partial, p, d, st);
+        }
+        switch (loads_of(R)) {
+            case 1: return launch_any_nl<NT, T, 1, 1, 1>(G, R, img, partial, p, d, st);
+            case 2: return launch_any_nl<NT, T, 2, 1, 1>(G, R, img, partial, p, d, st);
+            default: return launch_any_nl<NT, T, 4, 1, 1>(G, R, img, partial, p, d, st);
+        }
+    }
+    switch (loads_of(R)) {
+        case 1: return launch_split_nl<NT, T, 1>(G, R, img, partial, p, d, st);
+        case 2: return launch_split_nl<NT, T, 2>(G, R, img, partial, p, d, st);
+        case 4: return launch_split_nl<NT, T, 4>(G, R, img, partial, p, d, st);
+        default: return launch_split_nl<NT, T, 8>(G, R, img, partial, p, d, st);
+    }
 }
 
 template <int NT>
