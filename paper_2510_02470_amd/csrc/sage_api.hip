@@ -1374,7 +1374,7 @@ static int project_rows(sage_ctx* c, const RowSrc& src, int64_t R, int* slots) {
     if (parts) {
         if (int rc = ensure_images(c, parts); rc != SAGE_OK) return rc;
     }
-    ScorePlan p = parts ? score_split_plan(R, c->dtype, parts, c->KP, c->d, c->num_cu) : score_plan(R, c->d, c->num_cu);
+    ScorePlan p = parts ? score_split_plan(R, c->dtype, c->d, c->num_cu) : score_plan(R, c->d, c->num_cu);
     int rc = ensure_partial(c, (size_t)p.splits * R * c->KP);
     if (rc != SAGE_OK) return rc;
     if (parts)

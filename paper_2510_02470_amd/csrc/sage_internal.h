@@ -301,7 +301,7 @@ bool split_path_ok(const void* G, int dtype, const Dims& d);
 bool any_path_ok(const void* G, int dtype, const Dims& d);
 size_t basis_image_bytes(int KP, int dtype, int parts, const Dims& d);
 hipError_t launch_basis_split(const float* Vblk, int KP, int dtype, int parts, void* img, const Dims& d, hipStream_t st);
-ScorePlan score_split_plan(int64_t R, int dtype, int parts, int KP, const Dims& d, int num_cu);
+ScorePlan score_split_plan(int64_t R, int dtype, const Dims& d, int num_cu);
 hipError_t launch_project_split(const void* G, int dtype, int64_t R, int parts, const void* img, int KP, float* partial,
                                 const ScorePlan& p, const Dims& d, hipStream_t st);
 

@@ -383,18 +383,15 @@ __global__ __launch_bounds__(512, 1) void project_split_kernel(const T* __restri
 // before (157 us for 2048 rows of 51,300 with 64 vectors), so here the basis has three bf16 parts (24 bits) and fp32 rows
 // are split the same way: six products (three for bf16 rows, which are exact), the fp32 result to a few 2^-24 per term.
 //
-// With few basis vectors what bounds it is memory: a window's first and last line are shared with its neighbours, and half of the
-// times such a line has left the L2 when the next window asks for it. So there a wave takes 32 rows (256 a work-group) and 256 bytes
-// of each at a time, which lie in three lines; with 64 rows and 128 bytes, which lie in two, 604 MB were fetched for 440 (now 478;
-// 2048 rows of 51,300 fp32, 64 vectors: 108 us, now 102), and there were twice as many partial sums to write and to add up (12.0 us,
-// now 9.8). The basis operands are then read from LDS for 32 rows instead of 64. Where that, or the products, is the bound (fp32 rows
-// with four column tiles, bf16 rows, which have one product for three, with two or four), a window is 128 bytes of 64 rows (1024 rows
-// of 1,000,001 bf16, 128 vectors: 715 us, 790 with 256 bytes of 32 rows), or of 32 rows in batches of up to 256.
+// Shapes as in project_split_kernel: 512 threads, a wave owns 64 rows x KP columns, rows are loaded eight lanes to 128 bytes, two
+// windows ahead, and turned through LDS. Every window is a whole image, so the ring has three slots (two where three do not
+// fit, four column tiles of bf16 rows: a window is long there, an image requested at its start lands within it). The last,
+// partial window of the row is taken after the others, by the split that owns it.
 //
-// A window is one or two chunks of the basis (CH), each with an image of its own. Rows are requested two windows ahead, in the
-// registers in which they come, and turned to the matrix cores' order through LDS of the wave's own (as in
-// project_split_kernel). The ring of images has three slots, by chunk (two where three do not fit, four column tiles of bf16 rows: a
-// chunk is long there, an image requested at its start lands within it).
+// With rows loaded in the matrix cores' order (the vector cache stalled four fifths of the time), and turned: 2048 rows of
+// 51,300 fp32, 64 vectors 121 and 113 us; 512 rows of 1,000,001 fp32, 128 vectors 965 and 825; 1024 such rows of bf16 1100 and
+// 715. The rows' loads remain the bound of the first: each takes two lines (103 us where rows start on a line), and with one
+// product instead of six it takes 104.
 template <typename T>
 struct __attribute__((packed, aligned(sizeof(T)))) AnyPiece {
     u32x4 v;
@@ -404,103 +401,63 @@ template <int NT, typename T>
 struct AnyShape {
     static constexpr int IMG = 3 * NT * 32 * (16 / (int)sizeof(T));  // 16-byte pieces of an image
     static constexpr int SLOTS = sizeof(T) == 2 && NT == 4 ? 2 : 3;
-    static constexpr int lds(int pieces) { return (SLOTS * IMG + 8 * pieces) * 16; }  // bytes, with pieces of each wave's
+    static constexpr int LDS = (SLOTS * IMG + 8 * 256) * 16;
+    static_assert(LDS <= 160 * 1024, "of one CU");
 };
 
-// NL: row loads of a wave and window (64 / LPR rows each; the waves take the rows of a work-group in turn), as few as hold the batch
-template <int NT, typename T, int NL, int TILES, int CH>
+template <int NT, typename T, int NL>
 __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict__ G, int64_t R,
                                                              const u32x4* __restrict__ img, float* __restrict__ partial,
-                                                             int row_tiles, int64_t D, int64_t per, int last_split) {
+                                                             int row_tiles, int64_t D, int64_t chunks_total,
+                                                             int64_t chunks_per_split) {
     constexpr int KP = NT * 32;
+    constexpr int TILES = NL > 4 ? 2 : 1, LX = NL > 4 ? 4 : NL;
     constexpr int KC = 128 / (int)sizeof(T);
     constexpr int PPR = KC / 8;
     constexpr int IMG = AnyShape<NT, T>::IMG, SLOTS = AnyShape<NT, T>::SLOTS;
     constexpr int KS = KC / 16;
-    constexpr int ROWS = 256 * TILES;              // of a work-group
-    constexpr int LPR = 8 * CH;                    // lanes (pieces) to a row's bytes of a window
-    constexpr int NA = CH == 2 ? (NL + 1) / 2 : NL;  // row loads that a window's first chunk requests
-    constexpr int MINE = 256 * TILES * CH;         // pieces of a window of a wave's rows
-    static_assert(NL <= 4 * TILES * CH && AnyShape<NT, T>::lds(MINE) <= 160 * 1024, "rows of a wave; LDS of a CU");
-    extern __shared__ u32x4 lds[];                 // SLOTS * IMG, then MINE of each wave
+    extern __shared__ u32x4 lds[];  // SLOTS * IMG, then 256 pieces of each wave
 
     const int id = blockIdx.x;
     const int xcd = id & 7, y = id >> 3;
     const int rt = y % row_tiles;
     const int split = (y / row_tiles) * 8 + xcd;
-    const int64_t full = D / KC;  // whole chunks of a row
-    const int64_t c0 = min(split * per, full), c1 = min(c0 + per, full);
-    const bool tail = split == last_split && full * KC < D;
-    const int len = (int)(c1 - c0), windows = (len + CH - 1) / CH;
+    const int64_t full = D / KC;  // whole windows of a row
+    const int64_t c0 = (int64_t)split * chunks_per_split;
+    int64_t c1 = c0 + chunks_per_split;
+    if (c1 > chunks_total) c1 = chunks_total;
+    const bool tail = c0 < c1 && c1 > full;
+    if (c1 > full) c1 = full;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
     const int64_t S = D * (int64_t)sizeof(T);
-    const int64_t row0 = (int64_t)rt * ROWS;
+    const int64_t row0 = (int64_t)rt * 512;
     const char* gbase = reinterpret_cast<const char*>(G) + row0 * S;
     // rows >= R repeat row R - 1; their results are not written
-    const int64_t last = R - 1 - row0 < ROWS - 1 ? R - 1 - row0 : ROWS - 1;
-    const unsigned last_row = (unsigned)(last * S);
-    auto row_at = [&](int x) __attribute__((always_inline)) {  // of load x: the wave's row 64 / LPR * x + lane / LPR
-        const unsigned r = (unsigned)(wave + 8 * (64 / LPR * x + lane / LPR)) * (unsigned)S;
-        return r > last_row ? last_row : r;
-    };
-    const unsigned end = (unsigned)(c1 * 128) - 16u;  // the last piece of this split's whole chunks
-    u32x4 raw0[NL], raw1[NL];  // [x]: piece lane % LPR of that row
-    auto load_rows = [&](u32x4 (&raw)[NL], int w, int from, int to) __attribute__((always_inline)) {
-        w = w < windows - 1 ? w : windows - 1;  // beyond the last window: repeat it (never used)
-        unsigned o = (unsigned)(c0 * 128) + 16u * LPR * (unsigned)w + 16u * (unsigned)(lane % LPR);
-        o = o > end ? end : o;  // (a window of one chunk)
+    const int64_t last = R - 1 - row0 < 511 ? R - 1 - row0 : 511;
+    const unsigned lrow = (unsigned)((wave + 8 * (lane >> 3)) * S), last_row = (unsigned)(last * S);
+    auto load_rows = [&](RowRaw& a, int t, int64_t m) __attribute__((always_inline)) {
 #pragma unroll
-        for (int x = 0; x < NL; ++x)
-            if (x >= from && x < to) raw[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (row_at(x) + o))->v;
-    };
-    // Piece p of row r lies at r * LPR + (p ^ turned(r)): the 16 lanes that are served together fall on all banks, both ways.
-    char* const mine = reinterpret_cast<char*>(lds + SLOTS * IMG + wave * MINE);
-    auto turned = [](int r) { return LPR == 16 ? r & 15 : (r >> 1) & 7; };
-    const unsigned swz = (unsigned)turned(n) * 16u, line = (unsigned)(n * LPR) * 16u;
-    auto turn = [&](const u32x4 (&raw)[NL]) __attribute__((always_inline)) {
-        asm volatile("" ::: "memory");  // (a wave's LDS accesses keep their order)
-#pragma unroll
-        for (int x = 0; x < NL; ++x) {
-            const int r = 64 / LPR * x + lane / LPR;
-            *reinterpret_cast<u32x4*>(mine + (r * LPR + ((lane % LPR) ^ turned(r))) * 16) = raw[x];
+        for (int x = 0; x < LX; ++x) {
+            unsigned r = lrow + (unsigned)((t * 32 + 8 * x) * 8) * (unsigned)S;
+            r = r > last_row ? last_row : r;
+            a.v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (r + 16u * (unsigned)(lane & 7) + (unsigned)(m * 128)))->v;
         }
-        asm volatile("" ::: "memory");
     };
-    struct Op {
-        u32x4 v[4];  // bf16 rows: v[j] = k-step j; fp32 rows: v[2j], v[2j+1] = k-step j
-    };
-    auto operands = [&](int chunk, Op (&a)[TILES]) __attribute__((always_inline)) {
-        unsigned at = line + (((unsigned)(sizeof(T) == 2 ? h : 2 * h) * 16u) ^ swz);
-        asm volatile("" : "+v"(at));
-#pragma unroll
-        for (int t = 0; t < TILES; ++t)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const unsigned p = 8 * chunk + (sizeof(T) == 2 ? 2 * x : 4 * (x >> 1) + (x & 1));
-                a[t].v[x] = *reinterpret_cast<const u32x4*>(mine + t * 32 * LPR * 16 + (at ^ (p * 16)));
-            }
-        asm volatile("" ::: "memory");
-    };
-    // Splits of 256 bytes of fewer rows are half as many and sums twice as long. So the leading parts' products have accumulators of their
-    // own there, which the others, each a 256th of them or less, no longer round (zhat of 2048 rows of 51,300 fp32, 64 vectors, against
-    // 64 bits: 3.9e-7 with sums half as long, 5.5e-7, 1.7e-7 with these).
-    constexpr int SETS = CH;
-    f32x16 acc[TILES][SETS][NT];
+    const TurnAt turn = turn_at<T>(SLOTS * IMG + wave * 256, lane);
+    f32x16 acc[TILES][NT];
 #pragma unroll
     for (int t = 0; t < TILES; ++t)
 #pragma unroll
-        for (int u = 0; u < SETS; ++u)
+        for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
-            for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[t][u][ct][i] = 0.f;
+            for (int i = 0; i < 16; ++i) acc[t][ct][i] = 0.f;
 
     constexpr int VL = (IMG + 511) / 512;
-    auto chunk = [&](int i) { return c0 + (i < len ? i : len - 1); };  // beyond the split's: the last one again (never used)
     auto stage = [&](int64_t c, int slot) __attribute__((always_inline)) {
+        if (c > chunks_total - 1) c = chunks_total - 1;  // beyond the end: repeat (never used)
         const u32x4* src = img + c * IMG;
 #pragma unroll
         for (int q = 0; q < VL; ++q) {
@@ -512,9 +469,9 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
     };
 
     static_assert(NL + VL <= 15, "the low field of the count");
-    int sc = 0;  // slot of the present chunk's image
-    // the products of one chunk: row operands a
-    auto multiply = [&](const Op (&a)[TILES], auto&& between) __attribute__((always_inline)) {
+    int sc = 0;  // slot of the present window's image
+    // the products of one window: row operands a
+    auto multiply = [&](const RowOp<T> (&a)[TILES], auto&& between) __attribute__((always_inline)) {
         constexpr int STEPS = KS * 3 * NT;  // (k-step, part of the basis, column tile)
         int hq = h;
         asm volatile("" : "+v"(hq));  // (addresses are formed when they are needed: registers are short)
@@ -549,94 +506,94 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
             }
             if (s + 1 < STEPS) b[(s + 1) % 2] = lds[addr(s + 1)];
             if (s == STEPS / 4) between(0);
-            if (s == STEPS / 2) between(1);
+            if (s == STEPS / 2 && TILES == 2) between(1);
             const u32x4 bb = b[s % 2];
             constexpr int QS = sizeof(T) == 2 ? 1 : 3;
 #pragma unroll
             for (int q = 0; q < QS; ++q)
                 if (q + pt <= 2) {
-                    const int u = SETS == 2 && q + pt > 0 ? 1 : 0;
 #pragma unroll
-                    for (int t = 0; t < TILES; ++t) acc[t][u][ct] = mfma_bf16(ap[t][q], bb, acc[t][u][ct]);
+                    for (int t = 0; t < TILES; ++t) acc[t][ct] = mfma_bf16(ap[t][q], bb, acc[t][ct]);
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // One chunk, the first or the second of window w, its image in slot sc. The image requested is that of the chunk SLOTS - 1 further
-    // on, the rows are those of window w + 2 (in two bursts: the first operands' registers are free by then). more: false where the
-    // split has one window, or two of one chunk, as those of small projections have, and nothing beyond them is requested (333 rows of
-    // 25,447 bf16: 22.2 us with such requests, 19.5 without; 20.5 before rows were turned).
-    auto visit = [&](u32x4 (&raw)[NL], int w, auto second, auto more) __attribute__((always_inline)) {
-        constexpr bool SECOND = decltype(second)::value, MORE = decltype(more)::value;
-        constexpr int L0 = SECOND ? NA : 0, L1 = SECOND ? NL : NA, LH = TILES == 1 ? L1 : NL / 2;
-        Op a[TILES];
-        if constexpr (!SECOND) turn(raw);
-        operands(SECOND, a);
-        if (MORE || SLOTS == 2) stage(chunk(CH * w + SECOND + SLOTS - 1), sc == 0 ? SLOTS - 1 : sc - 1);
-        multiply(a, [&](int burst) __attribute__((always_inline)) {
-            if constexpr (MORE) load_rows(raw, w + 2, burst == 0 ? L0 : LH, burst == 0 ? LH : L1);
+    // One window: its image is in slot sc, its rows in raw as they were loaded, which receives the rows of window m + 2. The image
+    // requested is that of m + SLOTS - 1. more: false where the split has two windows at most, as those of small projections
+    // have, and nothing beyond them is requested (333 rows of 25,447 bf16: 22.2 us with such requests, 19.5
+    // without; 20.5 before rows were turned).
+    auto visit = [&](RowRaw (&raw)[TILES], int64_t m, auto more) __attribute__((always_inline)) {
+        constexpr bool MORE = decltype(more)::value;
+        const int64_t m2 = m + 2 > c1 - 1 ? c1 - 1 : m + 2;  // beyond the last window: repeat it (never used)
+        RowOp<T> a[TILES];
+        turn_rows<TILES, LX, T>(lds, turn, raw, a);
+        if (MORE || SLOTS == 2) stage(m + SLOTS - 1, sc == 0 ? SLOTS - 1 : sc - 1);
+        multiply(a, [&](int t) __attribute__((always_inline)) {
+            if constexpr (MORE) load_rows(raw[t], t, m2);
         });
-        // Every chunk requests an image and then rows: all of those of window w + 2 or, of two chunks, the first NA loads and the
-        // others. The image of the next chunk was requested in the chunk before this one, with rows after it, so it, and all that is
-        // older, the rows of window w + 1 at the end of window w, have landed once VL + NL loads are left. With two slots it is the
-        // image that this chunk requested, and only the rows requested after it may be left.
-        constexpr int LEFT = SLOTS == 3 ? NL + VL : L1 - L0;
+        // at most this window's row loads, with three slots its image loads too, stay outstanding: image m + 1 and rows m + 1
+        // have landed
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (MORE ? LEFT : 0));
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (MORE ? NL + (SLOTS == 3 ? VL : 0) : 0));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         sc = sc == SLOTS - 1 ? 0 : sc + 1;
     };
-    constexpr std::true_type YES{};
-    constexpr std::false_type NO{};
+    constexpr std::true_type MORE{};
+    constexpr std::false_type LAST{};
 
-    if (len > 0) {
+    const int64_t len = c1 - c0;
+    auto begin = [&](RowRaw (&a0)[TILES], RowRaw (&a1)[TILES]) __attribute__((always_inline)) {
         stage(c0, 0);
-        if (SLOTS == 3) stage(chunk(1), 1);
-        load_rows(raw0, 0, 0, NL);
-        if (windows > 1) {  // (begins before window 1 is there: 256 rows of 200,001 bf16, 128 vectors: 80 -> 74 us)
-            load_rows(raw1, 1, 0, NL);
-            __builtin_amdgcn_s_waitcnt(0x0F70 | NL);
-        } else {
-            __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (SLOTS == 3) stage(c0 + 1, 1);
+        const int64_t m1 = len > 1 ? c0 + 1 : c0;
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            load_rows(a0[t], t, c0);
+            load_rows(a1[t], t, m1);
         }
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
     if (len > 2) {
+        RowRaw a0[TILES], a1[TILES];
+        begin(a0, a1);
 #pragma unroll 1
-        for (int w = 0; w < windows; w += 2) {  // two windows per trip: the row buffers return to their roles
-            visit(raw0, w, NO, YES);
-            if constexpr (CH == 2)
-                if (2 * w + 1 < len) visit(raw0, w, YES, YES);
-            if (w + 1 < windows) {
-                visit(raw1, w + 1, NO, YES);
-                if constexpr (CH == 2)
-                    if (2 * w + 3 < len) visit(raw1, w + 1, YES, YES);
-            }
+        for (int64_t m = c0; m < c1; m += 2) {  // two windows per trip: the row buffers return to their roles
+            visit(a0, m, MORE);
+            if (m + 1 < c1) visit(a1, m + 1, MORE);
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing on its way to LDS any more
-    } else if (len > 0) {
-        visit(raw0, 0, NO, NO);
-        if (len == 2) {
-            if constexpr (CH == 2) visit(raw0, 0, YES, NO);
-            else visit(raw1, 1, NO, NO);
-        }
+    }
+    if (len == 1 || len == 2) {
+        RowRaw a0[TILES], a1[TILES];
+        begin(a0, a1);
+        visit(a0, c0, LAST);
+        if (len == 2) visit(a1, c0 + 1, LAST);
     }
     if (tail) {  // work-group uniform
         __syncthreads();
         stage(full, 0);
-        // The last 128 bytes of every row are loaded, and the columns beyond the whole chunks picked out of them in LDS.
+        // The last 128 bytes of every row are loaded, and the columns beyond the whole windows picked out of them in LDS.
         const int left = (int)(D - full * KC);
-#pragma unroll
-        for (int x = 0; x < NL; ++x)
-            raw0[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (row_at(x) + (unsigned)S - 128u + 16u * (unsigned)(lane & 7)))->v;
-        turn(raw0);
-        Op a[TILES];
+        RowRaw raw[TILES];
 #pragma unroll
         for (int t = 0; t < TILES; ++t)
+#pragma unroll
+            for (int x = 0; x < LX; ++x) {
+                unsigned r = lrow + (unsigned)((t * 32 + 8 * x) * 8) * (unsigned)S;
+                r = r > last_row ? last_row : r;
+                raw[t].v[x] = reinterpret_cast<const AnyPiece<T>*>(gbase + (r + (unsigned)S - 128u + 16u * (unsigned)(lane & 7)))->v;
+            }
+        RowOp<T> a[TILES];
+        char* const l = reinterpret_cast<char*>(lds);
+        const unsigned line = (unsigned)(SLOTS * IMG + wave * 256 + n * 8) * 16u, swz = (unsigned)((n >> 1) & 7) * 16u;
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+#pragma unroll
+            for (int x = 0; x < LX; ++x) *reinterpret_cast<u32x4*>(l + (x & 1 ? turn.w1 : turn.w0) + x * 1024) = raw[t].v[x];
+            asm volatile("" ::: "memory");  // (a wave's LDS accesses keep their order)
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
                 constexpr int E = 16 / (int)sizeof(T);
@@ -645,12 +602,13 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     const int c = at + e < left ? KC - left + at + e : 0;  // column of the 128 bytes
-                    const T w = *reinterpret_cast<const T*>(mine + t * 32 * LPR * 16 + line + (((unsigned)c * (unsigned)sizeof(T)) ^ swz));
+                    const T w = *reinterpret_cast<const T*>(l + line + (((unsigned)c * (unsigned)sizeof(T)) ^ swz));
                     v[e] = at + e < left ? w : (T)0;
                 }
                 __builtin_memcpy(&a[t].v[x], v, 16);
             }
-        asm volatile("" ::: "memory");
+            asm volatile("" ::: "memory");
+        }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         sc = 0;
@@ -665,12 +623,9 @@ __global__ __launch_bounds__(512, 1) void project_any_kernel(const T* __restrict
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int64_t r = row0 + wave + 8 * (t * 32 + 8 * (i >> 2) + 4 * h + (i & 3));
-                if (r < R) out[r * KP + ct * 32 + n] = SETS == 2 ? acc[t][0][ct][i] + acc[t][SETS - 1][ct][i] : acc[t][0][ct][i];
+                if (r < R) out[r * KP + ct * 32 + n] = acc[t][ct][i];
             }
 }
-// is memory the bound? (rows of a work-group; which shape is taken)
-constexpr bool any_wide(int dtype, int KP) { return KP <= (dtype == SAGE_BF16 ? 32 : 64); }
-int any_rows(int64_t R, int dtype, int KP) { return !any_wide(dtype, KP) && R > 256 ? 512 : 256; }
 
 // Any row start that is a multiple of the element, a row of at least one window, lane offsets of 32 bits.
 bool any_path_ok(const void* G, int dtype, const Dims& d) {
@@ -686,11 +641,11 @@ bool split_path_ok(const void* G, int dtype, const Dims& d) {
     return d.D % 8 == 0 && d.D >= KC && d.D * esz * 513 + 256 < ((int64_t)1 << 32) && ((uintptr_t)G) % (8 * esz) == 0;
 }
 
-ScorePlan score_split_plan(int64_t R, int dtype, int parts, int KP, const Dims& d, int num_cu) {
+ScorePlan score_split_plan(int64_t R, int dtype, const Dims& d, int num_cu) {
     ScorePlan p;
-    const int KC = dtype == SAGE_BF16 ? 64 : 32, rows = parts == 3 ? any_rows(R, dtype, KP) : 512;
+    const int KC = dtype == SAGE_BF16 ? 64 : 32;
     const int64_t chunks = (d.D + KC - 1) / KC;
-    p.row_tiles = (int)((R + rows - 1) / rows);
+    p.row_tiles = (int)((R + 511) / 512);
     int64_t want = ((int64_t)num_cu + p.row_tiles - 1) / p.row_tiles;  // one work-group per CU
     int64_t s = (want + 7) / 8 * 8;
     // At least ~2 chunks per split: a small projection is a chain of loads, 1 us per chunk and more (1024 rows of 5136 fp32:
@@ -700,60 +655,35 @@ ScorePlan score_split_plan(int64_t R, int dtype, int parts, int KP, const Dims& 
     if (s < 8) s = 8;
     if (s > 512) s = 512;
     p.splits = (int)s;
-    p.slabs_per_split = (chunks + s - 1) / s;  // chunks per split on this path (three parts: shared out evenly)
+    p.slabs_per_split = (chunks + s - 1) / s;  // chunks per split on this path
     return p;
 }
 
-template <int NT, typename T, int NL>
-static hipError_t launch_split_nl(const T* G, int64_t R, const void* img, float* partial, const ScorePlan& p, const Dims& d,
-                                  hipStream_t st) {
-    constexpr int KC = 128 / (int)sizeof(T), lds = 4 * 2 * NT * 32 * (KC / 8) * 16 + 8 * 256 * 16;
-    const auto kern = project_split_kernel<NT, T, NL>;
-    if (hipError_t ea = ensure_dynamic_lds((const void*)kern, lds); ea != hipSuccess) return ea;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(p.row_tiles * p.splits)), dim3(512), lds, st, G, R, (const u32x4*)img, partial,
-                       p.row_tiles, d.D, (d.D + KC - 1) / KC, p.slabs_per_split);
-    return hipGetLastError();
-}
-template <int NT, typename T, int NL, int TILES, int CH>
-static hipError_t launch_any_nl(const T* G, int64_t R, const void* img, float* partial, const ScorePlan& p, const Dims& d,
-                                hipStream_t st) {
-    constexpr int lds = AnyShape<NT, T>::lds(256 * TILES * CH);
-    // The last split, which has no more whole chunks than the others, takes the partial one. (Whole chunks shared out evenly, 36 or 37
-    // to a split instead of 37: 256 rows of 300,001 fp32, 64 vectors took 100 us instead of 94; 333 of 20,001 bf16, 50 vectors, with
-    // the partial chunk after a whole one, 15.6 instead of 14.2.)
-    const int64_t full = d.D * (int64_t)sizeof(T) / 128;
-    const auto kern = project_any_kernel<NT, T, NL, TILES, CH>;
-    if (hipError_t ea = ensure_dynamic_lds((const void*)kern, lds); ea != hipSuccess) return ea;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(p.row_tiles * p.splits)), dim3(512), lds, st, G, R, (const u32x4*)img, partial,
-                       p.row_tiles, d.D, (full + p.splits - 1) / p.splits, p.splits - 1);
-    return hipGetLastError();
-}
 // Row loads of a wave and window (eight rows each; the waves take the rows of a work-group in turn): as few as hold the batch.
 // (Eight whatever the batch: of 64 rows most loads ask for the last row again, a line that is on its way. 64 fp32 rows of 977,864
 // with 8 vectors: 183 us with eight, 101 with one; 128 bf16 rows of 200,001 with 100 vectors 67 and 41.)
 int loads_of(int64_t R) { return R > 256 ? 8 : R > 128 ? 4 : R > 64 ? 2 : 1; }
 
+template <int NT, typename T, int NL>
+static hipError_t launch_split_nl(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
+                                  const Dims& d, hipStream_t st) {
+    constexpr int KC = 128 / (int)sizeof(T);
+    const int lds = parts == 3 ? AnyShape<NT, T>::LDS : 4 * 2 * NT * 32 * (KC / 8) * 16 + 8 * 256 * 16;
+    void (*const kern)(const T*, int64_t, const u32x4*, float*, int, int64_t, int64_t, int64_t) =
+        parts == 3 ? project_any_kernel<NT, T, NL> : project_split_kernel<NT, T, NL>;
+    if (hipError_t ea = ensure_dynamic_lds((const void*)kern, lds); ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.row_tiles * p.splits)), dim3(512), lds, st, G, R, (const u32x4*)img, partial,
+                       p.row_tiles, d.D, (d.D + KC - 1) / KC, p.slabs_per_split);
+    return hipGetLastError();
+}
 template <int NT, typename T>
 static hipError_t launch_split_t(const T* G, int64_t R, int parts, const void* img, float* partial, const ScorePlan& p,
                                  const Dims& d, hipStream_t st) {
-    if (parts == 3) {
-        if (R > 256) {
-            if constexpr (any_wide(sizeof(T) == 2 ? SAGE_BF16 : SAGE_F32, 32 * NT))
-                return launch_any_nl<NT, T, 8, 1, 2>(G, R, img, partial, p, d, st);
-            else
-                return launch_any_nl<NT, T, 8, 2, 1>(G, R, img, partial, p, d, st);
-        }
-        switch (loads_of(R)) {
-            case 1: return launch_any_nl<NT, T, 1, 1, 1>(G, R, img, partial, p, d, st);
-            case 2: return launch_any_nl<NT, T, 2, 1, 1>(G, R, img, partial, p, d, st);
-            default: return launch_any_nl<NT, T, 4, 1, 1>(G, R, img, partial, p, d, st);
-        }
-    }
     switch (loads_of(R)) {
-        case 1: return launch_split_nl<NT, T, 1>(G, R, img, partial, p, d, st);
-        case 2: return launch_split_nl<NT, T, 2>(G, R, img, partial, p, d, st);
-        case 4: return launch_split_nl<NT, T, 4>(G, R, img, partial, p, d, st);
-        default: return launch_split_nl<NT, T, 8>(G, R, img, partial, p, d, st);
+        case 1: return launch_split_nl<NT, T, 1>(G, R, parts, img, partial, p, d, st);
+        case 2: return launch_split_nl<NT, T, 2>(G, R, parts, img, partial, p, d, st);
+        case 4: return launch_split_nl<NT, T, 4>(G, R, parts, img, partial, p, d, st);
+        default: return launch_split_nl<NT, T, 8>(G, R, parts, img, partial, p, d, st);
     }
 }
 

@@ -134,14 +134,6 @@ def test_projection_of_aligned_rows_at_the_edges_of_its_tiles(n, D, k, dtype):
     s.close()
 
 
-# Rows that start anywhere in a line, more than 256 of them with few vectors: windows of two chunks of the basis. Splits of three chunks
-# (one of them alone), four, a last split with one and with none, with and without a partial chunk.
-@pytest.mark.parametrize("n,D,k,dtype", [(n, D, k, "f32") for n in (257, 513) for D in (8193, 8228, 10273, 12324, 12345) for k in (20, 64)]
-                         + [(n, D, 20, "bf16") for n in (257, 513) for D in (16388, 16449, 20545, 24641)])
-def test_projection_in_windows_of_two_chunks(n, D, k, dtype):
-    test_projection_of_aligned_rows_at_the_edges_of_its_tiles(n, D, k, dtype)
-
-
 # the answer's signal: more callers than words, and the largest export that one work-group copies
 def test_topm_from_many_threads():
     from concurrent.futures import ThreadPoolExecutor
