@@ -1124,8 +1124,8 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, 
 // either way. HS: stages of 16 rows of a half in use.
 // Bound by memory where rows are long: with the rebuild 1.05 GB at 2,049,000 columns in 215 us, where a kernel for each took 130 and (all
 // four blocks, through LDS) 190; by the launch where they are short (512 columns: 6.2 us, were 5.2 and 4.9). In between the two are
-// even (51,300: a unit for each wave, 12.8 us for 7.5 and 6.3). 17 blocks of 32 rows: 11.1 -> 8.1 ms at 2,049,000, 3.85 -> 3.30 at
-// 524,288; 64 of 512 columns: 5.39 -> 5.24.
+// even (51,300: a unit for each wave, 12.8 us for 7.5 and 6.3). An update of 17 blocks of 32 rows: 9.5 -> 6.0 ms at 2,049,000, 3.31 -> 2.36 at
+// 524,288; a job of 64 blocks of 512 columns: 5.39 -> 5.24.
 template <int HS, bool REBUILD>
 __global__ __launch_bounds__(256, 2) void gram64_kernel(std::conditional_t<REBUILD, float, const float>* top, int top_rows,
                                                         const float* __restrict__ nw, const float* __restrict__ next, int rows,
