@@ -312,8 +312,9 @@ int sage_topm(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* 
  * per GPU, held until the process ends; the call allocates and frees nothing and does not wait: the work is enqueued
  * on hip_stream and out_idx is complete when that stream reaches the end of it. N > SAGE_TOPM_STATIC_MAX_N gives
  * SAGE_ERR_CAPACITY. All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
- * streams, two threads) race; calls on one stream, or otherwise ordered, are safe -- every call clears what it needs
- * cleared with its own first kernel.
+ * streams, two threads) race; calls on one stream, or otherwise ordered, are safe. Beyond 32768 scores a call relies on the
+ * runs before it on that GPU having come to their end, which leaves the histograms zero; it clears them first itself when a launch of a
+ * call before it was refused (SAGE_ERR_HIP), and always when it is captured, so that a graph may be replayed after anything.
  */
 #define SAGE_TOPM_STATIC_MAX_N 16777216
 int sage_topm_static(const float* alpha, int64_t N, int64_t m, int64_t* out_idx, void* hip_stream);

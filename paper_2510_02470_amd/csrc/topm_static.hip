@@ -1,10 +1,10 @@
 // Top-m selection for callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses that
 // forbid hipMalloc): the radix-select work space lives in a file-scope device array instead of a per-call allocation.
 // See sage_topm_static in include/sage.h.
-#include <atomic>
 #include <mutex>
 
 #include "sage_internal.h"
+#include "topm_kept.h"
 
 namespace {
 
@@ -21,8 +21,7 @@ static __device__ __align__(256) uint32_t scratch[SCRATCH_WORDS];
 constexpr int MAX_DEVICES = 64;
 std::mutex g_lock;
 uint32_t* g_ptr[MAX_DEVICES] = {nullptr};
-// A run of several launches of which one was refused may have left its histograms as they were: the next call clears them.
-std::atomic<bool> g_cut_short[MAX_DEVICES];
+sage::KeptHistograms g_kept[MAX_DEVICES];
 
 // Device address of `scratch` on the current device (looked up on the first call per device).
 int scratch_ptr(uint32_t** out, int& dev) {
@@ -56,14 +55,21 @@ extern "C" int sage_topm_static(const float* alpha, int64_t N, int64_t m, int64_
     if (rc != SAGE_OK) return rc;
     const sage::SelectWork w = sage::select_work_at(base, MAX_BLOCKS);
     // The histograms are zero when the module is loaded and when a run is over (two that overlapped too, once both are: each
-    // clears them after its own additions); the state, every per-block counter and every table that is read are written earlier in
-    // the same run. So nothing of the previous call's contents is used.
-    const bool clear = !g_cut_short[dev].load();
-    if (sage::launch_topm(alpha, N, m, out_idx, w, clear, (hipStream_t)hip_stream) != hipSuccess) {
+    // clears them after its own additions), but for runs that were cut short: see topm_kept.h. The state, every per-block counter
+    // and every table that is read are written earlier in the same run. So nothing of the previous call's contents is used.
+    const hipStream_t st = (hipStream_t)hip_stream;
+    const bool many = sage::topm_needs_work(N);  // (else one launch, which uses none of it)
+    bool eager = true;
+    if (many) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        eager = hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+        if (!eager) (void)hipGetLastError();
+    }
+    const bool clear = many && !g_kept[dev].clear_first(eager);
+    if (sage::launch_topm(alpha, N, m, out_idx, w, clear, st) != hipSuccess) {
         (void)hipGetLastError();
-        g_cut_short[dev].store(true);
+        if (many) g_kept[dev].refused();
         return SAGE_ERR_HIP;
     }
-    if (!clear && sage::topm_needs_work(N)) g_cut_short[dev].store(false);
     return SAGE_OK;
 }

@@ -72,6 +72,18 @@ def test_work_space_of_the_selection(tmp_path):
     assert _run(exe, "planted").returncode == 1
 
 
+def test_kept_histograms_are_zero_when_a_run_begins(tmp_path):
+    """topm_kept_check.cc; and the check itself: it must refuse a clearing launch that is taken for done when it is only captured, and
+    graphs without one."""
+    exe = _build(tmp_path, "topm_kept_check")
+    r = _run(exe)
+    assert r.returncode == 0 and "topm_kept_check ok" in r.stdout, r.stdout
+    r = _run(exe, "enqueued")
+    assert r.returncode == 1 and "eager: histogram" in r.stdout, r.stdout
+    r = _run(exe, "bare")
+    assert r.returncode == 1 and "replay: histogram" in r.stdout, r.stdout
+
+
 def test_events_that_order_streams_release_what_they_order():
     """No run shows a missing release reliably, so the flag is looked for: hipEventDisableSystemFence takes the release away that
     lets a stream see what was written, on another XCD, before the event."""

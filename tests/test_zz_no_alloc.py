@@ -81,3 +81,29 @@ def test_static_topm_leaves_its_work_space_clear():
         check(a, 20_000, out)
         b = _scores(n, 30 + i, torch)
         check(b, m, binding.topm_static(b, m, torch.empty(m, dtype=torch.int64, device="cuda")))
+
+
+def test_captured_static_topm_relies_on_no_other_run():
+    """A run that was cut short leaves the histograms as they were, and a graph may be replayed after it: a captured run has its own
+    clearing launch, whatever came before (five kernels; up to 32,768 scores one, which uses no work space)."""
+    import torch
+
+    from paper_2510_02470_amd import binding
+
+    hip = C.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))  # (the one that is in use)
+    hip.hipGraphGetNodes.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_size_t)]
+    for n, kernels in ((300_001, 5), (32_768, 1)):
+        a = _scores(n, n, torch)
+        out = torch.empty(3000, dtype=torch.int64, device="cuda")
+        want = binding.topm_static(a, 3000, out).clone()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            binding.topm_static(a, 3000, out)
+        nodes = C.c_size_t()
+        assert hip.hipGraphGetNodes(graph.raw_cuda_graph(), None, C.byref(nodes)) == 0
+        assert nodes.value == kernels
+        for _ in range(3):
+            out.fill_(-1)
+            graph.replay()
+            assert torch.equal(out, want)
