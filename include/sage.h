@@ -84,9 +84,12 @@ int sage_set_allocator(sage_alloc_fn alloc, sage_free_fn free, void* user);
  * Create a context for an FD sketch of fp32 rows on the default stream: a zeroed buffer of 2*ell rows by D
  * columns, fill pointer 0 (Algorithm 1, "Initialize S <- 0, row counter r <- 0"; the buffer has 2*ell rows so
  * that new rows only ever land in zero rows, Liberty's form of FD).
- * out: HOST pointer receiving the handle. 2 <= ell <= 256, D >= 1. Device memory: three to five halves of L*D*4 bytes, L =
- * ell padded to 32, 64, 128 or 256, for the sketch, the rows to come and those whose shrink is deferred, plus work space.
- * Where that does not fit, two (L = 32) or three halves will do; SAGE_ERR_ALLOC if those do not fit either. The others are given
+ * out: HOST pointer receiving the handle. 2 <= ell <= 256, D >= 1. Device memory: three to six halves of L*D*4 bytes, L =
+ * ell padded to 32, 64, 128 or 256, for the sketch, the rows to come and those whose shrink is deferred, plus work space: three for
+ * L = 32, and for L = 256 where shrinks are not put together (bf16 rows up to 180,224 columns, fp32 rows); five for L = 64 and 128 up to 196,608
+ * columns, three beyond; four for L = 256 and bf16 rows from there on, six from 524,288 columns on.
+ * Where six do not fit, four will do; where those or the others do not fit, two (L = 32) or three; SAGE_ERR_ALLOC if those do not fit either.
+ * With fewer halves updates take longer (shrinks in pairs instead of up to four at a time, or each at once). Halves are given
  * back, too, when something that a later call needs does not fit beside them (not by a context whose update or basis was captured in a graph).
  */
 int sage_fd_create(sage_ctx** out, int ell, int64_t D);

@@ -24,10 +24,13 @@ struct DeferPlan {
     int m = 0, w = 0;
     bool folded = true;
 
-    int halves() const { return max > 1 ? max + 1 : 2; }
-    // Between calls: two halves remain, the current rows in the first (which is all that 64 buffer rows need).
+    static int halves_of(int max) { return max > 1 ? max + 1 : 2; }
+    int halves() const { return halves_of(max); }
+    // The next smaller plan, where memory is short: of four blocks put together two remain, otherwise every shrink writes its rows at once.
+    int fewer() const { return !beside && max > 2 ? 2 : 0; }
+    // Between calls: the current rows are in the first of the halves that remain (which is all that 64 buffer rows need).
     void give_up() {
-        max = 0;
+        max = fewer();
         cur = 0;
         next = spare = 1;
     }

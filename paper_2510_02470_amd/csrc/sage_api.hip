@@ -198,8 +198,9 @@ void dev_free(const Allocator& m, void* p) {
 int give_up_halves(sage_ctx* c);
 // ... for what a context comes to need after its creation
 bool late_alloc(sage_ctx* c, void** p, size_t bytes) {
-    if (dev_alloc(c->mem, c->st, p, bytes)) return true;
-    return give_up_halves(c) == SAGE_OK && dev_alloc(c->mem, c->st, p, bytes);
+    while (!dev_alloc(c->mem, c->st, p, bytes))
+        if (give_up_halves(c) != SAGE_OK) return false;
+    return true;
 }
 #define NO_MEMORY(c) ((c)->poisoned ? SAGE_ERR_HIP : SAGE_ERR_ALLOC)
 // (`c` must be in scope)
@@ -213,12 +214,14 @@ bool late_alloc(sage_ctx* c, void** p, size_t bytes) {
         (ptr) = nullptr;                \
     } while (0)
 
-// The halves that only rows stored ahead (64 buffer rows) and deferred shrinks take, given back where memory is short after all:
-// between calls none of them is in use but, perhaps, the current one. The ring is one allocation, so what remains takes the place of
+// Of the halves that only rows stored ahead (64 buffer rows) and deferred shrinks take, those that the next smaller plan does without
+// (DeferPlan::fewer), given back where memory is short after all: between calls none of them is in use but, perhaps, the current one. The ring is one allocation, so what remains takes the place of
 // it, by way of the host where the two do not fit side by side. SAGE_ERR_ALLOC: there is nothing to give.
 bool capturing(hipStream_t st);
 int give_up_halves(sage_ctx* c) {
-    const int keep = c->d.NP == 64 ? 1 : 2;
+    DeferPlan less = c->df;
+    less.give_up();
+    int keep = c->d.NP == 64 ? 1 : less.halves();
     if (c->halves <= keep || c->df.count > 0 || c->df.captured || capturing(c->st)) return SAGE_ERR_ALLOC;
     HIPCHK(hipStreamSynchronize(c->st));
     if (c->st2) HIPCHK(hipStreamSynchronize(c->st2));
@@ -239,8 +242,12 @@ int give_up_halves(sage_ctx* c) {
         ok = copy(host, c->nw(cur), hipMemcpyDeviceToHost);
         if (ok) {
             FREE(c->ring);
-            ok = dev_alloc(c->mem, c->st, (void**)&ring, keep * half) &&  // (no more than what has just been given back)
-                 copy(ring, host, hipMemcpyHostToDevice);
+            // (no more than what has just been given back; should some of that be gone, there may be room for fewer)
+            while (!(ok = dev_alloc(c->mem, c->st, (void**)&ring, keep * half)) && less.max > 0) {
+                less.give_up();
+                keep = less.halves();
+            }
+            ok = ok && copy(ring, host, hipMemcpyHostToDevice);
         }
         free(host);
     }
@@ -253,7 +260,7 @@ int give_up_halves(sage_ctx* c) {
     c->nw_bf16[0] = c->nw_bf16[cur];
     c->nw_half[0] = c->nw_half[cur];
     for (int i = 1; i < MAX_HALVES; ++i) c->nw_bf16[i] = c->nw_half[i] = false;
-    c->df.give_up();
+    c->df = less;
     return SAGE_OK;
 }
 
@@ -920,6 +927,7 @@ int finish_basis(sage_ctx* c) {
 // more, which are formed beside the eigensolves as long as these last; and two halves more of memory. Two / up to four at a time, calls
 // of 4 cycles: ell = 256, 942 / 945 (190,000), 1081 / 1075 (300,000), 1424 / 1372 (600,000), 3190 / 3100 (2,049,000); ell = 200, 852 / 837
 // (260,000), 1644 / 1500 (1,000,000); calls of 3 and of 5 cycles gain more (an odd one is not left alone).
+// Below 524,288 columns what four gain over two, half a per cent to two, is less than runs of one side differ by: not worth the memory.
 void defer_plan(sage_ctx* c) {
     const int64_t D = c->d.D;
     if (c->d.NP < 128) return;
@@ -964,9 +972,11 @@ int sage_set_allocator(sage_alloc_fn alloc, sage_free_fn free_, void* user) {
     return SAGE_OK;
 }
 
-// lean: the halves that storing rows ahead (64 buffer rows) and deferring shrinks take are left out, where there is no memory for them.
-static int create(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64_t max_rows, void* hip_stream, bool lean) {
+// less: how many plans smaller than the usual one, for the halves that storing rows ahead (64 buffer rows) and deferring shrinks take.
+// more: there is a smaller one still.
+static int create(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64_t max_rows, void* hip_stream, int less, bool& more) {
     *out = nullptr;
+    more = false;
     if (ell < 2 || ell > 256 || D < 1 || max_rows < 0) return SAGE_ERR_ARG;
     if (in_dtype != SAGE_F32 && in_dtype != SAGE_BF16) return SAGE_ERR_ARG;
     sage_ctx* c = new (std::nothrow) sage_ctx();
@@ -1025,9 +1035,11 @@ static int create(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64
     do {                                                                          \
         if (!dev_alloc(c->mem, c->st, (void**)&(ptr), (bytes))) return fail(SAGE_ERR_ALLOC); \
     } while (0)
-    if (!lean) defer_plan(c);
+    defer_plan(c);
+    for (int i = 0; i < less; ++i) c->df.max = c->df.fewer();
+    more = less == 0 || c->df.max > 0;
     c->half_floats = (int64_t)(hbytes / sizeof(float));
-    c->halves = lean && c->d.NP == 64 ? 1 : c->df.halves();
+    c->halves = less > 0 && c->d.NP == 64 ? 1 : c->df.halves();
     CALLOC(c->top, hbytes);
     CALLOC(c->ring, (size_t)c->halves * hbytes);
     {
@@ -1101,8 +1113,10 @@ static int create(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64
 
 int sage_fd_create_ex(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64_t max_rows, void* hip_stream) {
     if (!out) return SAGE_ERR_ARG;
-    const int rc = create(out, ell, D, in_dtype, max_rows, hip_stream, false);
-    return rc == SAGE_ERR_ALLOC ? create(out, ell, D, in_dtype, max_rows, hip_stream, true) : rc;
+    int rc = SAGE_ERR_ALLOC;
+    bool more = true;
+    for (int less = 0; rc == SAGE_ERR_ALLOC && more; ++less) rc = create(out, ell, D, in_dtype, max_rows, hip_stream, less, more);
+    return rc;
 }
 
 int sage_fd_create(sage_ctx** out, int ell, int64_t D) { return sage_fd_create_ex(out, ell, D, SAGE_F32, 0, nullptr); }

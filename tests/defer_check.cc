@@ -180,7 +180,7 @@ int main(int argc, char** argv) {
         for (int calls = 1 + rand() % 9; calls > 0; --calls) {
             s.update(rand() % 5 < 3 ? 1 + rand() % (6 * s.ell) : s.ell * (1 + rand() % 5), false);
             if (rand() % 6 == 0) s.look();
-            if (rand() % 12 == 0) {  // memory is short: two halves remain
+            if (rand() % 12 == 0) {  // memory is short: the next smaller plan
                 s.half[0] = s.half[s.p.cur];
                 for (int i = 1; i < 16; ++i) s.half[i].clear();
                 s.p.give_up();

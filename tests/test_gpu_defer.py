@@ -249,3 +249,63 @@ def test_contexts_where_memory_gets_short_later(ell, dtype, D, keep, halves, res
     assert torch.equal(out[0][2], out[1][2])
     assert abs(out[1][1].frob2 - fro) <= BAR * fro and abs(out[1][1].sum_delta - out[0][1].sum_delta) <= BAR * fro
     assert _cov_diff(out[0][0], out[1][0]) <= BAR * fro
+
+
+@pytest.mark.parametrize("refused,later,store,want", [((5,), 0, 0, [3]), ((5, 3), 0, 0, [2]), ((), 2, 2.5, [5, 3]), ((), 3, 2.5, [5, 3, 2]),
+                                                      ((), 3, 0, [5, 2])])
+def test_four_blocks_together_are_given_up_for_two_first(refused, later, store, want):
+    """A wide bf16 context has a ring of five halves. Where those do not fit at its creation (refused), or something that a later call needs
+    does not fit beside them (later: so many halves too few, and a score store of that many), it takes three and shrinks in pairs, and two
+    only if three do not fit either. Against the usual context: the same covariance (bar as above), and other bits in the sketch than
+    with any other plan."""
+    import torch
+
+    from paper_2510_02470_amd import binding
+
+    ell, D = 129, 524_289
+    L, half = binding.lib(), (D + 15) // 16 * 16 * 256 * 4
+    held, limit, rings, peak, refuse = {}, [None], [], [0], [()]
+
+    def take(size, stream, user):
+        used = sum(t.numel() for t in held.values())
+        if limit[0] is not None and used + size > limit[0] or size in [r * half for r in refuse[0]]:
+            return None
+        peak[0] = max(peak[0], used + size)
+        t = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+        p = (t.data_ptr() + 255) // 256 * 256
+        held[p] = t[:size]
+        if size in (2 * half, 3 * half, 4 * half, 5 * half):
+            rings.append(size // half)
+        return p
+
+    def give(p, user):
+        torch.cuda.synchronize()
+        held.pop(p, None)
+
+    fns = binding._ALLOC_FN(take), binding._FREE_FN(give)
+    N = 6 * ell + 50
+    G = torch.randn((N, D), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).to(torch.bfloat16)
+    out = []
+    L.sage_set_allocator(fns[0], fns[1], None)
+    try:
+        for plan, short in (((), 0), (refused, later), ((5, 3), 0)):
+            refuse[0], limit[0] = plan, None
+            del rings[:]
+            s = binding.Sage(ell, D, dtype="bf16", max_rows=max(N, int(store * half / 512)))
+            s.fd_update(G[:3])
+            if short:
+                limit[0] = peak[0] - short * half
+            s.fd_basis(64)
+            s.score(G[:300])
+            s.select(0.1)
+            s.fd_update(G[3:])
+            out.append((s.sketch().double(), s.stats(), list(rings)))
+            s.close()
+    finally:
+        binding._torch_memory(L)
+    assert not held
+    (a, sa, ra), (b, sb, rb), (c, _, rc) = out
+    assert ra == [5] and rb == want and rc == [2]
+    assert abs(sb.frob2 - sa.frob2) <= BAR * sa.frob2 and abs(sb.sum_delta - sa.sum_delta) <= BAR * sa.frob2
+    assert _cov_diff(a, b) <= BAR * sa.frob2
+    assert not torch.equal(a, b) and torch.equal(b, c) == (want[-1] == 2)
