@@ -775,8 +775,8 @@ int shrink(sage_ctx* c, const RowSrc* next, int64_t next_rows) {
     const NewBlocks one{c->ring, c->half_floats, (unsigned)c->df.cur, 1};
     c->marked = false;
     if (inline_rows) {
-        HIPCHK(launch_rebuild_gram(c->top, c->nw(c->df.cur), c->nw(c->df.cur ^ 1), c->Mt, c->gram_partial, c->gp, c->d, c->st));
-        HIPCHK(launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st));
+        RUN(K_REBUILD, launch_rebuild_gram(c->top, c->nw(c->df.cur), c->nw(c->df.cur ^ 1), c->Mt, c->gram_partial, c->gp, c->d, c->st));
+        RUN(K_REDUCE, launch_gram_reduce(c->gram_partial, c->gp, nullptr, nullptr, c->ew.C, false, c->ew.known, c->d, c->st));
         c->C_ready = true;
     } else if (write_now) {
         if (split_rb)

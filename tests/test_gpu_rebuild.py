@@ -121,6 +121,27 @@ def test_cycles_of_64_buffer_rows_against_64_bits(ell, D, dtype, decades, factor
         s.close()
 
 
+def test_every_launch_of_cycles_of_64_buffer_rows_can_fail():
+    """The hook for failing launches (sage_debug_fail_launch) reaches all that a call of four cycles makes on its stream: the insert, the first
+    Gram matrix (2), four eigensolves, three fused rebuilds with the sum of the next Gram matrix (2 each), the last rebuild."""
+    import ctypes as C
+
+    import torch
+
+    from paper_2510_02470_amd import binding as B
+
+    ell, D, launches = 16, 200, 1 + 2 + 4 + 3 * 2 + 1
+    G = torch.randn((5 * ell, D), device="cuda")
+    for nth in range(1, launches + 2):
+        s = B.Sage(ell, D)
+        s.fd_update(G[:ell])
+        s.debug_fail_launch(nth)
+        rc = s.L.sage_fd_update(s.h, C.c_void_p(G[ell:].data_ptr()), 4 * ell)
+        assert rc == (B.SAGE_ERR_HIP if nth <= launches else B.SAGE_OK), nth
+        assert s.L.sage_sync(s.h) == (B.SAGE_ERR_STATE if nth <= launches else B.SAGE_OK), nth
+        s.close()
+
+
 @pytest.mark.parametrize("ell,D", [(129, 131_072), (256, 262_147)])
 def test_wide_rows_have_the_same_gram_blocks_however_the_stream_is_cut(ell, D):
     """Rows stored ahead of their shrink and rows that are not go through the same arithmetic: with all that is not zero in 16
