@@ -142,6 +142,27 @@ def test_every_launch_of_cycles_of_64_buffer_rows_can_fail():
         s.close()
 
 
+# Narrow, one and two slabs a unit, units for some and for all waves, sketch sizes that fill one stage of 16 rows, two, and neither
+@pytest.mark.parametrize("ell,D,dtype", [(2, 1, "f32"), (15, 47, "bf16"), (16, 4099, "f32"), (17, 1040, "bf16"), (32, 65, "f32"), (31, 131_089, "bf16")])
+def test_cycles_of_64_buffer_rows_have_the_same_bits_with_and_without_the_fused_kernel(ell, D, dtype):
+    """Timed launch by launch (sage_profile_enable) the next rows are not stored ahead, and rebuild and Gram matrix are a kernel each."""
+    import torch
+
+    from paper_2510_02470_amd.binding import Sage
+
+    g = torch.Generator(device="cuda").manual_seed(D + ell)
+    G = torch.randn(6 * ell, D, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    out = []
+    for alone in (False, True):
+        s = Sage(ell, D, dtype=dtype)
+        s.profile_enable(alone)
+        s.fd_update(G)
+        out.append((s.sketch(), s.stats()))
+        s.close()
+    assert torch.equal(out[0][0], out[1][0])
+    assert (out[0][1].sum_delta, out[0][1].frob2) == (out[1][1].sum_delta, out[1][1].frob2)
+
+
 @pytest.mark.parametrize("ell,D", [(129, 131_072), (256, 262_147)])
 def test_wide_rows_have_the_same_gram_blocks_however_the_stream_is_cut(ell, D):
     """Rows stored ahead of their shrink and rows that are not go through the same arithmetic: with all that is not zero in 16
