@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(GramTops tops, const float
         src[it] = row_in_use(hr, rows) * 4 + p;
         used[it] = hr < rows && (isnew[it] || !FRESH);
     }
-    constexpr int IT0 = FRESH && P > 1 ? P / 2 : 0;  // the first with new rows, where the others are not needed
+    constexpr int IT0 = FRESH ? P / 2 : 0;  // the first with new rows, where the others are not needed
     const f32x4* Tv = reinterpret_cast<const f32x4*>(top);
     const f32x4* Nv = reinterpret_cast<const f32x4*>(nw);
     // Slabs are requested two stages before they are used: one set of registers goes to LDS while the other fills (with P = 8
@@ -1122,7 +1122,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramSrc a, GramSrc b, 
 // over the columns takes; rows that are loaded come in the same order. No LDS but for the sums at the end, the coefficients stay in
 // registers, and a wave goes through its units with the next one's rows on their way. The bits of the Gram matrix are the same
 // either way. HS: stages of 16 rows of a half in use.
-// Bound by memory where rows are long: with the rebuild 1.05 GB at 2,049,000 columns in 215 us, where a kernel for each took 130 and (all
+// Bound by memory where rows are long: with the rebuild 1.05 GB at 2,049,000 columns in 215 to 235 us by the card, where a kernel for each took 130 and (all
 // four blocks, through LDS) 190; by the launch where they are short (512 columns: 6.2 us, were 5.2 and 4.9). In between the two are
 // even (51,300: a unit for each wave, 12.8 us for 7.5 and 6.3). An update of 17 blocks of 32 rows: 9.5 -> 6.0 ms at 2,049,000, 3.31 -> 2.36 at
 // 524,288; a job of 64 blocks of 512 columns: 5.39 -> 5.24.
@@ -1263,17 +1263,20 @@ GramPlan gram_plan(const Dims& d, int num_cu, int mode, bool skip_top, int wg_pe
     // gram_new8_kernel (the whole triangle in one work-group) when the launch has the chip to itself
     if (mode == 2 && P == 8 && !side) p.wg_per_group = 1;
     const int cus = side && num_cu > 32 ? num_cu / 8 * 7 : num_cu;
-    int g = (wg_per_cu * cus / p.wg_per_group) / 8 * 8;
-    if (g < 8) g = 8;
-    // At least 4 slabs per group so that small problems do not drown in partial tiles; 2 where there are so few slabs that
-    // the chain of loads of a group is what counts.
-    const int64_t least = d.S <= 256 ? 2 : 4;
-    int64_t gmax = ((d.S + least - 1) / least + 7) / 8 * 8;
-    if (gmax < 8) gmax = 8;
-    if (g > gmax) g = (int)gmax;
+    int g;
     if (P == 1) {  // gram64_kernel: a wave takes units of two slabs
         const int64_t wgs = ((d.S + 1) / 2 + 3) / 4;
         g = wgs < (int64_t)wg_per_cu * num_cu ? (int)wgs : wg_per_cu * num_cu;
+    } else {
+        g = (wg_per_cu * cus / p.wg_per_group) / 8 * 8;
+        if (g < 8) g = 8;
+        // At least 4 slabs per group so that small problems do not drown in partial tiles; 2 where there are few slabs: as fast (us a
+        // cycle, 2 / 4: ell = 64, 159.4 / 160.4 at 512 columns, 162.6 / 161.2 at 4096; 100, 256.0 / 254.9 and 262.6 / 260.5; 128, 304.6 / 303.1
+        // and 309.9 / 308.6; 256, 682.6 / 681.0 and 684.8 / 683.7; runs of a side differ by 1%) and half as long sums in fp32.
+        const int64_t least = d.S <= 256 ? 2 : 4;
+        int64_t gmax = ((d.S + least - 1) / least + 7) / 8 * 8;
+        if (gmax < 8) gmax = 8;
+        if (g > gmax) g = (int)gmax;
     }
     p.groups = g;
     p.slabs_per_group = (d.S + g - 1) / g;

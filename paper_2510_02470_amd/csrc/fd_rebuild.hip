@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256, 2) void rebuild_split_kernel(const float* top,
     const float* tcol = (live ? top : blocks.nw.at(0)) + coff;
     const int64_t away = blocks.nw.ring + coff - tcol;  // from there to the ring
     const int ntop = LP >> 4;
-    const int nstage = ntop + (nfill > 0 ? blocks.per * blocks.nw.count : 0);  // no stage without rows in use (a basis right after a shrink: half)
+    const int nstage = ntop + (nfill > 0 ? blocks.per * blocks.nw.count : 0);  // no stage without rows in use
     constexpr bool HALF = NPT == 512;
     const int64_t hoff = HALF ? ((dc / 8) * LP + h) * 4 + (dc % 8) / 2 : 0;  // in words, from the start of a block's pieces
     const unsigned pick = HALF && !(dc & 1) ? 0x05040100u : 0x07060302u;  // lower or upper halves of two words

@@ -558,7 +558,9 @@ int gram_whole_split(sage_ctx* c, hipEvent_t mark = nullptr) {
     return SAGE_OK;
 }
 
-// After a shrink the Gram matrix of the top rows is known (diagonal lambda_j - delta, recorded by the shrink).
+// After a shrink the Gram matrix of the top rows is known (diagonal lambda_j - delta, recorded by the shrink). At 64 buffer rows no plan
+// leaves that block out (gram64_kernel forms it with the others), and there even a buffer that was just shrunk is decomposed anew for a basis: a
+// solve of some 65 us, once a stream.
 bool top_known(const sage_ctx* c) { return c->top_shrunk && c->gp_skip.t0 > 0; }
 
 // Gram + eigensolve of the buffer as it stands, and the coefficients of a basis. A block that is known is not recomputed.
@@ -1017,7 +1019,8 @@ static int create(sage_ctx** out, int ell, int64_t D, sage_dtype in_dtype, int64
         const int side = c->num_cu > 32 ? c->num_cu / 8 * 7 : 8;
         c->gp_new_split = gram_plan_split(c->gp_new2, c->d, side);
         // The new x top kernels fill a CU, and the kernels after the reduction that do not fit beside them (divide and conquer's
-        // blocks: 77 KB of LDS) come to all XCDs: one CU of each is left to them (those blocks of 512 rows 290 -> 60 us). As many
+        // blocks: 77 KB of LDS) come to all XCDs: one CU of each is left to them (those blocks of 512 rows 290 -> 60 us; a launch for
+        // two or three blocks of a wide bf16 stream has as many again for each and leaves none: 300 us). As many
         // work-groups as the whole chip holds took two rounds of the 224 CUs.
         c->gp_cross_side = gram_plan_split(c->gp_cross, c->d, side > 56 ? side - 7 : side);
     }

@@ -49,8 +49,8 @@ hipError_t launch_cosine(const float* zhat, int64_t N, int k, const double* ssum
 //   else: two histograms, the third with a table for each block of keys, emit. Every work-group of the next kernel
 //         reads the histogram and finds the digit itself (a scan over the bins by 1024 threads), so there are no kernels
 //         between them. Each run clears a histogram after its last reader, so that work space that is kept is clear for the
-//         next run, and only new work space takes a launch for that (a million keys in kept work space: 20.0 us with it, 18.1
-//         without). The tables answer, whatever the last digit turns out to be, how many keys of a block are above it and
+//         next run, which may then do without the launch for that (eager calls of sage_topm_static: a million keys 18.1 us, 20.0
+//         with it). All other calls begin with it. The tables answer, whatever the last digit turns out to be, how many keys of a block are above it and
 //         how many equal it, which took a kernel of its own between the last histogram and emit (a million keys: 24.2 us
 //         with it, 22.4 without, 19.9 with fewer work-groups for the histograms, see launch_topm).
 // The first digit has 12 bits because scores crowd into a few binary orders of magnitude: with 8 bits most lanes of a wave
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(TOPM_T) void topm_emit_kernel(const float* __restri
     emit_keys<TOPM_T, C>(key, base, (state[2] << 10) | digit, rest, sg, se, cnt, tot, out_idx);
 }
 
-// One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of four launches wins.
+// One work-group up to 32 keys a thread, as many as fit its registers; beyond, the width of four or five launches wins.
 constexpr int64_t TOPM_ONE = 32 * TOPM_T;
 
 // Small copies for a caller that waits: one work-group, then the signal.
